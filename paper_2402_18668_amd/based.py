@@ -1,13 +1,16 @@
-"""ctypes binding of the C-ABI HIP library (``include/based.h``): argument marshalling only.
+"""Binding of the C-ABI HIP library (``include/based.h``): argument marshalling only.
 
 Every function takes torch CUDA tensors (used purely as device memory), checks their shapes and
 dtypes on the host, and forwards raw pointers plus the current HIP stream to the library.  No
 step of the method runs in Python or in torch; if the built library is missing the import
-fails loudly.
+fails loudly.  The calls of a model's forward pass and decode loop check and marshal their arguments
+in native code (``csrc/bind.cpp``, which calls the library loaded here); the rest go through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -15,6 +18,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # BASED_HIP_LIB lets a developer point the binding at another build of the same library
 LIB_PATH = os.environ.get("BASED_HIP_LIB") or os.path.join(_HERE, "lib", "libbased_hip.so")
+BIND_PATH = os.path.join(_HERE, "lib", "_bind.so")
 
 F32, BF16 = 0, 1
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_LAUNCH, ERR_TOO_LARGE = 0, 1, 2, 3, 4
@@ -137,6 +141,24 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+def _raise(status: int, what: str):
+    raise BasedError(status, what)
+
+
+def _load_bind():
+    if not os.path.exists(BIND_PATH):
+        raise ImportError(
+            f"{BIND_PATH} is not built; run `python -m paper_2402_18668_amd.build` (there is no fallback)")
+    loader = importlib.machinery.ExtensionFileLoader("_bind", BIND_PATH)
+    mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_bind", loader))
+    loader.exec_module(mod)
+    mod.init({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTS}, _raise)
+    return mod
+
+
+_bind = _load_bind()
+
+
 def strerror(status: int) -> str:
     return lib.based_strerror(int(status)).decode()
 
@@ -255,32 +277,7 @@ def prefill(q, k, v, y=None, state=None, has_init=False, workspace=None, packed=
     """based_prefill, based_prefill_packed (``packed=True``: ``state`` is a packed-state buffer) or
     based_prefill_numerator (``numerator_only=True``: y is the numerator of Eq. 2, not divided).
     q, k ``[B,H,N,d']``; v ``[B,H,N,d_v]``; returns y (allocated if not given)."""
-    _dev(q, k, v, y, state, workspace)
-    B, H, N, dp = q.shape
-    dv = v.shape[-1]
-    if k.shape != q.shape or tuple(v.shape[:3]) != (B, H, N) or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v shapes / dtypes disagree")
-    code = _dtype_code(q)
-    if y is None:
-        y = torch.empty_like(v)
-    elif y.shape != v.shape or y.dtype != v.dtype:
-        raise ValueError("y must match v")
-    sbytes = packed_state_bytes(B, H, dp, dv) if packed else state_bytes(B, H, dp, dv)
-    if state is not None and (state.dtype != torch.float32 or state.numel() * 4 < sbytes):
-        raise ValueError("state buffer too small or not fp32")
-    need = prefill_workspace_bytes(B, H, N, dp, dv, code)
-    if need and workspace is None:
-        workspace = alloc_prefill_workspace(B, H, N, dp, dv, code, q.device)
-    if need and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
-    if packed and numerator_only:
-        raise ValueError("there is no packed numerator-only prefill")
-    fn, what = (lib.based_prefill_packed, "based_prefill_packed") if packed else (lib.based_prefill, "based_prefill")
-    if numerator_only:
-        fn, what = lib.based_prefill_numerator, "based_prefill_numerator"
-    _check(fn(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(state), int(bool(has_init)),
-              _ptr(workspace), B, H, N, dp, dv, code, _stream()), what)
-    return y
+    return _bind.prefill(q, k, v, y, state, has_init, workspace, packed, numerator_only)
 
 
 def prefill_decay(q, k, v, gamma, y=None, state=None, has_init=False, gate=None):
@@ -361,23 +358,7 @@ def decode_step(q, k, v, state, y=None, packed=False, numerator_only=False):
     """based_decode_step (``packed=True``: based_decode_step_packed on a packed state;
     ``numerator_only=True``: based_decode_step_numerator, y = phi(q) S undivided).
     q, k ``[B,H,d']``; v ``[B,H,d_v]``; state updated in place."""
-    _dev(q, k, v, y, state)
-    B, H, dp = q.shape
-    dv = v.shape[-1]
-    if k.shape != q.shape or tuple(v.shape[:2]) != (B, H) or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v shapes / dtypes disagree")
-    need = packed_state_bytes(B, H, dp, dv) if packed else state_bytes(B, H, dp, dv)
-    if state.dtype != torch.float32 or state.numel() * 4 < need:
-        raise ValueError("state buffer too small or not fp32")
-    if y is None:
-        y = torch.empty_like(v)
-    if packed and numerator_only:
-        raise ValueError("there is no packed numerator-only decode step")
-    fn, what = (lib.based_decode_step_packed, "based_decode_step_packed") if packed else (lib.based_decode_step, "based_decode_step")
-    if numerator_only:
-        fn, what = lib.based_decode_step_numerator, "based_decode_step_numerator"
-    _check(fn(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(state), B, H, dp, dv, _dtype_code(q), _stream()), what)
-    return y
+    return _bind.decode_step(q, k, v, state, y, packed, numerator_only)
 
 
 def swa_ring_bytes(B, H, w, d_h, dtype_code) -> int:
@@ -403,140 +384,41 @@ def rotary_table(N: int, d_h: int, pos0: int = 0, base: float = 10000.0, device=
 def swa_prefill(q, k, v, w: int, scale: float, y=None, ring=None, rotary=None):
     """based_swa_prefill, or based_swa_prefill_rotary (``rotary``: a table from ``rotary_table`` whose row t
     belongs to token t).  q, k, v ``[B,H,N,d_h]``."""
-    _dev(q, k, v, y, ring)
-    B, H, N, dh = q.shape
-    if k.shape != q.shape or v.shape != q.shape or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v shapes / dtypes disagree")
-    if y is None:
-        y = torch.empty_like(v)
-    if ring is not None and (ring.dtype != q.dtype or ring.numel() != B * H * 2 * w * dh):
-        raise ValueError("ring must be [B,H,2,w,d_h] of the input dtype")
-    if rotary is not None:
-        _dev(rotary)
-        if rotary.dtype != torch.float32 or tuple(rotary.shape) != (N, dh // 2, 2) or not rotary.is_contiguous():
-            raise ValueError("rotary table must be contiguous fp32 [N, d_h / 2, 2]")
-        _check(lib.based_swa_prefill_rotary(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(ring), _ptr(rotary), B, H, N,
-                                            dh, int(w), float(scale), _dtype_code(q), _stream()),
-               "based_swa_prefill_rotary")
-        return y
-    _check(lib.based_swa_prefill(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(ring), B, H, N, dh, int(w),
-                                 float(scale), _dtype_code(q), _stream()), "based_swa_prefill")
-    return y
-
-
-def _check_pos(pos, B):
-    if pos.dtype != torch.int32 or pos.numel() != B or not pos.is_cuda or not pos.is_contiguous():
-        raise ValueError("per-sequence positions must be a contiguous int32 device tensor of B elements")
+    return _bind.swa_prefill(q, k, v, w, scale, y, ring, rotary)
 
 
 def linear(x, W, y=None):
     """based_linear: ``y = x W^T``; x ``[..., K]``, W ``[N, K]`` (bf16); returns y ``[..., N]``."""
-    _dev(x, W, y)
-    K = x.shape[-1]
-    N = W.shape[0]
-    M = x.numel() // K
-    if W.shape != (N, K) or W.dtype != x.dtype or not x.is_contiguous() or not W.is_contiguous():
-        raise ValueError("x [..., K] and W [N, K] must be contiguous and of one dtype")
-    if y is None:
-        y = torch.empty((*x.shape[:-1], N), dtype=x.dtype, device=x.device)
-    elif y.numel() != M * N or y.dtype != x.dtype or not y.is_contiguous():
-        raise ValueError("y must be [..., N], contiguous, of x's dtype")
-    _check(lib.based_linear(_ptr(x), _ptr(W), _ptr(y), M, K, N, _dtype_code(x), _stream()), "based_linear")
-    return y
+    return _bind.linear(x, W, y)
 
 
 def project_qkv(x, W, H: int, d_feat: int, d_v: int):
     """based_project_qkv: x ``[B,N,d_model]``, W ``[H (2 d' + d_v), d_model]`` (rows of Wq, Wk, Wv) ->
     head-major q, k ``[B,H,N,d']`` and v ``[B,H,N,d_v]``."""
-    _dev(x, W)
-    B, N, dm = x.shape
-    if tuple(W.shape) != (H * (2 * d_feat + d_v), dm) or W.dtype != x.dtype or not x.is_contiguous() \
-            or not W.is_contiguous():
-        raise ValueError("x [B, N, d_model] and W [H (2 d' + d_v), d_model] must be contiguous and of one dtype")
-    q = torch.empty((B, H, N, d_feat), dtype=x.dtype, device=x.device)
-    k = torch.empty_like(q)
-    v = torch.empty((B, H, N, d_v), dtype=x.dtype, device=x.device)
-    _check(lib.based_project_qkv(_ptr(x), _ptr(W), _ptr(q), _ptr(k), _ptr(v), B, N, dm, H, d_feat, d_v,
-                                 _dtype_code(x), _stream()), "based_project_qkv")
-    return q, k, v
+    return _bind.project_qkv(x, W, H, d_feat, d_v)
 
 
 def project_out(y_heads, W):
     """based_project_out: head-major ``[B,H,N,d_v]`` times W ``[d_model, H d_v]`` -> ``[B,N,d_model]``."""
-    _dev(y_heads, W)
-    B, H, N, dv = y_heads.shape
-    dm = W.shape[0]
-    if tuple(W.shape) != (dm, H * dv) or W.dtype != y_heads.dtype or not y_heads.is_contiguous() \
-            or not W.is_contiguous():
-        raise ValueError("y [B, H, N, d_v] and W [d_model, H d_v] must be contiguous and of one dtype")
-    out = torch.empty((B, N, dm), dtype=y_heads.dtype, device=y_heads.device)
-    _check(lib.based_project_out(_ptr(y_heads), _ptr(W), _ptr(out), B, N, H, dv, dm, _dtype_code(y_heads),
-                                 _stream()), "based_project_out")
-    return out
+    return _bind.project_out(y_heads, W)
 
 
 def short_conv_gate(a, c, h, b1, b2, c_prev=None, c_last=None, out=None):
     """based_short_conv_gate: ``(a + b1) * silu(causal 3-tap conv of c + b2)``; a, c ``[B,N,Dc]``, h ``[3,Dc]``
     and b1, b2 ``[Dc]`` fp32; c_prev / c_last ``[B,2,Dc]`` (rows before / at the end of the sequence)."""
-    _dev(a, c, h, b1, b2, c_prev, c_last, out)
-    B, N, Dc = a.shape
-    if c.shape != a.shape or c.dtype != a.dtype or not a.is_contiguous() or not c.is_contiguous():
-        raise ValueError("a, c must be contiguous [B, N, Dc] of one dtype")
-    for t_, shp in ((h, (3, Dc)), (b1, (Dc,)), (b2, (Dc,))):
-        if tuple(t_.shape) != shp or t_.dtype != torch.float32 or not t_.is_contiguous():
-            raise ValueError("h [3, Dc], b1, b2 [Dc] must be contiguous fp32")
-    for t_ in (c_prev, c_last):
-        if t_ is not None and (tuple(t_.shape) != (B, 2, Dc) or t_.dtype != a.dtype or not t_.is_contiguous()):
-            raise ValueError("c_prev / c_last must be contiguous [B, 2, Dc] of a's dtype")
-    if out is None:
-        out = torch.empty_like(a)
-    elif out.shape != a.shape or out.dtype != a.dtype or not out.is_contiguous():
-        raise ValueError("out must match a")
-    _check(lib.based_short_conv_gate(_ptr(a), _ptr(c), _ptr(h), _ptr(b1), _ptr(b2), _ptr(c_prev), _ptr(out),
-                                     _ptr(c_last), B, N, Dc, _dtype_code(a), _stream()), "based_short_conv_gate")
-    return out
+    return _bind.short_conv_gate(a, c, h, b1, b2, c_prev, c_last, out)
 
 
 def positions_advance(pos):
     """based_positions_advance: pos[b] += 1 where pos[b] >= 1, on the current stream."""
-    _check_pos(pos, pos.numel())
-    _check(lib.based_positions_advance(_ptr(pos), pos.numel(), _stream()), "based_positions_advance")
+    return _bind.positions_advance(pos)
 
 
 def swa_decode(q, k, v, ring, pos, w: int, scale: float, y=None, rotary=None):
     """based_swa_decode (``pos`` an int) or based_swa_decode_ragged (``pos`` an int32 device tensor
     ``[B]``); with ``rotary`` (a table from position 0) based_swa_decode_rotary for either kind of ``pos``.
     q, k, v ``[B,H,d_h]``; ring updated in place."""
-    _dev(q, k, v, y, ring)
-    B, H, dh = q.shape
-    if k.shape != q.shape or v.shape != q.shape or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v shapes / dtypes disagree")
-    if ring.dtype != q.dtype or ring.numel() != B * H * 2 * w * dh:
-        raise ValueError("ring must be [B,H,2,w,d_h] of the input dtype")
-    if y is None:
-        y = torch.empty_like(v)
-    if rotary is not None:
-        _dev(rotary)
-        if rotary.dtype != torch.float32 or rotary.dim() != 3 or tuple(rotary.shape[1:]) != (dh // 2, 2) \
-                or not rotary.is_contiguous():
-            raise ValueError("rotary table must be contiguous fp32 [rows, d_h / 2, 2]")
-        ragged = isinstance(pos, torch.Tensor)
-        if ragged:
-            _check_pos(pos, B)
-        _check(lib.based_swa_decode_rotary(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(ring), _ptr(rotary),
-                                           int(rotary.shape[0]), 0 if ragged else int(pos),
-                                           _ptr(pos) if ragged else None, B, H, dh, int(w), float(scale),
-                                           _dtype_code(q), _stream()), "based_swa_decode_rotary")
-        return y
-    if isinstance(pos, torch.Tensor):   # per-sequence positions in device memory
-        _check_pos(pos, B)
-        _check(lib.based_swa_decode_ragged(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(ring), _ptr(pos), B, H, dh,
-                                           int(w), float(scale), _dtype_code(q), _stream()),
-               "based_swa_decode_ragged")
-        return y
-    _check(lib.based_swa_decode(_ptr(q), _ptr(k), _ptr(v), _ptr(y), _ptr(ring), int(pos), B, H, dh,
-                                int(w), float(scale), _dtype_code(q), _stream()), "based_swa_decode")
-    return y
+    return _bind.swa_decode(q, k, v, ring, pos, w, scale, y, rotary)
 
 
 def decode_fused(q, k, v, state, swa_q, swa_k, swa_v, ring, pos, w: int, scale: float,
@@ -544,50 +426,4 @@ def decode_fused(q, k, v, state, swa_q, swa_k, swa_v, ring, pos, w: int, scale: 
     """based_decode_fused (``packed=True``: based_decode_fused_packed; ``pos`` a device tensor:
     based_decode_fused_ragged; ``rotary``: a table from position 0, based_decode_fused_rotary): both decode
     steps in one launch; returns ``(y_lin, y_swa)``."""
-    _dev(q, k, v, state, swa_q, swa_k, swa_v, ring, y_lin, y_swa)
-    B, H, dp = q.shape
-    dv = v.shape[-1]
-    dh = swa_q.shape[-1]
-    if k.shape != q.shape or tuple(v.shape[:2]) != (B, H) or tuple(swa_q.shape[:2]) != (B, H):
-        raise ValueError("shapes disagree")
-    if swa_k.shape != swa_q.shape or swa_v.shape != swa_q.shape:
-        raise ValueError("window attention shapes disagree")
-    for t in (k, v, swa_q, swa_k, swa_v, ring):
-        if t.dtype != q.dtype:
-            raise ValueError("dtypes disagree")
-    need = packed_state_bytes(B, H, dp, dv) if packed else state_bytes(B, H, dp, dv)
-    if state.dtype != torch.float32 or state.numel() * 4 < need:
-        raise ValueError("state buffer too small or not fp32")
-    if ring.numel() != B * H * 2 * w * dh:
-        raise ValueError("ring must be [B,H,2,w,d_h]")
-    if y_lin is None:
-        y_lin = torch.empty_like(v)
-    if y_swa is None:
-        y_swa = torch.empty_like(swa_v)
-    if rotary is not None:
-        _dev(rotary)
-        if rotary.dtype != torch.float32 or rotary.dim() != 3 or tuple(rotary.shape[1:]) != (dh // 2, 2) \
-                or not rotary.is_contiguous():
-            raise ValueError("rotary table must be contiguous fp32 [rows, d_h / 2, 2]")
-        ragged = isinstance(pos, torch.Tensor)
-        if ragged:
-            _check_pos(pos, B)
-        _check(lib.based_decode_fused_rotary(_ptr(q), _ptr(k), _ptr(v), _ptr(y_lin), _ptr(state), int(bool(packed)),
-                                             dp, dv, _ptr(swa_q), _ptr(swa_k), _ptr(swa_v), _ptr(y_swa), _ptr(ring),
-                                             _ptr(rotary), int(rotary.shape[0]), 0 if ragged else int(pos),
-                                             _ptr(pos) if ragged else None, dh, int(w), float(scale), B, H,
-                                             _dtype_code(q), _stream()), "based_decode_fused_rotary")
-        return y_lin, y_swa
-    if isinstance(pos, torch.Tensor):   # per-sequence positions in device memory
-        _check_pos(pos, B)
-        _check(lib.based_decode_fused_ragged(_ptr(q), _ptr(k), _ptr(v), _ptr(y_lin), _ptr(state), int(bool(packed)),
-                                             dp, dv, _ptr(swa_q), _ptr(swa_k), _ptr(swa_v), _ptr(y_swa), _ptr(ring),
-                                             _ptr(pos), dh, int(w), float(scale), B, H, _dtype_code(q), _stream()),
-               "based_decode_fused_ragged")
-        return y_lin, y_swa
-    fn = lib.based_decode_fused_packed if packed else lib.based_decode_fused
-    _check(fn(_ptr(q), _ptr(k), _ptr(v), _ptr(y_lin), _ptr(state), dp, dv, _ptr(swa_q), _ptr(swa_k),
-              _ptr(swa_v), _ptr(y_swa), _ptr(ring), int(pos), dh, int(w), float(scale), B, H,
-              _dtype_code(q), _stream()),
-           "based_decode_fused_packed" if packed else "based_decode_fused")
-    return y_lin, y_swa
+    return _bind.decode_fused(q, k, v, state, swa_q, swa_k, swa_v, ring, pos, w, scale, y_lin, y_swa, packed, rotary)

@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libbased_hip.so")
+BIND = os.path.join(LIBDIR, "_bind.so")
 
 SOURCES = [
     "api.hip",
@@ -33,13 +34,27 @@ FLAGS = [
 ]
 
 
+def bind_command() -> list:
+    """The host-only binding module: plain C++ against the Python and torch headers."""
+    import sysconfig
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", os.path.join(CSRC, "bind.cpp"), "-o", BIND]
+    cmd += ["-I" + d for d in [*include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]]
+    cmd += ["-L" + d for d in library_paths()]
+    return cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
-    """Compile every translation unit (in parallel) and link the shared library."""
+    """Compile every translation unit (in parallel), link the shared library and build the binding module."""
     os.makedirs(LIBDIR, exist_ok=True)
     objdir = os.path.join(LIBDIR, "obj")
     os.makedirs(objdir, exist_ok=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    procs = []
+    cmd = bind_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs = [("bind.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     objs = []
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
@@ -63,7 +78,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         elif verbose and out.strip():
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.check_call(cmd)
     return LIB
