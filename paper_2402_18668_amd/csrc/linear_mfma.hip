@@ -4,24 +4,23 @@
 // H d_v for v, and of the H d_v mixer output back to d_model; all without bias).
 //
 // x [M][K] and W [N][K] are both contiguous along K, so both MFMA operands are 16 contiguous bytes
-// of a row per lane.  One workgroup of four waves computes a 256 x 128 tile of y (tokens x
-// features); each wave a 128 x 64 quarter as 4 x 2 MFMA tiles of 32 x 32 (computed transposed: rows
-// = output features, columns = tokens, so that a lane holds runs of 4 consecutive features of one
-// token): 6 operand reads of 16 bytes per lane feed 8 MFMAs, which keeps the LDS pipe below the
-// matrix pipe.  The K dimension is walked in steps of 64: the rows of the next step are fetched into
-// registers while the current one is multiplied and written to LDS between two barriers.  The
-// finished tile is turned through LDS and leaves as 128-byte row segments.
+// of a row per lane.  Products are computed transposed (rows of the matrix instruction = output features,
+// columns = tokens), so that a lane holds runs of 4 consecutive features of one token.
+//
+// Two kernels, chosen by M (pick_variant):
+//   linear_tile_kernel   a BM x BN tile of y per workgroup, x and W staged through LDS
+//   linear_rows_kernel   a handful of tokens (decode): W streamed once from memory straight into registers
 //
 // Layouts.  The mixers read and write head-major tensors [B][H][N][d], the projections' natural output is
 // token-major [B N][H d].  Rather than a transposing pass in between (one more read and write of q, k,
-// v and of the mixer output through HBM), the kernel addresses head-major tensors directly:
+// v and of the mixer output through HBM), the kernels address head-major tensors directly:
 //   SPLIT_OUT  the output features are three groups of heads (q, k, v: H d' + H d' + H d_v rows of W in
 //              that order) and go to three head-major tensors; x is read once for all three;
 //   HEADS_IN   the A operand is a head-major tensor (the mixer output): a K step of 64 lies inside one head.
-//
-// Workgroups that share rows of x run back to back on the same XCD (its L2 then serves x once per
-// row of tiles): block b belongs to XCD b % 8, which walks its own rows of tiles one after another.
 #include "common.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace based {
 
@@ -34,25 +33,18 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = 256;        // tokens per workgroup tile
-constexpr int BN = 128;        // output features per workgroup tile
-constexpr int BK = 64;         // K step
-constexpr int NT = 256;
-constexpr int LD = BK + 8;     // bf16 elements per staged row (144-byte stride: 16-byte reads of 8 rows hit 32 banks)
-constexpr int OUT_LD = 64 + 8; // bf16 elements per row of a wave's output staging tile
 constexpr int kXcds = 8;
-
-constexpr int TI = BM / 2 / 32;   // MFMA tiles along the tokens per wave
-struct Lds {
-    uint16_t a[BM][LD];        // rows of x
-    uint16_t b[BN][LD];        // rows of W
-};
-static_assert(sizeof(Lds) <= 80 * 1024, "two workgroups per CU");
-static_assert(4 * 64 * OUT_LD * 2 <= (int)sizeof(Lds), "the output staging reuses the operand buffers");
+constexpr int KQ = 64;         // K is a multiple of this
+constexpr int NQ = 128;        // N is a multiple of this
 
 __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+}
+__device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
                                                    0, 0);
 }
 
@@ -96,350 +88,404 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
     return p;
 }
 
-// K % 64 == 0, N % 128 == 0 (checked by the launcher); any M >= 1.
-template <bool SPLIT_OUT, bool HEADS_IN>
-__global__ __launch_bounds__(NT, 2) void linear_kernel(const uint16_t *__restrict__ x,
-                                                       const uint16_t *__restrict__ W,
-                                                       uint16_t *__restrict__ y, int M, int K, int N,
-                                                       int tiles_m, int tiles_n, HeadLayout hl)
+// ---- tiles -------------------------------------------------------------------------------------------------
+// WM x WN waves compute a BM x BN tile (tokens x features), each a (BM / WM) x (BN / WN) part of it in MFMA tiles of
+// 32 x 32.
+//
+// Staging.  The rows go from memory to LDS directly (the 16-byte LDS DMA: no registers, no LDS write instructions), into
+// a ring of ST stages of BK columns.  One instruction of a wave moves 1 KB: 64 lanes x 16 bytes land side by
+// side in LDS, i.e. whole rows of BK elements without padding, so the bank spread comes from a permutation
+// instead: 16-byte piece c of row r sits at place c ^ f(r), which the lanes produce for free by choosing what
+// they fetch; the 8 rows that a group of lanes reads at a time then cover all banks.
+//
+// Pipeline.  One barrier per step, taken before the LAST 16-deep slab of a step: by then every operand of the step
+// is in registers, so behind the barrier this step's stage is free for the DMA of step kt + ST, and
+// the first operands of the next step are read under the matrix instructions of the last slab.  The DMA
+// pieces are dealt out between the matrix instructions; the wait before the barrier counts them (s_waitcnt
+// vmcnt), so ST - 1 stages stay in flight.  Steps past the end re-read the last one, which keeps the count
+// constant.  (The DMA is inline asm: through the builtin the compiler makes every LDS read wait for all of it.)
+//
+// The operand reads of the next slab and the DMA pieces sit one by one between the matrix instructions: in bursts they
+// hold up the wave, and with it the matrix pipe, until the LDS and the memory pipeline have taken them.  16x16x32 matrix
+// instructions, not 32x32x16: they move half the accumulator registers per product, and under this load the clock is
+// set by power (q / k / v projection of the 1.3B-shaped layer, 32768 x 1792 x 2560, on one GPU: 271 against 252 us; both run
+// at 1.85 GHz).  The same shape in steps: registers-staged 256 x 256 tiles of 32x32x16 284 us, DMA 276, reads and DMA
+// between the matrix instructions 268, 16x16x32 252, the DMA of a stage out by 6/8 of a step 240 us = 1255 TFLOP/s.
+template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_, int MT_ = 16, int SPREAD_ = 8> struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_, MT = MT_, SPREAD = SPREAD_;
+    static constexpr int NW = WM * WN, NT = 64 * NW;
+    static constexpr int TI = BM / WM / MT, TJ = BN / WN / MT;   // MFMA tiles of a wave: tokens, features
+    static constexpr int SD = MT == 32 ? 16 : 32;                // depth of a slab: 32x32x16 or 16x16x32
+    using Acc = std::conditional_t<MT == 32, f32x16, f32x4>;
+    static constexpr int CPR = BK / 8;                           // 16-byte pieces per staged row
+    static constexpr int RPI = 64 / CPR;                         // rows one DMA instruction moves
+    static constexpr int AP = BM / RPI / NW, BP = BN / RPI / NW, P = AP + BP;   // instructions of a wave per step
+    static constexpr int KS = BK / SD;                           // slabs per step
+    static constexpr int STAGE = (BM + BN) * BK * 2;             // bytes
+    static constexpr int OUT_LD = BN / WN + 8;                   // bf16 elements per row of a wave's output staging
+    static constexpr int OUT = NW * 32 * OUT_LD * 2;
+    static constexpr int LDS = ST * STAGE > OUT ? ST * STAGE : OUT;
+    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && KS % 2 == 0, "");
+};
+
+// f(0), f(1), .. f(N - 1) with constant arguments (the loops over accumulators must unroll, however long)
+template <typename F, int... I> __device__ __forceinline__ void constexpr_for_seq(F &&f, std::integer_sequence<int, I...>)
 {
-    __shared__ __align__(16) Lds lds;
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void constexpr_for(F &&f)
+{
+    constexpr_for_seq(f, std::make_integer_sequence<int, N>{});
+}
 
-    // block -> tile: XCD (b % 8) owns the rows of tiles xcd, xcd + 8, ... and walks each along N
-    const int b = blockIdx.x;
-    const int xcd = b % kXcds, local = b / kXcds;
-    const int tm = (local / tiles_n) * kXcds + xcd, tn = local % tiles_n;
-    if (tm >= tiles_m) return;   // uniform: the grid is padded to a multiple of 8 rows of tiles
+// 16 bytes per lane from base (uniform) + off bytes (per lane) to LDS address `to` (uniform) + 16 lane
+__device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t to)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(off), "s"(base) : "memory", "m0");
+}
+// this wave's DMA is complete but for the N newest instructions, its LDS reads are complete; then the barrier
+template <int N> __device__ __forceinline__ void dma_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
 
+// The tile whose first token is row0 and first feature col0.  K % 64 == 0, N % BN == 0 (checked by the launcher).
+template <typename T, bool SPLIT_OUT, bool HEADS_IN>
+__device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__restrict__ x, const uint16_t *__restrict__ W,
+                                          uint16_t *__restrict__ y, int M, int K, int N, int row0, int col0, const HeadLayout &hl)
+{
+    constexpr int MT = T::MT, TI = T::TI, TJ = T::TJ, BK = T::BK, KS = T::KS, P = T::P, ST = T::ST, CPR = T::CPR;
     const int tid = threadIdx.x;
-    const int w = tid >> 6, lane = tid & 63, g = lane >> 5, n = lane & 31;
-    const int wm = w >> 1, wn = w & 1;   // this wave's quarter: tokens 128 wm .., features 64 wn ..
-    const int row0 = tm * BM, col0 = tn * BN;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane / T::MT, n = lane % T::MT;
+    const int wm = w / T::WN, wn = w % T::WN;
 
-    // staging: thread t moves 16-byte chunk (t % 8) of rows t / 8 + 32 it of the two tiles
-    constexpr int AIT = BM / 32, BIT = BN / 32;
-    const int s_chunk = tid & 7, s_row = tid >> 3;
-    const uint16_t *xa[AIT], *wb[BIT];
+    // permutation of the 16-byte pieces of a row
+    auto swz = [](int row) { return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
+    // DMA instruction p of this wave: rows (p NW + w) RPI + lane / CPR of the tile of x (p < AP) or W
+    // (byte offsets from the tile's first row, whose address is uniform and moves along K)
+    uint32_t src[P];
+    const uint16_t *xbase, *wbase = W + (size_t)col0 * K;
+    {
+        static_assert(T::NW % 2 == 0, "the permutation of a wave's rows is the same in all its instructions");
+        const int r = lane / CPR, c = 8 * ((lane % CPR) ^ swz(w * T::RPI + r));
+        auto x_row = [&](int row) -> size_t {
+            if (HEADS_IN)   // token t of sequence b, head 0: [b][h][t][d_in]
+                return ((size_t)(row / hl.seq_len) * hl.H * hl.seq_len + row % hl.seq_len) * hl.d_in;
+            return (size_t)row * K;
+        };
+        xbase = x + x_row(row0);
 #pragma unroll
-    for (int it = 0; it < AIT; ++it) {   // rows past M re-read the last one
-        const int row = min(row0 + s_row + 32 * it, M - 1);
-        if (HEADS_IN)   // token t of sequence b, head 0: [b][h][t][d_in]
-            xa[it] = x + ((size_t)(row / hl.seq_len) * hl.H * hl.seq_len + row % hl.seq_len) * hl.d_in + 8 * s_chunk;
-        else
-            xa[it] = x + (size_t)row * K + 8 * s_chunk;
+        for (int p = 0; p < T::AP; ++p)   // rows past M re-read the last one
+            src[p] = (uint32_t)(2 * (x_row(min(row0 + (p * T::NW + w) * T::RPI + r, M - 1)) - x_row(row0) + c));
+#pragma unroll
+        for (int p = 0; p < T::BP; ++p) src[T::AP + p] = (uint32_t)(2 * ((size_t)((p * T::NW + w) * T::RPI + r) * K + c));
     }
-#pragma unroll
-    for (int it = 0; it < BIT; ++it) wb[it] = W + (size_t)(col0 + s_row + 32 * it) * K + 8 * s_chunk;
-    u32x4 ra[AIT], rb[BIT];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int it = 0; it < AIT; ++it) {
-            // head-major input: feature k0 is column k0 % d_in of head k0 / d_in, one head = seq_len rows on
-            const size_t off = HEADS_IN ? (size_t)(k0 / hl.d_in) * hl.seq_len * hl.d_in + k0 % hl.d_in : (size_t)k0;
-            ra[it] = *reinterpret_cast<const u32x4 *>(xa[it] + off);
-        }
-#pragma unroll
-        for (int it = 0; it < BIT; ++it) rb[it] = *reinterpret_cast<const u32x4 *>(wb[it] + k0);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds + (uint32_t)w * 1024;
+    const int steps = K / BK;
+    int next = 0;   // the step the addresses stand at
+    auto issue = [&](int p, int slot) {
+        const int at = p < T::AP ? p * T::NW : T::BM / T::RPI + (p - T::AP) * T::NW;
+        dma16(p < T::AP ? xbase : wbase, src[p], lds0 + (uint32_t)(slot * T::STAGE + at * 1024));
     };
-    auto stage = [&]() {
-#pragma unroll
-        for (int it = 0; it < AIT; ++it) *reinterpret_cast<u32x4 *>(&lds.a[s_row + 32 * it][8 * s_chunk]) = ra[it];
-#pragma unroll
-        for (int it = 0; it < BIT; ++it) *reinterpret_cast<u32x4 *>(&lds.b[s_row + 32 * it][8 * s_chunk]) = rb[it];
+    auto advance = [&]() {   // (the last step is re-read instead of a step past the end)
+        if (next + 1 >= steps) return;
+        ++next;
+        wbase += BK;
+        xbase += BK;   // head-major x: column k0 % d_in of head k0 / d_in, one head = seq_len rows on
+        if (HEADS_IN && (next * BK) % hl.d_in == 0) xbase += (size_t)(hl.seq_len - 1) * hl.d_in;
     };
 
-    // acc[j][i]: features 64 wn + 32 j .. (rows of the MFMA tile) x tokens 128 wm + 32 i .. (columns)
-    f32x16 acc[2][TI];
+    // acc[j][i]: features 32 TJ wn + 32 j .. (rows of the MFMA tile) x tokens 32 TI wm + 32 i .. (columns)
+    typename T::Acc acc[TJ][TI];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+            for (int r = 0; r < MT * MT / 64; ++r) acc[j][i][r] = 0.f;
 
-    fetch(0);
-    stage();
-    __syncthreads();
-    const int steps = K / BK;
-    for (int kt = 0; kt < steps; ++kt) {
-        const bool more = kt + 1 < steps;
-        if (more) fetch((kt + 1) * BK);
+    u32x4 fw[2][TJ], fx[2][TI];
+    int off[KS];   // element offset of slab ks in this lane's row (rows 32 apart have the same permutation)
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            u32x4 fw[2], fx[TI];
+    for (int ks = 0; ks < KS; ++ks) off[ks] = n * BK + 8 * ((T::SD / 8 * ks + g) ^ swz(n));
+    constexpr int NR = TI + TJ, NM = TI * TJ;   // operand reads and matrix instructions of a slab
+    auto read_op = [&](int slot, int ks, int set, int r) {
+        const uint16_t *a = reinterpret_cast<const uint16_t *>(lds + slot * T::STAGE) + off[ks];
+        // (in the order the matrix instructions need them)
+        if (r == 0 || r > TI) fw[set][r ? r - TI : 0] = *reinterpret_cast<const u32x4 *>(a + (T::BM + MT * (TJ * wn + (r ? r - TI : 0))) * BK);
+        else fx[set][r - 1] = *reinterpret_cast<const u32x4 *>(a + MT * (TI * wm + r - 1) * BK);
+    };
+
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                fw[j] = *reinterpret_cast<const u32x4 *>(&lds.b[64 * wn + 32 * j + n][16 * ks + 8 * g]);
+    for (int st = 0; st < ST; ++st) {
+        if (st == ST - 1) break;
 #pragma unroll
-            for (int i = 0; i < TI; ++i)
-                fx[i] = *reinterpret_cast<const u32x4 *>(&lds.a[(BM / 2) * wm + 32 * i + n][16 * ks + 8 * g]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < TI; ++i) acc[j][i] = mfma(fw[j], fx[i], acc[j][i]);
-        }
-        __syncthreads();   // every wave is done reading this step's rows
-        if (more) {
-            stage();
-            __syncthreads();
-        }
+        for (int p = 0; p < P; ++p) issue(p, st);
+        advance();
     }
+    // the last stage's pieces: what the loop issues after a barrier for the step ST ahead, here for step ST - 1
+    // Piece p of a stage goes out with matrix instruction p SPAN / P counted from the barrier that freed the stage, so that the
+    // youngest has some time left until the barrier that waits for it.
+    constexpr int SPAN = KS * NM * T::SPREAD / 8;
+    constexpr int PK = (P * NM + SPAN - 1) / SPAN < P ? (P * NM + SPAN - 1) / SPAN : P;   // pieces of the first slab
+#pragma unroll
+    for (int p = 0; p < PK; ++p) issue(p, ST - 1);
+    dma_barrier<(ST - 2) * P + PK>();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_op(0, 0, 0, r);
+    int slot = 0;
+    for (int kt = 0; kt < steps; ++kt) {
+        const int after = slot + 1 == ST ? 0 : slot + 1;       // slot of the next step
+        const int fill = slot == 0 ? ST - 1 : slot - 1;        // slot being filled: step kt + ST - 1
+        constexpr_for<KS>([&](auto kc) {
+            constexpr int ks = decltype(kc)::value;
+            if constexpr (ks + 1 == KS) {
+                advance();
+                dma_barrier<(ST - 2) * P>();
+            }
+            // the last slab starts the stage of step kt + ST, the others continue the one of step kt + ST - 1
+            constexpr_for<NM>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                acc[m / TI][m % TI] = mfma(fw[ks & 1][m / TI], fx[ks & 1][m % TI], acc[m / TI][m % TI]);
+                // between two matrix instructions: the share of the next slab's operand reads, and of the DMA
+                constexpr_for<NR>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    if constexpr (r * NM / NR == m) read_op(ks + 1 < KS ? slot : after, (ks + 1) % KS, (ks + 1) & 1, r);
+                });
+                constexpr_for<P>([&](auto pc) {
+                    constexpr int p = decltype(pc)::value;
+                    if constexpr (p * SPAN / P == (ks + 1) % KS * NM + m) issue(p, ks + 1 < KS ? fill : slot);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        slot = after;
+    }
+    dma_barrier<0>();   // nothing lands in LDS any more
 
-    // epilogue: lane (g, n) of tile (j, i) holds token 128 wm + 32 i + n, features 64 wn + 32 j + 8 (r / 4) +
-    // 4 g + r % 4.  64 tokens at a time through this wave's staging rows [64 tokens][64 features], then
-    // 128-byte row segments.
-    uint16_t *out = reinterpret_cast<uint16_t *>(&lds) + (size_t)w * 64 * OUT_LD;
-    const int f_lane = col0 + 64 * wn + 8 * (lane & 7);   // first of this lane's 8 features
+    // epilogue: lane (g, n) of tile (j, i) holds token MT (TI wm + i) + n, features MT (TJ wn + j) + 64 / MT * 4 q + 4 g + e
+    // in register 4 q + e.  32 tokens at a time through this wave's staging rows, then whole row segments.
+    constexpr int OUT_LD = T::OUT_LD, CP = MT * TJ / 8;   // 16-byte pieces per row
+    uint16_t *out = reinterpret_cast<uint16_t *>(lds) + (size_t)w * 32 * OUT_LD;
+    const int oc = lane % CP, orow = lane / CP;
+    const int f_lane = col0 + MT * TJ * wn + 8 * oc;   // first of this lane's 8 features
+    const int r_lane = row0 + MT * TI * wm + orow;
     FeatDst fd{};
     RowPos rp0{};
     if (SPLIT_OUT) {
         fd = feat_dst(hl, y, f_lane);
-        rp0 = row_pos(row0 + (BM / 2) * wm + (lane >> 3), hl.seq_len);
+        rp0 = row_pos(r_lane, hl.seq_len);
     }
+    constexpr int IT = 32 / MT;   // MFMA tiles in 32 tokens
 #pragma unroll
-    for (int half = 0; half < TI / 2; ++half) {
+    for (int i32 = 0; i32 < TI / IT; ++i32) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TJ; ++j)
 #pragma unroll
-            for (int i2 = 0; i2 < 2; ++i2)
+            for (int i = 0; i < IT; ++i)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
+                for (int q = 0; q < MT * MT / 256; ++q) {
                     f32x4 o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = acc[j][2 * half + i2][4 * q4 + e];
-                    const bf16x4 hv = __builtin_convertvector(o, bf16x4);
-                    *reinterpret_cast<u32x2 *>(out + (size_t)(32 * i2 + n) * OUT_LD + 32 * j + 8 * q4 + 4 * g) =
-                        __builtin_bit_cast(u32x2, hv);
+                    for (int e = 0; e < 4; ++e) o[e] = acc[j][i32 * IT + i][4 * q + e];
+                    *reinterpret_cast<u32x2 *>(out + (size_t)(MT * i + n) * OUT_LD + MT * j + 256 / MT * q + 4 * g) =
+                        __builtin_bit_cast(u32x2, __builtin_convertvector(o, bf16x4));
                 }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own 64 x 64 piece is complete in LDS
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own rows are complete in LDS
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int r = 8 * it + (lane >> 3), c = lane & 7;
-            const u32x4 val = *reinterpret_cast<const u32x4 *>(out + (size_t)r * OUT_LD + 8 * c);
-            const int row = row0 + (BM / 2) * wm + 64 * half + r;
+        for (int it = 0; it < CP / 2; ++it) {
+            const int dr = it * (64 / CP);
+            const u32x4 val = *reinterpret_cast<const u32x4 *>(out + (size_t)(dr + orow) * OUT_LD + 8 * oc);
+            const int row = r_lane + 32 * i32 + dr;
             if (row < M) {
                 if (SPLIT_OUT) {
-                    const RowPos rp = row_after(rp0, 64 * half + 8 * it, hl.seq_len);
+                    const RowPos rp = row_after(rp0, 32 * i32 + dr, hl.seq_len);
                     *reinterpret_cast<u32x4 *>(fd.dst + (size_t)rp.b * fd.batch_stride + fd.fixed + (size_t)rp.t * fd.dh) = val;
                 } else {
                     *reinterpret_cast<u32x4 *>(y + (size_t)row * N + f_lane) = val;
                 }
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the next piece overwrites it
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the next rows overwrite it
     }
 }
 
-// ---- the wide tiling: 256 x 256 outputs per workgroup ------------------------------------------------------
-// For large projections with N a multiple of 256.  Four waves, each a 128 x 128 quarter as 4 x 4 MFMA tiles:
-// 8 operand reads of 16 bytes per lane feed 16 MFMAs (half the LDS traffic per matrix instruction of the
-// 4 x 2 tiling), with the 256 accumulator registers a wave then needs: one workgroup per CU, one wave per
-// SIMD, the whole register file to a wave.  The LDS holds two generations of the 256 + 256 staged rows and
-// one barrier per step separates them.  The global loads run two K steps ahead and are dealt out between the
-// matrix instructions, one after every four: with the sixteen loads of a thread issued in one burst a wave
-// stood 1,500 of a step's 5,500 clock counts just getting them accepted by the memory pipeline, and another
-// 850 writing them to LDS, all of it with the matrix pipe idle.  During step kt a thread writes the piece it
-// fetched a step ago (rows of step kt + 1) into the other generation and refills the same register with the
-// same piece of step kt + 2, sixteen times, so sixteen loads stay in flight and each is a step old when it is
-// needed.  Inside a step the operands of the next 16-deep slab are read while the matrix instructions of the
-// current one run.
-constexpr int WBM = 256, WBN = 256;
-struct LdsWide {
-    uint16_t a[2][WBM][LD];    // rows of x, two generations
-    uint16_t b[2][WBN][LD];    // rows of W
-};
-static_assert(sizeof(LdsWide) <= 160 * 1024, "one workgroup per CU");
-
-template <bool SPLIT_OUT, bool HEADS_IN>
-__global__ __launch_bounds__(NT, 1) void linear_wide_kernel(const uint16_t *__restrict__ x,
-                                                            const uint16_t *__restrict__ W,
-                                                            uint16_t *__restrict__ y, int M, int K, int N,
-                                                            int tiles_m, int tiles_n, HeadLayout hl)
+// Blocks 0 .. : the first `whole` tiles of T; the blocks after them: the remaining tiles in halves of BM / 2 tokens (T2).
+// Block -> tile: XCD b % 8 works through a contiguous eighth of the tiles, features fastest, so that the tiles it has in
+// hand share rows of x and W in its L2 (and a problem of one band of rows still uses all XCDs).
+template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
+__global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NW / 4 : T::NW / 2) void linear_tile_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, uint16_t *__restrict__ y, int M, int K, int N,
+    int tiles_n, int whole, int halves, HeadLayout hl)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    LdsWide &lds = *reinterpret_cast<LdsWide *>(lds_raw);
+    __shared__ __align__(1024) unsigned char lds[T::LDS];
+    const int per = (whole + kXcds - 1) / kXcds;
+    int b = blockIdx.x;
+    if (b < per * kXcds) {
+        const int tile = b % kXcds * per + b / kXcds;
+        if (tile >= whole) return;   // uniform
+        tile_body<T, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, tile / tiles_n * T::BM, tile % tiles_n * T::BN, hl);
+    } else if constexpr (!std::is_same_v<T, T2>) {
+        static_assert(T2::BM * 2 == T::BM && T2::BN == T::BN && T2::NT == T::NT && T2::LDS <= T::LDS, "");
+        b -= per * kXcds;
+        const int per2 = (halves + kXcds - 1) / kXcds, h = b % kXcds * per2 + b / kXcds;
+        if (h >= halves) return;     // uniform
+        const int tile = whole + h / 2, row0 = tile / tiles_n * T::BM + h % 2 * T2::BM;
+        if (row0 >= M) return;       // uniform: the second half of a last band
+        tile_body<T2, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, row0, tile % tiles_n * T::BN, hl);
+    }
+}
 
-    const int b = blockIdx.x;
-    const int xcd = b % kXcds, local = b / kXcds;
-    const int tm = (local / tiles_n) * kXcds + xcd, tn = local % tiles_n;
-    if (tm >= tiles_m) return;   // uniform: the grid is padded to a multiple of 8 rows of tiles
-
+// ---- a handful of tokens -------------------------------------------------------------------------------------
+// M of a few: bound by reading W once (and, for a small W, by the latency of one trip to memory).  A workgroup takes 16
+// output features and 16 TT tokens; its eight waves split K, each with the whole of its share of W (and x)
+// requested up front, straight into operand registers (MFMA 16x16x32: lane = row n of W / token n, 8
+// consecutive k); partial sums meet in LDS.  N / 16 workgroups of eight waves put the whole W in flight at once.
+constexpr int RW = 8;           // waves
+template <int TT, bool SPLIT_OUT, bool HEADS_IN>
+__global__ __launch_bounds__(64 * RW, 2) void linear_rows_kernel(const uint16_t *__restrict__ x,
+                                                                 const uint16_t *__restrict__ W,
+                                                                 uint16_t *__restrict__ y, int M, int K, int N,
+                                                                 HeadLayout hl)
+{
+    constexpr int G = TT == 4 ? 4 : 8;   // steps of 32 in flight per wave
+    __shared__ __align__(16) float red[RW][16 * TT][20];   // (row stride 20: 16-byte writes of 16 rows spread over the banks)
     const int tid = threadIdx.x;
-    const int w = tid >> 6, lane = tid & 63, g = lane >> 5, n = lane & 31;
-    const int wm = w >> 1, wn = w & 1;   // this wave's quarter: tokens 128 wm .., features 128 wn ..
-    const int row0 = tm * WBM, col0 = tn * WBN;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, n = lane & 15;
+    const int col0 = blockIdx.x * 16, row0 = blockIdx.y * 16 * TT;
 
-    // staging: thread t moves 16-byte chunk (t % 8) of rows t / 8 + 32 it of the two tiles
-    constexpr int AIT = WBM / 32, BIT = WBN / 32;
-    const int s_chunk = tid & 7, s_row = tid >> 3;
-    const uint16_t *xa[AIT], *wb[BIT];
+    const uint16_t *wp = W + (size_t)(col0 + n) * K + 8 * g;
+    const uint16_t *xp[TT];
 #pragma unroll
-    for (int it = 0; it < AIT; ++it) {   // rows past M re-read the last one
-        const int row = min(row0 + s_row + 32 * it, M - 1);
-        if (HEADS_IN)   // token t of sequence b, head 0: [b][h][t][d_in]
-            xa[it] = x + ((size_t)(row / hl.seq_len) * hl.H * hl.seq_len + row % hl.seq_len) * hl.d_in + 8 * s_chunk;
-        else
-            xa[it] = x + (size_t)row * K + 8 * s_chunk;
+    for (int t = 0; t < TT; ++t) {   // rows past M re-read the last one
+        const int row = min(row0 + 16 * t + n, M - 1);
+        xp[t] = x + 8 * g + (HEADS_IN ? ((size_t)(row / hl.seq_len) * hl.H * hl.seq_len + row % hl.seq_len) * hl.d_in
+                                      : (size_t)row * K);
     }
+    f32x4 acc[TT];
 #pragma unroll
-    for (int it = 0; it < BIT; ++it) wb[it] = W + (size_t)(col0 + s_row + 32 * it) * K + 8 * s_chunk;
-    // piece p of a thread: p < AIT a row chunk of x, else of W
-    u32x4 rp[AIT + BIT];
-    auto fetch_piece = [&](int p, int k0) {
-        if (p < AIT) {
-            const size_t off = HEADS_IN ? (size_t)(k0 / hl.d_in) * hl.seq_len * hl.d_in + k0 % hl.d_in : (size_t)k0;
-            rp[p] = *reinterpret_cast<const u32x4 *>(xa[p] + off);
-        } else {
-            rp[p] = *reinterpret_cast<const u32x4 *>(wb[p - AIT] + k0);
+    for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int steps = K / 32, s1 = steps * (w + 1) / RW;
+    for (int s = steps * w / RW; s < s1; s += G) {
+        u32x4 a[G], b[G][TT];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int k0 = 32 * min(s + j, s1 - 1);
+            const size_t xo = HEADS_IN ? (size_t)(k0 / hl.d_in) * hl.seq_len * hl.d_in + k0 % hl.d_in : (size_t)k0;
+            a[j] = *reinterpret_cast<const u32x4 *>(wp + k0);
+#pragma unroll
+            for (int t = 0; t < TT; ++t) b[j][t] = *reinterpret_cast<const u32x4 *>(xp[t] + xo);
         }
-    };
-    auto stage_piece = [&](int p, int gen) {
-        if (p < AIT) *reinterpret_cast<u32x4 *>(&lds.a[gen][s_row + 32 * p][8 * s_chunk]) = rp[p];
-        else *reinterpret_cast<u32x4 *>(&lds.b[gen][s_row + 32 * (p - AIT)][8 * s_chunk]) = rp[p];
-    };
-
-    // acc[j][i]: features 128 wn + 32 j .. (rows of the MFMA tile) x tokens 128 wm + 32 i .. (columns)
-    f32x16 acc[4][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < G; ++j) {
+            if (s + j < s1) {   // uniform
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
-
-    const int steps = K / BK;
-    // K steps past the end re-read the last one (the loads are unconditional so that the number in flight is
-    // known; what they fetch is staged into a generation nobody reads any more)
-    auto k_of = [&](int step) { return min(step, steps - 1) * BK; };
-#pragma unroll
-    for (int p = 0; p < AIT + BIT; ++p) fetch_piece(p, 0);
-#pragma unroll
-    for (int p = 0; p < AIT + BIT; ++p) {
-        stage_piece(p, 0);
-        fetch_piece(p, k_of(1));
+                for (int t = 0; t < TT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[j]),
+                                                                     __builtin_bit_cast(bf16x8, b[j][t]), acc[t], 0, 0, 0);
+            }
+        }
     }
+    // lane (g, n): token n, features 4 g .. 4 g + 3
+#pragma unroll
+    for (int t = 0; t < TT; ++t) *reinterpret_cast<f32x4 *>(&red[w][16 * t + n][4 * g]) = acc[t];
     __syncthreads();
-    for (int kt = 0; kt < steps; ++kt) {
-        const int cur = kt & 1;
-        const int k_next2 = k_of(kt + 2);
-        const uint16_t *pb = &lds.b[cur][128 * wn + n][8 * g];
-        const uint16_t *pa = &lds.a[cur][128 * wm + n][8 * g];
-        u32x4 fw[2][4], fx[2][4];
-        auto read_ops = [&](int ks, int set) {
+    if (tid < 128 * TT) {   // two features of one token per thread
+        const int tok = tid >> 3, f2 = 2 * (tid & 7), row = row0 + tok;
+        float s0 = 0.f, s1v = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) fw[set][j] = *reinterpret_cast<const u32x4 *>(pb + (size_t)32 * j * LD + 16 * ks);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) fx[set][i] = *reinterpret_cast<const u32x4 *>(pa + (size_t)32 * i * LD + 16 * ks);
-        };
-        read_ops(0, 0);
-        static_assert((BK / 16) * 4 == AIT + BIT, "one staged piece per group of four matrix instructions");
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            if (ks + 1 < BK / 16) read_ops(ks + 1, (ks + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][i] = mfma(fw[ks & 1][j], fx[ks & 1][i], acc[j][i]);
-                // the piece fetched a step ago goes to the other generation (every wave left it at the last
-                // barrier), and its register takes the same piece of the step after the next
-                const int p = 4 * ks + j;
-                stage_piece(p, cur ^ 1);
-                fetch_piece(p, k_next2);
-                __builtin_amdgcn_sched_barrier(0);
+        for (int v = 0; v < RW; ++v) { s0 += red[v][tok][f2]; s1v += red[v][tok][f2 + 1]; }
+        if (row < M) {
+            const uint32_t o = (uint32_t)f32_to_bf16_bits(s0) | ((uint32_t)f32_to_bf16_bits(s1v) << 16);
+            const int f = col0 + f2;
+            uint16_t *dst = y + (size_t)row * N + f;
+            if (SPLIT_OUT) {
+                const FeatDst fd = feat_dst(hl, y, f);
+                const RowPos rp = row_pos(row, hl.seq_len);
+                dst = fd.dst + (size_t)rp.b * fd.batch_stride + fd.fixed + (size_t)rp.t * fd.dh;
             }
-        }
-        __syncthreads();
-    }
-    // (the loads of the two steps past the end are still in flight: their registers are dead)
-
-    // epilogue: lane (g, n) of tile (j, i) holds token 128 wm + 32 i + n, features 128 wn + 32 j + 8 (r / 4) +
-    // 4 g + r % 4.  64 tokens x 64 features at a time through this wave's staging rows, then 128-byte row
-    // segments.  (The last barrier of the loop has passed: nobody reads the operand buffers any more.)
-    uint16_t *out = reinterpret_cast<uint16_t *>(lds_raw) + (size_t)w * 64 * OUT_LD;
-    const int f_lane = col0 + 128 * wn + 8 * (lane & 7);   // first of this lane's 8 features of the piece jh = 0
-    FeatDst fd[2] = {};
-    RowPos rp0{};
-    if (SPLIT_OUT) {
-        fd[0] = feat_dst(hl, y, f_lane);
-        fd[1] = feat_dst(hl, y, f_lane + 64);
-        rp0 = row_pos(row0 + 128 * wm + (lane >> 3), hl.seq_len);
-    }
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int jh = 0; jh < 2; ++jh) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        f32x4 o;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = acc[2 * jh + j][2 * half + i2][4 * q4 + e];
-                        const bf16x4 hv = __builtin_convertvector(o, bf16x4);
-                        *reinterpret_cast<u32x2 *>(out + (size_t)(32 * i2 + n) * OUT_LD + 32 * j + 8 * q4 + 4 * g) =
-                            __builtin_bit_cast(u32x2, hv);
-                    }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own 64 x 64 piece is complete in LDS
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int r = 8 * it + (lane >> 3), c = lane & 7;
-                const u32x4 val = *reinterpret_cast<const u32x4 *>(out + (size_t)r * OUT_LD + 8 * c);
-                const int row = row0 + 128 * wm + 64 * half + r;
-                if (row < M) {
-                    if (SPLIT_OUT) {
-                        const RowPos rp = row_after(rp0, 64 * half + 8 * it, hl.seq_len);
-                        *reinterpret_cast<u32x4 *>(fd[jh].dst + (size_t)rp.b * fd[jh].batch_stride + fd[jh].fixed +
-                                                   (size_t)rp.t * fd[jh].dh) = val;
-                    } else {
-                        *reinterpret_cast<u32x4 *>(y + (size_t)row * N + f_lane + 64 * jh) = val;
-                    }
-                }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read back before the next piece overwrites it
+            *reinterpret_cast<uint32_t *>(dst) = o;
         }
     }
 }
 
-// The wide tiling pays when its tiles, one per CU at a time, come in nearly whole rounds of the chip: measured
-// at 256, 512, 1280 tiles it is 6-16 % faster than the narrow one (4096^3: 1032 against 894 TFLOP/s), at 384
-// tiles (a round and a half) 4 % slower.
-__host__ inline bool use_wide(int M, int N)
+// ---- choice of the variant ---------------------------------------------------------------------------------
+using T64 = Tile<64, 64, 2, 2, 64, 4>;                 // 64 KB of LDS: two workgroups per CU
+using T128N = Tile<128, 64, 2, 2, 64, 3>;              // 72 KB: two
+using T128 = Tile<128, 128, 2, 2, 64, 2, 16, 5>;       // 64 KB: two
+using T256 = Tile<256, 256, 2, 2, 64, 2, 16, 6>;       // 128 KB: one
+using T256H = Tile<128, 256, 2, 2, 64, 2, 16, 6>;
+enum Variant { ROWS1, ROWS2, TILE64, TILE128N, TILE128, TILE256 };
+
+inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
+
+// A handful of tokens: 16 or 32 per workgroup (above 32 the 64 x 64 tiles, which read W fewer times, are as fast or faster).
+// Otherwise the tiling with the smallest expected time.  The figures are microseconds per 64-deep step, measured at
+// K 768 .. 2048, 40 .. 5120 tiles: a launch of up to 256 tiles (one per CU) is bound by the latency of a step, after
+// that each further tile per CU adds its share.  (The larger the tile the less it reads per product: at 32768 x 1792 x
+// 2560 the four tilings take 630, 417, 308 and 240 us; at 512 x 1792 x 2560 they take 17, 12, 21 and 37.)
+inline Variant pick_variant(int M, int K, int N)
 {
-    if (N % WBN != 0) return false;
-    const long tiles = (long)((M + WBM - 1) / WBM) * (N / WBN);
-    const long rounds = (tiles + 255) / 256;
-    return tiles * 5 >= rounds * 256 * 4;   // the last round at least 80 % of the way to full, on average
+    if (M <= 16) return ROWS1;
+    if (M <= 32 || K >= (1 << 22)) return ROWS2;   // (tiles address their rows with 32-bit offsets)
+    auto per_cu = [](long tiles) { return (float)((tiles + 255) / 256); };
+    Variant best = TILE64;
+    float t = 0.05f + 0.21f * per_cu(tiles_of(M, N, T64::BM, T64::BN));
+    auto offer = [&](Variant v, float tv) {
+        if (tv < t) { t = tv; best = v; }
+    };
+    offer(TILE128N, 0.02f + 0.31f * per_cu(tiles_of(M, N, T128N::BM, T128N::BN)));
+    const long n128 = tiles_of(M, N, T128::BM, T128::BN);
+    offer(TILE128, n128 <= 256 ? 0.7f : 0.9f * (float)((n128 + 511) / 512));   // two per CU run side by side
+    if (N % T256::BN == 0) {
+        const long n256 = tiles_of(M, N, T256::BM, T256::BN), rem = n256 % 256;
+        offer(TILE256, 1.5f * (float)(n256 / 256) + (rem == 0 ? 0.f : rem <= 128 ? 1.f : 1.5f));   // (see launch_tile)
+    }
+    return best;
 }
 
+template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
+void launch_tile(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N, const HeadLayout &hl, hipStream_t s)
+{
+    const long tiles = tiles_of(M, N, T::BM, T::BN);
+    // a last round of the chip that would be at most half full is dealt out in half tiles
+    const long rem = tiles % 256, halves = !std::is_same_v<T, T2> && rem <= 128 ? 2 * rem : 0, whole = tiles - halves / 2;
+    const long grid = (whole + kXcds - 1) / kXcds * kXcds + (halves + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL((linear_tile_kernel<T, T2, SPLIT_OUT, HEADS_IN>), dim3((unsigned)grid), dim3(T::NT), 0, s, x, W, y, M, K,
+                       N, N / T::BN, (int)whole, (int)halves, hl);
+}
+template <int TT, bool SPLIT_OUT, bool HEADS_IN>
+void launch_rows(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N, const HeadLayout &hl, hipStream_t s)
+{
+    hipLaunchKernelGGL((linear_rows_kernel<TT, SPLIT_OUT, HEADS_IN>), dim3((unsigned)(N / 16), (unsigned)((M + 16 * TT - 1) / (16 * TT))),
+                       dim3(64 * RW), 0, s, x, W, y, M, K, N, hl);
+}
+template <bool SPLIT_OUT, bool HEADS_IN>
+hipError_t launch_variant(Variant v, const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N,
+                          const HeadLayout &hl, hipStream_t s)
+{
+    switch (v) {
+    case ROWS1: launch_rows<1, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case ROWS2: launch_rows<2, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE64: launch_tile<T64, T64, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE128N: launch_tile<T128N, T128N, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE128: launch_tile<T128, T128, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE256: launch_tile<T256, T256H, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    }
+    return hipGetLastError();
+}
 template <bool SPLIT_OUT, bool HEADS_IN>
 hipError_t launch_any(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N, const HeadLayout &hl,
                       hipStream_t s)
 {
-    if (use_wide(M, N)) {
-        const int tiles_m = (M + WBM - 1) / WBM, tiles_n = N / WBN;
-        const int rows_padded = (tiles_m + kXcds - 1) / kXcds * kXcds;
-        const void *kern = reinterpret_cast<const void *>(linear_wide_kernel<SPLIT_OUT, HEADS_IN>);
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(LdsWide));
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((linear_wide_kernel<SPLIT_OUT, HEADS_IN>), dim3((unsigned)((size_t)rows_padded * tiles_n)),
-                           dim3(NT), sizeof(LdsWide), s, x, W, y, M, K, N, tiles_m, tiles_n, hl);
-        return hipGetLastError();
-    }
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
-    const int rows_padded = (tiles_m + kXcds - 1) / kXcds * kXcds;
-    hipLaunchKernelGGL((linear_kernel<SPLIT_OUT, HEADS_IN>), dim3((unsigned)((size_t)rows_padded * tiles_n)), dim3(NT), 0,
-                       s, x, W, y, M, K, N, tiles_m, tiles_n, hl);
-    return hipGetLastError();
+    return launch_variant<SPLIT_OUT, HEADS_IN>(pick_variant(M, K, N), x, W, y, M, K, N, hl, s);
 }
 
 }  // namespace lin
 
 bool linear_supported(int M, int K, int N, int dtype)
 {
-    return dtype == BASED_BF16 && M >= 1 && K >= lin::BK && K % lin::BK == 0 && N >= lin::BN && N % lin::BN == 0;
+    return dtype == BASED_BF16 && M >= 1 && K >= lin::KQ && K % lin::KQ == 0 && N >= lin::NQ && N % lin::NQ == 0;
 }
 
 hipError_t launch_linear(const void *x, const void *W, void *y, int M, int K, int N, hipStream_t s)
@@ -450,8 +496,8 @@ hipError_t launch_linear(const void *x, const void *W, void *y, int M, int K, in
 
 bool project_qkv_supported(int K, int H, int d_feat, int d_v, int dtype)
 {
-    return dtype == BASED_BF16 && K >= lin::BK && K % lin::BK == 0 && H >= 1 && d_feat >= 8 && d_feat % 8 == 0 &&
-           d_v >= 8 && d_v % 8 == 0 && (H * (2 * d_feat + d_v)) % lin::BN == 0;
+    return dtype == BASED_BF16 && K >= lin::KQ && K % lin::KQ == 0 && H >= 1 && d_feat >= 8 && d_feat % 8 == 0 &&
+           d_v >= 8 && d_v % 8 == 0 && (H * (2 * d_feat + d_v)) % lin::NQ == 0;
 }
 
 hipError_t launch_project_qkv(const void *x, const void *W, void *q, void *k, void *v, int B, int seq_len, int K,
@@ -464,7 +510,7 @@ hipError_t launch_project_qkv(const void *x, const void *W, void *q, void *k, vo
 
 bool project_out_supported(int H, int d_v, int N, int dtype)
 {
-    return dtype == BASED_BF16 && H >= 1 && d_v >= lin::BK && d_v % lin::BK == 0 && N >= lin::BN && N % lin::BN == 0;
+    return dtype == BASED_BF16 && H >= 1 && d_v >= lin::KQ && d_v % lin::KQ == 0 && N >= lin::NQ && N % lin::NQ == 0;
 }
 
 hipError_t launch_project_out(const void *y_heads, const void *W, void *out, int B, int seq_len, int H, int d_v,
@@ -472,7 +518,17 @@ hipError_t launch_project_out(const void *y_heads, const void *W, void *out, int
 {
     const int M = B * seq_len, K = H * d_v;
     lin::HeadLayout hl{seq_len, H, {0, 0, 0}, nullptr, nullptr, d_v};
-    return lin::launch_any<false, true>((const uint16_t *)y_heads, (const uint16_t *)W, (uint16_t *)out, M, K, N, hl, s);
+    const uint16_t *x16 = (const uint16_t *)y_heads;
+    uint16_t *o16 = (uint16_t *)out;
+    const size_t seq_elems = (size_t)K * seq_len;
+    if (B == 1 || seq_elems < (1u << 30))
+        return lin::launch_any<false, true>(x16, (const uint16_t *)W, o16, M, K, N, hl, s);
+    // a tile addresses its rows with 32-bit byte offsets, which must not have to reach from one such sequence into the next
+    for (int b = 0; b < B; ++b) {
+        const hipError_t e = lin::launch_any<false, true>(x16 + b * seq_elems, (const uint16_t *)W, o16 + (size_t)b * seq_len * N, seq_len, K, N, hl, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace based

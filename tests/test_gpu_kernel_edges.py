@@ -1,0 +1,48 @@
+"""Edges of the kernels' own tilings and dispatch rules (GPU): sizes at which a variant can go wrong, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2402_18668_amd import synth
+from parity import TOL, check_close, down, up
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def based():
+    from paper_2402_18668_amd import based as b
+    return b
+
+
+def rows(a):
+    """Every output row is its own group for the parity criterion."""
+    return np.asarray(a).reshape(-1, a.shape[-1])
+
+
+# tokens of a decode batch (16 and 32 rows to a workgroup), one and several 64-token tiles, the 128 x 64 and 128 x 128
+# tilings, and a last round of 256 x 256 tiles in halves, the second half of its last band past the end
+@pytest.mark.parametrize("M,K,N", [(16, 64, 128), (17, 320, 256), (32, 1792, 128), (33, 128, 256), (64, 64, 384),
+                                   (65, 192, 128), (600, 128, 2560), (2049, 64, 2560), (300 * 256 + 100, 64, 256),
+                                   (300 * 256 + 130, 128, 256)])
+def test_linear_tilings(based, M, K, N):
+    x, W = synth.linear_inputs(61, M, K, N)
+    y = down(based.linear(up(x, "bf16"), up(W, "bf16")))
+    at = np.unique(np.r_[0:min(M, 300), np.arange(0, M, 509), max(0, M - 300):M])
+    check_close(y[at], oracle.linear(x[at], W), TOL["bf16"], f"linear {M}x{K}x{N}")
+
+
+# the same with head-major addressing: sequences that end inside a tile or a group of decode rows
+@pytest.mark.parametrize("B,N,dm,H,dp,dv", [(9, 1, 256, 4, 16, 64), (3, 7, 192, 4, 32, 64), (5, 13, 128, 8, 16, 128),
+                                            (3, 203, 128, 16, 16, 128), (2, 1100, 1792, 16, 16, 128)])
+def test_projection_tilings(based, B, N, dm, H, dp, dv):
+    x, W = synth.linear_inputs(62, B * N, dm, H * (2 * dp + dv))
+    x = x.reshape(B, N, dm)
+    got = based.project_qkv(up(x, "bf16"), up(W, "bf16"), H, dp, dv)
+    f = H * dp
+    for name, t, Wp in zip("qkv", got, (W[:f], W[f:2 * f], W[2 * f:])):
+        check_close(rows(down(t)), rows(oracle.project_heads(x, Wp, H)), TOL["bf16"], f"project {name}")
+    yh = synth.linear_inputs(63, B * H * N, dv, 8)[0].reshape(B, H, N, dv)
+    Wo = synth.linear_inputs(64, 8, H * dv, dm + dm % 128)[1]
+    check_close(rows(down(based.project_out(up(yh, "bf16"), up(Wo, "bf16")))), rows(oracle.project_out(yh, Wo)), TOL["bf16"],
+                "project out")
