@@ -24,7 +24,7 @@
  *     BASED_F32 or BASED_BF16.  All accumulation and the recurrent state are fp32.
  *     Outputs are rounded to dtype with round-to-nearest-even.
  *   - Supported sizes: d_feat in {8, 16, 24, 32} (the feature dimensions of the ablation table;
- *     16 and 32 have matrix-core prefill kernels for bf16, 8 and 24 run on the fp32 vector kernel
+ *     16 and 32 have bf16 matrix-core prefill kernels, 8 and 24 run on the fp32 matrix-core kernel
  *     for both dtypes; the packed-state prefill and the fused decode step exist for 16 and 32
  *     only); d_v, d_h in {64, 128}; w in {16, 32, 64, 128}; any B, H, N >= 1 with
  *     B * H * N < 2^31.  Anything else: BASED_ERR_UNSUPPORTED.
@@ -206,7 +206,7 @@ int based_decode_step_numerator(const void *q, const void *k, const void *v, voi
  *   gamma  [H]        in, fp32, device: the rate of every head (1 = no decay)
  *   gate   [B][N][H]  in, dtype, device, or NULL (based_decode_step_decay: [B][H]): scales the rows of y
  * Everything else as based_prefill / based_decode_step (canonical state).  Both dtypes run on the fp32
- * vector kernels (there is no matrix-core kernel for this variant), so based_prefill_decay needs a
+ * kernels (fp32 matrix instructions for the prefill), so based_prefill_decay needs a
  * workspace of based_prefill_decay_workspace_bytes, which differs from based_prefill's for bf16.
  */
 size_t based_prefill_decay_workspace_bytes(int B, int H, int N, int d_feat, int d_v, int dtype);

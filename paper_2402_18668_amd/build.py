@@ -15,7 +15,8 @@ SOURCES = [
     "api.hip",
     "state_io.hip",
     "decode.hip",
-    "linattn_prefill_ref.hip",
+    "linattn_prefill_f32.hip",
+    "linattn_prefill_f32_dp32.hip",
     "linattn_prefill_mfma.hip",
     "linattn_prefill_mfma32.hip",
     "swa_prefill_ref.hip",

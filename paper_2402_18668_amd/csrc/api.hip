@@ -120,7 +120,7 @@ static size_t prefill_scratch_bytes(int U, int N, int d_feat, int d_v, int dtype
 {
     if (prefill_mfma32_supported(d_feat, d_v, dtype)) return prefill_mfma32_workspace_bytes(U, N, d_feat, d_v);
     if (prefill_mfma_supported(d_feat, d_v, dtype)) return prefill_mfma_workspace_bytes(U, N, d_feat, d_v);
-    return prefill_ref_workspace_bytes(U, N, d_feat, d_v);
+    return prefill_f32_workspace_bytes(U, N, d_feat, d_v);
 }
 
 size_t based_prefill_workspace_bytes(int B, int H, int N, int d_feat, int d_v, int dtype)
@@ -156,7 +156,7 @@ static int prefill_any(const void *q, const void *k, const void *v, void *y, voi
     if (m16)
         return status_of(launch_prefill_mfma(q, k, v, y, st, fl, packed, inner,
                                              static_cast<unsigned *>(workspace), U, N, d_feat, d_v, s));
-    return status_of(launch_prefill_ref(q, k, v, y, st, fl, inner, U, N, d_feat, d_v, dtype, s));
+    return status_of(launch_prefill_f32(q, k, v, y, st, fl, inner, nullptr, nullptr, H, U, N, d_feat, d_v, dtype, s));
 }
 
 int based_prefill(const void *q, const void *k, const void *v, void *y, void *state, int has_init,
@@ -255,7 +255,7 @@ int based_decode_step_numerator(const void *q, const void *k, const void *v, voi
 size_t based_prefill_decay_workspace_bytes(int B, int H, int N, int d_feat, int d_v, int dtype)
 {
     if (!ok_lin_dims(d_feat, d_v) || !ok_dtype(dtype) || !ok_counts(B, H, N)) return 0;
-    const size_t scratch_bytes = prefill_ref_workspace_bytes(B * H, N, d_feat, d_v);
+    const size_t scratch_bytes = prefill_f32_workspace_bytes(B * H, N, d_feat, d_v);
     return scratch_bytes ? kWsHeader + scratch_bytes : 0;
 }
 
@@ -271,10 +271,10 @@ int based_prefill_decay(const void *q, const void *k, const void *v, void *y, vo
     if (state && !aligned16(state)) return BASED_ERR_INVALID_ARG;
     if (has_init && !state) return BASED_ERR_INVALID_ARG;
     const int U = B * H;
-    const size_t need = prefill_ref_workspace_bytes(U, N, d_feat, d_v);
+    const size_t need = prefill_f32_workspace_bytes(U, N, d_feat, d_v);
     if (need && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u))) return BASED_ERR_INVALID_ARG;
     void *inner = workspace ? static_cast<char *>(workspace) + kWsHeader : nullptr;
-    return status_of(launch_prefill_ref_decay(q, k, v, y, static_cast<float *>(state), has_init ? 1 : 0, inner, gamma,
+    return status_of(launch_prefill_f32(q, k, v, y, static_cast<float *>(state), has_init ? 1 : 0, inner, gamma,
                                               gate, H, U, N, d_feat, d_v, dtype, (hipStream_t)stream));
 }
 

@@ -83,10 +83,12 @@ template <typename Chunk> __device__ __forceinline__ void rotate_chunk(Chunk &c,
 
 // ---- launchers implemented in the kernel translation units ---------------------------------
 // Each returns a hipError_t from the launch (hipGetLastError), never synchronises.
-hipError_t launch_prefill_ref(const void *q, const void *k, const void *v, void *y, float *state,
-                              int has_init, void *workspace, int U, int N, int dp, int dv, int dtype,
-                              hipStream_t s);
-size_t prefill_ref_workspace_bytes(int U, int N, int dp, int dv);
+// all-fp32 arithmetic: fp32 at every d', bf16 at d' = 8 and 24, and the decay variant of both dtypes: gamma [H] (device,
+// or null: none) the rate of every head, gate [B][N][H] in the dtype of y (or null) scales the rows of y
+hipError_t launch_prefill_f32(const void *q, const void *k, const void *v, void *y, float *state, int has_init,
+                              void *workspace, const float *gamma, const void *gate, int H, int U, int N, int dp, int dv,
+                              int dtype, hipStream_t s);
+size_t prefill_f32_workspace_bytes(int U, int N, int dp, int dv);
 bool prefill_mfma_supported(int dp, int dv, int dtype);
 size_t prefill_mfma_workspace_bytes(int U, int N, int dp, int dv);
 // packed_state != 0: the state buffer is the packed layout (one row per unordered feature pair);
@@ -108,10 +110,6 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
 hipError_t launch_decode_step(const void *q, const void *k, const void *v, void *y, float *state,
                               int U, int dp, int dv, int dtype, int packed, int numerator_only,
                               const float *gamma, const void *gate, int H, hipStream_t s);
-// the fp32 vector kernel with a per-head decay gamma [H] and an optional gate [B][N][H] in the dtype of y
-hipError_t launch_prefill_ref_decay(const void *q, const void *k, const void *v, void *y, float *state,
-                                    int has_init, void *workspace, const float *gamma, const void *gate, int H,
-                                    int U, int N, int dp, int dv, int dtype, hipStream_t s);
 // rot (everywhere below): the rotary table, (cos, sin) per [position][pair], row 0 = the first token of
 // the call (prefill) or position 0 of the sequence (decode); null = no rotation
 hipError_t launch_rotary_table(float *table, int pos0, int N, int dh, float base, hipStream_t s);

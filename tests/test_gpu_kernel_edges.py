@@ -46,3 +46,41 @@ def test_projection_tilings(based, B, N, dm, H, dp, dv):
     Wo = synth.linear_inputs(64, 8, H * dv, dm + dm % 128)[1]
     check_close(rows(down(based.project_out(up(yh, "bf16"), up(Wo, "bf16")))), rows(oracle.project_out(yh, Wo)), TOL["bf16"],
                 "project out")
+
+
+# fp32 matrix-core prefill: chunks of 16 and stages of 64 tokens with remainders, one and several segments, both widths (two
+# 64-column slices share one K-state), each block count of d'; the second part continues from the first one's state
+@pytest.mark.parametrize("dtype,dp", [("f32", 8), ("f32", 16), ("f32", 24), ("f32", 32), ("bf16", 8), ("bf16", 24)])
+@pytest.mark.parametrize("dv,N1,N", [(64, 15, 33), (128, 17, 145), (64, 255, 600), (128, 256, 1321)])
+def test_prefill_fp32_arithmetic(based, dtype, dp, dv, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
+    B, H = 1, 3
+    q, k, v = synth.linattn_inputs(wl, units=B * H, N=N)
+    state = based.alloc_state(B, H, dp, dv)
+    got = [down(based.prefill(*(up(a[:, lo:hi], dtype, (B, H, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state,
+                              has_init=lo > 0)).reshape(B * H, hi - lo, dv) for lo, hi in ((0, N1), (N1, N))]
+    check_close(rows(np.concatenate(got, 1)), rows(oracle.linattn_quadratic(q, k, v)), TOL[dtype], "y")
+    S, z = based.state_export(state, B, H, dp, dv)
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(down(S).reshape(Sw.shape), Sw, 1e-4, "S")   # (bf16 inputs too: the arithmetic is fp32)
+    check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
+
+
+# decay at the same edges: the last chunk holds fewer than 16 tokens, increments of several segments, gate
+@pytest.mark.parametrize("dtype,dp,dv,N", [("bf16", 32, 64, 90), ("f32", 32, 128, 300), ("bf16", 24, 128, 801), ("bf16", 16, 64, 31)])
+def test_prefill_decay_edges(based, dtype, dp, dv, N):
+    import torch
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
+    B, H = 1, 3
+    q, k, v = synth.linattn_inputs(wl, units=B * H, N=N)
+    gamma = np.array([1.0, 0.95, 0.0], dtype=np.float32)
+    gate = synth.round_to(synth.normal(77, (B, N, H), 1.0), dtype)
+    want, Sw, zw = oracle.linattn_decay(q, k, v, gamma.astype(np.float64), gate=gate[0].T.astype(np.float64))
+    state = based.alloc_state(B, H, dp, dv)
+    y = based.prefill_decay(*(up(a, dtype, (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), up(gamma, "f32"), state=state,
+                            gate=up(gate, dtype))
+    torch.cuda.synchronize()
+    check_close(rows(down(y).reshape(B * H, N, dv)), rows(want), TOL[dtype], "y")
+    S, z = based.state_export(state, B, H, dp, dv)
+    check_close(down(S).reshape(Sw.shape), Sw, 1e-4, "S")
+    check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
