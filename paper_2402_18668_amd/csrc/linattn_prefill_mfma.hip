@@ -59,6 +59,7 @@
 #include "common.h"
 
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 namespace based {
@@ -275,14 +276,15 @@ struct SegTable { int begin[kMaxSegments + 1]; };
 
 }  // namespace
 
-// MODE 0: full prefill of the segment (readout + update); starts from the sum of workspace entries.
+// MODE 0: full prefill of the segment (readout + update); starts from the sum of workspace entries 1 .. seg.
 // MODE 1: state increment of the segment only (update GEMMs), written to workspace entry 1 + seg.
-// MODE 2: the caller's initial state, converted to accumulator layout, written to entry 0.
-// The main pass never reads the caller's state buffer, so writing the final state back into it
-// cannot race with another workgroup still starting up.
+// The caller's initial state is read by the main pass of segment 0 and by the increment of segment 0, which starts from
+// it (so that the other segments get it with their first entry).  The last segment overwrites it with the final state, and
+// waits until both have read it.
 // Increments and main pass run in ONE launch.  A main-pass workgroup of segment g > 0 waits (bounded)
 // for the flags of the increments before it.  Flag word F[unit][p][g] == epoch tells the main-pass
-// workgroup of segment g that entry p of this call is complete: every word has one writer and one
+// workgroup of segment g that entry p of this call is complete (p = 0, g = G - 1: that the main pass of segment 0
+// has read the initial state): every word has one writer and one
 // reader, and the reader zeroes it once it has seen it, so the words are clear again when the launch
 // ends (a replay of a captured launch, which repeats the same epoch, starts from cleared flags).
 template <int NC, int MODE>
@@ -318,8 +320,8 @@ __device__ __forceinline__ void prefill_body(
     uint16_t *yu = y + (size_t)u * N * DV;
     float *Su = state ? state + (size_t)u * (packed_state ? packed_state_stride(DP, DV) : state_stride(DP, DV))
                       : nullptr;
-    float *zu = Su ? Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV : nullptr;
-    float *ws_unit = ws ? ws + (size_t)u * G * entry_floats(NC) : nullptr;
+    // (entry p = 1 .. G - 1 of the unit starts at (p - 1) entry_floats)
+    float *ws_unit = ws ? ws + (size_t)u * (G - 1) * entry_floats(NC) : nullptr;
     unsigned *flags_unit = flags ? flags + (size_t)u * G * G : nullptr;
     // this lane's 16 bytes of register group 0 of slot 0 of column tile c (producer 0 keeps the moment
     // tile, which travels in the sixth slot of column tile 0), inside an entry
@@ -327,10 +329,10 @@ __device__ __forceinline__ void prefill_body(
     const bool holds_x = is_p && c == 0;
 
     if (MODE == 0 && G > 1 && seg > 0) {
-        // wait for the increments of this call (entry 0 comes from an earlier launch)
+        // wait for the increments of this call, the last segment also for the initial state to have been read
         if (tid == 0) {
             bool gave_up = false;
-            for (int p = 1; p <= seg; ++p) {
+            for (int p = has_init && seg == G - 1 ? 0 : 1; p <= seg; ++p) {
                 unsigned *f = flags_unit + p * G + seg;
                 int polls = 0;
                 while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != epoch) {
@@ -383,7 +385,67 @@ __device__ __forceinline__ void prefill_body(
         }
     };
 
-    if (MODE != 2 && tid == 0) lds.staged = 0u;   // ordered before its first use by the prologue's barriers
+    // The state buffer moves through LDS (which holds nothing else at either end of a segment), as an image of the consumers'
+    // tiles: image[column tile][32 T + row][IMG_LD].  A consumer reaches its registers' places at constant offsets from one
+    // address, and the whole workgroup moves 16-byte pieces between the image and the buffer's rows.  (Read and
+    // written by the consumers straight from and to memory, 160 four-byte accesses to a lane with an address each, it took
+    // 12 us to read and 5-6 us to write at 16 units, d_v 64.)
+    constexpr int NTHR = 64 * (NC + NPW), IMG_LD = 40;   // (the two rows that the halves of a wave access lie in different banks)
+    static_assert(sizeof(Lds<NC>) >= sizeof(float) * NC * 32 * NTILE * IMG_LD, "the image fits the LDS");
+    float *image = reinterpret_cast<float *>(&lds);
+    float *image_lane = image + c * 32 * NTILE * IMG_LD + 4 * g * IMG_LD + n;   // (consumers)
+    constexpr int IMG_Q = 32 * NTILE * (DV / 4), IMG_STEPS = (IMG_Q + NTHR - 1) / NTHR;   // 16-byte pieces: all, per thread
+    auto image_piece = [&](int i) -> float * {   // columns 4 (i % (DV / 4)) .. of row i / (DV / 4)
+        return image + ((i % (DV / 4)) / 8 * 32 * NTILE + i / (DV / 4)) * IMG_LD + 4 * (i % 8);
+    };
+    auto piece_rows = [&](int i) { return canon_rows(i / (DV / 4) >> 5, i / (DV / 4) & 31, packed_state); };
+    auto import_image = [&]() {
+        constexpr int BATCH = 5;
+        for (int s0 = 0; s0 < IMG_STEPS; s0 += BATCH) {
+            f32x4 t[BATCH][2];
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {
+                const int i = min((s0 + j) * NTHR + tid, IMG_Q - 1);
+                const CanonRows cr = piece_rows(i);
+                const float *p = Su + 4 * (i % (DV / 4));
+                t[j][0] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r1, 0) * DV);
+                t[j][1] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r2, 0) * DV);
+            }
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) {
+                const int i = (s0 + j) * NTHR + tid;
+                const float w = piece_rows(i).r1 < 0 ? 0.f : 0.5f;   // (padding rows are zero)
+                if (i < IMG_Q) *reinterpret_cast<f32x4 *>(image_piece(i)) = w == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * w;
+            }
+        }
+    };
+    auto export_image = [&]() {
+#pragma unroll 5
+        for (int st = 0; st < IMG_STEPS; ++st) {
+            const int i = st * NTHR + tid;
+            const CanonRows cr = piece_rows(i);
+            if (i < IMG_Q && cr.r1 >= 0) {
+                const f32x4 t = *reinterpret_cast<const f32x4 *>(image_piece(i));
+                float *p = Su + 4 * (i % (DV / 4));
+                *reinterpret_cast<f32x4 *>(p + (size_t)cr.r1 * DV) = t;
+                if (cr.r2 != cr.r1) *reinterpret_cast<f32x4 *>(p + (size_t)cr.r2 * DV) = t;
+            }
+        }
+    };
+    float *zu = Su ? Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV : nullptr;
+    if (has_init && seg == 0) {
+        import_image();
+        __syncthreads();
+    }
+    // every wave, once it has what it needs of the image
+    auto state_was_read = [&]() {
+        __syncthreads();
+        if (tid == 0) lds.staged = 0u;   // (it lies in the image)
+        if (MODE == 0 && G > 1) {
+            if (tid == 0) __hip_atomic_store(flags_unit + (G - 1), epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    };
+    if (!(has_init && seg == 0) && tid == 0) lds.staged = 0u;   // ordered before its first use by the prologue's barriers
     if (!is_p) {
         // =================================== consumer waves =========================================
         f32x16 S[NTILE];       // the five state tiles of this wave's 32 columns
@@ -391,9 +453,9 @@ __device__ __forceinline__ void prefill_body(
         for (int T = 0; T < NTILE; ++T) zero16(S[T]);
 
         if (MODE == 0) {
-            // start of segment: initial state (entry 0, if any) plus the increments of earlier segments
-            for (int p = has_init ? 0 : 1; p <= seg; ++p) {
-                const float *e = ws_unit + (size_t)p * entry_floats(NC) + lane_off;
+            // start of segment: the increments of earlier segments
+            for (int p = 1; p <= seg; ++p) {
+                const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
                 f32x4 t[24];
                 load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, t);
 #pragma unroll
@@ -402,20 +464,15 @@ __device__ __forceinline__ void prefill_body(
                     for (int r = 0; r < 16; ++r) S[T][r] += t[T * 4 + (r >> 2)][r & 3];
             }
         }
-        if (MODE == 2) {
+        if (has_init && seg == 0) {   // the caller's state
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-                const size_t col = (size_t)32 * c + n;
+            for (int T = 0; T < NTILE; ++T)
 #pragma unroll
-                for (int T = 0; T < NTILE; ++T) {
-                    const CanonRows cr = canon_rows(T, fl, packed_state);
-                    if (cr.r1 >= 0) S[T][r] = 0.5f * (Su[(size_t)cr.r1 * DV + col] + Su[(size_t)cr.r2 * DV + col]);
-                }
-            }
+                for (int r = 0; r < 16; ++r) S[T][r] = image_lane[(32 * T + 8 * (r >> 2) + (r & 3)) * IMG_LD];
+            state_was_read();
         }
 
-        if (MODE != 2) {
+        {
             // V operand of an MFMA (lane (g, n): column 32 c + n at the 8 tokens of its k-slots, two runs of
             // 4 consecutive tokens starting at tok4 and tok4 + 8) from the row-major V rows: the transposing
             // LDS read.  In each group of 16 lanes, lane k supplies the address of 4 consecutive columns
@@ -554,7 +611,7 @@ __device__ __forceinline__ void prefill_body(
 
         // ---- end of segment --------------------------------------------------------------------
         if (MODE != 0) {
-            float *e = ws_unit + (size_t)(MODE == 1 ? 1 + seg : 0) * entry_floats(NC) + lane_off;
+            float *e = ws_unit + (size_t)seg * entry_floats(NC) + lane_off;
 #pragma unroll
             for (int T = 0; T < NTILE; ++T)
 #pragma unroll
@@ -566,18 +623,9 @@ __device__ __forceinline__ void prefill_body(
                 }
         } else if (Su && seg == G - 1) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-                const size_t col = (size_t)32 * c + n;
+            for (int T = 0; T < NTILE; ++T)
 #pragma unroll
-                for (int T = 0; T < NTILE; ++T) {
-                    const CanonRows cr = canon_rows(T, fl, packed_state);
-                    if (cr.r1 >= 0) {
-                        Su[(size_t)cr.r1 * DV + col] = S[T][r];
-                        if (cr.r2 != cr.r1) Su[(size_t)cr.r2 * DV + col] = S[T][r];
-                    }
-                }
-            }
+                for (int r = 0; r < 16; ++r) image_lane[(32 * T + 8 * (r >> 2) + (r & 3)) * IMG_LD] = S[T][r];
         }
     } else {
         // =================================== producer waves =========================================
@@ -585,28 +633,28 @@ __device__ __forceinline__ void prefill_body(
         f32x16 X;                      // producer 0: the moment tile M' = [k, 1]^T [k, 1]
         zero16(X);
         if (MODE == 0 && holds_x) {
-            for (int p = has_init ? 0 : 1; p <= seg; ++p) {
-                const float *e = ws_unit + (size_t)p * entry_floats(NC) + lane_off;
+            for (int p = 1; p <= seg; ++p) {
+                const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
                 f32x4 t[24];
                 load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, t);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) X[r] += t[20 + (r >> 2)][r & 3];
             }
         }
-        if (MODE == 2 && holds_x) {
+        if (has_init && seg == 0 && holds_x) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-                float m = 0.f;   // M'[fl][n]
-                if (fl < DP && n < DP) m = zu[canon_pair(fl, n, packed_state).r1] * 1.41421356237309504880f;
-                else if (fl == DP && n < DP) m = zu[1 + n];
-                else if (fl < DP && n == DP) m = zu[1 + fl];
-                else if (fl == DP && n == DP) m = zu[0];
+                // M'[fl][n] (a place in z for every lane: conditional loads would wait for each other)
+                const bool in = fl <= DP && n <= DP, pair = fl < DP && n < DP;
+                const int at = pair ? canon_pair(fl, n, packed_state).r1 : !in ? 0 : fl < DP ? 1 + fl : n < DP ? 1 + n : 0;
+                const float m = zu[at] * (pair ? 1.41421356237309504880f : in ? 1.f : 0.f);
                 X[r] = m;
             }
         }
+        if (has_init && seg == 0) state_was_read();
 
-        if (MODE != 2) {
+        {
             // once: the zero row of K^T, and the row sums of a block that does not exist (key tile 1
             // against query tile 0)
             // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
@@ -890,7 +938,7 @@ __device__ __forceinline__ void prefill_body(
         // ---- end of segment: the moments ----------------------------------------------------------
         if (holds_x) {
             if (MODE != 0) {
-                float *e = ws_unit + (size_t)(MODE == 1 ? 1 + seg : 0) * entry_floats(NC) + lane_off;
+                float *e = ws_unit + (size_t)seg * entry_floats(NC) + lane_off;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     f32x4 o;
@@ -911,6 +959,10 @@ __device__ __forceinline__ void prefill_body(
                 }
             }
         }
+    }
+    if (MODE == 0 && Su && seg == G - 1) {
+        __syncthreads();
+        export_image();
     }
     if (MODE == 1) {
         // the entry has reached memory (the stores are written through) before the flag is raised
@@ -946,32 +998,24 @@ __global__ __launch_bounds__(64 * (NC + 4), 2) void prefill_mfma_kernel(
     }
 }
 
-// The caller's initial state into entry 0 of every unit.
-template <int NC>
-__global__ __launch_bounds__(64 * (NC + 4), 2) void prefill_mfma_import_kernel(
-    float *__restrict__ state, int has_init, float *__restrict__ ws, int N, SegTable segs, int G)
-{
-    __shared__ __align__(16) Lds<NC> lds;
-    prefill_body<NC, 2>(lds, nullptr, nullptr, nullptr, nullptr, state, has_init, ws, nullptr, nullptr, 0, 0u, N,
-                        segs, G, 0, blockIdx.x);
-}
-
 // ---- host side ----------------------------------------------------------------------------------
 namespace {
 
-// Segments per sequence: enough main-pass workgroups to fill the chip once (one workgroup per CU fits),
-// but segments of at least 512 tokens so that the state increments stay small next to q, k, v, y.
-// More segments than that only add increment work and workspace traffic (360M-shaped prefill, 128 units:
-// 4 segments 72 us, 3 segments 71 us, 2 segments 60.5 us).
+// Segments per sequence.  At most what fills the chip once (one workgroup per CU fits): beyond that more segments only add
+// increment work and workspace traffic (128 units of 2048 tokens, d_v 64: 1 segment 60 us, 2 52, 3 and 4 60).  With few
+// units the chip is not the limit: G segments make a chain of chunks / G increment chunks, G entries to sum up and
+// chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment 28 us, 3
+// 22, 5 19, 8 21; 24 chunks 2 39, 4 27, 8 23, 12 27; 64 chunks 8 35, 12 32, 16 36); below 6 chunks a second segment does
+// not pay for its hand-over (4 chunks: 1 segment 14.0 us, 3 15.1).
 int pick_segments(int U, int N, int dv)
 {
-    const long want = 256;
-    int G = (int)((want + U - 1) / U);
-    const int max_by_len = N / 512;
-    if (G > max_by_len) G = max_by_len;
+    (void)dv;
+    const int chunks = (N + C - 1) / C;
+    int G = 256 / U;
+    const int chain = (int)(sqrtf(2.f * (float)chunks) + 0.5f);
+    if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
-    if (G < 1) G = 1;
-    return G;
+    return G < 1 || chunks < 6 ? 1 : G;
 }
 
 // Segment boundaries.  The main pass starts segment g by summing g workspace entries and the last
@@ -982,6 +1026,16 @@ int make_segments(int N, int G, SegTable &t)
 {
     const int T = (N + C - 1) / C;   // chunks
     if (G > T) G = T;
+    if (G == 2) {
+        // Segment 0's main pass runs beside its increment, and only the other one waits: at three quarters of the tokens
+        // both end together (128 units of 2048 tokens, d_v 64: halves 52 us, 0.66 48.6, 0.75 46.6, 0.8 46.4; d_v 128: 65.5,
+        // 62.5, 61.6).
+        const int first = T < 4 ? 1 : 3 * T / 4;
+        t.begin[0] = 0;
+        t.begin[1] = first * C;
+        for (int g = 2; g <= kMaxSegments; ++g) t.begin[g] = T * C;
+        return T < 2 ? T : 2;
+    }
     int len[kMaxSegments];
     int sum = 0;
     for (int g = 0; g < G; ++g) {
@@ -1002,10 +1056,10 @@ int make_segments(int N, int G, SegTable &t)
     return G;
 }
 
-// Workspace: G entries per unit, then G x G ready-flag words per unit (256-byte aligned).
+// Workspace: G - 1 entries per unit, then G x G ready-flag words per unit (256-byte aligned).
 size_t ws_entry_bytes(int U, int N, int dv)
 {
-    return (size_t)U * pick_segments(U, N, dv) * entry_floats(dv / 32) * sizeof(float);
+    return (size_t)U * (pick_segments(U, N, dv) - 1) * entry_floats(dv / 32) * sizeof(float);
 }
 size_t ws_flag_bytes(int U, int N, int dv)
 {
@@ -1028,12 +1082,6 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     if ((long long)U * (2 * G - 1) >= (1ll << 31)) return hipErrorInvalidValue;
     float *ws = static_cast<float *>(workspace);
     unsigned *flags = reinterpret_cast<unsigned *>((char *)workspace + ws_entry_bytes(U, N, dv));
-    hipError_t e;
-    if (flags_word & 1) {
-        hipLaunchKernelGGL((prefill_mfma_import_kernel<NC>), dim3((unsigned)U), dim3(64 * (NC + 4)), 0, s, state,
-                           flags_word, ws, N, segs, G);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
     // Every call raises its flags to a value no earlier call used: the flag words of a workspace
     // that has never been used hold whatever was in that memory.
     static std::atomic<unsigned> calls{0};

@@ -84,3 +84,24 @@ def test_prefill_decay_edges(based, dtype, dp, dv, N):
     S, z = based.state_export(state, B, H, dp, dv)
     check_close(down(S).reshape(Sw.shape), Sw, 1e-4, "S")
     check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
+
+
+# bf16 d' = 16 prefill: the rule for the number of segments (below and at 6 chunks, few units with many short segments, two
+# uneven segments), the initial state read by two workgroups and overwritten by a third, both state layouts
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N1,N", [(3, 64, 70, 380), (3, 64, 70, 385 + 70), (2, 128, 1, 900), (3, 128, 64, 2300), (120, 64, 65, 450),
+                                       (120, 128, 17, 401)])
+def test_prefill_segments_from_a_state(based, packed, U, dv, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    state = (based.alloc_packed_state if packed else based.alloc_state)(1, U, 16, dv)
+    got = [down(based.prefill(*(up(a[:, lo:hi], "bf16", (1, U, hi - lo, d)) for a, d in ((q, 16), (k, 16), (v, dv))), state=state,
+                              has_init=lo > 0, packed=packed)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N))]
+    at = np.unique(np.r_[0:3, U // 2, U - 1][np.r_[0:3, U // 2, U - 1] < U] if U > 3 else np.arange(U))
+    check_close(rows(np.concatenate(got, 1)[at]), rows(oracle.linattn_quadratic(q[at], k[at], v[at])), TOL["bf16"], "y")
+    if packed:
+        state = based.state_unpack(state, based.alloc_state(1, U, 16, dv), 1, U, 16, dv)
+    S, z = based.state_export(state, 1, U, 16, dv)
+    Sw, zw = oracle.linattn_state(k[at], v[at])
+    check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
+    check_close(down(z)[0, at], zw, TOL["bf16"], "z")
