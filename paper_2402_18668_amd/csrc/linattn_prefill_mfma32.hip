@@ -2,36 +2,52 @@
 // accumulate), d' = 32.
 //
 // Same method as the d' = 16 kernel (chunked form of Sec. 4: masked quadratic product inside a
-// chunk of 64 tokens, running KV-state across chunks, features of Eq. 4 built in registers in
-// MFMA operand layout, k-slots mapped onto the rows a lane holds in its accumulators), laid out
-// for the larger state:
+// chunk, running KV-state across chunks, features of Eq. 4 built in registers in MFMA operand layout, k-slots mapped onto
+// the rows a lane holds in its accumulators), laid out for the larger state:
 //
 // Symmetric packing.  One state row per unordered pair {a, b}: row (a, delta) stands for the
 // pair {a, (a + delta) mod 32}, delta = 0 .. 15 for every a (16 tiles of exactly 32 rows, one
 // delta per tile) and delta = 16 for a < 16.  The k side builds x_a x_b / sqrt(2), the q side
-// sqrt(2) x_a x_b (delta != 0) or x_a^2 / sqrt(2) (delta = 0).  528 pair rows instead of 1024.
+// sqrt(2) x_a x_b (delta != 0) or x_a^2 / sqrt(2) (delta = 0).  528 pair rows instead of 1024.  Two more tiles: E1 = the
+// 32 linear rows, E2 = [1, 0 x 15, the 16 rows of delta = 16].
 //
-// Work split.  One workgroup of four waves per (unit, 32-column slice of d_v, sequence segment);
-// wave w owns the four main tiles delta = 4w .. 4w+3.  Two extra tiles: E1 = the 32 linear rows
-// (wave 2), E2 = [1, 0 x 15, the 16 rows of delta = 16] (wave 0); wave 3 has the K-state.  The
-// three blocks of the intra-chunk product go to waves 0 (keys 0, queries 0), 1 (keys 1, queries 1)
-// and 2 (keys 0, queries 1).  Per chunk each wave produces a partial Y^T over its feature rows for
-// both query tiles; wave 0 finishes query tile 0, wave 1 tile 1.  (Roles are spread so that the
-// waves reach the two barriers of a chunk at about the same time.)
+// Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment); wave w owns the tiles delta = 2 w and
+// 2 w + 1 for both column tiles of 32.  So every feature operand is built once per workgroup and used where it is built: nothing
+// of it passes through LDS, only the rows it is made of do.  The eight partial outputs of a chunk meet in LDS and each
+// wave finishes four tokens.  Waves 0 .. 3 also have E1 / E2 (one column tile of one of them each) and a 16 x 16 block
+// of the K-state, waves 4 .. 7 the intra-chunk block (one half of the keys, one column tile each).
 //
-// Denominator.  Wave 3 carries the K-state as moments: M[a][b] = sum_t k_a k_b (one tile, an MFMA
-// of the K rows with themselves), z1[a] = sum_t k_a (vector adds) and the token count.  Per query
+// Pipeline.  Chunks of 32 tokens, global -> registers (two chunks ahead) -> LDS (two generations).  Two barriers a chunk: rows
+// and partial outputs are there | the previous chunk's partial outputs have been read.
+//
+// Denominator.  The K-state is kept as moments: M[a][b] = sum_t k_a k_b (an MFMA of the K rows with
+// themselves), z1[a] = sum_t k_a (vector adds) and the token count.  Per query
 // phi(q).z = z0 + sum_a q_a (z1[a] + (M q)[a] / 2); the part from inside the chunk is the column
-// sum of the masked block P the intra-chunk waves hold anyway.
+// sum of the masked block P.
 //
-// Long sequences / few units: G segments; a first launch computes each segment's state increment
-// (update GEMMs only), the later launches start each segment from the sum of the entries before it.
+// Long sequences / few units: G segments; a first launch computes each segment's state increment, segment 0's starting from
+// the caller's state, and the main launch starts segment g from the sum of the entries before it (read at full width: all
+// loads of an entry in flight together, the segments of a unit on one XCD).
+//
+// What bounds it: per chunk and SIMD 44 matrix instructions (1400 cycles) and 600 vector instructions (half of them the products,
+// conversions and the state's rounding to bf16), which share the register ports, and 290 KB through LDS, a third of it the
+// partial outputs; 5000 cycles in all, because the eight waves do the same things at the same time.  (Operands built by one wave and shared through
+// LDS: the same time, more LDS.  Four waves with 512 registers and half the exchange: the same, a lone wave issues a
+// vector instruction every 4 cycles instead of 2.  Reading operands' rows a phase ahead: no gain.)
+// Measured (d_v 64; before: four waves per 32 columns, 500 vector instructions per wave and 32 tokens, state buffer accessed
+// element by element): 32 units of 16384 tokens 266 -> 213 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 27 us, from
+// a state 83 -> 40 us.
 #include "common.h"
+
+#include <cmath>
+#include <type_traits>
 
 namespace based {
 
 namespace dp32 {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -43,45 +59,44 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int DP = 32;            // d'
-constexpr int C = 64;             // chunk length (tokens)
-constexpr int NW = 4;             // waves per workgroup
+constexpr int C = 32;             // chunk length (tokens)
+constexpr int NW = 8;             // waves per workgroup
 constexpr int NT = NW * 64;
-constexpr int DVS = 32;           // d_v columns per workgroup
-constexpr int TPW = 4;            // main tiles per wave
+constexpr int PF = 2;             // chunks whose rows are on their way; generations of the rows in LDS
+constexpr int COLS = 64;          // d_v columns per workgroup
+constexpr int TPW = 2;            // main tiles per wave (and column tile)
+constexpr int TILES = 18;         // 16 main tiles, E1, E2
 constexpr float kCK = 0.84089641525371454303f;   // 2^(-1/4): (c k_a)(c k_b) = k_a k_b / sqrt(2)
 constexpr float kCQ = 1.18920711500272106672f;   // 2^(+1/4): (c q_a)(c q_b) = sqrt(2) q_a q_b
 
-// LDS strides (elements)
+// LDS strides (elements).  (64 banks: the 16-byte reads of 16 consecutive rows fall into different ones.)
 constexpr int KTS_LD = C + 4;     // fp32 K^T rows
-constexpr int VR_LD = DVS + 16;   // bf16 V rows (96-byte stride)
+constexpr int VR_LD = COLS + 16;  // bf16 V rows
 constexpr int QS_LD = DP + 4;     // fp32 Q rows
-constexpr int QR_LD = DP + 8;     // bf16 Q rows as given (80-byte stride)
-constexpr int KR_LD = 64 + 16;    // bf16 extended K rows (160-byte stride)
-constexpr int YT_LD = 32 + 8;     // bf16 rows of a finished output tile on its way out
+constexpr int KR_LD = 64 + 8;     // bf16 extended K and Q rows (144-byte stride)
+constexpr int IMG_LD = 40;        // fp32 rows of the state image (the halves of a wave access different banks)
 
-// Workspace entry (one segment's state in accumulator layout): 20 slots of 16 registers x 64 lanes:
-// slot 4w + tt = main tile tt of wave w; 16 = E1; 17 = E2; 18 = M; 19 = [z1, z0] in the first two
-// registers.  Within a slot: [r / 4][lane][r % 4].
-constexpr int WS_SLOTS = 20;
+// Workspace entry (one segment's state in accumulator layout): 40 slots of 16 registers x 64 lanes: column tile c:
+// slots 20 c + 2 w + tt = main tile 2 w + tt, 20 c + 16 = E1, 20 c + 17 = E2; 18 = M; 19 = [z1, z0] in the first two
+// registers.  Within a slot: [reg / 4][lane][reg % 4].
+constexpr int WS_SLOTS = 40;
 constexpr size_t kWsEntryFloats = (size_t)WS_SLOTS * 16 * 64;
 
-struct Stage {
-    float kts[DP][KTS_LD];        // c_k * K^T
-    uint16_t krow[C][KR_LD];      // extended K rows: [k_0..k_31 as given, 1 (0 past the end), 0 x 15,
-                                  // k_a k_(a+16) / sqrt(2) for a < 16]
-    uint16_t vrow[C][VR_LD];      // V rows of the slice, bf16 as given
-    float qs[C][QS_LD];           // c_q * Q
-    uint16_t qrow[C][QR_LD];      // Q rows, bf16 as given
+struct Rows {   // a chunk's rows
+    float kts[DP][KTS_LD];     // c_k * K^T
+    uint16_t krow[C][KR_LD];   // extended K rows: [k_0..k_31 as given, 1, 0 x 15, k_a k_(a+16) / sqrt(2) for a < 16]
+    uint16_t vrow[C][VR_LD];   // V rows of the slice, bf16 as given
+    float qs[C][QS_LD];        // c_q * Q
+    uint16_t qrow[C][KR_LD];   // extended Q rows: [q as given, 1, 0 x 15, sqrt(2) q_a q_(a+16)]
 };
-
 struct Lds {
-    Stage st;
-    float xbuf[2][3][4][64][4];   // partial Y^T tiles: [query tile][sender slot][r / 4][lane][r % 4]
-    float z1s[DP];                // z1, for wave 3's own broadcast reads
-    float dint[2][32];            // denominators: the part from before the chunk, [query tile][query]
-    float dsum[3][32];            // ... and from inside it: column sums of the blocks (k0,q0), (k0,q1), (k1,q1)
-                                  // (written by waves 0, 2, 1)
+    Rows rows[PF];                     // generation: chunk mod 2
+    float xbuf[NW][2 * 4][64][4];      // partial Y^T: [sender][4 column tile + reg / 4][place of the lane][reg % 4]
+    float den[2][C][8];                // denominators: the waves' parts from before the chunk (4) and from inside it (2)
+    float z1s[4][16];                  // a wave's z1, for its own broadcast reads
 };
+static_assert(sizeof(Lds) <= 160 * 1024, "one workgroup per CU");
+static_assert(sizeof(Lds) >= sizeof(float) * 32 * TILES * IMG_LD, "the state image of one column tile fits the LDS");
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
 {
@@ -104,6 +119,11 @@ __device__ __forceinline__ bf16x8 pack8_acc(const f32x16 &acc, int s)   // regis
     return __builtin_convertvector(f, bf16x8);
 }
 
+__device__ __forceinline__ uint32_t pack2(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 w) { return __builtin_bit_cast(bf16x8, w); }
 
 __device__ __forceinline__ void zero16(f32x16 &a)
@@ -124,11 +144,6 @@ __device__ __forceinline__ void role_guard() { asm volatile("; wave-role block: 
 
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
-__device__ __forceinline__ size_t ws_slot_off(int slot, int j, int lane)
-{
-    return (((size_t)slot * 4 + j) * 64 + lane) * 4;
-}
 
 // Canonical state rows (Eq. 4 order) of a packed row; a pair row has two (equal for delta = 0).
 // With packed_state the buffer is the packed layout (one row per unordered pair: a single row).
@@ -153,16 +168,23 @@ __device__ __forceinline__ CanonRows canon_rows_e2(int fl, bool packed_state)
     return {-1, -1};
 }
 
+// row fl of tile T (T < 16: delta = T; 16: E1; 17: E2)
+__device__ __forceinline__ CanonRows canon_rows(int T, int fl, bool packed_state)
+{
+    return T < 16 ? canon_rows_main(T, fl, packed_state) : T == 16 ? canon_rows_e1(fl) : canon_rows_e2(fl, packed_state);
+}
+
 constexpr int kMaxSegments = 16;
 struct SegTable { int begin[kMaxSegments + 1]; };
 
-// MODE 0: full prefill of the segment; MODE 1: state increment only, to workspace entry 1 + seg;
-// MODE 2: the caller's initial state, converted, to entry 0.
-// Slice: columns [32 slice, 32 slice + 32) of v / y.
-template <int MODE>
+// INC: state increment of the segment only, to workspace entry 1 + seg; segment 0 starts from the caller's state, if any,
+// and also leaves that, converted, in entry 0 (import_only: nothing else).  Otherwise the full prefill of the segment.
+// init_in_entry: the caller's state is in entry 0 (one workgroup per unit reads it from the buffer itself).
+// Slice: columns [64 slice, 64 slice + 64) of v / y.
+template <bool INC>
 __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
-    uint16_t *__restrict__ y, float *__restrict__ state, int has_init, float *__restrict__ ws,
+    uint16_t *__restrict__ y, float *state, int has_init, int import_only, int init_in_entry, float *__restrict__ ws,
     int N, int dv, SegTable segs, int G)
 {
     __shared__ __align__(16) Lds lds;
@@ -172,488 +194,575 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const bool packed_state = (has_init & 2) != 0;
     const bool numerator_only = (has_init & 4) != 0;
     has_init &= 1;
-    const int tid = threadIdx.x;
-    const int w = tid >> 6;
-    const int lane = tid & 63;
-    const int g = lane >> 5, n = lane & 31;
+    int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = w & 3;   // waves 0 .. 3: E1 / E2 and the K-state; 4 .. 7: the intra-chunk block
+    const bool low = w < 4;
+    int lane = tid & 63;
+    int g = lane >> 5, n = lane & 31, lq = lane >> 4, ln = lane & 15;
 
-    const int slices = dv / DVS;
-    const int gseg = MODE == 1 ? G - 1 : (MODE == 2 ? 1 : G);
+    const int slices = dv / COLS;
+    const int gseg = !INC ? G : import_only ? 1 : G - 1;
     int bid = blockIdx.x;
-    const int seg = bid % gseg; bid /= gseg;
+    // the segments of a unit on one XCD (workgroup index mod 8), whose L2 then holds its entries
+    const int groups = gridDim.x / gseg;
+    int seg;
+    if (groups % 8 == 0) {
+        seg = (bid >> 3) % gseg;
+        bid = ((bid >> 3) / gseg << 3) + (bid & 7);
+    } else {
+        seg = bid % gseg;
+        bid /= gseg;
+    }
     const int slice = bid % slices;
     const int u = bid / slices;
-    const int col0 = slice * DVS;
+    const int col0 = slice * COLS;
 
     const int tok_begin = segs.begin[seg];
     const int tok_end = min(N, segs.begin[seg + 1]);
+    const int n_chunks = (tok_end - tok_begin + C - 1) / C;
 
     const uint16_t *qu = q + (size_t)u * N * DP;
     const uint16_t *ku = k + (size_t)u * N * DP;
     const uint16_t *vu = v + (size_t)u * N * dv + col0;
     uint16_t *yu = y + (size_t)u * N * dv + col0;
-    float *Su = state ? state + (size_t)u * (packed_state ? packed_state_stride(DP, dv) : state_stride(DP, dv))
+    float *Su = state ? state + (size_t)u * (packed_state ? packed_state_stride(DP, dv) : state_stride(DP, dv)) + col0
                       : nullptr;
-    float *zu = Su ? Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * dv : nullptr;
+    float *zu = Su ? Su - col0 + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * dv : nullptr;
     float *ws_unit = ws + ((size_t)(u * slices + slice) * G) * kWsEntryFloats;
 
     // ---- accumulators -------------------------------------------------------------------------
-    f32x16 S[TPW];         // main tiles delta = 4w + tt
-    f32x16 X;              // wave 0: E2; wave 2: E1; wave 3: M; unused by wave 1
-    float z1 = 0.f, z0 = 0.f;   // wave 3: z1[n] (both halves of the wave), tokens before this call's first
-#pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) zero16(S[tt]);
+    f32x16 S[2][TPW];      // main tiles delta = 2 w + tt, column tile c ^ (r % 2)
+    f32x16 X;              // waves 0 .. 3: column tile r % 2 of E1 (r < 2) or E2
+    f32x4 M;               // M[16 (r / 2) + 4 (lane / 16) + i][16 (r % 2) + lane % 16]
+    float z1 = 0.f, z0 = 0.f;   // z1[16 (r / 2) + lane % 16], tokens before this call's first
+    const int xc = r & 1, xe = r >> 1;
     zero16(X);
-
-    if (MODE == 0) {
-        // start of segment: entry 0 (the initial state, if any) plus the increments before it
-        const int xs = w == 0 ? 17 : (w == 2 ? 16 : 18);
-        for (int p = has_init ? 0 : 1; p <= seg; ++p) {
-            const float *e = ws_unit + (size_t)p * kWsEntryFloats;
+    M = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int tt = 0; tt < TPW; ++tt)
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const f32x4 t = *reinterpret_cast<const f32x4 *>(e + ws_slot_off(4 * w + tt, j, lane));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) S[tt][4 * j + i] += t[i];
-                }
-            if (w != 1) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const f32x4 t = *reinterpret_cast<const f32x4 *>(e + ws_slot_off(xs, j, lane));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) X[4 * j + i] += t[i];
-                }
-            }
-            if (w == 3) {
-                const f32x4 t = *reinterpret_cast<const f32x4 *>(e + ws_slot_off(19, 0, lane));
-                z1 += t[0];
-                z0 += t[1];
-            }
-        }
+        for (int tt = 0; tt < TPW; ++tt) zero16(S[c][tt]);
     }
-    if (MODE == 2) {
-        // canonical rows -> accumulator layout (the symmetric part of a pair's two rows)
-        auto fetch = [&](CanonRows cr) -> float {
-            if (cr.r1 < 0) return 0.f;
-            const size_t col = (size_t)col0 + n;
-            return 0.5f * (Su[(size_t)cr.r1 * dv + col] + Su[(size_t)cr.r2 * dv + col]);
+
+    auto add_entry = [&](int p) {
+        const float *e = ws_unit + (size_t)p * kWsEntryFloats + 4 * lane;
+        f32x4 t[2][TPW][4], tx[4], tm;
+        auto fetch = [&](int slot, f32x4 *x) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const f32x4 *>(e + (slot * 4 + j) * 256);
         };
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) S[tt][r] = fetch(canon_rows_main(4 * w + tt, fl, packed_state));
-            if (w == 2) X[r] = fetch(canon_rows_e1(fl));
-            else if (w == 0) X[r] = fetch(canon_rows_e2(fl, packed_state));
-            else if (w == 3) {   // M[a][b] = sqrt(2) x the symmetric part of z's pair rows, a = fl, b = n
-                const CanonRows cr = canon_pair(fl, n, packed_state);
-                X[r] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
-            }
-        }
-        if (w == 3) { z1 = zu[1 + n]; z0 = zu[0]; }
-    }
-
-    // ---- staging: global -> registers -> LDS ----------------------------------------------------
-    // Thread (s_tok, s_q) stages, of token s_tok: elements 8h .. 8h+7 and 16+8h .. 16+8h+7 (h = s_q % 2)
-    // of the K row (waves 0, 1) or of the Q row (waves 2, 3), and a quarter of the slice's V row.
-    const int s_tok = tid & 63, s_q = tid >> 6, s_h = s_q & 1;
-    u32x4 raw_x[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-    u32x4 raw_v;
-    auto load_raw = [&](int tok0) {
-        const int tok = min(tok0 + s_tok, tok_end - 1);
-        const uint16_t *xc = (s_q < 2 ? ku : qu) + (size_t)tok * DP + 8 * s_h;
-        if (MODE == 0 || s_q < 2) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) raw_x[j] = *reinterpret_cast<const u32x4 *>(xc + 16 * j);
-        }
-        raw_v = *reinterpret_cast<const u32x4 *>(vu + (size_t)tok * dv + 8 * s_q);
-    };
-    auto stage = [&](int tok0) {
-        Stage &st = lds.st;
-        const bool valid = tok0 + s_tok < tok_end;
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
-        if (!valid) { raw_x[0] = zero4; raw_x[1] = zero4; raw_v = zero4; }
-        if (s_q < 2) {
-            float kf[2][8];   // c_k * k: [j][i] = element 16 j + 8 h + i
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t wd = raw_x[j][i];
-                    const int a = 16 * j + 8 * s_h + 2 * i;
-                    kf[j][2 * i] = bf16lo(wd) * kCK;
-                    kf[j][2 * i + 1] = bf16hi(wd) * kCK;
-                    st.kts[a][s_tok] = kf[j][2 * i];
-                    st.kts[a + 1][s_tok] = kf[j][2 * i + 1];
-                }
-                *reinterpret_cast<u32x4 *>(&st.krow[s_tok][16 * j + 8 * s_h]) = raw_x[j];
-            }
-            f32x8 pr;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) pr[i] = kf[0][i] * kf[1][i];
-            *reinterpret_cast<u32x4 *>(&st.krow[s_tok][48 + 8 * s_h]) =
-                __builtin_bit_cast(u32x4, __builtin_convertvector(pr, bf16x8));
-            // columns 32 .. 47: the constant feature, then zeros
-            u32x4 c = zero4;
-            if (s_h == 0 && valid) c[0] = 0x3F80u;
-            if (s_q == s_h) *reinterpret_cast<u32x4 *>(&st.krow[s_tok][32 + 8 * s_h]) = c;
-        } else if (MODE == 0) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    f32x4 qv;
-                    qv[0] = bf16lo(raw_x[j][2 * hh]) * kCQ; qv[1] = bf16hi(raw_x[j][2 * hh]) * kCQ;
-                    qv[2] = bf16lo(raw_x[j][2 * hh + 1]) * kCQ; qv[3] = bf16hi(raw_x[j][2 * hh + 1]) * kCQ;
-                    *reinterpret_cast<f32x4 *>(&st.qs[s_tok][16 * j + 8 * s_h + 4 * hh]) = qv;
-                }
-                *reinterpret_cast<u32x4 *>(&st.qrow[s_tok][16 * j + 8 * s_h]) = raw_x[j];
-            }
-        }
-        *reinterpret_cast<u32x4 *>(&st.vrow[s_tok][8 * s_q]) = raw_v;
-    };
-
-    // V^T operand (lane (g, n): column n at the 8 tokens of its k-slots, two runs of 4 tokens
-    // starting at tok4 and tok4 + 8) from row-major rows, by the transposing LDS read: in each group
-    // of 16 lanes, lane k supplies the address of 4 consecutive columns (4 (k % 4) ..) of row k / 4 of
-    // the group's 16-column block and receives column k of that block at the 4 rows.
-    const int tr_kk = lane & 15, tr_grp = (lane >> 4) & 1;
-    const uint16_t *tr_vbase = &lds.st.vrow[tr_kk >> 2][16 * tr_grp + 4 * (tr_kk & 3)];
-    const uint16_t *tr_kbase = &lds.st.krow[tr_kk >> 2][16 * tr_grp + 4 * (tr_kk & 3)];
-    auto tr_read = [&](const uint16_t *p, int stride, s16x4 &a, s16x4 &b) {
-        a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-        b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 8 * stride));
-    };
-    auto join = [](s16x4 a, s16x4 b) {
-        s16x8 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { o[i] = a[i]; o[4 + i] = b[i]; }
-        return __builtin_bit_cast(bf16x8, o);
-    };
-
-    if (MODE != 2) {
-        load_raw(tok_begin);
-        stage(tok_begin);
-        if (w == 3 && g == 0) lds.z1s[n] = z1;
-    }
-    for (int tok0 = tok_begin; MODE != 2 && tok0 < tok_end; tok0 += C) {
-        const Stage &st = lds.st;
-        wg_sync();   // this chunk's staging is visible
-        const bool more = tok0 + C < tok_end;
-        if (more) load_raw(tok0 + C);   // a whole chunk ahead: consumed by stage() at the bottom
-
-        f32x4 acc[4];     // the output tile this wave finishes (waves 0, 1)
-        float inv = 1.f;
-        if (MODE == 0) {
-            // =============================== readout ============================================
-            f32x16 Yown;
-            zero16(Yown);
-#pragma unroll 1
-            for (int qt = 0; qt < 2; ++qt) {
-                f32x16 Y;
-                zero16(Y);
-                // This lane's query row: qa[4m + i] = c_q q[4g + 8m + i] (m = 0..3: the "a side", k-slot
-                // (s, jj, i) is a = 16 s + 8 jj + 4 g + i = element 4m + i with m = 2s + jj) and
-                // qr[j] = c_q q[(4g + 4w + j) % 32] (the "b side" of delta = 4w + tt is
-                // qr[(16 s + 8 jj + i + tt) % 32]).
-                float qa[16], qr[32];
-                {
-                    const float *row = st.qs[32 * qt + n];
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const f32x4 t = *reinterpret_cast<const f32x4 *>(row + 4 * g + 8 * m);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) qa[4 * m + i] = t[i];
-                    }
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) {
-                        const f32x4 t = *reinterpret_cast<const f32x4 *>(row + ((4 * g + 4 * w + 4 * m) & 31));
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) qr[4 * m + i] = t[i];
-                    }
-                }
-                // inter-chunk: Y^T += S^T phi(Q)^T over this wave's feature rows.  (The empty asm keeps the
-                // bf16 copies of the state from being made once per chunk and held in 32 registers.)
-#pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
-                    asm volatile("" : "+v"(S[tt]));
-                    const float dw = (w == 0 && tt == 0) ? 0.5f : 1.f;   // delta = 0: x_a^2 / sqrt(2)
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        float pr[8];
-#pragma unroll
-                        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                pr[4 * jj + i] = qa[4 * (2 * sl + jj) + i] * dw * qr[(16 * sl + 8 * jj + i + tt) & 31];
-                        Y = mfma(pack8_acc(S[tt], sl), pack8(pr), Y);
-                    }
-                }
-                if (w == 0 || w == 2) {
-                    role_guard();
-                    const bf16x8 xlo = pack8_acc(X, 0), xhi = pack8_acc(X, 1);
-                    if (w == 2) {
-                        role_guard();
-                        // E1: the linear rows; the operand is q itself (k-slot (s, jj, i) = element
-                        // 16 s + 8 jj + 4 g + i)
-                        const uint16_t *p = &st.qrow[32 * qt + n][4 * g];
-#pragma unroll
-                        for (int sl = 0; sl < 2; ++sl) {
-                            const u32x2 a = *reinterpret_cast<const u32x2 *>(p + 16 * sl);
-                            const u32x2 b = *reinterpret_cast<const u32x2 *>(p + 16 * sl + 8);
-                            u32x4 o; o[0] = a[0]; o[1] = a[1]; o[2] = b[0]; o[3] = b[1];
-                            Y = mfma(sl == 0 ? xlo : xhi, as_bf16x8(o), Y);
-                        }
-                    } else {
-                        role_guard();
-                        // E2: row 0 constant (slab 0, k-slot 0 of g = 0); rows 16 + a, a = 8 jj + 4 g + i:
-                        // sqrt(2) q_a q_(a+16)
-                        float c0[8], c1[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) c0[e] = 0.f;
-                        c0[0] = g == 0 ? 1.f : 0.f;
-#pragma unroll
-                        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) c1[4 * jj + i] = qa[4 * jj + i] * qa[4 * (2 + jj) + i];
-                        Y = mfma(xlo, pack8(c0), Y);
-                        Y = mfma(xhi, pack8(c1), Y);
-                    }
-                }
-                if (w == 3) {
-                    role_guard();
-                    // denominator from before the chunk: T[b][query] = sum_a M[a][b] q_a, then
-                    // z0 + sum_b q_b (z1[b] + T[b] / 2) over this lane's 16 rows b and the other half's
-                    f32x16 T;
-                    zero16(T);
-                    const uint16_t *p = &st.qrow[32 * qt + n][4 * g];
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        const u32x2 a = *reinterpret_cast<const u32x2 *>(p + 16 * sl);
-                        const u32x2 b = *reinterpret_cast<const u32x2 *>(p + 16 * sl + 8);
-                        u32x4 o; o[0] = a[0]; o[1] = a[1]; o[2] = b[0]; o[3] = b[1];
-                        T = mfma(pack8_acc(X, sl), as_bf16x8(o), T);
-                    }
-                    float d = 0.f;
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const f32x4 zv = *reinterpret_cast<const f32x4 *>(&lds.z1s[8 * m + 4 * g]);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) d = fmaf(qa[4 * m + i], fmaf(0.5f, T[4 * m + i], zv[i]), d);
-                    }
-                    d *= 1.f / kCQ;
-                    d += __shfl_xor(d, 32, 64);
-                    if (g == 0) lds.dint[qt][n] = z0 + (float)(tok0) + d;
-                }
-                // ---- intra-chunk block: P^T = mask(1 + A^T + A^T^2 / 2), Y^T += V^T P^T ----------
-                // wave 0: key tile 0 against query tile 0; wave 1: keys 1, queries 1; wave 2: keys 0, queries 1
-                if ((w == 0 && qt == 0) || ((w == 1 || w == 2) && qt == 1)) {
-                    role_guard();
-                    const int kt = w == 1 ? 1 : 0;
-                    const bool diag = kt == qt;
-                    f32x16 P;
-                    zero16(P);
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) {   // contraction over d' = 32 in two steps of 16
-                        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&st.krow[32 * kt + n][16 * ks + 8 * g]);
-                        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&st.qrow[32 * qt + n][16 * ks + 8 * g]);
-                        P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float x = P[r];
-                        const float pv = fmaf(x, fmaf(x, 0.5f, 1.f), 1.f);
-                        const int key = 8 * (r >> 2) + 4 * g + (r & 3);
-                        P[r] = (!diag || key <= n) ? pv : 0.f;
-                    }
-                    {   // this block's share of the denominators: sum over its keys
-                        float cs = 0.f;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) cs += P[r];
-                        cs += __shfl_xor(cs, 32, 64);
-                        if (g == 0) lds.dsum[w == 0 ? 0 : (w == 2 ? 1 : 2)][n] = cs;
-                    }
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        s16x4 a, b;
-                        tr_read(tr_vbase + (32 * kt + 16 * sl + 4 * g) * VR_LD, VR_LD, a, b);
-                        Y = mfma(join(a, b), pack8_acc(P, sl), Y);
-                    }
-                }
-                // the partial tile goes to the wave that finishes this query tile
-                if (qt == w) {
-                    Yown = Y;
-                } else {
-                    const int slot = ((w - qt) & 3) - 1;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        f32x4 o;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o[i] = Y[4 * j + i];
-                        *reinterpret_cast<f32x4 *>(&lds.xbuf[qt][slot][j][lane][0]) = o;
-                    }
-                }
-            }
-            wg_sync();
+        auto add = [&](const f32x4 *x, f32x16 &a) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][i] = Yown[4 * j + i];
-            if (w < 2) inv = lds.dint[w][n] + lds.dsum[w][n] + (w == 1 ? lds.dsum[2][n] : 0.f);
-        }
-
-        // =================================== update =============================================
-        {
-            const int arow = n;
-            float z1c = 0.f;   // wave 3: this chunk's share of z1[n] from this half's tokens
+                for (int k = 0; k < 4; ++k) a[4 * j + k] += x[j][k];
+        };
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                const int tcol = 16 * i4 + 4 * g;   // first token of this lane's k-slots
-                s16x4 va, vb;
-                tr_read(tr_vbase + tcol * VR_LD, VR_LD, va, vb);
-                const bf16x8 vk = join(va, vb);
-                const f32x4 ka0 = *reinterpret_cast<const f32x4 *>(&st.kts[arow][tcol]);
-                const f32x4 ka1 = *reinterpret_cast<const f32x4 *>(&st.kts[arow][tcol + 8]);
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
-                    const int brow = (n + 4 * w + tt) & 31;
-                    const f32x4 kb0 = *reinterpret_cast<const f32x4 *>(&st.kts[brow][tcol]);
-                    const f32x4 kb1 = *reinterpret_cast<const f32x4 *>(&st.kts[brow][tcol + 8]);
-                    float pr[8];
+            for (int tt = 0; tt < TPW; ++tt) fetch(20 * (c ^ xc) + 2 * w + tt, t[c][tt]);
+        const f32x4 tz = *reinterpret_cast<const f32x4 *>(e + (19 * 4 + r) * 256);
+        fetch(20 * xc + 16 + xe, tx);   // (waves 4 .. 7 do not use theirs)
+        tm = *reinterpret_cast<const f32x4 *>(e + (18 * 4 + r) * 256);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) { pr[i] = ka0[i] * kb0[i]; pr[4 + i] = ka1[i] * kb1[i]; }
-                    S[tt] = mfma(pack8(pr), vk, S[tt]);
-                }
-                if (w == 0 || w == 2) {
-                    role_guard();
-                    s16x4 ea, eb;
-                    tr_read(tr_kbase + tcol * KR_LD + (w == 0 ? 32 : 0), KR_LD, ea, eb);
-                    X = mfma(join(ea, eb), vk, X);
-                }
-                if (w == 3) {
-                    role_guard();
-                    // the K rows against themselves: lane (g, n) holds k_n at its 8 tokens, which is both
-                    // the row n of K^T and the column n of K
-                    s16x4 ea, eb;
-                    tr_read(tr_kbase + tcol * KR_LD, KR_LD, ea, eb);
-                    const bf16x8 ek = join(ea, eb);
-                    X = mfma(ek, ek, X);
-                    const u32x4 kw = __builtin_bit_cast(u32x4, ek);
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) z1c += bf16lo(kw[i]) + bf16hi(kw[i]);
-                }
-                if (MODE == 0 && w < 2) {
-                    // collect a quarter of the other waves' partial tiles under this step's MFMAs
-#pragma unroll
-                    for (int sl = 0; sl < 3; ++sl) {
-                        const f32x4 o = *reinterpret_cast<const f32x4 *>(&lds.xbuf[w][sl][i4][lane][0]);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[i4][i] += o[i];
-                    }
-                }
-            }
-            if (w == 3) {
-                z1 += z1c + __shfl_xor(z1c, 32, 64);
-                if (g == 0) lds.z1s[n] = z1;
-            }
-        }
-        if (MODE == 0 && w < 2) {
-            const int qt = w;
-            {
-                // normalise and turn the tile through LDS (this wave's own exchange slots, which it has
-                // finished reading): the tile leaves as 64-byte row segments, 16 rows a store
-                const float rinv = numerator_only ? 1.f : 1.f / inv;
-                uint16_t *yt = reinterpret_cast<uint16_t *>(&lds.xbuf[w][0][0][0][0]);   // [32][YT_LD] bf16
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[j][i] *= rinv;
-                    const bf16x4 hv = __builtin_convertvector(acc[j], bf16x4);
-                    *reinterpret_cast<u32x2 *>(yt + n * YT_LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                uint16_t *yc = yu + (size_t)tok0 * dv;
-                u32x4 val[2];
-                uint32_t yoff[2];
-#pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const int row = 16 * it + (lane >> 2), c = lane & 3;
-                    val[it] = *reinterpret_cast<const u32x4 *>(yt + row * YT_LD + 8 * c);
-                    yoff[it] = (uint32_t)(32 * qt + row) * (uint32_t)dv + (uint32_t)(8 * c);
-                }
-                if (tok0 + C <= tok_end) {
-#pragma unroll
-                    for (int it = 0; it < 2; ++it) *reinterpret_cast<u32x4 *>(yc + yoff[it]) = val[it];
-                } else {
-#pragma unroll
-                    for (int it = 0; it < 2; ++it)
-                        if (tok0 + 32 * qt + 16 * it + (lane >> 2) < tok_end) *reinterpret_cast<u32x4 *>(yc + yoff[it]) = val[it];
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                }
-            }
-        }
-        if (more) {
-            wg_sync();   // every wave is done reading this chunk's staging
-            stage(tok0 + C);
-        }
-    }
-
-    // ---- end of segment -----------------------------------------------------------------------
-    if (MODE != 0) {
-        float *e = ws_unit + (size_t)(MODE == 1 ? 1 + seg : 0) * kWsEntryFloats;
+            for (int tt = 0; tt < TPW; ++tt) add(t[c][tt], S[c][tt]);
+        add(tx, X);
+        M += tm;
+        z1 += tz[0];
+        z0 += tz[1];
+    };
+    auto put_entry = [&](int p) {
+        float *e = ws_unit + (size_t)p * kWsEntryFloats;
         auto put = [&](int slot, const f32x16 &a) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 f32x4 o;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[i] = a[4 * j + i];
-                *reinterpret_cast<f32x4 *>(e + ws_slot_off(slot, j, lane)) = o;
+                *reinterpret_cast<f32x4 *>(e + (slot * 4 + j) * 256 + 4 * lane) = o;
             }
         };
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) put(4 * w + tt, S[tt]);
-        if (w == 0) put(17, X);
-        if (w == 2) put(16, X);
-        if (w == 3) {
-            put(18, X);
-            const f32x4 o = {z1, MODE == 2 ? z0 : 0.f, 0.f, 0.f};
-            *reinterpret_cast<f32x4 *>(e + ws_slot_off(19, 0, lane)) = o;
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt) put(20 * (c ^ xc) + 2 * w + tt, S[c][tt]);
         }
-    } else if (Su && seg == G - 1) {
-        // final state in the canonical layout (both rows of a pair); slice 0 writes z
-        auto emit = [&](CanonRows cr, float val) {
-            if (cr.r1 < 0) return;
-            const size_t col = (size_t)col0 + n;
-            Su[(size_t)cr.r1 * dv + col] = val;
-            if (cr.r2 != cr.r1) Su[(size_t)cr.r2 * dv + col] = val;
+        if (!low) return;
+        put(20 * xc + 16 + xe, X);
+        *reinterpret_cast<f32x4 *>(e + (18 * 4 + r) * 256 + 4 * lane) = M;
+        *reinterpret_cast<f32x4 *>(e + (19 * 4 + r) * 256 + 4 * lane) = f32x4{z1, z0, 0.f, 0.f};
+    };
+
+    // The state buffer moves through LDS, one column tile at a time, as an image of its tiles: image[32 T + row][IMG_LD].
+    // A wave reaches its registers' places at constant offsets, and the whole workgroup moves 16-byte pieces between the
+    // image and the buffer's rows.
+    float *image = reinterpret_cast<float *>(&lds);
+    constexpr int IMG_Q = 32 * TILES * 8, IMG_STEPS = IMG_Q / NT;   // 16-byte pieces of a column tile: all, per thread
+    static_assert(IMG_Q % NT == 0, "");
+    auto import_state = [&]() {
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+            constexpr int BATCH = 3;
+#pragma unroll 1
+            for (int s0 = 0; s0 < IMG_STEPS; s0 += BATCH) {
+                f32x4 t[BATCH][2];
+#pragma unroll
+                for (int j = 0; j < BATCH; ++j) {
+                    const int i = (s0 + j) * NT + tid, row = i >> 3;
+                    const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
+                    const float *p = Su + 32 * cc + 4 * (i & 7);
+                    t[j][0] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r1, 0) * dv);
+                    t[j][1] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r2, 0) * dv);
+                }
+#pragma unroll
+                for (int j = 0; j < BATCH; ++j) {
+                    const int i = (s0 + j) * NT + tid, row = i >> 3;
+                    const bool zero = canon_rows(row >> 5, row & 31, packed_state).r1 < 0;   // (padding)
+                    *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
+                        zero ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * 0.5f;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                const int fl = 8 * (rr >> 2) + (rr & 3);
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) {
+                    const float t = image[4 * g * IMG_LD + n + (32 * (2 * w + tt) + fl) * IMG_LD];
+                    S[0][tt][rr] = cc == xc ? t : S[0][tt][rr];
+                    S[1][tt][rr] = cc == xc ? S[1][tt][rr] : t;
+                }
+                if (low && cc == xc) X[rr] = image[4 * g * IMG_LD + n + (32 * (16 + xe) + fl) * IMG_LD];
+            }
+            __syncthreads();
+        }
+        // M[a][b] = sqrt(2) x the symmetric part of z's pair rows
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const CanonRows cr = canon_pair(16 * xe + 4 * lq + i, 16 * xc + ln, packed_state);
+            M[i] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+        }
+        z1 = zu[1 + 16 * xe + ln];
+        z0 = zu[0];
+    };
+    auto export_state = [&]() {   // (both rows of a pair; slice 0 writes z)
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+            __syncthreads();
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                const int fl = 8 * (rr >> 2) + (rr & 3);
+#pragma unroll
+                for (int tt = 0; tt < TPW; ++tt) {
+                    const float t0 = S[0][tt][rr], t1 = S[1][tt][rr];
+                    image[4 * g * IMG_LD + n + (32 * (2 * w + tt) + fl) * IMG_LD] = cc == xc ? t0 : t1;
+                }
+                if (low && cc == xc) image[4 * g * IMG_LD + n + (32 * (16 + xe) + fl) * IMG_LD] = X[rr];
+            }
+            __syncthreads();
+#pragma unroll 3
+            for (int st = 0; st < IMG_STEPS; ++st) {
+                const int i = st * NT + tid, row = i >> 3;
+                const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
+                if (cr.r1 >= 0) {
+                    const f32x4 t = *reinterpret_cast<const f32x4 *>(image + row * IMG_LD + 4 * (i & 7));
+                    float *p = Su + 32 * cc + 4 * (i & 7);
+                    *reinterpret_cast<f32x4 *>(p + (size_t)cr.r1 * dv) = t;
+                    if (cr.r2 != cr.r1) *reinterpret_cast<f32x4 *>(p + (size_t)cr.r2 * dv) = t;
+                }
+            }
+        }
+        if (slice == 0 && low) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int a = 16 * xe + 4 * lq + i, b = 16 * xc + ln;
+                if (!packed_state || a <= b) zu[canon_pair(a, b, packed_state).r1] = kRsqrt2 * M[i];
+            }
+            if (xc == 0 && lq == 0) {
+                zu[1 + 16 * xe + ln] = z1;
+                if (r == 0 && ln == 0) zu[0] = z0 + (float)N;
+            }
+        }
+    };
+
+    if (INC) {
+        if (has_init && seg == 0) {
+            import_state();
+            put_entry(0);
+            if (import_only) return;   // uniform
+        }
+    } else if (seg > 0) {
+#pragma unroll 1
+        for (int p = 1; p <= seg; ++p) add_entry(p);
+    } else if (has_init) {
+        if (init_in_entry) add_entry(0);
+        else import_state();
+    }
+
+    // What is computed from the lane's place before the loop is not kept through it, and the other way round.
+    auto fresh_lane = [&]() {
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        g = lane >> 5; n = lane & 31; lq = lane >> 4; ln = lane & 15;
+    };
+    fresh_lane();
+
+    // ---- staging: global -> registers -> LDS ----------------------------------------------------
+    // A thread moves elements 2 j, 2 j + 1 of the K and Q rows of a token and 4 columns of its V row (j = tid % 16).  Loads are
+    // unconditional (rows past the end re-read the last one, and are zeroed when staged), so that the number in flight is known.
+    const int s_tok = tid >> 4, s_j = tid & 15;
+    struct Raw { uint32_t k, q; u32x2 v; } raw[PF];   // chunk mod PF
+    auto load_raw = [&](int tok0, Raw &x) {
+        const int tok = min(tok0 + s_tok, tok_end - 1);
+        x.k = *reinterpret_cast<const uint32_t *>(ku + (size_t)tok * DP + 2 * s_j);
+        if (!INC) x.q = *reinterpret_cast<const uint32_t *>(qu + (size_t)tok * DP + 2 * s_j);
+        x.v = *reinterpret_cast<const u32x2 *>(vu + (size_t)tok * dv + 4 * s_j);
+    };
+    auto stage = [&](int tok0, const Raw &x, Rows &rows) {
+        const bool past = tok0 + s_tok >= tok_end;
+        const uint32_t kraw = past ? 0u : x.k;
+        const u32x2 vraw = {past ? 0u : x.v[0], past ? 0u : x.v[1]};
+        // product of the elements a and a + 16, which is eight lanes to the right (row_shl:8)
+        auto pair = [&](float a) {
+            return a * __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(a), 0x108, 0xf, 0xf, false));
         };
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) emit(canon_rows_main(4 * w + tt, fl, packed_state), S[tt][r]);
-            if (w == 2) emit(canon_rows_e1(fl), X[r]);
-            else if (w == 0) emit(canon_rows_e2(fl, packed_state), X[r]);
-            else if (w == 3 && slice == 0 && (!packed_state || fl <= n))
-                zu[canon_pair(fl, n, packed_state).r1] = kRsqrt2 * X[r];
+        const float k0 = bf16lo(kraw) * kCK, k1 = bf16hi(kraw) * kCK;
+        rows.kts[2 * s_j][s_tok] = k0;
+        rows.kts[2 * s_j + 1][s_tok] = k1;
+        *reinterpret_cast<uint32_t *>(&rows.krow[s_tok][2 * s_j]) = kraw;
+        const uint32_t kp = pack2(pair(k0), pair(k1));
+        uint32_t qp = 0;
+        if (!INC) {
+            const float q0 = bf16lo(x.q) * kCQ, q1 = bf16hi(x.q) * kCQ;
+            *reinterpret_cast<f32x2 *>(&rows.qs[s_tok][2 * s_j]) = f32x2{q0, q1};
+            *reinterpret_cast<uint32_t *>(&rows.qrow[s_tok][2 * s_j]) = x.q;
+            qp = pack2(pair(q0), pair(q1));
         }
-        if (w == 3 && slice == 0 && g == 0) {
-            zu[1 + n] = z1;
-            if (n == 0) zu[0] = z0 + (float)N;
+        *reinterpret_cast<u32x2 *>(&rows.vrow[s_tok][4 * s_j]) = vraw;
+        if (s_j < 8) {
+            *reinterpret_cast<uint32_t *>(&rows.krow[s_tok][48 + 2 * s_j]) = kp;
+            if (!INC) *reinterpret_cast<uint32_t *>(&rows.qrow[s_tok][48 + 2 * s_j]) = qp;
         }
+    };
+
+    // ---- operands ---------------------------------------------------------------------------------
+    // phi(Q)^T operand of slab sl of tile tt: k-slot (jj, i) is row a = 16 sl + 8 jj + 4 g + i, the pair (a, (a + delta) mod 32)
+    struct QSrc { float a[8], b[2][6]; };
+    auto q_source = [&](const Rows &rows, int sl) {
+        const float *row = rows.qs[n];
+        QSrc o;
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+            const int base = 16 * sl + 8 * jj + 4 * g;
+            const f32x4 t = *reinterpret_cast<const f32x4 *>(row + base);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o.a[4 * jj + i] = t[i];
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                const f32x2 b = *reinterpret_cast<const f32x2 *>(row + ((base + 2 * w + 2 * h) & 31));
+                o.b[jj][2 * h] = b[0];
+                o.b[jj][2 * h + 1] = b[1];
+            }
+        }
+        return o;
+    };
+    const float dw = w == 0 ? 0.5f : 1.f;   // delta = 0: x_a^2 / sqrt(2)
+    auto q_op = [&](const QSrc &s, int tt) {
+        float pr[8];
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                pr[4 * jj + i] = (tt == 0 ? s.a[4 * jj + i] * dw : s.a[4 * jj + i]) * s.b[jj][i + tt];
+        return pack8(pr);
+    };
+    // phi(K)^T operand of token slab ts of tile tt: row n, k-slots the tokens 16 ts + 4 g + {0..3, 8..11}
+    struct KSrc { f32x4 a[2], b[TPW][2]; };
+    auto k_source = [&](const Rows &rows, int ts) {
+        const int tcol = 16 * ts + 4 * g;
+        KSrc o;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) o.a[h] = *reinterpret_cast<const f32x4 *>(&rows.kts[n][tcol + 8 * h]);
+#pragma unroll
+        for (int tt = 0; tt < TPW; ++tt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                o.b[tt][h] = *reinterpret_cast<const f32x4 *>(&rows.kts[(n + 2 * w + tt) & 31][tcol + 8 * h]);
+        return o;
+    };
+    auto k_op = [&](const KSrc &s, int tt) {
+        float pr[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { pr[i] = s.a[0][i] * s.b[tt][0][i]; pr[4 + i] = s.a[1][i] * s.b[tt][1][i]; }
+        return pack8(pr);
+    };
+    // V^T operand (lane (g, n): column n of the tile at the 8 tokens of its k-slots, two runs of 4 tokens
+    // starting at tok4 and tok4 + 8) from row-major rows, by the transposing LDS read: in each group
+    // of 16 lanes, lane k supplies the address of 4 consecutive columns (4 (k % 4) ..) of row k / 4 of
+    // the group's 16-column block and receives column k of that block at the 4 rows.
+    const int tr_row = ((lane & 15) >> 2) + 4 * g, tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    auto tr_read = [&](const uint16_t *p, int stride) {
+        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+        const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 8 * stride));
+        s16x8 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { o[i] = a[i]; o[4 + i] = b[i]; }
+        return __builtin_bit_cast(bf16x8, o);
+    };
+    auto read_v = [&](const Rows &rows, int ts, int c) { return tr_read(&rows.vrow[16 * ts + tr_row][32 * c + tr_col], VR_LD); };
+    auto read_k = [&](const Rows &rows, int ts, int col) { return tr_read(&rows.krow[16 * ts + tr_row][col + tr_col], KR_LD); };
+    // 16 columns of K at all 32 tokens (operand of the 16 x 16 x 32 product)
+    auto read_k16 = [&](const Rows &rows, int col) {
+        const uint16_t *p = &rows.krow[(ln >> 2) + 4 * lq][col + 4 * (lane & 3)];
+        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+        const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 16 * KR_LD));
+        s16x8 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { o[i] = a[i]; o[4 + i] = b[i]; }
+        return __builtin_bit_cast(bf16x8, o);
+    };
+    // sums over the wave's halves / over the two rows of 16 lanes of each half
+    auto add_halves = [&](float a, float b) {   // lanes < 32: a, lanes >= 32: b
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    };
+    auto add_rows = [&](float a) {
+        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+        return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    };
+
+    struct VSrc { bf16x8 v[2]; };
+    auto v_source = [&](const Rows &rows, int ts) {
+        VSrc o;
+        o.v[0] = read_v(rows, ts, xc);
+        o.v[1] = read_v(rows, ts, xc ^ 1);
+        return o;
+    };
+    // S += phi(K)^T V over this wave's tiles
+    auto update_slab = [&](const KSrc &src, const VSrc &vs) {
+#pragma unroll
+        for (int tt = 0; tt < TPW; ++tt) {
+            const bf16x8 op = k_op(src, tt);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) S[c][tt] = mfma(op, vs.v[c], S[c][tt]);
+        }
+    };
+    // waves 0 .. 3: E1 / E2, M += K^T K, z1 += sum of the rows
+    auto update_e = [&](const Rows &rows, const VSrc &v0, const VSrc &v1) {
+        const bf16x8 e0 = read_k(rows, 0, 32 * xe), e1 = read_k(rows, 1, 32 * xe);
+        const bf16x8 ea = read_k16(rows, 16 * xe), eb = read_k16(rows, 16 * xc);
+        X = mfma(e0, v0.v[0], X);
+        X = mfma(e1, v1.v[0], X);
+        M = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ea, eb, M, 0, 0, 0);
+        const u32x4 kw = __builtin_bit_cast(u32x4, ea);
+        float z1c = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z1c += bf16lo(kw[i]) + bf16hi(kw[i]);
+        z1c = add_halves(z1c, z1c);
+        z1 += add_rows(z1c);
+        if (!INC) lds.z1s[r][ln] = xe == xc ? z1 : 0.f;
+    };
+
+    // columns 32 .. 47 of the K and Q rows: the constant feature (past the end its V row is zero), then zeros
+    if (s_j < 8)
+#pragma unroll
+        for (int gen = 0; gen < 2; ++gen) {
+            const uint32_t t = s_j == 0 ? 0x3F80u : 0u;
+            *reinterpret_cast<uint32_t *>(&lds.rows[gen].krow[s_tok][32 + 2 * s_j]) = t;
+            if (!INC) *reinterpret_cast<uint32_t *>(&lds.rows[gen].qrow[s_tok][32 + 2 * s_j]) = t;
+        }
+#pragma unroll
+    for (int i = 0; i < PF; ++i) load_raw(tok_begin + C * i, raw[i]);
+    stage(tok_begin, raw[0], lds.rows[0]);
+    load_raw(tok_begin + C * PF, raw[0]);
+    // chunk t: f(t mod PF, first token)
+    auto for_chunks = [&](auto &&f) {
+        for (int t = 0; t < n_chunks; t += PF) {
+            const int tok0 = tok_begin + C * t;
+            f(std::integral_constant<int, 0>{}, tok0);
+            if (t + 1 >= n_chunks) break;
+            f(std::integral_constant<int, 1>{}, tok0 + C);
+        }
+    };
+
+    if (INC) {
+        wg_sync();
+        for_chunks([&](auto gen, int tok0) {
+            constexpr int p = decltype(gen)::value, p1 = (p + 1) % PF;
+            const Rows &rows = lds.rows[p];
+            const KSrc k0 = k_source(rows, 0);
+            const VSrc v0 = v_source(rows, 0);
+            __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
+            const KSrc k1 = k_source(rows, 1);
+            const VSrc v1 = v_source(rows, 1);
+            __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
+            update_slab(k0, v0);
+            stage(tok0 + C, raw[p1], lds.rows[p1]);
+            load_raw(tok0 + (PF + 1) * C, raw[p1]);
+            update_slab(k1, v1);
+            if (low) {
+                role_guard();
+                update_e(rows, v0, v1);
+            }
+            wg_sync();
+        });
+        put_entry(1 + seg);
+        return;
+    }
+
+    // ---- full pass ----------------------------------------------------------------------------------
+    // A chunk's outputs: lane (tk, cq) finishes columns 4 cq .. of token 4 w + tk; the partial sums are read across (the sender's
+    // lane l puts its four of column group cj at place l ^ (cj + 8 (l / 32)): 16 consecutive lanes in different banks).
+    const int o_tok = 4 * w + (lane >> 4), o_cq = lane & 15;
+    const int o_place = (32 * (o_cq & 1) + o_tok) ^ ((o_cq >> 1) + 8 * (o_cq & 1));
+    struct Out { f32x4 d4, d2, part[NW]; };
+    auto out_source = [&](int g2) {
+        Out o;
+        o.d4 = *reinterpret_cast<const f32x4 *>(&lds.den[g2][o_tok][0]);
+        o.d2 = *reinterpret_cast<const f32x4 *>(&lds.den[g2][o_tok][4]);
+#pragma unroll
+        for (int sl = 0; sl < NW; ++sl) o.part[sl] = *reinterpret_cast<const f32x4 *>(&lds.xbuf[sl][o_cq >> 1][o_place][0]);
+        return o;
+    };
+    auto output = [&](const Out &x, int tok0) {
+        const float den = z0 + (float)tok0 + ((x.d4[0] + x.d4[1]) + (x.d4[2] + x.d4[3])) + (x.d2[0] + x.d2[1]);
+        const float inv = numerator_only ? 1.f : 1.f / den;
+        const f32x4 sum = ((x.part[0] + x.part[1]) + (x.part[2] + x.part[3])) + ((x.part[4] + x.part[5]) + (x.part[6] + x.part[7]));
+        if (tok0 >= tok_begin && tok0 + o_tok < tok_end)
+            *reinterpret_cast<u32x2 *>(yu + (ptrdiff_t)(tok0 + o_tok) * dv + 4 * o_cq) =
+                __builtin_bit_cast(u32x2, __builtin_convertvector(sum * inv, bf16x4));
+    };
+    if (low) lds.z1s[r][ln] = xe == xc ? z1 : 0.f;
+    wg_sync();
+    for_chunks([&](auto gen, int tok0) {
+        constexpr int p = decltype(gen)::value, p1 = (p + 1) % PF;
+        const Rows &rows = lds.rows[p];
+        // the previous chunk's partial outputs, the queries
+        const Out prev = out_source(p1);
+        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
+        output(prev, tok0 - C);
+        __builtin_amdgcn_sched_barrier(0);
+        const QSrc q0 = q_source(rows, 0);
+        const QSrc q1 = q_source(rows, 1);
+        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
+        f32x16 Y[2];
+        zero16(Y[0]);
+        zero16(Y[1]);
+        auto readout = [&](const QSrc &src, int sl) {
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt) {
+                const bf16x8 op = q_op(src, tt);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) Y[c] = mfma(pack8_acc(S[c][tt], sl), op, Y[c]);
+            }
+        };
+        readout(q0, 0);
+        readout(q1, 1);
+        if (low) {
+            role_guard();
+            // E1 / E2 for column tile xc
+            u32x2 qx[2][2], qa[2];
+            f32x4 qb[2];
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    qx[sl][h] = *reinterpret_cast<const u32x2 *>(&rows.qrow[n][32 * xe + 4 * g + 16 * sl + 8 * h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                qa[h] = *reinterpret_cast<const u32x2 *>(&rows.qrow[16 * h + ln][16 * xe + 4 * lq]);
+                qb[h] = *reinterpret_cast<const f32x4 *>(&rows.qs[16 * h + ln][16 * xc + 4 * lq]);
+            }
+            const f32x4 zv = *reinterpret_cast<const f32x4 *>(&lds.z1s[r][4 * lq]);
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl)
+                Y[0] = mfma(pack8_acc(X, sl), as_bf16x8(u32x4{qx[sl][0][0], qx[sl][0][1], qx[sl][1][0], qx[sl][1][1]}), Y[0]);
+            // denominator from before the chunk: T[b][query] = sum_a M[a][b] q_a over this wave's a and b, then
+            // sum_b q_b (z1[b] + T[b] / 2)
+            const s16x4 m4 = __builtin_bit_cast(s16x4, __builtin_convertvector(M, bf16x4));
+            float d[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 T = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(m4, __builtin_bit_cast(s16x4, qa[h]), f32x4{0.f, 0.f, 0.f, 0.f},
+                                                                         0, 0, 0);
+                d[h] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[h] = fmaf(qb[h][i], fmaf(0.5f, T[i], zv[i]), d[h]);
+            }
+            lds.den[p][16 * g + ln][r] = add_rows(add_halves(d[0], d[1])) * (1.f / kCQ);
+        } else {
+            role_guard();
+            // intra-chunk block, keys 16 xe .. + 15 and column tile xc: P^T = mask(1 + A^T + A^T^2 / 2), Y^T += V^T P^T
+            f32x16 P;
+            zero16(P);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {   // contraction over d' = 32 in two steps; rows 0 .. 15 of P are used
+                const u32x4 kop = *reinterpret_cast<const u32x4 *>(&rows.krow[(n + 16 * xe) & 31][16 * ks + 8 * g]);
+                const u32x4 qop = *reinterpret_cast<const u32x4 *>(&rows.qrow[n][16 * ks + 8 * g]);
+                P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
+            }
+            const bf16x8 vp = read_v(rows, xe, xc);
+            float cs = 0.f;
+#pragma unroll
+            for (int rr = 0; rr < 8; ++rr) {
+                const float x = P[rr];
+                const float pv = fmaf(x, fmaf(x, 0.5f, 1.f), 1.f);
+                P[rr] = 8 * (rr >> 2) + (rr & 3) <= n - 16 * xe - 4 * g ? pv : 0.f;
+                cs += P[rr];
+            }
+            lds.den[p][n][4 + xe] = add_halves(cs, cs);
+            Y[0] = mfma(vp, pack8_acc(P, 0), Y[0]);
+        }
+        wg_sync();   // every wave has the previous chunk's partial outputs
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                f32x4 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = Y[c][4 * j + i];
+                const int cj = 4 * (c ^ xc) + j;
+                *reinterpret_cast<f32x4 *>(&lds.xbuf[w][cj][lane ^ (cj + 8 * g)][0]) = o;
+            }
+        const KSrc k0 = k_source(rows, 0);
+        const VSrc v0 = v_source(rows, 0);
+        const KSrc k1 = k_source(rows, 1);
+        const VSrc v1 = v_source(rows, 1);
+        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
+        update_slab(k0, v0);
+        stage(tok0 + C, raw[p1], lds.rows[p1]);
+        load_raw(tok0 + (PF + 1) * C, raw[p1]);
+        update_slab(k1, v1);
+        if (low) {
+            role_guard();
+            update_e(rows, v0, v1);
+        }
+        wg_sync();
+    });
+    {
+        const int last = n_chunks - 1;
+        output(last & 1 ? out_source(1) : out_source(0), tok_begin + C * last);
+    }
+    if (Su && seg == G - 1) {
+        fresh_lane();
+        export_state();
     }
 }
 
-// Segments: enough workgroups for two per CU, segments of at least 512 tokens.
+// Segments: at most one round of the chip (one workgroup per CU).  With few units the chain of an increment, up to G - 1 entries
+// to sum and the main pass is shortest near sqrt(1.5 chunks) segments (16 units, N 2048: 4 segments 61 us, 8 47, 10 45, 16 50; N 777:
+// 1 59, 3 38, 6 32, 12 36); from 8 chunks on it is shorter than one segment.
 static int pick_segments(int U, int N, int dv)
 {
-    const long groups = (long)U * (dv / DVS);
-    int G = (int)((512 + groups - 1) / groups);
-    if (G > N / 512) G = N / 512;
+    const int groups = U * (dv / COLS), chunks = (N + C - 1) / C;
+    int G = 256 / groups;
+    const int chain = (int)(sqrtf(1.5f * chunks) + 0.5f);
+    if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
-    return G < 1 ? 1 : G;
+    return G < 1 || chunks < 8 ? 1 : G;
 }
 
 static int make_segments(int N, int G, SegTable &t)
@@ -671,7 +780,7 @@ static int make_segments(int N, int G, SegTable &t)
 
 static size_t entry_bytes(int U, int N, int dv)
 {
-    return (size_t)U * (dv / DVS) * pick_segments(U, N, dv) * kWsEntryFloats * sizeof(float);
+    return (size_t)U * (dv / COLS) * pick_segments(U, N, dv) * kWsEntryFloats * sizeof(float);
 }
 
 }  // namespace dp32
@@ -696,24 +805,23 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
     has_init = (has_init & 1) | (packed_state ? 2 : 0) | (has_init & 4);
     using namespace dp32;
     (void)dp;
-    const int slices = dv / DVS;
+    const int slices = dv / COLS;
     SegTable segs;
     const int G = make_segments(N, pick_segments(U, N, dv), segs);
     const uint16_t *q16 = (const uint16_t *)q, *k16 = (const uint16_t *)k, *v16 = (const uint16_t *)v;
     float *ws = static_cast<float *>(workspace);
-    hipError_t e;
-    if (has_init & 1) {
-        hipLaunchKernelGGL((prefill_kernel<2>), dim3((unsigned)(U * slices)), dim3(NT), 0, s, q16, k16, v16,
-                           (uint16_t *)y, state, has_init, ws, N, dv, segs, G);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((long long)U * slices * G >= (1ll << 31)) return hipErrorInvalidValue;
+    // Several workgroups of a unit read the caller's state and one overwrites it (at d_v = 128 also its K-state): then it goes
+    // through entry 0, which the first launch writes.
+    const int in_entry = (has_init & 1) && G * slices > 1;
+    if (G > 1 || in_entry) {
+        hipLaunchKernelGGL((prefill_kernel<true>), dim3((unsigned)(U * slices * (G > 1 ? G - 1 : 1))), dim3(NT), 0, s, q16, k16,
+                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    if (G > 1) {
-        hipLaunchKernelGGL((prefill_kernel<1>), dim3((unsigned)(U * slices * (G - 1))), dim3(NT), 0, s, q16, k16,
-                           v16, (uint16_t *)y, state, has_init, ws, N, dv, segs, G);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((prefill_kernel<0>), dim3((unsigned)(U * slices * G)), dim3(NT), 0, s, q16, k16, v16,
-                       (uint16_t *)y, state, has_init, ws, N, dv, segs, G);
+    hipLaunchKernelGGL((prefill_kernel<false>), dim3((unsigned)(U * slices * G)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
+                       state, has_init, 0, in_entry, ws, N, dv, segs, G);
     return hipGetLastError();
 }
 

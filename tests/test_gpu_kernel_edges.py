@@ -105,3 +105,24 @@ def test_prefill_segments_from_a_state(based, packed, U, dv, N1, N):
     Sw, zw = oracle.linattn_state(k[at], v[at])
     check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
+
+
+# bf16 d' = 32 prefill: one token, around a chunk and the smallest number of chunks that is cut into segments, few and many segments,
+# the initial state read by one workgroup (one segment, d_v 64) and by several, both state layouts
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N1,N", [(2, 64, 1, 32), (3, 64, 31, 64), (3, 128, 33, 257), (2, 64, 224, 481), (3, 128, 64, 1100), (130, 64, 65, 330),
+                                       (9, 128, 225, 1500)])
+def test_prefill_dp32_edges(based, packed, U, dv, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    state = (based.alloc_packed_state if packed else based.alloc_state)(1, U, 32, dv)
+    got = [down(based.prefill(*(up(a[:, lo:hi], "bf16", (1, U, hi - lo, d)) for a, d in ((q, 32), (k, 32), (v, dv))), state=state,
+                              has_init=lo > 0, packed=packed)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N))]
+    at = np.unique([0, 1, U // 2, U - 1])
+    check_close(rows(np.concatenate(got, 1)[at]), rows(oracle.linattn_quadratic(q[at], k[at], v[at])), TOL["bf16"], "y")
+    if packed:
+        state = based.state_unpack(state, based.alloc_state(1, U, 32, dv), 1, U, 32, dv)
+    S, z = based.state_export(state, 1, U, 32, dv)
+    Sw, zw = oracle.linattn_state(k[at], v[at])
+    check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
+    check_close(down(z)[0, at], zw, TOL["bf16"], "z")
