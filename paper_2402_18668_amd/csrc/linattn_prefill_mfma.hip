@@ -1056,10 +1056,11 @@ int make_segments(int N, int G, SegTable &t)
     return G;
 }
 
-// Workspace: G - 1 entries per unit, then G x G ready-flag words per unit (256-byte aligned).
+// Workspace: room for G entries per unit (G - 1 are used; what fits the static scratch is part of the interface and stays as it
+// was), then G x G ready-flag words per unit (256-byte aligned).
 size_t ws_entry_bytes(int U, int N, int dv)
 {
-    return (size_t)U * (pick_segments(U, N, dv) - 1) * entry_floats(dv / 32) * sizeof(float);
+    return (size_t)U * pick_segments(U, N, dv) * entry_floats(dv / 32) * sizeof(float);
 }
 size_t ws_flag_bytes(int U, int N, int dv)
 {
