@@ -5,9 +5,13 @@
 // of g written once, so the kernel is laid out for the memory system and nothing else (loads and stores
 // carry the streaming hint: nothing is touched twice; 306 -> 290 us on the 1.3B shape).
 //
-// Work split.  A thread owns 16 bytes of channels (8 bf16 or 4 fp32) and walks a run of kRun tokens with
+// Work split.  A thread owns 16 bytes of channels (8 bf16 or 4 fp32) and a run of tokens, with
 // the two previous rows of c in registers, so c is read once (plus a two-row halo per run).  The threads
 // of a wave cover 1 KB of consecutive channels of one token: every load and store is a whole-row segment.
+// Runs of 8 tokens, all their loads issued together: latency is paid once per thread, and that is worth more than the halo,
+// also where the chip is full (runs of 32 with 4 rows in flight -> 8 with 8: 1.3B shape 274 -> 231 us, 6 x 262 tokens of
+// 4808 channels 36 -> 13 us; 4 tokens 263, 12 239, 16 251 us on the first).  Runs of 2 where 8 would leave less than a wave to a SIMD
+// (24 tokens x 9 of 2336 channels: 6.1 -> 5.0 us, 14.4 before).
 // The last two rows of c of every sequence can be written out as the state from which a later call (the
 // next part of the sequence, or a decode step, which is the N = 1 case) continues.
 #include "common.h"
@@ -16,7 +20,7 @@ namespace based {
 
 namespace {
 
-constexpr int kRun = 32;        // tokens per thread
+constexpr int kRun = 32;        // tokens per thread, at most: where c_last is c_prev
 constexpr int kThreads = 128;
 
 template <typename T> struct Vec16;
@@ -42,8 +46,8 @@ template <> struct Vec16<bf16_t> {
     }
 };
 
-// grid: (channel chunks / kThreads, runs of kRun tokens, B)
-template <typename T>
+// grid: (channel chunks / kThreads, runs of RUN tokens, B).  BATCH rows of a and c are on their way at a time.
+template <typename T, int RUN, int BATCH>
 __global__ __launch_bounds__(kThreads) void short_conv_gate_kernel(
     const T *__restrict__ a, const T *__restrict__ c, const float *__restrict__ h, const float *__restrict__ b1,
     const float *__restrict__ b2, const T *c_prev, T *__restrict__ out, T *c_last, int N, int Dc)
@@ -54,9 +58,10 @@ __global__ __launch_bounds__(kThreads) void short_conv_gate_kernel(
     if (chunk * CE >= Dc) return;
     const int ch0 = chunk * CE;
     const int b = blockIdx.z;
-    const int t0 = blockIdx.y * kRun, t1 = min(N, t0 + kRun);
+    const int t0 = blockIdx.y * RUN, t1 = min(N, t0 + RUN);
     const size_t seq = (size_t)b * N * Dc;
     using Raw = decltype(V::raw);
+    constexpr bool kStreamC = CE == 4;   // (bf16: the halo is read again sooner, 234 -> 231 us; fp32: 122 us, 131 without the hint)
     typedef uint32_t nt16 __attribute__((ext_vector_type(4)));   // 16 bytes, the type the streaming hints take
 
     float h0[CE], h1[CE], h2[CE], bb1[CE], bb2[CE];
@@ -80,21 +85,32 @@ __global__ __launch_bounds__(kThreads) void short_conv_gate_kernel(
     // channels and has read it by then, so c_last may be the same buffer.
     const bool owns_end = c_last && t1 == N;
 
-#pragma unroll 4
-    for (int t = t0; t < t1; ++t) {
-        V av, cv, o;
-        av.raw = __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const nt16 *>(a + seq + (size_t)t * Dc + ch0)));
-        cv.raw = __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const nt16 *>(c + seq + (size_t)t * Dc + ch0)));
-        float g[CE];
+    for (int tb = t0; tb < t1; tb += BATCH) {
+        V av[BATCH], cv[BATCH];
 #pragma unroll
-        for (int i = 0; i < CE; ++i) {
-            const float pre = fmaf(h0[i], cv.get(i), fmaf(h1[i], p1.get(i), fmaf(h2[i], p2.get(i), bb2[i])));
-            const float sg = pre / (1.f + __expf(-pre));
-            g[i] = (av.get(i) + bb1[i]) * sg;
+        for (int j = 0; j < BATCH; ++j) {   // (past the end: the last row again)
+            const size_t at = seq + (size_t)min(tb + j, t1 - 1) * Dc + ch0;
+            av[j].raw = __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const nt16 *>(a + at)));
+            cv[j].raw = kStreamC ? __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const nt16 *>(c + at)))
+                                 : *reinterpret_cast<const Raw *>(c + at);
         }
-        o.set(g);
-        __builtin_nontemporal_store(__builtin_bit_cast(nt16, o.raw), reinterpret_cast<nt16 *>(out + seq + (size_t)t * Dc + ch0));
-        p2 = p1; p1 = cv;
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            V o;
+            float g[CE];
+#pragma unroll
+            for (int i = 0; i < CE; ++i) {
+                const float pre = fmaf(h0[i], cv[j].get(i), fmaf(h1[i], p1.get(i), fmaf(h2[i], p2.get(i), bb2[i])));
+                const float sg = pre / (1.f + __expf(-pre));
+                g[i] = (av[j].get(i) + bb1[i]) * sg;
+            }
+            o.set(g);
+            if (tb + j < t1) {
+                __builtin_nontemporal_store(__builtin_bit_cast(nt16, o.raw),
+                                            reinterpret_cast<nt16 *>(out + seq + (size_t)(tb + j) * Dc + ch0));
+                p2 = p1; p1 = cv[j];
+            }
+        }
     }
     if (owns_end) {
         *reinterpret_cast<Raw *>(c_last + ((size_t)b * 2 + 0) * Dc + ch0) = p2.raw;
@@ -115,16 +131,22 @@ hipError_t launch_short_conv_gate(const void *a, const void *c, const float *h, 
                                   hipStream_t s)
 {
     const int ce = dtype == BASED_F32 ? 4 : 8;
-    const int chunks = Dc / ce;
-    const dim3 grid((unsigned)((chunks + kThreads - 1) / kThreads), (unsigned)((N + kRun - 1) / kRun), (unsigned)B);
-    if (grid.y > 65535u || grid.z > 65535u) return hipErrorInvalidValue;
-    if (dtype == BASED_F32)
-        hipLaunchKernelGGL(short_conv_gate_kernel<float>, grid, dim3(kThreads), 0, s, (const float *)a,
-                           (const float *)c, h, b1, b2, (const float *)c_prev, (float *)out, (float *)c_last, N, Dc);
-    else
-        hipLaunchKernelGGL(short_conv_gate_kernel<bf16_t>, grid, dim3(kThreads), 0, s, (const bf16_t *)a,
-                           (const bf16_t *)c, h, b1, b2, (const bf16_t *)c_prev, (bf16_t *)out, (bf16_t *)c_last, N,
-                           Dc);
+    const unsigned blocks = (unsigned)((Dc / ce + kThreads - 1) / kThreads);
+    auto launch = [&](auto kernel, int run, auto type) {
+        using T = decltype(type);
+        hipLaunchKernelGGL(kernel, dim3(blocks, (unsigned)((N + run - 1) / run), (unsigned)B), dim3(kThreads), 0, s, (const T *)a,
+                           (const T *)c, h, b1, b2, (const T *)c_prev, (T *)out, (T *)c_last, N, Dc);
+    };
+    auto pick = [&](auto type) {
+        using T = decltype(type);
+        // In place, one thread has to read and write the state rows of its channels: a single run.  (A launch has 65535 runs.)
+        if ((c_last && c_last == c_prev) || N > 8 * 65535) return launch(short_conv_gate_kernel<T, kRun, 4>, kRun, type);
+        // a wave per SIMD: 65536 threads
+        if ((long long)B * ((N + 7) / 8) * (Dc / ce) >= 65536 || N > 2 * 65535)
+            return launch(short_conv_gate_kernel<T, 8, 8>, 8, type);
+        launch(short_conv_gate_kernel<T, 2, 2>, 2, type);
+    };
+    if (dtype == BASED_F32) pick(float{}); else pick(bf16_t{});
     return hipGetLastError();
 }
 

@@ -126,3 +126,24 @@ def test_prefill_dp32_edges(based, packed, U, dv, N1, N):
     Sw, zw = oracle.linattn_state(k[at], v[at])
     check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
+
+
+# convolution gate: runs of 2, 8 and 32 tokens (the last for a state updated in place and for the longest sequences), a last run that is
+# not full, sequences shorter than the filter
+@pytest.mark.parametrize("dtype,B,N,Dc,in_place", [("bf16", 2, 1, 64, False), ("bf16", 3, 2, 72, False), ("f32", 3, 5, 12, False), ("bf16", 5, 9, 264, False),
+                                                   ("bf16", 9, 65, 8192, False), ("f32", 9, 71, 4100, False), ("bf16", 3, 31, 4096, True),
+                                                   ("f32", 2, 32, 64, True), ("f32", 1, 131073, 8, False), ("f32", 1, 524290, 8, False)])
+def test_conv_gate_runs(based, dtype, B, N, Dc, in_place):
+    import torch
+    import torch.nn.functional as F
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(N + Dc)
+    a, c, prev = (torch.randn(*s, generator=gen).to(dt) for s in ((B, N, Dc), (B, N, Dc), (B, 2, Dc)))
+    h, b1, b2 = (torch.randn(*s, generator=gen) for s in ((3, Dc), (Dc,), (Dc,)))
+    ext = torch.cat([prev, c], 1).float()
+    want = (a.float() + b1) * F.silu(h[0] * ext[:, 2:] + h[1] * ext[:, 1:-1] + h[2] * ext[:, :-2] + b2)
+    state = prev.cuda()
+    last = state if in_place else torch.full_like(state, float("nan"))
+    got = based.short_conv_gate(a.cuda(), c.cuda(), h.cuda(), b1.cuda(), b2.cuda(), c_prev=state, c_last=last)
+    check_close(rows(down(got)), rows(want.numpy()), TOL[dtype], "gate")
+    assert torch.equal(last.cpu(), ext[:, -2:].to(dt))
