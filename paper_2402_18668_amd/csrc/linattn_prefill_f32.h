@@ -51,7 +51,7 @@ constexpr int STAGE = 64;       // tokens staged at a time
 constexpr int LD = STAGE + 4;   // floats per staged row
 constexpr int NW = 4;           // waves of a workgroup: 16 columns each
 constexpr int COLS = 16 * NW;
-constexpr int kMaxSegments = 16;
+constexpr int kMaxSegments = 64;
 
 __host__ __device__ constexpr int blocks(int dp) { return dp / 4; }
 __host__ __device__ constexpr int tiles(int dp) { return blocks(dp) * (blocks(dp) + 1) / 2; }
@@ -193,13 +193,36 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
             for_n<ZS>([&](auto i) { z[i.value] = 0.f; });
         }
     } else if (G > 1) {
-        for (int e = init ? 0 : 1; e <= seg; ++e) {
-            const float *p = entry_s(e), *pz = entry_z(e);
-            for_n<NT>([&](auto t) {
-                S[t.value] = S[t.value] * g_seg + *reinterpret_cast<const f32x4 *>(p + (size_t)t.value * 256);
-                if (t.value % NW == w) z[t.value / NW] = z[t.value / NW] * g_seg + pz[16 * t.value + n];
-                if constexpr (t.value % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+        // the sum of the entries before the segment (up to 64 of them), some at a time with their loads in flight together
+        constexpr int EB = NT <= 3 ? 8 : NT <= 10 ? 4 : 1;
+        int e = init ? 0 : 1;
+        auto add_entries = [&](auto count) {
+            constexpr int n_e = decltype(count)::value;
+            f32x4 x[n_e][NT];
+            float xz[n_e][ZS];
+            for_n<n_e>([&](auto i) {
+                const float *p = entry_s(e + i.value), *pz = entry_z(e + i.value);
+                for_n<NT>([&](auto t) { x[i.value][t.value] = *reinterpret_cast<const f32x4 *>(p + (size_t)t.value * 256); });
+                for_n<ZS>([&](auto j) { xz[i.value][j.value] = NW * j.value + w < NT ? pz[16 * (NW * j.value + w) + n] : 0.f; });
             });
+            for_n<n_e>([&](auto i) {
+                for_n<NT>([&](auto t) { S[t.value] = S[t.value] * g_seg + x[i.value][t.value]; });
+                for_n<ZS>([&](auto j) { z[j.value] = z[j.value] * g_seg + xz[i.value][j.value]; });
+            });
+            e += n_e;
+        };
+        if constexpr (EB == 1) {
+            for (; e <= seg; ++e) {
+                const float *p = entry_s(e), *pz = entry_z(e);
+                for_n<NT>([&](auto t) {
+                    S[t.value] = S[t.value] * g_seg + *reinterpret_cast<const f32x4 *>(p + (size_t)t.value * 256);
+                    if (t.value % NW == w) z[t.value / NW] = z[t.value / NW] * g_seg + pz[16 * t.value + n];
+                    if constexpr (t.value % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+                });
+            }
+        } else {
+            for (int rest = (seg + 1 - e) % EB; rest > 0; --rest) add_entries(std::integral_constant<int, 1>{});
+            while (e <= seg) add_entries(std::integral_constant<int, EB>{});
         }
     } else if (init) {
         import_state();
@@ -399,13 +422,15 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     }
 }
 
-// Segments: one round of what the chip holds, segments of at least 128 tokens, at most 16.  (128 units of 2048 tokens at
-// d' 16, d_v 64: 2 segments 273 us, 4 205, 6 = a full round 190, 8 227.)
+// Segments: one round of what the chip holds, segments of at least 64 tokens (below that the increment launch and the sum
+// over the entries cost what the shorter chain gives), at most 64.  (128 units of 2048 tokens at d' 16, d_v 64: 2 segments
+// 273 us, 4 205, 6 = a full round 190, 8 227.  16 units: 777 tokens at d' 16 6 segments 52, 12 46, 24 60; at d' 32
+// 6 segments 137, 12 109; d' 8, 500 tokens 1 segment 51, 4 23, 8 17, 16 18; 14926 tokens 16 segments 145, 32 103, 64 99.)
 inline int segments(int U, int N, int dp, int dv)
 {
     const long groups = (long)U * (dv / COLS);
     long G = 256 * resident(dp) / groups;
-    if (G > N / 128) G = N / 128;
+    if (G > N / 64) G = N / 64;
     if (G > kMaxSegments) G = kMaxSegments;
     return G < 1 ? 1 : (int)G;
 }

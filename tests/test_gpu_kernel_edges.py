@@ -48,10 +48,10 @@ def test_projection_tilings(based, B, N, dm, H, dp, dv):
                 "project out")
 
 
-# fp32 matrix-core prefill: chunks of 16 and stages of 64 tokens with remainders, one and several segments, both widths (two
+# fp32 matrix-core prefill: chunks of 16 and stages of 64 tokens with remainders, one to 64 segments, both widths (two
 # 64-column slices share one K-state), each block count of d'; the second part continues from the first one's state
 @pytest.mark.parametrize("dtype,dp", [("f32", 8), ("f32", 16), ("f32", 24), ("f32", 32), ("bf16", 8), ("bf16", 24)])
-@pytest.mark.parametrize("dv,N1,N", [(64, 15, 33), (128, 17, 145), (64, 255, 600), (128, 256, 1321)])
+@pytest.mark.parametrize("dv,N1,N", [(64, 15, 33), (128, 17, 145), (64, 255, 600), (128, 256, 1321), (64, 30, 4401)])
 def test_prefill_fp32_arithmetic(based, dtype, dp, dv, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
     B, H = 1, 3
