@@ -349,18 +349,15 @@ static int swa_prefill_any(const void *q, const void *k, const void *v, void *y,
     if (ring && !aligned16(ring)) return BASED_ERR_INVALID_ARG;
     const int U = B * H;
     hipError_t e;
-    // the matrix-core kernel takes the row maximum of the unscaled scores, which is the maximum of
-    // the scaled ones only for a positive scale; anything else goes to the vector-ALU kernel
+    // the bf16 kernels take the row maximum of the unscaled scores, which is the maximum of the scaled ones only for a
+    // positive scale; anything else goes to the fp32 kernel.  All of them fill the ring too.
     if (!rot && swa_prefill_mfma16_supported(d_h, w, dtype) && scale > 0.f) {
-        // (the tiling of 16 queries to a wave, for the sizes where it is the faster one; fills the ring too)
+        // (the tiling of 16 queries to a wave, for the sizes where it is the faster one)
         e = launch_swa_prefill_mfma16(q, k, v, y, ring, U, N, d_h, w, scale, (hipStream_t)stream);
     } else if (swa_prefill_mfma_supported(d_h, w, dtype, rot != nullptr) && scale > 0.f) {
-        // this kernel also fills the ring
         e = launch_swa_prefill_mfma(q, k, v, y, ring, rot, U, N, d_h, w, scale, (hipStream_t)stream);
     } else {
-        e = launch_swa_prefill_ref(q, k, v, y, rot, U, N, d_h, w, scale, dtype, (hipStream_t)stream);
-        if (e == hipSuccess && ring)
-            e = launch_swa_ring_fill(k, v, ring, rot, U, N, d_h, w, dtype, (hipStream_t)stream);
+        e = launch_swa_prefill_f32(q, k, v, y, ring, rot, U, N, d_h, w, scale, dtype, (hipStream_t)stream);
     }
     return status_of(e);
 }

@@ -113,7 +113,8 @@ hipError_t launch_decode_step(const void *q, const void *k, const void *v, void 
 // rot (everywhere below): the rotary table, (cos, sin) per [position][pair], row 0 = the first token of
 // the call (prefill) or position 0 of the sequence (decode); null = no rotation
 hipError_t launch_rotary_table(float *table, int pos0, int N, int dh, float base, hipStream_t s);
-hipError_t launch_swa_prefill_ref(const void *q, const void *k, const void *v, void *y, const float *rot, int U,
+// the window prefill kernels also fill the decode ring (slot j mod w holds row j of the last min(N, w)), if one is given
+hipError_t launch_swa_prefill_f32(const void *q, const void *k, const void *v, void *y, void *ring, const float *rot, int U,
                                   int N, int dh, int w, float scale, int dtype, hipStream_t s);
 bool swa_prefill_mfma_supported(int dh, int w, int dtype, int rotary);
 hipError_t launch_swa_prefill_mfma(const void *q, const void *k, const void *v, void *y, void *ring,
@@ -122,8 +123,6 @@ hipError_t launch_swa_prefill_mfma(const void *q, const void *k, const void *v, 
 bool swa_prefill_mfma16_supported(int dh, int w, int dtype);
 hipError_t launch_swa_prefill_mfma16(const void *q, const void *k, const void *v, void *y, void *ring, int U, int N,
                                      int dh, int w, float scale, hipStream_t s);
-hipError_t launch_swa_ring_fill(const void *k, const void *v, void *ring, const float *rot, int U, int N, int dh,
-                                int w, int dtype, hipStream_t s);
 // Position of the decoded token: one value for every sequence, or (per_seq != NULL) one per batch
 // element in device memory, where a value < 1 marks a sequence that does not take part in the step.
 struct PosArg {

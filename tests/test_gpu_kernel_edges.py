@@ -147,3 +147,28 @@ def test_conv_gate_runs(based, dtype, B, N, Dc, in_place):
     got = based.short_conv_gate(a.cuda(), c.cuda(), h.cuda(), b1.cuda(), b2.cuda(), c_prev=state, c_last=last)
     check_close(rows(down(got)), rows(want.numpy()), TOL[dtype], "gate")
     assert torch.equal(last.cpu(), ext[:, -2:].to(dt))
+
+
+def window_case(based, dtype, dh, w, U, N, scale, rotary):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_h": dh, "w": w, "dtype": dtype})
+    q, k, v = synth.swa_inputs(wl, units=U, N=N)
+    want = oracle.swa_rotary(q, k, v, w, scale) if rotary else oracle.swa(q, k, v, w, scale)
+    dev = [up(a, dtype, (1, U, N, dh)) for a in (q, k, v)]
+    ring = based.alloc_swa_ring(1, U, w, dh, dev[0].dtype)
+    y = based.swa_prefill(*dev, w, scale, ring=ring, rotary=based.rotary_table(N, dh) if rotary else None)
+    check_close(rows(down(y).reshape(U, N, dh)), rows(want), TOL[dtype], "y")
+    r = down(ring).reshape(U, 2, w, dh)
+    kw = oracle.rotary(k, np.arange(N)) if rotary else k
+    last = np.arange(max(0, N - w), N)
+    check_close(rows(r[:, 0, last % w]), rows(kw[:, last]), TOL[dtype] / 4 if rotary else 0.0, "ring keys")
+    assert np.array_equal(r[:, 1, last % w], v[:, last].astype(np.float64))
+
+
+# fp32 matrix-core window attention: tiles of 16 and workgroups of 64 queries with remainders, sequences below and above
+# the window, every window; bf16 reaches it with a scale that is not positive
+@pytest.mark.parametrize("dtype,scale", [("f32", 0.125), ("f32", -0.2), ("bf16", -0.2), ("bf16", 0.0)])
+@pytest.mark.parametrize("dh,w,N", [(64, 16, 15), (128, 16, 81), (64, 32, 64), (128, 32, 65), (64, 64, 47), (128, 64, 200),
+                                    (64, 128, 130), (128, 128, 257)])
+@pytest.mark.parametrize("rotary", [False, True])
+def test_window_fp32_arithmetic(based, dtype, scale, dh, w, N, rotary):
+    window_case(based, dtype, dh, w, 3, N, scale, rotary)
