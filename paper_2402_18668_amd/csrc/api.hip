@@ -354,7 +354,7 @@ static int swa_prefill_any(const void *q, const void *k, const void *v, void *y,
     if (!rot && swa_prefill_mfma16_supported(d_h, w, dtype) && scale > 0.f) {
         // (the tiling of 16 queries to a wave, for the sizes where it is the faster one)
         e = launch_swa_prefill_mfma16(q, k, v, y, ring, U, N, d_h, w, scale, (hipStream_t)stream);
-    } else if (swa_prefill_mfma_supported(d_h, w, dtype, rot != nullptr) && scale > 0.f) {
+    } else if (swa_prefill_mfma_supported(d_h, w, dtype) && scale > 0.f) {
         e = launch_swa_prefill_mfma(q, k, v, y, ring, rot, U, N, d_h, w, scale, (hipStream_t)stream);
     } else {
         e = launch_swa_prefill_f32(q, k, v, y, ring, rot, U, N, d_h, w, scale, dtype, (hipStream_t)stream);

@@ -172,3 +172,9 @@ def window_case(based, dtype, dh, w, U, N, scale, rotary):
 @pytest.mark.parametrize("rotary", [False, True])
 def test_window_fp32_arithmetic(based, dtype, scale, dh, w, N, rotary):
     window_case(based, dtype, dh, w, 3, N, scale, rotary)
+
+
+# the rotated queries of the largest ring pass through its rows: segments of one and of several steps, a ragged last one
+@pytest.mark.parametrize("U,N", [(2, 1), (3, 129), (200, 300)])
+def test_window_rotary_largest_ring(based, U, N):
+    window_case(based, "bf16", 128, 128, U, N, 128 ** -0.5, True)
