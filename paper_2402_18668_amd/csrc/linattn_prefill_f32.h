@@ -393,7 +393,9 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     if (INCREMENT) {
         store_entry(1 + seg);
     } else if (state && seg == G - 1) {
-        // Both rows of a pair.  A state that is not symmetric (none of this recurrence is) keeps its antisymmetric part.
+        // Both rows of a pair.  A state that is not symmetric (none of this recurrence is) keeps its antisymmetric part,
+        // which decays like the rest: nothing is added to it, so over the N tokens of the call by gamma^N.
+        const float g_all = decay ? powf(gm, (float)N) : 1.f;
         int g2 = g, n2 = n;   // (hidden from the compiler, which would keep the rows' offsets alive through the loop)
         asm volatile("" : "+v"(g2), "+v"(n2));
         for_tiles<NB>([&](auto t, auto A, auto B) {
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 if (c.r1 >= 0) {
                     const float s = S[t.value][r.value] * c.scale;
                     float d = 0.f;
-                    if (init) d = 0.5f * (Su[(size_t)c.r1 * DV] - Su[(size_t)c.r2 * DV]);
+                    if (init) d = 0.5f * (Su[(size_t)c.r1 * DV] - Su[(size_t)c.r2 * DV]) * g_all;
                     Su[(size_t)c.r1 * DV] = s + d;
                     if (c.r2 != c.r1) Su[(size_t)c.r2 * DV] = s - d;
                 }
@@ -412,7 +414,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 if (c.r1 >= 0) {
                     const float s = z[t.value / NW] * c.scale;
                     float d = 0.f;
-                    if (init) d = 0.5f * (zu[c.r1] - zu[c.r2]);
+                    if (init) d = 0.5f * (zu[c.r1] - zu[c.r2]) * g_all;
                     zu[c.r1] = s + d;
                     if (c.r2 != c.r1) zu[c.r2] = s - d;
                 }

@@ -178,3 +178,26 @@ def test_window_fp32_arithmetic(based, dtype, scale, dh, w, N, rotary):
 @pytest.mark.parametrize("U,N", [(2, 1), (3, 129), (200, 300)])
 def test_window_rotary_largest_ring(based, U, N):
     window_case(based, "bf16", 128, 128, U, N, 128 ** -0.5, True)
+
+
+# decay from a state that is not symmetric in the feature pairs: both halves of it decay (gamma^N at the end of the call), in
+# one segment and in several, also at a rate of zero
+@pytest.mark.parametrize("dtype,dp,dv,N", [("f32", 8, 64, 5), ("f32", 16, 128, 40), ("bf16", 24, 64, 33), ("f32", 32, 64, 300)])
+def test_prefill_decay_from_asymmetric_state(based, dtype, dp, dv, N):
+    import torch
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
+    B, H, D = 1, 4, oracle.feature_dim(dp)
+    q, k, v = synth.linattn_inputs(wl, units=B * H, N=N)
+    gamma = np.array([1.0, 0.9, 0.0, 0.995], dtype=np.float32)
+    S0, z0 = synth.normal(78, (B * H, D, dv), 1.0), np.abs(synth.normal(79, (B * H, D), 1.0))
+    z0[:, 0] += 4.0 * D   # (denominators well away from zero)
+    want, Sw, zw = oracle.linattn_decay(q, k, v, gamma.astype(np.float64), S=S0, z=z0)
+    state = based.alloc_state(B, H, dp, dv)
+    based.state_import(state, up(S0, "f32", (B, H, D, dv)), up(z0, "f32", (B, H, D)), dp)
+    y = based.prefill_decay(*(up(a, dtype, (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), up(gamma, "f32"), state=state,
+                            has_init=True)
+    torch.cuda.synchronize()
+    check_close(rows(down(y).reshape(B * H, N, dv)), rows(want), TOL[dtype], "y")
+    S, z = based.state_export(state, B, H, dp, dv)
+    check_close(down(S).reshape(Sw.shape), Sw, 1e-4, "S")
+    check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
