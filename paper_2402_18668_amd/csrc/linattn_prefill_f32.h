@@ -396,6 +396,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
         // Both rows of a pair.  A state that is not symmetric (none of this recurrence is) keeps its antisymmetric part,
         // which decays like the rest: nothing is added to it, so over the N tokens of the call by gamma^N.
         const float g_all = decay ? powf(gm, (float)N) : 1.f;
+        auto half_difference = [](float a, float b) { return a == b ? 0.f : 0.5f * (a - b); };   // (equal infinities: none)
         int g2 = g, n2 = n;   // (hidden from the compiler, which would keep the rows' offsets alive through the loop)
         asm volatile("" : "+v"(g2), "+v"(n2));
         for_tiles<NB>([&](auto t, auto A, auto B) {
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 if (c.r1 >= 0) {
                     const float s = S[t.value][r.value] * c.scale;
                     float d = 0.f;
-                    if (init) d = 0.5f * (Su[(size_t)c.r1 * DV] - Su[(size_t)c.r2 * DV]) * g_all;
+                    if (init) d = half_difference(Su[(size_t)c.r1 * DV], Su[(size_t)c.r2 * DV]) * g_all;
                     Su[(size_t)c.r1 * DV] = s + d;
                     if (c.r2 != c.r1) Su[(size_t)c.r2 * DV] = s - d;
                 }
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 if (c.r1 >= 0) {
                     const float s = z[t.value / NW] * c.scale;
                     float d = 0.f;
-                    if (init) d = 0.5f * (zu[c.r1] - zu[c.r2]) * g_all;
+                    if (init) d = half_difference(zu[c.r1], zu[c.r2]) * g_all;
                     zu[c.r1] = s + d;
                     if (c.r2 != c.r1) zu[c.r2] = s - d;
                 }

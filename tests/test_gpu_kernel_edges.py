@@ -201,3 +201,19 @@ def test_prefill_decay_from_asymmetric_state(based, dtype, dp, dv, N):
     S, z = based.state_export(state, B, H, dp, dv)
     check_close(down(S).reshape(Sw.shape), Sw, 1e-4, "S")
     check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
+
+
+# a state that holds an infinity keeps it (the two rows of a pair are equal: there is no difference to carry over)
+def test_prefill_fp32_infinite_state(based):
+    B, H, N, dp, dv = 1, 1, 20, 16, 64
+    D = oracle.feature_dim(dp)
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "dtype": "f32"})
+    q, k, v = synth.linattn_inputs(wl, units=1, N=N)
+    S0, z0 = np.zeros((1, 1, D, dv)), np.zeros((1, 1, D))
+    S0[0, 0, 1 + dp + 2 * dp + 5, 9] = S0[0, 0, 1 + dp + 5 * dp + 2, 9] = np.inf
+    S0[0, 0, 1 + dp + 3 * dp + 3, 11] = -np.inf
+    state = based.alloc_state(B, H, dp, dv)
+    based.state_import(state, up(S0, "f32"), up(z0, "f32"), dp)
+    based.prefill(*(up(a, "f32", (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state, has_init=True)
+    S = down(based.state_export(state, B, H, dp, dv)[0])
+    assert np.array_equal(np.where(np.isfinite(S), 0.0, S), S0)
