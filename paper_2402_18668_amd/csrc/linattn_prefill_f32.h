@@ -320,10 +320,25 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 P[r.value] = 4 * g + r.value <= n ? p : 0.f;
                 if (w == 0) dsum += P[r.value];
             });
-            for_n<4>([&](auto s) {
-                if (s.value & 1) Y2 = mfma(vr[s.value], P[s.value], Y2);
-                else Y = mfma(vr[s.value], P[s.value], Y);
-            });
+            // A key that a query cannot see stands in the product as 0 V, which is not 0 where V is not finite: a block with such a
+            // value is summed key by key, without the hidden ones.
+            const float probe = fmaf(0.f, vr[0], fmaf(0.f, vr[1], fmaf(0.f, vr[2], 0.f * vr[3])));
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(probe != 0.f) == 0, 1)) {
+                for_n<4>([&](auto s) {
+                    if (s.value & 1) Y2 = mfma(vr[s.value], P[s.value], Y2);
+                    else Y = mfma(vr[s.value], P[s.value], Y);
+                });
+            } else {
+#pragma unroll 1
+                for (int j = 0; j < 4; ++j)
+                    for_n<4>([&](auto s) {
+                        const float p = __shfl(P[s.value], 16 * j + n, 64);
+                        for_n<4>([&](auto r) {
+                            const float x = __shfl(vr[s.value], 16 * j + 4 * g + r.value, 64);
+                            if (4 * j + s.value <= n) Y[r.value] = fmaf(p, x, Y[r.value]);
+                        });
+                    });
+            }
             Y += Y2;
             dsum += __shfl_xor(dsum, 16, 64);
             dsum += __shfl_xor(dsum, 32, 64);

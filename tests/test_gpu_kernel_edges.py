@@ -217,3 +217,29 @@ def test_prefill_fp32_infinite_state(based):
     based.prefill(*(up(a, "f32", (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state, has_init=True)
     S = down(based.state_export(state, B, H, dp, dv)[0])
     assert np.array_equal(np.where(np.isfinite(S), 0.0, S), S0)
+
+
+# a value that is not finite reaches nothing that does not see its token: earlier tokens and other columns (fp32 arithmetic; 16
+# tokens share a matrix product with it).  The tokens sit at the ends and inside of such a block, of a stage and of a segment.
+@pytest.mark.parametrize("decay", [False, True])
+@pytest.mark.parametrize("dtype,dp,dv,N", [("f32", 8, 64, 70), ("f32", 16, 64, 150), ("bf16", 24, 128, 37), ("f32", 32, 128, 200)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_prefill_fp32_nonfinite_values(based, dtype, dp, dv, N, bad, decay):
+    import torch
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
+    at = [0, 15, 21, 64, N - 2, N - 1]   # one token per unit, none in the last one
+    H = len(at) + 1
+    q, k, v = synth.linattn_inputs(wl, units=H, N=N)
+    tq, tk, tv = (up(a, dtype, (1, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv)))
+    gamma = torch.full((H,), 0.97, device="cuda")
+    call = (lambda x: based.prefill_decay(tq, tk, x, gamma)) if decay else (lambda x: based.prefill(tq, tk, x))
+    want = oracle.linattn_decay(q, k, v, np.full(H, 0.97))[0] if decay else oracle.linattn_quadratic(q, k, v)
+    dirty = tv.clone()
+    seen = np.zeros((H, N, dv), dtype=bool)
+    for u, t in enumerate(at):
+        t, c = min(t, N - 1), (7 * u + 3) % dv
+        dirty[0, u, t, c] = bad
+        seen[u, t:, c] = True
+    y = down(call(dirty)).reshape(H, N, dv)
+    assert not np.isfinite(y[seen]).any()
+    check_close(rows(np.where(seen, want, y)), rows(want), TOL[dtype], "y")
