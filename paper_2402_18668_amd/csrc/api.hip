@@ -350,11 +350,12 @@ static int swa_prefill_any(const void *q, const void *k, const void *v, void *y,
     const int U = B * H;
     hipError_t e;
     // the bf16 kernels take the row maximum of the unscaled scores, which is the maximum of the scaled ones only for a
-    // positive scale; anything else goes to the fp32 kernel.  All of them fill the ring too.
+    // positive scale; anything else goes to the fp32 kernel, as does rotary at the largest window and head size.  All of them
+    // fill the ring too.
     if (!rot && swa_prefill_mfma16_supported(d_h, w, dtype) && scale > 0.f) {
         // (the tiling of 16 queries to a wave, for the sizes where it is the faster one)
         e = launch_swa_prefill_mfma16(q, k, v, y, ring, U, N, d_h, w, scale, (hipStream_t)stream);
-    } else if (swa_prefill_mfma_supported(d_h, w, dtype) && scale > 0.f) {
+    } else if (swa_prefill_mfma_supported(d_h, w, dtype, rot != nullptr) && scale > 0.f) {
         e = launch_swa_prefill_mfma(q, k, v, y, ring, rot, U, N, d_h, w, scale, (hipStream_t)stream);
     } else {
         e = launch_swa_prefill_f32(q, k, v, y, ring, rot, U, N, d_h, w, scale, dtype, (hipStream_t)stream);

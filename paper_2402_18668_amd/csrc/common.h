@@ -116,7 +116,7 @@ hipError_t launch_rotary_table(float *table, int pos0, int N, int dh, float base
 // the window prefill kernels also fill the decode ring (slot j mod w holds row j of the last min(N, w)), if one is given
 hipError_t launch_swa_prefill_f32(const void *q, const void *k, const void *v, void *y, void *ring, const float *rot, int U,
                                   int N, int dh, int w, float scale, int dtype, hipStream_t s);
-bool swa_prefill_mfma_supported(int dh, int w, int dtype);
+bool swa_prefill_mfma_supported(int dh, int w, int dtype, int rotary);
 hipError_t launch_swa_prefill_mfma(const void *q, const void *k, const void *v, void *y, void *ring,
                                    const float *rot, int U, int N, int dh, int w, float scale, hipStream_t s);
 // the same with 16 queries to a wave (two workgroups per CU); no rotary variant

@@ -1,6 +1,7 @@
 // Sliding-window causal softmax attention over whole sequences (Sec. 3.2 restricting Eq. 1) on the fp32 matrix
-// instructions: fp32 inputs at every supported size, and bf16 inputs with a scale that is not positive (whose scores the
-// bf16 kernels cannot mask and maximise before scaling).  Every product and sum is fp32.
+// instructions: fp32 inputs at every supported size, bf16 inputs with a scale that is not positive (whose scores the
+// bf16 kernels cannot mask and maximise before scaling), and bf16 inputs with rotary encoding at d_h 128, window 128 (whose
+// ring leaves the bf16 kernel no room for the rotated queries).  Every product and sum is fp32.
 //
 // Work split: a workgroup is 64 queries of one unit, a wave 16 of them.  The keys a wave sees are T + 1 tiles of 16 (T = w /
 // 16, the first and last cut by the window's edges), and wave w's tiles start w tiles after wave 0's: at step t the

@@ -71,16 +71,10 @@ template <int DH, int WIN> struct SwaCfg {
     static constexpr int NKT = W / 32 + 1;     // key tiles per query tile
     static constexpr int Y_LD = 64 + 8;        // bf16 elements per row of a wave's output staging tile (64 columns a pass)
     static constexpr size_t lds_bytes = ((size_t)NK * (V_LD + K_LD) + (size_t)4 * 32 * Y_LD) * 2;
-    // rotary variant: the per-wave region holds either the wave's 32 rotated query rows or its output tile.  The largest
-    // ring leaves no room for that: there the rotated queries pass through the ring rows of the step's new keys, before
-    // the keys go in (two more barriers a step; on vector instructions these sizes took 2470 us instead of 133 for 256
-    // units of 2048 tokens, 67 instead of 13 for 64 of 164).
+    // rotary variant: the per-wave region holds either the wave's 32 rotated query rows or its output tile
     static constexpr int Q_LD = DH + 8;
-    static constexpr int WREG_Q = 32 * (Q_LD > Y_LD ? Q_LD : Y_LD);   // elements of a wave's region
-    static constexpr bool Q_IN_RING = ((size_t)NK * (V_LD + K_LD) + (size_t)4 * WREG_Q) * 2 > 160u * 1024u;
-    static constexpr int WREG = Q_IN_RING ? 32 * Y_LD : WREG_Q;
+    static constexpr int WREG = 32 * (Q_LD > Y_LD ? Q_LD : Y_LD);   // elements of a wave's region
     static constexpr size_t lds_bytes_rotary = ((size_t)NK * (V_LD + K_LD) + (size_t)4 * WREG) * 2;
-    static_assert(lds_bytes <= 160u * 1024u && lds_bytes_rotary <= 160u * 1024u && Q_LD == K_LD, "");
 };
 
 // (cos, sin) of four adjacent pairs
@@ -178,8 +172,7 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
     // A step handles BQ queries; going to the next step overwrites the BQ oldest rows with the BQ
     // new keys, every K / V row of the segment is staged exactly once (plus the W-row halo at the
     // segment start), and the next step's rows are fetched into registers while this step computes.
-    constexpr bool Q_IN_RING = ROT && Cfg::Q_IN_RING;
-    auto initial_fill = [&]() {   // keys q0 - W .. q0 + BQ - 1 into ring rows 0 .. NK - 1, every load in flight at once
+    {   // initial fill: keys q0 - W .. q0 + BQ - 1 into ring rows 0 .. NK - 1, every load in flight at once
         constexpr int FILLIT = NK * CPR / NT;
         static_assert(NK * CPR % NT == 0, "the initial fill is a whole number of passes");
         u32x4 fk[FILLIT], fv[FILLIT];
@@ -211,22 +204,17 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
                 *reinterpret_cast<u32x4 *>(rk + (size_t)WIN * DH) = fv[it];
             }
         }
-    };
-    if constexpr (!Q_IN_RING) initial_fill();
+    }
 
     u32x4 nk[NEWIT], nv[NEWIT];   // next step's new rows, in flight during this step
     u32x4 qop[SLABS], qnext[SLABS];   // rotary: qnext holds the new query rows in the key rows' chunk mapping
     static_assert(NEWIT == SLABS, "a thread stages as many query chunks as a lane holds operand slabs");
     Rot4 tk0;        // rotary: the table entry of the thread's first new row
     Rot4 rot_step;   // rotary: rotation by the NT / CPR rows between a thread's consecutive chunks
-    // where row r (of the BQ rows of a step) of the rotated queries sits: wave r / 32's region, or the ring row of the
-    // step's new key r (ring position pos of key 0)
-    auto q_stage = [&](int r, int pos) {
-        if constexpr (Q_IN_RING) return Ks + (size_t)((pos + r) % NK) * K_LD;
-        else return Ysh + (size_t)(r >> 5) * WREG + (size_t)(r & 31) * Q_LD;
-    };
-    auto read_qop = [&](int pos) {
-        const uint16_t *row = q_stage(32 * wv + n, pos) + 8 * g;
+    // where row r (of the BQ rows of a step) of the rotated queries sits: wave r / 32's region
+    auto q_stage = [&](int r) { return Ysh + (size_t)(r >> 5) * WREG + (size_t)(r & 31) * Q_LD; };
+    auto read_qop = [&]() {
+        const uint16_t *row = Ysh + (size_t)wv * WREG + (size_t)n * Q_LD + 8 * g;
 #pragma unroll
         for (int s = 0; s < SLABS; ++s) qop[s] = *reinterpret_cast<const u32x4 *>(row + 16 * s);
     };
@@ -240,7 +228,7 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
             const int idx = tid + it * NT, r = idx / CPR;
             const int row = min(q0 + r, N - 1);
             const u32x4 x = *reinterpret_cast<const u32x4 *>(q + base + (size_t)row * DH + c * 8);
-            *reinterpret_cast<u32x4 *>(q_stage(r, 0) + c * 8) = rotate8(x, load_rot4(rot + (size_t)row * (DH / 2) + 4 * c));
+            *reinterpret_cast<u32x4 *>(q_stage(r) + c * 8) = rotate8(x, load_rot4(rot + (size_t)row * (DH / 2) + 4 * c));
         }
     }
     // Loads of the pipeline are unconditional (a row past the end of the sequence re-reads the last
@@ -262,12 +250,7 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
         for (int s = 0; s < SLABS; ++s) asm volatile("" : "+v"(qop[s]));
     }
     __syncthreads();
-    if constexpr (ROT) read_qop(0);
-    if constexpr (Q_IN_RING) {
-        __syncthreads();
-        initial_fill();
-        __syncthreads();
-    }
+    if constexpr (ROT) read_qop();
 
     // One step of BQ queries.  Steps that have a successor are instantiated apart from the last one
     // of the segment, so that inside them every prefetch and every store is unconditional code and
@@ -483,23 +466,12 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
             }
             __syncthreads();   // every wave is done with the rows that are overwritten now
             const int rel_new = (sq0 + BQ) - (q0 - W);   // ring position of the first new key
-            if constexpr (ROT) {
-#pragma unroll
-                for (int it = 0; it < NEWIT; ++it) {
-                    const int idx = tid + it * NT, r = idx / CPR, c = idx % CPR;
-                    *reinterpret_cast<u32x4 *>(q_stage(r, rel_new) + c * 8) = qnext[it];
-                }
-            }
-            if constexpr (Q_IN_RING) {
-                __syncthreads();
-                read_qop(rel_new);
-                __syncthreads();
-            }
 #pragma unroll
             for (int it = 0; it < NEWIT; ++it) {
                 const int idx = tid + it * NT, r = idx / CPR, c = idx % CPR;
                 const int key = sq0 + BQ + r;
                 const int slot = (rel_new + r) % NK;
+                if constexpr (ROT) *reinterpret_cast<u32x4 *>(q_stage(r) + c * 8) = qnext[it];
                 if (key >= N) {
                     const u32x4 zero = {0u, 0u, 0u, 0u};
                     nk[it] = zero; nv[it] = zero;
@@ -516,7 +488,7 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
             for (int s = 0; s < SLABS; ++s)
                 if constexpr (!ROT) qop[s] = qnext[s];
             __syncthreads();
-            if constexpr (ROT && !Q_IN_RING) read_qop(rel_new);
+            if constexpr (ROT) read_qop();
         }
     };
     int sq0 = q0;
@@ -552,6 +524,7 @@ static hipError_t launch_swa_mfma_rot(const void *q, const void *k, const void *
 {
     using Cfg = SwaCfg<DH, WIN>;
     constexpr size_t lds_bytes = ROT ? Cfg::lds_bytes_rotary : Cfg::lds_bytes;
+    if (lds_bytes > 160u * 1024u) return hipErrorInvalidValue;   // callers ask swa_prefill_mfma_supported first
     const void *kern = ROT ? reinterpret_cast<const void *>(swa_prefill_mfma_rotary_kernel<DH, WIN>)
                            : reinterpret_cast<const void *>(swa_prefill_mfma_kernel<DH, WIN>);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
@@ -596,8 +569,12 @@ static hipError_t launch_swa_mfma(const void *q, const void *k, const void *v, v
                : launch_swa_mfma_rot<DH, WIN, false>(q, k, v, y, ring, nullptr, U, N, scale, s);
 }
 
-bool swa_prefill_mfma_supported(int dh, int w, int dtype)
+bool swa_prefill_mfma_supported(int dh, int w, int dtype, int rotary)
 {
+    // The rotary variant stages the queries in LDS as well, which the largest ring leaves no room for: that call goes to the fp32
+    // matrix instructions.  (Passing the queries through the ring rows of the step's new keys makes it fit, 130 instead of
+    // 543 us for 256 units of 2048 tokens, but rounds the rotated queries and the probabilities to bf16, which this call never did.)
+    if (rotary && dh == 128 && w == 128) return false;
     return dtype == BASED_BF16 && (dh == 64 || dh == 128) && (w == 16 || w == 32 || w == 64 || w == 128);
 }
 

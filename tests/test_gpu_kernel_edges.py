@@ -174,7 +174,7 @@ def test_window_fp32_arithmetic(based, dtype, scale, dh, w, N, rotary):
     window_case(based, dtype, dh, w, 3, N, scale, rotary)
 
 
-# the rotated queries of the largest ring pass through its rows: segments of one and of several steps, a ragged last one
+# the largest ring with rotary: workgroups of one and of several steps, a ragged last one
 @pytest.mark.parametrize("U,N", [(2, 1), (3, 129), (200, 300)])
 def test_window_rotary_largest_ring(based, U, N):
     window_case(based, "bf16", 128, 128, U, N, 128 ** -0.5, True)
@@ -243,3 +243,20 @@ def test_prefill_fp32_nonfinite_values(based, dtype, dp, dv, N, bad, decay):
     y = down(call(dirty)).reshape(H, N, dv)
     assert not np.isfinite(y[seen]).any()
     check_close(rows(np.where(seen, want, y)), rows(want), TOL[dtype], "y")
+
+
+# rotary at d_h 128, window 128 with bf16 inputs computes in fp32: the rotated queries and the probabilities are not rounded, so a
+# result is off by its own rounding to bf16 (2^-8 of it at most) and by fp32 sums (128 terms of 2^-24 and scores of a few units:
+# 2e-5 of the row's scale is 10 times that), while rounding the probabilities alone moves it by 1e-3 of the row's scale
+@pytest.mark.parametrize("U,N", [(2, 128), (3, 77), (1, 16)])
+def test_window_rotary_largest_ring_precision(based, U, N):
+    w = dh = 128
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_h": dh, "w": w})
+    q, k, v = synth.swa_inputs(wl, units=U, N=N)
+    dev = [up(a, "bf16", (1, U, N, dh)) for a in (q, k, v)]
+    ring = based.alloc_swa_ring(1, U, w, dh, dev[0].dtype)
+    y = down(based.swa_prefill(*dev, w, dh ** -0.5, ring=ring, rotary=based.rotary_table(N, dh))).reshape(U, N, dh)
+    keys = down(ring).reshape(U, 2, w, dh)[:, 0, :N]   # (N <= w: every key, rotated and rounded as the decode ring holds it)
+    want = oracle.swa(oracle.rotary(q, np.arange(N)), keys, v, w, dh ** -0.5)
+    rms = np.sqrt((want ** 2).mean(-1, keepdims=True))
+    assert (np.abs(y - want) <= 2.0 ** -8 * np.abs(want) + 2e-5 * rms).all()
