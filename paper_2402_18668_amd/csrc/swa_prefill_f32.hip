@@ -196,6 +196,27 @@ __global__ __launch_bounds__(NT, resident(DH, W)) void kernel(const T *__restric
             __syncthreads();
         }
     });
+    // In the window's first and last tile a key that a query cannot see stood in the product as 0 V, which is NaN where V is not
+    // finite.  Results that are not finite are summed again, key by key and without the hidden ones, V from memory.
+    float probe = 0.f;
+    for_n<DC>([&](auto c) { for_n<4>([&](auto r) { probe = fmaf(0.f, Y[c.value][r.value], probe); }); });
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(query < N && probe != 0.f) != 0, 0)) {
+        for_n<DC>([&](auto c) { Y[c.value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+        for_n<TL + 1>([&](auto t) {
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j)
+                for_n<4>([&](auto s) {
+                    const float p = __shfl(P[t.value][s.value], 16 * j + n, 64);
+                    const int key = qbase - W + 16 * t.value + 4 * j + s.value;
+                    const bool visible = key >= 0 && key > query - W && key <= query;
+                    const T *row = vu + (size_t)min(max(key, 0), N - 1) * DH + 4 * g;
+                    for_n<DC>([&](auto c) {
+                        const f32x4 x = load4(row + 16 * c.value);
+                        for_n<4>([&](auto r) { Y[c.value][r.value] = fmaf(p, visible ? x[r.value] : 0.f, Y[c.value][r.value]); });
+                    });
+                });
+        });
+    }
     if (query < N) {
         const float inv = 1.f / sum;
         for_n<DC>([&](auto c) { store4(y + base + (size_t)query * DH + 16 * c.value + 4 * g, Y[c.value] * inv); });

@@ -260,3 +260,30 @@ def test_window_rotary_largest_ring_precision(based, U, N):
     want = oracle.swa(oracle.rotary(q, np.arange(N)), keys, v, w, dh ** -0.5)
     rms = np.sqrt((want ** 2).mean(-1, keepdims=True))
     assert (np.abs(y - want) <= 2.0 ** -8 * np.abs(want) + 2e-5 * rms).all()
+
+
+# the same for the window: neither earlier tokens nor those behind the window see it.  Keys too: a score that is not a number is
+# hidden where the key is
+NONFINITE_SIZES = [(64, 16, 81), (128, 32, 100), (64, 64, 200), (128, 128, 321)]
+
+
+@pytest.mark.parametrize("dtype,scale,rotary,dh,w,N", [(*kind, *size) for kind in (("f32", 0.125, False), ("f32", 0.125, True), ("bf16", -0.2, False))
+                                                       for size in NONFINITE_SIZES] + [("bf16", 0.125, True, 128, 128, 321)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_window_fp32_nonfinite_values(based, dtype, scale, rotary, dh, w, N, bad):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_h": dh, "w": w, "dtype": dtype})
+    at = [0, 1, 15, 16, 40, 63, 64, 79, N - 1]   # one token per unit; the last unit gets a key instead
+    H = len(at) + 1
+    q, k, v = synth.swa_inputs(wl, units=H, N=N)
+    want = oracle.swa_rotary(q, k, v, w, scale) if rotary else oracle.swa(q, k, v, w, scale)
+    tq, tk, tv = (up(a, dtype, (1, H, N, dh)) for a in (q, k, v))
+    seen = np.zeros((H, N, dh), dtype=bool)
+    for u, t in enumerate(at):
+        c = (11 * u + 2) % dh
+        tv[0, u, t, c] = bad
+        seen[u, t:t + w, c] = True
+    tk[0, H - 1, 50, 4] = float("nan")
+    seen[H - 1, 50:50 + w] = True
+    y = down(based.swa_prefill(tq, tk, tv, w, scale, rotary=based.rotary_table(N, dh) if rotary else None)).reshape(H, N, dh)
+    assert not np.isfinite(y[seen]).any()
+    check_close(rows(np.where(seen, want, y)), rows(want), TOL[dtype], "y")
