@@ -439,6 +439,8 @@ __device__ __forceinline__ void prefill_body(
     }
     // every wave, once it has what it needs of the image
     auto state_was_read = [&]() {
+        // (a barrier does not wait for loads into registers, and the flag lets another workgroup overwrite what they read)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) lds.staged = 0u;   // (it lies in the image)
         if (MODE == 0 && G > 1) {

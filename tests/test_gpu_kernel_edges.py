@@ -287,3 +287,22 @@ def test_window_fp32_nonfinite_values(based, dtype, scale, rotary, dh, w, N, bad
     y = down(based.swa_prefill(tq, tk, tv, w, scale, rotary=based.rotary_table(N, dh) if rotary else None)).reshape(H, N, dh)
     assert not np.isfinite(y[seen]).any()
     check_close(rows(np.where(seen, want, y)), rows(want), TOL[dtype], "y")
+
+
+# the last segment overwrites the state that two workgroups of other segments read first: the same call from the same state gives
+# the same bits every time (short last segments, more workgroups than fit at once, both widths and layouts)
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N", [(128, 64, 6 * 64), (40, 128, 12 * 64), (3, 64, 30 * 64)])
+def test_prefill_state_handover_repeats(based, packed, U, dv, N):
+    import torch
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    args = [up(a, "bf16", (1, U, N, d)) for a, d in ((q, 16), (k, 16), (v, dv))]
+    start = (based.alloc_packed_state if packed else based.alloc_state)(1, U, 16, dv)
+    based.prefill(*args, state=start, packed=packed)
+    runs = []
+    for _ in range(6):
+        state = start.clone()
+        runs.append((based.prefill(*args, state=state, has_init=True, packed=packed), state))
+    for y, s in runs[1:]:
+        assert torch.equal(y, runs[0][0]) and torch.equal(s, runs[0][1])
