@@ -11,6 +11,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
+#include <ATen/DimVector.h>
 #include <ATen/core/LegacyTypeDispatch.h>
 #include <c10/hip/HIPStream.h>
 
@@ -48,6 +49,22 @@ void check(int status, const char *what)
     Py_XDECREF(r);
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, what);
     throw PyError{};
+}
+
+// Allocates what a call returns and makes the call, without the interpreter lock: a launch into a full queue and an allocation
+// that has to wait for the GPU would otherwise stop every Python thread.  (Both in one stretch without the lock: giving it up and
+// taking it back costs 0.1 us, and longer with other threads running.)  f touches nothing of Python.
+template <typename F> void call(const char *what, F &&f)
+{
+    int status;
+    {
+        struct Unlocked {
+            PyThreadState *state = PyEval_SaveThread();
+            ~Unlocked() { PyEval_RestoreThread(state); }
+        } unlocked;
+        status = f();
+    }
+    check(status, what);
 }
 
 // A tensor argument: a borrowed handle, checked to live on the GPU and to be contiguous.
@@ -114,25 +131,29 @@ float as_float(PyObject *o)
 }
 
 // A result: the tensor the caller gave (of the same shape and type where `msg` says what to answer otherwise, else any
-// buffer that is large enough), or a new one shaped like `like`.
+// buffer that is large enough), or one that make() allocates (inside call()), shaped like `like` or of the given shape.
 struct Out {
-    at::Tensor made;
     PyObject *given = nullptr;
     void *data = nullptr;
-    Out(PyObject *o, Arg like, const char *msg = nullptr)
+    at::Tensor made;
+    Arg like;
+    at::DimVector shape;   // (empty: like's own)
+    Out(PyObject *o, Arg like_, const char *msg = nullptr) : like(like_)
     {
-        if (o == Py_None) {
-            made = at::empty_like(*like);
-            data = made.data_ptr();
-        } else {
-            Arg t = tensor(o);
-            if (msg ? t->sizes() != like->sizes() || !same_type(t, like) : nbytes(t) < nbytes(like))
-                bad(msg ? msg : "output buffer too small");
-            given = o;
-            data = t->data_ptr();
-        }
+        if (o == Py_None) return;
+        Arg t = tensor(o);
+        if (msg ? t->sizes() != like->sizes() || !same_type(t, like) : nbytes(t) < nbytes(like))
+            bad(msg ? msg : "output buffer too small");
+        given = o;
+        data = t->data_ptr();
     }
-    explicit Out(at::Tensor t) : made(std::move(t)), data(made.data_ptr()) {}
+    Out(Arg like_, std::initializer_list<int64_t> shape_) : like(like_), shape(shape_) {}
+    void make()
+    {
+        if (given) return;
+        made = shape.empty() ? at::empty_like(*like) : at::empty(shape, like->options());
+        data = made.data_ptr();
+    }
     PyObject *take()
     {
         if (given) { Py_INCREF(given); return given; }
@@ -167,16 +188,18 @@ PyObject *prefill(PyObject *const *a)
     Out y(a[3], v, "y must match v");
     if (state) check_state(state, packed ? fn.based_packed_state_bytes(B, H, dp, dv) : fn.based_state_bytes(B, H, dp, dv));
     const size_t need = fn.based_prefill_workspace_bytes(B, H, N, dp, dv, code);
-    at::Tensor own;
-    if (need && !ws) {   // zero-filled once, as the library asks
-        own = at::zeros({(int64_t)((need + 3) / 4)}, q->options().dtype(at::kFloat));
-        ws = &own;
-    }
-    if (need && nbytes(ws) < need) bad("workspace too small");
+    if (need && ws && nbytes(ws) < need) bad("workspace too small");
     if (packed && numer) bad("there is no packed numerator-only prefill");
-    auto call = numer ? fn.based_prefill_numerator : packed ? fn.based_prefill_packed : fn.based_prefill;
-    check(call(ptr(q), ptr(k), ptr(v), y.data, ptr(state), has_init, ptr(ws), B, H, N, dp, dv, code, stream()),
-          numer ? "based_prefill_numerator" : packed ? "based_prefill_packed" : "based_prefill");
+    auto f = numer ? fn.based_prefill_numerator : packed ? fn.based_prefill_packed : fn.based_prefill;
+    call(numer ? "based_prefill_numerator" : packed ? "based_prefill_packed" : "based_prefill", [&] {
+        y.make();
+        at::Tensor own;
+        if (need && !ws) {   // zero-filled once, as the library asks
+            own = at::zeros({(int64_t)((need + 3) / 4)}, q->options().dtype(at::kFloat));
+            ws = &own;
+        }
+        return f(ptr(q), ptr(k), ptr(v), y.data, ptr(state), has_init, ptr(ws), B, H, N, dp, dv, code, stream());
+    });
     return y.take();
 }
 
@@ -193,9 +216,12 @@ PyObject *decode_step(PyObject *const *a)
     check_state(state, packed ? fn.based_packed_state_bytes(B, H, dp, dv) : fn.based_state_bytes(B, H, dp, dv));
     Out y(a[4], v);
     if (packed && numer) bad("there is no packed numerator-only decode step");
-    auto call = numer ? fn.based_decode_step_numerator : packed ? fn.based_decode_step_packed : fn.based_decode_step;
-    check(call(ptr(q), ptr(k), ptr(v), y.data, ptr(state), B, H, dp, dv, code_of(q), stream()),
-          numer ? "based_decode_step_numerator" : packed ? "based_decode_step_packed" : "based_decode_step");
+    const int code = code_of(q);
+    auto f = numer ? fn.based_decode_step_numerator : packed ? fn.based_decode_step_packed : fn.based_decode_step;
+    call(numer ? "based_decode_step_numerator" : packed ? "based_decode_step_packed" : "based_decode_step", [&] {
+        y.make();
+        return f(ptr(q), ptr(k), ptr(v), y.data, ptr(state), B, H, dp, dv, code, stream());
+    });
     return y.take();
 }
 
@@ -225,12 +251,12 @@ PyObject *swa_prefill(PyObject *const *a)
     Arg rot = rotary_table(a[7], N, dh);
     const int code = code_of(q);
     Out y(a[5], v);
-    if (rot)
-        check(fn.based_swa_prefill_rotary(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), (const float *)ptr(rot), B, H, N,
-                                          dh, w, scale, code, stream()), "based_swa_prefill_rotary");
-    else
-        check(fn.based_swa_prefill(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), B, H, N, dh, w, scale, code, stream()),
-              "based_swa_prefill");
+    call(rot ? "based_swa_prefill_rotary" : "based_swa_prefill", [&] {
+        y.make();
+        return rot ? fn.based_swa_prefill_rotary(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), (const float *)ptr(rot), B, H, N, dh,
+                                                 w, scale, code, stream())
+                   : fn.based_swa_prefill(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), B, H, N, dh, w, scale, code, stream());
+    });
     return y.take();
 }
 
@@ -269,16 +295,16 @@ PyObject *swa_decode(PyObject *const *a)
     const Pos pos = position(a[4], B);
     const int code = code_of(q);
     Out y(a[7], v);
-    if (rot)
-        check(fn.based_swa_decode_rotary(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), (const float *)ptr(rot),
-                                         (int)rot->size(0), pos.value, pos.per_seq, B, H, dh, w, scale, code, stream()),
-              "based_swa_decode_rotary");
-    else if (pos.per_seq)
-        check(fn.based_swa_decode_ragged(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), pos.per_seq, B, H, dh, w, scale,
-                                         code, stream()), "based_swa_decode_ragged");
-    else
-        check(fn.based_swa_decode(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), pos.value, B, H, dh, w, scale, code,
-                                  stream()), "based_swa_decode");
+    call(rot ? "based_swa_decode_rotary" : pos.per_seq ? "based_swa_decode_ragged" : "based_swa_decode", [&] {
+        y.make();
+        if (rot)
+            return fn.based_swa_decode_rotary(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), (const float *)ptr(rot),
+                                              (int)rot->size(0), pos.value, pos.per_seq, B, H, dh, w, scale, code, stream());
+        if (pos.per_seq)
+            return fn.based_swa_decode_ragged(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), pos.per_seq, B, H, dh, w, scale, code,
+                                              stream());
+        return fn.based_swa_decode(ptr(q), ptr(k), ptr(v), y.data, ptr(ring), pos.value, B, H, dh, w, scale, code, stream());
+    });
     return y.take();
 }
 
@@ -303,20 +329,22 @@ PyObject *decode_fused(PyObject *const *a)
     const Pos pos = position(a[8], B);
     const int code = code_of(q);
     Out yl(a[11], v), ys(a[12], sv);
-    if (rot)
-        check(fn.based_decode_fused_rotary(ptr(q), ptr(k), ptr(v), yl.data, ptr(state), packed, dp, dv, ptr(sq), ptr(sk),
-                                           ptr(sv), ys.data, ptr(ring), (const float *)ptr(rot), (int)rot->size(0),
-                                           pos.value, pos.per_seq, dh, w, scale, B, H, code, stream()),
-              "based_decode_fused_rotary");
-    else if (pos.per_seq)
-        check(fn.based_decode_fused_ragged(ptr(q), ptr(k), ptr(v), yl.data, ptr(state), packed, dp, dv, ptr(sq), ptr(sk),
-                                           ptr(sv), ys.data, ptr(ring), pos.per_seq, dh, w, scale, B, H, code, stream()),
-              "based_decode_fused_ragged");
-    else
-        check((packed ? fn.based_decode_fused_packed : fn.based_decode_fused)(
-                  ptr(q), ptr(k), ptr(v), yl.data, ptr(state), dp, dv, ptr(sq), ptr(sk), ptr(sv), ys.data, ptr(ring),
-                  pos.value, dh, w, scale, B, H, code, stream()),
-              packed ? "based_decode_fused_packed" : "based_decode_fused");
+    call(rot ? "based_decode_fused_rotary" : pos.per_seq ? "based_decode_fused_ragged"
+                                           : packed      ? "based_decode_fused_packed"
+                                                         : "based_decode_fused", [&] {
+        yl.make();
+        ys.make();
+        if (rot)
+            return fn.based_decode_fused_rotary(ptr(q), ptr(k), ptr(v), yl.data, ptr(state), packed, dp, dv, ptr(sq), ptr(sk),
+                                                ptr(sv), ys.data, ptr(ring), (const float *)ptr(rot), (int)rot->size(0),
+                                                pos.value, pos.per_seq, dh, w, scale, B, H, code, stream());
+        if (pos.per_seq)
+            return fn.based_decode_fused_ragged(ptr(q), ptr(k), ptr(v), yl.data, ptr(state), packed, dp, dv, ptr(sq), ptr(sk),
+                                                ptr(sv), ys.data, ptr(ring), pos.per_seq, dh, w, scale, B, H, code, stream());
+        return (packed ? fn.based_decode_fused_packed : fn.based_decode_fused)(
+            ptr(q), ptr(k), ptr(v), yl.data, ptr(state), dp, dv, ptr(sq), ptr(sk), ptr(sv), ys.data, ptr(ring), pos.value, dh, w,
+            scale, B, H, code, stream());
+    });
     return pair(yl, ys);
 }
 
@@ -326,7 +354,7 @@ PyObject *positions_advance(PyObject *const *a)
     if (!THPVariable_Check(a[0])) fail(PyExc_TypeError, "expected a torch.Tensor");
     const int B = (int)THPVariable_Unpack(a[0]).numel();
     const Pos pos = position(a[0], B);
-    check(fn.based_positions_advance(const_cast<int *>(pos.per_seq), B, stream()), "based_positions_advance");
+    call("based_positions_advance", [&] { return fn.based_positions_advance(const_cast<int *>(pos.per_seq), B, stream()); });
     Py_RETURN_NONE;
 }
 
@@ -339,14 +367,14 @@ PyObject *linear(PyObject *const *a)
     const int64_t K = W->size(1), N = W->size(0), M = x->numel() / K;
     if (y_given && (y_given->numel() != M * N || !same_type(y_given, x)))
         bad("y must be [..., N], contiguous, of x's dtype");
+    auto shape = x->sizes().vec();
+    shape.back() = N;
+    const int code = code_of(x);
     at::Tensor made;
-    if (!y_given) {
-        auto shape = x->sizes().vec();
-        shape.back() = N;
-        made = at::empty(shape, x->options());
-    }
-    check(fn.based_linear(ptr(x), ptr(W), y_given ? ptr(y_given) : made.data_ptr(), (int)M, (int)K, (int)N, code_of(x),
-                          stream()), "based_linear");
+    call("based_linear", [&] {
+        if (!y_given) made = at::empty(shape, x->options());
+        return fn.based_linear(ptr(x), ptr(W), y_given ? ptr(y_given) : made.data_ptr(), (int)M, (int)K, (int)N, code, stream());
+    });
     if (y_given) { Py_INCREF(a[2]); return a[2]; }
     return THPVariable_Wrap(std::move(made));
 }
@@ -360,10 +388,14 @@ PyObject *project_qkv(PyObject *const *a)
     const int B = x->size(0), N = x->size(1), dm = x->size(2);
     if (!shape_is(W, {(int64_t)H * (2 * dp + dv), dm}) || !same_type(W, x))
         bad("x [B, N, d_model] and W [H (2 d' + d_v), d_model] must be contiguous and of one dtype");
-    Out q(at::empty({B, H, N, dp}, x->options())), k(at::empty({B, H, N, dp}, x->options())),
-        v(at::empty({B, H, N, dv}, x->options()));
-    check(fn.based_project_qkv(ptr(x), ptr(W), q.data, k.data, v.data, B, N, dm, H, dp, dv, code_of(x), stream()),
-          "based_project_qkv");
+    Out q(x, {B, H, N, dp}), k(x, {B, H, N, dp}), v(x, {B, H, N, dv});
+    const int code = code_of(x);
+    call("based_project_qkv", [&] {
+        q.make();
+        k.make();
+        v.make();
+        return fn.based_project_qkv(ptr(x), ptr(W), q.data, k.data, v.data, B, N, dm, H, dp, dv, code, stream());
+    });
     PyObject *t = PyTuple_New(3);
     if (!t) throw PyError{};
     PyTuple_SET_ITEM(t, 0, q.take());
@@ -381,8 +413,12 @@ PyObject *project_out(PyObject *const *a)
     if (W->dim() != 2 || W->size(1) != (int64_t)H * dv || !same_type(W, y))
         bad("y [B, H, N, d_v] and W [d_model, H d_v] must be contiguous and of one dtype");
     const int dm = W->size(0);
-    Out out(at::empty({B, N, dm}, y->options()));
-    check(fn.based_project_out(ptr(y), ptr(W), out.data, B, N, H, dv, dm, code_of(y), stream()), "based_project_out");
+    Out out(y, {B, N, dm});
+    const int code = code_of(y);
+    call("based_project_out", [&] {
+        out.make();
+        return fn.based_project_out(ptr(y), ptr(W), out.data, B, N, H, dv, dm, code, stream());
+    });
     return out.take();
 }
 
@@ -401,9 +437,12 @@ PyObject *short_conv_gate(PyObject *const *p)
         if (t && (!shape_is(t, {B, 2, Dc}) || !same_type(t, a)))
             bad("c_prev / c_last must be contiguous [B, 2, Dc] of a's dtype");
     Out out(p[7], a, "out must match a");
-    check(fn.based_short_conv_gate(ptr(a), ptr(c), (const float *)ptr(h), (const float *)ptr(b1), (const float *)ptr(b2),
-                                   ptr(prev), out.data, ptr(last), (int)B, (int)N, (int)Dc, code_of(a), stream()),
-          "based_short_conv_gate");
+    const int code = code_of(a);
+    call("based_short_conv_gate", [&] {
+        out.make();
+        return fn.based_short_conv_gate(ptr(a), ptr(c), (const float *)ptr(h), (const float *)ptr(b1), (const float *)ptr(b2),
+                                        ptr(prev), out.data, ptr(last), (int)B, (int)N, (int)Dc, code, stream());
+    });
     return out.take();
 }
 

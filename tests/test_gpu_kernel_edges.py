@@ -306,3 +306,37 @@ def test_prefill_state_handover_repeats(based, packed, U, dv, N):
         runs.append((based.prefill(*args, state=state, has_init=True, packed=packed), state))
     for y, s in runs[1:]:
         assert torch.equal(y, runs[0][0]) and torch.equal(s, runs[0][1])
+
+
+# other Python threads run while a call is inside the library (a stand-in that sleeps: no kernel is launched)
+def test_calls_release_the_interpreter_lock(based, tmp_path):
+    import ctypes
+    import subprocess
+    import threading
+    import time
+    import torch
+    src, so = tmp_path / "slow.c", tmp_path / "slow.so"
+    src.write_text("#include <unistd.h>\nint slow(int *pos, int B, void *stream) { usleep(400000); return 0; }\n")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)])
+    slow = ctypes.CDLL(str(so)).slow
+    addresses = {n: ctypes.cast(getattr(based.lib, n), ctypes.c_void_p).value for n in based.EXPORTS}
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks.append(time.monotonic())
+            time.sleep(0.005)
+
+    pos = torch.ones(3, dtype=torch.int32, device="cuda")
+    thread = threading.Thread(target=tick)
+    thread.start()
+    based._bind.init({**addresses, "based_positions_advance": ctypes.cast(slow, ctypes.c_void_p).value}, based._raise)
+    try:
+        t0 = time.monotonic()
+        based.positions_advance(pos)
+        t1 = time.monotonic()
+    finally:
+        based._bind.init(addresses, based._raise)
+        stop.set()
+        thread.join()
+    assert t1 - t0 >= 0.4 and any(t0 + 0.1 < t < t1 - 0.1 for t in ticks)
