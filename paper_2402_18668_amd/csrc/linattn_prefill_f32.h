@@ -55,6 +55,11 @@ constexpr int kMaxSegments = 64;
 
 __host__ __device__ constexpr int blocks(int dp) { return dp / 4; }
 __host__ __device__ constexpr int tiles(int dp) { return blocks(dp) * (blocks(dp) + 1) / 2; }
+// tiles of the state that pass through LDS together on their way from and to the state buffer, and the floats of their rows there
+__host__ __device__ constexpr int image_tiles(int dp) { return dp == 32 ? 12 : dp == 24 ? 7 : dp == 16 ? 5 : 3; }
+constexpr int IMG_LD = COLS + 4;
+// of these, tiles whose loads from the state buffer are in flight together
+__host__ __device__ constexpr int image_unroll(int dp) { return dp == 32 ? 4 : image_tiles(dp); }
 // Workspace entry of one (unit, slice, segment): per wave the tiles' accumulators [tile][lane][4], then z [tile][16].
 __host__ __device__ constexpr size_t entry_floats(int dp) { return (size_t)tiles(dp) * (NW * 256 + 16); }
 
@@ -124,7 +129,12 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
 {
     constexpr int NB = blocks(DP), NT = tiles(DP), SL = DV / COLS, D = feature_dim(DP);
     constexpr int ZS = (NT + NW - 1) / NW;   // K-state tiles of a wave
-    __shared__ __align__(16) float kt[2][DP][LD], qt[2][INCREMENT ? 1 : DP][LD];
+    constexpr int IT = image_tiles(DP), IU = image_unroll(DP);
+    static_assert(NT % IT == 0 && IT % IU == 0, "");
+    struct Rows { float kt[2][DP][LD], qt[2][INCREMENT ? 1 : DP][LD]; };
+    __shared__ __align__(16) union { Rows rows; float image[IT][16][IMG_LD]; } lds;
+    auto &kt = lds.rows.kt;
+    auto &qt = lds.rows.qt;
     __shared__ __align__(16) float zl[NW][ZS][16];
     __shared__ float den[2][NW][16];
 
@@ -137,7 +147,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     const T *qu = q + (size_t)u * N * DP, *ku = k + (size_t)u * N * DP;
     const T *vu = v + (size_t)u * N * DV + col0 + 16 * w + n;
     T *yu = y + (size_t)u * N * DV + col0 + 16 * w;
-    float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 + 16 * w + n : nullptr;
+    float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 : nullptr;
     float *zu = state ? state + (size_t)u * state_stride(DP, DV) + (size_t)D * DV : nullptr;
     float *entries = ws ? ws + ((size_t)u * SL + slice) * G * entry_floats(DP) : nullptr;
     auto entry_s = [&](int e) { return entries + (size_t)e * entry_floats(DP) + (size_t)w * NT * 256 + 4 * lane; };
@@ -164,19 +174,101 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     float z[ZS];   // lane n (any g): row n of tile ZS-th tile w, w + NW, ..
     for_n<NT>([&](auto t) { S[t.value] = zero4(); });
     for_n<ZS>([&](auto i) { z[i.value] = 0.f; });
+    // The state buffer moves through LDS, some tiles at a time: a wave reaches its registers' places there at constant offsets, and
+    // the workgroup moves 16-byte pieces of rows in short loops: thread (w, j, c) row (w, j) of a tile, columns 4 c .. 4 c + 3.  (Element
+    // by element from the registers it was unrolled code, which a short call runs once and waits for while it is fetched: 64 units
+    // from a state, d' 32, d_v 64, 1 token 52 -> 31 us; d' 24, d_v 128, 16 tokens 62 -> 34.)
+    const int s_j = lane >> 4, s_c = 4 * (lane & 15);
+    auto next_tile = [](int &A, int &B) {
+        if (++B == NB) B = ++A;
+    };
+    auto z_canon = [&](int p) {   // row p of the K-state's tiles
+        int A = 0, B = p >> 4;
+        while (B >= NB - A) B -= NB - A++;
+        return canon<DP>(A, A + B, (p >> 2) & 3, p & 3);
+    };
     // the caller's state, symmetric part, into S and z
     auto import_state = [&]() {
-        for_tiles<NB>([&](auto t, auto A, auto B) {
-            for_n<4>([&](auto r) {
-                const Canon c = canon<DP>(A.value, B.value, g, r.value);
-                if (c.r1 >= 0) S[t.value][r.value] = (0.5f / c.scale) * (Su[(size_t)c.r1 * DV] + Su[(size_t)c.r2 * DV]);
-            });
-            if (t.value % NW == w) {
-                const Canon c = canon<DP>(A.value, B.value, n >> 2, n & 3);
-                if (c.r1 >= 0) z[t.value / NW] = (0.5f / c.scale) * (zu[c.r1] + zu[c.r2]);
+        for (int p = tid; p < 16 * NT; p += 64 * NW) {
+            const Canon c = z_canon(p);
+            zl[(p >> 4) % NW][(p >> 4) / NW][p & 15] = c.r1 < 0 ? 0.f : (0.5f / c.scale) * (zu[c.r1] + zu[c.r2]);
+        }
+        int A = 0, B = 0;
+        for_n<NT / IT>([&](auto part) {
+#pragma unroll 1
+            for (int i0 = 0; i0 < IT; i0 += IU) {
+                f32x4 x[IU][2];
+                float scale[IU];
+                for_n<IU>([&](auto i) {
+                    const Canon c = canon<DP>(A, B, w, s_j);
+                    x[i.value][0] = *reinterpret_cast<const f32x4 *>(Su + (size_t)max(c.r1, 0) * DV + s_c);
+                    x[i.value][1] = *reinterpret_cast<const f32x4 *>(Su + (size_t)max(c.r2, 0) * DV + s_c);
+                    scale[i.value] = c.r1 < 0 ? 0.f : 0.5f / c.scale;
+                    next_tile(A, B);
+                });
+                for_n<IU>([&](auto i) {
+                    const f32x4 sum = (x[i.value][0] + x[i.value][1]) * scale[i.value];
+                    *reinterpret_cast<f32x4 *>(&lds.image[i0 + i.value][4 * w + s_j][s_c]) = scale[i.value] == 0.f ? zero4() : sum;
+                });
             }
-            asm volatile("" ::: "memory");   // (one tile's loads at a time: registers)
+            __syncthreads();
+            for_n<IT>([&](auto i) {
+                for_n<4>([&](auto r) { S[part.value * IT + i.value][r.value] = lds.image[i.value][4 * g + r.value][16 * w + n]; });
+            });
+            __syncthreads();
         });
+        for_n<ZS>([&](auto i) { z[i.value] = NW * i.value + w < NT ? zl[w][i.value][n] : 0.f; });
+    };
+    // Both rows of a pair.  A state that is not symmetric (none of this recurrence is) keeps its antisymmetric part, which
+    // decays like the rest: nothing is added to it, so over the N tokens of the call by gamma^N.
+    auto export_state = [&]() {
+        const float g_all = decay ? powf(gm, (float)N) : 1.f;
+        auto half_difference = [&](float a, float b) { return a == b ? 0.f : 0.5f * (a - b) * g_all; };   // (equal infinities: none)
+        int A = 0, B = 0;
+        for_n<NT / IT>([&](auto part) {
+            for_n<IT>([&](auto i) {
+                for_n<4>([&](auto r) { lds.image[i.value][4 * g + r.value][16 * w + n] = S[part.value * IT + i.value][r.value]; });
+            });
+            __syncthreads();
+#pragma unroll 1
+            for (int i0 = 0; i0 < IT; i0 += IU) {
+                f32x4 d[IU];
+                float *p[IU][2];
+                float scale[IU];
+                for_n<IU>([&](auto i) {
+                    const Canon c = canon<DP>(A, B, w, s_j);
+                    p[i.value][0] = Su + (size_t)max(c.r1, 0) * DV + s_c;
+                    p[i.value][1] = Su + (size_t)max(c.r2, 0) * DV + s_c;
+                    scale[i.value] = c.r1 < 0 ? 0.f : c.scale;
+                    d[i.value] = zero4();
+                    next_tile(A, B);
+                });
+                if (init)
+                    for_n<IU>([&](auto i) {
+                        const f32x4 x1 = *reinterpret_cast<const f32x4 *>(p[i.value][0]), x2 = *reinterpret_cast<const f32x4 *>(p[i.value][1]);
+                        for_n<4>([&](auto k) { d[i.value][k.value] = half_difference(x1[k.value], x2[k.value]); });
+                    });
+                for_n<IU>([&](auto i) {
+                    if (scale[i.value] == 0.f) return;   // (a zero row; a row of its own is written twice)
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(&lds.image[i0 + i.value][4 * w + s_j][s_c]) * scale[i.value];
+                    *reinterpret_cast<f32x4 *>(p[i.value][0]) = x + d[i.value];
+                    *reinterpret_cast<f32x4 *>(p[i.value][1]) = x - d[i.value];
+                });
+            }
+            __syncthreads();
+        });
+        if (col0 != 0) return;
+        for_n<ZS>([&](auto i) {
+            if (g == 0) zl[w][i.value][n] = z[i.value];
+        });
+        __syncthreads();
+        for (int p = tid; p < 16 * NT; p += 64 * NW) {
+            const Canon c = z_canon(p);
+            if (c.r1 < 0) continue;
+            const float s = zl[(p >> 4) % NW][(p >> 4) / NW][p & 15] * c.scale, d = init ? half_difference(zu[c.r1], zu[c.r2]) : 0.f;
+            zu[c.r1] = s + d;
+            if (c.r2 != c.r1) zu[c.r2] = s - d;
+        }
     };
     auto store_entry = [&](int e) {
         float *p = entry_s(e), *pz = entry_z(e);
@@ -408,35 +500,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     if (INCREMENT) {
         store_entry(1 + seg);
     } else if (state && seg == G - 1) {
-        // Both rows of a pair.  A state that is not symmetric (none of this recurrence is) keeps its antisymmetric part,
-        // which decays like the rest: nothing is added to it, so over the N tokens of the call by gamma^N.
-        const float g_all = decay ? powf(gm, (float)N) : 1.f;
-        auto half_difference = [](float a, float b) { return a == b ? 0.f : 0.5f * (a - b); };   // (equal infinities: none)
-        int g2 = g, n2 = n;   // (hidden from the compiler, which would keep the rows' offsets alive through the loop)
-        asm volatile("" : "+v"(g2), "+v"(n2));
-        for_tiles<NB>([&](auto t, auto A, auto B) {
-            for_n<4>([&](auto r) {
-                const Canon c = canon<DP>(A.value, B.value, g2, r.value);
-                if (c.r1 >= 0) {
-                    const float s = S[t.value][r.value] * c.scale;
-                    float d = 0.f;
-                    if (init) d = half_difference(Su[(size_t)c.r1 * DV], Su[(size_t)c.r2 * DV]) * g_all;
-                    Su[(size_t)c.r1 * DV] = s + d;
-                    if (c.r2 != c.r1) Su[(size_t)c.r2 * DV] = s - d;
-                }
-            });
-            if (t.value % NW == w && g == 0 && col0 == 0) {
-                const Canon c = canon<DP>(A.value, B.value, n2 >> 2, n2 & 3);
-                if (c.r1 >= 0) {
-                    const float s = z[t.value / NW] * c.scale;
-                    float d = 0.f;
-                    if (init) d = half_difference(zu[c.r1], zu[c.r2]) * g_all;
-                    zu[c.r1] = s + d;
-                    if (c.r2 != c.r1) zu[c.r2] = s - d;
-                }
-            }
-            asm volatile("" ::: "memory");
-        });
+        export_state();
     }
 }
 
