@@ -340,3 +340,10 @@ def test_calls_release_the_interpreter_lock(based, tmp_path):
         stop.set()
         thread.join()
     assert t1 - t0 >= 0.4 and any(t0 + 0.1 < t < t1 - 0.1 for t in ticks)
+
+
+# sequences that end before the largest window does: the tiles in front of them are skipped, by all waves or by some
+@pytest.mark.parametrize("dh,N", [(64, 15), (64, 113), (128, 33), (128, 70)])
+@pytest.mark.parametrize("rotary", [False, True])
+def test_window_fp32_short_sequences(based, dh, N, rotary):
+    window_case(based, "f32", dh, 128, 3, N, dh ** -0.5, rotary)
