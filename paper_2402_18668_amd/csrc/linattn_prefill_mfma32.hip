@@ -27,7 +27,7 @@
 //
 // Long sequences / few units: G segments; a first launch computes each segment's state increment, segment 0's starting from
 // the caller's state, and the main launch starts segment g from the sum of the entries before it (read at full width: all
-// loads of an entry in flight together, the segments of a unit on one XCD).
+// loads of an entry in flight together).
 //
 // What bounds it: per chunk and SIMD 44 matrix instructions (1400 cycles) and 600 vector instructions (half of them the products,
 // conversions and the state's rounding to bf16), which share the register ports, and 290 KB through LDS, a third of it the
@@ -185,7 +185,7 @@ template <bool INC>
 __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, float *state, int has_init, int import_only, int init_in_entry, float *__restrict__ ws,
-    int N, int dv, SegTable segs, int G)
+    int N, int dv, SegTable segs, int G, int groups)
 {
     __shared__ __align__(16) Lds lds;
 
@@ -204,16 +204,12 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const int slices = dv / COLS;
     const int gseg = !INC ? G : import_only ? 1 : G - 1;
     int bid = blockIdx.x;
-    // the segments of a unit on one XCD (workgroup index mod 8), whose L2 then holds its entries
-    const int groups = gridDim.x / gseg;
-    int seg;
-    if (groups % 8 == 0) {
-        seg = (bid >> 3) % gseg;
-        bid = ((bid >> 3) / gseg << 3) + (bid & 7);
-    } else {
-        seg = bid % gseg;
-        bid /= gseg;
-    }
+    // The segments of a group on one XCD (workgroup index mod 8), whose L2 then holds its entries.  The grid has room for a multiple
+    // of 8 groups; what is over leaves at once.  (Segment after segment of a group on different XCDs, their entries read from
+    // memory: 60 groups of 1024 tokens in 4 segments 56 us instead of 46, of 448 45 instead of 32.)
+    const int seg = (bid >> 3) % gseg;
+    bid = ((bid >> 3) / gseg << 3) + (bid & 7);
+    if (bid >= groups) return;
     const int slice = bid % slices;
     const int u = bid / slices;
     const int col0 = slice * COLS;
@@ -754,15 +750,19 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 
 // Segments: at most one round of the chip (one workgroup per CU).  With few units the chain of an increment, up to G - 1 entries
 // to sum and the main pass is shortest near sqrt(1.5 chunks) segments (16 units, N 2048: 4 segments 61 us, 8 47, 10 45, 16 50; N 777:
-// 1 59, 3 38, 6 32, 12 36); from 8 chunks on it is shorter than one segment.
+// 1 59, 3 38, 6 32, 12 36); from 8 chunks on it is shorter than one segment.  The more groups, the fewer segments there is room for and the
+// more entries move at a time, so the longer a sequence has to be (1 segment against what there is room for, us: 48 groups N 256 25.8,
+// 24.5; 64 groups N 256 26.2, 26.2, N 320 30.4, 29.0; 80 groups N 256 26.5, 27.3, N 320 30.6, 30.0; 86 groups N 448 38.9, 37.9; 100 groups
+// N 384 34.9, 36.3, N 512 43.2, 41.8; 128 groups N 448 39.7, 40.5, N 512 43.7, 43.5).
 static int pick_segments(int U, int N, int dv)
 {
-    const int groups = U * (dv / COLS), chunks = (N + C - 1) / C;
-    int G = 256 / groups;
+    const int groups = U * (dv / COLS), chunks = (N + C - 1) / C, room = 256 / groups;
+    if (chunks < (room >= 5 ? 8 : room >= 3 ? 10 : 16)) return 1;
+    int G = room;
     const int chain = (int)(sqrtf(1.5f * chunks) + 0.5f);
     if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
-    return G < 1 || chunks < 8 ? 1 : G;
+    return G < 1 ? 1 : G;
 }
 
 static int make_segments(int N, int G, SegTable &t)
@@ -810,18 +810,19 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
     const int G = make_segments(N, pick_segments(U, N, dv), segs);
     const uint16_t *q16 = (const uint16_t *)q, *k16 = (const uint16_t *)k, *v16 = (const uint16_t *)v;
     float *ws = static_cast<float *>(workspace);
-    if ((long long)U * slices * G >= (1ll << 31)) return hipErrorInvalidValue;
+    const int groups = U * slices, blocks = (groups + 7) / 8 * 8;   // (see the kernel's workgroup index)
+    if (((long long)groups + 7) * G >= (1ll << 31)) return hipErrorInvalidValue;
     // Several workgroups of a unit read the caller's state and one overwrites it (at d_v = 128 also its K-state): then it goes
     // through entry 0, which the first launch writes.
     const int in_entry = (has_init & 1) && G * slices > 1;
     if (G > 1 || in_entry) {
-        hipLaunchKernelGGL((prefill_kernel<true>), dim3((unsigned)(U * slices * (G > 1 ? G - 1 : 1))), dim3(NT), 0, s, q16, k16,
-                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G);
+        hipLaunchKernelGGL((prefill_kernel<true>), dim3((unsigned)(blocks * (G > 1 ? G - 1 : 1))), dim3(NT), 0, s, q16, k16,
+                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G, groups);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((prefill_kernel<false>), dim3((unsigned)(U * slices * G)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
-                       state, has_init, 0, in_entry, ws, N, dv, segs, G);
+    hipLaunchKernelGGL((prefill_kernel<false>), dim3((unsigned)(blocks * G)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
+                       state, has_init, 0, in_entry, ws, N, dv, segs, G, groups);
     return hipGetLastError();
 }
 

@@ -347,3 +347,20 @@ def test_calls_release_the_interpreter_lock(based, tmp_path):
 @pytest.mark.parametrize("rotary", [False, True])
 def test_window_fp32_short_sequences(based, dh, N, rotary):
     window_case(based, "f32", dh, 128, 3, N, dh ** -0.5, rotary)
+
+
+# bf16 d' = 32 prefill: numbers of (unit, 64 columns) groups that are not a multiple of 8 (the grid has room for one) or just are, around
+# the sequence lengths from which they are cut into segments
+@pytest.mark.parametrize("U,dv,N", [(1, 64, 255), (1, 64, 260), (45, 64, 289), (60, 64, 288), (60, 64, 289), (100, 64, 480), (100, 64, 481),
+                                    (24, 128, 290), (37, 128, 330), (65, 128, 300)])
+def test_prefill_dp32_group_counts(based, U, dv, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    state = based.alloc_state(1, U, 32, dv)
+    y = down(based.prefill(*(up(a, "bf16", (1, U, N, d)) for a, d in ((q, 32), (k, 32), (v, dv))), state=state)).reshape(U, N, dv)
+    at = np.unique([0, min(U - 1, 7), U // 2, U - 1])
+    check_close(rows(y[at]), rows(oracle.linattn_quadratic(q[at], k[at], v[at])), TOL["bf16"], "y")
+    S, z = based.state_export(state, 1, U, 32, dv)
+    Sw, zw = oracle.linattn_state(k[at], v[at])
+    check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
+    check_close(down(z)[0, at], zw, TOL["bf16"], "z")
