@@ -1004,20 +1004,28 @@ __global__ __launch_bounds__(64 * (NC + 4), 2) void prefill_mfma_kernel(
 namespace {
 
 // Segments per sequence.  At most what fills the chip once (one workgroup per CU fits): beyond that more segments only add
-// increment work and workspace traffic (128 units of 2048 tokens, d_v 64: 1 segment 60 us, 2 52, 3 and 4 60).  With few
-// units the chip is not the limit: G segments make a chain of chunks / G increment chunks, G entries to sum up and
-// chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment 28 us, 3
-// 22, 5 19, 8 21; 24 chunks 2 39, 4 27, 8 23, 12 27; 64 chunks 8 35, 12 32, 16 36); below 6 chunks a second segment does
-// not pay for its hand-over (4 chunks: 1 segment 14.0 us, 3 15.1).
+// increment work and workspace traffic (d_v 64, 2048 tokens: 128 units 1 segment 59 us, 2 45, 3 59; 86 units 59, 44, 44; 129 units 59,
+// 66, 59; 200 units 60, 80, 80).  With few units the chip is not the limit: G segments make a chain of chunks / G increment chunks,
+// G entries to sum up and chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment
+// 28 us, 3 22, 5 19, 8 21; 24 chunks 2 39, 4 27, 8 23, 12 27; 64 chunks 8 35, 12 32, 16 36); below 6 chunks a second segment does not
+// pay for its hand-over (4 chunks: 1 segment 14.0 us, 3 15.1).  Two exceptions:
+// - Short sequences: increments and main pass, U (2 G - 1) workgroups, in one round of the chip, since what a second round adds is
+//   more than the chain saves (d_v 128, 512 tokens, 60 units: 1 segment 21.8 us, 2 21.8, 3 22.4, 4 25.0; 384 tokens, 128 units: 1 19.7, 2
+//   22.0; d_v 64, where the hand-over is half as much, 448 tokens, 60 units: 2 16.6, 4 18.6).
+// - Long sequences, 86 .. 102 units: 5 U workgroups, three segments, are two rounds of the chip like the two segments' 3 U (d_v
+//   64, 100 units: 4096 tokens 2 segments 83.7 us, 3 81.0; 8192 163, 151; 110 units 8192 163, 188; d_v 128, 86 units: 4096 95.9, 93.7; 16384
+//   371, 345).
 int pick_segments(int U, int N, int dv)
 {
-    (void)dv;
     const int chunks = (N + C - 1) / C;
+    if (chunks < 6) return 1;
     int G = 256 / U;
+    if (G == 2 && 5 * U <= 512 && chunks >= 64) G = 3;
+    if (chunks < (dv == 128 ? 10 : 8)) G = (256 / U + 1) / 2;
     const int chain = (int)(sqrtf(2.f * (float)chunks) + 0.5f);
     if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
-    return G < 1 || chunks < 6 ? 1 : G;
+    return G < 1 ? 1 : G;
 }
 
 // Segment boundaries.  The main pass starts segment g by summing g workspace entries and the last

@@ -364,3 +364,20 @@ def test_prefill_dp32_group_counts(based, U, dv, N):
     Sw, zw = oracle.linattn_state(k[at], v[at])
     check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
+
+
+# bf16 d' = 16 prefill: the exceptions of the rule for the number of segments (few chunks, where all workgroups have to fit at once; long
+# sequences of 86 to 102 units in three segments), and its neighbours
+@pytest.mark.parametrize("U,dv,N", [(60, 64, 380), (60, 128, 600), (86, 128, 513), (48, 128, 384), (86, 64, 4033), (102, 64, 4100), (103, 64, 4100),
+                                    (100, 128, 4097)])
+def test_prefill_segment_rule(based, U, dv, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    state = based.alloc_state(1, U, 16, dv)
+    y = down(based.prefill(*(up(a, "bf16", (1, U, N, d)) for a, d in ((q, 16), (k, 16), (v, dv))), state=state)).reshape(U, N, dv)
+    at = np.unique([0, U - 1])
+    check_close(rows(y[at]), rows(oracle.linattn_quadratic(q[at], k[at], v[at])), TOL["bf16"], "y")
+    S, z = based.state_export(state, 1, U, 16, dv)
+    Sw, zw = oracle.linattn_state(k[at], v[at])
+    check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
+    check_close(down(z)[0, at], zw, TOL["bf16"], "z")
