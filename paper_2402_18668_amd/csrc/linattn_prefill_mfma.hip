@@ -351,8 +351,8 @@ __device__ __forceinline__ void prefill_body(
     // query tile 0, 1 = key tile 0 against query tile 1, 2 = key tile 1 against query tile 1 (0 and 2 are
     // cut by the diagonal).  P^T = mask(1 + A^T + A^T^2 / 2), A^T = K Q^T: lane (g, n) is query 32 qt + n,
     // register r is key 32 kt + 8 (r / 4) + 4 g + r % 4.  Keys past the end of the segment come after every
-    // valid query and fall to the causal mask.  Built by the consumer waves (one block each), which wait
-    // for the producers otherwise.
+    // valid query and fall to the causal mask.  Built by the consumer waves (one block each) at d_v 128, which wait
+    // for the producers otherwise, and by the producers at d_v 64, which has only two consumers.
     auto build_block = [&](const int b, const int bb) {
         const int kt = bb == 2 ? 1 : 0, qt = bb == 0 ? 0 : 1;
         const bool diag = bb != 1;
@@ -376,7 +376,7 @@ __device__ __forceinline__ void prefill_body(
         dsum += __shfl_xor(dsum, 32, 64);
         if (g == 0) lds.den[b][1 + kt][32 * qt + n] = dsum;
     };
-    // which blocks a consumer builds: four consumers: c = 0..2 one each; two: 0 -> blocks 0 and 1, 1 -> block 2
+    // which blocks a consumer builds: of four consumers c = 0..2 one each
     auto build_my_blocks = [&](const int b) {
         if (NC == 4) {
 #pragma unroll
@@ -670,28 +670,22 @@ __device__ __forceinline__ void prefill_body(
             // ---- staging: global -> registers -> LDS --------------------------------------------
             // A chunk of V is one contiguous block of 64 rows x DV columns: 16-byte piece p = ptid + NP j
             // (j = 0..3) is row p / (DV / 8), columns 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128
-            // pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  With four producer waves the
-            // first two stage K and the other two Q; with two every thread stages one piece of each.
+            // pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  The first two waves stage K, the
+            // other two Q.
             constexpr int VPR = DV / 8;   // pieces per V row
-            constexpr bool kBoth = false;
             constexpr int NVP = VPR * C / NP;   // V pieces per producer thread
             const int xp = ptid & 127;
-            const bool is_k = kBoth || ptid < 128;
+            const bool is_k = ptid < 128;
             const int x_tok = xp >> 1, x_h = xp & 1;
-            u32x4 raw_k = {0u, 0u, 0u, 0u}, raw_q = {0u, 0u, 0u, 0u};   // four waves: raw_k is the thread's one piece
+            u32x4 raw_x = {0u, 0u, 0u, 0u};   // the thread's piece of K or Q
             u32x4 raw_v[NVP];
             // Loads are unconditional (rows past the end of the segment re-read its last row and are
             // zeroed when staged): a conditional load would have the compiler pre-zero its destination
             // registers, and before that write it waits for every memory operation still in flight.
             auto load_raw = [&](int tok0) {
                 const int tok = min(tok0 + x_tok, tok_end - 1);
-                if (kBoth) {
-                    raw_k = *reinterpret_cast<const u32x4 *>(ku + (size_t)tok * DP + 8 * x_h);
-                    if (MODE == 0) raw_q = *reinterpret_cast<const u32x4 *>(qu + (size_t)tok * DP + 8 * x_h);
-                } else {
-                    const uint16_t *src = (is_k || MODE != 0) ? ku : qu;   // increment pass: q is not needed
-                    raw_k = *reinterpret_cast<const u32x4 *>(src + (size_t)tok * DP + 8 * x_h);
-                }
+                const uint16_t *src = (is_k || MODE != 0) ? ku : qu;   // increment pass: q is not needed
+                raw_x = *reinterpret_cast<const u32x4 *>(src + (size_t)tok * DP + 8 * x_h);
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
                     const int p = ptid + NP * j;
@@ -725,14 +719,8 @@ __device__ __forceinline__ void prefill_body(
             };
             auto stage = [&](int tok0, int b) {
                 const bool valid = tok0 + x_tok < tok_end;
-                if (kBoth) {
-                    stage_k(raw_k, valid);
-                    if (MODE == 0) stage_q(raw_q);
-                } else if (is_k) {
-                    stage_k(raw_k, valid);
-                } else if (MODE == 0) {
-                    stage_q(raw_k);
-                }
+                if (is_k) stage_k(raw_x, valid);
+                else if (MODE == 0) stage_q(raw_x);
                 const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
@@ -878,9 +866,9 @@ __device__ __forceinline__ void prefill_body(
                 }
             };
             // The producers' share of the operands of one chunk, into generation b (the intra-chunk blocks
-            // are built by the consumers, which have the time).  Four producer waves: 0 = denominators; 1 =
-            // phi(Q) of both query tiles; 2 = phi(K) of token slabs 0, 1; 3 = phi(K) of token slabs 2, 3.
-            // Two: 0 = denominators, phi(Q); 1 = phi(K).  Increment pass: phi(K) only.
+            // are built by the consumers at d_v 128, which have the time).  Wave 0: denominators, phi(Q) of query
+            // tile 0; 1: phi(Q) of query tile 1; 2: phi(K) of token slabs 0, 1; 3: phi(K) of token slabs 2, 3; at d_v 64
+            // 1 .. 3 also an intra-chunk block each.  Increment pass: phi(K) only.
             auto build = [&](const int b) {
                 if (MODE == 0) {
                     if (c == 0) {

@@ -26,7 +26,6 @@ namespace based {
 
 namespace lin {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -37,11 +36,6 @@ constexpr int kXcds = 8;
 constexpr int KQ = 64;         // K is a multiple of this
 constexpr int NQ = 128;        // N is a multiple of this
 
-__device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-}
 __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
@@ -90,10 +84,10 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
 
 // ---- tiles -------------------------------------------------------------------------------------------------
 // WM x WN waves compute a BM x BN tile (tokens x features), each a (BM / WM) x (BN / WN) part of it in MFMA tiles of
-// 32 x 32.
+// 16 x 16.
 //
 // Staging.  The rows go from memory to LDS directly (the 16-byte LDS DMA: no registers, no LDS write instructions), into
-// a ring of ST stages of BK columns.  One instruction of a wave moves 1 KB: 64 lanes x 16 bytes land side by
+// a ring of ST stages of BK = 64 columns.  One instruction of a wave moves 1 KB: 64 lanes x 16 bytes land side by
 // side in LDS, i.e. whole rows of BK elements without padding, so the bank spread comes from a permutation
 // instead: 16-byte piece c of row r sits at place c ^ f(r), which the lanes produce for free by choosing what
 // they fetch; the 8 rows that a group of lanes reads at a time then cover all banks.
@@ -111,12 +105,13 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
 // set by power (q / k / v projection of the 1.3B-shaped layer, 32768 x 1792 x 2560, on one GPU: 271 against 252 us; both run
 // at 1.85 GHz).  The same shape in steps: registers-staged 256 x 256 tiles of 32x32x16 284 us, DMA 276, reads and DMA
 // between the matrix instructions 268, 16x16x32 252, the DMA of a stage out by 6/8 of a step 240 us = 1255 TFLOP/s.
-template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_, int MT_ = 16, int SPREAD_ = 8> struct Tile {
-    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_, MT = MT_, SPREAD = SPREAD_;
+constexpr int MT = 16;         // MFMA tile: 16 x 16, in
+constexpr int SD = 32;         // slabs of 32 (the 16x16x32 instruction)
+constexpr int BK = 64;         // columns of a stage
+template <int BM_, int BN_, int WM_, int WN_, int ST_, int SPREAD_ = 8> struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_, SPREAD = SPREAD_;
     static constexpr int NW = WM * WN, NT = 64 * NW;
     static constexpr int TI = BM / WM / MT, TJ = BN / WN / MT;   // MFMA tiles of a wave: tokens, features
-    static constexpr int SD = MT == 32 ? 16 : 32;                // depth of a slab: 32x32x16 or 16x16x32
-    using Acc = std::conditional_t<MT == 32, f32x16, f32x4>;
     static constexpr int CPR = BK / 8;                           // 16-byte pieces per staged row
     static constexpr int RPI = 64 / CPR;                         // rows one DMA instruction moves
     static constexpr int AP = BM / RPI / NW, BP = BN / RPI / NW, P = AP + BP;   // instructions of a wave per step
@@ -154,13 +149,13 @@ template <typename T, bool SPLIT_OUT, bool HEADS_IN>
 __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__restrict__ x, const uint16_t *__restrict__ W,
                                           uint16_t *__restrict__ y, int M, int K, int N, int row0, int col0, const HeadLayout &hl)
 {
-    constexpr int MT = T::MT, TI = T::TI, TJ = T::TJ, BK = T::BK, KS = T::KS, P = T::P, ST = T::ST, CPR = T::CPR;
+    constexpr int TI = T::TI, TJ = T::TJ, KS = T::KS, P = T::P, ST = T::ST, CPR = T::CPR;
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane / T::MT, n = lane % T::MT;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane / MT, n = lane % MT;
     const int wm = w / T::WN, wn = w % T::WN;
 
     // permutation of the 16-byte pieces of a row
-    auto swz = [](int row) { return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
+    auto swz = [](int row) { return (row >> 1) & 7; };
     // DMA instruction p of this wave: rows (p NW + w) RPI + lane / CPR of the tile of x (p < AP) or W
     // (byte offsets from the tile's first row, whose address is uniform and moves along K)
     uint32_t src[P];
@@ -195,19 +190,17 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
         if (HEADS_IN && (next * BK) % hl.d_in == 0) xbase += (size_t)(hl.seq_len - 1) * hl.d_in;
     };
 
-    // acc[j][i]: features 32 TJ wn + 32 j .. (rows of the MFMA tile) x tokens 32 TI wm + 32 i .. (columns)
-    typename T::Acc acc[TJ][TI];
+    // acc[j][i]: features 16 (TJ wn + j) .. (rows of the MFMA tile) x tokens 16 (TI wm + i) .. (columns)
+    f32x4 acc[TJ][TI];
 #pragma unroll
     for (int j = 0; j < TJ; ++j)
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int r = 0; r < MT * MT / 64; ++r) acc[j][i][r] = 0.f;
+        for (int i = 0; i < TI; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     u32x4 fw[2][TJ], fx[2][TI];
-    int off[KS];   // element offset of slab ks in this lane's row (rows 32 apart have the same permutation)
+    int off[KS];   // element offset of slab ks in this lane's row (rows 16 apart have the same permutation)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) off[ks] = n * BK + 8 * ((T::SD / 8 * ks + g) ^ swz(n));
+    for (int ks = 0; ks < KS; ++ks) off[ks] = n * BK + 8 * ((SD / 8 * ks + g) ^ swz(n));
     constexpr int NR = TI + TJ, NM = TI * TJ;   // operand reads and matrix instructions of a slab
     auto read_op = [&](int slot, int ks, int set, int r) {
         const uint16_t *a = reinterpret_cast<const uint16_t *>(lds + slot * T::STAGE) + off[ks];
@@ -263,8 +256,8 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
     }
     dma_barrier<0>();   // nothing lands in LDS any more
 
-    // epilogue: lane (g, n) of tile (j, i) holds token MT (TI wm + i) + n, features MT (TJ wn + j) + 64 / MT * 4 q + 4 g + e
-    // in register 4 q + e.  32 tokens at a time through this wave's staging rows, then whole row segments.
+    // epilogue: lane (g, n) of tile (j, i) holds token MT (TI wm + i) + n, features MT (TJ wn + j) + 4 g + e in register e.  32
+    // tokens at a time through this wave's staging rows, then whole row segments.
     constexpr int OUT_LD = T::OUT_LD, CP = MT * TJ / 8;   // 16-byte pieces per row
     uint16_t *out = reinterpret_cast<uint16_t *>(lds) + (size_t)w * 32 * OUT_LD;
     const int oc = lane % CP, orow = lane / CP;
@@ -283,14 +276,8 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int i = 0; i < IT; ++i)
-#pragma unroll
-                for (int q = 0; q < MT * MT / 256; ++q) {
-                    f32x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = acc[j][i32 * IT + i][4 * q + e];
-                    *reinterpret_cast<u32x2 *>(out + (size_t)(MT * i + n) * OUT_LD + MT * j + 256 / MT * q + 4 * g) =
-                        __builtin_bit_cast(u32x2, __builtin_convertvector(o, bf16x4));
-                }
+                *reinterpret_cast<u32x2 *>(out + (size_t)(MT * i + n) * OUT_LD + MT * j + 4 * g) =
+                    __builtin_bit_cast(u32x2, __builtin_convertvector(acc[j][i32 * IT + i], bf16x4));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own rows are complete in LDS
 #pragma unroll
         for (int it = 0; it < CP / 2; ++it) {
@@ -410,11 +397,11 @@ __global__ __launch_bounds__(64 * RW, 2) void linear_rows_kernel(const uint16_t 
 }
 
 // ---- choice of the variant ---------------------------------------------------------------------------------
-using T64 = Tile<64, 64, 2, 2, 64, 4>;                 // 64 KB of LDS: two workgroups per CU
-using T128N = Tile<128, 64, 2, 2, 64, 3>;              // 72 KB: two
-using T128 = Tile<128, 128, 2, 2, 64, 2, 16, 5>;       // 64 KB: two
-using T256 = Tile<256, 256, 2, 2, 64, 2, 16, 6>;       // 128 KB: one
-using T256H = Tile<128, 256, 2, 2, 64, 2, 16, 6>;
+using T64 = Tile<64, 64, 2, 2, 4>;                 // 64 KB of LDS: two workgroups per CU
+using T128N = Tile<128, 64, 2, 2, 3>;              // 72 KB: two
+using T128 = Tile<128, 128, 2, 2, 2, 5>;       // 64 KB: two
+using T256 = Tile<256, 256, 2, 2, 2, 6>;       // 128 KB: one
+using T256H = Tile<128, 256, 2, 2, 2, 6>;
 enum Variant { ROWS1, ROWS2, TILE64, TILE128N, TILE128, TILE256 };
 
 inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
