@@ -101,9 +101,9 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
 //
 // The operand reads of the next slab and the DMA pieces sit one by one between the matrix instructions: in bursts they
 // hold up the wave, and with it the matrix pipe, until the LDS and the memory pipeline have taken them.  16x16x32 matrix
-// instructions, not 32x32x16: they move half the accumulator registers per product, and under this load the clock is
-// set by power (q / k / v projection of the 1.3B-shaped layer, 32768 x 1792 x 2560, on one GPU: 271 against 252 us; both run
-// at 1.85 GHz).  The same shape in steps: registers-staged 256 x 256 tiles of 32x32x16 284 us, DMA 276, reads and DMA
+// instructions, not 32x32x16: they move half the accumulator registers per product, and under this load the chip does not hold
+// its clock (1.9 to 2.05 GHz by the cycle counters, 2.4 in the memory-bound kernels; q / k / v projection of the 1.3B-shaped layer,
+// 32768 x 1792 x 2560, on one GPU: 271 against 252 us).  The same shape in steps: registers-staged 256 x 256 tiles of 32x32x16 284 us, DMA 276, reads and DMA
 // between the matrix instructions 268, 16x16x32 252, the DMA of a stage out by 6/8 of a step 240 us = 1255 TFLOP/s.
 constexpr int MT = 16;         // MFMA tile: 16 x 16, in
 constexpr int SD = 32;         // slabs of 32 (the 16x16x32 instruction)
