@@ -185,7 +185,7 @@ template <bool INC>
 __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, float *state, int has_init, int import_only, int init_in_entry, float *__restrict__ ws,
-    int N, int dv, SegTable segs, int G, int groups)
+    int N, int dv, SegTable segs, int G, int groups, int local)
 {
     __shared__ __align__(16) Lds lds;
 
@@ -204,12 +204,18 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const int slices = dv / COLS;
     const int gseg = !INC ? G : import_only ? 1 : G - 1;
     int bid = blockIdx.x;
-    // The segments of a group on one XCD (workgroup index mod 8), whose L2 then holds its entries.  The grid has room for a multiple
-    // of 8 groups; what is over leaves at once.  (Segment after segment of a group on different XCDs, their entries read from
-    // memory: 60 groups of 1024 tokens in 4 segments 56 us instead of 46, of 448 45 instead of 32.)
-    const int seg = (bid >> 3) % gseg;
-    bid = ((bid >> 3) / gseg << 3) + (bid & 7);
-    if (bid >= groups) return;
+    // The segments of a group on one XCD (workgroup index mod 8), whose L2 then holds its entries, for the first `local` groups (a
+    // multiple of 8; what lies beyond the last group leaves at once); segment by segment over all XCDs for the rest.
+    int seg;
+    if (bid < local * gseg) {
+        seg = (bid >> 3) % gseg;
+        bid = ((bid >> 3) / gseg << 3) + (bid & 7);
+        if (bid >= groups) return;
+    } else {
+        bid -= local * gseg;
+        seg = bid / (groups - local);
+        bid = local + bid % (groups - local);
+    }
     const int slice = bid % slices;
     const int u = bid / slices;
     const int col0 = slice * COLS;
@@ -765,6 +771,17 @@ static int pick_segments(int U, int N, int dv)
     return G < 1 ? 1 : G;
 }
 
+// Groups whose segments share an XCD each: all of them (the grid has room for a multiple of 8) where the XCD with the most has a CU for
+// every segment, else as many as make up a multiple of 8, the others' segments going to all XCDs.  (Segment after segment of a group
+// on different XCDs, the entries read from memory: 60 groups of 1024 tokens in 4 segments 56 us instead of 45, of 448 45 instead of 32.
+// 41 groups in 6 segments, where one XCD would hold 36: all groups on their XCD 79 us at 2048 tokens and 228 at 8192, as here 54 and 143,
+// none 61 and 149.)
+static int local_groups(int groups, int G)
+{
+    const int most = (groups + 7) / 8;
+    return most * G <= 32 ? most * 8 : groups / 8 * 8;
+}
+
 static int make_segments(int N, int G, SegTable &t)
 {
     const int T = (N + C - 1) / C;
@@ -810,19 +827,19 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
     const int G = make_segments(N, pick_segments(U, N, dv), segs);
     const uint16_t *q16 = (const uint16_t *)q, *k16 = (const uint16_t *)k, *v16 = (const uint16_t *)v;
     float *ws = static_cast<float *>(workspace);
-    const int groups = U * slices, blocks = (groups + 7) / 8 * 8;   // (see the kernel's workgroup index)
+    const int groups = U * slices, local = local_groups(groups, G), blocks = local > groups ? local : groups;
     if (((long long)groups + 7) * G >= (1ll << 31)) return hipErrorInvalidValue;
     // Several workgroups of a unit read the caller's state and one overwrites it (at d_v = 128 also its K-state): then it goes
     // through entry 0, which the first launch writes.
     const int in_entry = (has_init & 1) && G * slices > 1;
     if (G > 1 || in_entry) {
         hipLaunchKernelGGL((prefill_kernel<true>), dim3((unsigned)(blocks * (G > 1 ? G - 1 : 1))), dim3(NT), 0, s, q16, k16,
-                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G, groups);
+                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G, groups, local);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((prefill_kernel<false>), dim3((unsigned)(blocks * G)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
-                       state, has_init, 0, in_entry, ws, N, dv, segs, G, groups);
+                       state, has_init, 0, in_entry, ws, N, dv, segs, G, groups, local);
     return hipGetLastError();
 }
 

@@ -349,10 +349,11 @@ def test_window_fp32_short_sequences(based, dh, N, rotary):
     window_case(based, "f32", dh, 128, 3, N, dh ** -0.5, rotary)
 
 
-# bf16 d' = 32 prefill: numbers of (unit, 64 columns) groups that are not a multiple of 8 (the grid has room for one) or just are, around
-# the sequence lengths from which they are cut into segments
+# bf16 d' = 32 prefill: numbers of (unit, 64 columns) groups that are not a multiple of 8 (the grid has room for one, or the rest is dealt out
+# over all XCDs) or just are, around the sequence lengths from which they are cut into segments
 @pytest.mark.parametrize("U,dv,N", [(1, 64, 255), (1, 64, 260), (45, 64, 289), (60, 64, 288), (60, 64, 289), (100, 64, 480), (100, 64, 481),
-                                    (24, 128, 290), (37, 128, 330), (65, 128, 300)])
+                                    (24, 128, 290), (37, 128, 330), (65, 128, 300), (33, 64, 1030), (9, 128, 3000),
+                                    (50, 64, 1025)])
 def test_prefill_dp32_group_counts(based, U, dv, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
     q, k, v = synth.linattn_inputs(wl, units=U, N=N)
