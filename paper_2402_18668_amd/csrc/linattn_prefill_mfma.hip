@@ -997,9 +997,12 @@ namespace {
 // G entries to sum up and chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment
 // 28 us, 3 22, 5 19, 8 21; 24 chunks 2 39, 4 27, 8 23, 12 27; 64 chunks 8 35, 12 32, 16 36); below 6 chunks a second segment does not
 // pay for its hand-over (4 chunks: 1 segment 14.0 us, 3 15.1).  Two exceptions:
-// - Short sequences: increments and main pass, U (2 G - 1) workgroups, in one round of the chip, since what a second round adds is
-//   more than the chain saves (d_v 128, 512 tokens, 60 units: 1 segment 21.8 us, 2 21.8, 3 22.4, 4 25.0; 384 tokens, 128 units: 1 19.7, 2
-//   22.0; d_v 64, where the hand-over is half as much, 448 tokens, 60 units: 2 16.6, 4 18.6).
+// - Below 10 chunks the hand-over is a large part of the call, the more so the wider the heads and the more units share the memory:
+//   one segment with more than 40 units (d_v 128, up to 7 chunks), 51 (d_v 64, 6 chunks) or 85 (d_v 128, and d_v 64 up to 7 chunks), and no
+//   more than three up to 8 chunks or with more than 42 units at d_v 128.  (us without and from a state; d_v 128, 384 tokens: 60
+//   units 1 segment 18.4, 20.6, 3 22.6, 23.3; 128 units 1 19.8, 22.9, 2 21.9, 26.1; 512 tokens, 60 units 1 21.9, 24.2, 3 22.6, 24.2, 4 25.5,
+//   25.8; 72 units 1 22.3, 24.7, 3 20.8, 24.7; d_v 64, 384 tokens, 60 units 1 15.7, 17.6, 3 16.6, 19.8; 512 tokens, 48 units 3 15.7, 18.6, 4 16.5,
+//   18.3.)
 // - Long sequences, 86 .. 102 units: 5 U workgroups, three segments, are two rounds of the chip like the two segments' 3 U (d_v
 //   64, 100 units: 4096 tokens 2 segments 83.7 us, 3 81.0; 8192 163, 151; 110 units 8192 163, 188; d_v 128, 86 units: 4096 95.9, 93.7; 16384
 //   371, 345).
@@ -1007,9 +1010,13 @@ int pick_segments(int U, int N, int dv)
 {
     const int chunks = (N + C - 1) / C;
     if (chunks < 6) return 1;
+    const bool wide = dv == 128;
     int G = 256 / U;
     if (G == 2 && 5 * U <= 512 && chunks >= 64) G = 3;
-    if (chunks < (dv == 128 ? 10 : 8)) G = (256 / U + 1) / 2;
+    if (chunks < 10) {
+        if (U > 85 ? wide || chunks < 8 : wide ? U > 40 && chunks < 8 : U > 51 && chunks < 7) return 1;
+        if (G > 3 && (chunks < 9 || (wide && U > 42))) G = 3;
+    }
     const int chain = (int)(sqrtf(2.f * (float)chunks) + 0.5f);
     if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
