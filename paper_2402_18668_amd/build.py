@@ -17,6 +17,7 @@ SOURCES = [
     "decode.hip",
     "linattn_prefill_f32.hip",
     "linattn_prefill_f32_dp32.hip",
+    "linattn_prefill_f32x3.hip",
     "linattn_prefill_mfma.hip",
     "linattn_prefill_mfma32.hip",
     "swa_prefill_f32.hip",

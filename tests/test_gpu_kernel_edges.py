@@ -66,6 +66,32 @@ def test_prefill_fp32_arithmetic(based, dtype, dp, dv, N1, N):
     check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
 
 
+# fp32 d' = 16 in three bf16 parts: its shortest call, chunks of 32 tokens with remainders, one and several segments, both widths, more
+# workgroups than the chip holds; values far from 1.  Sums of a few thousand terms in fp32 are off by 1e-7 (2-norm), two parts
+# instead of three by 1e-5.  The state's antisymmetric part, which no output sees, stays as it was.
+@pytest.mark.parametrize("H,dv,N1,N,exp", [(3, 64, 49, 98, 0), (2, 128, 64, 161, 90), (3, 64, 95, 224, -90), (1, 128, 130, 1321, 0), (2, 64, 257, 2400, 0),
+                                           (300, 128, 50, 107, 0)])
+def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
+    dp, D = 16, oracle.feature_dim(16)
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "dtype": "f32"})
+    q, k, v = synth.linattn_inputs(wl, units=H, N=N)
+    v = v * np.float32(2.0 ** exp)
+    odd = np.zeros((1, H, D, dv))
+    odd[0, :, 1 + dp + 2 * dp + 5] = 2.0 ** exp
+    odd[0, :, 1 + dp + 5 * dp + 2] = -2.0 ** exp
+    state = based.alloc_state(1, H, dp, dv)
+    based.state_import(state, up(odd, "f32"), up(np.zeros((1, H, D)), "f32"), dp)
+    got = [down(based.prefill(*(up(a[:, lo:hi], "f32", (1, H, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state,
+                              has_init=True)).reshape(H, hi - lo, dv) for lo, hi in ((0, N1), (N1, N))]
+    S, z = based.state_export(state, 1, H, dp, dv)
+    Sw, zw = oracle.linattn_state(k, v)
+    for a, want, what in ((np.concatenate(got, 1), oracle.linattn_quadratic(q, k, v), "y"), (down(S), Sw + odd[0].reshape(Sw.shape), "S"),
+                          (down(z), zw, "z")):
+        want = np.asarray(want, dtype=np.float64)
+        err = np.linalg.norm(a.reshape(want.shape) - want) / np.linalg.norm(want)
+        assert err < 1e-6, (what, err)
+
+
 # decay at the same edges: the last chunk holds fewer than 16 tokens, increments of several segments, gate
 @pytest.mark.parametrize("dtype,dp,dv,N", [("bf16", 32, 64, 90), ("f32", 32, 128, 300), ("bf16", 24, 128, 801), ("bf16", 16, 64, 31)])
 def test_prefill_decay_edges(based, dtype, dp, dv, N):
