@@ -324,24 +324,28 @@ __global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NW / 4 : T::NW / 2) 
 }
 
 // ---- a handful of tokens -------------------------------------------------------------------------------------
-// M of a few: bound by reading W once (and, for a small W, by the latency of one trip to memory).  A workgroup takes 16
-// output features and 16 TT tokens; its eight waves split K, each with the whole of its share of W (and x)
+// M of a few: bound by reading W once, by what a CU can take in of it and of x (which every workgroup reads whole), and by the latency of
+// one trip to memory.  A workgroup takes F output features (a sixteenth of the matrix instruction's columns each, the rest idle: it is
+// the CUs that count) and 16 TT tokens; its eight waves split K, each with the whole of its share of W (and x)
 // requested up front, straight into operand registers (MFMA 16x16x32: lane = row n of W / token n, 8
-// consecutive k); partial sums meet in LDS.  N / 16 workgroups of eight waves put the whole W in flight at once.
+// consecutive k); partial sums meet in LDS.  One workgroup of eight waves per CU puts the whole W in flight at once.  Where a thread's
+// results go (divisions by the sequence length and the head dim) is worked out while the rows are on their way: 9 tokens, d_model
+// 1792, H 16, d' 16, d_v 128: 5.2 and 5.7 us for the two projections with 16 features and that at the end, 5.0 and 5.1 with it here,
+// 4.55 and 4.53 with 10 and 8 features.
 constexpr int RW = 8;           // waves
 template <int TT, bool SPLIT_OUT, bool HEADS_IN>
 __global__ __launch_bounds__(64 * RW, 2) void linear_rows_kernel(const uint16_t *__restrict__ x,
                                                                  const uint16_t *__restrict__ W,
-                                                                 uint16_t *__restrict__ y, int M, int K, int N,
+                                                                 uint16_t *__restrict__ y, int M, int K, int N, int F,
                                                                  HeadLayout hl)
 {
     constexpr int G = TT == 4 ? 4 : 8;   // steps of 32 in flight per wave
     __shared__ __align__(16) float red[RW][16 * TT][20];   // (row stride 20: 16-byte writes of 16 rows spread over the banks)
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, n = lane & 15;
-    const int col0 = blockIdx.x * 16, row0 = blockIdx.y * 16 * TT;
+    const int col0 = blockIdx.x * F, row0 = blockIdx.y * 16 * TT;
 
-    const uint16_t *wp = W + (size_t)(col0 + n) * K + 8 * g;
+    const uint16_t *wp = W + (size_t)min(col0 + min(n, F - 1), N - 1) * K + 8 * g;   // (rows past the F-th re-read it)
     const uint16_t *xp[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) {   // rows past M re-read the last one
@@ -352,17 +356,40 @@ __global__ __launch_bounds__(64 * RW, 2) void linear_rows_kernel(const uint16_t 
     f32x4 acc[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int steps = K / 32, s1 = steps * (w + 1) / RW;
-    for (int s = steps * w / RW; s < s1; s += G) {
-        u32x4 a[G], b[G][TT];
+    const int steps = K / 32, s0 = steps * w / RW, s1 = steps * (w + 1) / RW;
+    u32x4 a[G], b[G][TT];
+    auto load = [&](int s) {
+        int head = HEADS_IN ? 32 * s / hl.d_in : 0, in_head = 32 * s - head * hl.d_in;   // (d_in is a multiple of 32)
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const int k0 = 32 * min(s + j, s1 - 1);
-            const size_t xo = HEADS_IN ? (size_t)(k0 / hl.d_in) * hl.seq_len * hl.d_in + k0 % hl.d_in : (size_t)k0;
+            const size_t xo = HEADS_IN ? (size_t)head * hl.seq_len * hl.d_in + in_head : (size_t)k0;
             a[j] = *reinterpret_cast<const u32x4 *>(wp + k0);
 #pragma unroll
             for (int t = 0; t < TT; ++t) b[j][t] = *reinterpret_cast<const u32x4 *>(xp[t] + xo);
+            if (HEADS_IN && s + j + 1 < s1) {
+                in_head += 32;
+                if (in_head >= hl.d_in) { in_head = 0; ++head; }
+            }
         }
+    };
+    if (s0 < s1) load(s0);
+    // where this thread's two features of one token go, worked out while the rows are on their way
+    const int tok = tid >> 3, f2 = 2 * (tid & 7), f = col0 + f2, row = row0 + tok;
+    const bool mine = tid < 128 * TT && row < M && f2 < F && f < N;
+    uint16_t *dst = y;
+    if (mine) {
+        if (SPLIT_OUT) {
+            const FeatDst fd = feat_dst(hl, y, f);
+            const RowPos rp = row_pos(row, hl.seq_len);
+            dst = fd.dst + (size_t)rp.b * fd.batch_stride + fd.fixed + (size_t)rp.t * fd.dh;
+        } else {
+            dst = y + (size_t)row * N + f;
+        }
+    }
+    asm volatile("" : "+v"(dst));
+    for (int s = s0; s < s1; s += G) {
+        if (s > s0) load(s);
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             if (s + j < s1) {   // uniform
@@ -377,23 +404,11 @@ __global__ __launch_bounds__(64 * RW, 2) void linear_rows_kernel(const uint16_t 
 #pragma unroll
     for (int t = 0; t < TT; ++t) *reinterpret_cast<f32x4 *>(&red[w][16 * t + n][4 * g]) = acc[t];
     __syncthreads();
-    if (tid < 128 * TT) {   // two features of one token per thread
-        const int tok = tid >> 3, f2 = 2 * (tid & 7), row = row0 + tok;
-        float s0 = 0.f, s1v = 0.f;
+    if (!mine) return;
+    float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
-        for (int v = 0; v < RW; ++v) { s0 += red[v][tok][f2]; s1v += red[v][tok][f2 + 1]; }
-        if (row < M) {
-            const uint32_t o = (uint32_t)f32_to_bf16_bits(s0) | ((uint32_t)f32_to_bf16_bits(s1v) << 16);
-            const int f = col0 + f2;
-            uint16_t *dst = y + (size_t)row * N + f;
-            if (SPLIT_OUT) {
-                const FeatDst fd = feat_dst(hl, y, f);
-                const RowPos rp = row_pos(row, hl.seq_len);
-                dst = fd.dst + (size_t)rp.b * fd.batch_stride + fd.fixed + (size_t)rp.t * fd.dh;
-            }
-            *reinterpret_cast<uint32_t *>(dst) = o;
-        }
-    }
+    for (int v = 0; v < RW; ++v) { sum0 += red[v][tok][f2]; sum1 += red[v][tok][f2 + 1]; }
+    *reinterpret_cast<uint32_t *>(dst) = (uint32_t)f32_to_bf16_bits(sum0) | ((uint32_t)f32_to_bf16_bits(sum1) << 16);
 }
 
 // ---- choice of the variant ---------------------------------------------------------------------------------
@@ -444,8 +459,12 @@ void launch_tile(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K
 template <int TT, bool SPLIT_OUT, bool HEADS_IN>
 void launch_rows(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N, const HeadLayout &hl, hipStream_t s)
 {
-    hipLaunchKernelGGL((linear_rows_kernel<TT, SPLIT_OUT, HEADS_IN>), dim3((unsigned)(N / 16), (unsigned)((M + 16 * TT - 1) / (16 * TT))),
-                       dim3(64 * RW), 0, s, x, W, y, M, K, N, hl);
+    // Features per workgroup: the smallest even number that leaves at most one workgroup per CU, 4 to 16.  (q / k / v and output projection of 9
+    // tokens, d_model 1792, 2560 and 1792 features, us: 16 5.0 and 5.1, 12 4.7 and 4.8, 10 4.55 and 4.64, 8 6.5 and 4.53, 6 6.2 and 6.3; 3
+    // tokens, d_model 512, 1024 features: 16 3.95, 8 3.4, 4 3.2.)
+    const int per = (N + 255) / 256, even = (per + 1) / 2 * 2, F = even < 4 ? 4 : even > 16 ? 16 : even;
+    hipLaunchKernelGGL((linear_rows_kernel<TT, SPLIT_OUT, HEADS_IN>), dim3((unsigned)((N + F - 1) / F), (unsigned)((M + 16 * TT - 1) / (16 * TT))),
+                       dim3(64 * RW), 0, s, x, W, y, M, K, N, F, hl);
 }
 template <bool SPLIT_OUT, bool HEADS_IN>
 hipError_t launch_variant(Variant v, const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N,

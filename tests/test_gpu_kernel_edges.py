@@ -32,6 +32,27 @@ def test_linear_tilings(based, M, K, N):
     check_close(y[at], oracle.linear(x[at], W), TOL["bf16"], f"linear {M}x{K}x{N}")
 
 
+# a decode batch: 4 to 16 features to a workgroup, the last one with fewer; K shorter than the eight waves share
+@pytest.mark.parametrize("M,K,N", [(1, 64, 1024), (9, 128, 1408), (16, 256, 2304), (5, 1792, 2560), (17, 64, 3328), (31, 320, 4224)])
+def test_linear_rows_features(based, M, K, N):
+    x, W = synth.linear_inputs(65, M, K, N)
+    check_close(down(based.linear(up(x, "bf16"), up(W, "bf16"))), oracle.linear(x, W), TOL["bf16"], f"linear {M}x{K}x{N}")
+
+
+# the head-major input's heads of one and of several steps, a decode batch
+@pytest.mark.parametrize("B,N,dm,H,dp,dv", [(1, 1, 1408, 12, 16, 128), (9, 1, 512, 8, 32, 64), (3, 7, 1152, 12, 16, 128), (2, 9, 640, 20, 32, 64)])
+def test_projection_rows_features(based, B, N, dm, H, dp, dv):
+    x, W = synth.linear_inputs(66, B * N, dm, H * (2 * dp + dv))
+    x = x.reshape(B, N, dm)
+    got = based.project_qkv(up(x, "bf16"), up(W, "bf16"), H, dp, dv)
+    f = H * dp
+    for name, t, Wp in zip("qkv", got, (W[:f], W[f:2 * f], W[2 * f:])):
+        check_close(rows(down(t)), rows(oracle.project_heads(x, Wp, H)), TOL["bf16"], f"project {name}")
+    yh = synth.linear_inputs(67, B * H * N, dv, 8)[0].reshape(B, H, N, dv)
+    Wo = synth.linear_inputs(68, 8, H * dv, dm)[1]
+    check_close(rows(down(based.project_out(up(yh, "bf16"), up(Wo, "bf16")))), rows(oracle.project_out(yh, Wo)), TOL["bf16"], "project out")
+
+
 # the same with head-major addressing: sequences that end inside a tile or a group of decode rows
 @pytest.mark.parametrize("B,N,dm,H,dp,dv", [(9, 1, 256, 4, 16, 64), (3, 7, 192, 4, 32, 64), (5, 13, 128, 8, 16, 128),
                                             (3, 203, 128, 16, 16, 128), (2, 1100, 1792, 16, 16, 128)])
