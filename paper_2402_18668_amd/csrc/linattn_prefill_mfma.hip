@@ -100,6 +100,9 @@ constexpr int WS_WAVE_SLOTS = 6;
 constexpr size_t kSlotFloats = 16 * 64;
 __host__ __device__ constexpr size_t entry_floats(int nc) { return (size_t)nc * WS_WAVE_SLOTS * kSlotFloats; }
 
+// Producer waves beside NC consumers.
+__host__ __device__ constexpr int producers(int nc) { return nc == 2 ? 6 : 4; }
+
 template <int NC>
 struct Lds {
     // the producers' own staging of the q and k rows of the chunk they are preparing
@@ -294,7 +297,7 @@ __device__ __forceinline__ void prefill_body(
     float *__restrict__ ws, unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls,
     unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
 {
-    constexpr int NPW = 4;            // producer waves
+    constexpr int NPW = producers(NC);
     constexpr int NP = 64 * NPW;      // producer threads
     constexpr int DV = 32 * NC;       // d_v
     constexpr int VR_LD = DV + 16;
@@ -668,27 +671,30 @@ __device__ __forceinline__ void prefill_body(
             }
 
             // ---- staging: global -> registers -> LDS --------------------------------------------
-            // A chunk of V is one contiguous block of 64 rows x DV columns: 16-byte piece p = ptid + NP j
-            // (j = 0..3) is row p / (DV / 8), columns 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128
-            // pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  The first two waves stage K, the
-            // other two Q.
+            // A chunk of V is one contiguous block of 64 rows x DV columns, in 16-byte pieces: piece p is row p / (DV / 8), columns
+            // 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128 pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  The
+            // first two waves stage K, the next two Q.  Of six producers these have the first 256 pieces of V as well, the other two
+            // the last 256.
             constexpr int VPR = DV / 8;   // pieces per V row
-            constexpr int NVP = VPR * C / NP;   // V pieces per producer thread
+            constexpr int NVP = VPR * C / 256;   // V pieces per producer thread
+            constexpr int VSTEP = NPW == 6 ? 128 : NP;
+            static_assert(NPW == 4 || (NPW == 6 && NVP == 2), "");
             const int xp = ptid & 127;
-            const bool is_k = ptid < 128;
+            const bool is_k = ptid < 128, has_x = NPW == 4 || ptid < 256;
             const int x_tok = xp >> 1, x_h = xp & 1;
             u32x4 raw_x = {0u, 0u, 0u, 0u};   // the thread's piece of K or Q
             u32x4 raw_v[NVP];
             // Loads are unconditional (rows past the end of the segment re-read its last row and are
             // zeroed when staged): a conditional load would have the compiler pre-zero its destination
             // registers, and before that write it waits for every memory operation still in flight.
+            auto v_piece = [&](int j) { return ptid + VSTEP * j; };
             auto load_raw = [&](int tok0) {
                 const int tok = min(tok0 + x_tok, tok_end - 1);
                 const uint16_t *src = (is_k || MODE != 0) ? ku : qu;   // increment pass: q is not needed
                 raw_x = *reinterpret_cast<const u32x4 *>(src + (size_t)tok * DP + 8 * x_h);
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
-                    const int p = ptid + NP * j;
+                    const int p = v_piece(j);
                     const int row = min(tok0 + p / VPR, tok_end - 1);
                     raw_v[j] = *reinterpret_cast<const u32x4 *>(vu + (size_t)row * DV + 8 * (p % VPR));
                 }
@@ -720,13 +726,14 @@ __device__ __forceinline__ void prefill_body(
             auto stage = [&](int tok0, int b) {
                 const bool valid = tok0 + x_tok < tok_end;
                 if (is_k) stage_k(raw_x, valid);
-                else if (MODE == 0) stage_q(raw_x);
+                else if (MODE == 0 && has_x) stage_q(raw_x);
                 const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
-                    const int p = ptid + NP * j;
+                    const int p = v_piece(j);
                     const int row = p / VPR;
-                    *reinterpret_cast<u32x4 *>(&lds.vrow[b][row][8 * (p % VPR)]) = tok0 + row < tok_end ? raw_v[j] : zero4;
+                    if (NPW == 4 || j == 0 || !has_x)
+                        *reinterpret_cast<u32x4 *>(&lds.vrow[b][row][8 * (p % VPR)]) = tok0 + row < tok_end ? raw_v[j] : zero4;
                 }
             };
 
@@ -867,28 +874,40 @@ __device__ __forceinline__ void prefill_body(
             };
             // The producers' share of the operands of one chunk, into generation b (the intra-chunk blocks
             // are built by the consumers at d_v 128, which have the time).  Wave 0: denominators, phi(Q) of query
-            // tile 0; 1: phi(Q) of query tile 1; 2: phi(K) of token slabs 0, 1; 3: phi(K) of token slabs 2, 3; at d_v 64
-            // 1 .. 3 also an intra-chunk block each.  Increment pass: phi(K) only.
+            // tile 0; 1: phi(Q) of query tile 1; 2: phi(K) of token slabs 0, 1; 3: phi(K) of token slabs 2, 3.  Of six
+            // (d_v 64), 0: denominators and the intra-chunk block off the diagonal; 1, 2: phi(Q); 3, 4: phi(K); 5: the blocks on the
+            // diagonal.  Increment pass: phi(K) only, of a token slab each.
             auto build = [&](const int b) {
-                if (MODE == 0) {
+                if (MODE == 0 && NPW == 6) {
+                    if (c == 0) {
+                        role_guard();
+                        build_den(b);
+                        build_block(b, 1);
+                    } else if (c < 3) {
+                        build_phiq(b, c - 1);
+                    } else if (c < 5) {
+                        build_phik2(b, 2 * (c - 3));
+                    } else {
+                        role_guard();
+                        build_block(b, 0);
+                        build_block(b, 2);
+                    }
+                } else if (MODE == 0) {
                     if (c == 0) {
                         role_guard();
                         build_den(b);
                         build_phiq(b, 0);
                     } else if (c == 1) {
                         build_phiq(b, 1);
-                        if (NC == 2) build_block(b, 1);
                     } else if (c == 2) {
                         build_phik2(b, 0);
-                        if (NC == 2) build_block(b, 0);
                     } else {
                         build_phik2(b, 2);
-                        if (NC == 2) build_block(b, 2);
                     }
                 } else {
 #pragma unroll
                     for (int ts = 0; ts < 4; ++ts)
-                        if (c == ts) build_phik(b, ts);
+                        if (c == ts + (NPW == 6 ? 1 : 0)) build_phik(b, ts);
                 }
             };
 
@@ -969,7 +988,7 @@ __device__ __forceinline__ void prefill_body(
 // (all segment-0 workgroups first: they depend on nothing and fill the slots the increment
 // workgroups leave free).
 template <int NC>
-__global__ __launch_bounds__(64 * (NC + 4), 2) void prefill_mfma_kernel(
+__global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, float *__restrict__ state, int has_init, float *__restrict__ ws,
     unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls, unsigned epoch, int N,
@@ -1092,7 +1111,7 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     // that has never been used hold whatever was in that memory.
     static std::atomic<unsigned> calls{0};
     const unsigned epoch = 0x5EED0000u + calls.fetch_add(1u) + 1u;
-    hipLaunchKernelGGL((prefill_mfma_kernel<NC>), dim3((unsigned)(U * (2 * G - 1))), dim3(64 * (NC + 4)), 0, s, q, k, v,
+    hipLaunchKernelGGL((prefill_mfma_kernel<NC>), dim3((unsigned)(U * (2 * G - 1))), dim3(64 * (NC + producers(NC))), 0, s, q, k, v,
                        y, state, flags_word, ws, flags, status, g_flag_poll_limit.load(), epoch, N, segs, G, U);
     return hipGetLastError();
 }
