@@ -82,12 +82,10 @@ constexpr int NTILE = 5;          // state tiles of 32 rows
 constexpr int NSLAB = 2 * NTILE;  // feature slabs of 16 rows
 constexpr float kCK = 0.84089641525371454303f;   // 2^(-1/4): (c k_a)(c k_b) = k_a k_b / sqrt(2)
 constexpr float kCQ = 1.18920711500272106672f;   // 2^(+1/4): (c q_a)(c q_b) = sqrt(2) q_a q_b
-constexpr float kHalfInvCQ = 0.42044820762685725f;   // 0.5 / kCQ
 
 // LDS strides (elements)
 constexpr int KTS_LD = C + 4;     // fp32 K^T rows
 constexpr int KT_ROWS = DP + 3;   // c_k k_a (16 rows); valid / c_k; valid * c_k; zeros
-constexpr int QS_LD = DP + 4;     // fp32 Q rows
 constexpr int RB_LD = DP + 8;     // bf16 row-major Q and K rows as given (48-byte stride)
 constexpr int YT_LD = 32 + 8;     // bf16 rows of a finished output tile on its way out (80-byte stride)
 
@@ -105,11 +103,12 @@ __host__ __device__ constexpr int producers(int nc) { return nc == 2 ? 6 : 4; }
 
 template <int NC>
 struct Lds {
-    // the producers' own staging of the q and k rows of the chunk they are preparing
-    float kts[KT_ROWS][KTS_LD];         // c_k * K^T, then the rows [valid / c_k], [valid * c_k], [0]
-    float qs[C][QS_LD];                 // c_q * Q
-    uint16_t qrow[C][RB_LD];            // Q rows, bf16 as given
-    uint16_t krow[C][RB_LD];            // K rows, bf16 as given
+    // the q and k rows of a chunk, by its parity: the producers stage one chunk's while they build from the other's
+    struct alignas(16) Rows {
+        float kts[KT_ROWS][KTS_LD];     // c_k * K^T, then the rows [valid / c_k], [valid * c_k], [0]
+        uint16_t qrow[C][RB_LD];        // Q rows, bf16 as given
+        uint16_t krow[C][RB_LD];        // K rows, bf16 as given
+    } rows[2];
     // everything the consumers read exists twice, indexed by the parity of the chunk: the producers fill
     // one generation while the consumers work on the other
     uint16_t vrow[2][C][32 * NC + 16];  // V rows, bf16 as given (operands are read transposed; the stride
@@ -118,8 +117,9 @@ struct Lds {
     u32x4 phik[2][NTILE][4][64];        // phi(K)^T operands: [parity][state tile][16-token slab][lane]
     u32x4 pop[2][3][2][64];             // masked intra-chunk blocks as operands: [parity][block][slab][lane]
     float den[2][3][C];                 // per query: inter-chunk part; row sums of the blocks of key tile 0, 1
-    uint16_t yt[NC][32][YT_LD];         // per consumer wave: a finished output tile on its way out
-    unsigned staged;                    // producer waves that have staged their part, summed over the chunks so far
+    // per consumer wave: a finished output tile on its way out (at d_v 128 in the columns of vrow that only this wave reads, once it has
+    // read them)
+    uint16_t yt[NC == 2 ? 2 : 1][NC == 2 ? 32 : 1][YT_LD];
 };
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
@@ -159,23 +159,6 @@ __device__ __forceinline__ void zero16(f32x16 &a)
 __device__ __forceinline__ void wg_sync()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// The rows of a chunk are staged by the producer waves only, and read by every wave that builds an
-// operand from them.  That hand-over does not stop the whole workgroup: a producer wave that has finished
-// its LDS writes adds one to a counter in LDS, and whoever needs the rows waits until the counter has
-// reached the number of producer waves times the number of chunks staged so far.  (LDS operations of a
-// wave complete in order, and the add is issued after the wave's own writes have completed.)
-__device__ __forceinline__ void signal_staged(unsigned *counter, int lane)
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (lane == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void wait_staged(unsigned *counter, unsigned target)
-{
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target)
-        __builtin_amdgcn_s_sleep(1);
-    asm volatile("" ::: "memory");
 }
 
 // MFMA instructions ignore the EXEC mask.  A branch on the wave's role is uniform across the wave
@@ -361,8 +344,8 @@ __device__ __forceinline__ void prefill_body(
         const bool diag = bb != 1;
         f32x16 P;
         zero16(P);
-        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.krow[32 * kt + n][8 * g]);
-        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.qrow[32 * qt + n][8 * g]);
+        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].krow[32 * kt + n][8 * g]);
+        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].qrow[32 * qt + n][8 * g]);
         P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
         float dsum = 0.f;
 #pragma unroll
@@ -445,12 +428,10 @@ __device__ __forceinline__ void prefill_body(
         // (a barrier does not wait for loads into registers, and the flag lets another workgroup overwrite what they read)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) lds.staged = 0u;   // (it lies in the image)
         if (MODE == 0 && G > 1) {
             if (tid == 0) __hip_atomic_store(flags_unit + (G - 1), epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     };
-    if (!(has_init && seg == 0) && tid == 0) lds.staged = 0u;   // ordered before its first use by the prologue's barriers
     if (!is_p) {
         // =================================== consumer waves =========================================
         f32x16 S[NTILE];       // the five state tiles of this wave's 32 columns
@@ -513,39 +494,32 @@ __device__ __forceinline__ void prefill_body(
                     // conversion: accumulator registers 8 sl .. 8 sl + 7 are the k-slots of slab 2T + sl) is the
                     // A operand.  The LDS loads go out in groups, into registers of their own, ahead of the
                     // matrix instructions that consume them.
-                    u32x4 oa[2][5], ob[2][5];
+                    constexpr int RG = 5, NG = NSLAB / RG;
+                    u32x4 o[2][RG][2];
+                    auto load_group = [&](int gi) {
 #pragma unroll
-                    for (int sl = 0; sl < 5; ++sl)
+                        for (int sl = 0; sl < RG; ++sl)
 #pragma unroll
-                        for (int qt = 0; qt < 2; ++qt) oa[qt][sl] = lds.phiq[b][qt][sl][lane];
-#pragma unroll
-                    for (int sl = 0; sl < 5; ++sl)
-#pragma unroll
-                        for (int qt = 0; qt < 2; ++qt) ob[qt][sl] = lds.phiq[b][qt][5 + sl][lane];
-#pragma unroll
-                    for (int qt = 0; qt < 2; ++qt)
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) dn[qt][d] = lds.den[b][d][32 * qt + n];
-                    __builtin_amdgcn_sched_barrier(0);
+                            for (int qt = 0; qt < 2; ++qt) o[gi & 1][sl][qt] = lds.phiq[b][qt][RG * gi + sl][lane];
+                    };
+                    load_group(0);
                     zero16(Y[0]); zero16(Y[1]);
 #pragma unroll
-                    for (int sl = 0; sl < 5; ++sl) {
-                        const bf16x8 sb = pack8_acc(S[sl >> 1], sl & 1);
+                    for (int gi = 0; gi < NG; ++gi) {
+                        if (gi + 1 < NG) load_group(gi + 1);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int qt = 0; qt < 2; ++qt) Y[qt] = mfma(sb, as_bf16x8(oa[qt][sl]), Y[qt]);
+                        for (int sl = 0; sl < RG; ++sl) {
+                            const bf16x8 sb = pack8_acc(S[(RG * gi + sl) >> 1], (RG * gi + sl) & 1);
+#pragma unroll
+                            for (int qt = 0; qt < 2; ++qt) Y[qt] = mfma(sb, as_bf16x8(o[gi & 1][sl][qt]), Y[qt]);
+                        }
                     }
-                    // the intra-chunk blocks, into the registers the first group has left
                     u32x4 op[3][2];
 #pragma unroll
                     for (int bb = 0; bb < 3; ++bb)
 #pragma unroll
                         for (int sl = 0; sl < 2; ++sl) op[bb][sl] = lds.pop[b][bb][sl][lane];
-#pragma unroll
-                    for (int sl = 5; sl < NSLAB; ++sl) {
-                        const bf16x8 sb = pack8_acc(S[sl >> 1], sl & 1);
-#pragma unroll
-                        for (int qt = 0; qt < 2; ++qt) Y[qt] = mfma(sb, as_bf16x8(ob[qt][sl - 5]), Y[qt]);
-                    }
                     // intra-chunk: Y^T += V^T P^T over the key tiles at or before the query tile
 #pragma unroll
                     for (int sl = 0; sl < 2; ++sl) {
@@ -555,10 +529,7 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                     for (int sl = 0; sl < 2; ++sl) Y[1] = mfma(vop[2 + sl], as_bf16x8(op[2][sl]), Y[1]);
                 }
-                if (MODE == 0 && NC == 4 && t + 1 < n_chunks) {
-                    wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // the next chunk's rows are staged
-                    build_my_blocks(b ^ 1);
-                }
+                if (MODE == 0 && NC == 4 && t + 1 < n_chunks) build_my_blocks(b ^ 1);
 
                 // ---- update: S += phi(K)^T V over all 160 rows, with the normalisation and the store of
                 // the outputs placed between the matrix instructions
@@ -570,23 +541,27 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
 #pragma unroll
-                    for (int ts = 2 * half; ts < 2 * half + 2; ++ts)
+                    for (int ts = 2 * half; ts < 2 * half + 2; ++ts) {
 #pragma unroll
                         for (int T = 0; T < NTILE; ++T) S[T] = mfma(as_bf16x8(ok[ts][T]), vop[ts], S[T]);
+                    }
                     if (MODE == 0) {
                         const int qt = half;
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) dn[qt][d] = lds.den[b][d][32 * qt + n];
                         // normalise and turn the tile through LDS: a lane holds 8-byte pieces of its token's
                         // row, and stored directly those become 16-byte write requests that stall the memory
                         // pipeline; from LDS the tile leaves as 64-byte row segments, 16 rows a store.
                         const float inv = numerator_only ? 1.f : __builtin_amdgcn_rcpf(dn[qt][0] + dn[qt][1] + dn[qt][2]);
-                        uint16_t *yt = &lds.yt[c][0][0];
+                        constexpr int LD = NC == 2 ? YT_LD : VR_LD;
+                        uint16_t *yt = NC == 2 ? &lds.yt[c & 1][0][0] : &lds.vrow[b][32 * qt][32 * c];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             f32x4 o;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) o[i] = Y[qt][4 * j + i] * inv;
                             const bf16x4 hv = __builtin_convertvector(o, bf16x4);
-                            *reinterpret_cast<u32x2 *>(yt + n * YT_LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
+                            *reinterpret_cast<u32x2 *>(yt + n * LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
                         }
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                         uint16_t *yc = yu + (size_t)tok0 * DV;
@@ -595,7 +570,7 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                         for (int it = 0; it < 2; ++it) {
                             const int row = 16 * it + (lane >> 2), cc = lane & 3;
-                            val[it] = *reinterpret_cast<const u32x4 *>(yt + row * YT_LD + 8 * cc);
+                            val[it] = *reinterpret_cast<const u32x4 *>(yt + row * LD + 8 * cc);
                             yoff[it] = (uint32_t)(32 * qt + row) * (uint32_t)DV + (uint32_t)(32 * c + 8 * cc);
                         }
                         if (tok0 + C <= tok_end) {
@@ -664,7 +639,7 @@ __device__ __forceinline__ void prefill_body(
             // against query tile 0)
             // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
             // not wait for this wave)
-            if (ptid < C) lds.kts[DP + 2][ptid] = 0.f;
+            if (ptid < 2 * C) lds.rows[ptid / C].kts[DP + 2][ptid % C] = 0.f;
             if (ptid < 32) {
                 lds.den[0][2][ptid] = 0.f;
                 lds.den[1][2][ptid] = 0.f;
@@ -676,22 +651,23 @@ __device__ __forceinline__ void prefill_body(
             // first two waves stage K, the next two Q.  Of six producers these have the first 256 pieces of V as well, the other two
             // the last 256.
             constexpr int VPR = DV / 8;   // pieces per V row
-            constexpr int NVP = VPR * C / 256;   // V pieces per producer thread
-            constexpr int VSTEP = NPW == 6 ? 128 : NP;
-            static_assert(NPW == 4 || (NPW == 6 && NVP == 2), "");
+            constexpr int NVP = NPW == 6 ? 2 : 4;   // V pieces per producer thread
+            static_assert((NPW == 6 ? 256 + 2 * 128 : NP * NVP) == VPR * C, "");
             const int xp = ptid & 127;
-            const bool is_k = ptid < 128, has_x = NPW == 4 || ptid < 256;
+            const bool is_k = ptid < 128, has_x = ptid < 256;
             const int x_tok = xp >> 1, x_h = xp & 1;
             u32x4 raw_x = {0u, 0u, 0u, 0u};   // the thread's piece of K or Q
             u32x4 raw_v[NVP];
             // Loads are unconditional (rows past the end of the segment re-read its last row and are
             // zeroed when staged): a conditional load would have the compiler pre-zero its destination
             // registers, and before that write it waits for every memory operation still in flight.
-            auto v_piece = [&](int j) { return ptid + VSTEP * j; };
-            auto load_raw = [&](int tok0) {
+            auto v_piece = [&](int j) { return NPW == 4 ? ptid + NP * j : has_x ? ptid : ptid + 128 * j; };
+            auto load_x = [&](int tok0) {
                 const int tok = min(tok0 + x_tok, tok_end - 1);
                 const uint16_t *src = (is_k || MODE != 0) ? ku : qu;   // increment pass: q is not needed
                 raw_x = *reinterpret_cast<const u32x4 *>(src + (size_t)tok * DP + 8 * x_h);
+            };
+            auto load_v = [&](int tok0) {
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
                     const int p = v_piece(j);
@@ -699,40 +675,33 @@ __device__ __forceinline__ void prefill_body(
                     raw_v[j] = *reinterpret_cast<const u32x4 *>(vu + (size_t)row * DV + 8 * (p % VPR));
                 }
             };
-            auto stage_k = [&](u32x4 raw, bool valid) {
-                const u32x4 zero4 = {0u, 0u, 0u, 0u};
-                if (!valid) raw = zero4;
+            auto stage_x = [&](int tok0, int b) {
+                auto &rows = lds.rows[b];
+                u32x4 raw = raw_x;
+                if (is_k) {
+                    const bool valid = tok0 + x_tok < tok_end;
+                    if (!valid) raw = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    lds.kts[8 * x_h + 2 * i][x_tok] = bf16lo(raw[i]) * kCK;
-                    lds.kts[8 * x_h + 2 * i + 1][x_tok] = bf16hi(raw[i]) * kCK;
-                }
-                *reinterpret_cast<u32x4 *>(&lds.krow[x_tok][8 * x_h]) = raw;
-                if (x_h == 0) {
-                    lds.kts[DP][x_tok] = valid ? 1.f / kCK : 0.f;
-                    lds.kts[DP + 1][x_tok] = valid ? kCK : 0.f;
+                    for (int i = 0; i < 4; ++i) {
+                        rows.kts[8 * x_h + 2 * i][x_tok] = bf16lo(raw[i]) * kCK;
+                        rows.kts[8 * x_h + 2 * i + 1][x_tok] = bf16hi(raw[i]) * kCK;
+                    }
+                    *reinterpret_cast<u32x4 *>(&rows.krow[x_tok][8 * x_h]) = raw;
+                    if (x_h == 0) {
+                        rows.kts[DP][x_tok] = valid ? 1.f / kCK : 0.f;
+                        rows.kts[DP + 1][x_tok] = valid ? kCK : 0.f;
+                    }
+                } else if (MODE == 0 && has_x) {
+                    *reinterpret_cast<u32x4 *>(&rows.qrow[x_tok][8 * x_h]) = raw;
                 }
             };
-            auto stage_q = [&](u32x4 raw) {
-                f32x4 lo, hi;
-                lo[0] = bf16lo(raw[0]) * kCQ; lo[1] = bf16hi(raw[0]) * kCQ;
-                lo[2] = bf16lo(raw[1]) * kCQ; lo[3] = bf16hi(raw[1]) * kCQ;
-                hi[0] = bf16lo(raw[2]) * kCQ; hi[1] = bf16hi(raw[2]) * kCQ;
-                hi[2] = bf16lo(raw[3]) * kCQ; hi[3] = bf16hi(raw[3]) * kCQ;
-                *reinterpret_cast<f32x4 *>(&lds.qs[x_tok][8 * x_h]) = lo;
-                *reinterpret_cast<f32x4 *>(&lds.qs[x_tok][8 * x_h + 4]) = hi;
-                *reinterpret_cast<u32x4 *>(&lds.qrow[x_tok][8 * x_h]) = raw;
-            };
-            auto stage = [&](int tok0, int b) {
-                const bool valid = tok0 + x_tok < tok_end;
-                if (is_k) stage_k(raw_x, valid);
-                else if (MODE == 0 && has_x) stage_q(raw_x);
+            auto stage_v = [&](int tok0, int b) {
                 const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
                     const int p = v_piece(j);
                     const int row = p / VPR;
-                    if (NPW == 4 || j == 0 || !has_x)
+                    if (j == 0 || NPW == 4 || !has_x)
                         *reinterpret_cast<u32x4 *>(&lds.vrow[b][row][8 * (p % VPR)]) = tok0 + row < tok_end ? raw_v[j] : zero4;
                 }
             };
@@ -745,18 +714,19 @@ __device__ __forceinline__ void prefill_body(
             // at compile time.
             auto build_phiq = [&](const int b, const int qt) {
                 float xr[16];
-                const float *row = lds.qs[32 * qt + n];
-                f32x4 t[4];
+                // (slab 8: the linear rows; the operand is q itself, as given)
+                const uint16_t *row = lds.rows[b].qrow[32 * qt + n];
+                u32x2 raw[4];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) t[m] = *reinterpret_cast<const f32x4 *>(row + ((4 * g + 4 * m) & 15));
-                // slab 8: the linear rows; the operand is q itself, as given
-                const uint16_t *p = &lds.qrow[32 * qt + n][4 * g];
-                const u32x2 ra = *reinterpret_cast<const u32x2 *>(p);
-                const u32x2 rb = *reinterpret_cast<const u32x2 *>(p + 8);
+                for (int m = 0; m < 4; ++m) raw[m] = *reinterpret_cast<const u32x2 *>(row + ((4 * g + 4 * m) & 15));
+                const u32x2 ra = raw[0], rb = raw[2];
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) xr[4 * m + i] = t[m][i];
+                    for (int i = 0; i < 2; ++i) {
+                        xr[4 * m + 2 * i] = bf16lo(raw[m][i]) * kCQ;
+                        xr[4 * m + 2 * i + 1] = bf16hi(raw[m][i]) * kCQ;
+                    }
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {   // pair slabs: delta = s
                     float pr[8];
@@ -790,12 +760,14 @@ __device__ __forceinline__ void prefill_body(
             // fp32 rounding only, far below half a bf16 step, so the conversion returns k_a exactly.)  The
             // "a" row of the four pair tiles is the same (a = n % 16), so a slab costs 14 LDS loads, all
             // issued before the products.
-            const float *kt_a03 = &lds.kts[n & 15][4 * g];
-            const float *kt_a4 = &lds.kts[n < DP ? n : (n == DP ? DP + 1 : (n < 24 ? DP + 2 : n - 24))][4 * g];
+            const float *kts0 = &lds.rows[0].kts[0][4 * g];
+            constexpr int GEN = sizeof(typename Lds<NC>::Rows) / sizeof(float);
+            const float *kt_a03 = kts0 + (n & 15) * KTS_LD;
+            const float *kt_a4 = kts0 + (n < DP ? n : (n == DP ? DP + 1 : (n < 24 ? DP + 2 : n - 24))) * KTS_LD;
             const float *kt_b[NTILE];
 #pragma unroll
-            for (int T = 0; T < 4; ++T) kt_b[T] = &lds.kts[((n & 15) + 2 * T + (n >> 4)) & 15][4 * g];
-            kt_b[4] = &lds.kts[n < DP ? DP : (n == DP ? DP : (n < 24 ? DP + 2 : n - 16))][4 * g];
+            for (int T = 0; T < 4; ++T) kt_b[T] = kts0 + (((n & 15) + 2 * T + (n >> 4)) & 15) * KTS_LD;
+            kt_b[4] = kts0 + (n < DP ? DP : (n == DP ? DP : (n < 24 ? DP + 2 : n - 16))) * KTS_LD;
             // (NTS token slabs at a time: all their LDS loads go out before the first product)
             auto build_phik_n = [&](const int b, const int ts0, auto nts_tag) {
                 constexpr int NTS = decltype(nts_tag)::value;
@@ -804,7 +776,7 @@ __device__ __forceinline__ void prefill_body(
                 for (int s2 = 0; s2 < NTS; ++s2)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const int off = 16 * (ts0 + s2) + 8 * h;
+                        const int off = GEN * b + 16 * (ts0 + s2) + 8 * h;
                         a03[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a03 + off);
                         a4[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a4 + off);
 #pragma unroll
@@ -828,14 +800,10 @@ __device__ __forceinline__ void prefill_body(
             auto build_phik2 = [&](const int b, const int ts) { build_phik_n(b, ts, std::integral_constant<int, 2>{}); };
             // Inter-chunk denominators of both query tiles from the moments: count + q.z1 + q^T M q / 2.
             auto build_den = [&](const int b) {
-                f32x4 a0[2], a1[2];
                 u32x2 ra[2], rb[2];
 #pragma unroll
                 for (int qt = 0; qt < 2; ++qt) {
-                    const float *row = lds.qs[32 * qt + n];
-                    a0[qt] = *reinterpret_cast<const f32x4 *>(row + 4 * g);
-                    a1[qt] = *reinterpret_cast<const f32x4 *>(row + 8 + 4 * g);
-                    const uint16_t *p = &lds.qrow[32 * qt + n][4 * g];
+                    const uint16_t *p = &lds.rows[b].qrow[32 * qt + n][4 * g];
                     ra[qt] = *reinterpret_cast<const u32x2 *>(p);
                     rb[qt] = *reinterpret_cast<const u32x2 *>(p + 8);
                 }
@@ -864,10 +832,12 @@ __device__ __forceinline__ void prefill_body(
                     float d2 = 0.f;
                     // row of T[e] = 8 (e / 4) + 4 g + e % 4
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][e], a0[qt][e], d2);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][4 + e], a1[qt][e], d2);
-                    const float d = fmaf(d2, kHalfInvCQ, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t qa = ra[qt][e >> 1], qb = rb[qt][e >> 1];
+                        d2 = fmaf(T[qt][e], e & 1 ? bf16hi(qa) : bf16lo(qa), d2);
+                        d2 = fmaf(T[qt][4 + e], e & 1 ? bf16hi(qb) : bf16lo(qb), d2);
+                    }
+                    const float d = fmaf(d2, 0.5f, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
                     const float tot = d + __shfl_xor(d, 32, 64) + cnt_prev;
                     if (g == 0) lds.den[b][0][32 * qt + n] = tot;
                 }
@@ -899,35 +869,36 @@ __device__ __forceinline__ void prefill_body(
                         build_phiq(b, 0);
                     } else if (c == 1) {
                         build_phiq(b, 1);
-                    } else if (c == 2) {
-                        build_phik2(b, 0);
                     } else {
-                        build_phik2(b, 2);
+                        build_phik2(b, 2 * (c - 2));
                     }
                 } else {
 #pragma unroll
                     for (int ts = 0; ts < 4; ++ts)
-                        if (c == ts + (NPW == 6 ? 1 : 0)) build_phik(b, ts);
+                        if (c == NPW - 4 + ts) build_phik(b, ts);
                 }
             };
 
-            // ---- the producers' loop: one chunk ahead of the consumers -----------------------------
-            load_raw(tok_begin);
-            stage(tok_begin, 0);
-            if (n_chunks > 1) load_raw(tok_begin + C);
+            // ---- the producers' loop: operands one chunk ahead of the consumers, rows of K and Q two -------
+            auto next_rows = [&](int t) {   // in registers: K and Q of chunk t + 2, V of chunk t + 1
+                const int tok_next = tok_begin + C * (t + 1);
+                stage_v(tok_next, (t + 1) & 1);
+                stage_x(tok_next + C, t & 1);
+                load_v(tok_next + C);
+                load_x(tok_next + 2 * C);
+            };
+            load_x(tok_begin);
+            load_v(tok_begin);
+            stage_x(tok_begin, 0);
+            load_x(tok_begin + C);
             wg_sync();   // the first chunk's rows are staged
+            next_rows(-1);
             build(0);
             wg_sync();   // the first chunk's operands are visible
             for (int t = 0; t < n_chunks; ++t) {
                 const int b = t & 1;
-                const int tok_next = tok_begin + C * (t + 1);
                 const bool has_next = t + 1 < n_chunks;
-                if (has_next) {
-                    stage(tok_next, b ^ 1);
-                    signal_staged(&lds.staged, lane);
-                }
-                if (t + 2 < n_chunks) load_raw(tok_next + C);   // two chunks ahead of the consumers
-                if (has_next) wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // all of the next chunk's rows
+                if (has_next) next_rows(t);
                 if (holds_x) {
                     // M' += K'^T K' of the chunk the consumers are working on (the operand of tile 4 carries k
                     // as given in rows 0..15 and the valid flag in row 16); the denominators of the next chunk
