@@ -1,8 +1,8 @@
 // Sliding-window causal softmax attention over whole sequences (Sec. 3.2 restricting Eq. 1) on
 // the gfx950 matrix cores: bf16 in, fp32 scores / softmax / accumulation.
 //
-// Work split.  One workgroup of four waves per (unit, segment of the sequence) walks its segment
-// in steps of 128 queries; each wave owns one tile of 32 queries of the step and walks the
+// Work split.  One workgroup of four waves (at d_h 64, window 128 eight) per (unit, segment of the sequence) walks its segment
+// in steps of 128 (256) queries; each wave owns one tile of 32 queries of the step and walks the
 // w / 32 + 1 key tiles that overlap its window.
 //
 // Staging.  The w + 128 key and value rows a step can see sit in an LDS ring.  Each step
@@ -51,6 +51,8 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -58,23 +60,22 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int BQ = 128;   // queries per workgroup
-constexpr int NT = 256;
-
 // WIN is the attention window; the key tiles are laid out for W = max(WIN, 32) (a window below one
 // tile of 32 keys walks two tiles and masks the rest).
-template <int DH, int WIN> struct SwaCfg {
+template <int DH, int WIN, int NWV> struct SwaCfg {   // NWV: waves of a workgroup, 32 queries of a step each
+    static constexpr int BQ = 32 * NWV;        // queries per workgroup and step
+    static constexpr int NT = 64 * NWV;
     static constexpr int W = WIN < 32 ? 32 : WIN;
     static constexpr int NK = W + BQ;          // staged key rows
     static constexpr int V_LD = DH + 16;       // bf16 elements per staged V row (row stride = 8 banks mod 32)
     static constexpr int K_LD = DH + 8;        // bf16 elements per staged K row (16-byte pad)
     static constexpr int NKT = W / 32 + 1;     // key tiles per query tile
     static constexpr int Y_LD = 64 + 8;        // bf16 elements per row of a wave's output staging tile (64 columns a pass)
-    static constexpr size_t lds_bytes = ((size_t)NK * (V_LD + K_LD) + (size_t)4 * 32 * Y_LD) * 2;
+    static constexpr size_t lds_bytes = ((size_t)NK * (V_LD + K_LD) + (size_t)NWV * 32 * Y_LD) * 2;
     // rotary variant: the per-wave region holds either the wave's 32 rotated query rows or its output tile
     static constexpr int Q_LD = DH + 8;
     static constexpr int WREG = 32 * (Q_LD > Y_LD ? Q_LD : Y_LD);   // elements of a wave's region
-    static constexpr size_t lds_bytes_rotary = ((size_t)NK * (V_LD + K_LD) + (size_t)4 * WREG) * 2;
+    static constexpr size_t lds_bytes_rotary = ((size_t)NK * (V_LD + K_LD) + (size_t)NWV * WREG) * 2;
 };
 
 // (cos, sin) of four adjacent pairs
@@ -105,7 +106,7 @@ __device__ __forceinline__ u32x4 rotate8(u32x4 x, const Rot4 &r)
         const float x0 = __uint_as_float(x[j] << 16), x1 = __uint_as_float(x[j] & 0xffff0000u);
         const float c = cs[2 * j], s = cs[2 * j + 1];
         const float r0 = fmaf(x0, c, -x1 * s), r1 = fmaf(x0, s, x1 * c);
-        o[j] = (uint32_t)f32_to_bf16_bits(r0) | ((uint32_t)f32_to_bf16_bits(r1) << 16);
+        o[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
     }
     return o;
 }
@@ -131,7 +132,7 @@ __device__ __forceinline__ Rot4 rot_mul(const Rot4 &a, const Rot4 &b, bool conj_
 
 }  // namespace
 
-template <int DH, int WIN, bool ROT>
+template <int DH, int WIN, int NWV, bool ROT>
 __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict__ q,
                                                       const uint16_t *__restrict__ k,
                                                       const uint16_t *__restrict__ v,
@@ -140,8 +141,8 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
                                                       const float2 *__restrict__ rot, int N,
                                                       int seg_len, int nseg, float scale_log2e)
 {
-    using Cfg = SwaCfg<DH, WIN>;
-    constexpr int W = Cfg::W;
+    using Cfg = SwaCfg<DH, WIN, NWV>;
+    constexpr int W = Cfg::W, BQ = Cfg::BQ, NT = Cfg::NT;
     constexpr int NK = Cfg::NK, V_LD = Cfg::V_LD, K_LD = Cfg::K_LD, NKT = Cfg::NKT;
     constexpr int SLABS = DH / 16;   // k-slabs of the score contraction
     constexpr int CT = DH / 32;      // column tiles of the output
@@ -499,37 +500,42 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
     step(sq0, std::false_type{});
 }
 
-template <int DH, int WIN>
-__global__ __launch_bounds__(NT) void swa_prefill_mfma_kernel(const uint16_t *__restrict__ q,
-                                                              const uint16_t *__restrict__ k,
-                                                              const uint16_t *__restrict__ v,
-                                                              uint16_t *__restrict__ y,
-                                                              uint16_t *__restrict__ ring, int N,
-                                                              int seg_len, int nseg, float scale_log2e)
+// Waves of a SIMD: as many as the LDS ring leaves room for (a wave alone on its SIMD may have the whole register file).
+constexpr int waves_per_simd(int nwv, size_t lds_bytes) { return nwv == 8 ? 2 : lds_bytes > 80u * 1024u ? 1 : 2; }
+template <int DH, int WIN, int NWV>
+__global__ __launch_bounds__(64 * NWV, NWV == 8 ? 2 : 1) void swa_prefill_mfma_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+    uint16_t *__restrict__ y, uint16_t *__restrict__ ring, int N, int seg_len, int nseg, float scale_log2e)
 {
-    swa_prefill_mfma_body<DH, WIN, false>(q, k, v, y, ring, nullptr, N, seg_len, nseg, scale_log2e);
+    swa_prefill_mfma_body<DH, WIN, NWV, false>(q, k, v, y, ring, nullptr, N, seg_len, nseg, scale_log2e);
 }
 
-// The rotary variant keeps the table entries of the rows in flight in registers: where the LDS ring
-// leaves room for one workgroup per CU only, a wave may have the whole register file of its SIMD.
-template <int DH, int WIN>
-__global__ __launch_bounds__(NT, (SwaCfg<DH, WIN>::lds_bytes_rotary > 80u * 1024u ? 1 : 2)) void swa_prefill_mfma_rotary_kernel(
+// (The rotary variant keeps the table entries of the rows in flight in registers.)
+template <int DH, int WIN, int NWV>
+__global__ __launch_bounds__(64 * NWV, waves_per_simd(NWV, SwaCfg<DH, WIN, NWV>::lds_bytes_rotary)) void swa_prefill_mfma_rotary_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, uint16_t *__restrict__ ring, const float2 *__restrict__ rot, int N, int seg_len,
     int nseg, float scale_log2e)
 {
-    swa_prefill_mfma_body<DH, WIN, true>(q, k, v, y, ring, rot, N, seg_len, nseg, scale_log2e);
+    swa_prefill_mfma_body<DH, WIN, NWV, true>(q, k, v, y, ring, rot, N, seg_len, nseg, scale_log2e);
 }
 
-template <int DH, int WIN, bool ROT>
+// d_h 64, window 128: the ring of four waves (96 KB) leaves a CU one workgroup, one wave to a SIMD.  Eight waves and steps of 256 queries (153
+// KB) are two, where the chip is full of workgroups either way.  (us with four and with eight, without and with rotary: 32 units of 16384 tokens
+// 61.1, 57.7 and 68.7, 64.8; 64 of 2048 17.7, 15.5 and 21.8, 19.2; 64 of 777 11.6, 10.0 and 14.4, 12.0; 512 of 200 22.3, 19.1; but 16 of
+// 2048 8.6, 8.4 and 10.2, 10.3; 16 of 777 6.8, 7.3; 512 of 100 15.4, 15.4 and 17.0, 17.5.)
+static bool eight_waves(int U, int N) { return N > 128 && (long)U * ((N + 127) / 128) > 256; }
+
+template <int DH, int WIN, int NWV, bool ROT>
 static hipError_t launch_swa_mfma_rot(const void *q, const void *k, const void *v, void *y, void *ring,
                                       const float *rot, int U, int N, float scale, hipStream_t s)
 {
-    using Cfg = SwaCfg<DH, WIN>;
+    using Cfg = SwaCfg<DH, WIN, NWV>;
+    constexpr int BQ = Cfg::BQ, NT = Cfg::NT;
     constexpr size_t lds_bytes = ROT ? Cfg::lds_bytes_rotary : Cfg::lds_bytes;
     static_assert(lds_bytes <= 160u * 1024u, "");
-    const void *kern = ROT ? reinterpret_cast<const void *>(swa_prefill_mfma_rotary_kernel<DH, WIN>)
-                           : reinterpret_cast<const void *>(swa_prefill_mfma_kernel<DH, WIN>);
+    const void *kern = ROT ? reinterpret_cast<const void *>(swa_prefill_mfma_rotary_kernel<DH, WIN, NWV>)
+                           : reinterpret_cast<const void *>(swa_prefill_mfma_kernel<DH, WIN, NWV>);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
     // Segments per sequence.  The launch should be whole rounds of resident workgroups (256 CUs x as
@@ -554,11 +560,11 @@ static hipError_t launch_swa_mfma_rot(const void *q, const void *k, const void *
     const dim3 grid((unsigned)((size_t)nseg * U));
     const float scale_log2e = scale * 1.44269504088896340736f;
     if (ROT)
-        hipLaunchKernelGGL((swa_prefill_mfma_rotary_kernel<DH, WIN>), grid, dim3(NT), lds_bytes, s,
+        hipLaunchKernelGGL((swa_prefill_mfma_rotary_kernel<DH, WIN, NWV>), grid, dim3(NT), lds_bytes, s,
                            (const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, (uint16_t *)y,
                            (uint16_t *)ring, reinterpret_cast<const float2 *>(rot), N, seg_len, nseg, scale_log2e);
     else
-        hipLaunchKernelGGL((swa_prefill_mfma_kernel<DH, WIN>), grid, dim3(NT), Cfg::lds_bytes, s,
+        hipLaunchKernelGGL((swa_prefill_mfma_kernel<DH, WIN, NWV>), grid, dim3(NT), Cfg::lds_bytes, s,
                            (const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, (uint16_t *)y,
                            (uint16_t *)ring, N, seg_len, nseg, scale_log2e);
     return hipGetLastError();
@@ -568,9 +574,14 @@ template <int DH, int WIN>
 static hipError_t launch_swa_mfma(const void *q, const void *k, const void *v, void *y, void *ring,
                                   const float *rot, int U, int N, float scale, hipStream_t s)
 {
-    if (!rot) return launch_swa_mfma_rot<DH, WIN, false>(q, k, v, y, ring, nullptr, U, N, scale, s);
-    if constexpr (SwaCfg<DH, WIN>::lds_bytes_rotary <= 160u * 1024u)
-        return launch_swa_mfma_rot<DH, WIN, true>(q, k, v, y, ring, rot, U, N, scale, s);
+    if constexpr (DH == 64 && WIN == 128) {
+        if (eight_waves(U, N))
+            return rot ? launch_swa_mfma_rot<DH, WIN, 8, true>(q, k, v, y, ring, rot, U, N, scale, s)
+                       : launch_swa_mfma_rot<DH, WIN, 8, false>(q, k, v, y, ring, nullptr, U, N, scale, s);
+    }
+    if (!rot) return launch_swa_mfma_rot<DH, WIN, 4, false>(q, k, v, y, ring, nullptr, U, N, scale, s);
+    if constexpr (SwaCfg<DH, WIN, 4>::lds_bytes_rotary <= 160u * 1024u)
+        return launch_swa_mfma_rot<DH, WIN, 4, true>(q, k, v, y, ring, rot, U, N, scale, s);
     else
         return hipErrorInvalidValue;   // callers ask swa_prefill_mfma_supported first
 }

@@ -221,6 +221,13 @@ def test_window_fp32_arithmetic(based, dtype, scale, dh, w, N, rotary):
     window_case(based, dtype, dh, w, 3, N, scale, rotary)
 
 
+# d_h 64, window 128 in steps of 256 queries: its shortest sequences, one step and several, ragged last ones, segments
+@pytest.mark.parametrize("U,N", [(130, 129), (129, 256), (87, 257), (52, 601), (9, 3701)])
+@pytest.mark.parametrize("rotary", [False, True])
+def test_window_eight_waves(based, U, N, rotary):
+    window_case(based, "bf16", 64, 128, U, N, 0.125, rotary)
+
+
 # the largest ring with rotary: workgroups of one and of several steps, a ragged last one
 @pytest.mark.parametrize("U,N", [(2, 1), (3, 129), (200, 300)])
 def test_window_rotary_largest_ring(based, U, N):
