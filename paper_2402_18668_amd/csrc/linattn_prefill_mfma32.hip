@@ -471,14 +471,17 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
         }
         return o;
     };
-    const float dw = w == 0 ? 0.5f : 1.f;   // delta = 0: x_a^2 / sqrt(2)
     auto q_op = [&](const QSrc &s, int tt) {
         float pr[8];
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                pr[4 * jj + i] = (tt == 0 ? s.a[4 * jj + i] * dw : s.a[4 * jj + i]) * s.b[jj][i + tt];
+                pr[4 * jj + i] = s.a[4 * jj + i] * s.b[jj][i + tt];
+        if (tt == 0 && w == 0) {   // delta = 0: x_a^2 / sqrt(2)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pr[e] *= 0.5f;
+        }
         return pack8(pr);
     };
     // phi(K)^T operand of token slab ts of tile tt: row n, k-slots the tokens 16 ts + 4 g + {0..3, 8..11}
@@ -580,14 +583,16 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     for (int i = 0; i < PF; ++i) load_raw(tok_begin + C * i, raw[i]);
     stage(tok_begin, raw[0], lds.rows[0]);
     load_raw(tok_begin + C * PF, raw[0]);
-    // chunk t: f(t mod PF, first token)
+    // chunk t: f(t mod PF, first token).  (Pairs, and an odd chunk after the loop: with a way out between the two the compiler sees a path on
+    // which the first one's loads are the newest, and has the first chunk of every pair wait for all of them.)
     auto for_chunks = [&](auto &&f) {
-        for (int t = 0; t < n_chunks; t += PF) {
+        int t = 0;
+        for (; t + 1 < n_chunks; t += PF) {
             const int tok0 = tok_begin + C * t;
             f(std::integral_constant<int, 0>{}, tok0);
-            if (t + 1 >= n_chunks) break;
             f(std::integral_constant<int, 1>{}, tok0 + C);
         }
+        if (t < n_chunks) f(std::integral_constant<int, 0>{}, tok_begin + C * t);
     };
 
     if (INC) {
