@@ -21,7 +21,7 @@
 // row (16), seven rows of padding and the eight rows of delta = 8 (24..31).
 //
 // Work split.  One workgroup per (unit, sequence segment): one CONSUMER wave per 32 columns of d_v
-// (two at d_v = 64, four at 128) and four PRODUCER waves.  A consumer owns ALL 160 state rows of its
+// (two at d_v = 64, four at 128) and six or four PRODUCER waves (two waves to a SIMD).  A consumer owns ALL 160 state rows of its
 // 32 columns: five 32x32 fp32 accumulator tiles that stay in its registers for the whole segment (the
 // paper keeps its 2nd-order state in registers for the same reason), and issues every matrix
 // instruction for those columns: readout Y^T = S^T phi(Q)^T, intra-chunk Y^T += V^T P^T, update
@@ -36,9 +36,15 @@
 // Pipeline.  The producers run one chunk ahead of the consumers: while the consumers multiply the
 // operands of chunk t (LDS generation t % 2), the producers stage the rows of chunk t + 1 (fetched
 // into registers during chunk t - 1), and build its operands into the other generation.  Per chunk
-// there is one workgroup barrier (chunk t + 1's operands are visible, chunk t's are free) and one
+// there is one workgroup barrier (chunk t + 1's operands are visible, chunk t's are free).  At d_v = 64 the staged rows exist twice
+// and are staged one chunk earlier still; at d_v = 128, where the LDS has no room for that, there is one
 // counter in LDS that the producer waves bump when their rows are staged and that only the waves
 // building from those rows poll.
+//
+// Measured (d_v 64, four producers and rows staged once, six, rows staged twice): 128 units of 2048 tokens 45.2, 41.7, 39.4 us; 200 units 62.4,
+// 55.9, 56.3; 16 units of 777 tokens from a state 19.3, 18.1, 18.2.  At d_v 128 neither helps: eight producers (12 waves of 168
+// registers) 87.7, rows staged twice 87.2 against 86.5 us for 256 units; what a CU takes for a chunk, 2.2 us with up to 160 of them at
+// work and 2.7 with all, is the consumers' 46 matrix instructions at one operand read from LDS each, the stores and the clock.
 //
 // MFMA 32x32x16 register layouts used throughout (lane = 32 g + n):
 //   A operand: row n, k-slots 8g .. 8g+7;  B operand: column n, k-slots 8g .. 8g+7;
@@ -82,10 +88,12 @@ constexpr int NTILE = 5;          // state tiles of 32 rows
 constexpr int NSLAB = 2 * NTILE;  // feature slabs of 16 rows
 constexpr float kCK = 0.84089641525371454303f;   // 2^(-1/4): (c k_a)(c k_b) = k_a k_b / sqrt(2)
 constexpr float kCQ = 1.18920711500272106672f;   // 2^(+1/4): (c q_a)(c q_b) = sqrt(2) q_a q_b
+constexpr float kHalfInvCQ = 0.42044820762685725f;   // 0.5 / kCQ
 
 // LDS strides (elements)
 constexpr int KTS_LD = C + 4;     // fp32 K^T rows
 constexpr int KT_ROWS = DP + 3;   // c_k k_a (16 rows); valid / c_k; valid * c_k; zeros
+constexpr int QS_LD = DP + 4;     // fp32 Q rows
 constexpr int RB_LD = DP + 8;     // bf16 row-major Q and K rows as given (48-byte stride)
 constexpr int YT_LD = 32 + 8;     // bf16 rows of a finished output tile on its way out (80-byte stride)
 
@@ -100,15 +108,19 @@ __host__ __device__ constexpr size_t entry_floats(int nc) { return (size_t)nc * 
 
 // Producer waves beside NC consumers.
 __host__ __device__ constexpr int producers(int nc) { return nc == 2 ? 6 : 4; }
+// The staged rows of K and Q exist twice where the LDS has the room: then building one chunk's operands and staging the next one's rows
+// need nothing but the chunk's barrier.
+__host__ __device__ constexpr int row_generations(int nc) { return nc == 2 ? 2 : 1; }
 
 template <int NC>
 struct Lds {
-    // the q and k rows of a chunk, by its parity: the producers stage one chunk's while they build from the other's
+    // the producers' own staging of the q and k rows of a chunk (d_v 64: by its parity)
     struct alignas(16) Rows {
         float kts[KT_ROWS][KTS_LD];     // c_k * K^T, then the rows [valid / c_k], [valid * c_k], [0]
+        float qs[C][QS_LD];             // c_q * Q
         uint16_t qrow[C][RB_LD];        // Q rows, bf16 as given
         uint16_t krow[C][RB_LD];        // K rows, bf16 as given
-    } rows[2];
+    } rows[row_generations(NC)];
     // everything the consumers read exists twice, indexed by the parity of the chunk: the producers fill
     // one generation while the consumers work on the other
     uint16_t vrow[2][C][32 * NC + 16];  // V rows, bf16 as given (operands are read transposed; the stride
@@ -117,9 +129,8 @@ struct Lds {
     u32x4 phik[2][NTILE][4][64];        // phi(K)^T operands: [parity][state tile][16-token slab][lane]
     u32x4 pop[2][3][2][64];             // masked intra-chunk blocks as operands: [parity][block][slab][lane]
     float den[2][3][C];                 // per query: inter-chunk part; row sums of the blocks of key tile 0, 1
-    // per consumer wave: a finished output tile on its way out (at d_v 128 in the columns of vrow that only this wave reads, once it has
-    // read them)
-    uint16_t yt[NC == 2 ? 2 : 1][NC == 2 ? 32 : 1][YT_LD];
+    uint16_t yt[NC][32][YT_LD];         // per consumer wave: a finished output tile on its way out
+    unsigned staged;                    // (rows once) producer waves that have staged their part, summed over the chunks so far
 };
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
@@ -159,6 +170,23 @@ __device__ __forceinline__ void zero16(f32x16 &a)
 __device__ __forceinline__ void wg_sync()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Rows that exist once: they are staged by the producer waves only, and read by every wave that builds an
+// operand from them.  That hand-over does not stop the whole workgroup: a producer wave that has finished
+// its LDS writes adds one to a counter in LDS, and whoever needs the rows waits until the counter has
+// reached the number of producer waves times the number of chunks staged so far.  (LDS operations of a
+// wave complete in order, and the add is issued after the wave's own writes have completed.)
+__device__ __forceinline__ void signal_staged(unsigned *counter, int lane)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (lane == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void wait_staged(unsigned *counter, unsigned target)
+{
+    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target)
+        __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
 }
 
 // MFMA instructions ignore the EXEC mask.  A branch on the wave's role is uniform across the wave
@@ -273,14 +301,15 @@ struct SegTable { int begin[kMaxSegments + 1]; };
 // has read the initial state): every word has one writer and one
 // reader, and the reader zeroes it once it has seen it, so the words are clear again when the launch
 // ends (a replay of a captured launch, which repeats the same epoch, starts from cleared flags).
-template <int NC, int MODE>
+// SEG: the launch has several segments.
+template <int NC, int MODE, bool SEG>
 __device__ __forceinline__ void prefill_body(
     Lds<NC> &lds, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ y, float *__restrict__ state, int has_init,
     float *__restrict__ ws, unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls,
     unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
 {
-    constexpr int NPW = producers(NC);
+    constexpr int NPW = producers(NC), GENS = row_generations(NC);
     constexpr int NP = 64 * NPW;      // producer threads
     constexpr int DV = 32 * NC;       // d_v
     constexpr int VR_LD = DV + 16;
@@ -314,24 +343,24 @@ __device__ __forceinline__ void prefill_body(
     const size_t lane_off = (size_t)(is_p ? 0 : c) * WS_WAVE_SLOTS * kSlotFloats + (size_t)lane * 4;
     const bool holds_x = is_p && c == 0;
 
-    if (MODE == 0 && G > 1 && seg > 0) {
-        // wait for the increments of this call, the last segment also for the initial state to have been read
-        if (tid == 0) {
-            bool gave_up = false;
-            for (int p = has_init && seg == G - 1 ? 0 : 1; p <= seg; ++p) {
-                unsigned *f = flags_unit + p * G + seg;
-                int polls = 0;
-                while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != epoch) {
-                    if (polls++ >= max_polls) { gave_up = true; break; }
-                    __builtin_amdgcn_s_sleep(8);
-                }
-                __hip_atomic_store(f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // A main pass that starts from entries waits for the increments of this call (the last segment also for the initial state to have been
+    // read) while its producers stage the first chunk and build what does not need the sum: 16 units of 777 tokens from a state
+    // 18.1 us with the wait at the start, 17.0 with it here; without one, d_v 128 22.0, 19.5.
+    const bool from_entries = SEG && MODE == 0 && seg > 0;
+    auto wait_flags = [&]() {   // one thread
+        bool gave_up = false;
+        for (int p = has_init && seg == G - 1 ? 0 : 1; p <= seg; ++p) {
+            unsigned *f = flags_unit + p * G + seg;
+            int polls = 0;
+            while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != epoch) {
+                if (polls++ >= max_polls) { gave_up = true; break; }
+                __builtin_amdgcn_s_sleep(8);
             }
-            // sticky: stays set until based_prefill_status has reported it
-            if (gave_up) __hip_atomic_store(status, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        __syncthreads();
-    }
+        // sticky: stays set until based_prefill_status has reported it
+        if (gave_up) __hip_atomic_store(status, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
 
     // Intra-chunk block bb of the chunk whose rows are staged, into generation b: 0 = key tile 0 against
     // query tile 0, 1 = key tile 0 against query tile 1, 2 = key tile 1 against query tile 1 (0 and 2 are
@@ -344,8 +373,8 @@ __device__ __forceinline__ void prefill_body(
         const bool diag = bb != 1;
         f32x16 P;
         zero16(P);
-        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].krow[32 * kt + n][8 * g]);
-        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].qrow[32 * qt + n][8 * g]);
+        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.rows[b % GENS].krow[32 * kt + n][8 * g]);
+        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.rows[b % GENS].qrow[32 * qt + n][8 * g]);
         P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
         float dsum = 0.f;
 #pragma unroll
@@ -428,28 +457,18 @@ __device__ __forceinline__ void prefill_body(
         // (a barrier does not wait for loads into registers, and the flag lets another workgroup overwrite what they read)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (MODE == 0 && G > 1) {
+        if (tid == 0) lds.staged = 0u;   // (it lies in the image)
+        if (MODE == 0 && SEG) {
             if (tid == 0) __hip_atomic_store(flags_unit + (G - 1), epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     };
+    if (!(has_init && seg == 0) && tid == 0) lds.staged = 0u;   // ordered before its first use by the prologue's barriers
     if (!is_p) {
         // =================================== consumer waves =========================================
         f32x16 S[NTILE];       // the five state tiles of this wave's 32 columns
 #pragma unroll
         for (int T = 0; T < NTILE; ++T) zero16(S[T]);
 
-        if (MODE == 0) {
-            // start of segment: the increments of earlier segments
-            for (int p = 1; p <= seg; ++p) {
-                const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
-                f32x4 t[24];
-                load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, t);
-#pragma unroll
-                for (int T = 0; T < NTILE; ++T)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) S[T][r] += t[T * 4 + (r >> 2)][r & 3];
-            }
-        }
         if (has_init && seg == 0) {   // the caller's state
 #pragma unroll
             for (int T = 0; T < NTILE; ++T)
@@ -479,7 +498,20 @@ __device__ __forceinline__ void prefill_body(
 
             wg_sync();   // the producers have staged the first chunk
             if (MODE == 0) build_my_blocks(0);
-            wg_sync();   // the operands of the first chunk are visible
+            if (from_entries && tid == 0) wait_flags();
+            wg_sync();   // the operands of the first chunk are visible (but the denominators, where these need the entries)
+            if (from_entries) {   // the increments of earlier segments
+                for (int p = 1; p <= seg; ++p) {
+                    const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
+                    f32x4 x[24];
+                    load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, x);
+#pragma unroll
+                    for (int T = 0; T < NTILE; ++T)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) S[T][r] += x[T * 4 + (r >> 2)][r & 3];
+                }
+                wg_sync();
+            }
             for (int t = 0; t < n_chunks; ++t) {
                 const int b = t & 1;
                 const int tok0 = tok_begin + C * t;
@@ -529,7 +561,10 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                     for (int sl = 0; sl < 2; ++sl) Y[1] = mfma(vop[2 + sl], as_bf16x8(op[2][sl]), Y[1]);
                 }
-                if (MODE == 0 && NC == 4 && t + 1 < n_chunks) build_my_blocks(b ^ 1);
+                if (MODE == 0 && NC == 4 && t + 1 < n_chunks) {
+                    wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // the next chunk's rows are staged
+                    build_my_blocks(b ^ 1);
+                }
 
                 // ---- update: S += phi(K)^T V over all 160 rows, with the normalisation and the store of
                 // the outputs placed between the matrix instructions
@@ -553,15 +588,14 @@ __device__ __forceinline__ void prefill_body(
                         // row, and stored directly those become 16-byte write requests that stall the memory
                         // pipeline; from LDS the tile leaves as 64-byte row segments, 16 rows a store.
                         const float inv = numerator_only ? 1.f : __builtin_amdgcn_rcpf(dn[qt][0] + dn[qt][1] + dn[qt][2]);
-                        constexpr int LD = NC == 2 ? YT_LD : VR_LD;
-                        uint16_t *yt = NC == 2 ? &lds.yt[c & 1][0][0] : &lds.vrow[b][32 * qt][32 * c];
+                        uint16_t *yt = &lds.yt[c][0][0];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             f32x4 o;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) o[i] = Y[qt][4 * j + i] * inv;
                             const bf16x4 hv = __builtin_convertvector(o, bf16x4);
-                            *reinterpret_cast<u32x2 *>(yt + n * LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
+                            *reinterpret_cast<u32x2 *>(yt + n * YT_LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
                         }
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                         uint16_t *yc = yu + (size_t)tok0 * DV;
@@ -570,7 +604,7 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                         for (int it = 0; it < 2; ++it) {
                             const int row = 16 * it + (lane >> 2), cc = lane & 3;
-                            val[it] = *reinterpret_cast<const u32x4 *>(yt + row * LD + 8 * cc);
+                            val[it] = *reinterpret_cast<const u32x4 *>(yt + row * YT_LD + 8 * cc);
                             yoff[it] = (uint32_t)(32 * qt + row) * (uint32_t)DV + (uint32_t)(32 * c + 8 * cc);
                         }
                         if (tok0 + C <= tok_end) {
@@ -612,15 +646,6 @@ __device__ __forceinline__ void prefill_body(
         const int ptid = tid - 64 * NC;   // thread index among the producers
         f32x16 X;                      // producer 0: the moment tile M' = [k, 1]^T [k, 1]
         zero16(X);
-        if (MODE == 0 && holds_x) {
-            for (int p = 1; p <= seg; ++p) {
-                const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
-                f32x4 t[24];
-                load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, t);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) X[r] += t[20 + (r >> 2)][r & 3];
-            }
-        }
         if (has_init && seg == 0 && holds_x) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -639,7 +664,7 @@ __device__ __forceinline__ void prefill_body(
             // against query tile 0)
             // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
             // not wait for this wave)
-            if (ptid < 2 * C) lds.rows[ptid / C].kts[DP + 2][ptid % C] = 0.f;
+            if (ptid < GENS * C) lds.rows[ptid / C].kts[DP + 2][ptid % C] = 0.f;
             if (ptid < 32) {
                 lds.den[0][2][ptid] = 0.f;
                 lds.den[1][2][ptid] = 0.f;
@@ -676,7 +701,7 @@ __device__ __forceinline__ void prefill_body(
                 }
             };
             auto stage_x = [&](int tok0, int b) {
-                auto &rows = lds.rows[b];
+                auto &rows = lds.rows[b % GENS];
                 u32x4 raw = raw_x;
                 if (is_k) {
                     const bool valid = tok0 + x_tok < tok_end;
@@ -692,6 +717,13 @@ __device__ __forceinline__ void prefill_body(
                         rows.kts[DP + 1][x_tok] = valid ? kCK : 0.f;
                     }
                 } else if (MODE == 0 && has_x) {
+                    f32x4 lo, hi;
+                    lo[0] = bf16lo(raw[0]) * kCQ; lo[1] = bf16hi(raw[0]) * kCQ;
+                    lo[2] = bf16lo(raw[1]) * kCQ; lo[3] = bf16hi(raw[1]) * kCQ;
+                    hi[0] = bf16lo(raw[2]) * kCQ; hi[1] = bf16hi(raw[2]) * kCQ;
+                    hi[2] = bf16lo(raw[3]) * kCQ; hi[3] = bf16hi(raw[3]) * kCQ;
+                    *reinterpret_cast<f32x4 *>(&rows.qs[x_tok][8 * x_h]) = lo;
+                    *reinterpret_cast<f32x4 *>(&rows.qs[x_tok][8 * x_h + 4]) = hi;
                     *reinterpret_cast<u32x4 *>(&rows.qrow[x_tok][8 * x_h]) = raw;
                 }
             };
@@ -714,19 +746,18 @@ __device__ __forceinline__ void prefill_body(
             // at compile time.
             auto build_phiq = [&](const int b, const int qt) {
                 float xr[16];
-                // (slab 8: the linear rows; the operand is q itself, as given)
-                const uint16_t *row = lds.rows[b].qrow[32 * qt + n];
-                u32x2 raw[4];
+                const float *row = lds.rows[b % GENS].qs[32 * qt + n];
+                f32x4 t[4];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) raw[m] = *reinterpret_cast<const u32x2 *>(row + ((4 * g + 4 * m) & 15));
-                const u32x2 ra = raw[0], rb = raw[2];
+                for (int m = 0; m < 4; ++m) t[m] = *reinterpret_cast<const f32x4 *>(row + ((4 * g + 4 * m) & 15));
+                // slab 8: the linear rows; the operand is q itself, as given
+                const uint16_t *p = &lds.rows[b % GENS].qrow[32 * qt + n][4 * g];
+                const u32x2 ra = *reinterpret_cast<const u32x2 *>(p);
+                const u32x2 rb = *reinterpret_cast<const u32x2 *>(p + 8);
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        xr[4 * m + 2 * i] = bf16lo(raw[m][i]) * kCQ;
-                        xr[4 * m + 2 * i + 1] = bf16hi(raw[m][i]) * kCQ;
-                    }
+                    for (int i = 0; i < 4; ++i) xr[4 * m + i] = t[m][i];
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {   // pair slabs: delta = s
                     float pr[8];
@@ -776,7 +807,7 @@ __device__ __forceinline__ void prefill_body(
                 for (int s2 = 0; s2 < NTS; ++s2)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const int off = GEN * b + 16 * (ts0 + s2) + 8 * h;
+                        const int off = GEN * (b % GENS) + 16 * (ts0 + s2) + 8 * h;
                         a03[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a03 + off);
                         a4[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a4 + off);
 #pragma unroll
@@ -800,10 +831,14 @@ __device__ __forceinline__ void prefill_body(
             auto build_phik2 = [&](const int b, const int ts) { build_phik_n(b, ts, std::integral_constant<int, 2>{}); };
             // Inter-chunk denominators of both query tiles from the moments: count + q.z1 + q^T M q / 2.
             auto build_den = [&](const int b) {
+                f32x4 a0[2], a1[2];
                 u32x2 ra[2], rb[2];
 #pragma unroll
                 for (int qt = 0; qt < 2; ++qt) {
-                    const uint16_t *p = &lds.rows[b].qrow[32 * qt + n][4 * g];
+                    const float *row = lds.rows[b % GENS].qs[32 * qt + n];
+                    a0[qt] = *reinterpret_cast<const f32x4 *>(row + 4 * g);
+                    a1[qt] = *reinterpret_cast<const f32x4 *>(row + 8 + 4 * g);
+                    const uint16_t *p = &lds.rows[b % GENS].qrow[32 * qt + n][4 * g];
                     ra[qt] = *reinterpret_cast<const u32x2 *>(p);
                     rb[qt] = *reinterpret_cast<const u32x2 *>(p + 8);
                 }
@@ -832,12 +867,10 @@ __device__ __forceinline__ void prefill_body(
                     float d2 = 0.f;
                     // row of T[e] = 8 (e / 4) + 4 g + e % 4
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t qa = ra[qt][e >> 1], qb = rb[qt][e >> 1];
-                        d2 = fmaf(T[qt][e], e & 1 ? bf16hi(qa) : bf16lo(qa), d2);
-                        d2 = fmaf(T[qt][4 + e], e & 1 ? bf16hi(qb) : bf16lo(qb), d2);
-                    }
-                    const float d = fmaf(d2, 0.5f, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
+                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][e], a0[qt][e], d2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][4 + e], a1[qt][e], d2);
+                    const float d = fmaf(d2, kHalfInvCQ, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
                     const float tot = d + __shfl_xor(d, 32, 64) + cnt_prev;
                     if (g == 0) lds.den[b][0][32 * qt + n] = tot;
                 }
@@ -847,11 +880,11 @@ __device__ __forceinline__ void prefill_body(
             // tile 0; 1: phi(Q) of query tile 1; 2: phi(K) of token slabs 0, 1; 3: phi(K) of token slabs 2, 3.  Of six
             // (d_v 64), 0: denominators and the intra-chunk block off the diagonal; 1, 2: phi(Q); 3, 4: phi(K); 5: the blocks on the
             // diagonal.  Increment pass: phi(K) only, of a token slab each.
-            auto build = [&](const int b) {
+            auto build = [&](const int b, const bool den) {   // den: the denominators too
                 if (MODE == 0 && NPW == 6) {
                     if (c == 0) {
                         role_guard();
-                        build_den(b);
+                        if (den) build_den(b);
                         build_block(b, 1);
                     } else if (c < 3) {
                         build_phiq(b, c - 1);
@@ -865,7 +898,7 @@ __device__ __forceinline__ void prefill_body(
                 } else if (MODE == 0) {
                     if (c == 0) {
                         role_guard();
-                        build_den(b);
+                        if (den) build_den(b);
                         build_phiq(b, 0);
                     } else if (c == 1) {
                         build_phiq(b, 1);
@@ -879,26 +912,54 @@ __device__ __forceinline__ void prefill_body(
                 }
             };
 
-            // ---- the producers' loop: operands one chunk ahead of the consumers, rows of K and Q two -------
-            auto next_rows = [&](int t) {   // in registers: K and Q of chunk t + 2, V of chunk t + 1
+            // ---- the producers' loop: operands one chunk ahead of the consumers; rows two ahead of them where these exist twice ----
+            // in registers: V of chunk t + 1, K and Q of chunk t + GENS
+            auto stage_next = [&](int t) {
                 const int tok_next = tok_begin + C * (t + 1);
                 stage_v(tok_next, (t + 1) & 1);
-                stage_x(tok_next + C, t & 1);
-                load_v(tok_next + C);
-                load_x(tok_next + 2 * C);
+                stage_x(tok_next + C * (GENS - 1), (t + GENS) & 1);
+            };
+            auto load_next = [&](int t) {   // for stage_next(t)
+                const int tok_next = tok_begin + C * (t + 1);
+                load_v(tok_next);
+                load_x(tok_next + C * (GENS - 1));
             };
             load_x(tok_begin);
             load_v(tok_begin);
             stage_x(tok_begin, 0);
-            load_x(tok_begin + C);
-            wg_sync();   // the first chunk's rows are staged
-            next_rows(-1);
-            build(0);
+            if (GENS == 2) {
+                load_x(tok_begin + C);
+                wg_sync();   // the first chunk's rows are staged
+                stage_next(-1);
+                load_next(0);
+            } else {
+                stage_v(tok_begin, 0);
+                if (n_chunks > 1) load_next(0);
+                wg_sync();
+            }
+            build(0, !from_entries);
             wg_sync();   // the first chunk's operands are visible
+            if (from_entries) {
+                if (holds_x) {
+                    role_guard();
+                    for (int p = 1; p <= seg; ++p) {
+                        const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
+                        f32x4 x[24];
+                        load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, x);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) X[r] += x[20 + (r >> 2)][r & 3];
+                    }
+                    build_den(0);
+                }
+                wg_sync();
+            }
             for (int t = 0; t < n_chunks; ++t) {
                 const int b = t & 1;
                 const bool has_next = t + 1 < n_chunks;
-                if (has_next) next_rows(t);
+                if (has_next) stage_next(t);
+                if (GENS == 1 && has_next) signal_staged(&lds.staged, lane);
+                if (GENS == 2 ? has_next : t + 2 < n_chunks) load_next(t + 1);   // (rows past the end: the last one again)
+                if (GENS == 1 && has_next) wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // all of the next chunk's rows
                 if (holds_x) {
                     // M' += K'^T K' of the chunk the consumers are working on (the operand of tile 4 carries k
                     // as given in rows 0..15 and the valid flag in row 16); the denominators of the next chunk
@@ -910,7 +971,7 @@ __device__ __forceinline__ void prefill_body(
                         X = mfma(e, e, X);
                     }
                 }
-                if (has_next) build(b ^ 1);
+                if (has_next) build(b ^ 1, true);
                 wg_sync();   // the next chunk's operands are visible
             }
         }
@@ -957,8 +1018,9 @@ __device__ __forceinline__ void prefill_body(
 
 // Grid: first the (G - 1) increments of every unit, then the main-pass workgroups segment by segment
 // (all segment-0 workgroups first: they depend on nothing and fill the slots the increment
-// workgroups leave free).
-template <int NC>
+// workgroups leave free).  A launch of one segment is a kernel of its own, without the code of increments and entries: a short call runs
+// its code once and waits for its instructions (16 units of 64 tokens: 6.5 and 7.8 us at the two widths with one kernel for all, 6.1 and 7.3).
+template <int NC, bool SEG>
 __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, float *__restrict__ state, int has_init, float *__restrict__ ws,
@@ -966,15 +1028,19 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
     SegTable segs, int G, int U)
 {
     __shared__ __align__(16) Lds<NC> lds;
-    const int n_inc = U * (G - 1);
     int bid = blockIdx.x;
-    if (bid < n_inc) {
-        prefill_body<NC, 1>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
-                            bid % (G - 1), bid / (G - 1));
+    if constexpr (!SEG) {
+        prefill_body<NC, 0, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, bid);
     } else {
-        bid -= n_inc;
-        prefill_body<NC, 0>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
-                            bid / U, bid % U);
+        const int n_inc = U * (G - 1);
+        if (bid < n_inc) {
+            prefill_body<NC, 1, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
+                                      bid % (G - 1), bid / (G - 1));
+        } else {
+            bid -= n_inc;
+            prefill_body<NC, 0, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
+                                      bid / U, bid % U);
+        }
     }
 }
 
@@ -1082,7 +1148,8 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     // that has never been used hold whatever was in that memory.
     static std::atomic<unsigned> calls{0};
     const unsigned epoch = 0x5EED0000u + calls.fetch_add(1u) + 1u;
-    hipLaunchKernelGGL((prefill_mfma_kernel<NC>), dim3((unsigned)(U * (2 * G - 1))), dim3(64 * (NC + producers(NC))), 0, s, q, k, v,
+    const auto kernel = G > 1 ? prefill_mfma_kernel<NC, true> : prefill_mfma_kernel<NC, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(U * (2 * G - 1))), dim3(64 * (NC + producers(NC))), 0, s, q, k, v,
                        y, state, flags_word, ws, flags, status, g_flag_poll_limit.load(), epoch, N, segs, G, U);
     return hipGetLastError();
 }
