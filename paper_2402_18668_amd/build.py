@@ -44,7 +44,7 @@ def bind_command() -> list:
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", os.path.join(CSRC, "bind.cpp"), "-o", BIND]
     cmd += ["-I" + d for d in [*include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]]
     cmd += ["-L" + d for d in library_paths()]
-    return cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    return cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python"]
 
 
 def build(verbose: bool = False, jobs: int = 8) -> str:

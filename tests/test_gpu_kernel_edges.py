@@ -437,3 +437,26 @@ def test_prefill_segment_rule(based, U, dv, N):
     Sw, zw = oracle.linattn_state(k[at], v[at])
     check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
+
+
+# outputs are allocated past the dispatcher, except under a mode that looks at every operator
+def test_outputs_under_a_dispatch_mode(based):
+    import torch
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.ops = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    q, k, v = (up(synth.round_to(synth.normal(91 + i, (1, 2, 20, d), 0.5), "bf16"), "bf16") for i, d in enumerate((16, 16, 64)))
+    want = based.prefill(q, k, v)
+    assert want.shape == v.shape and want.dtype == v.dtype and want.device == v.device and want.is_contiguous()
+    with Seen() as seen:
+        got = based.prefill(q, k, v)
+    assert any("empty" in op for op in seen.ops)
+    assert torch.equal(got, want)
