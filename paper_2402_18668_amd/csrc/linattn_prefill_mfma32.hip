@@ -471,17 +471,15 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
         }
         return o;
     };
+    // (every wave multiplies: the first one, alone, would be the last to finish)
+    const float dw = w == 0 ? 0.5f : 1.f;   // delta = 0: x_a^2 / sqrt(2)
     auto q_op = [&](const QSrc &s, int tt) {
         float pr[8];
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                pr[4 * jj + i] = s.a[4 * jj + i] * s.b[jj][i + tt];
-        if (tt == 0 && w == 0) {   // delta = 0: x_a^2 / sqrt(2)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pr[e] *= 0.5f;
-        }
+                pr[4 * jj + i] = (tt == 0 ? s.a[4 * jj + i] * dw : s.a[4 * jj + i]) * s.b[jj][i + tt];
         return pack8(pr);
     };
     // phi(K)^T operand of token slab ts of tile tt: row n, k-slots the tokens 16 ts + 4 g + {0..3, 8..11}
