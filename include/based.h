@@ -205,9 +205,9 @@ int based_decode_step_numerator(const void *q, const void *k, const void *v, voi
  *
  *   gamma  [H]        in, fp32, device: the rate of every head (1 = no decay)
  *   gate   [B][N][H]  in, dtype, device, or NULL (based_decode_step_decay: [B][H]): scales the rows of y
- * Everything else as based_prefill / based_decode_step (canonical state).  Both dtypes run on the fp32
- * kernels (fp32 matrix instructions for the prefill), so based_prefill_decay needs a
- * workspace of based_prefill_decay_workspace_bytes, which differs from based_prefill's for bf16.
+ * Everything else as based_prefill / based_decode_step (canonical state).  Both dtypes run on the
+ * kernels of fp32 precision, so based_prefill_decay needs a workspace of
+ * based_prefill_decay_workspace_bytes, which differs from based_prefill's for bf16.
  */
 size_t based_prefill_decay_workspace_bytes(int B, int H, int N, int d_feat, int d_v, int dtype);
 int based_prefill_decay(const void *q, const void *k, const void *v, void *y, void *state, int has_init,

@@ -89,11 +89,10 @@ hipError_t launch_prefill_f32(const void *q, const void *k, const void *v, void 
                               void *workspace, const float *gamma, const void *gate, int H, int U, int N, int dp, int dv,
                               int dtype, hipStream_t s);
 size_t prefill_f32_workspace_bytes(int U, int N, int dp, int dv);
-// the same call on the bf16 matrix instructions, operands in three parts (fp32, d' = 16, no decay, more than 48 tokens);
-// workspace as above
+// the same call on the bf16 matrix instructions, operands in three parts (fp32, d' = 16, more than 48 tokens); workspace as above
 bool prefill_f32x3_supported(int dp, int dtype, int N);
 hipError_t launch_prefill_f32x3(const void *q, const void *k, const void *v, void *y, float *state, int has_init, void *workspace,
-                                int U, int N, int dv, hipStream_t s);
+                                const float *gamma, const void *gate, int H, int U, int N, int dv, hipStream_t s);
 bool prefill_mfma_supported(int dp, int dv, int dtype);
 size_t prefill_mfma_workspace_bytes(int U, int N, int dp, int dv);
 // packed_state != 0: the state buffer is the packed layout (one row per unordered feature pair);

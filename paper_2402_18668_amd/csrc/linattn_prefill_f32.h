@@ -1,5 +1,6 @@
 // Causal Taylor linear attention, chunked prefill on the fp32 matrix instructions: fp32 inputs at every supported d' (at d' = 16
-// calls of up to 48 tokens: linattn_prefill_f32x3.hip has the others), bf16 inputs at the d' that have no bf16 matrix-core kernel (8, 24), and the decay variant.  Every product and sum is fp32.
+// calls of up to 48 tokens: linattn_prefill_f32x3.hip has the others), bf16 inputs at the d' that have no bf16 matrix-core
+// kernel (8, 24), and the decay variant of both and of every bf16 call.  Every product and sum is fp32.
 //
 // Chunked form of Sec. 4 with chunks of 16 tokens: inside a chunk the masked quadratic product P = 1 + A + A^2/2,
 // A = Q K^T; across chunks the running KV-state S (Eq. 3), read out with phi(Q) and updated with phi(K)^T V.

@@ -19,8 +19,8 @@ hipError_t launch_prefill_f32(const void *q, const void *k, const void *v, void 
                               void *workspace, const float *gamma, const void *gate, int H, int U, int N, int dp, int dv,
                               int dtype, hipStream_t s)
 {
-    if (!gamma && !gate && prefill_f32x3_supported(dp, dtype, N))
-        return launch_prefill_f32x3(q, k, v, y, state, has_init, workspace, U, N, dv, s);
+    if (prefill_f32x3_supported(dp, dtype, N))
+        return launch_prefill_f32x3(q, k, v, y, state, has_init, workspace, gamma, gate, H, U, N, dv, s);
     const pf32::DecayArg dec{gamma, gate, H};
     switch (dp) {
     case 8: return pf32::launch_dp<8>(q, k, v, y, state, has_init, workspace, U, N, dv, dtype, dec, s);

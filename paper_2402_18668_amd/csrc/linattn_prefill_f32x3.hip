@@ -1,5 +1,5 @@
-// Causal Taylor linear attention, chunked prefill of fp32 inputs at d' = 16 (no decay) on the bf16 matrix instructions, at
-// fp32 precision: every operand is cut into three bf16 parts, x = h + m + l, and a product is the sum of the six
+// Causal Taylor linear attention, plain and with decay, chunked prefill of fp32 inputs at d' = 16 on the bf16 matrix instructions,
+// at fp32 precision: every operand is cut into three bf16 parts, x = h + m + l, and a product is the sum of the six
 // products of parts down to 2^-18 of it (h h, h m, m h, m m, h l, l h; what is left out is below 2^-25).
 //
 // Why: a fp32 matrix instruction occupies the vector ALU (measured with two waves on a SIMD, one of them all 16x16x4 fp32
@@ -16,23 +16,32 @@
 // delta = 2 T (rows 0 .. 15, a = row) and 2 T + 1; tile 4 the 16 linear rows, the constant row (16), zeros (17 .. 23), and delta = 8
 // for a < 8 (24 .. 31).  A row holds the plain sum of k_a k_b v; the readout weighs q_a q_b with 1, with 1/2 for a = b.
 //
-// Work split.  A workgroup of six waves takes 64 columns of one (unit, segment), chunks of 32 tokens.  Waves 0 .. 4 own a tile each, for
+// Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment), chunks of 32 tokens.  Waves 0 .. 4 own a tile each, for
 // both column tiles of 32: a feature is built and cut once per workgroup and used where it is built.  Wave 5 has the
-// intra-chunk block P = 1 + A + A^2 / 2.  48 and 30 matrix instructions per chunk; two workgroups to a CU are three waves on every
-// SIMD.  The six partial outputs and denominators of a chunk meet in LDS.  K-state: fp32 sums of the features a lane builds.
+// intra-chunk block P = 1 + A + A^2 / 2.  48 and 30 matrix instructions per chunk.  Waves 6 and 7 help to stage rows and to finish
+// outputs (a workgroup of six reserves two waves on every SIMD all the same, and one went to a CU instead of two).  The six partial
+// outputs and denominators of a chunk meet in LDS.  K-state: fp32 sums of the features a lane builds.
 // Two barriers a chunk: rows staged, partial outputs free | partial outputs written, rows free.
 //
 // Segments as in linattn_prefill_f32.h: an increment launch, then the main launch, each segment from the sum of the entries before it.
+//
+// Decay: as there, in a variant of its own.  The factors are powers of the rate from a table in LDS: on the features of the update,
+// the old state, the state's part of the outputs and P.
 //
 // Values that are not finite: as in linattn_prefill_f32.h (a chunk with one in V is summed key by key).
 //
 // Measured against linattn_prefill_f32.h (us): 128 units of 2048 tokens, d_v 64, 193 -> 141 (increments 48, main launch 126 in a trace with cold
 // inputs, at 2.0 GHz); 16 units of 2048 111 -> 57, of 777 43 -> 28; 512 units of 2048 505 -> 381.  Bound by vector instructions, 590 per
-// tile, wave and chunk, 350 of them cutting features and state: vector ALU 52 %, matrix pipe 27 % of the cycles, LDS 33 %.  Error against
-// float64 (2-norm, 16 to 8192 tokens): y 0.6e-7 to 1.5e-7, S 0.5e-7 to 2.1e-7; there 0.8e-7 to 3.2e-7 and 0.8e-7 to 3.9e-7.
+// tile, wave and chunk, 350 of them cutting features and state: vector ALU 52 %, matrix pipe 27 % of the cycles, LDS 33 %.  With
+// decay: 128 units of 2048, d_v 64, 230 -> 172; 16 of 300 50 -> 33; 2 of 49 24 -> 17.
+// Error against float64 (2-norm, 16 to 8192 tokens): y 0.6e-7 to 1.5e-7, S 0.5e-7 to 2.1e-7; there 0.8e-7 to 3.2e-7 and 0.8e-7 to 3.9e-7;
+// with decay 1.1e-7 to 1.6e-7 and 0.8e-7 to 2.5e-7, there 1.6e-7 to 2.8e-7 and 1.6e-7 to 3.5e-7.
 #include "common.h"
 
 #include <utility>
+
+// Sums and products as they are written: at a rate of 1 the decay variant multiplies by ones and gives the plain kernel's bits.
+#pragma clang fp contract(off)
 
 namespace based {
 
@@ -57,6 +66,7 @@ constexpr size_t kEntryFloats = (size_t)ROWS * COLS + ROWS;
 
 constexpr int K_LD = C + 4;            // K^T rows (the 16-byte reads of 16 rows fall into different banks)
 constexpr int K_ONE = 16, K_ZERO = 17; // rows of ones (zero past the end) and of zeros
+constexpr int K_DECAY = 18;            // row of each token's factor in the state after the chunk
 // Q rows, so that both factors of a slab's rows are runs of 16 from one place: q, q again (indices a + delta need no wrap), 1 x 16,
 // q_8 .. q_15, [1, 0 x 7], q_0 .. q_7
 constexpr int Q_LD = 76, Q_ONES = 32, Q_ONES_HI = 40, Q_UNIT_LO = 56;
@@ -64,7 +74,7 @@ constexpr int V_LD = COLS + 16;
 constexpr int IMG_LD = COLS + 4;
 
 struct alignas(16) Rows {
-    float kt[18][K_LD];
+    float kt[19][K_LD];
     float q[C][Q_LD];
     uint16_t v[3][C][V_LD];   // the three parts
     int bad;                  // number of the last chunk with a value in V that is not finite, plus one
@@ -75,6 +85,7 @@ template <bool INC> struct Lds {
     float den[SEND][C];
     float z[ROWS];
     int turn;
+    float power[C + 1];       // of the decay rate
 };
 static_assert(2 * sizeof(Lds<false>) <= 160 * 1024, "two workgroups to a CU");
 static_assert(sizeof(Lds<true>) <= 80 * 1024, "");
@@ -147,13 +158,18 @@ __device__ __forceinline__ Canon canon(int row)
     return {fl == 16 ? 0 : -1, fl == 16 ? 0 : -1, 1.f};
 }
 
+struct DecayArg {
+    const float *gamma, *gate;   // [H] (null: 1); [B][N][H], factors of the rows of y (null: 1)
+    int H;
+};
+
 // The launch covers `slices` slices of 64 columns from first_slice on.  has_init: bit 0 an initial state is given, bit 2 the outputs are
 // the numerators alone.  INC: state increment of the segment only, to entry 1 + seg (segment 0 also converts the caller's state
 // into entry 0).
-template <int DV, bool INC>
+template <int DV, bool INC, bool DECAY>
 __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict__ q, const float *__restrict__ k,
                                                         const float *__restrict__ v, float *__restrict__ y, float *state, int has_init,
-                                                        int N, float *ws, int seg_len, int G, int first_slice, int slices)
+                                                        int N, float *ws, int seg_len, int G, int first_slice, int slices, DecayArg dec)
 {
     constexpr int SL = DV / COLS;
     __shared__ __align__(16) Lds<INC> lds;
@@ -180,6 +196,10 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 : nullptr;
     float *zu = state ? state + (size_t)u * state_stride(DP, DV) + (size_t)D * DV : nullptr;
     float *entries = ws ? ws + ((size_t)u * SL + slice) * G * kEntryFloats : nullptr;
+
+    const float gm = DECAY && dec.gamma ? dec.gamma[u % dec.H] : 1.f;
+    const float *gate = DECAY && dec.gate ? dec.gate + (size_t)(u / dec.H) * N * dec.H + u % dec.H : nullptr;
+    auto tokens = [&](int t) { return min(C, end - begin - C * t); };   // of chunk t
 
     // waves 0 .. 4: S[c][r] = row 8 (r / 4) + 4 g + r % 4 of the tile, column 32 c + n; z: row n of the tile, summed over the halves
     f32x16 S[2];
@@ -235,7 +255,8 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         if (g == 0) image_z[32 * w + n] = zt;
     };
     auto export_image = [&]() {
-        auto half_difference = [&](float a, float b) { return a == b ? 0.f : 0.5f * (a - b); };   // (equal infinities: none)
+        const float g_all = DECAY ? powf(gm, (float)N) : 1.f;
+        auto half_difference = [&](float a, float b) { return a == b ? 0.f : 0.5f * (a - b) * g_all; };   // (equal infinities: none)
         __syncthreads();
 #pragma unroll 1
         for (int i = tid; i < PIECES; i += NT) {
@@ -284,6 +305,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         if (tile) {
             // the sum of the entries before the segment, two at a time
             int e = init ? 0 : 1;
+            const float g_seg = DECAY ? powf(gm, (float)seg_len) : 1.f;
             auto add = [&](auto count) {
                 constexpr int E = decltype(count)::value;
                 f32x4 x[E][8];
@@ -293,7 +315,12 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                     xz[i.value] = *entry_z(e + i.value);
                 });
                 for_n<E>([&](auto i) {
-                    for_n<32>([&](auto r) { S[r.value / 16][r.value % 16] += x[i.value][r.value / 4][r.value % 4]; });
+                    for_n<32>([&](auto r) {
+                        float &a = reinterpret_cast<float *>(&S[r.value / 16])[r.value % 16];
+                        if (DECAY) a *= g_seg;
+                        a += x[i.value][r.value / 4][r.value % 4];
+                    });
+                    if (DECAY) z *= g_seg;
                     z += g == 0 ? xz[i.value] : 0.f;
                 });
                 e += E;
@@ -374,6 +401,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             const bool past = tok0 + p.k >= end;
             for_n<4>([&](auto i) { rows.kt[p.ck + i.value][p.k] = past ? 0.f : raw[1][i.value]; });
             if (p.ck == 0) rows.kt[K_ONE][p.k] = past ? 0.f : 1.f;
+            if (DECAY && p.ck == 4) rows.kt[K_DECAY][p.k] = lds.power[max(tokens(t) - 1 - p.k, 0)];
         }
         if (!INC && q_piece) {
             *reinterpret_cast<f32x4 *>(&rows.q[p.k][p.ck]) = raw[1];
@@ -383,7 +411,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     };
 
     // S += phi(K)^T V of a chunk
-    auto update = [&](const Rows &rows) {
+    auto update = [&](const Rows &rows, int t) {
         f32x16 d[2];
         float zc = 0.f;
         int ka, kb;
@@ -395,6 +423,10 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                 const int tok = 16 * s.value + 4 * g + 8 * h.value;
                 const f32x4 a = *reinterpret_cast<const f32x4 *>(&rows.kt[ka][tok]), b = *reinterpret_cast<const f32x4 *>(&rows.kt[kb][tok]);
                 for_n<4>([&](auto i) { f[4 * h.value + i.value] = a[i.value] * b[i.value]; });
+                if (DECAY) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(&rows.kt[K_DECAY][tok]);
+                    for_n<4>([&](auto i) { f[4 * h.value + i.value] *= x[i.value]; });
+                }
             });
             zc += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
             const Parts op = split8([&](int i) { return f[i]; });
@@ -403,6 +435,11 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                 __builtin_amdgcn_sched_barrier(0);   // (bounds what is in flight at a time)
             });
         });
+        if (DECAY) {
+            const float g_s = lds.power[tokens(t)];
+            z *= g_s;
+            for_n<2>([&](auto c) { S[c.value] *= g_s; });
+        }
         z += zc;
         for_n<2>([&](auto c) { S[c.value] += d[c.value]; });
     };
@@ -414,6 +451,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         for_n<8>([&](auto j) { rows.q[i % C][Q_UNIT_LO + j.value] = j.value == 0 ? 1.f : 0.f; });
     }
     if (tid == 0) lds.rows[0].bad = 0;
+    if (DECAY && tid <= C) lds.power[tid] = powf(gm, (float)tid);
     __syncthreads();
     load_raw(begin, place());
     stage(0, lds.rows[0], place());
@@ -430,7 +468,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             role_guard();
             for (int t = 0; t < chunks; ++t) {
                 fresh_lane();
-                update(lds.rows[t & 1]);
+                update(lds.rows[t & 1], t);
                 next_chunk(t);
             }
         } else {
@@ -451,7 +489,8 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             d[s.value] = lds.den[s.value][tok];
         });
         const float den = ((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]);
-        const float inv = numerator_only ? 1.f : 1.f / den;
+        float inv = numerator_only ? 1.f : 1.f / den;
+        if (gate && tok0 + tok < end) inv *= gate[(size_t)(tok0 + tok) * dec.H];
         const f32x4 sum = ((x[0] + x[1]) + (x[2] + x[3])) + (x[4] + x[5]);
         if (tok0 + tok < end) *reinterpret_cast<f32x4 *>(yu + (size_t)tok0 * DV + (unsigned)(tok * DV + 4 * cq)) = sum * inv;
     };
@@ -502,12 +541,17 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                 });
                 __builtin_amdgcn_sched_barrier(0);   // (bounds what is in flight at a time)
             });
+            if (DECAY) {   // the state before the chunk, at query n
+                const float g_q = lds.power[n + 1];
+                for_n<2>([&](auto c) { Y[c.value] *= g_q; });
+                dsum *= g_q;
+            }
             dsum = add_halves(dsum);
             if (g == 0) lds.den[w][n] = dsum;
             put_partial(Y);
             fresh_lane();
             __builtin_amdgcn_sched_barrier(0);
-            update(rows);
+            update(rows, t);
             next_chunk(t);
         }
         if (writes_state) put_image();
@@ -529,8 +573,11 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             }
             float dsum = 0.f;
             for_n<16>([&](auto r) {
-                const float x = P[r.value], p = fmaf(x, fmaf(x, 0.5f, 1.f), 1.f);
-                P[r.value] = 8 * (r.value >> 2) + 4 * g + (r.value & 3) <= n ? p : 0.f;
+                const int key = 8 * (r.value >> 2) + 4 * g + (r.value & 3);
+                const float x = P[r.value];
+                float p = fmaf(x, fmaf(x, 0.5f, 1.f), 1.f);
+                if (DECAY) p *= lds.power[max(n - key, 0)];
+                P[r.value] = key <= n ? p : 0.f;
                 dsum += P[r.value];
             });
             dsum = add_halves(dsum);
@@ -580,9 +627,9 @@ inline int segments(int U, int N, int dv)
 }
 inline int segment_len(int N, int G) { return ((N + G - 1) / G + C - 1) / C * C; }
 
-template <int DV>
+template <int DV, bool DECAY>
 hipError_t launch(const void *q, const void *k, const void *v, void *y, float *state, int has_init, void *workspace, int U, int N,
-                  hipStream_t s)
+                  DecayArg dec, hipStream_t s)
 {
     constexpr int SL = DV / COLS;
     int G = segments(U, N, DV);
@@ -594,8 +641,8 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     float *ws = static_cast<float *>(workspace);
     auto go = [&](auto increment, int first_slice, int slices) {
         constexpr bool INC = decltype(increment)::value;
-        hipLaunchKernelGGL((prefill_kernel<DV, INC>), dim3((unsigned)(U * slices * (INC ? G - 1 : G))), dim3(NT), 0, s, (const float *)q,
-                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, G, first_slice, slices);
+        hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY>), dim3((unsigned)(U * slices * (INC ? G - 1 : G))), dim3(NT), 0, s, (const float *)q,
+                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, G, first_slice, slices, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;
@@ -616,11 +663,14 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
 // 15 to 68 and 12 to 59.)
 bool prefill_f32x3_supported(int dp, int dtype, int N) { return dtype == BASED_F32 && dp == f32x3::DP && N > 48; }
 
-hipError_t launch_prefill_f32x3(const void *q, const void *k, const void *v, void *y, float *state, int has_init, void *workspace, int U,
-                                int N, int dv, hipStream_t s)
+hipError_t launch_prefill_f32x3(const void *q, const void *k, const void *v, void *y, float *state, int has_init, void *workspace,
+                                const float *gamma, const void *gate, int H, int U, int N, int dv, hipStream_t s)
 {
-    return dv == 64 ? f32x3::launch<64>(q, k, v, y, state, has_init, workspace, U, N, s)
-                    : f32x3::launch<128>(q, k, v, y, state, has_init, workspace, U, N, s);
+    const f32x3::DecayArg dec{gamma, static_cast<const float *>(gate), H};
+#define F32X3_LAUNCH(DV, DECAY) f32x3::launch<DV, DECAY>(q, k, v, y, state, has_init, workspace, U, N, dec, s)
+    if (gamma || gate) return dv == 64 ? F32X3_LAUNCH(64, true) : F32X3_LAUNCH(128, true);
+    return dv == 64 ? F32X3_LAUNCH(64, false) : F32X3_LAUNCH(128, false);
+#undef F32X3_LAUNCH
 }
 
 }  // namespace based

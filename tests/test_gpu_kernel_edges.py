@@ -113,6 +113,25 @@ def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
         assert err < 1e-6, (what, err)
 
 
+# .. and with decay: a rate of 1, a usual one and 0, a gate, the second part from the state of the first
+@pytest.mark.parametrize("dv,N1,N", [(64, 49, 98), (128, 64, 161), (64, 95, 224), (128, 130, 1321)])
+def test_prefill_fp32_decay_three_parts(based, dv, N1, N):
+    dp, H = 16, 3
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "dtype": "f32"})
+    q, k, v = synth.linattn_inputs(wl, units=H, N=N)
+    gamma, gate = np.array([1.0, 0.95, 0.0], dtype=np.float32), synth.normal(78, (1, N, H), 1.0).astype(np.float32)
+    want = oracle.linattn_decay(q, k, v, gamma.astype(np.float64), gate=gate[0].T.astype(np.float64))
+    state = based.alloc_state(1, H, dp, dv)
+    got = [down(based.prefill_decay(*(up(a[:, lo:hi], "f32", (1, H, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))),
+                                    up(gamma, "f32"), state=state, has_init=lo > 0, gate=up(gate[:, lo:hi], "f32"))).reshape(H, hi - lo, dv)
+           for lo, hi in ((0, N1), (N1, N))]
+    S, z = based.state_export(state, 1, H, dp, dv)
+    for a, w, what in zip((np.concatenate(got, 1), down(S), down(z)), want, "ySz"):
+        w = np.asarray(w, dtype=np.float64)
+        err = np.linalg.norm(a.reshape(w.shape) - w) / np.linalg.norm(w)
+        assert err < 1e-6, (what, err)
+
+
 # decay at the same edges: the last chunk holds fewer than 16 tokens, increments of several segments, gate
 @pytest.mark.parametrize("dtype,dp,dv,N", [("bf16", 32, 64, 90), ("f32", 32, 128, 300), ("bf16", 24, 128, 801), ("bf16", 16, 64, 31)])
 def test_prefill_decay_edges(based, dtype, dp, dv, N):
