@@ -35,7 +35,7 @@
 // LDS: the same time, more LDS.  Four waves with 512 registers and half the exchange: the same, a lone wave issues a
 // vector instruction every 4 cycles instead of 2.  Reading operands' rows a phase ahead: no gain.)
 // Measured (d_v 64; before: four waves per 32 columns, 500 vector instructions per wave and 32 tokens, state buffer accessed
-// element by element): 32 units of 16384 tokens 266 -> 213 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 27 us, from
+// element by element): 32 units of 16384 tokens 266 -> 210 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 27 us, from
 // a state 83 -> 40 us.
 #include "common.h"
 
