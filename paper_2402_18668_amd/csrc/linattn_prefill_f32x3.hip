@@ -30,6 +30,16 @@
 //
 // Values that are not finite: as in linattn_prefill_f32.h (a chunk with one in V is summed key by key).
 //
+// Range.  Below 2^-103 the third part of a value is not a normal bf16 number and the three hold it to 2^-134 only; a part past the
+// largest bf16 number is infinite.  So a segment goes on with the fp32 matrix instructions (32x32x2: the same operands, uncut, and the same
+// accumulators) from the first chunk on that holds a value, not 0, outside 2^-38 .. 2^20 in K or Q (their products: 2^-76 .. 2^40) or 2^-60 ..
+// 2^40 in V, or from its start if the state it starts from has an entry outside 2^-100 .. 2^100.  Inside, the parts hold all 24 bits of every
+// value of the rows and of every feature, and no sum passes 2^112.  An entry of the state may get below 2^-103 (a sum of products of small
+// values, or what cancellation leaves): what a query, 2^40 at most per row, then misses is 2^-34 of the smallest value of V at most, for 153 rows 2^-26.
+// With decay, where a state shrinks, it is looked at in every chunk, and a rate whose 32nd power is outside 2^-26 .. 2^26 (and
+// not 0) has no other instructions.  Of N(0, 1 / 4) values one in 2e11 of K and Q is outside.  Looking takes 1.5 % of the time, by the
+// threads that stage the rows (waves 6 and 7 alone, with loads of their own: 4 %).  128 units of 2048 tokens, d_v 64, all of them uncut: 253 us.
+//
 // Measured against linattn_prefill_f32.h (us): 128 units of 2048 tokens, d_v 64, 193 -> 141 (increments 48, main launch 126 in a trace with cold
 // inputs, at 2.0 GHz); 16 units of 2048 111 -> 57, of 777 43 -> 28; 512 units of 2048 505 -> 381.  Bound by vector instructions, 590 per
 // tile, wave and chunk, 350 of them cutting features and state: vector ALU 52 %, matrix pipe 27 % of the cycles, LDS 33 %.  With
@@ -37,6 +47,8 @@
 // Error against float64 (2-norm, 16 to 8192 tokens): y 0.6e-7 to 1.5e-7, S 0.5e-7 to 2.1e-7; there 0.8e-7 to 3.2e-7 and 0.8e-7 to 3.9e-7;
 // with decay 1.1e-7 to 1.6e-7 and 0.8e-7 to 2.5e-7, there 1.6e-7 to 2.8e-7 and 1.6e-7 to 3.5e-7.
 #include "common.h"
+
+#include <limits.h>
 
 #include <utility>
 
@@ -77,7 +89,6 @@ struct alignas(16) Rows {
     float kt[19][K_LD];
     float q[C][Q_LD];
     uint16_t v[3][C][V_LD];   // the three parts
-    int bad;                  // number of the last chunk with a value in V that is not finite, plus one
 };
 template <bool INC> struct Lds {
     Rows rows[INC ? 2 : 1];   // (the increment has no partial outputs: two generations, one barrier)
@@ -85,6 +96,8 @@ template <bool INC> struct Lds {
     float den[SEND][C];
     float z[ROWS];
     int turn;
+    int wide_from;            // the first chunk seen with a value in K, Q or V whose parts would not hold it
+    int bad[2];               // number of the last even and odd chunk with a value in V that is not finite, plus one
     float power[C + 1];       // of the decay rate
 };
 static_assert(2 * sizeof(Lds<false>) <= 160 * 1024, "two workgroups to a CU");
@@ -145,6 +158,27 @@ __device__ __forceinline__ void mfma6(const Parts &a, const Parts &b, f32x16 &ac
     constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
     for_n<6>([&](auto i) { acc = mfma(a.p[pa[i.value]], b.p[pb[i.value]], acc); });
 }
+
+// The same of the values themselves, each lane's eight, on the fp32 matrix instruction.
+template <typename A, typename B> __device__ __forceinline__ void mfma_f32(A &&a, B &&b, f32x16 &acc)
+{
+    for_n<8>([&](auto i) { acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a(i.value), b(i.value), acc, 0, 0, 0); });
+}
+// Largest and smallest magnitude but 0 of the values seen, as their bits without the sign, doubled (less 1 for the smallest: 0 is last).
+struct Magnitudes {
+    uint32_t most = 0, least = ~0u;
+    __device__ __forceinline__ void see(float x)
+    {
+        const uint32_t u = __float_as_uint(x) << 1;
+        most = max(most, u);
+        least = min(least, u - 1);
+    }
+    // one below 2^LO, or above 2^HI or not finite
+    template <int LO, int HI> __device__ __forceinline__ bool outside() const
+    {
+        return least < ((127u + LO) << 24) - 1 || most > (127u + HI) << 24;
+    }
+};
 
 // Canonical rows (Eq. 4 order) of a state row, and what a stored value is multiplied by to give the canonical one; r1 < 0: zeros.
 struct Canon { int r1, r2; float scale; };
@@ -332,6 +366,14 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         import_state();
     }
 
+    bool wide = false;   // something but the rows keeps this wave from cutting its operands: the state (waves 0 .. 4), the rate's powers
+    auto state_outside = [&]() {
+        Magnitudes m;
+        for_n<32>([&](auto r) { m.see(S[r.value / 16][r.value % 16]); });
+        return __any(m.outside<-100, 100>()) != 0;
+    };
+    if (!INC && tile && (init || G > 1)) wide = state_outside();
+
     // What is computed from the lane's place is not kept past a call of this.
     auto fresh_lane = [&]() {
         asm volatile("" : "+v"(lane));
@@ -360,6 +402,16 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a));
         const u32x2 x8 = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a + 8 * V_LD)));
         return __builtin_bit_cast(bf16x8, u32x4{x[0], x[1], x8[0], x8[1]});
+    };
+    // the values themselves, from memory
+    auto read_v_f32 = [&](int tok0, int s, int c) {
+        f32x8 x;
+        for_n<8>([&](auto i) {
+            const int tok = tok0 + 16 * s + 4 * g + (i.value & 3) + 8 * (i.value >> 2);
+            const float t = vu[(size_t)min(tok, end - 1) * DV + 32 * c + n];
+            x[i.value] = tok < end ? t : 0.f;
+        });
+        return x;
     };
     auto v_parts = [&](const Rows &rows, int s, int c) {
         Parts o;
@@ -394,8 +446,6 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             *reinterpret_cast<u32x2 *>(&rows.v[0][p.v][p.cv]) = u32x2{a.h, b.h};
             *reinterpret_cast<u32x2 *>(&rows.v[1][p.v][p.cv]) = u32x2{a.m, b.m};
             *reinterpret_cast<u32x2 *>(&rows.v[2][p.v][p.cv]) = u32x2{a.l, b.l};
-            const float probe = fmaf(0.f, x[0], fmaf(0.f, x[1], fmaf(0.f, x[2], 0.f * x[3])));
-            if (!INC && probe != 0.f) rows.bad = t + 1;
         }
         if (k_piece) {
             const bool past = tok0 + p.k >= end;
@@ -410,8 +460,30 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         }
     };
 
-    // S += phi(K)^T V of a chunk
-    auto update = [&](const Rows &rows, int t) {
+    // A look at the pieces of chunk t, in registers.
+    auto look = [&](int t) {
+        // (0 is inside too, but rare enough to be looked for separately; minimum and maximum keep a NaN, which no comparison lets pass)
+        auto least = [](f32x4 x) {
+            return __builtin_elementwise_minimum(__builtin_elementwise_minimum(__builtin_elementwise_minimum(fabsf(x[0]), fabsf(x[1])), fabsf(x[2])), fabsf(x[3]));
+        };
+        auto most = [](f32x4 x) {
+            return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x[0]), fabsf(x[1])), fabsf(x[2])), fabsf(x[3]));
+        };
+        if (!(least(raw[0]) >= 0x1p-60f && most(raw[0]) <= 0x1p40f)) {
+            Magnitudes m;
+            for_n<4>([&](auto j) { m.see(raw[0][j.value]); });
+            if (m.outside<-60, 40>()) atomicMin(&lds.wide_from, t);
+            if (m.most >= 0xff000000u) lds.bad[t & 1] = t + 1;
+        }
+        if ((k_piece || (!INC && q_piece)) && !(least(raw[1]) >= 0x1p-38f && most(raw[1]) <= 0x1p20f)) {
+            Magnitudes m;
+            for_n<4>([&](auto j) { m.see(raw[1][j.value]); });
+            if (m.outside<-38, 20>()) atomicMin(&lds.wide_from, t);
+        }
+    };
+
+    // S += phi(K)^T V of a chunk (uncut: on the fp32 matrix instructions)
+    auto update = [&](const Rows &rows, int t, auto uncut) {
         f32x16 d[2];
         float zc = 0.f;
         int ka, kb;
@@ -429,19 +501,27 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                 }
             });
             zc += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
-            const Parts op = split8([&](int i) { return f[i]; });
-            for_n<2>([&](auto c) {
-                mfma6(op, v_parts(rows, s.value, c.value), d[c.value]);
-                __builtin_amdgcn_sched_barrier(0);   // (bounds what is in flight at a time)
-            });
+            if constexpr (decltype(uncut)::value) {
+                for_n<2>([&](auto c) {
+                    const f32x8 x = read_v_f32(begin + C * t, s.value, c.value);
+                    mfma_f32([&](int i) { return f[i]; }, [&](int i) { return x[i]; }, d[c.value]);
+                });
+            } else {
+                const Parts op = split8([&](int i) { return f[i]; });
+                for_n<2>([&](auto c) {
+                    mfma6(op, v_parts(rows, s.value, c.value), d[c.value]);
+                    __builtin_amdgcn_sched_barrier(0);   // (bounds what is in flight at a time)
+                });
+            }
         });
         if (DECAY) {
             const float g_s = lds.power[tokens(t)];
             z *= g_s;
-            for_n<2>([&](auto c) { S[c.value] *= g_s; });
+            for_n<32>([&](auto r) { S[r.value / 16][r.value % 16] *= g_s; });
         }
         z += zc;
-        for_n<2>([&](auto c) { S[c.value] += d[c.value]; });
+        // (value by value: as vectors the compiler spills them, with a second copy of this in the kernel)
+        for_n<32>([&](auto r) { S[r.value / 16][r.value % 16] += d[r.value / 16][r.value % 16]; });
     };
 
     for (int i = tid; i < (INC ? 2 : 1) * C; i += NT) {
@@ -450,25 +530,39 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         for_n<16>([&](auto j) { rows.q[i % C][Q_ONES + j.value] = 1.f; });
         for_n<8>([&](auto j) { rows.q[i % C][Q_UNIT_LO + j.value] = j.value == 0 ? 1.f : 0.f; });
     }
-    if (tid == 0) lds.rows[0].bad = 0;
+    if (tid == 0) {
+        lds.bad[0] = lds.bad[1] = 0;
+        lds.wide_from = INT_MAX;
+    }
     if (DECAY && tid <= C) lds.power[tid] = powf(gm, (float)tid);
     __syncthreads();
     load_raw(begin, place());
+    look(0);
     stage(0, lds.rows[0], place());
     load_raw(begin + C, place());
     wg_sync();
+    // wide_from as read for a chunk: it has that one, and may have the next, which is told by its number
+    int wide_from = __builtin_amdgcn_readfirstlane(lds.wide_from);
+    if (DECAY) {
+        const float g_c = fabsf(lds.power[C]);
+        wide = wide || !(gm == 0.f || (g_c >= 0x1p-26f && g_c <= 0x1p26f));
+    }
+    auto is_wide = [&](int t) { return wide || t >= wide_from; };
     if (INC) {
         auto next_chunk = [&](int t) {
             const Place p = place();
+            look(t + 1);
             stage(t + 1, lds.rows[(t + 1) & 1], p);
             load_raw(begin + C * (t + 2), p);
             wg_sync();
+            wide_from = __builtin_amdgcn_readfirstlane(lds.wide_from);
         };
         if (tile) {
             role_guard();
             for (int t = 0; t < chunks; ++t) {
                 fresh_lane();
-                update(lds.rows[t & 1], t);
+                if (__builtin_expect(is_wide(t), 0)) update(lds.rows[t & 1], t, std::true_type{});
+                else update(lds.rows[t & 1], t, std::false_type{});
                 next_chunk(t);
             }
         } else {
@@ -502,10 +596,13 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         });
     };
     auto next_chunk = [&](int t) {
+        look(t + 1);
         wg_sync();
         const Place p = place();
+        const int from = lds.wide_from;
         output(begin + C * t, p);
         stage(t + 1, rows, p);
+        wide_from = __builtin_amdgcn_readfirstlane(from);
         load_raw(begin + C * (t + 2), p);
         wg_sync();
     };
@@ -513,7 +610,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     // (a loop for each role: what one keeps in registers is not kept by the others)
     if (tile) {
         role_guard();
-        for (int t = 0; t < chunks; ++t) {
+        auto chunk = [&](int t, auto uncut) {
             fresh_lane();
             f32x16 Y[2];
             for_n<2>([&](auto c) { Y[c.value] = zero16(); });
@@ -533,12 +630,18 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                     const f32x4 zv = *reinterpret_cast<const f32x4 *>(&lds.z[32 * w + 16 * s.value + 8 * jj.value + 4 * g]);
                     for_n<4>([&](auto i) { dsum = fmaf(f[4 * jj.value + i.value], zv[i.value], dsum); });
                 });
-                const Parts op = split8([&](int i) { return f[i]; });
-                __builtin_amdgcn_sched_barrier(0);
-                for_n<2>([&](auto c) {
-                    mfma6(split8([&](int i) { return S[c.value][8 * s.value + i]; }), op, Y[c.value]);
+                if constexpr (decltype(uncut)::value) {
+                    for_n<2>([&](auto c) {
+                        mfma_f32([&](int i) { return S[c.value][8 * s.value + i]; }, [&](int i) { return f[i]; }, Y[c.value]);
+                    });
+                } else {
+                    const Parts op = split8([&](int i) { return f[i]; });
                     __builtin_amdgcn_sched_barrier(0);
-                });
+                    for_n<2>([&](auto c) {
+                        mfma6(split8([&](int i) { return S[c.value][8 * s.value + i]; }), op, Y[c.value]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                }
                 __builtin_amdgcn_sched_barrier(0);   // (bounds what is in flight at a time)
             });
             if (DECAY) {   // the state before the chunk, at query n
@@ -551,7 +654,12 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             put_partial(Y);
             fresh_lane();
             __builtin_amdgcn_sched_barrier(0);
-            update(rows, t);
+            update(rows, t, uncut);
+        };
+        for (int t = 0; t < chunks; ++t) {
+            if (DECAY && gm != 1.f) wide = wide || state_outside();
+            if (__builtin_expect(is_wide(t), 0)) chunk(t, std::true_type{});
+            else chunk(t, std::false_type{});
             next_chunk(t);
         }
         if (writes_state) put_image();
@@ -560,16 +668,18 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         for (int t = 0; t < chunks; ++t) {
             const int tok0 = begin + C * t;
             fresh_lane();
+            const bool uncut = is_wide(t);
             f32x16 Y[2];
             for_n<2>([&](auto c) { Y[c.value] = zero16(); });
             // P^T: register r is key 8 (r / 4) + 4 g + r % 4, lane n the query
             f32x16 P;
             {
-                const Parts kop = split8([&](int i) { return rows.kt[8 * g + i][n]; });
+                auto key = [&](int i) { return rows.kt[8 * g + i][n]; };
                 const f32x4 q0 = *reinterpret_cast<const f32x4 *>(&rows.q[n][8 * g]), q1 = *reinterpret_cast<const f32x4 *>(&rows.q[n][8 * g + 4]);
-                const Parts qop = split8([&](int i) { return i < 4 ? q0[i & 3] : q1[i & 3]; });
+                auto query = [&](int i) { return i < 4 ? q0[i & 3] : q1[i & 3]; };
                 P = zero16();
-                mfma6(kop, qop, P);
+                if (__builtin_expect(uncut, 0)) mfma_f32(key, query, P);
+                else mfma6(split8(key), split8(query), P);
             }
             float dsum = 0.f;
             for_n<16>([&](auto r) {
@@ -584,10 +694,16 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
             if (g == 0) lds.den[w][n] = dsum;
             // A key that a query cannot see stands in the product as 0 V, which is not 0 where V is not finite: a chunk with such a value is
             // summed key by key, V from memory, without the hidden ones.
-            if (__builtin_expect(__builtin_amdgcn_readfirstlane(rows.bad) != t + 1, 1)) {
+            if (__builtin_expect(!uncut, 1)) {
                 for_n<2>([&](auto s) {
                     const Parts op = split8([&](int i) { return P[8 * s.value + i]; });
                     for_n<2>([&](auto c) { mfma6(v_parts(rows, s.value, c.value), op, Y[c.value]); });
+                });
+            } else if (__builtin_amdgcn_readfirstlane(lds.bad[t & 1]) != t + 1) {
+                for_n<4>([&](auto sc) {
+                    constexpr int s = sc.value / 2, c = sc.value % 2;
+                    const f32x8 x = read_v_f32(tok0, s, c);
+                    mfma_f32([&](int i) { return x[i]; }, [&](int i) { return P[8 * s + i]; }, Y[c]);
                 });
             } else {
                 float *pb = &lds.x[w][0][0][0][0];   // P^T [key][query] (this wave's own partial outputs come here afterwards)

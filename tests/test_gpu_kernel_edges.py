@@ -113,6 +113,55 @@ def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
         assert err < 1e-6, (what, err)
 
 
+# .. values that three bf16 parts do not hold: from 2^-103 on the third is no normal bf16 number, and a state shrinks to there by itself
+# under decay.  Every output and every state entry keeps the accuracy of fp32 sums, whatever stands in other columns, tokens and segments.
+@pytest.mark.parametrize("dv,N", [(64, 96), (128, 300)])
+@pytest.mark.parametrize("what", ["values", "keys", "column", "first half", "state", "decay", "small rate", "large"])
+def test_prefill_fp32_range(based, what, dv, N):
+    dp, H, D, axis = 16, 2, oracle.feature_dim(16), -1
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "dtype": "f32"})
+    q, k, v = (a.astype(np.float32) for a in synth.linattn_inputs(wl, units=H, N=N))
+    S0, z0, gamma = np.zeros((H, D, dv)), np.zeros((H, D)), np.ones(H, dtype=np.float32)
+    z0[:, 0] = 3.0
+    tiny = np.float32(2.0 ** -118)
+    if what == "values":
+        v *= tiny
+    elif what == "keys":
+        q, k = q * np.float32(2.0 ** 60), k * np.float32(2.0 ** -60)
+    elif what == "column":
+        v[:, :, 37] *= tiny
+        axis = -2
+    elif what == "first half":
+        v *= tiny
+        v[:, N // 2:] = 0.0
+    elif what == "state":
+        v[:] = 0.0
+        S0[:, :1 + dp] = synth.normal(80, (H, 1 + dp, dv), 1.0) * tiny
+    elif what == "decay":
+        gamma[:] = 0.7
+        v[:, 40:], k[:, 40:] = 0.0, 0.0
+        v[:, :40] *= np.float32(2.0 ** -34)
+    elif what == "small rate":
+        gamma[:] = 0.05
+    else:
+        v *= np.float32(2.0 ** 115)
+    want, Sw, zw = oracle.linattn_decay(q, k, v.astype(np.float64), gamma.astype(np.float64), S=S0, z=z0)
+    state = based.alloc_state(1, H, dp, dv)
+    based.state_import(state, up(S0, "f32", (1, H, D, dv)), up(z0, "f32", (1, H, D)), dp)
+    dev = [up(a, "f32", (1, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))]
+    if (gamma == 1.0).all():
+        y = based.prefill(*dev, state=state, has_init=True)
+    else:
+        y = based.prefill_decay(*dev, up(gamma, "f32"), state=state, has_init=True)
+    S = down(based.state_export(state, 1, H, dp, dv)[0]).reshape(Sw.shape)
+    for a, w, name in ((down(y).reshape(want.shape), want, "y"), (S, Sw, "S")):
+        scale = np.sqrt((w * w).sum(axis))
+        seen = scale > 2.0 ** -123   # (below, fp32 does not hold them to this either)
+        assert name == "S" or seen.mean() > 0.5
+        err = np.sqrt(((a - w) ** 2).sum(axis))
+        assert (err[seen] <= 1e-6 * scale[seen]).all(), (name, (err[seen] / scale[seen]).max())
+
+
 # .. and with decay: a rate of 1, a usual one and 0, a gate, the second part from the state of the first
 @pytest.mark.parametrize("dv,N1,N", [(64, 49, 98), (128, 64, 161), (64, 95, 224), (128, 130, 1321)])
 def test_prefill_fp32_decay_three_parts(based, dv, N1, N):
