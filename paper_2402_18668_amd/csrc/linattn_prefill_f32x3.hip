@@ -1,6 +1,7 @@
 // Causal Taylor linear attention, plain and with decay, chunked prefill of fp32 inputs at d' = 16 on the bf16 matrix instructions,
 // at fp32 precision: every operand is cut into three bf16 parts, x = h + m + l, and a product is the sum of the six
-// products of parts down to 2^-18 of it (h h, h m, m h, m m, h l, l h; what is left out is below 2^-25).
+// largest products of parts (h h, h m, m h, m m, h l, l h).  What is left out, m l + l m + l l, is 2^-24 of the product at most, one rounding, and
+// 2^-27.4 in the root mean square (emulated, uniform mantissas and N(0, 1 / 4): largest 2^-24.0, at mantissas 0x007fc0).
 //
 // Why: a fp32 matrix instruction occupies the vector ALU (measured with two waves on a SIMD, one of them all 16x16x4 fp32
 // products, the other all fused multiply-adds: 583 and 740 cycles alone, 1282 together), so the kernel on those
@@ -8,8 +9,8 @@
 // cycles per wave and 16 tokens.  Six bf16 products take 3/8 of the fp32 one's cycles and run beside the vector ALU
 // (667 and 740 cycles alone, 996 together).
 //
-// Parts.  h = the upper 16 bits of x (never rounds up to infinity), m = x - h rounded to bf16, l = x - h - m, which bf16 holds
-// exactly or to 2^-25 of x.  Each product's terms enter the accumulator smallest first; a chunk's part of the state is summed in an
+// Parts.  h = x rounded to bf16, m = x - h rounded to bf16, l = x - h - m: |m| <= 2^-8 and |l| <= 2^-17 for x in 1 .. 2, all exact, 24
+// bits together.  (Cutting h off instead of rounding it doubles m and l: 2^-22 left out.)  Each product's terms enter the accumulator smallest first; a chunk's part of the state is summed in an
 // accumulator of its own and added to the state once, so the state is rounded once per 32 tokens.
 //
 // State rows.  One row per unordered pair, 153 of them in five tiles of 32: tile T < 4 holds the pairs {a, (a + delta) mod 16} for
@@ -44,8 +45,8 @@
 // inputs, at 2.0 GHz); 16 units of 2048 111 -> 57, of 777 43 -> 28; 512 units of 2048 505 -> 381.  Bound by vector instructions, 590 per
 // tile, wave and chunk, 350 of them cutting features and state: vector ALU 52 %, matrix pipe 27 % of the cycles, LDS 33 %.  With
 // decay: 128 units of 2048, d_v 64, 230 -> 172; 16 of 300 50 -> 33; 2 of 49 24 -> 17.
-// Error against float64 (2-norm, 16 to 8192 tokens): y 0.6e-7 to 1.5e-7, S 0.5e-7 to 2.1e-7; there 0.8e-7 to 3.2e-7 and 0.8e-7 to 3.9e-7;
-// with decay 1.1e-7 to 1.6e-7 and 0.8e-7 to 2.5e-7, there 1.6e-7 to 2.8e-7 and 1.6e-7 to 3.5e-7.
+// Error against float64 (2-norm; 49 to 8192 tokens, values of scale 1e-3 to 30, both widths): y 0.7e-7 to 1.5e-7, S 0.5e-7 to 2.2e-7; there 0.9e-7 to
+// 2.4e-7 and 1.1e-7 to 4.1e-7.  With decay 0.7e-7 to 1.4e-7 and 0.6e-7 to 0.9e-7, there 0.9e-7 to 1.9e-7 and 1.0e-7 to 1.3e-7.
 #include "common.h"
 
 #include <limits.h>
@@ -130,10 +131,9 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
 struct Parts2 { uint32_t h, m, l; };   // of two values
 __device__ __forceinline__ Parts2 split2(float a, float b)
 {
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    const float ra = a - bf16hi(ua), rb = b - bf16hi(ub);
     Parts2 o;
-    o.h = __builtin_amdgcn_perm(ub, ua, 0x07060302);
+    o.h = pack2(a, b);
+    const float ra = a - bf16lo(o.h), rb = b - bf16hi(o.h);
     o.m = pack2(ra, rb);
     o.l = pack2(ra - bf16lo(o.m), rb - bf16hi(o.m));
     return o;

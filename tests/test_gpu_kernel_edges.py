@@ -113,6 +113,21 @@ def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
         assert err < 1e-6, (what, err)
 
 
+# .. single products: mantissas that make what three parts leave out of a product largest, the same in every operand.  That is 2^-24 of
+# the product at most; the roundings of the sums differ from entry to entry and fall out of the mean.
+@pytest.mark.parametrize("low", [0xff80, 0xfd80, 0x7fc0, 0x7f80, 0x8040])
+def test_prefill_fp32_products(based, low):
+    H, N, dp, dv = 1, 64, 16, 64
+    x = (np.uint32(0x3f800000) + (np.arange(64, dtype=np.uint32) % 37 << 16) + np.uint32(low)).view(np.float32)
+    k, v, q = np.tile(x[:dp], (H, N, 1)), np.tile(x, (H, N, 1)), np.zeros((H, N, dp), dtype=np.float32)
+    state = based.alloc_state(1, H, dp, dv)
+    based.prefill(*(up(a, "f32", (1, H, N, a.shape[-1])) for a in (q, k, v)), state=state)
+    S = down(based.state_export(state, 1, H, dp, dv)[0])[0, 0]
+    want = oracle.linattn_state(k, v)[0].reshape(S.shape)
+    error = (S / want - 1.0)[1:]
+    assert abs(error[:dp].mean()) <= 2.0 ** -24 and abs(error[dp:].mean()) <= 2.0 ** -24
+
+
 # .. values that three bf16 parts do not hold: from 2^-103 on the third is no normal bf16 number, and a state shrinks to there by itself
 # under decay.  Every output and every state entry keeps the accuracy of fp32 sums, whatever stands in other columns, tokens and segments.
 @pytest.mark.parametrize("dv,N", [(64, 96), (128, 300)])
