@@ -14,6 +14,7 @@
 #include <ATen/DimVector.h>
 #include <ATen/core/LegacyTypeDispatch.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 
@@ -132,16 +133,22 @@ float as_float(PyObject *o)
     return (float)v;
 }
 
-// A new tensor of like's type and device.  Straight from the device's allocation function (two trips through the dispatcher are a third of what
-// an allocation costs, 0.9 -> 0.6 us: the fused decode step's call 5.7 -> 5.1 us, the q / k / v projection's 6.0 -> 5.3), unless a mode or a transformation that looks at every operator is on.
-at::Tensor new_tensor(Arg like, at::IntArrayRef shape)
+// A new tensor of like's type and device, of the given shape (null: like's own).  Straight from the device's allocation function
+// (two trips through the dispatcher are a third of what an allocation costs, 0.9 us), unless somebody looks at operators or has a
+// say in them: a mode or transformation, the tracer, like's own class, a profiler's callbacks, the fill of uninitialised memory.
+// (Asking takes 0.02 us.)
+at::Tensor new_tensor(Arg like, const at::IntArrayRef *shape)
 {
     using c10::DispatchKey;
-    constexpr c10::DispatchKeySet modes({DispatchKey::Python, DispatchKey::PythonTLSSnapshot, DispatchKey::PythonDispatcher,
-                                         DispatchKey::FuncTorchDynamicLayerFrontMode, DispatchKey::FuncTorchDynamicLayerBackMode,
-                                         DispatchKey::Functionalize});
-    if (c10::impl::tls_local_dispatch_key_set().included_.has_any(modes)) return at::empty(shape, like->options());
-    return at::Tensor(at::detail::empty_cuda(shape, like->scalar_type(), like->device(), std::nullopt));
+    constexpr c10::DispatchKeySet classes({DispatchKey::Python, DispatchKey::PythonTLSSnapshot, DispatchKey::PythonDispatcher,
+                                           DispatchKey::FuncTorchDynamicLayerFrontMode, DispatchKey::FuncTorchDynamicLayerBackMode,
+                                           DispatchKey::Functionalize, DispatchKey::FuncTorchBatched, DispatchKey::Tracer});
+    const at::Context &context = at::globalContext();
+    if ((c10::impl::tls_local_dispatch_key_set().included_ | like->key_set()).has_any(classes) ||
+        at::getStepCallbacksUnlessEmpty(at::RecordScope::FUNCTION).has_value() ||
+        (context.deterministicAlgorithms() && context.deterministicFillUninitializedMemory()))
+        return shape ? at::empty(*shape, like->options()) : at::empty_like(*like);
+    return at::Tensor(at::detail::empty_cuda(shape ? *shape : like->sizes(), like->scalar_type(), like->device(), std::nullopt));
 }
 
 // A result: the tensor the caller gave (of the same shape and type where `msg` says what to answer otherwise, else any
@@ -165,7 +172,8 @@ struct Out {
     void make()
     {
         if (given) return;
-        made = new_tensor(like, shape.empty() ? like->sizes() : at::IntArrayRef(shape));
+        const at::IntArrayRef own(shape);
+        made = new_tensor(like, shape.empty() ? nullptr : &own);
         data = made.data_ptr();
     }
     PyObject *take()
@@ -386,7 +394,8 @@ PyObject *linear(PyObject *const *a)
     const int code = code_of(x);
     at::Tensor made;
     call("based_linear", [&] {
-        if (!y_given) made = new_tensor(x, shape);
+        const at::IntArrayRef sizes(shape);
+        if (!y_given) made = new_tensor(x, &sizes);
         return fn.based_linear(ptr(x), ptr(W), y_given ? ptr(y_given) : made.data_ptr(), (int)M, (int)K, (int)N, code, stream());
     });
     if (y_given) { Py_INCREF(a[2]); return a[2]; }

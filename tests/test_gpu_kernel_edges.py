@@ -543,3 +543,41 @@ def test_outputs_under_a_dispatch_mode(based):
         got = based.prefill(q, k, v)
     assert any("empty" in op for op in seen.ops)
     assert torch.equal(got, want)
+
+
+# .. nor where the input's own class, a profiler or the fill of uninitialised memory has to see it (the last with a stand-in for the kernel)
+def test_outputs_seen_without_a_mode(based, tmp_path):
+    import ctypes
+    import subprocess
+    import torch
+    q, k, v = (up(synth.round_to(synth.normal(91 + i, (1, 2, 20, d), 0.5), "bf16"), "bf16") for i, d in enumerate((16, 16, 64)))
+    x, W = (up(synth.round_to(synth.normal(95 + i, s, 0.5), "bf16"), "bf16") for i, s in enumerate(((3, 64), (128, 64))))
+    want, want_linear, ops = based.prefill(q, k, v), based.linear(x, W), []
+
+    class Logged(torch.Tensor):
+        @classmethod
+        def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+            ops.append(str(func))
+            return torch.empty_like(v)
+
+    got = based.prefill(q, k, torch.Tensor._make_subclass(Logged, v))
+    assert any("empty_like" in op for op in ops) and torch.equal(got, want)
+
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as profile:
+        got, got_linear = based.prefill(q, k, v), based.linear(x, W)
+    assert {"aten::empty_like", "aten::empty"} <= {e.key for e in profile.key_averages()}
+    assert torch.equal(got, want) and torch.equal(got_linear, want_linear)
+
+    src, so = tmp_path / "none.c", tmp_path / "none.so"
+    src.write_text("int none(void) { return 0; }\n")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)])
+    none = ctypes.cast(ctypes.CDLL(str(so)).none, ctypes.c_void_p).value
+    addresses = {n: ctypes.cast(getattr(based.lib, n), ctypes.c_void_p).value for n in based.EXPORTS}
+    based._bind.init({**addresses, "based_linear": none}, based._raise)
+    torch.use_deterministic_algorithms(True)
+    try:
+        filled = based.linear(x, W)
+    finally:
+        torch.use_deterministic_algorithms(False)
+        based._bind.init(addresses, based._raise)
+    assert filled.isnan().all()
