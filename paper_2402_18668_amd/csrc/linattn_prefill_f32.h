@@ -37,8 +37,8 @@
 // the unit, one in Q its own token.  What they make of the results they reach (Inf or NaN) is not specified: the zero rows of
 // the diagonal tiles turn an infinite sum into NaN.
 //
-// Measured (B 8, H 16, N 2048, d' 16, d_v 64, fp32): 1230 us on vector instructions (273 unpacked rows, two fused
-// multiply-adds per row and token) -> 193.  The fp32 matrix instructions occupy the vector ALU: per wave and chunk 2816 cycles of them
+// Measured (B 8, H 16, N 2048, d' 16, d_v 64, fp32, a call that linattn_prefill_f32x3.hip has now): 1230 us on vector instructions (273
+// unpacked rows, two fused multiply-adds per row and token) -> 193.  The fp32 matrix instructions occupy the vector ALU: per wave and chunk 2816 cycles of them
 // and 1640 of vector instructions add up to 4456 of 5555.
 #pragma once
 #include "common.h"
@@ -122,6 +122,9 @@ struct DecayArg {
     const void *gate;     // [B][N][H] in the dtype of y, device; null: none
     int H;
 };
+
+// fp32 calls come here at d' = 16 up to 48 tokens only: one segment.
+template <int DP, typename T> constexpr bool HAS_SEGMENTS = DP != 16 || !std::is_same<T, float>::value;
 
 // The launch covers `slices` slices of 64 columns from first_slice on.
 // has_init: bit 0 an initial state is given, bit 2 the outputs are the numerators alone.
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
             for_n<NT>([&](auto t) { S[t.value] = zero4(); });
             for_n<ZS>([&](auto i) { z[i.value] = 0.f; });
         }
-    } else if (G > 1) {
+    } else if (HAS_SEGMENTS<DP, T> && G > 1) {
         // the sum of the entries before the segment (up to 64 of them), some at a time with their loads in flight together
         constexpr int EB = NT <= 3 ? 8 : NT <= 10 ? 4 : 1;
         int e = init ? 0 : 1;
@@ -511,9 +514,10 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
 }
 
 // Segments: one round of what the chip holds, segments of at least 64 tokens (below that the increment launch and the sum
-// over the entries cost what the shorter chain gives), at most 64.  (128 units of 2048 tokens at d' 16, d_v 64: 2 segments
-// 273 us, 4 205, 6 = a full round 190, 8 227.  16 units: 777 tokens at d' 16 6 segments 52, 12 46, 24 60; at d' 32
-// 6 segments 137, 12 109; d' 8, 500 tokens 1 segment 51, 4 23, 8 17, 16 18; 14926 tokens 16 segments 145, 32 103, 64 99.)
+// over the entries cost what the shorter chain gives), at most 64.  (d' 16, d_v 64, bf16 with decay: 128 units of 2048 tokens 2
+// segments 315 us, 4 237, 6 = a full round 226, 8 275; 16 units: 300 tokens 1 segment 66, 2 61, 4 41; 777 tokens 6 66, 12 59, 24 76.
+// fp32, 16 units: 777 tokens at d' 32 6 segments 137, 12 109; d' 8, 500 tokens 1 segment 51, 4 23, 8 17, 16 18; 14926 tokens 16
+// segments 145, 32 103, 64 99.  The scratch of fp32 calls at d' 16 is sized by this rule too.)
 inline int segments(int U, int N, int dp, int dv)
 {
     const long groups = (long)U * (dv / COLS);
@@ -529,7 +533,7 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
                   int N, DecayArg dec, hipStream_t s)
 {
     constexpr int SL = DV / COLS;
-    int G = segments(U, N, DP, DV);
+    int G = HAS_SEGMENTS<DP, T> ? segments(U, N, DP, DV) : 1;
     const int len = segment_len(N, G);
     while (G > 1 && (G - 1) * len >= N) --G;   // rounding the length up can empty trailing segments
     if ((long long)U * SL * G >= (1ll << 31)) return hipErrorInvalidValue;
@@ -543,7 +547,7 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     };
     hipError_t e = hipSuccess;
     if (G > 1) {
-        e = go(std::true_type{}, 0, SL);
+        if constexpr (HAS_SEGMENTS<DP, T>) e = go(std::true_type{}, 0, SL);
     } else if ((has_init & 1) && SL > 1) {
         // every slice reads the caller's K-state and the first one overwrites it: the others go before it
         e = go(std::false_type{}, 1, SL - 1);
