@@ -88,8 +88,8 @@ def test_prefill_fp32_arithmetic(based, dtype, dp, dv, N1, N):
 
 
 # fp32 d' = 16 in three bf16 parts: its shortest call, chunks of 32 tokens with remainders, one and several segments, both widths, more
-# workgroups than the chip holds; values far from 1.  Sums of a few thousand terms in fp32 are off by 1e-7 (2-norm), two parts
-# instead of three by 1e-5.  The state's antisymmetric part, which no output sees, stays as it was.
+# workgroups than the chip holds; values far from 1.  Sums of a few thousand terms in fp32 are off by 0.5e-7 to 2.2e-7 (2-norm; one rounding
+# of every entry is 0.3e-7): 3e-7 tells products one bit worse, two parts instead of three are off by 1e-5.  The state's antisymmetric part, which no output sees, stays as it was.
 @pytest.mark.parametrize("H,dv,N1,N,exp", [(3, 64, 49, 98, 0), (2, 128, 64, 161, 90), (3, 64, 95, 224, -90), (1, 128, 130, 1321, 0), (2, 64, 257, 2400, 0),
                                            (300, 128, 50, 107, 0)])
 def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
@@ -110,7 +110,7 @@ def test_prefill_fp32_three_parts(based, H, dv, N1, N, exp):
                           (down(z), zw, "z")):
         want = np.asarray(want, dtype=np.float64)
         err = np.linalg.norm(a.reshape(want.shape) - want) / np.linalg.norm(want)
-        assert err < 1e-6, (what, err)
+        assert err < 3e-7, (what, err)
 
 
 # .. single products: mantissas that make what three parts leave out of a product largest, the same in every operand.  That is 2^-24 of
@@ -193,7 +193,7 @@ def test_prefill_fp32_decay_three_parts(based, dv, N1, N):
     for a, w, what in zip((np.concatenate(got, 1), down(S), down(z)), want, "ySz"):
         w = np.asarray(w, dtype=np.float64)
         err = np.linalg.norm(a.reshape(w.shape) - w) / np.linalg.norm(w)
-        assert err < 1e-6, (what, err)
+        assert err < 3e-7, (what, err)
 
 
 # decay at the same edges: the last chunk holds fewer than 16 tokens, increments of several segments, gate
@@ -319,7 +319,8 @@ def test_window_rotary_largest_ring(based, U, N):
 
 # decay from a state that is not symmetric in the feature pairs: both halves of it decay (gamma^N at the end of the call), in
 # one segment and in several, also at a rate of zero
-@pytest.mark.parametrize("dtype,dp,dv,N", [("f32", 8, 64, 5), ("f32", 16, 128, 40), ("bf16", 24, 64, 33), ("f32", 32, 64, 300)])
+@pytest.mark.parametrize("dtype,dp,dv,N", [("f32", 8, 64, 5), ("f32", 16, 128, 40), ("f32", 16, 64, 60), ("f32", 16, 128, 100), ("f32", 16, 128, 300),
+                                           ("bf16", 24, 64, 33), ("f32", 32, 64, 300)])
 def test_prefill_decay_from_asymmetric_state(based, dtype, dp, dv, N):
     import torch
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_feat": dp, "d_v": dv, "dtype": dtype})
@@ -340,20 +341,24 @@ def test_prefill_decay_from_asymmetric_state(based, dtype, dp, dv, N):
     check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
 
 
-# a state that holds an infinity keeps it (the two rows of a pair are equal: there is no difference to carry over)
-def test_prefill_fp32_infinite_state(based):
-    B, H, N, dp, dv = 1, 1, 20, 16, 64
+# a state that holds an infinity keeps it (the two rows of a pair are equal: there is no difference to carry over), in the kernels of short and
+# of longer calls, in one segment and in several
+@pytest.mark.parametrize("dv,N", [(64, 20), (64, 60), (128, 300)])
+def test_prefill_fp32_infinite_state(based, dv, N):
+    B, H, dp = 1, 1, 16
     D = oracle.feature_dim(dp)
-    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "dtype": "f32"})
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "dtype": "f32"})
     q, k, v = synth.linattn_inputs(wl, units=1, N=N)
     S0, z0 = np.zeros((1, 1, D, dv)), np.zeros((1, 1, D))
     S0[0, 0, 1 + dp + 2 * dp + 5, 9] = S0[0, 0, 1 + dp + 5 * dp + 2, 9] = np.inf
-    S0[0, 0, 1 + dp + 3 * dp + 3, 11] = -np.inf
+    S0[0, 0, 1 + dp + 3 * dp + 3, dv - 7] = -np.inf
     state = based.alloc_state(B, H, dp, dv)
     based.state_import(state, up(S0, "f32"), up(z0, "f32"), dp)
-    based.prefill(*(up(a, "f32", (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state, has_init=True)
+    y = based.prefill(*(up(a, "f32", (B, H, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state, has_init=True)
     S = down(based.state_export(state, B, H, dp, dv)[0])
     assert np.array_equal(np.where(np.isfinite(S), 0.0, S), S0)
+    others = np.setdiff1d(np.arange(dv), (9, dv - 7))
+    check_close(rows(down(y).reshape(N, dv)[:, others]), rows(oracle.linattn_quadratic(q, k, v)[0][:, others]), TOL["f32"], "y")
 
 
 # a value that is not finite reaches nothing that does not see its token: earlier tokens and other columns (fp32 arithmetic; 16
