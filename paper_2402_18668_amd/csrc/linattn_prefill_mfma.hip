@@ -41,8 +41,8 @@
 // counter in LDS that the producer waves bump when their rows are staged and that only the waves
 // building from those rows poll.
 //
-// Measured (d_v 64, four producers and rows staged once, six, rows staged twice): 128 units of 2048 tokens 45.2, 41.7, 39.4 us; 200 units 62.4,
-// 55.9, 56.3; 16 units of 777 tokens from a state 19.3, 18.1, 18.2.  At d_v 128 neither helps: eight producers (12 waves of 168
+// Measured (d_v 64, four producers and rows staged once, and as it is): 128 units of 2048 tokens 45.3 and 39.3 us (41.7 with six producers
+// alone); 200 units 60.5 and 52.0; 16 units of 777 tokens from a state 19.0 and 16.7 (here also the wait under the builds).  At d_v 128 neither helps: eight producers (12 waves of 168
 // registers) 87.7, rows staged twice 87.2 against 86.5 us for 256 units; what a CU takes for a chunk, 2.2 us with up to 160 of them at
 // work and 2.7 with all, is the consumers' 46 matrix instructions at one operand read from LDS each, the stores and the clock.
 //
@@ -1048,20 +1048,24 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
 namespace {
 
 // Segments per sequence.  At most what fills the chip once (one workgroup per CU fits): beyond that more segments only add
-// increment work and workspace traffic (d_v 64, 2048 tokens: 128 units 1 segment 59 us, 2 45, 3 59; 86 units 59, 44, 44; 129 units 59,
-// 66, 59; 200 units 60, 80, 80).  With few units the chip is not the limit: G segments make a chain of chunks / G increment chunks,
+// increment work and workspace traffic (d_v 64, 2048 tokens: 128 units 1 segment 50.5 us, 2 39.6, 3 51.9; 86 units 49.8, 38.2, 39.1; 129 units
+// 50.6, 55.8, 51.9; 200 units 50.9, 70.0, 70.9).  With few units the chip is not the limit: G segments make a chain of chunks / G increment chunks,
 // G entries to sum up and chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment
-// 28 us, 3 22, 5 19, 8 21; 24 chunks 2 39, 4 27, 8 23, 12 27; 64 chunks 8 35, 12 32, 16 36); below 6 chunks a second segment does not
-// pay for its hand-over (4 chunks: 1 segment 14.0 us, 3 15.1).  Two exceptions:
+// 22.6 us, 3 16.6, 5 14.8, 8 16.9; 24 chunks 2 28.7, 4 21.2, 6 18.1, 8 18.5, 12 24.3; 64 chunks 8 28.1, 12 27.6, 16 31.7); below 6 chunks
+// a second segment does not pay for its hand-over (4 chunks: 1 segment 10.0 us, 2 10.6, 3 11.1; 5 chunks 11.6, 11.9, 11.8; 6 chunks 12.9, 12.5, 11.8).
+// Two exceptions:
 // - Below 10 chunks the hand-over is a large part of the call, the more so the wider the heads and the more units share the memory:
 //   one segment with more than 40 units (d_v 128, up to 7 chunks), 51 (d_v 64, 6 chunks) or 85 (d_v 128, and d_v 64 up to 7 chunks), and no
-//   more than three up to 8 chunks or with more than 42 units at d_v 128.  (us without and from a state; d_v 128, 384 tokens: 60
-//   units 1 segment 18.4, 20.6, 3 22.6, 23.3; 128 units 1 19.8, 22.9, 2 21.9, 26.1; 512 tokens, 60 units 1 21.9, 24.2, 3 22.6, 24.2, 4 25.5,
-//   25.8; 72 units 1 22.3, 24.7, 3 20.8, 24.7; d_v 64, 384 tokens, 60 units 1 15.7, 17.6, 3 16.6, 19.8; 512 tokens, 48 units 3 15.7, 18.6, 4 16.5,
-//   18.3.)
+//   more than three up to 8 chunks or with more than 42 units at d_v 128.  (us without and from a state; d_v 128, 384 tokens: 40
+//   units 1 segment 17.6, 19.6, 3 16.7, 19.7; 41 units 1 17.5, 19.7, 3 17.6, 21.7; 60 units 1 18.0, 20.2, 3 20.9, 23.2; 128 units 1 19.1, 22.3, 2 22.0,
+//   26.0; 448 tokens, 60 units 1 19.8, 22.0, 2 18.9, 23.6; 512 tokens, 60 units 1 21.6, 23.9, 3 21.8, 23.8, 4 26.4, 25.3; 72 units 1 21.8, 24.1, 3 21.9,
+//   24.9; d_v 64, 384 tokens, 52 units 1 13.5, 15.2, 3 14.7, 17.3; 448 tokens, 86 units 1 15.5, 17.0, 2 16.8, 21.5; 512 tokens, 48 units 3 13.7,
+//   16.2, 4 15.5, 16.0.)  The lines are from before one segment had a kernel of its own, which moved them a little: just below, one segment
+//   would gain (85 units of 512 tokens, d_v 128, 3 as chosen 23.6, 26.4, 1 22.0, 24.6; d_v 64, 86 units of 512 2 17.4, 21.5, 1 17.0, 18.5; 51 of 384 3 14.1,
+//   17.5, 1 13.4, 15.1).
 // - Long sequences, 86 .. 102 units: 5 U workgroups, three segments, are two rounds of the chip like the two segments' 3 U (d_v
-//   64, 100 units: 4096 tokens 2 segments 83.7 us, 3 81.0; 8192 163, 151; 110 units 8192 163, 188; d_v 128, 86 units: 4096 95.9, 93.7; 16384
-//   371, 345).
+//   64, 100 units: 4096 tokens 2 segments 71.7 us, 3 70.6; 8192 138, 130; 110 units 8192 139, 160; d_v 128, 86 units: 4096 94.6, 92.5; 16384
+//   364, 342).
 int pick_segments(int U, int N, int dv)
 {
     const int chunks = (N + C - 1) / C;
@@ -1089,8 +1093,8 @@ int make_segments(int N, int G, SegTable &t)
     if (G > T) G = T;
     if (G == 2) {
         // Segment 0's main pass runs beside its increment, and only the other one waits: at three quarters of the tokens
-        // both end together (128 units of 2048 tokens, d_v 64: halves 52 us, 0.66 48.6, 0.75 46.6, 0.8 46.4; d_v 128: 65.5,
-        // 62.5, 61.6).
+        // both end together (128 units of 2048 tokens, d_v 64: halves 43.7 us, 0.66 40.6, 0.75 39.3, 0.8 40.3; d_v 128: 61.5,
+        // 58.3, 57.4, 57.2).
         const int first = T < 4 ? 1 : 3 * T / 4;
         t.begin[0] = 0;
         t.begin[1] = first * C;

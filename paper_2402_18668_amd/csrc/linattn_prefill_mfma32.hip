@@ -35,8 +35,8 @@
 // LDS: the same time, more LDS.  Four waves with 512 registers and half the exchange: the same, a lone wave issues a
 // vector instruction every 4 cycles instead of 2.  Reading operands' rows a phase ahead: no gain.)
 // Measured (d_v 64; before: four waves per 32 columns, 500 vector instructions per wave and 32 tokens, state buffer accessed
-// element by element): 32 units of 16384 tokens 266 -> 210 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 27 us, from
-// a state 83 -> 40 us.
+// element by element): 32 units of 16384 tokens 266 -> 208 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 30 us, from
+// a state 83 -> 38 us.
 #include "common.h"
 
 #include <cmath>
@@ -758,11 +758,12 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 }
 
 // Segments: at most one round of the chip (one workgroup per CU).  With few units the chain of an increment, up to G - 1 entries
-// to sum and the main pass is shortest near sqrt(1.5 chunks) segments (16 units, N 2048: 4 segments 61 us, 8 47, 10 45, 16 50; N 777:
-// 1 59, 3 38, 6 32, 12 36); from 8 chunks on it is shorter than one segment.  The more groups, the fewer segments there is room for and the
-// more entries move at a time, so the longer a sequence has to be (1 segment against what there is room for, us: 48 groups N 256 25.8,
-// 24.5; 64 groups N 256 26.2, 26.2, N 320 30.4, 29.0; 80 groups N 256 26.5, 27.3, N 320 30.6, 30.0; 86 groups N 448 38.9, 37.9; 100 groups
-// N 384 34.9, 36.3, N 512 43.2, 41.8; 128 groups N 448 39.7, 40.5, N 512 43.7, 43.5).
+// to sum and the main pass is shortest near sqrt(1.5 chunks) segments (16 units, N 2048: 4 segments 57.1 us, 8 41.1, 10 38.8, 16 43.9; N 777:
+// 1 59.6, 3 36.2, 6 28.6, 12 34.0; N 256 1 24.7, 3 19.7).  The more groups, the fewer segments there is room for and the more entries move at a
+// time, so the longer a sequence has to be, the more so from a state (1 segment and what there is room for, us: 48 groups N 256 26.1, 22.7; 64
+// groups N 256 26.3, 26.4, from a state 32.0, 33.2, N 320 30.4, 26.9; 80 groups N 256 26.6, 25.2, from a state 32.8, 35.0, N 320 30.6, 27.9; 86
+// groups N 448 39.0, 35.7; 100 groups N 384 35.1, 34.1, from a state 41.8, 44.4, N 512 43.2, 39.3; 128 groups N 448 39.7, 38.3, from a state 47.3,
+// 49.5, N 512 43.8, 41.0).
 static int pick_segments(int U, int N, int dv)
 {
     const int groups = U * (dv / COLS), chunks = (N + C - 1) / C, room = 256 / groups;
@@ -776,9 +777,9 @@ static int pick_segments(int U, int N, int dv)
 
 // Groups whose segments share an XCD each: all of them (the grid has room for a multiple of 8) where the XCD with the most has a CU for
 // every segment, else as many as make up a multiple of 8, the others' segments going to all XCDs.  (Segment after segment of a group
-// on different XCDs, the entries read from memory: 60 groups of 1024 tokens in 4 segments 56 us instead of 45, of 448 45 instead of 32.
-// 41 groups in 6 segments, where one XCD would hold 36: all groups on their XCD 79 us at 2048 tokens and 228 at 8192, as here 54 and 143,
-// none 61 and 149.)
+// on different XCDs, the entries read from memory: 60 groups of 1024 tokens in 4 segments 45 us instead of 41, of 448 34 instead of 28.
+// 41 groups in 6 segments, where one XCD would hold 36: all groups on their XCD 77 us at 2048 tokens and 225 at 8192, as here 50 and 136,
+// none 59 and 144.)
 static int local_groups(int groups, int G)
 {
     const int most = (groups + 7) / 8;

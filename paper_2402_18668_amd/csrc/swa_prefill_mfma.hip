@@ -5,8 +5,8 @@
 // in steps of 128 (256) queries; each wave owns one tile of 32 queries of the step and walks the
 // w / 32 + 1 key tiles that overlap its window.
 //
-// Staging.  The w + 128 key and value rows a step can see sit in an LDS ring.  Each step
-// overwrites the 128 oldest rows with its 128 new ones, which were fetched into registers during
+// Staging.  The key and value rows a step can see, w and its own, sit in an LDS ring.  Each step
+// overwrites the oldest rows with its new ones, which were fetched into registers during
 // the previous step, so every row is read from global memory once per segment, with fully
 // coalesced row-major loads, and its latency hides under the arithmetic.  (Fetching K per query
 // tile instead multiplies the L2 traffic by w / 32 + 1.)  The Q tile of the next step is
@@ -153,7 +153,7 @@ __device__ __forceinline__ void swa_prefill_mfma_body(const uint16_t *__restrict
     uint16_t *Vs = reinterpret_cast<uint16_t *>(lds_raw);      // [NK][V_LD]: ring of staged V rows
     uint16_t *Ks = Vs + (size_t)NK * V_LD;                     // [NK][K_LD]: ring of staged K rows
     constexpr int Y_LD = Cfg::Y_LD;
-    // [4 waves][32][Y_LD]: output tiles on their way out.  Rotary: a wave's region is WREG elements and
+    // [NWV waves][32][Y_LD]: output tiles on their way out.  Rotary: a wave's region is WREG elements and
     // starts the step as its 32 rotated query rows [32][Q_LD].
     uint16_t *Ysh = Ks + (size_t)NK * K_LD;
     constexpr int Q_LD = Cfg::Q_LD;
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(NWV, SwaCfg<DH, WIN, NWV>:
 
 // d_h 64, window 128: the ring of four waves (96 KB) leaves a CU one workgroup, one wave to a SIMD.  Eight waves and steps of 256 queries (153
 // KB) are two, where the chip is full of workgroups either way.  (us with four and with eight, without and with rotary: 32 units of 16384 tokens
-// 61.1, 57.7 and 68.7, 64.8; 64 of 2048 17.7, 15.5 and 21.8, 19.2; 64 of 777 11.6, 10.0 and 14.4, 12.0; 512 of 200 22.3, 19.1; but 16 of
+// 59.8, 56.9 and 68.0, 62.5; 64 of 2048 17.7, 15.5 and 21.8, 18.8; 64 of 777 11.6, 10.0 and 14.8, 12.2; 512 of 200 22.3, 19.1; but 16 of
 // 2048 8.6, 8.4 and 10.2, 10.3; 16 of 777 6.8, 7.3; 512 of 100 15.4, 15.4 and 17.0, 17.5.)
 static bool eight_waves(int U, int N) { return N > 128 && (long)U * ((N + 127) / 128) > 256; }
 
