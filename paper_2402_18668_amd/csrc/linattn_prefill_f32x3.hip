@@ -10,8 +10,9 @@
 // (667 and 740 cycles alone, 996 together).
 //
 // Parts.  h = x rounded to bf16, m = x - h rounded to bf16, l = x - h - m: |m| <= 2^-8 and |l| <= 2^-17 for x in 1 .. 2, all exact, 24
-// bits together.  (Cutting h off instead of rounding it doubles m and l: 2^-22 left out.)  Each product's terms enter the accumulator smallest first; a chunk's part of the state is summed in an
-// accumulator of its own and added to the state once, so the state is rounded once per 32 tokens.
+// bits together.  (Cutting h off instead of rounding it doubles m and l: 2^-22 left out; 1 % faster.)  Each product's terms enter the accumulator
+// smallest first; a chunk's part of the state is summed in an accumulator of its own and added to the state once, so the state is rounded
+// once per 32 tokens.  (Values split into narrower parts for exact products: Dekker 1971; for matrix products: Ozaki et al. 2012.)
 //
 // State rows.  One row per unordered pair, 153 of them in five tiles of 32: tile T < 4 holds the pairs {a, (a + delta) mod 16} for
 // delta = 2 T (rows 0 .. 15, a = row) and 2 T + 1; tile 4 the 16 linear rows, the constant row (16), zeros (17 .. 23), and delta = 8
@@ -38,13 +39,13 @@
 // value of the rows and of every feature, and no sum passes 2^112.  An entry of the state may get below 2^-103 (a sum of products of small
 // values, or what cancellation leaves): what a query, 2^40 at most per row, then misses is 2^-34 of the smallest value of V at most, for 153 rows 2^-26.
 // With decay, where a state shrinks, it is looked at in every chunk, and a rate whose 32nd power is outside 2^-26 .. 2^26 (and
-// not 0) has no other instructions.  Of N(0, 1 / 4) values one in 2e11 of K and Q is outside.  Looking takes 1.5 % of the time, by the
-// threads that stage the rows (waves 6 and 7 alone, with loads of their own: 4 %).  128 units of 2048 tokens, d_v 64, all of them uncut: 253 us.
+// not 0) has no other instructions.  Of N(0, 1 / 4) values one in 2e11 of K and Q is outside.  All of this takes 3 % of the time, 1 % of it
+// the look, by the threads that stage the rows (waves 6 and 7 alone, with loads of their own: 4 %).  128 units of 2048 tokens, d_v 64, uncut: 253 us.
 //
-// Measured against linattn_prefill_f32.h (us): 128 units of 2048 tokens, d_v 64, 193 -> 141 (increments 48, main launch 126 in a trace with cold
-// inputs, at 2.0 GHz); 16 units of 2048 111 -> 57, of 777 43 -> 28; 512 units of 2048 505 -> 381.  Bound by vector instructions, 590 per
-// tile, wave and chunk, 350 of them cutting features and state: vector ALU 52 %, matrix pipe 27 % of the cycles, LDS 33 %.  With
-// decay: 128 units of 2048, d_v 64, 230 -> 172; 16 of 300 50 -> 33; 2 of 49 24 -> 17.
+// Measured against linattn_prefill_f32.h (us): 128 units of 2048 tokens, d_v 64, 193 -> 144 to 150 (increments 50, main launch 129 in a trace with cold
+// inputs); 16 units of 2048 111 -> 57, of 777 43 -> 28; 512 units of 2048 507 -> 403.  Bound by vector instructions, 600 per
+// tile, wave and chunk, 350 of them cutting features and state: vector ALU 50 %, matrix pipe 26 % of the cycles, LDS 30 %.  With
+// decay and gate: 128 units of 2048, d_v 64, 225 -> 171; 16 of 300 41 -> 31.
 // Error against float64 (2-norm; 49 to 8192 tokens, values of scale 1e-3 to 30, both widths): y 0.7e-7 to 1.5e-7, S 0.5e-7 to 2.2e-7; there 0.9e-7 to
 // 2.4e-7 and 1.1e-7 to 4.1e-7.  With decay 0.7e-7 to 1.4e-7 and 0.6e-7 to 0.9e-7, there 0.9e-7 to 1.9e-7 and 1.0e-7 to 1.3e-7.
 #include "common.h"
