@@ -4,7 +4,7 @@
 // A small call is bound by the host, not by the GPU: one token of the fused decode step is 3-6 us of kernel, and
 // marshalling its 25 arguments in Python (ctypes boxes, tensor attributes, the stream object) took 20 us.
 // Here a tensor's pointer, shape and dtype are field reads (the same checks as before: 23 -> 10 us for a fused step
-// and the advance of its positions on the GPU machine).
+// and the advance of its positions).
 // based.py keeps the public functions (names, defaults, documentation) and hands their arguments over
 // positionally; the entry points' addresses come from the library it has loaded, so that there is one library
 // in the process whichever build of it the user points the binding at.
