@@ -20,6 +20,7 @@ SOURCES = [
     "linattn_prefill_f32x3.hip",
     "linattn_prefill_mfma.hip",
     "linattn_prefill_mfma32.hip",
+    "linattn_prefill_mfma32_short.hip",
     "swa_prefill_f32.hip",
     "swa_prefill_mfma.hip",
     "swa_prefill_mfma16.hip",

@@ -1,42 +1,41 @@
 // Causal Taylor linear attention, chunked prefill on the gfx950 matrix cores (bf16 in, fp32
-// accumulate), d' = 32.
+// accumulate), d' = 32.  (Short calls: linattn_prefill_mfma32_short.hip.)
 //
-// Same method as the d' = 16 kernel (chunked form of Sec. 4: masked quadratic product inside a
-// chunk, running KV-state across chunks, features of Eq. 4 built in registers in MFMA operand layout, k-slots mapped onto
-// the rows a lane holds in its accumulators), laid out for the larger state:
+// Chunked form of Sec. 4 in blocks of 256 tokens: for a query, the keys of its block come through the masked quadratic
+// product 1 + A + A^2 / 2, the tokens before the block through the running state.
 //
-// Symmetric packing.  One state row per unordered pair {a, b}: row (a, delta) stands for the
-// pair {a, (a + delta) mod 32}, delta = 0 .. 15 for every a (16 tiles of exactly 32 rows, one
-// delta per tile) and delta = 16 for a < 16.  The k side builds x_a x_b / sqrt(2), the q side
-// sqrt(2) x_a x_b (delta != 0) or x_a^2 / sqrt(2) (delta = 0).  528 pair rows instead of 1024.  Two more tiles: E1 = the
-// 32 linear rows, E2 = [1, 0 x 15, the 16 rows of delta = 16].
+// Symmetric packing.  One state row per unordered pair of features.  Write a vector as two halves (x, y) of 16 and take indices mod 16.
+// Tiles of 32 rows: T = 0 .. 7: x_n x_(n + T), then y_n y_(n + T); T = 8 .. 15: x_n y_(n + T - 8), then y_n x_(n + d), d = 7, 8, 5, 6, 3, 4, 1, 2
+// (differences 0 .. 7 and 8 .. 15 of y's index over x's).  Two more: E1 = the linear rows, E2 = x_n x_(n + 8), then y_n y_(n + 8), of which n < 8
+// counts.  528 pair rows instead of 1024; the constant's row is kept apart.  Rows hold sum k_a k_b v, without the 1 / sqrt(2) of Eq. 4: the
+// readout weighs a pair of different features 1 and a square (tile 0) 1/2.
 //
-// Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment); wave w owns the tiles delta = 2 w and
-// 2 w + 1 for both column tiles of 32.  So every feature operand is built once per workgroup and used where it is built: nothing
-// of it passes through LDS, only the rows it is made of do.  The eight partial outputs of a chunk meet in LDS and each
-// wave finishes four tokens.  Waves 0 .. 3 also have E1 / E2 (one column tile of one of them each) and a 16 x 16 block
-// of the K-state, waves 4 .. 7 the intra-chunk block (one half of the keys, one column tile each).
+// Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment).  Wave w owns tiles 2 w, 2 w + 1 (both column tiles of
+// 32) and one more product, in accumulators throughout.  A block's phases:
+//   operand   every wave writes its tiles, rounded to bf16, to LDS in MFMA operand layout; the rows of K and V go to LDS
+//   readout   a wave has 32 queries and all state rows: phi(q) is built from 32 registers, no sum crosses waves
+//   intra     the same queries with the key tiles up to their own
+//   update    a wave adds the block to its tiles; phi(k) is the product of two rows of K^T, which lies in LDS in fp32.  Of a wave's two tiles
+//             the second one's factor is the first one's a lane further within 16 (a DPP operand of the multiplication), so that
+//             all waves run the same code and differ in an address
+// Two barriers a block; between them waves drift through intra, readout and update.
 //
-// Pipeline.  Chunks of 32 tokens, global -> registers (two chunks ahead) -> LDS (two generations).  Two barriers a chunk: rows
-// and partial outputs are there | the previous chunk's partial outputs have been read.
-//
-// Denominator.  The K-state is kept as moments: M[a][b] = sum_t k_a k_b (an MFMA of the K rows with
-// themselves), z1[a] = sum_t k_a (vector adds) and the token count.  Per query
-// phi(q).z = z0 + sum_a q_a (z1[a] + (M q)[a] / 2); the part from inside the chunk is the column
-// sum of the masked block P.
+// Denominator.  The K-state is kept as moments: M[a][b] = sum_t k_a k_b, z1[a] = sum_t k_a and the token count.  Per query
+// phi(q).z = z0 + sum_a q_a (z1[a] + (M q)[a] / 2); the part from inside the block is the column sum of the masked products.
 //
 // Long sequences / few units: G segments; a first launch computes each segment's state increment, segment 0's starting from
 // the caller's state, and the main launch starts segment g from the sum of the entries before it (read at full width: all
 // loads of an entry in flight together).
 //
-// What bounds it: per chunk and SIMD 44 matrix instructions (1400 cycles) and 600 vector instructions (half of them the products,
-// conversions and the state's rounding to bf16), which share the register ports, and 290 KB through LDS, a third of it the
-// partial outputs; 5000 cycles in all, because the eight waves do the same things at the same time.  (Operands built by one wave and shared through
-// LDS: the same time, more LDS.  Four waves with 512 registers and half the exchange: the same, a lone wave issues a
-// vector instruction every 4 cycles instead of 2.  Reading operands' rows a phase ahead: no gain.)
-// Measured (d_v 64; before: four waves per 32 columns, 500 vector instructions per wave and 32 tokens, state buffer accessed
-// element by element): 32 units of 16384 tokens 266 -> 208 us, 256 units of 2048 172 -> 147 us, 16 units of 777 tokens 50 -> 30 us, from
-// a state 83 -> 38 us.
+// What bounds it: per block and SIMD 358 matrix instructions (11,500 cycles) and some 3,300 vector instructions (at 4 cycles each, 13,500), of
+// which the hardware overlaps little with two waves to a SIMD: 24,500 cycles in all (phase clocks: operand 3,800, intra 3,500, readout 6,100,
+// outputs 1,900, update 8,300, waiting 800), LDS half busy.  What helped on the way (512 units of 2048 tokens, us): the split itself 312 -> 270 (the
+// kernel of short calls exchanges 64 KB of partial outputs and rounds the state for every 32 tokens); phi(k) without a branch or an address
+// in the slab loop, the matrix instructions at priority 1, 270 -> 249; waves 4 .. 7 ahead in intra and readout, 249 -> 240; half as many LDS writes
+// of K^T 240 -> 237.  Tried and not kept: phi(k) from eight code variants with the rotation in the instruction (269), three fp32 rows a slab
+// (LDS-bound, 256), two workgroups of four waves in the other kernel's split (300).
+// Measured (d_v 64, before and now): 32 units of 16384 tokens 208 -> 168 us, 512 units of 2048 312 -> 237, 128 of 2048 106 -> 85, 192 of 1024
+// 78.5 -> 50.6, 64 of 8192 199 -> 160, 16 of 2048 39.2 -> 37.4, of 256 19.5 -> 15.9.
 #include "common.h"
 
 #include <cmath>
@@ -52,51 +51,46 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int DP = 32;            // d'
-constexpr int C = 32;             // chunk length (tokens)
 constexpr int NW = 8;             // waves per workgroup
 constexpr int NT = NW * 64;
-constexpr int PF = 2;             // chunks whose rows are on their way; generations of the rows in LDS
+constexpr int QT = 32;            // queries to a wave
+constexpr int BLOCK = NW * QT;    // tokens of a block
 constexpr int COLS = 64;          // d_v columns per workgroup
-constexpr int TPW = 2;            // main tiles per wave (and column tile)
-constexpr int TILES = 18;         // 16 main tiles, E1, E2
-constexpr float kCK = 0.84089641525371454303f;   // 2^(-1/4): (c k_a)(c k_b) = k_a k_b / sqrt(2)
-constexpr float kCQ = 1.18920711500272106672f;   // 2^(+1/4): (c q_a)(c q_b) = sqrt(2) q_a q_b
-
-// LDS strides (elements).  (64 banks: the 16-byte reads of 16 consecutive rows fall into different ones.)
-constexpr int KTS_LD = C + 4;     // fp32 K^T rows
-constexpr int VR_LD = COLS + 16;  // bf16 V rows
-constexpr int QS_LD = DP + 4;     // fp32 Q rows
-constexpr int KR_LD = 64 + 8;     // bf16 extended K and Q rows (144-byte stride)
+constexpr int TILES = 18;
+constexpr int SLABS = 35;         // state operands of 16 rows: two to a tile, one of E2
+constexpr int KT_LD = BLOCK + 4;  // fp32 rows of K^T (64 banks: the 16-byte reads of 16 consecutive rows fall into different ones)
 constexpr int IMG_LD = 40;        // fp32 rows of the state image (the halves of a wave access different banks)
 
-// Workspace entry (one segment's state in accumulator layout): 40 slots of 16 registers x 64 lanes: column tile c:
-// slots 20 c + 2 w + tt = main tile 2 w + tt, 20 c + 16 = E1, 20 c + 17 = E2; 18 = M; 19 = [z1, z0] in the first two
-// registers.  Within a slot: [reg / 4][lane][reg % 4].
-constexpr int WS_SLOTS = 40;
+// Workspace entry (one segment's state in accumulator layout): 40 slots of 16 registers x 64 lanes, wave w's from 5 w on: tile 2 w + tt of
+// column tile c ^ (w % 2) in slot 2 c + tt, X (below) in slot 4.  Within a slot: [reg / 4][lane][reg % 4].
+constexpr int WS_SLOTS = 5 * NW;
 constexpr size_t kWsEntryFloats = (size_t)WS_SLOTS * 16 * 64;
 
-struct Rows {   // a chunk's rows
-    float kts[DP][KTS_LD];     // c_k * K^T
-    uint16_t krow[C][KR_LD];   // extended K rows: [k_0..k_31 as given, 1, 0 x 15, k_a k_(a+16) / sqrt(2) for a < 16]
-    uint16_t vrow[C][VR_LD];   // V rows of the slice, bf16 as given
-    float qs[C][QS_LD];        // c_q * Q
-    uint16_t qrow[C][KR_LD];   // extended Q rows: [q as given, 1, 0 x 15, sqrt(2) q_a q_(a+16)]
+struct Kv {   // a block's rows
+    float kt[DP][KT_LD];         // K^T
+    uint16_t v[BLOCK][COLS];     // 16-byte piece c of row t at c ^ 4 ((t / 2) % 2): the operand reads spread over the banks
 };
 struct Lds {
-    Rows rows[PF];                     // generation: chunk mod 2
-    float xbuf[NW][2 * 4][64][4];      // partial Y^T: [sender][4 column tile + reg / 4][place of the lane][reg % 4]
-    float den[2][C][8];                // denominators: the waves' parts from before the chunk (4) and from inside it (2)
-    float z1s[4][16];                  // a wave's z1, for its own broadcast reads
+    Kv kv;
+    uint16_t k[BLOCK][DP];         // 16-byte piece c of row t at c ^ (t / 4) % 4
+    uint16_t s[SLABS][2][64][8];   // state operands: [slab 2 T + half][column tile][lane][k-slot]
+    uint16_t m[2][64][8];          // the same of M
+    float cst[COLS], z1[DP];       // the constant's row; K-state
 };
 static_assert(sizeof(Lds) <= 160 * 1024, "one workgroup per CU");
 static_assert(sizeof(Lds) >= sizeof(float) * 32 * TILES * IMG_LD, "the state image of one column tile fits the LDS");
+struct LdsInc {
+    union {
+        Kv kv[2];   // block mod 2
+        float image[32 * TILES * IMG_LD];
+    };
+};
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
 {
@@ -108,14 +102,6 @@ __device__ __forceinline__ bf16x8 pack8(const float *v)
     f32x8 f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = v[e];
-    return __builtin_convertvector(f, bf16x8);
-}
-
-__device__ __forceinline__ bf16x8 pack8_acc(const f32x16 &acc, int s)   // registers 8s .. 8s+7
-{
-    f32x8 f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = acc[8 * s + e];
     return __builtin_convertvector(f, bf16x8);
 }
 
@@ -145,7 +131,20 @@ __device__ __forceinline__ void role_guard() { asm volatile("; wave-role block: 
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Canonical state rows (Eq. 4 order) of a packed row; a pair row has two (equal for delta = 0).
+// lane i of every 16 gets lane (i + D) % 16
+template <int D> __device__ __forceinline__ float rotate16(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x120 + 16 - D, 0xf, 0xf, true));
+}
+
+// the second factor's index in row fl of tile T < 16
+__host__ __device__ constexpr int partner(int T, int fl)
+{
+    if (T < 8) return (fl & 16) + ((fl + T) & 15);
+    return fl < 16 ? 16 + ((fl + T - 8) & 15) : (fl + 7 - (T & 6) + (T & 1)) & 15;
+}
+
+// Canonical state rows (Eq. 4 order) of a packed row; a pair row has two (equal for a square).
 // With packed_state the buffer is the packed layout (one row per unordered pair: a single row).
 struct CanonRows { int r1, r2; };   // r1 < 0: padding
 __device__ __forceinline__ CanonRows canon_pair(int a, int b, bool packed_state)
@@ -156,23 +155,15 @@ __device__ __forceinline__ CanonRows canon_pair(int a, int b, bool packed_state)
     }
     return {1 + DP + a * DP + b, 1 + DP + b * DP + a};
 }
-__device__ __forceinline__ CanonRows canon_rows_main(int delta, int fl, bool packed_state)
-{
-    return canon_pair(fl, (fl + delta) & (DP - 1), packed_state);
-}
-__device__ __forceinline__ CanonRows canon_rows_e1(int fl) { return {1 + fl, 1 + fl}; }
-__device__ __forceinline__ CanonRows canon_rows_e2(int fl, bool packed_state)
-{
-    if (fl == 0) return {0, 0};
-    if (fl >= 16) return canon_pair(fl - 16, fl, packed_state);
-    return {-1, -1};
-}
-
-// row fl of tile T (T < 16: delta = T; 16: E1; 17: E2)
+// row fl of tile T (16: E1; 17: E2)
 __device__ __forceinline__ CanonRows canon_rows(int T, int fl, bool packed_state)
 {
-    return T < 16 ? canon_rows_main(T, fl, packed_state) : T == 16 ? canon_rows_e1(fl) : canon_rows_e2(fl, packed_state);
+    if (T == 16) return {1 + fl, 1 + fl};
+    if (T < 16) return canon_pair(fl, partner(T, fl), packed_state);
+    return fl & 8 ? CanonRows{-1, -1} : canon_pair(fl, fl + 8, packed_state);
 }
+// state rows hold sum k_a k_b v for a pair
+__device__ __forceinline__ bool is_pair(CanonRows c) { return c.r1 > DP; }
 
 constexpr int kMaxSegments = 16;
 struct SegTable { int begin[kMaxSegments + 1]; };
@@ -187,7 +178,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     uint16_t *__restrict__ y, float *state, int has_init, int import_only, int init_in_entry, float *__restrict__ ws,
     int N, int dv, SegTable segs, int G, int groups, int local)
 {
-    __shared__ __align__(16) Lds lds;
+    __shared__ __align__(16) std::conditional_t<INC, LdsInc, Lds> lds;
 
     // has_init carries three flags: bit 0 an initial state is given, bit 1 the state buffer is packed,
     // bit 2 the outputs are the numerators alone (no division by the denominator)
@@ -196,10 +187,8 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     has_init &= 1;
     int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = w & 3;   // waves 0 .. 3: E1 / E2 and the K-state; 4 .. 7: the intra-chunk block
-    const bool low = w < 4;
     int lane = tid & 63;
-    int g = lane >> 5, n = lane & 31, lq = lane >> 4, ln = lane & 15;
+    int g = lane >> 5, n = lane & 31;
 
     const int slices = dv / COLS;
     const int gseg = !INC ? G : import_only ? 1 : G - 1;
@@ -216,13 +205,13 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
         seg = bid / (groups - local);
         bid = local + bid % (groups - local);
     }
-    const int slice = bid % slices;
-    const int u = bid / slices;
+    seg = __builtin_amdgcn_readfirstlane(seg);
+    const int slice = __builtin_amdgcn_readfirstlane(bid % slices);
+    const int u = __builtin_amdgcn_readfirstlane(bid / slices);
     const int col0 = slice * COLS;
 
     const int tok_begin = segs.begin[seg];
     const int tok_end = min(N, segs.begin[seg + 1]);
-    const int n_chunks = (tok_end - tok_begin + C - 1) / C;
 
     const uint16_t *qu = q + (size_t)u * N * DP;
     const uint16_t *ku = k + (size_t)u * N * DP;
@@ -234,68 +223,48 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     float *ws_unit = ws + ((size_t)(u * slices + slice) * G) * kWsEntryFloats;
 
     // ---- accumulators -------------------------------------------------------------------------
-    f32x16 S[2][TPW];      // main tiles delta = 2 w + tt, column tile c ^ (r % 2)
-    f32x16 X;              // waves 0 .. 3: column tile r % 2 of E1 (r < 2) or E2
-    f32x4 M;               // M[16 (r / 2) + 4 (lane / 16) + i][16 (r % 2) + lane % 16]
-    float z1 = 0.f, z0 = 0.f;   // z1[16 (r / 2) + lane % 16], tokens before this call's first
-    const int xc = r & 1, xe = r >> 1;
+    f32x16 S[2][2];   // [column tile ^ (w % 2)][tile 2 w + tt]
+    // wave 0: M; 1: z1 (column b, the same in every row); 2, 3: the constant's row (column c of column tile w - 2, the same in every
+    // row); 4, 5: column tile w - 4 of E1; 6, 7: column tile w - 6 of E2
+    f32x16 X;
+    float z0 = 0.f;   // tokens before this call's first
     zero16(X);
-    M = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) zero16(S[c][tt]);
-    }
+        for (int tt = 0; tt < 2; ++tt) zero16(S[c][tt]);
 
     auto add_entry = [&](int p) {
-        const float *e = ws_unit + (size_t)p * kWsEntryFloats + 4 * lane;
-        f32x4 t[2][TPW][4], tx[4], tm;
-        auto fetch = [&](int slot, f32x4 *x) {
+        const float *e = ws_unit + (size_t)p * kWsEntryFloats;
+        const float z = e[4 * 5 * 1024 - 1];
+        f32x4 t[5][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const f32x4 *>(e + (slot * 4 + j) * 256);
-        };
-        auto add = [&](const f32x4 *x, f32x16 &a) {
+        for (int s = 0; s < 5; ++s)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[s][j] = *reinterpret_cast<const f32x4 *>(e + 5 * 1024 * w + 4 * lane + (s * 4 + j) * 256);
+#pragma unroll
+        for (int s = 0; s < 5; ++s)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) a[4 * j + k] += x[j][k];
-        };
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) fetch(20 * (c ^ xc) + 2 * w + tt, t[c][tt]);
-        const f32x4 tz = *reinterpret_cast<const f32x4 *>(e + (19 * 4 + r) * 256);
-        fetch(20 * xc + 16 + xe, tx);   // (waves 4 .. 7 do not use theirs)
-        tm = *reinterpret_cast<const f32x4 *>(e + (18 * 4 + r) * 256);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) add(t[c][tt], S[c][tt]);
-        add(tx, X);
-        M += tm;
-        z1 += tz[0];
-        z0 += tz[1];
+                for (int i = 0; i < 4; ++i) {
+                    if (s < 4) S[s >> 1][s & 1][4 * j + i] += t[s][j][i];
+                    else X[4 * j + i] += t[s][j][i];
+                }
+        z0 += z;
     };
     auto put_entry = [&](int p) {
-        float *e = ws_unit + (size_t)p * kWsEntryFloats;
-        auto put = [&](int slot, const f32x16 &a) {
+        float *e = ws_unit + (size_t)p * kWsEntryFloats + 5 * 1024 * w + 4 * lane;
+#pragma unroll
+        for (int s = 0; s < 5; ++s)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 f32x4 o;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = a[4 * j + i];
-                *reinterpret_cast<f32x4 *>(e + (slot * 4 + j) * 256 + 4 * lane) = o;
+                for (int i = 0; i < 4; ++i) o[i] = s < 4 ? S[s >> 1][s & 1][4 * j + i] : X[4 * j + i];
+                if (s == 4 && j == 3 && w == 3) o[3] = lane == 63 ? z0 : o[3];   // (rows hold copies of the constant's)
+                *reinterpret_cast<f32x4 *>(e + (s * 4 + j) * 256) = o;
             }
-        };
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) put(20 * (c ^ xc) + 2 * w + tt, S[c][tt]);
-        }
-        if (!low) return;
-        put(20 * xc + 16 + xe, X);
-        *reinterpret_cast<f32x4 *>(e + (18 * 4 + r) * 256 + 4 * lane) = M;
-        *reinterpret_cast<f32x4 *>(e + (19 * 4 + r) * 256 + 4 * lane) = f32x4{z1, z0, 0.f, 0.f};
     };
 
     // The state buffer moves through LDS, one column tile at a time, as an image of its tiles: image[32 T + row][IMG_LD].
@@ -304,10 +273,11 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     float *image = reinterpret_cast<float *>(&lds);
     constexpr int IMG_Q = 32 * TILES * 8, IMG_STEPS = IMG_Q / NT;   // 16-byte pieces of a column tile: all, per thread
     static_assert(IMG_Q % NT == 0, "");
+    auto place = [&](int T, int rr) -> float & { return image[4 * g * IMG_LD + n + (32 * T + 8 * (rr >> 2) + (rr & 3)) * IMG_LD]; };
     auto import_state = [&]() {
 #pragma unroll
         for (int cc = 0; cc < 2; ++cc) {
-            constexpr int BATCH = 3;
+            constexpr int BATCH = 9;
 #pragma unroll 1
             for (int s0 = 0; s0 < IMG_STEPS; s0 += BATCH) {
                 f32x4 t[BATCH][2];
@@ -322,32 +292,36 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
                 for (int j = 0; j < BATCH; ++j) {
                     const int i = (s0 + j) * NT + tid, row = i >> 3;
-                    const bool zero = canon_rows(row >> 5, row & 31, packed_state).r1 < 0;   // (padding)
+                    const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                     *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
-                        zero ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * 0.5f;
+                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * (is_pair(cr) ? kRsqrt2 : 0.5f);
                 }
             }
             __syncthreads();
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) {
-                const int fl = 8 * (rr >> 2) + (rr & 3);
 #pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
-                    const float t = image[4 * g * IMG_LD + n + (32 * (2 * w + tt) + fl) * IMG_LD];
-                    S[0][tt][rr] = cc == xc ? t : S[0][tt][rr];
-                    S[1][tt][rr] = cc == xc ? S[1][tt][rr] : t;
+                for (int tt = 0; tt < 2; ++tt) {
+                    const float t = place(2 * w + tt, rr);
+                    S[0][tt][rr] = (w & 1) == cc ? t : S[0][tt][rr];
+                    S[1][tt][rr] = (w & 1) == cc ? S[1][tt][rr] : t;
                 }
-                if (low && cc == xc) X[rr] = image[4 * g * IMG_LD + n + (32 * (16 + xe) + fl) * IMG_LD];
+                if (w >= 4 && (w & 1) == cc) X[rr] = place(14 + (w >> 1), rr);
             }
             __syncthreads();
         }
-        // M[a][b] = sqrt(2) x the symmetric part of z's pair rows
+        if (w == 0) {   // M = sqrt(2) x the symmetric part of z's pair rows
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const CanonRows cr = canon_pair(16 * xe + 4 * lq + i, 16 * xc + ln, packed_state);
-            M[i] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+            for (int rr = 0; rr < 16; ++rr) {
+                const CanonRows cr = canon_pair(8 * (rr >> 2) + 4 * g + (rr & 3), n, packed_state);
+                X[rr] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+            }
         }
-        z1 = zu[1 + 16 * xe + ln];
+        if (w > 0 && w < 4) {
+            const float t = w == 1 ? zu[1 + n] : Su[32 * (w - 2) + n];
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) X[rr] = t;
+        }
         z0 = zu[0];
     };
     auto export_state = [&]() {   // (both rows of a pair; slice 0 writes z)
@@ -356,13 +330,12 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             __syncthreads();
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) {
-                const int fl = 8 * (rr >> 2) + (rr & 3);
 #pragma unroll
-                for (int tt = 0; tt < TPW; ++tt) {
+                for (int tt = 0; tt < 2; ++tt) {
                     const float t0 = S[0][tt][rr], t1 = S[1][tt][rr];
-                    image[4 * g * IMG_LD + n + (32 * (2 * w + tt) + fl) * IMG_LD] = cc == xc ? t0 : t1;
+                    place(2 * w + tt, rr) = (w & 1) == cc ? t0 : t1;
                 }
-                if (low && cc == xc) image[4 * g * IMG_LD + n + (32 * (16 + xe) + fl) * IMG_LD] = X[rr];
+                if (w >= 4 && (w & 1) == cc) place(14 + (w >> 1), rr) = X[rr];
             }
             __syncthreads();
 #pragma unroll 3
@@ -370,26 +343,65 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                 const int i = st * NT + tid, row = i >> 3;
                 const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                 if (cr.r1 >= 0) {
-                    const f32x4 t = *reinterpret_cast<const f32x4 *>(image + row * IMG_LD + 4 * (i & 7));
+                    const f32x4 t = *reinterpret_cast<const f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) * (is_pair(cr) ? kRsqrt2 : 1.f);
                     float *p = Su + 32 * cc + 4 * (i & 7);
                     *reinterpret_cast<f32x4 *>(p + (size_t)cr.r1 * dv) = t;
                     if (cr.r2 != cr.r1) *reinterpret_cast<f32x4 *>(p + (size_t)cr.r2 * dv) = t;
                 }
             }
         }
-        if (slice == 0 && low) {
+        if (slice == 0) {
+            if (w == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int a = 16 * xe + 4 * lq + i, b = 16 * xc + ln;
-                if (!packed_state || a <= b) zu[canon_pair(a, b, packed_state).r1] = kRsqrt2 * M[i];
+                for (int rr = 0; rr < 16; ++rr) {
+                    const int a = 8 * (rr >> 2) + 4 * g + (rr & 3);
+                    if (!packed_state || a <= n) zu[canon_pair(a, n, packed_state).r1] = kRsqrt2 * X[rr];
+                }
             }
-            if (xc == 0 && lq == 0) {
-                zu[1 + 16 * xe + ln] = z1;
-                if (r == 0 && ln == 0) zu[0] = z0 + (float)N;
-            }
+            if (w == 1 && g == 0) zu[1 + n] = X[0];
+            if (tid == 0) zu[0] = z0 + (float)N;
         }
+        if ((w == 2 || w == 3) && g == 0) Su[32 * (w - 2) + n] = X[0];
     };
 
+    // The lane's number, worked out anew: what is computed from it in one phase of a block is not kept through the others.
+    auto fresh_lane = [&]() {
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        tid = 64 * w + lane;
+        g = lane >> 5;
+        n = lane & 31;
+    };
+
+    // ---- a block's rows: global -> registers -> LDS -----------------------------------------------
+    // Loads are unconditional (rows past the end re-read the last one, and are zeroed when staged).
+    struct Raw { u32x4 k[2], v[4]; } raw;
+    auto load_raw = [&](int tok0) {
+        const int last = tok_end - 1 - tok0;
+        const uint16_t *kb = ku + (size_t)tok0 * DP, *vb = vu + (size_t)tok0 * dv;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t t = min(2 * (tid >> 2) + h, last);
+            raw.k[h] = *reinterpret_cast<const u32x4 *>(kb + (t * DP + 8 * (tid & 3)));
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t t = min((tid >> 3) + 64 * h, last);
+            raw.v[h] = *reinterpret_cast<const u32x4 *>(vb + (t * (uint32_t)dv + 8 * (tid & 7)));
+        }
+    };
+    // Queries 32 qt .. + 31 of a block, lane n the n-th.  (Waves w and w + 4 are on one SIMD: nine key tiles for the two.)
+    const int qt = w < 4 ? w : 11 - w;
+    u32x2 qraw[8];   // elements 16 (b / 4) + 4 ((b + g) % 4) ..
+    auto load_q = [&](int tok0) {
+        const uint16_t *qb = qu + (size_t)tok0 * DP;
+        const uint32_t t = min(QT * qt + n, tok_end - 1 - tok0);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) qraw[b] = *reinterpret_cast<const u32x2 *>(qb + (t * DP + 16 * (b >> 2) + 4 * ((b + g) & 3)));
+    };
+    load_raw(tok_begin);
+    if (!INC) load_q(tok_begin);
+
+    bool have_state = true;   // (uniform) something to read out before the first block
     if (INC) {
         if (has_init && seg == 0) {
             import_state();
@@ -402,375 +414,422 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     } else if (has_init) {
         if (init_in_entry) add_entry(0);
         else import_state();
+    } else {
+        have_state = false;
     }
 
-    // What is computed from the lane's place before the loop is not kept through it, and the other way round.
-    auto fresh_lane = [&]() {
-        asm volatile("" : "+v"(tid));
-        lane = tid & 63;
-        g = lane >> 5; n = lane & 31; lq = lane >> 4; ln = lane & 15;
-    };
-    fresh_lane();
+    z0 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(z0)));   // (the same in every lane)
 
-    // ---- staging: global -> registers -> LDS ----------------------------------------------------
-    // A thread moves elements 2 j, 2 j + 1 of the K and Q rows of a token and 4 columns of its V row (j = tid % 16).  Loads are
-    // unconditional (rows past the end re-read the last one, and are zeroed when staged), so that the number in flight is known.
-    const int s_tok = tid >> 4, s_j = tid & 15;
-    struct Raw { uint32_t k, q; u32x2 v; } raw[PF];   // chunk mod PF
-    auto load_raw = [&](int tok0, Raw &x) {
-        const int tok = min(tok0 + s_tok, tok_end - 1);
-        x.k = *reinterpret_cast<const uint32_t *>(ku + (size_t)tok * DP + 2 * s_j);
-        if (!INC) x.q = *reinterpret_cast<const uint32_t *>(qu + (size_t)tok * DP + 2 * s_j);
-        x.v = *reinterpret_cast<const u32x2 *>(vu + (size_t)tok * dv + 4 * s_j);
-    };
-    auto stage = [&](int tok0, const Raw &x, Rows &rows) {
-        const bool past = tok0 + s_tok >= tok_end;
-        const uint32_t kraw = past ? 0u : x.k;
-        const u32x2 vraw = {past ? 0u : x.v[0], past ? 0u : x.v[1]};
-        // product of the elements a and a + 16, which is eight lanes to the right (row_shl:8)
-        auto pair = [&](float a) {
-            return a * __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(a), 0x108, 0xf, 0xf, false));
-        };
-        const float k0 = bf16lo(kraw) * kCK, k1 = bf16hi(kraw) * kCK;
-        rows.kts[2 * s_j][s_tok] = k0;
-        rows.kts[2 * s_j + 1][s_tok] = k1;
-        *reinterpret_cast<uint32_t *>(&rows.krow[s_tok][2 * s_j]) = kraw;
-        const uint32_t kp = pack2(pair(k0), pair(k1));
-        uint32_t qp = 0;
-        if (!INC) {
-            const float q0 = bf16lo(x.q) * kCQ, q1 = bf16hi(x.q) * kCQ;
-            *reinterpret_cast<f32x2 *>(&rows.qs[s_tok][2 * s_j]) = f32x2{q0, q1};
-            *reinterpret_cast<uint32_t *>(&rows.qrow[s_tok][2 * s_j]) = x.q;
-            qp = pack2(pair(q0), pair(q1));
+    auto stage = [&](int tok0, Kv &kv, uint16_t (*krow)[DP]) {
+        const int rows = tok_end - tok0;
+        const int t0 = 2 * (tid >> 2), c = tid & 3;
+        if (rows < BLOCK) {   // (uniform) rows past the end
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) raw.k[h] = t0 + h < rows ? raw.k[h] : zero;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) raw.v[h] = (tid >> 3) + 64 * h < rows ? raw.v[h] : zero;
         }
-        *reinterpret_cast<u32x2 *>(&rows.vrow[s_tok][4 * s_j]) = vraw;
-        if (s_j < 8) {
-            *reinterpret_cast<uint32_t *>(&rows.krow[s_tok][48 + 2 * s_j]) = kp;
-            if (!INC) *reinterpret_cast<uint32_t *>(&rows.qrow[s_tok][48 + 2 * s_j]) = qp;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (!INC) *reinterpret_cast<u32x4 *>(&krow[t0 + h][8 * (c ^ ((t0 >> 2) & 3))]) = raw.k[h];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i][t0]) = f32x2{bf16lo(raw.k[0][i]), bf16lo(raw.k[1][i])};
+            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i + 1][t0]) = f32x2{bf16hi(raw.k[0][i]), bf16hi(raw.k[1][i])};
         }
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
     };
 
     // ---- operands ---------------------------------------------------------------------------------
-    // phi(Q)^T operand of slab sl of tile tt: k-slot (jj, i) is row a = 16 sl + 8 jj + 4 g + i, the pair (a, (a + delta) mod 32)
-    struct QSrc { float a[8], b[2][6]; };
-    auto q_source = [&](const Rows &rows, int sl) {
-        const float *row = rows.qs[n];
-        QSrc o;
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int base = 16 * sl + 8 * jj + 4 * g;
-            const f32x4 t = *reinterpret_cast<const f32x4 *>(row + base);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o.a[4 * jj + i] = t[i];
-#pragma unroll
-            for (int h = 0; h < 3; ++h) {
-                const f32x2 b = *reinterpret_cast<const f32x2 *>(row + ((base + 2 * w + 2 * h) & 31));
-                o.b[jj][2 * h] = b[0];
-                o.b[jj][2 * h + 1] = b[1];
-            }
-        }
-        return o;
+    // V^T operand ("8 tokens of one column": lane (g, n): column n of the tile at two runs of 4 tokens) from row-major rows, by the
+    // transposing LDS read: in each group of 16 lanes, lane k supplies the address of 4 consecutive columns (4 (k % 4) ..)
+    // of row k / 4 of the group's 16-column block and receives column k of that block at the 4 rows.
+    // GS: tokens between the runs of g = 0 and 1, RS: between a lane's two runs.
+    auto v_place = [&](int GS) {
+        return (((lane & 15) >> 2) + GS * g) * COLS + 8 * ((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (((lane >> 3) & 1) << 2)) + 4 * (lane & 1);
     };
-    // (every wave multiplies: the first one, alone, would be the last to finish)
-    const float dw = w == 0 ? 0.5f : 1.f;   // delta = 0: x_a^2 / sqrt(2)
-    auto q_op = [&](const QSrc &s, int tt) {
-        float pr[8];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                pr[4 * jj + i] = (tt == 0 ? s.a[4 * jj + i] * dw : s.a[4 * jj + i]) * s.b[jj][i + tt];
-        return pack8(pr);
-    };
-    // phi(K)^T operand of token slab ts of tile tt: row n, k-slots the tokens 16 ts + 4 g + {0..3, 8..11}
-    struct KSrc { f32x4 a[2], b[TPW][2]; };
-    auto k_source = [&](const Rows &rows, int ts) {
-        const int tcol = 16 * ts + 4 * g;
-        KSrc o;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) o.a[h] = *reinterpret_cast<const f32x4 *>(&rows.kts[n][tcol + 8 * h]);
-#pragma unroll
-        for (int tt = 0; tt < TPW; ++tt)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                o.b[tt][h] = *reinterpret_cast<const f32x4 *>(&rows.kts[(n + 2 * w + tt) & 31][tcol + 8 * h]);
-        return o;
-    };
-    auto k_op = [&](const KSrc &s, int tt) {
-        float pr[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { pr[i] = s.a[0][i] * s.b[tt][0][i]; pr[4 + i] = s.a[1][i] * s.b[tt][1][i]; }
-        return pack8(pr);
-    };
-    // V^T operand (lane (g, n): column n of the tile at the 8 tokens of its k-slots, two runs of 4 tokens
-    // starting at tok4 and tok4 + 8) from row-major rows, by the transposing LDS read: in each group
-    // of 16 lanes, lane k supplies the address of 4 consecutive columns (4 (k % 4) ..) of row k / 4 of
-    // the group's 16-column block and receives column k of that block at the 4 rows.
-    const int tr_row = ((lane & 15) >> 2) + 4 * g, tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    auto tr_read = [&](const uint16_t *p, int stride) {
-        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-        const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 8 * stride));
+    auto read_v = [&](const uint16_t *p, int RS) {   // p: the place in the first row of the 16
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+        const s16x4 z = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + RS * COLS));
         s16x8 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { o[i] = a[i]; o[4 + i] = b[i]; }
+        for (int i = 0; i < 4; ++i) { o[i] = x[i]; o[4 + i] = z[i]; }
         return __builtin_bit_cast(bf16x8, o);
     };
-    auto read_v = [&](const Rows &rows, int ts, int c) { return tr_read(&rows.vrow[16 * ts + tr_row][32 * c + tr_col], VR_LD); };
-    auto read_k = [&](const Rows &rows, int ts, int col) { return tr_read(&rows.krow[16 * ts + tr_row][col + tr_col], KR_LD); };
-    // 16 columns of K at all 32 tokens (operand of the 16 x 16 x 32 product)
-    auto read_k16 = [&](const Rows &rows, int col) {
-        const uint16_t *p = &rows.krow[(ln >> 2) + 4 * lq][col + 4 * (lane & 3)];
-        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-        const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 16 * KR_LD));
-        s16x8 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { o[i] = a[i]; o[4 + i] = b[i]; }
-        return __builtin_bit_cast(bf16x8, o);
-    };
-    // sums over the wave's halves / over the two rows of 16 lanes of each half
-    auto add_halves = [&](float a, float b) {   // lanes < 32: a, lanes >= 32: b
-        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-        return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-    };
-    auto add_rows = [&](float a) {
-        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
-        return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-    };
 
-    struct VSrc { bf16x8 v[2]; };
-    auto v_source = [&](const Rows &rows, int ts) {
-        VSrc o;
-        o.v[0] = read_v(rows, ts, xc);
-        o.v[1] = read_v(rows, ts, xc ^ 1);
-        return o;
-    };
-    // S += phi(K)^T V over this wave's tiles
-    auto update_slab = [&](const KSrc &src, const VSrc &vs) {
+    // ---- state update: S += phi(K)^T V over this wave's tiles; k-slot j of lane (g, n) is token 16 ts + 8 g + j --------
+    auto update = [&](const Kv &kv, int slabs) {
+        fresh_lane();
+        const float *ka = &kv.kt[n][8 * g], *kb = &kv.kt[partner(2 * w, n)][8 * g];
+        const uint16_t *v0 = &kv.v[0][0] + (v_place(8) ^ ((w & 1) << 5)), *v1 = &kv.v[0][0] + (v_place(8) ^ ((~w & 1) << 5));
+        struct Src { f32x4 a[2], b[2]; bf16x8 v[2]; };
+        auto source_k = [&](int ts, Src &s) {
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) {
-            const bf16x8 op = k_op(src, tt);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) S[c][tt] = mfma(op, vs.v[c], S[c][tt]);
-        }
-    };
-    // waves 0 .. 3: E1 / E2, M += K^T K, z1 += sum of the rows
-    auto update_e = [&](const Rows &rows, const VSrc &v0, const VSrc &v1) {
-        const bf16x8 e0 = read_k(rows, 0, 32 * xe), e1 = read_k(rows, 1, 32 * xe);
-        const bf16x8 ea = read_k16(rows, 16 * xe), eb = read_k16(rows, 16 * xc);
-        X = mfma(e0, v0.v[0], X);
-        X = mfma(e1, v1.v[0], X);
-        M = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ea, eb, M, 0, 0, 0);
-        const u32x4 kw = __builtin_bit_cast(u32x4, ea);
-        float z1c = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) z1c += bf16lo(kw[i]) + bf16hi(kw[i]);
-        z1c = add_halves(z1c, z1c);
-        z1 += add_rows(z1c);
-        if (!INC) lds.z1s[r][ln] = xe == xc ? z1 : 0.f;
-    };
-
-    // columns 32 .. 47 of the K and Q rows: the constant feature (past the end its V row is zero), then zeros
-    if (s_j < 8)
-#pragma unroll
-        for (int gen = 0; gen < 2; ++gen) {
-            const uint32_t t = s_j == 0 ? 0x3F80u : 0u;
-            *reinterpret_cast<uint32_t *>(&lds.rows[gen].krow[s_tok][32 + 2 * s_j]) = t;
-            if (!INC) *reinterpret_cast<uint32_t *>(&lds.rows[gen].qrow[s_tok][32 + 2 * s_j]) = t;
-        }
-#pragma unroll
-    for (int i = 0; i < PF; ++i) load_raw(tok_begin + C * i, raw[i]);
-    stage(tok_begin, raw[0], lds.rows[0]);
-    load_raw(tok_begin + C * PF, raw[0]);
-    // chunk t: f(t mod PF, first token).  (Pairs, and an odd chunk after the loop: with a way out between the two the compiler sees a path on
-    // which the first one's loads are the newest, and has the first chunk of every pair wait for all of them.)
-    auto for_chunks = [&](auto &&f) {
-        int t = 0;
-        for (; t + 1 < n_chunks; t += PF) {
-            const int tok0 = tok_begin + C * t;
-            f(std::integral_constant<int, 0>{}, tok0);
-            f(std::integral_constant<int, 1>{}, tok0 + C);
-        }
-        if (t < n_chunks) f(std::integral_constant<int, 0>{}, tok_begin + C * t);
-    };
-
-    if (INC) {
-        wg_sync();
-        for_chunks([&](auto gen, int tok0) {
-            constexpr int p = decltype(gen)::value, p1 = (p + 1) % PF;
-            const Rows &rows = lds.rows[p];
-            const KSrc k0 = k_source(rows, 0);
-            const VSrc v0 = v_source(rows, 0);
-            __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
-            const KSrc k1 = k_source(rows, 1);
-            const VSrc v1 = v_source(rows, 1);
-            __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
-            update_slab(k0, v0);
-            stage(tok0 + C, raw[p1], lds.rows[p1]);
-            load_raw(tok0 + (PF + 1) * C, raw[p1]);
-            update_slab(k1, v1);
-            if (low) {
-                role_guard();
-                update_e(rows, v0, v1);
-            }
-            wg_sync();
-        });
-        put_entry(1 + seg);
-        return;
-    }
-
-    // ---- full pass ----------------------------------------------------------------------------------
-    // A chunk's outputs: lane (tk, cq) finishes columns 4 cq .. of token 4 w + tk; the partial sums are read across (the sender's
-    // lane l puts its four of column group cj at place l ^ (cj + 8 (l / 32)): 16 consecutive lanes in different banks).
-    const int o_tok = 4 * w + (lane >> 4), o_cq = lane & 15;
-    const int o_place = (32 * (o_cq & 1) + o_tok) ^ ((o_cq >> 1) + 8 * (o_cq & 1));
-    struct Out { f32x4 d4, d2, part[NW]; };
-    auto out_source = [&](int g2) {
-        Out o;
-        o.d4 = *reinterpret_cast<const f32x4 *>(&lds.den[g2][o_tok][0]);
-        o.d2 = *reinterpret_cast<const f32x4 *>(&lds.den[g2][o_tok][4]);
-#pragma unroll
-        for (int sl = 0; sl < NW; ++sl) o.part[sl] = *reinterpret_cast<const f32x4 *>(&lds.xbuf[sl][o_cq >> 1][o_place][0]);
-        return o;
-    };
-    auto output = [&](const Out &x, int tok0) {
-        const float den = z0 + (float)tok0 + ((x.d4[0] + x.d4[1]) + (x.d4[2] + x.d4[3])) + (x.d2[0] + x.d2[1]);
-        const float inv = numerator_only ? 1.f : 1.f / den;
-        const f32x4 sum = ((x.part[0] + x.part[1]) + (x.part[2] + x.part[3])) + ((x.part[4] + x.part[5]) + (x.part[6] + x.part[7]));
-        if (tok0 >= tok_begin && tok0 + o_tok < tok_end)
-            *reinterpret_cast<u32x2 *>(yu + (ptrdiff_t)(tok0 + o_tok) * dv + 4 * o_cq) =
-                __builtin_bit_cast(u32x2, __builtin_convertvector(sum * inv, bf16x4));
-    };
-    if (low) lds.z1s[r][ln] = xe == xc ? z1 : 0.f;
-    wg_sync();
-    for_chunks([&](auto gen, int tok0) {
-        constexpr int p = decltype(gen)::value, p1 = (p + 1) % PF;
-        const Rows &rows = lds.rows[p];
-        // the previous chunk's partial outputs, the queries
-        const Out prev = out_source(p1);
-        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
-        output(prev, tok0 - C);
-        __builtin_amdgcn_sched_barrier(0);
-        const QSrc q0 = q_source(rows, 0);
-        const QSrc q1 = q_source(rows, 1);
-        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
-        f32x16 Y[2];
-        zero16(Y[0]);
-        zero16(Y[1]);
-        auto readout = [&](const QSrc &src, int sl) {
-#pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
-                const bf16x8 op = q_op(src, tt);
-#pragma unroll
-                for (int c = 0; c < 2; ++c) Y[c] = mfma(pack8_acc(S[c][tt], sl), op, Y[c]);
+            for (int h = 0; h < 2; ++h) {
+                s.a[h] = *reinterpret_cast<const f32x4 *>(ka + 16 * ts + 4 * h);
+                s.b[h] = *reinterpret_cast<const f32x4 *>(kb + 16 * ts + 4 * h);
             }
         };
-        readout(q0, 0);
-        readout(q1, 1);
-        if (low) {
-            role_guard();
-            // E1 / E2 for column tile xc
-            u32x2 qx[2][2], qa[2];
-            f32x4 qb[2];
+        auto source_v = [&](int ts, Src &s) {
+            s.v[0] = read_v(v0 + 16 * COLS * ts, 4);   // column tile w % 2
+            s.v[1] = read_v(v1 + 16 * COLS * ts, 4);
+        };
+        // phi(K)^T of the tiles (0, 1), E1 (2), E2 (3)
+        auto phi = [&](const Src &s, auto which) {
+            constexpr int P = decltype(which)::value;
+            float pr[8];
 #pragma unroll
-            for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    qx[sl][h] = *reinterpret_cast<const u32x2 *>(&rows.qrow[n][32 * xe + 4 * g + 16 * sl + 8 * h]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                qa[h] = *reinterpret_cast<const u32x2 *>(&rows.qrow[16 * h + ln][16 * xe + 4 * lq]);
-                qb[h] = *reinterpret_cast<const f32x4 *>(&rows.qs[16 * h + ln][16 * xc + 4 * lq]);
+            for (int i = 0; i < 8; ++i) {
+                const float a = s.a[i >> 2][i & 3], b = s.b[i >> 2][i & 3];
+                pr[i] = P == 0 ? a * b : P == 1 ? a * rotate16<1>(b) : P == 2 ? a : a * rotate16<8>(a);
             }
-            const f32x4 zv = *reinterpret_cast<const f32x4 *>(&lds.z1s[r][4 * lq]);
+            return pack8(pr);
+        };
+        constexpr int UNROLL = 4;
+        Src src[2];
+        source_k(0, src[0]);
+        __builtin_amdgcn_sched_barrier(0);   // (in the loop's order, for the count of what is in flight)
+        source_v(0, src[0]);
+        source_k(1, src[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        source_v(1, src[1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+        for (int ts = 0; ts < slabs; ts += UNROLL) {   // (past the last token there are zeros, past the end the last ones are read again)
+            const int on = ts + UNROLL < slabs ? UNROLL : 0;
 #pragma unroll
-            for (int sl = 0; sl < 2; ++sl)
-                Y[0] = mfma(pack8_acc(X, sl), as_bf16x8(u32x4{qx[sl][0][0], qx[sl][0][1], qx[sl][1][0], qx[sl][1][1]}), Y[0]);
-            // denominator from before the chunk: T[b][query] = sum_a M[a][b] q_a over this wave's a and b, then
-            // sum_b q_b (z1[b] + T[b] / 2)
-            const s16x4 m4 = __builtin_bit_cast(s16x4, __builtin_convertvector(M, bf16x4));
-            float d[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const f32x4 T = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(m4, __builtin_bit_cast(s16x4, qa[h]), f32x4{0.f, 0.f, 0.f, 0.f},
-                                                                         0, 0, 0);
-                d[h] = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) d[h] = fmaf(qb[h][i], fmaf(0.5f, T[i], zv[i]), d[h]);
+            for (int i = 0; i < UNROLL; ++i) {
+                Src &x = src[i & 1];
+                const bf16x8 op0 = phi(x, std::integral_constant<int, 0>{}), op1 = phi(x, std::integral_constant<int, 1>{});
+                if (i == UNROLL - 2) {
+                    ka += 16 * on, kb += 16 * on;
+                    v0 += 16 * COLS * on, v1 += 16 * COLS * on;
+                }
+                const int next = i < UNROLL - 2 ? i + 2 : i + 2 - UNROLL;
+                // (loads stay where they are, two slabs ahead of their use)
+                __builtin_amdgcn_sched_barrier(0);
+                source_k(next, x);
+                __builtin_amdgcn_s_setprio(1);   // (a wave that has its operands goes first: the other one builds its own meanwhile)
+                __builtin_amdgcn_sched_barrier(0);
+                S[0][0] = mfma(op0, x.v[0], S[0][0]);
+                S[1][0] = mfma(op0, x.v[1], S[1][0]);
+                S[0][1] = mfma(op1, x.v[0], S[0][1]);
+                S[1][1] = mfma(op1, x.v[1], S[1][1]);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_setprio(0);
+                source_v(next, x);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            lds.den[p][16 * g + ln][r] = add_rows(add_halves(d[0], d[1])) * (1.f / kCQ);
-        } else {
-            role_guard();
-            // intra-chunk block, keys 16 xe .. + 15 and column tile xc: P^T = mask(1 + A^T + A^T^2 / 2), Y^T += V^T P^T
-            f32x16 P;
-            zero16(P);
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {   // contraction over d' = 32 in two steps; rows 0 .. 15 of P are used
-                const u32x4 kop = *reinterpret_cast<const u32x4 *>(&rows.krow[(n + 16 * xe) & 31][16 * ks + 8 * g]);
-                const u32x4 qop = *reinterpret_cast<const u32x4 *>(&rows.qrow[n][16 * ks + 8 * g]);
-                P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
-            }
-            const bf16x8 vp = read_v(rows, xe, xc);
-            float cs = 0.f;
-#pragma unroll
-            for (int rr = 0; rr < 8; ++rr) {
-                const float x = P[rr];
-                const float pv = fmaf(x, fmaf(x, 0.5f, 1.f), 1.f);
-                P[rr] = 8 * (rr >> 2) + (rr & 3) <= n - 16 * xe - 4 * g ? pv : 0.f;
-                cs += P[rr];
-            }
-            lds.den[p][n][4 + xe] = add_halves(cs, cs);
-            Y[0] = mfma(vp, pack8_acc(P, 0), Y[0]);
+            asm volatile("" ::: "memory");
         }
-        wg_sync();   // every wave has the previous chunk's partial outputs
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                f32x4 o;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = Y[c][4 * j + i];
-                const int cj = 4 * (c ^ xc) + j;
-                *reinterpret_cast<f32x4 *>(&lds.xbuf[w][cj][lane ^ (cj + 8 * g)][0]) = o;
-            }
-        const KSrc k0 = k_source(rows, 0);
-        const VSrc v0 = v_source(rows, 0);
-        const KSrc k1 = k_source(rows, 1);
-        const VSrc v1 = v_source(rows, 1);
-        __builtin_amdgcn_sched_barrier(1);   // (only arithmetic crosses)
-        update_slab(k0, v0);
-        stage(tok0 + C, raw[p1], lds.rows[p1]);
-        load_raw(tok0 + (PF + 1) * C, raw[p1]);
-        update_slab(k1, v1);
-        if (low) {
+        // X: M = K^T K, z1 = 1 K, the constant 1 V; E1, E2
+        const u32x4 one = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+        const float *kx = &kv.kt[n][8 * g];
+        const uint16_t *vx = &kv.v[0][0] + (v_place(8) ^ ((w & 1) << 5));
+        auto add_x = [&](auto kind) {
+            constexpr int P = decltype(kind)::value;
             role_guard();
-            update_e(rows, v0, v1);
+#pragma unroll 1
+            for (int t0 = 0; t0 < slabs; t0 += UNROLL) {
+                Src x[UNROLL];
+#pragma unroll
+                for (int i = 0; i < UNROLL; ++i) {
+                    if (P != 2) {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) x[i].a[h] = *reinterpret_cast<const f32x4 *>(kx + 16 * i + 4 * h);
+                    }
+                    if (P >= 2) x[i].v[0] = read_v(vx + 16 * COLS * i, 4);
+                }
+                kx += 16 * UNROLL, vx += 16 * COLS * UNROLL;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < UNROLL; ++i) {
+                    bf16x8 op = as_bf16x8(one);
+                    if (P != 2) op = phi(x[i], std::integral_constant<int, P == 4 ? 3 : 2>{});
+                    X = P == 0 ? mfma(op, op, X) : P == 1 ? mfma(as_bf16x8(one), op, X) : mfma(op, x[i].v[0], X);
+                }
+            }
+        };
+        if (w == 0) add_x(std::integral_constant<int, 0>{});
+        else if (w == 1) add_x(std::integral_constant<int, 1>{});
+        else if (w < 4) add_x(std::integral_constant<int, 2>{});
+        else if (w < 6) add_x(std::integral_constant<int, 3>{});
+        else add_x(std::integral_constant<int, 4>{});
+    };
+    auto slabs_of = [&](int tok0) { return 2 * min((tok_end - tok0 + QT - 1) / QT, NW); };
+
+    fresh_lane();
+    if constexpr (INC) {
+        int gen = 0;
+#pragma unroll 1
+        for (int tok0 = tok_begin; tok0 < tok_end; tok0 += BLOCK, gen ^= 1) {
+            fresh_lane();
+            stage(tok0, lds.kv[gen], nullptr);
+            load_raw(min(tok0 + BLOCK, tok_end - 1));
+            wg_sync();
+            update(lds.kv[gen], slabs_of(tok0));
+        }
+        put_entry(1 + seg);
+        return;
+    } else {
+    // ---- full pass ----------------------------------------------------------------------------------
+
+#pragma unroll 1
+    for (int tok0 = tok_begin; tok0 < tok_end; tok0 += BLOCK) {
+        const bool more = tok0 + BLOCK < tok_end;
+        // ---- operand
+        fresh_lane();
+        stage(tok0, lds.kv, lds.k);
+        if (have_state) {
+            auto put = [&](uint16_t *p, const f32x16 &a, int r0, int r1) {   // registers r0 .. + 3, r1 .. + 3
+                f32x8 f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { f[i] = a[r0 + i]; f[4 + i] = a[r1 + i]; }
+                *reinterpret_cast<bf16x8 *>(p + 8 * lane) = __builtin_convertvector(f, bf16x8);
+            };
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int sl = 0; sl < 2; ++sl) {
+                        put(lds.s[4 * w + 2 * tt + sl][c ^ (w & 1)][0], S[c][tt], 8 * sl, 8 * sl + 4);
+                    }
+            if (w == 0) {
+                put(lds.m[0][0], X, 0, 4);
+                put(lds.m[1][0], X, 8, 12);
+            } else if (w < 4) {
+                if (g == 0) (w == 1 ? lds.z1 : lds.cst + 32 * (w - 2))[n] = X[0];
+            } else if (w < 6) {
+                put(lds.s[32][w - 4][0], X, 0, 4);
+                put(lds.s[33][w - 4][0], X, 8, 12);
+            } else {
+                put(lds.s[34][w - 6][0], X, 0, 8);
+            }
         }
         wg_sync();
-    });
-    {
-        const int last = n_chunks - 1;
-        output(last & 1 ? out_source(1) : out_source(0), tok_begin + C * last);
+
+        fresh_lane();
+        const bool mine = tok0 + QT * qt < tok_end;   // (uniform) this wave has queries
+        f32x16 Y[2];
+        float den = 0.f;
+        if (mine) {
+            role_guard();
+            bf16x8 qop[2];   // contraction slots (jj, i): element 16 h + 8 jj + 4 g + i
+#pragma unroll
+            for (int h = 0; h < 2; ++h) qop[h] = as_bf16x8(u32x4{qraw[4 * h][0], qraw[4 * h][1], qraw[4 * h + 2][0], qraw[4 * h + 2][1]});
+            // ---- intra: 2 P^T = 1 + (1 + A^T)^2, masked in the queries' own tile; 2 Y^T = V^T 2 P^T
+            zero16(Y[0]);
+            zero16(Y[1]);
+            if (w >= 4) __builtin_amdgcn_s_setprio(2);   // (these waves have the most key tiles)
+            const int k_row = n * DP + 4 * g, k_sw = (n >> 2) & 3;
+            const uint16_t *kr = &lds.k[0][0] + k_row;
+            const uint16_t *v0 = &lds.kv.v[0][0] + v_place(4), *v1 = &lds.kv.v[0][0] + (v_place(4) ^ 32);
+            u32x2 ko[4];
+            bf16x8 va[2][2];
+            auto load_k = [&](int kt) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) ko[c] = *reinterpret_cast<const u32x2 *>(kr + QT * DP * kt + 8 * (c ^ k_sw));
+            };
+            auto load_v = [&](int kt) {
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) {
+                    va[sl][0] = read_v(v0 + COLS * (QT * kt + 16 * sl), 8);
+                    va[sl][1] = read_v(v1 + COLS * (QT * kt + 16 * sl), 8);
+                }
+            };
+            auto scores = [&](f32x16 &P) {   // 1 + A^T
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) P[rr] = 1.f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    P = mfma(as_bf16x8(u32x4{ko[2 * h][0], ko[2 * h][1], ko[2 * h + 1][0], ko[2 * h + 1][1]}), qop[h], P);
+            };
+            auto multiply = [&](f32x16 &P, bool own) {
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) P[rr] = fmaf(P[rr], P[rr], 1.f);
+                if (own) {
+#pragma unroll
+                    for (int rr = 0; rr < 16; ++rr) P[rr] = 8 * (rr >> 2) + (rr & 3) <= n - 4 * g ? P[rr] : 0.f;
+                }
+                float cs[2] = {0.f, 0.f};
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) cs[rr & 1] += P[rr];
+                den += cs[0] + cs[1];
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) {
+                    float pr[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pr[e] = P[8 * sl + e];
+                    const bf16x8 op = pack8(pr);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) Y[c] = mfma(va[sl][c], op, Y[c]);
+                }
+            };
+            // (a tile's scores are under way while the one before is multiplied with its values)
+            f32x16 P0, P1;
+            load_k(0);
+            load_v(0);
+            scores(P0);
+            load_k(min(1, qt));
+            int kt = 0;
+#pragma unroll 1
+            for (; kt + 2 <= qt; kt += 2) {
+                auto step = [&](f32x16 &now, f32x16 &next, int kt) {
+                    scores(next);
+                    load_k(min(kt + 2, qt));
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(now, false);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_v(kt + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                step(P0, P1, kt);
+                step(P1, P0, kt + 1);
+            }
+            if (kt < qt) {
+                scores(P1);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(P0, false);
+                load_v(kt + 1);
+                P0 = P1;
+            }
+            multiply(P0, true);
+            Y[0] *= 0.5f;
+            Y[1] *= 0.5f;
+            den *= 0.5f;
+            if (have_state) {
+                // ---- readout: Y^T += S^T phi(q)
+                float r[2][16];   // r[h][m]: element 16 h + (m + 4 g) % 16
+#pragma unroll
+                for (int b = 0; b < 8; ++b)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        r[b >> 2][4 * (b & 3) + 2 * i] = bf16lo(qraw[b][i]);
+                        r[b >> 2][4 * (b & 3) + 2 * i + 1] = bf16hi(qraw[b][i]);
+                    }
+                // (the state operands are requested AHEAD slabs early; the next slab's phi(q) is built under the matrix instructions)
+                constexpr int AHEAD = 4;
+                const __attribute__((address_space(3))) bf16x8 *sp[2];   // (an LDS offset reaches 64 KB)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    sp[i] = (const __attribute__((address_space(3))) bf16x8 *)&lds.s[18 * i][0][lane][0];
+                    asm volatile("" : "+v"(sp[i]));
+                }
+                bf16x8 ring[AHEAD][2];
+                auto request = [&](int s) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) ring[s % AHEAD][c] = sp[s / 18][(2 * (s % 18) + c) * 64];
+                };
+                auto phi = [&](int s) {   // k-slot (jj, i) = row 16 h + 8 jj + 4 g + i of tile T
+                    const int T = s >> 1, h = s & 1;
+                    if (T == 16) return qop[h];
+                    float pr[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int m = 8 * (e >> 2) + (e & 3);
+                        if (T < 16) {
+                            const int to = partner(T, 16 * h + m);
+                            pr[e] = (T == 0 ? 0.5f * r[h][m] : r[h][m]) * r[to >> 4][to & 15];
+                        } else {   // (the slab's rows are those of E2 that count)
+                            pr[e] = r[e >> 2][e & 3] * r[e >> 2][(e & 3) + 8];
+                        }
+                    }
+                    return pack8(pr);
+                };
+#pragma unroll
+                for (int s = 0; s < AHEAD; ++s) request(s);
+                bf16x8 op = phi(0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < SLABS; ++s) {
+                    Y[0] = mfma(ring[s % AHEAD][0], op, Y[0]);
+                    Y[1] = mfma(ring[s % AHEAD][1], op, Y[1]);
+                    if (s + 1 < SLABS) op = phi(s + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (s + AHEAD < SLABS) request(s + AHEAD);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // the constant
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x4 t = *reinterpret_cast<const f32x4 *>(&lds.cst[32 * c + 8 * j + 4 * g]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) Y[c][4 * j + i] += t[i];
+                    }
+                // denominator: T[a][query] = (M q)[a], then sum_a q_a (z1[a] + T[a] / 2)
+                f32x16 T;
+                zero16(T);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) T = mfma(*reinterpret_cast<const bf16x8 *>(lds.m[h][lane]), qop[h], T);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4 t = *reinterpret_cast<const f32x4 *>(&lds.z1[8 * j + 4 * g]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) den = fmaf(r[j >> 1][8 * (j & 1) + i], fmaf(0.5f, T[4 * j + i], t[i]), den);
+                }
+            }
+        }
+        if (more) {   // the next block's rows, on their way during the rest of this one
+            fresh_lane();
+            load_raw(tok0 + BLOCK);
+            load_q(min(tok0 + BLOCK, tok_end - 1));
+        }
+        if (mine) {
+            role_guard();
+            // ---- outputs: the halves of a wave exchange quads, 16 bytes a lane
+            const auto d = __builtin_amdgcn_permlane32_swap(__float_as_uint(den), __float_as_uint(den), false, false);
+            const float before = have_state ? z0 + (float)tok0 : 0.f;   // tokens in the state
+            const float inv = numerator_only ? 1.f : 1.f / (before + (__uint_as_float(d[0]) + __uint_as_float(d[1])));
+            const int tok = QT * qt + n;
+            uint16_t *yb = yu + (size_t)tok0 * dv + (uint32_t)(tok * dv + 8 * g);
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; j += 2) {
+                    uint32_t p[2][2];
+#pragma unroll
+                    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            p[jj][i] = pack2(Y[c][4 * (j + jj) + 2 * i] * inv, Y[c][4 * (j + jj) + 2 * i + 1] * inv);
+                    const auto x = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+                    const auto z = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+                    if (tok0 + tok < tok_end) *reinterpret_cast<u32x4 *>(yb + 32 * c + 8 * j) = u32x4{x[0], z[0], x[1], z[1]};
+                }
+        }
+        // ---- update
+        __builtin_amdgcn_s_setprio(0);
+        if (more || (Su && seg == G - 1)) update(lds.kv, slabs_of(tok0));
+        have_state = true;
+        wg_sync();
     }
     if (Su && seg == G - 1) {
         fresh_lane();
         export_state();
     }
+    }
 }
 
-// Segments: at most one round of the chip (one workgroup per CU).  With few units the chain of an increment, up to G - 1 entries
-// to sum and the main pass is shortest near sqrt(1.5 chunks) segments (16 units, N 2048: 4 segments 57.1 us, 8 41.1, 10 38.8, 16 43.9; N 777:
-// 1 59.6, 3 36.2, 6 28.6, 12 34.0; N 256 1 24.7, 3 19.7).  The more groups, the fewer segments there is room for and the more entries move at a
-// time, so the longer a sequence has to be, the more so from a state (1 segment and what there is room for, us: 48 groups N 256 26.1, 22.7; 64
-// groups N 256 26.3, 26.4, from a state 32.0, 33.2, N 320 30.4, 26.9; 80 groups N 256 26.6, 25.2, from a state 32.8, 35.0, N 320 30.6, 27.9; 86
-// groups N 448 39.0, 35.7; 100 groups N 384 35.1, 34.1, from a state 41.8, 44.4, N 512 43.2, 39.3; 128 groups N 448 39.7, 38.3, from a state 47.3,
-// 49.5, N 512 43.8, 41.0).
+// Segments: at most one round of the chip (one workgroup per CU).  With few units the chain of an increment, up to G - 1 entries to sum and
+// the main pass is shortest at segments of about 5 tiles of 32 tokens, from some 10 segments on of more (16 units, us: N 777 3 segments 32.5,
+// 4 28.4, 5 30.4; N 1024 4 33.7, 6 32.2, 8 34.9; N 2048 6 39.4, 8 40.8, 10 39.3, 16 48.7; N 4096 8 56.9, 10 48.3, 16 51.6; N 16384 10 119.7, 16
+// 103.1).  With more units there is room for fewer, and one block after the other is the shorter chain for longer (1 segment and what there is room
+// for: 16 units N 512 25.6, 26.1; 32 units N 512 26.3, 28.9, N 1024 45, 34; 64 units N 512 27.9, 32.9, N 1024 47.8, 40.4; 96 units N 2048 86.6, 80.2; 128 units N
+// 1024 48.6, 54.2, N 4096 178, 156).
 static int pick_segments(int U, int N, int dv)
 {
-    const int groups = U * (dv / COLS), chunks = (N + C - 1) / C, room = 256 / groups;
-    if (chunks < (room >= 5 ? 8 : room >= 3 ? 10 : 16)) return 1;
-    int G = room;
-    const int chain = (int)(sqrtf(1.5f * chunks) + 0.5f);
-    if (G > chain) G = chain;
+    const int groups = U * (dv / COLS), tiles = (N + QT - 1) / QT, room = 256 / groups;
+    if (tiles < (room >= 4 ? 17 : room >= 3 ? 28 : 56)) return 1;
+    const int chain = (int)(sqrtf((float)tiles) + 0.5f), longest = chain > 10 ? chain : 10;
+    int G = 3 * tiles / 16;
+    if (G > longest) G = longest;
+    if (G > room) G = room;
     if (G > kMaxSegments) G = kMaxSegments;
     return G < 1 ? 1 : G;
 }
@@ -786,29 +845,30 @@ static int local_groups(int groups, int G)
     return most * G <= 32 ? most * 8 : groups / 8 * 8;
 }
 
-// Segment g's main pass starts by summing g entries, which takes about as long as 0.75 chunks each, and the last one writes the state: the later a
-// segment, the shorter.  (Equal ones and these, us: 32 units of 16384 tokens 211.3, 208.9, of 4096 73.5, 67.3; 16 units of 8192 84.2, 74.6, of
-// 2048 46.1, 39.6, of 777 33.2, 30.2; 60 units of 512 34.9, 31.3; d_v 128: 8 units of 4096 60.8, 52.1.  A whole chunk each: 210, 66.6, 77.5,
-// 42.7, 30.6, 31.5, 56.6.)
+// Segment g's main pass starts by summing g entries, which takes about as long as 0.75 tiles each, and the last one writes the state (1.5
+// tiles): the later a segment, the shorter, but none longer than the blocks that the average takes.  (The last one as long as the rest, and these, us: 16 units
+// of 1024 tokens 32.2, 31.2; 32 units 34.4, 33.4.)
 static int make_segments(int N, int G, SegTable &t)
 {
-    const int T = (N + C - 1) / C;
+    const int T = (N + QT - 1) / QT;
     if (G > T) G = T;
+    const int most = (T + NW * G - 1) / (NW * G) * NW;
     int len[kMaxSegments], sum = 0;
     for (int g = 0; g < G; ++g) {
-        const float off = 0.75f * (0.5f * (G - 1) - g) - (g == G - 1 && G > 1 ? 0.5f : 0.f);
+        const float off = 0.75f * (0.5f * (G - 1) - g) - (g == G - 1 && G > 1 ? 1.5f : 0.f);
         len[g] = T / G + (int)(off >= 0.f ? off + 0.5f : off - 0.5f);
         if (len[g] < 1) len[g] = 1;
+        if (len[g] > most) len[g] = most;
         sum += len[g];
     }
-    // the rounding's remainder is handed to (or taken from) the early segments, one chunk at a time
+    // the rounding's remainder is handed to (or taken from) the early segments, one tile at a time
     for (int g = 0; sum != T; g = (g + 1) % G) {
-        if (sum < T) { ++len[g]; ++sum; }
-        else if (len[g] > 1) { --len[g]; --sum; }
+        if (sum < T && len[g] < most) { ++len[g]; ++sum; }
+        else if (sum > T && len[g] > 1) { --len[g]; --sum; }
     }
     int pos = 0;
-    for (int g = 0; g < G; ++g) { t.begin[g] = pos * C; pos += len[g]; }
-    for (int g = G; g <= kMaxSegments; ++g) t.begin[g] = pos * C;
+    for (int g = 0; g < G; ++g) { t.begin[g] = pos * QT; pos += len[g]; }
+    for (int g = G; g <= kMaxSegments; ++g) t.begin[g] = pos * QT;
     return G;
 }
 
@@ -824,17 +884,22 @@ bool prefill_mfma32_supported(int dp, int dv, int dtype)
     return dtype == BASED_BF16 && dp == dp32::DP && (dv == 64 || dv == 128);
 }
 
-// Workspace: one entry per (unit, slice, segment).
+// Workspace: one entry per (unit, slice, segment).  (Which kernel takes a call may depend on whether there is a state to start from.)
 size_t prefill_mfma32_workspace_bytes(int U, int N, int dp, int dv)
 {
     (void)dp;
-    return (dp32::entry_bytes(U, N, dv) + 255) / 256 * 256;
+    const size_t a = dp32::entry_bytes(U, N, dv);
+    if (!prefill_mfma32_short_takes(U, N, dv, 1)) return (a + 255) / 256 * 256;
+    const size_t b = prefill_mfma32_short_workspace_bytes(U, N, dv);
+    return ((a > b ? a : b) + 255) / 256 * 256;
 }
 
 hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, void *y, float *state,
                                  int has_init, int packed_state, void *workspace, int U, int N, int dp, int dv,
                                  hipStream_t s)
 {
+    if (prefill_mfma32_short_takes(U, N, dv, has_init & 1))
+        return launch_prefill_mfma32_short(q, k, v, y, state, has_init, packed_state, workspace, U, N, dv, s);
     // the kernels' flag word (has_init arrives with bit 2 set for numerator-only outputs)
     has_init = (has_init & 1) | (packed_state ? 2 : 0) | (has_init & 4);
     using namespace dp32;

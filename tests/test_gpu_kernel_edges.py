@@ -258,6 +258,59 @@ def test_prefill_dp32_edges(based, packed, U, dv, N1, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
+# bf16 d' = 32 prefill in blocks of 256 tokens: a tile of 32 queries and a block with remainders, blocks with one to eight tiles, calls on either side of
+# the lines to the kernel of short calls, segments shorter and longer than a block, both widths, more workgroups than the chip holds; without and from a
+# state (the second call)
+@pytest.mark.parametrize("numerator", [False, True])
+@pytest.mark.parametrize("U,dv,N1,N", [(3, 64, 33, 130), (3, 64, 97, 194), (2, 128, 255, 512), (3, 64, 256, 513), (66, 64, 257, 290), (21, 64, 512, 525),
+                                       (2, 64, 737, 1505), (65, 64, 100, 700), (3, 128, 1030, 1130), (2, 64, 96, 3400), (5, 64, 200, 4500), (270, 64, 300, 420)])
+def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    state = based.alloc_state(1, U, 32, dv)
+    got = [down(based.prefill(*(up(a[:, lo:hi], "bf16", (1, U, hi - lo, d)) for a, d in ((q, 32), (k, 32), (v, dv))), state=state,
+                              has_init=lo > 0, numerator_only=numerator)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N))]
+    at = np.unique([0, U // 2, U - 1])
+    want = oracle.linattn_numerator(q[at], k[at], v[at]) if numerator else oracle.linattn_quadratic(q[at], k[at], v[at])
+    check_close(rows(np.concatenate(got, 1)[at]), rows(want), TOL["bf16"], "y")
+    S, z = based.state_export(state, 1, U, 32, dv)
+    Sw, zw = oracle.linattn_state(k[at], v[at])
+    check_close(down(S)[0, at], Sw, TOL["bf16"], "S")
+    check_close(down(z)[0, at], zw, TOL["bf16"], "z")
+
+
+# bf16 d' = 32 prefill from a state that is not symmetric in a pair's two rows (its mean counts) and holds an infinite row: every other entry is finite,
+# and the infinite ones reach the outputs
+@pytest.mark.parametrize("N", [64, 300, 2000])
+def test_prefill_dp32_odd_state(based, N):
+    dp, dv, U, D = 32, 64, 3, 1057
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": dp})
+    q, k, v = synth.linattn_inputs(wl, units=U, N=N)
+    S0, z0 = synth.normal(5, (U, D, dv), 0.1), np.abs(synth.normal(6, (U, D), 0.1))
+    z0[:, 0] = 50.0   # (tokens)
+    state = based.alloc_state(1, U, dp, dv)
+    sym = lambda a: np.concatenate([a[:, :1 + dp], (lambda m: (m + m.swapaxes(1, 2)) / 2)(a[:, 1 + dp:].reshape(U, dp, dp, -1)).reshape(U, dp * dp, -1)], 1)
+    Sm, zm = sym(S0), sym(z0[..., None])[..., 0]
+    phi = lambda x: np.concatenate([np.ones((U, N, 1)), x, (x[..., :, None] * x[..., None, :]).reshape(U, N, dp * dp) / 2 ** 0.5], -1)
+    pq, pk = phi(q.astype(np.float64)), phi(k.astype(np.float64))
+    w = np.tril(pq @ pk.swapaxes(1, 2))
+    want = (pq @ Sm + w @ v) / ((pq @ zm[..., None])[..., 0] + w.sum(-1))[..., None]
+    dev = [up(a, "bf16", (1, U, N, d)) for a, d in ((q, dp), (k, dp), (v, dv))]
+    based.state_import(state, up(S0, "f32", (1, U, D, dv)), up(z0, "f32", (1, U, D)), dp)
+    y = down(based.prefill(*dev, state=state, has_init=True)).reshape(U, N, dv)
+    check_close(rows(y), rows(want), TOL["bf16"], "y")
+    S, z = (down(a).reshape(U, D, -1) for a in based.state_export(state, 1, U, dp, dv))
+    check_close(S, Sm + pk.swapaxes(1, 2) @ v, TOL["bf16"], "S")
+    check_close(z[..., 0], zm + pk.sum(1), TOL["bf16"], "z")
+    S0[1, 1 + 3, 7] = np.inf   # a linear row
+    based.state_import(state, up(S0, "f32", (1, U, D, dv)), up(z0, "f32", (1, U, D)), dp)
+    y = down(based.prefill(*dev, state=state, has_init=True)).reshape(U, N, dv)
+    bad = ~np.isfinite(y)
+    assert bad[1, :, 7].all() and bad.sum() == N
+    S = down(based.state_export(state, 1, U, dp, dv)[0]).reshape(U, D, dv)
+    assert np.isposinf(S[1, 1 + 3, 7]) and (~np.isfinite(S)).sum() == 1
+
+
 # convolution gate: runs of 2, 8 and 32 tokens (the last for a state updated in place and for the longest sequences), a last run that is
 # not full, sequences shorter than the filter
 @pytest.mark.parametrize("dtype,B,N,Dc,in_place", [("bf16", 2, 1, 64, False), ("bf16", 3, 2, 72, False), ("f32", 3, 5, 12, False), ("bf16", 5, 9, 264, False),
