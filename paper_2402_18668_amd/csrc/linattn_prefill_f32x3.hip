@@ -25,7 +25,9 @@
 // outputs and denominators of a chunk meet in LDS.  K-state: fp32 sums of the features a lane builds.
 // Two barriers a chunk: rows staged, partial outputs free | partial outputs written, rows free.
 //
-// Segments as in linattn_prefill_f32.h: an increment launch, then the main launch, each segment from the sum of the entries before it.
+// Segments as in linattn_prefill_f32.h: an increment launch, then the main launch, each segment from the sum of the entries before it.  The G - 1
+// increments of a unit would leave a part of the chip idle, so without decay G workgroups share their tokens evenly (inc_len each): one whose share
+// goes on past the end of a segment leaves an entry there and starts anew.
 //
 // Decay: as there, in a variant of its own.  The factors are powers of the rate from a table in LDS: on the features of the update,
 // the old state, the state's part of the outputs and P.
@@ -201,19 +203,22 @@ struct DecayArg {
 // The launch covers `slices` slices of 64 columns from first_slice on.  has_init: bit 0 an initial state is given, bit 2 the outputs are
 // the numerators alone.  INC: state increment of the segment only, to entry 1 + seg (segment 0 also converts the caller's state
 // into entry 0).
-template <int DV, bool INC, bool DECAY>
+// SHARED: the increments are shared out over `shares` workgroups of inc_len tokens (else one to a segment).
+template <int DV, bool INC, bool DECAY, bool SHARED>
 __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict__ q, const float *__restrict__ k,
                                                         const float *__restrict__ v, float *__restrict__ y, float *state, int has_init,
-                                                        int N, float *ws, int seg_len, int G, int first_slice, int slices, DecayArg dec)
+                                                        int N, float *ws, int seg_len, int inc_len, int shares, int G, int slots, int first_slice, int slices,
+                                                        DecayArg dec)
 {
     constexpr int SL = DV / COLS;
     __shared__ __align__(16) Lds<INC> lds;
     const bool numerator_only = (has_init & 4) != 0, init = (has_init & 1) != 0;
-    const int gseg = INC ? G - 1 : G;
+    static_assert(!(DECAY && SHARED), "an entry is scaled by the decay of a whole segment");
+    const int gseg = !INC ? G : SHARED ? shares : G - 1;
     const int seg = blockIdx.x % gseg, us = blockIdx.x / gseg, u = us / slices, slice = first_slice + us % slices, col0 = slice * COLS;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63, g = lane >> 5, n = lane & 31;
-    const int begin = seg * seg_len, end = min(N, begin + seg_len), chunks = (end - begin + C - 1) / C;
+    const int len = INC && SHARED ? inc_len : seg_len, begin = seg * len, end = min(INC && SHARED ? (G - 1) * seg_len : N, begin + len), chunks = (end - begin + C - 1) / C;
     // Six of the eight waves have matrix work, five of them a tile, and consecutive waves sit on SIMDs 0, 2, 1, 3, 0, .. from any of them on.
     // The roles are dealt out from the first wave's SIMD, and from two places further in the workgroup whose LDS does not start at 0:
     // the two workgroups on a CU then put two or three tiles on every SIMD.  (Any turn gives the same result.)
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     float *yu = y + (size_t)u * N * DV + col0;
     float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 : nullptr;
     float *zu = state ? state + (size_t)u * state_stride(DP, DV) + (size_t)D * DV : nullptr;
-    float *entries = ws ? ws + ((size_t)u * SL + slice) * G * kEntryFloats : nullptr;
+    float *entries = ws ? ws + ((size_t)u * SL + slice) * slots * kEntryFloats : nullptr;
 
     const float gm = DECAY && dec.gamma ? dec.gamma[u % dec.H] : 1.f;
     const float *gate = DECAY && dec.gate ? dec.gate + (size_t)(u / dec.H) * N * dec.H + u % dec.H : nullptr;
@@ -316,6 +321,9 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     };
     auto entry_s = [&](int e) { return entries + (size_t)e * kEntryFloats + (size_t)w * 2048 + 4 * lane; };
     auto entry_z = [&](int e) { return entries + (size_t)e * kEntryFloats + ROWS * COLS + 32 * w + n; };
+    // of the tokens that share i of the increments has in segment k (entry 0: the caller's state, if any).  In order without a gap: the launcher's
+    // shares end with no segment but the last one.
+    auto entry_at = [&](int i, int k) { return init + k + (SHARED ? i : 0); };
     auto store_entry = [&](int e) {
         if (!tile) return;
         float *p = entry_s(e);
@@ -339,10 +347,11 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     } else if (G > 1) {
         if (tile) {
             // the sum of the entries before the segment, two at a time
-            int e = init ? 0 : 1;
+            int e = 0;
+            const int count = init + seg + (SHARED && seg > 0 ? (seg * seg_len - 1) / inc_len : 0);
             const float g_seg = DECAY ? powf(gm, (float)seg_len) : 1.f;
-            auto add = [&](auto count) {
-                constexpr int E = decltype(count)::value;
+            auto add = [&](auto of) {
+                constexpr int E = decltype(of)::value;
                 f32x4 x[E][8];
                 float xz[E];
                 for_n<E>([&](auto i) {
@@ -360,8 +369,8 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
                 });
                 e += E;
             };
-            if ((seg + 1 - e) & 1) add(std::integral_constant<int, 1>{});
-            while (e <= seg) add(std::integral_constant<int, 2>{});
+            if (count & 1) add(std::integral_constant<int, 1>{});
+            while (e < count) add(std::integral_constant<int, 2>{});
         }
     } else if (init) {
         import_state();
@@ -560,16 +569,24 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
         };
         if (tile) {
             role_guard();
+            int k = begin / seg_len, boundary = (k + 1) * seg_len;   // (SHARED)
             for (int t = 0; t < chunks; ++t) {
                 fresh_lane();
                 if (__builtin_expect(is_wide(t), 0)) update(lds.rows[t & 1], t, std::true_type{});
                 else update(lds.rows[t & 1], t, std::false_type{});
+                const int next = begin + C * (t + 1);
+                if (SHARED && next == boundary && next < end) {
+                    store_entry(entry_at(seg, k++));
+                    boundary += seg_len;
+                    for_n<32>([&](auto r) { S[r.value / 16][r.value % 16] = 0.f; });
+                    z = 0.f;
+                }
                 next_chunk(t);
             }
         } else {
             for (int t = 0; t < chunks; ++t) next_chunk(t);
         }
-        store_entry(1 + seg);
+        store_entry(entry_at(seg, SHARED ? (end - 1) / seg_len : seg));
         return;
     }
     Rows &rows = lds.rows[0];
@@ -754,12 +771,35 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     while (G > 1 && (G - 1) * len >= N) --G;   // rounding the length up can empty trailing segments
     if ((long long)U * SL * G >= (1ll << 31)) return hipErrorInvalidValue;
     // (the workspace is sized for the fp32 matrix kernel, which has at least as many segments and entries of this size)
-    if (G > 1 && (size_t)U * SL * G * kEntryFloats * sizeof(float) > prefill_f32_workspace_bytes(U, N, DP, DV)) return hipErrorInvalidValue;
+    const size_t room = prefill_f32_workspace_bytes(U, N, DP, DV) / (sizeof(float) * kEntryFloats * U * SL);   // entries
+    if (G > 1 && (size_t)G > room) return hipErrorInvalidValue;
+    // Shares of the increments: G, where what would be idle is worth the entries that come on top, which take time to write and to sum: two or three
+    // segments of 320 tokens or more, four of 1024 (more segments leave little idle), and where the workspace holds two entries a segment.
+    // (us, G - 1 shares and G: 200 units of 512 tokens 70.6, 70.5, of 768 97.1, 94.0, of 2048 235, 219; 180 of 640 83.0, 81.1; 256 of 512 73.9,
+    // 74.4; 160 of 512 57.6, 56.1, of 2048 175, 165; 150 of 448 50.3, 52.2; 128 of 512 52.8, 59.5, of 2048 160, 162, of 4096, 110 units, 256.6,
+    // 251.6, of 8192, 106 units, 492, 473; d_v 128: 100 of 2048 232, 216.)
+    int inc_len = len, entries = G;
+    const int share = ((G - 1) * (len / C) + G - 1) / G * C, share_entries = 2 * (G - 1) + (has_init & 1);
+    bool shared = !DECAY && G > 1 && G <= 4 && len >= (G < 4 ? 320 : 1024) && (size_t)share_entries <= room;
+    for (int i = 1; shared && i < G; ++i) shared = i * share % len != 0 || i * share >= (G - 1) * len;   // no share ends with a segment but the last
+    if (shared) {
+        inc_len = share;
+        entries = share_entries;
+    }
+    const int shares = ((G - 1) * len + inc_len - 1) / inc_len;
     float *ws = static_cast<float *>(workspace);
     auto go = [&](auto increment, int first_slice, int slices) {
         constexpr bool INC = decltype(increment)::value;
-        hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY>), dim3((unsigned)(U * slices * (INC ? G - 1 : G))), dim3(NT), 0, s, (const float *)q,
-                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, G, first_slice, slices, dec);
+        if constexpr (!DECAY) {
+            if (shared) {
+                hipLaunchKernelGGL((prefill_kernel<DV, INC, false, true>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
+                                   (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice,
+                                   slices, dec);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY, false>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
+                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;

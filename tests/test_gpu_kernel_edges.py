@@ -258,6 +258,28 @@ def test_prefill_dp32_edges(based, packed, U, dv, N1, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
+# fp32 d' = 16 prefill of two to four segments, whose increments are shared out evenly over as many workgroups: segments on either side of the shortest that
+# are, shares that end inside a segment and with it, a last one that is shorter, a workspace with room for two entries a segment and without; from a state too
+@pytest.mark.parametrize("U,dv,N,init", [(171, 64, 639, False), (171, 64, 641, False), (256, 64, 700, True), (65, 128, 1025, False), (129, 64, 961, True),
+                                         (160, 64, 1500, True), (85, 128, 800, False), (103, 64, 4090, True), (128, 64, 4097, False), (60, 128, 4100, True)])
+def test_prefill_fp32_shared_increments(based, U, dv, N, init):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "dtype": "f32"})
+    few = min(U, 6)   # (the others have the same values again)
+    N1 = 37 if init else 0
+    q, k, v = synth.linattn_inputs(wl, units=few, N=N1 + N)
+    state, at = based.alloc_state(1, U, 16, dv), np.arange(U) % few
+    got = [down(based.prefill(*(up(a[at, lo:hi], "f32", (1, U, hi - lo, d)) for a, d in ((q, 16), (k, 16), (v, dv))), state=state,
+                              has_init=lo > 0)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N1 + N)) if hi > lo]
+    y = np.concatenate(got, 1)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, 16, dv))
+    for a in (y, S, z):
+        assert (a == a[at]).all()
+    check_close(rows(y[:few]), rows(oracle.linattn_quadratic(q, k, v)), TOL["f32"], "y")
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(S[:few], Sw, TOL["f32"], "S")
+    check_close(z[:few], zw, TOL["f32"], "z")
+
+
 # bf16 d' = 32 prefill in blocks of 256 tokens: a tile of 32 queries and a block with remainders, blocks with one to eight tiles, calls on either side of
 # the lines to the kernel of short calls, segments shorter and longer than a block, both widths, more workgroups than the chip holds; without and from a
 # state (the second call)
