@@ -168,15 +168,16 @@ __device__ __forceinline__ bool is_pair(CanonRows c) { return c.r1 > DP; }
 constexpr int kMaxSegments = 16;
 struct SegTable { int begin[kMaxSegments + 1]; };
 
-// INC: state increment of the segment only, to workspace entry 1 + seg; segment 0 starts from the caller's state, if any,
-// and also leaves that, converted, in entry 0 (import_only: nothing else).  Otherwise the full prefill of the segment.
+// INC: state increment of piece `seg` of segs only (G - 1 of them, `pieces` to a segment), to workspace entry first_entry + seg; piece 0 starts from the
+// caller's state, if any, and also leaves that, converted, in entry 0 (import_only: nothing else).  Otherwise the full prefill of the segment, from
+// the sum of the entries of the pieces before it.  A group has `slots` entries.
 // init_in_entry: the caller's state is in entry 0 (one workgroup per unit reads it from the buffer itself).
 // Slice: columns [64 slice, 64 slice + 64) of v / y.
 template <bool INC>
 __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     uint16_t *__restrict__ y, float *state, int has_init, int import_only, int init_in_entry, float *__restrict__ ws,
-    int N, int dv, SegTable segs, int G, int groups, int local)
+    int N, int dv, SegTable segs, int G, int pieces, int first_entry, int slots, int groups, int local)
 {
     __shared__ __align__(16) std::conditional_t<INC, LdsInc, Lds> lds;
 
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
     float *Su = state ? state + (size_t)u * (packed_state ? packed_state_stride(DP, dv) : state_stride(DP, dv)) + col0
                       : nullptr;
     float *zu = Su ? Su - col0 + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * dv : nullptr;
-    float *ws_unit = ws + ((size_t)(u * slices + slice) * G) * kWsEntryFloats;
+    float *ws_unit = ws + ((size_t)(u * slices + slice) * slots) * kWsEntryFloats;
 
     // ---- accumulators -------------------------------------------------------------------------
     f32x16 S[2][2];   // [column tile ^ (w % 2)][tile 2 w + tt]
@@ -410,7 +411,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
         }
     } else if (seg > 0) {
 #pragma unroll 1
-        for (int p = 1; p <= seg; ++p) add_entry(p);
+        for (int p = 0; p < seg * pieces; ++p) add_entry(first_entry + p);
     } else if (has_init) {
         if (init_in_entry) add_entry(0);
         else import_state();
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             wg_sync();
             update(lds.kv[gen], slabs_of(tok0));
         }
-        put_entry(1 + seg);
+        put_entry(first_entry + seg);
         return;
     } else {
     // ---- full pass ----------------------------------------------------------------------------------
@@ -821,11 +822,13 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 // 4 28.4, 5 30.4; N 1024 4 33.7, 6 32.2, 8 34.9; N 2048 6 39.4, 8 40.8, 10 39.3, 16 48.7; N 4096 8 56.9, 10 48.3, 16 51.6; N 16384 10 119.7, 16
 // 103.1).  With more units there is room for fewer, and one block after the other is the shorter chain for longer (1 segment and what there is room
 // for: 16 units N 512 25.6, 26.1; 32 units N 512 26.3, 28.9, N 1024 45, 34; 64 units N 512 27.9, 32.9, N 1024 47.8, 40.4; 96 units N 2048 86.6, 80.2; 128 units N
-// 1024 48.6, 54.2, N 4096 178, 156).
-static int pick_segments(int U, int N, int dv)
+// 1024 48.6, 54.2, N 4096 178, 156).  Two segments whose increment two workgroups share (without a state) are the shorter chain from 41 tiles on with up to 104 groups
+// (one and two: 87 units N 1000 47.4, 47.7, N 1400 63.4, 58.3, N 1664 73.0, 64.5; 100 units N 1280 57.3, 57.8, N 1400 63.7, 60.8, N 1664 73.4, 67.6; 128
+// units N 1400 64.1, 67.3, N 1664 73.7, 76.0).
+static int pick_segments(int U, int N, int dv, int has_init)
 {
     const int groups = U * (dv / COLS), tiles = (N + QT - 1) / QT, room = 256 / groups;
-    if (tiles < (room >= 4 ? 17 : room >= 3 ? 28 : 56)) return 1;
+    if (tiles < (room >= 4 ? 17 : room >= 3 ? 28 : groups <= 104 && !has_init ? 41 : 56)) return 1;
     const int chain = (int)(sqrtf((float)tiles) + 0.5f), longest = chain > 10 ? chain : 10;
     int G = 3 * tiles / 16;
     if (G > longest) G = longest;
@@ -872,9 +875,19 @@ static int make_segments(int N, int G, SegTable &t)
     return G;
 }
 
+// The first segment in two pieces of whole blocks, as many in the second.
+static SegTable halves(const SegTable &t)
+{
+    SegTable o = t;
+    const int tiles = t.begin[1] / QT, half = ((tiles + 1) / 2 + NW - 1) / NW * NW;
+    o.begin[1] = (half < tiles ? half : tiles - 1) * QT;
+    for (int g = 2; g <= kMaxSegments; ++g) o.begin[g] = t.begin[1];
+    return o;
+}
+
 static size_t entry_bytes(int U, int N, int dv)
 {
-    return (size_t)U * (dv / COLS) * pick_segments(U, N, dv) * kWsEntryFloats * sizeof(float);
+    return (size_t)U * (dv / COLS) * pick_segments(U, N, dv, 0) * kWsEntryFloats * sizeof(float);   // (never more of them from a state)
 }
 
 }  // namespace dp32
@@ -906,7 +919,7 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
     (void)dp;
     const int slices = dv / COLS;
     SegTable segs;
-    const int G = make_segments(N, pick_segments(U, N, dv), segs);
+    const int G = make_segments(N, pick_segments(U, N, dv, has_init & 1), segs);
     const uint16_t *q16 = (const uint16_t *)q, *k16 = (const uint16_t *)k, *v16 = (const uint16_t *)v;
     float *ws = static_cast<float *>(workspace);
     const int groups = U * slices, local = local_groups(groups, G), blocks = local > groups ? local : groups;
@@ -914,15 +927,23 @@ hipError_t launch_prefill_mfma32(const void *q, const void *k, const void *v, vo
     // Several workgroups of a unit read the caller's state and one overwrites it (at d_v = 128 also its K-state): then it goes
     // through entry 0, which the first launch writes.
     const int in_entry = (has_init & 1) && G * slices > 1;
+    // The increment of the first of two segments would leave half of the chip idle: two workgroups halve it where entry 0 is free for the second's.  (us,
+    // one and two: 128 units N 2048 82.5, 80.5, N 4096 147, 140; 100 units N 2048 76.5, 72.8, N 4096 134.6, 121.9; 88 units N 8192 260, 229; d_v 128, 48 units
+    // N 4096 132.5, 119.1.)
+    const int pieces = G == 2 && (has_init & 1) == 0 && groups <= 128 ? 2 : 1, first_entry = pieces == 2 ? 0 : 1;
+    auto go = [&](auto increment, const SegTable &table, int g, int workgroups) {
+        hipLaunchKernelGGL((prefill_kernel<decltype(increment)::value>), dim3((unsigned)(blocks * workgroups)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
+                           state, has_init, decltype(increment)::value && G == 1, in_entry, ws, N, dv, table, g, pieces, first_entry, G, groups, local);
+        return hipGetLastError();
+    };
     if (G > 1 || in_entry) {
-        hipLaunchKernelGGL((prefill_kernel<true>), dim3((unsigned)(blocks * (G > 1 ? G - 1 : 1))), dim3(NT), 0, s, q16, k16,
-                           v16, (uint16_t *)y, state, has_init, G > 1 ? 0 : 1, in_entry, ws, N, dv, segs, G, groups, local);
-        const hipError_t e = hipGetLastError();
+        SegTable inc = segs;
+        if (pieces == 2) inc = halves(segs);
+        const int n = G > 1 ? (G - 1) * pieces : 1;
+        const hipError_t e = go(std::true_type{}, inc, n + 1, n);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((prefill_kernel<false>), dim3((unsigned)(blocks * G)), dim3(NT), 0, s, q16, k16, v16, (uint16_t *)y,
-                       state, has_init, 0, in_entry, ws, N, dv, segs, G, groups, local);
-    return hipGetLastError();
+    return go(std::false_type{}, segs, G, G);
 }
 
 }  // namespace based

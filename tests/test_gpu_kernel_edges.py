@@ -285,7 +285,7 @@ def test_prefill_fp32_shared_increments(based, U, dv, N, init):
 # state (the second call)
 @pytest.mark.parametrize("numerator", [False, True])
 @pytest.mark.parametrize("U,dv,N1,N", [(3, 64, 33, 130), (3, 64, 97, 194), (2, 128, 255, 512), (3, 64, 256, 513), (66, 64, 257, 290), (21, 64, 512, 525),
-                                       (2, 64, 737, 1505), (28, 64, 257, 513), (20, 128, 400, 801), (32, 128, 225, 449), (29, 64, 401, 433), (65, 64, 100, 700), (3, 128, 1030, 1130), (2, 64, 96, 3400), (5, 64, 200, 4500), (270, 64, 300, 420)])
+                                       (2, 64, 737, 1505), (28, 64, 257, 513), (20, 128, 400, 801), (32, 128, 225, 449), (29, 64, 401, 433), (65, 64, 100, 700), (3, 128, 1030, 1130), (2, 64, 96, 3400), (5, 64, 200, 4500), (270, 64, 300, 420), (87, 64, 1281, 2600), (104, 64, 1800, 1900), (64, 128, 2100, 2150)])
 def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
     q, k, v = synth.linattn_inputs(wl, units=U, N=N)
