@@ -128,13 +128,14 @@ template <int DP, typename T> constexpr bool HAS_SEGMENTS = DP != 16 || !std::is
 
 // The launch covers `slices` slices of 64 columns from first_slice on.
 // has_init: bit 0 an initial state is given, bit 2 the outputs are the numerators alone.
-// INCREMENT: state increment of the segment only, written to entry 1 + seg (segment 0 also converts the caller's state
+// A unit's slice has `slots` entries, those of the segment before which a segment starts end with first + seg * pieces - 1.
+// INCREMENT: state increment of the segment (or piece) only, written to entry first + seg (segment 0 also converts the caller's state
 // into entry 0: the main launch overwrites that buffer while other segments may still be starting).
 template <int DP, int DV, typename T, bool INCREMENT>
 __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                            const T *__restrict__ v, T *__restrict__ y, float *state,
-                                                           int has_init, int N, float *ws, int seg_len, int G, int first_slice,
-                                                           int slices, DecayArg dec)
+                                                           int has_init, int N, float *ws, int seg_len, int G, int slots, int first, int pieces,
+                                                           int first_slice, int slices, DecayArg dec)
 {
     constexpr int NB = blocks(DP), NT = tiles(DP), SL = DV / COLS, D = feature_dim(DP);
     constexpr int ZS = (NT + NW - 1) / NW;   // K-state tiles of a wave
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     T *yu = y + (size_t)u * N * DV + col0 + 16 * w;
     float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 : nullptr;
     float *zu = state ? state + (size_t)u * state_stride(DP, DV) + (size_t)D * DV : nullptr;
-    float *entries = ws ? ws + ((size_t)u * SL + slice) * G * entry_floats(DP) : nullptr;
+    float *entries = ws ? ws + ((size_t)u * SL + slice) * slots * entry_floats(DP) : nullptr;
     auto entry_s = [&](int e) { return entries + (size_t)e * entry_floats(DP) + (size_t)w * NT * 256 + 4 * lane; };
     auto entry_z = [&](int e) { return entries + (size_t)e * entry_floats(DP) + (size_t)NW * NT * 256; };
 
@@ -296,7 +297,8 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     } else if (HAS_SEGMENTS<DP, T> && G > 1) {
         // the sum of the entries before the segment (up to 64 of them), some at a time with their loads in flight together
         constexpr int EB = NT <= 3 ? 8 : NT <= 10 ? 4 : 1;
-        int e = init ? 0 : 1;
+        int e = init ? 0 : first;
+        const int last = first + seg * pieces;
         auto add_entries = [&](auto count) {
             constexpr int n_e = decltype(count)::value;
             f32x4 x[n_e][NT];
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
             e += n_e;
         };
         if constexpr (EB == 1) {
-            for (; e <= seg; ++e) {
+            for (; e < last; ++e) {
                 const float *p = entry_s(e), *pz = entry_z(e);
                 for_n<NT>([&](auto t) {
                     S[t.value] = S[t.value] * g_seg + *reinterpret_cast<const f32x4 *>(p + (size_t)t.value * 256);
@@ -322,8 +324,8 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
                 });
             }
         } else {
-            for (int rest = (seg + 1 - e) % EB; rest > 0; --rest) add_entries(std::integral_constant<int, 1>{});
-            while (e <= seg) add_entries(std::integral_constant<int, EB>{});
+            for (int rest = (last - e) % EB; rest > 0; --rest) add_entries(std::integral_constant<int, 1>{});
+            while (e < last) add_entries(std::integral_constant<int, EB>{});
         }
     } else if (init) {
         import_state();
@@ -507,7 +509,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     if (w == 0 && n == 8) z[0] -= (float)(chunks * C - (end - begin));
 
     if (INCREMENT) {
-        store_entry(1 + seg);
+        store_entry(first + seg);
     } else if (state && seg == G - 1) {
         export_state();
     }
@@ -534,15 +536,21 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
 {
     constexpr int SL = DV / COLS;
     int G = HAS_SEGMENTS<DP, T> ? segments(U, N, DP, DV) : 1;
-    const int len = segment_len(N, G);
+    // The increment of the first of two segments is shared by two workgroups where entry 0 is free for the second's: one to a unit's slice left half of
+    // the chip idle.  (us, one and two: d' 32, fp32, 100 units N 200 105, 93, N 512 212, 186, 90 units N 1024 395, 336, d_v 128, 60 units N 700 280, 242; d' 24, bf16,
+    // 200 units N 160 74.0, 67.9, N 512 178, 172, 256 units N 1024 329, 313; d' 8, fp32, 350 units N 1000 110.7, 103.5, but bf16, 400 units N 200 37.1, 39.6, N
+    // 512 74.1, 73.9.)
+    const bool shared = G == 2 && !(has_init & 1) && !dec.gamma && (DP > 8 || N >= 640);
+    const int len = shared ? (segment_len(N, G) + 2 * C - 1) / (2 * C) * (2 * C) : segment_len(N, G);
     while (G > 1 && (G - 1) * len >= N) --G;   // rounding the length up can empty trailing segments
     if ((long long)U * SL * G >= (1ll << 31)) return hipErrorInvalidValue;
     float *ws = static_cast<float *>(workspace);
     auto go = [&](auto increment, int first_slice, int slices) {
         constexpr bool INC = decltype(increment)::value;
-        hipLaunchKernelGGL((prefill_kernel<DP, DV, T, INC>), dim3((unsigned)(U * slices * (INC ? G - 1 : G))), dim3(64 * NW), 0, s,
-                           (const T *)q, (const T *)k, (const T *)v, (T *)y, state, has_init, N, ws, len, G, first_slice, slices,
-                           dec);
+        const int pieces = shared ? 2 : 1, parts = INC ? (G - 1) * pieces : G;
+        hipLaunchKernelGGL((prefill_kernel<DP, DV, T, INC>), dim3((unsigned)(U * slices * parts)), dim3(64 * NW), 0, s, (const T *)q, (const T *)k,
+                           (const T *)v, (T *)y, state, has_init, N, ws, INC ? len / pieces : len, INC ? parts + 1 : G, G, shared ? 0 : 1, pieces,
+                           first_slice, slices, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;

@@ -280,6 +280,27 @@ def test_prefill_fp32_shared_increments(based, U, dv, N, init):
     check_close(z[:few], zw, TOL["f32"], "z")
 
 
+# .. and on the fp32 matrix instructions: two segments, the increment of the first one shared by two workgroups (d' = 8: from 640 tokens on); then from the
+# state that this left, where it is not
+@pytest.mark.parametrize("dtype,dp,dv,U,N1,N", [("f32", 32, 64, 90, 200, 390), ("f32", 32, 128, 64, 129, 129), ("bf16", 24, 128, 100, 170, 345), ("f32", 24, 64, 256, 161, 161),
+                                                ("f32", 8, 64, 343, 641, 800), ("bf16", 8, 128, 256, 639, 639)])
+def test_prefill_fp32_halved_increment(based, dtype, dp, dv, U, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": dp, "dtype": dtype})
+    few = 5
+    q, k, v = synth.linattn_inputs(wl, units=few, N=N)
+    state, at = based.alloc_state(1, U, dp, dv), np.arange(U) % few
+    got = [down(based.prefill(*(up(a[at, lo:hi], dtype, (1, U, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state,
+                              has_init=lo > 0)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N)) if hi > lo]
+    y = np.concatenate(got, 1)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, dp, dv))
+    for a in (y, S, z):
+        assert (a == a[at]).all()
+    check_close(rows(y[:few]), rows(oracle.linattn_quadratic(q, k, v)), TOL[dtype], "y")
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(S[:few], Sw, TOL["f32"], "S")
+    check_close(z[:few], zw, TOL["f32"], "z")
+
+
 # bf16 d' = 32 prefill in blocks of 256 tokens: a tile of 32 queries and a block with remainders, blocks with one to eight tiles, calls on either side of
 # the lines to the kernel of short calls, segments shorter and longer than a block, both widths, more workgroups than the chip holds; without and from a
 # state (the second call)
