@@ -207,7 +207,7 @@ struct DecayArg {
 template <int DV, bool INC, bool DECAY, bool SHARED>
 __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict__ q, const float *__restrict__ k,
                                                         const float *__restrict__ v, float *__restrict__ y, float *state, int has_init,
-                                                        int N, float *ws, int seg_len, int inc_len, int shares, int G, int slots, int first_slice, int slices,
+                                                        int N, float *ws, int seg_len, int inc_len, int shares, int G, int slots, int first_slice, int slices, int local,
                                                         DecayArg dec)
 {
     constexpr int SL = DV / COLS;
@@ -215,7 +215,13 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     const bool numerator_only = (has_init & 4) != 0, init = (has_init & 1) != 0;
     static_assert(!(DECAY && SHARED), "an entry is scaled by the decay of a whole segment");
     const int gseg = !INC ? G : SHARED ? shares : G - 1;
-    const int seg = blockIdx.x % gseg, us = blockIdx.x / gseg, u = us / slices, slice = first_slice + us % slices, col0 = slice * COLS;
+    // The workgroups of a unit's slice run on one XCD (workgroup index mod 8), whose L2 then holds the entries that they write and sum, for the first `local`
+    // slices, a multiple of 8; the rest's run on all XCDs.  (All on all XCDs, and this, us: 16 units N 777 31.2, 26.5, N 2048 59.5, 47.1, 32 units
+    // N 2048 66.5, 54.5, 60 units N 1500 69.8, 61.0, 128 units N 2048 141.2, 138.4; d_v 128, 8 units N 1024 36.1, 26.0.)
+    const int bid = blockIdx.x;
+    const bool on_one = bid < local * gseg;
+    const int idx = on_one ? bid / 8 : bid - local * gseg, seg = idx % gseg, us = on_one ? idx / gseg * 8 + bid % 8 : local + idx / gseg;
+    const int u = us / slices, slice = first_slice + us % slices, col0 = slice * COLS;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63, g = lane >> 5, n = lane & 31;
     const int len = INC && SHARED ? inc_len : seg_len, begin = seg * len, end = min(INC && SHARED ? (G - 1) * seg_len : N, begin + len), chunks = (end - begin + C - 1) / C;
@@ -794,12 +800,13 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
             if (shared) {
                 hipLaunchKernelGGL((prefill_kernel<DV, INC, false, true>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
                                    (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice,
-                                   slices, dec);
+                                   slices, U * slices / 8 * 8, dec);
                 return hipGetLastError();
             }
         }
         hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY, false>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
-                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, dec);
+                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, U * slices / 8 * 8,
+                           dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;
