@@ -107,7 +107,9 @@ int based_state_import(void *state, const float *S, const float *z, int B, int H
  *          the two rows and writes both rows equal.  For a state produced by this library, or
  *          imported from the canonical arrays of such a state, that changes nothing.
  *   workspace  scratch of at least based_prefill_workspace_bytes(...) bytes, 256-byte aligned;
- *          may be NULL when that size is 0 (it never is for bf16).  It must be zero-filled ONCE
+ *          may be NULL when that size is 0 (never for bf16 at d' = 16 and 32).  The size does not
+ *          shrink as N grows, so that one for the longest sequence serves the shorter ones of the
+ *          same B, H, d_feat, d_v and dtype.  It must be zero-filled ONCE
  *          after it is allocated; after that the library maintains it, and calls may reuse it
  *          without clearing.  For few units and long sequences the sequence is cut into segments
  *          that run side by side; state increments of the segments travel through the workspace.

@@ -113,7 +113,7 @@ int based_state_import(void *state, const float *S, const float *z, int B, int H
 
 // A prefill workspace is a 256-byte header followed by the scratch of the kernel family that serves
 // the call.  The header's first word is the sticky status of the bounded waits; it sits at offset 0
-// whatever the sizes, so a workspace can be reused for calls of any shape.
+// whatever the sizes, so a workspace can be reused for calls of any shape that need no more of it.
 constexpr size_t kWsHeader = 256;
 
 static size_t prefill_scratch_bytes(int U, int N, int d_feat, int d_v, int dtype)

@@ -106,7 +106,7 @@ void prefill_mfma_flags_region(int U, int N, int dp, int dv, size_t *offset, siz
 void prefill_mfma_set_poll_limit(int polls);
 bool prefill_mfma32_supported(int dp, int dv, int dtype);
 size_t prefill_mfma32_workspace_bytes(int U, int N, int dp, int dv);
-// the kernel for short calls at d' = 32, and which those are (called by launch_prefill_mfma32)
+// the kernel for short calls at d' = 32, and which those are (called by launch_prefill_mfma32); its workspace serves every call of up to N tokens
 bool prefill_mfma32_short_takes(int U, int N, int dv, int has_init);
 size_t prefill_mfma32_short_workspace_bytes(int U, int N, int dv);
 hipError_t launch_prefill_mfma32_short(const void *q, const void *k, const void *v, void *y, float *state,

@@ -897,13 +897,13 @@ bool prefill_mfma32_supported(int dp, int dv, int dtype)
     return dtype == BASED_BF16 && dp == dp32::DP && (dv == 64 || dv == 128);
 }
 
-// Workspace: one entry per (unit, slice, segment).  (Which kernel takes a call may depend on whether there is a state to start from.)
+// Workspace: one entry per (unit, slice, segment), for the kernel that needs more: which one takes a call may depend on whether there is a state to
+// start from.  The size never shrinks with N: what was allocated for the longest sequence serves the shorter ones, and those that go to the kernel of
+// short calls may be cut into more segments.
 size_t prefill_mfma32_workspace_bytes(int U, int N, int dp, int dv)
 {
     (void)dp;
-    const size_t a = dp32::entry_bytes(U, N, dv);
-    if (!prefill_mfma32_short_takes(U, N, dv, 1)) return (a + 255) / 256 * 256;
-    const size_t b = prefill_mfma32_short_workspace_bytes(U, N, dv);
+    const size_t a = dp32::entry_bytes(U, N, dv), b = prefill_mfma32_short_workspace_bytes(U, N, dv);
     return ((a > b ? a : b) + 255) / 256 * 256;
 }
 

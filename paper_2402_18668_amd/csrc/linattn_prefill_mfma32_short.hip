@@ -783,6 +783,8 @@ static int make_segments(int N, int G, SegTable &t)
 
 }  // namespace dp32s
 
+static constexpr int kLongest = 736;
+
 // Up to 32 tokens, up to 96 from a state (a block's readout is one wave's for 32 queries; here all eight waves have a part), and from 257, 401 or 513
 // tokens on, by the number of groups of 64 columns, up to 736 (a last block that is mostly empty, chains of increments of whole blocks); at d_v 128 from a
 // state, which blocks take through a launch of their own, from 225 on.  (This kernel and blocks, us: 16 groups N 32 10.0, 11.9, N 33 12.2, 12.0, N 272 20.2, 20.2, N 448 23.9, 25.3, N 768 30.0, 28.2; 200 groups N 32 14.9, 15.2, N 33 17.0,
@@ -795,12 +797,15 @@ bool prefill_mfma32_short_takes(int U, int N, int dv, int has_init)
 {
     const int groups = U * (dv / dp32s::COLS);
     const int from = has_init && dv == 128 ? 224 : groups <= 28 ? 256 : groups <= 40 ? 400 : 512;
-    return N <= (has_init ? 96 : 32) || (groups <= 64 && N > from && N <= 736);
+    return N <= (has_init ? 96 : 32) || (groups <= 64 && N > from && N <= kLongest);
 }
 
-size_t prefill_mfma32_short_workspace_bytes(int U, int N, int dv)   // one entry per (unit, slice, segment)
+// One entry per (unit, slice, segment), for a call of N tokens and for every shorter one that comes here: segments only get more with N.
+size_t prefill_mfma32_short_workspace_bytes(int U, int N, int dv)
 {
-    return (size_t)U * (dv / dp32s::COLS) * dp32s::pick_segments(U * (dv / dp32s::COLS), N) * dp32s::kWsEntryFloats * sizeof(float);
+    const int groups = U * (dv / dp32s::COLS), longest = N < kLongest ? N : kLongest;
+    if (!prefill_mfma32_short_takes(U, longest, dv, 1)) return 0;   // (up to 96 tokens are one segment, for which blocks need as much)
+    return (size_t)groups * dp32s::pick_segments(groups, longest) * dp32s::kWsEntryFloats * sizeof(float);
 }
 
 hipError_t launch_prefill_mfma32_short(const void *q, const void *k, const void *v, void *y, float *state,

@@ -153,6 +153,20 @@ def test_bad_arguments_are_rejected_before_launch(based):
     assert lib.based_state_import(p, p, p, 1, 1, 16, 100, st) == based.ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("d_feat", [8, 16, 24, 32])
+def test_prefill_workspace_never_shrinks_with_the_sequence(based, d_feat):
+    """A workspace for the longest sequence serves the shorter ones: every length up to where the kernels' rules change, then some."""
+    sizes = [1, 2, 7, 8, 9, 15, 20, 21, 28, 29, 32, 33, 40, 41, 42, 51, 52, 60, 64, 65, 85, 86, 102, 104, 105, 128, 129, 170, 200, 256, 257, 400, 600]
+    lengths = [*range(1, 1100), *range(1100, 5000, 37), *range(5000, 33000, 1009)]
+    for query, dtypes in ((based.lib.based_prefill_workspace_bytes, (based.F32, based.BF16)), (based.lib.based_prefill_decay_workspace_bytes, (based.BF16,))):
+        for d_v in (64, 128):
+            for dtype in dtypes:
+                for U in sizes:
+                    need = [query(1, U, N, d_feat, d_v, dtype) for N in lengths]
+                    shrinks = [N for N, a, b in zip(lengths[1:], need, need[1:]) if b < a]
+                    assert not shrinks, (U, d_v, dtype, shrinks[:3])
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py runs on one GPU only: --gpus 2 exits with a message and a non-zero status before
     touching any device; the credited-work helper matches the hand count for both state layouts."""
