@@ -7,8 +7,10 @@
 // Symmetric packing.  One state row per unordered pair of features.  Write a vector as two halves (x, y) of 16 and take indices mod 16.
 // Tiles of 32 rows: T = 0 .. 7: x_n x_(n + T), then y_n y_(n + T); T = 8 .. 15: x_n y_(n + T - 8), then y_n x_(n + d), d = 7, 8, 5, 6, 3, 4, 1, 2
 // (differences 0 .. 7 and 8 .. 15 of y's index over x's).  Two more: E1 = the linear rows, E2 = x_n x_(n + 8), then y_n y_(n + 8), of which n < 8
-// counts.  528 pair rows instead of 1024; the constant's row is kept apart.  Rows hold sum k_a k_b v, without the 1 / sqrt(2) of Eq. 4: the
-// readout weighs a pair of different features 1 and a square (tile 0) 1/2.
+// counts.  528 pair rows instead of 1024; the constant's row is kept apart.  Rows are built without the 1 / sqrt(2) of Eq. 4: the readout weighs a
+// pair of different features 1 and a square (tile 0) 1/2.  Keys are staged halved, rows hold sum (k_a / 2) (k_b / 2) v, sum (k_a / 2) v, and the outputs
+// and denominators are summed as quarters: then nothing inside overflows before the state of Eq. 4 and the kernel's values do.  (Powers of two: no result
+// changes by it.  Unhalved, 32 units of 16384 tokens take 161.8 us instead of 162.7, 512 of 2048 238.8 and 238.7.)
 //
 // Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment).  Wave w owns tiles 2 w, 2 w + 1 (both column tiles of
 // 32) and one more product, in accumulators throughout.  A block's phases:
@@ -21,7 +23,7 @@
 // Two barriers a block; between them waves drift through intra, readout and update.
 //
 // Denominator.  The K-state is kept as moments: M[a][b] = sum_t k_a k_b, z1[a] = sum_t k_a and the token count.  Per query
-// phi(q).z = z0 + sum_a q_a (z1[a] + (M q)[a] / 2); the part from inside the block is the column sum of the masked products.
+// phi(q).z = z0 + sum_a q_a (z1[a] + (M q)[a] / 2); the part from inside the block is the column sum of the masked products.  (M / 4, z1 / 2 are kept.)
 //
 // Long sequences / few units: G segments; a first launch computes each segment's state increment, segment 0's starting from
 // the caller's state, and the main launch starts segment g from the sum of the entries before it (read at full width: all
@@ -73,15 +75,15 @@ constexpr int WS_SLOTS = 5 * NW;
 constexpr size_t kWsEntryFloats = (size_t)WS_SLOTS * 16 * 64;
 
 struct Kv {   // a block's rows
-    float kt[DP][KT_LD];         // K^T
+    float kt[DP][KT_LD];         // K^T / 2
     uint16_t v[BLOCK][COLS];     // 16-byte piece c of row t at c ^ 4 ((t / 2) % 2): the operand reads spread over the banks
 };
 struct Lds {
     Kv kv;
-    uint16_t k[BLOCK][DP];         // 16-byte piece c of row t at c ^ (t / 4) % 4
+    uint16_t k[BLOCK][DP];         // K / 2; 16-byte piece c of row t at c ^ (t / 4) % 4
     uint16_t s[SLABS][2][64][8];   // state operands: [slab 2 T + half][column tile][lane][k-slot]
     uint16_t m[2][64][8];          // the same of M
-    float cst[COLS], z1[DP];       // the constant's row; K-state
+    float cst[COLS], z1[DP];       // a quarter of the constant's row and of the K-state's linear part
 };
 static_assert(sizeof(Lds) <= 160 * 1024, "one workgroup per CU");
 static_assert(sizeof(Lds) >= sizeof(float) * 32 * TILES * IMG_LD, "the state image of one column tile fits the LDS");
@@ -162,8 +164,9 @@ __device__ __forceinline__ CanonRows canon_rows(int T, int fl, bool packed_state
     if (T < 16) return canon_pair(fl, partner(T, fl), packed_state);
     return fl & 8 ? CanonRows{-1, -1} : canon_pair(fl, fl + 8, packed_state);
 }
-// state rows hold sum k_a k_b v for a pair
-__device__ __forceinline__ bool is_pair(CanonRows c) { return c.r1 > DP; }
+// what a row is multiplied with on its way out (sum (k_a / 2) (k_b / 2) v to sum k_a k_b v / sqrt(2), sum (k_a / 2) v to sum k_a v)
+__device__ __forceinline__ float out_scale(CanonRows c) { return c.r1 > DP ? 4.f * kRsqrt2 : 2.f; }
+__device__ __forceinline__ float in_scale(CanonRows c) { return c.r1 > DP ? 0.5f * kRsqrt2 : 0.5f; }   // and in
 
 constexpr int kMaxSegments = 16;
 struct SegTable { int begin[kMaxSegments + 1]; };
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                     const int i = (s0 + j) * NT + tid, row = i >> 3;
                     const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                     *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
-                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * (is_pair(cr) ? kRsqrt2 : 0.5f);
+                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * (0.5f * in_scale(cr));
                 }
             }
             __syncthreads();
@@ -311,15 +314,15 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             }
             __syncthreads();
         }
-        if (w == 0) {   // M = sqrt(2) x the symmetric part of z's pair rows
+        if (w == 0) {   // M / 4 from the symmetric part of z's pair rows
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) {
                 const CanonRows cr = canon_pair(8 * (rr >> 2) + 4 * g + (rr & 3), n, packed_state);
-                X[rr] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+                X[rr] = 0.25f * kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
             }
         }
         if (w > 0 && w < 4) {
-            const float t = w == 1 ? zu[1 + n] : Su[32 * (w - 2) + n];
+            const float t = w == 1 ? 0.5f * zu[1 + n] : Su[32 * (w - 2) + n];
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) X[rr] = t;
         }
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                 const int i = st * NT + tid, row = i >> 3;
                 const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                 if (cr.r1 >= 0) {
-                    const f32x4 t = *reinterpret_cast<const f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) * (is_pair(cr) ? kRsqrt2 : 1.f);
+                    const f32x4 t = *reinterpret_cast<const f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) * out_scale(cr);
                     float *p = Su + 32 * cc + 4 * (i & 7);
                     *reinterpret_cast<f32x4 *>(p + (size_t)cr.r1 * dv) = t;
                     if (cr.r2 != cr.r1) *reinterpret_cast<f32x4 *>(p + (size_t)cr.r2 * dv) = t;
@@ -356,10 +359,10 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
                 for (int rr = 0; rr < 16; ++rr) {
                     const int a = 8 * (rr >> 2) + 4 * g + (rr & 3);
-                    if (!packed_state || a <= n) zu[canon_pair(a, n, packed_state).r1] = kRsqrt2 * X[rr];
+                    if (!packed_state || a <= n) zu[canon_pair(a, n, packed_state).r1] = 4.f * kRsqrt2 * X[rr];
                 }
             }
-            if (w == 1 && g == 0) zu[1 + n] = X[0];
+            if (w == 1 && g == 0) zu[1 + n] = 2.f * X[0];
             if (tid == 0) zu[0] = z0 + (float)N;
         }
         if ((w == 2 || w == 3) && g == 0) Su[32 * (w - 2) + n] = X[0];
@@ -431,14 +434,22 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
             for (int h = 0; h < 4; ++h) raw.v[h] = (tid >> 3) + 64 * h < rows ? raw.v[h] : zero;
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (!INC) *reinterpret_cast<u32x4 *>(&krow[t0 + h][8 * (c ^ ((t0 >> 2) & 3))]) = raw.k[h];
+        u32x4 half[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i][t0]) = f32x2{bf16lo(raw.k[0][i]), bf16lo(raw.k[1][i])};
-            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i + 1][t0]) = f32x2{bf16hi(raw.k[0][i]), bf16hi(raw.k[1][i])};
+            float lo[2], hi[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                lo[h] = 0.5f * bf16lo(raw.k[h][i]);
+                hi[h] = 0.5f * bf16hi(raw.k[h][i]);
+                half[h][i] = pack2(lo[h], hi[h]);
+            }
+            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i][t0]) = f32x2{lo[0], lo[1]};
+            *reinterpret_cast<f32x2 *>(&kv.kt[8 * c + 2 * i + 1][t0]) = f32x2{hi[0], hi[1]};
         }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (!INC) *reinterpret_cast<u32x4 *>(&krow[t0 + h][8 * (c ^ ((t0 >> 2) & 3))]) = half[h];
 #pragma unroll
         for (int h = 0; h < 4; ++h)
             *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
@@ -526,7 +537,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             }
             asm volatile("" ::: "memory");
         }
-        // X: M = K^T K, z1 = 1 K, the constant 1 V; E1, E2
+        // X: M / 4 = (K / 2)^T (K / 2), z1 / 2 = 1 (K / 2), the constant 1 V; E1, E2
         const u32x4 one = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
         const float *kx = &kv.kt[n][8 * g];
         const uint16_t *vx = &kv.v[0][0] + (v_place(8) ^ ((w & 1) << 5));
@@ -585,10 +596,10 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
         fresh_lane();
         stage(tok0, lds.kv, lds.k);
         if (have_state) {
-            auto put = [&](uint16_t *p, const f32x16 &a, int r0, int r1) {   // registers r0 .. + 3, r1 .. + 3
+            auto put = [&](uint16_t *p, const f32x16 &a, int r0, int r1, float scale = 1.f) {   // registers r0 .. + 3, r1 .. + 3
                 f32x8 f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { f[i] = a[r0 + i]; f[4 + i] = a[r1 + i]; }
+                for (int i = 0; i < 4; ++i) { f[i] = scale * a[r0 + i]; f[4 + i] = scale * a[r1 + i]; }
                 *reinterpret_cast<bf16x8 *>(p + 8 * lane) = __builtin_convertvector(f, bf16x8);
             };
 #pragma unroll
@@ -603,10 +614,10 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                 put(lds.m[0][0], X, 0, 4);
                 put(lds.m[1][0], X, 8, 12);
             } else if (w < 4) {
-                if (g == 0) (w == 1 ? lds.z1 : lds.cst + 32 * (w - 2))[n] = X[0];
+                if (g == 0) (w == 1 ? lds.z1 : lds.cst + 32 * (w - 2))[n] = (w == 1 ? 0.5f : 0.25f) * X[0];
             } else if (w < 6) {
-                put(lds.s[32][w - 4][0], X, 0, 4);
-                put(lds.s[33][w - 4][0], X, 8, 12);
+                put(lds.s[32][w - 4][0], X, 0, 4, 0.5f);
+                put(lds.s[33][w - 4][0], X, 8, 12, 0.5f);
             } else {
                 put(lds.s[34][w - 6][0], X, 0, 8);
             }
@@ -622,7 +633,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             bf16x8 qop[2];   // contraction slots (jj, i): element 16 h + 8 jj + 4 g + i
 #pragma unroll
             for (int h = 0; h < 2; ++h) qop[h] = as_bf16x8(u32x4{qraw[4 * h][0], qraw[4 * h][1], qraw[4 * h + 2][0], qraw[4 * h + 2][1]});
-            // ---- intra: 2 P^T = 1 + (1 + A^T)^2, masked in the queries' own tile; 2 Y^T = V^T 2 P^T
+            // ---- intra: P^T / 2 = 1 / 4 + (1 / 2 + A^T / 2)^2, masked in the queries' own tile; Y^T / 2 = V^T P^T / 2
             zero16(Y[0]);
             zero16(Y[1]);
             if (w >= 4) __builtin_amdgcn_s_setprio(2);   // (these waves have the most key tiles)
@@ -642,16 +653,16 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                     va[sl][1] = read_v(v1 + COLS * (QT * kt + 16 * sl), 8);
                 }
             };
-            auto scores = [&](f32x16 &P) {   // 1 + A^T
+            auto scores = [&](f32x16 &P) {   // 1 / 2 + A^T / 2
 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) P[rr] = 1.f;
+                for (int rr = 0; rr < 16; ++rr) P[rr] = 0.5f;
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     P = mfma(as_bf16x8(u32x4{ko[2 * h][0], ko[2 * h][1], ko[2 * h + 1][0], ko[2 * h + 1][1]}), qop[h], P);
             };
             auto multiply = [&](f32x16 &P, bool own) {
 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) P[rr] = fmaf(P[rr], P[rr], 1.f);
+                for (int rr = 0; rr < 16; ++rr) P[rr] = fmaf(P[rr], P[rr], 0.25f);
                 if (own) {
 #pragma unroll
                     for (int rr = 0; rr < 16; ++rr) P[rr] = 8 * (rr >> 2) + (rr & 3) <= n - 4 * g ? P[rr] : 0.f;
@@ -703,7 +714,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             Y[1] *= 0.5f;
             den *= 0.5f;
             if (have_state) {
-                // ---- readout: Y^T += S^T phi(q)
+                // ---- readout: Y^T / 4 += S^T phi(q) / 4
                 float r[2][16];   // r[h][m]: element 16 h + (m + 4 g) % 16
 #pragma unroll
                 for (int b = 0; b < 8; ++b)
@@ -763,7 +774,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
                         for (int i = 0; i < 4; ++i) Y[c][4 * j + i] += t[i];
                     }
-                // denominator: T[a][query] = (M q)[a], then sum_a q_a (z1[a] + T[a] / 2)
+                // denominator: T[a][query] = (M q)[a] / 4, then sum_a q_a (z1[a] / 4 + T[a] / 2)
                 f32x16 T;
                 zero16(T);
 #pragma unroll
@@ -785,8 +796,8 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
             role_guard();
             // ---- outputs: the halves of a wave exchange quads, 16 bytes a lane
             const auto d = __builtin_amdgcn_permlane32_swap(__float_as_uint(den), __float_as_uint(den), false, false);
-            const float before = have_state ? z0 + (float)tok0 : 0.f;   // tokens in the state
-            const float inv = numerator_only ? 1.f : 1.f / (before + (__uint_as_float(d[0]) + __uint_as_float(d[1])));
+            const float before = have_state ? 0.25f * (z0 + (float)tok0) : 0.f;   // tokens in the state
+            const float inv = numerator_only ? 4.f : 1.f / (before + (__uint_as_float(d[0]) + __uint_as_float(d[1])));
             const int tok = QT * qt + n;
             uint16_t *yb = yu + (size_t)tok0 * dv + (uint32_t)(tok * dv + 8 * g);
 #pragma unroll

@@ -354,6 +354,29 @@ def test_prefill_dp32_odd_state(based, N):
     assert np.isposinf(S[1, 1 + 3, 7]) and (~np.isfinite(S)).sum() == 1
 
 
+# bf16 d' = 32 prefill up to the largest numbers: state rows of 3.0e38 (the sum of k_a k_b v itself would be 4.25e38), and one score of 2.2e19, whose
+# square's half is 2.5e38 (its square 4.9e38); in one block, in several, over segments, at both widths
+@pytest.mark.parametrize("U,dv,N", [(2, 64, 32), (2, 64, 200), (3, 128, 200), (130, 64, 600), (2, 64, 2000), (3, 128, 1100), (100, 64, 1700)])
+def test_prefill_dp32_range(based, U, dv, N):
+    q, k, v = np.zeros((U, N, 32)), np.zeros((U, N, 32)), synth.round_to(synth.normal(85, (U, N, dv), 0.5), "bf16").astype(np.float64)
+    k[:, 3, [3, 17]] = 2.0 ** 63
+    v[:, 3, 5] = 5.0
+    k[:, 20, 9], q[:, 25, 9] = 2.0 ** 32, 1.203125 * 2.0 ** 32
+    state = based.alloc_state(1, U, 32, dv)
+    y = down(based.prefill(*(up(a, "bf16", (1, U, N, a.shape[-1])) for a in (q, k, v)), state=state)).reshape(U, N, dv)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, 32, dv))
+    want = np.cumsum(v, 1) / np.arange(1, N + 1)[:, None]   # (scores of 0)
+    want[:, 25] = v[:, 20]
+    check_close(rows(y), rows(want), TOL["bf16"], "y")
+    at = [3, 20]   # (the other keys are 0)
+    phi = np.concatenate([np.ones((U, 2, 1)), k[:, at], (k[:, at, :, None] * k[:, at, None, :]).reshape(U, 2, 1024) / 2 ** 0.5], -1)
+    Sw, zw = phi.swapaxes(1, 2) @ v[:, at], phi.sum(1)
+    assert 2.9e38 < Sw.max() < 3.1e38
+    Sw[:, 0], zw[:, 0] = v.sum(1), N
+    check_close(S.reshape(-1, dv), Sw.reshape(-1, dv), TOL["bf16"], "S")
+    check_close(z.reshape(-1, 1), zw.reshape(-1, 1), TOL["bf16"], "z")
+
+
 # convolution gate: runs of 2, 8 and 32 tokens (the last for a state updated in place and for the longest sequences), a last run that is
 # not full, sequences shorter than the filter
 @pytest.mark.parametrize("dtype,B,N,Dc,in_place", [("bf16", 2, 1, 64, False), ("bf16", 3, 2, 72, False), ("f32", 3, 5, 12, False), ("bf16", 5, 9, 264, False),
