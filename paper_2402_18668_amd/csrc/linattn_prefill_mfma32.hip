@@ -298,7 +298,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                     const int i = (s0 + j) * NT + tid, row = i >> 3;
                     const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                     *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
-                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * (0.5f * in_scale(cr));
+                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (0.5f * t[j][0] + 0.5f * t[j][1]) * in_scale(cr);   // (halves: the sum may overflow)
                 }
             }
             __syncthreads();
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) {
                 const CanonRows cr = canon_pair(8 * (rr >> 2) + 4 * g + (rr & 3), n, packed_state);
-                X[rr] = 0.25f * kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+                X[rr] = 0.5f * kRsqrt2 * (0.5f * zu[cr.r1] + 0.5f * zu[cr.r2]);
             }
         }
         if (w > 0 && w < 4) {

@@ -314,7 +314,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
                     const int i = (s0 + j) * NT + tid, row = i >> 3;
                     const bool zero = canon_rows(row >> 5, row & 31, packed_state).r1 < 0;   // (padding)
                     *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
-                        zero ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * 0.5f;
+                        zero ? f32x4{0.f, 0.f, 0.f, 0.f} : 0.5f * t[j][0] + 0.5f * t[j][1];   // (the sum may overflow)
                 }
             }
             __syncthreads();
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const CanonRows cr = canon_pair(16 * xe + 4 * lq + i, 16 * xc + ln, packed_state);
-            M[i] = kRsqrt2 * (zu[cr.r1] + zu[cr.r2]);
+            M[i] = 2.f * kRsqrt2 * (0.5f * zu[cr.r1] + 0.5f * zu[cr.r2]);
         }
         z1 = zu[1 + 16 * xe + ln];
         z0 = zu[0];

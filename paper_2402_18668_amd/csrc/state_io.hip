@@ -51,11 +51,11 @@ __global__ void state_repack_kernel(float *state, float *packed, int dp, int dv,
             r1 = 1 + dp + a * dp + b; r2 = 1 + dp + b * dp + a;
         }
         for (int c = threadIdx.x; c < dv; c += blockDim.x) {
-            if (to_packed) pu[(size_t)r * dv + c] = 0.5f * (su[(size_t)r1 * dv + c] + su[(size_t)r2 * dv + c]);
+            if (to_packed) pu[(size_t)r * dv + c] = 0.5f * su[(size_t)r1 * dv + c] + 0.5f * su[(size_t)r2 * dv + c];   // (the sum may overflow)
             else { const float x = pu[(size_t)r * dv + c]; su[(size_t)r1 * dv + c] = x; su[(size_t)r2 * dv + c] = x; }
         }
         if (threadIdx.x == 0) {
-            if (to_packed) pz[r] = 0.5f * (sz[r1] + sz[r2]);
+            if (to_packed) pz[r] = 0.5f * sz[r1] + 0.5f * sz[r2];
             else { sz[r1] = pz[r]; sz[r2] = pz[r]; }
         }
     }

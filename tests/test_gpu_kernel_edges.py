@@ -377,6 +377,32 @@ def test_prefill_dp32_range(based, U, dv, N):
     check_close(z.reshape(-1, 1), zw.reshape(-1, 1), TOL["bf16"], "z")
 
 
+# .. and from a state with such rows: a pair's two rows, a square's and a linear one of 3.0e38, whose sum with itself is infinite (K-state 2.2e38); one
+# workgroup that reads it and several, both state layouts
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N", [(2, 64, 20), (2, 64, 200), (3, 128, 300), (3, 64, 400), (3, 128, 200), (2, 64, 2000), (130, 64, 300)])
+def test_prefill_dp32_large_state(based, packed, U, dv, N):
+    q, v = np.zeros((U, N, 32)), synth.round_to(synth.normal(86, (U, N, dv), 0.5), "bf16").astype(np.float64)
+    S0, z0 = np.zeros((U, 1057, dv)), np.zeros((U, 1057))
+    S0[:, 0] = synth.normal(87, (U, dv), 3.0)
+    z0[:, 0] = 50.0
+    for f in (1 + 3, 33 + 3 * 32 + 17, 33 + 17 * 32 + 3, 33 + 9 * 32 + 9):
+        S0[:, f, 5], z0[:, f] = 3.0e38, 2.2e38
+    state = based.alloc_state(1, U, 32, dv)
+    based.state_import(state, up(S0, "f32", (1, U, 1057, dv)), up(z0, "f32", (1, U, 1057)), 32)
+    if packed:
+        state = based.state_pack(state, based.alloc_packed_state(1, U, 32, dv), 1, U, 32, dv)
+    y = down(based.prefill(*(up(a, "bf16", (1, U, N, a.shape[-1])) for a in (q, q, v)), state=state, has_init=True, packed=packed)).reshape(U, N, dv)
+    check_close(rows(y), rows((S0[:, :1] + np.cumsum(v, 1)) / (50.0 + np.arange(1, N + 1)[:, None])), TOL["bf16"], "y")
+    if packed:
+        state = based.state_unpack(state, based.alloc_state(1, U, 32, dv), 1, U, 32, dv)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, 32, dv))
+    S0[:, 0] += v.sum(1)
+    z0[:, 0] += N
+    check_close(S.reshape(-1, dv), S0.reshape(-1, dv), 1e-4, "S")   # (nothing but the constant's row is added to, in fp32)
+    check_close(z.reshape(-1, 1), z0.reshape(-1, 1), 1e-4, "z")
+
+
 # convolution gate: runs of 2, 8 and 32 tokens (the last for a state updated in place and for the longest sequences), a last run that is
 # not full, sequences shorter than the filter
 @pytest.mark.parametrize("dtype,B,N,Dc,in_place", [("bf16", 2, 1, 64, False), ("bf16", 3, 2, 72, False), ("f32", 3, 5, 12, False), ("bf16", 5, 9, 264, False),
