@@ -152,11 +152,17 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     const int gseg = INCREMENT ? G - 1 : G;
     // The workgroups of a unit's slice run on one XCD (workgroup index mod 8), whose L2 then holds the entries that they write and sum, for the first `local`
     // slices, a multiple of 8; the rest's run on all XCDs.  (All on all XCDs, and this, us: fp32, 16 units, d' 32 N 777 110.7, 95.2, d' 8 N 1000 20.9,
-    // 18.3; bf16, d' 24 16 units N 2048 141.2, 132.5, d' 8 33 units N 4096 66.3, 59.4.)
-    const int bid = blockIdx.x;
-    const bool on_one = bid < local * gseg;
-    const int idx = on_one ? bid / 8 : bid - local * gseg, seg = idx % gseg, us = on_one ? idx / gseg * 8 + bid % 8 : local + idx / gseg;
-    const int u = us / slices, slice = first_slice + us % slices, col0 = slice * COLS;
+    // 18.3; bf16, d' 24 16 units N 2048 141.2, 132.5, d' 8 33 units N 4096 66.3, 59.4.)  Fewer than 8 slices have a row of the grid each: dealt out with them
+    // 7 units of 500 tokens, d' 8, bf16, took 18.0 us instead of 17.7, one of 16 4.91 instead of 4.78.
+    int seg = blockIdx.x, us = blockIdx.y;
+    if (local > 0) {
+        const uint32_t bid = blockIdx.x, here = local * gseg;
+        const bool on_one = bid < here;
+        const uint32_t idx = on_one ? bid / 8 : bid - here, at = idx / (uint32_t)gseg;
+        seg = idx - at * gseg;
+        us = on_one ? at * 8 + bid % 8 : local + at;
+    }
+    const int u = slices == 1 ? us : (uint32_t)us / SL, slice = first_slice + (slices == 1 ? 0 : (uint32_t)us % SL), col0 = slice * COLS;   // (slices: 1 or SL)
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, n = lane & 15;
     const int begin = seg * seg_len, end = min(N, begin + seg_len);
 
@@ -553,10 +559,10 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     float *ws = static_cast<float *>(workspace);
     auto go = [&](auto increment, int first_slice, int slices) {
         constexpr bool INC = decltype(increment)::value;
-        const int pieces = shared ? 2 : 1, parts = INC ? (G - 1) * pieces : G;
-        hipLaunchKernelGGL((prefill_kernel<DP, DV, T, INC>), dim3((unsigned)(U * slices * parts)), dim3(64 * NW), 0, s, (const T *)q, (const T *)k,
-                           (const T *)v, (T *)y, state, has_init, N, ws, INC ? len / pieces : len, INC ? parts + 1 : G, G, shared ? 0 : 1, pieces,
-                           first_slice, slices, U * slices / 8 * 8, dec);
+        const int pieces = shared ? 2 : 1, parts = INC ? (G - 1) * pieces : G, all = U * slices, local = all / 8 * 8;
+        hipLaunchKernelGGL((prefill_kernel<DP, DV, T, INC>), local ? dim3((unsigned)(all * parts)) : dim3(parts, all), dim3(64 * NW), 0, s, (const T *)q,
+                           (const T *)k, (const T *)v, (T *)y, state, has_init, N, ws, INC ? len / pieces : len, INC ? parts + 1 : G, G,
+                           shared ? 0 : 1, pieces, first_slice, slices, local, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;

@@ -217,11 +217,17 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     const int gseg = !INC ? G : SHARED ? shares : G - 1;
     // The workgroups of a unit's slice run on one XCD (workgroup index mod 8), whose L2 then holds the entries that they write and sum, for the first `local`
     // slices, a multiple of 8; the rest's run on all XCDs.  (All on all XCDs, and this, us: 16 units N 777 31.2, 26.5, N 2048 59.5, 47.1, 32 units
-    // N 2048 66.5, 54.5, 60 units N 1500 69.8, 61.0, 128 units N 2048 141.2, 138.4; d_v 128, 8 units N 1024 36.1, 26.0.)
-    const int bid = blockIdx.x;
-    const bool on_one = bid < local * gseg;
-    const int idx = on_one ? bid / 8 : bid - local * gseg, seg = idx % gseg, us = on_one ? idx / gseg * 8 + bid % 8 : local + idx / gseg;
-    const int u = us / slices, slice = first_slice + us % slices, col0 = slice * COLS;
+    // N 2048 66.5, 54.5, 60 units N 1500 69.8, 61.0, 128 units N 2048 141.2, 138.4; d_v 128, 8 units N 1024 36.1, 26.0.)  Fewer than 8 slices have a row of the grid each:
+    // dealt out with them 4 units of 777 tokens took 27.0 us instead of 26.8, 2 of 2000 at d_v 128 35.9 instead of 35.4.
+    int seg = blockIdx.x, us = blockIdx.y;
+    if (local > 0) {
+        const uint32_t bid = blockIdx.x, here = local * gseg;
+        const bool on_one = bid < here;
+        const uint32_t idx = on_one ? bid / 8 : bid - here, at = idx / (uint32_t)gseg;
+        seg = idx - at * gseg;
+        us = on_one ? at * 8 + bid % 8 : local + at;
+    }
+    const int u = slices == 1 ? us : (uint32_t)us / SL, slice = first_slice + (slices == 1 ? 0 : (uint32_t)us % SL), col0 = slice * COLS;   // (slices: 1 or SL)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63, g = lane >> 5, n = lane & 31;
     const int len = INC && SHARED ? inc_len : seg_len, begin = seg * len, end = min(INC && SHARED ? (G - 1) * seg_len : N, begin + len), chunks = (end - begin + C - 1) / C;
@@ -796,17 +802,17 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     float *ws = static_cast<float *>(workspace);
     auto go = [&](auto increment, int first_slice, int slices) {
         constexpr bool INC = decltype(increment)::value;
+        const int parts = INC ? shares : G, all = U * slices, local = all / 8 * 8;
+        const dim3 grid = local ? dim3((unsigned)(all * parts)) : dim3(parts, all);
         if constexpr (!DECAY) {
             if (shared) {
-                hipLaunchKernelGGL((prefill_kernel<DV, INC, false, true>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
-                                   (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice,
-                                   slices, U * slices / 8 * 8, dec);
+                hipLaunchKernelGGL((prefill_kernel<DV, INC, false, true>), grid, dim3(NT), 0, s, (const float *)q, (const float *)k, (const float *)v,
+                                   (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, local, dec);
                 return hipGetLastError();
             }
         }
-        hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY, false>), dim3((unsigned)(U * slices * (INC ? shares : G))), dim3(NT), 0, s, (const float *)q,
-                           (const float *)k, (const float *)v, (float *)y, state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, U * slices / 8 * 8,
-                           dec);
+        hipLaunchKernelGGL((prefill_kernel<DV, INC, DECAY, false>), grid, dim3(NT), 0, s, (const float *)q, (const float *)k, (const float *)v, (float *)y,
+                           state, has_init, N, ws, len, inc_len, shares, G, entries, first_slice, slices, local, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;

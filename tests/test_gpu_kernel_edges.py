@@ -301,6 +301,24 @@ def test_prefill_fp32_halved_increment(based, dtype, dp, dv, U, N1, N):
     check_close(z[:few], zw, TOL["f32"], "z")
 
 
+# .. in both fp32 kernels, the grid of fewer than 8 slices of 64 columns (each a row), of 8 and of 8 with a remainder; one segment, where at d_v 128 the second
+# slice of a state goes before the first, and several
+@pytest.mark.parametrize("dtype,dp", [("f32", 16), ("f32", 32), ("bf16", 8), ("bf16", 24)])
+@pytest.mark.parametrize("U,dv", [(7, 64), (8, 64), (9, 64), (3, 128), (4, 128), (5, 128), (7, 128), (9, 128)])
+def test_prefill_fp32_slices(based, dtype, dp, U, dv):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": dp, "dtype": dtype})
+    cuts = (0, 50, 113, 300)
+    q, k, v = synth.linattn_inputs(wl, units=U, N=cuts[-1])
+    state = based.alloc_state(1, U, dp, dv)
+    y = np.concatenate([down(based.prefill(*(up(a[:, lo:hi], dtype, (1, U, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state,
+                                           has_init=lo > 0)).reshape(U, hi - lo, dv) for lo, hi in zip(cuts, cuts[1:])], 1)
+    check_close(rows(y), rows(oracle.linattn_quadratic(q, k, v)), TOL[dtype], "y")
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, dp, dv))
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(S, Sw, TOL["f32"], "S")
+    check_close(z, zw, TOL["f32"], "z")
+
+
 # bf16 d' = 32 prefill in blocks of 256 tokens: a tile of 32 queries and a block with remainders, blocks with one to eight tiles, calls on either side of
 # the lines to the kernel of short calls, segments shorter and longer than a block, both widths, more workgroups than the chip holds; without and from a
 # state (the second call)
