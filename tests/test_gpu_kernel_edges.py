@@ -340,6 +340,26 @@ def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
+# .. where a rule takes a call to other segments or the other kernel: d_v 128 from a state, where three segments are cut from 9 tiles on or, up to 80 groups and 352
+# tokens, the kernel of short calls takes them; every unit against one with the same values
+@pytest.mark.parametrize("U,dv,N1,N", [(33, 128, 33, 33 + 256), (33, 128, 33, 33 + 257), (40, 128, 40, 40 + 352), (40, 128, 40, 40 + 353), (41, 128, 20, 20 + 288),
+                                       (41, 128, 64, 64 + 289), (42, 128, 97, 97 + 513), (43, 128, 50, 50 + 600), (37, 128, 64, 64 + 800)])
+def test_prefill_dp32_rules(based, U, dv, N1, N):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
+    few = min(U, 5)
+    q, k, v = synth.linattn_inputs(wl, units=few, N=N)
+    state, at = based.alloc_state(1, U, 32, dv), np.arange(U) % few
+    y = np.concatenate([down(based.prefill(*(up(a[at, lo:hi], "bf16", (1, U, hi - lo, d)) for a, d in ((q, 32), (k, 32), (v, dv))), state=state,
+                                           has_init=lo > 0)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N)) if hi > lo], 1)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, 32, dv))
+    for a in (y, S, z):
+        assert (a == a[at]).all()
+    check_close(rows(y[:few]), rows(oracle.linattn_quadratic(q, k, v)), TOL["bf16"], "y")
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(S[:few], Sw, TOL["bf16"], "S")
+    check_close(z[:few], zw, TOL["bf16"], "z")
+
+
 # bf16 d' = 32 prefill from a state that is not symmetric in a pair's two rows (its mean counts) and holds an infinite row: every other entry is finite,
 # and the infinite ones reach the outputs
 @pytest.mark.parametrize("N", [64, 300, 2000])
