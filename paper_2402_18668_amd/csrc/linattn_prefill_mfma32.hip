@@ -832,7 +832,8 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 // the main pass is shortest at segments of about 5 tiles of 32 tokens, from some 10 segments on of more (16 units, us: N 777 3 segments 32.5,
 // 4 28.4, 5 30.4; N 1024 4 33.7, 6 32.2, 8 34.9; N 2048 6 39.4, 8 40.8, 10 39.3, 16 48.7; N 4096 8 56.9, 10 48.3, 16 51.6; N 16384 10 119.7, 16
 // 103.1).  With more units there is room for fewer, and one block after the other is the shorter chain for longer (1 segment and what there is room
-// for: 16 units N 512 25.6, 26.1; 32 units N 512 26.3, 28.9, N 1024 45, 34; 64 units N 512 27.9, 32.9, N 1024 47.8, 40.4; 96 units N 2048 86.6, 80.2; 128 units N
+// for: 16 units N 512 25.6, 26.1; 32 units N 512 26.3, 28.9, N 1024 45, 34; 64 units N 512 27.9, 32.9, N 1024 47.8, 40.4; 66 units N 769 42.7, 36.0, from a state 52.0, 46.4; 85
+// units N 769 42.9, 39.1, N 833 44.1, 40.2, from a state 53.6, 51.1; 96 units N 2048 86.6, 80.2; 128 units N
 // 1024 48.6, 54.2, N 4096 178, 156).  Two segments whose increment two workgroups share (without a state) are the shorter chain from 41 tiles on with up to 104 groups
 // (one and two: 87 units N 1000 47.4, 47.7, N 1400 63.4, 58.3, N 1664 73.0, 64.5; 100 units N 1280 57.3, 57.8, N 1400 63.7, 60.8, N 1664 73.4, 67.6; 128
 // units N 1400 64.1, 67.3, N 1664 73.7, 76.0).  At d_v 128 a state goes through a launch of its own anyhow, which increments can share: room for three is used from 9
@@ -841,7 +842,7 @@ static int pick_segments(int U, int N, int dv, int has_init)
 {
     const int groups = U * (dv / COLS), tiles = (N + QT - 1) / QT, room = 256 / groups;
     if (has_init && dv == 2 * COLS && room == 3 && tiles >= 9) return 3;
-    if (tiles < (room >= 4 ? 17 : room >= 3 ? 28 : groups <= 104 && !has_init ? 41 : 56)) return 1;
+    if (tiles < (room >= 4 ? 17 : room >= 3 ? 25 : groups <= 104 && !has_init ? 41 : 56)) return 1;
     const int chain = (int)(sqrtf((float)tiles) + 0.5f), longest = chain > 10 ? chain : 10;
     int G = 3 * tiles / 16;
     if (G > longest) G = longest;
