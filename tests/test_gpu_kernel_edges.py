@@ -340,10 +340,10 @@ def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
-# .. where a rule takes a call to other segments or the other kernel: d_v 128 from a state, where three segments are cut from 9 tiles on or, up to 80 groups and 352
+# .. where a rule takes a call to other segments or the other kernel: up to 32 groups from a state from 257 tokens on, up to 40 from 385 on; d_v 128 from a state, where three segments are cut from 9 tiles on or, up to 80 groups and 352
 # tokens, the kernel of short calls takes them, and 65 to 85 groups in three segments from 25 tiles on; every unit against one with the same values
 @pytest.mark.parametrize("U,dv,N1,N", [(33, 128, 33, 33 + 256), (33, 128, 33, 33 + 257), (40, 128, 40, 40 + 352), (40, 128, 40, 40 + 353), (41, 128, 20, 20 + 288),
-                                       (41, 128, 64, 64 + 289), (42, 128, 97, 97 + 513), (43, 128, 50, 50 + 600), (37, 128, 64, 64 + 800), (65, 64, 0, 768), (83, 64, 769, 769 + 769), (85, 64, 0, 864), (36, 128, 0, 801)])
+                                       (41, 128, 64, 64 + 289), (42, 128, 97, 97 + 513), (43, 128, 50, 50 + 600), (37, 128, 64, 64 + 800), (31, 64, 70, 70 + 257), (33, 64, 384, 384 + 385), (65, 64, 0, 768), (83, 64, 769, 769 + 769), (85, 64, 0, 864), (36, 128, 0, 801)])
 def test_prefill_dp32_rules(based, U, dv, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
     few = min(U, 5)
