@@ -128,13 +128,13 @@ template <int DP, typename T> constexpr bool HAS_SEGMENTS = DP != 16 || !std::is
 
 // The launch covers `slices` slices of 64 columns from first_slice on.
 // has_init: bit 0 an initial state is given, bit 2 the outputs are the numerators alone.
-// A unit's slice has `slots` entries, those of the segment before which a segment starts end with first + seg * pieces - 1.
-// INCREMENT: state increment of the segment (or piece) only, written to entry first + seg (segment 0 also converts the caller's state
+// A unit's slice has G entries, those of the segments before a segment end with first + seg * pieces - 1.
+// INCREMENT: state increment of the segment (or piece; of the first segment's two, the first one is the longer) only, written to entry first + seg (segment 0 also converts the caller's state
 // into entry 0: the main launch overwrites that buffer while other segments may still be starting).
 template <int DP, int DV, typename T, bool INCREMENT>
 __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                            const T *__restrict__ v, T *__restrict__ y, float *state,
-                                                           int has_init, int N, float *ws, int seg_len, int G, int slots, int first, int pieces,
+                                                           int has_init, int N, float *ws, int seg_len, int G, int first, int pieces,
                                                            int first_slice, int slices, int local, DecayArg dec)
 {
     constexpr int NB = blocks(DP), NT = tiles(DP), SL = DV / COLS, D = feature_dim(DP);
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     __shared__ float den[2][NW][16];
 
     const bool numerator_only = (has_init & 4) != 0, init = (has_init & 1) != 0;
-    const int gseg = INCREMENT ? G - 1 : G;
+    const int gseg = INCREMENT ? (G - 1) * pieces : G;
     // The workgroups of a unit's slice run on one XCD (workgroup index mod 8), whose L2 then holds the entries that they write and sum, for the first `local`
     // slices, a multiple of 8; the rest's run on all XCDs.  (All on all XCDs, and this, us: fp32, 16 units, d' 32 N 777 110.7, 95.2, d' 8 N 1000 20.9,
     // 18.3; bf16, d' 24 16 units N 2048 141.2, 132.5, d' 8 33 units N 4096 66.3, 59.4.)  Fewer than 8 slices have a row of the grid each: dealt out with them
@@ -164,14 +164,15 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
     }
     const int u = slices == 1 ? us : (uint32_t)us / SL, slice = first_slice + (slices == 1 ? 0 : (uint32_t)us % SL), col0 = slice * COLS;   // (slices: 1 or SL)
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, n = lane & 15;
-    const int begin = seg * seg_len, end = min(N, begin + seg_len);
+    const int len = INCREMENT && pieces == 2 ? (seg_len + 2 * C - 1) / (2 * C) * C : seg_len;
+    const int begin = seg * len, end = min(INCREMENT ? (G - 1) * seg_len : N, begin + len);
 
     const T *qu = q + (size_t)u * N * DP, *ku = k + (size_t)u * N * DP;
     const T *vu = v + (size_t)u * N * DV + col0 + 16 * w + n;
     T *yu = y + (size_t)u * N * DV + col0 + 16 * w;
     float *Su = state ? state + (size_t)u * state_stride(DP, DV) + col0 : nullptr;
     float *zu = state ? state + (size_t)u * state_stride(DP, DV) + (size_t)D * DV : nullptr;
-    float *entries = ws ? ws + ((size_t)u * SL + slice) * slots * entry_floats(DP) : nullptr;
+    float *entries = ws ? ws + ((size_t)u * SL + slice) * G * entry_floats(DP) : nullptr;
     auto entry_s = [&](int e) { return entries + (size_t)e * entry_floats(DP) + (size_t)w * NT * 256 + 4 * lane; };
     auto entry_z = [&](int e) { return entries + (size_t)e * entry_floats(DP) + (size_t)NW * NT * 256; };
 
@@ -549,11 +550,13 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     constexpr int SL = DV / COLS;
     int G = HAS_SEGMENTS<DP, T> ? segments(U, N, DP, DV) : 1;
     // The increment of the first of two segments is shared by two workgroups where entry 0 is free for the second's: one to a unit's slice left half of
-    // the chip idle.  (us, one and two: d' 32, fp32, 100 units N 200 105, 93, N 512 212, 186, 90 units N 1024 395, 336, d_v 128, 60 units N 700 280, 242; d' 24, bf16,
-    // 200 units N 160 74.0, 67.9, N 512 178, 172, 256 units N 1024 329, 313; d' 8, fp32, 350 units N 1000 110.7, 103.5, but bf16, 400 units N 200 37.1, 39.6, N
-    // 512 74.1, 73.9.)
-    const bool shared = G == 2 && !(has_init & 1) && !dec.gamma && (DP > 8 || N >= 640);
-    const int len = shared ? (segment_len(N, G) + 2 * C - 1) / (2 * C) * (2 * C) : segment_len(N, G);
+    // the chip idle.  Where the rest of the sequence is an odd number of chunks the first segment takes one more: its pieces are no longer for it.  (us, one
+    // and two: d' 32, fp32, 100 units N 160 83.2, 73.1, N 512 210, 183, 90 units N 1024 395, 335, d_v 128, 60 units N 700 280, 242; d' 24, bf16, 200 units N
+    // 160 66.8, 66.2, N 200 78.9, 78.7, N 224 85.9, 83.4, N 512 172, 165, 256 units N 200 80.2, 80.6, N 1024 328, 310; d' 8, fp32, 350 units N 512 61.4, 58.1, N
+    // 1000 110.7, 102.6, bf16, 400 units N 320 50.0, 50.0, N 512 73.5, 72.6, N 1000 136.1, 130.8.  Without the one more, d' 32, 100 units N 160 79.8, N 224 98.8;
+    // with the first segment rounded up to two equal pieces, d' 24, bf16, 200 units N 200 83.6, N 336 119.5 instead of 114.7.)
+    const bool shared = G == 2 && !(has_init & 1) && !dec.gamma && (DP == 32 || N > (DP == 24 ? 208 : 511));
+    const int len = segment_len(N, G) + (shared && (N + C - 1) / C % 4 == 2 ? C : 0);
     while (G > 1 && (G - 1) * len >= N) --G;   // rounding the length up can empty trailing segments
     if ((long long)U * SL * G >= (1ll << 31)) return hipErrorInvalidValue;
     float *ws = static_cast<float *>(workspace);
@@ -561,8 +564,8 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
         constexpr bool INC = decltype(increment)::value;
         const int pieces = shared ? 2 : 1, parts = INC ? (G - 1) * pieces : G, all = U * slices, local = all / 8 * 8;
         hipLaunchKernelGGL((prefill_kernel<DP, DV, T, INC>), local ? dim3((unsigned)(all * parts)) : dim3(parts, all), dim3(64 * NW), 0, s, (const T *)q,
-                           (const T *)k, (const T *)v, (T *)y, state, has_init, N, ws, INC ? len / pieces : len, INC ? parts + 1 : G, G,
-                           shared ? 0 : 1, pieces, first_slice, slices, local, dec);
+                           (const T *)k, (const T *)v, (T *)y, state, has_init, N, ws, len, G, shared ? 0 : 1, pieces,
+                           first_slice, slices, local, dec);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;
