@@ -532,7 +532,7 @@ __global__ __launch_bounds__(64 * NW, resident(DP)) void prefill_kernel(const T 
 // over the entries cost what the shorter chain gives), at most 64.  (d' 16, d_v 64, bf16 with decay: 128 units of 2048 tokens 2
 // segments 315 us, 4 237, 6 = a full round 226, 8 275; 16 units: 300 tokens 1 segment 66, 2 61, 4 41; 777 tokens 6 66, 12 59, 24 76.
 // fp32, 16 units: 777 tokens at d' 32 6 segments 137, 12 109; d' 8, 500 tokens 1 segment 51, 4 23, 8 17, 16 18; 14926 tokens 16
-// segments 145, 32 103, 64 99.  The scratch of fp32 calls at d' 16 is sized by this rule too.)
+// segments 145, 32 103, 64 99.  All from before a unit's segments shared an XCD.  The scratch of fp32 calls at d' 16 is sized by this rule too.)
 inline int segments(int U, int N, int dp, int dv)
 {
     const long groups = (long)U * (dv / COLS);

@@ -201,9 +201,10 @@ struct DecayArg {
 };
 
 // The launch covers `slices` slices of 64 columns from first_slice on.  has_init: bit 0 an initial state is given, bit 2 the outputs are
-// the numerators alone.  INC: state increment of the segment only, to entry 1 + seg (segment 0 also converts the caller's state
-// into entry 0).
-// SHARED: the increments are shared out over `shares` workgroups of inc_len tokens (else one to a segment).
+// the numerators alone.  INC: state increments only.  A unit's slice has `slots` entries: entry 0 is the caller's state, if there is one (segment 0 also
+// converts it), then come the increments in the order of their tokens, one to a segment.
+// SHARED: the increments are shared out over `shares` workgroups of inc_len tokens (else one to a segment); a share that starts inside a segment has an entry
+// of its own.
 template <int DV, bool INC, bool DECAY, bool SHARED>
 __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict__ q, const float *__restrict__ k,
                                                         const float *__restrict__ v, float *__restrict__ y, float *state, int has_init,
@@ -762,7 +763,8 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     if (writes_state) export_image();
 }
 
-// Segments: one round of the chip (two workgroups to a CU), segments of at least 64 tokens, at most 64 of them.
+// Segments: one round of the chip (two workgroups to a CU), segments of at least 64 tokens, at most 64 of them.  (The line is that of the fp32 matrix kernel,
+// whose scratch this one uses; not measured again since a unit's segments share an XCD.)
 inline int segments(int U, int N, int dv)
 {
     const long groups = (long)U * (dv / COLS);
