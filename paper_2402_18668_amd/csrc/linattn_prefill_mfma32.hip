@@ -10,7 +10,8 @@
 // counts.  528 pair rows instead of 1024; the constant's row is kept apart.  Rows are built without the 1 / sqrt(2) of Eq. 4: the readout weighs a
 // pair of different features 1 and a square (tile 0) 1/2.  Keys are staged halved, rows hold sum (k_a / 2) (k_b / 2) v, sum (k_a / 2) v, and the outputs
 // and denominators are summed as quarters: then nothing inside overflows before the state of Eq. 4 and the kernel's values do.  (Powers of two: no result
-// changes by it.  Unhalved, 32 units of 16384 tokens take 161.8 us instead of 162.7, 512 of 2048 238.8 and 238.7.)
+// changes by it.  Unhalved and now, us, inputs from memory: 32 units of 16384 tokens 172.8, 172.9, 512 of 2048 235.8, 235.1, 128 of 2048 94.8, 93.7, 128 of
+// 200 from a state 30.0, 30.4; with the rows of V written after those of K 174.0, 235.1, 94.5, 30.3.)
 //
 // Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment).  Wave w owns tiles 2 w, 2 w + 1 (both column tiles of
 // 32) and one more product, in accumulators throughout.  A block's phases:
@@ -434,6 +435,9 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
             for (int h = 0; h < 4; ++h) raw.v[h] = (tid >> 3) + 64 * h < rows ? raw.v[h] : zero;
         }
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
         u32x4 half[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -450,9 +454,6 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             if (!INC) *reinterpret_cast<u32x4 *>(&krow[t0 + h][8 * (c ^ ((t0 >> 2) & 3))]) = half[h];
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-            *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
     };
 
     // ---- operands ---------------------------------------------------------------------------------
