@@ -346,7 +346,7 @@ def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
     check_close(z[:few], zw, TOL["bf16"], "z")
 
 
-# .. where a rule takes a call to other segments or the other kernel: up to 32 groups from a state from 257 tokens on, up to 40 from 385 on; d_v 128 from a
+# .. where a rule takes a call to other segments or the other kernel: up to 32 groups from a state of 257 to 352 tokens, up to 40 from 385 on; d_v 128 from a
 # state, where three segments are cut from 9 tiles on or, up to 80 groups and 352 tokens, the kernel of short calls takes them; 65 to 85 groups in three
 # segments from 25 tiles on, 86 to 128 in two from 41 (up to 104 groups without a state) or 56; every unit against one with the same values
 @pytest.mark.parametrize("U,dv,N1,N", [(33, 128, 33, 33 + 256), (33, 128, 33, 33 + 257), (40, 128, 40, 40 + 352), (40, 128, 40, 40 + 353), (41, 128, 20, 20 + 288),
