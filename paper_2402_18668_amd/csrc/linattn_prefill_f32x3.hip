@@ -788,14 +788,14 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     const size_t room = prefill_f32_workspace_bytes(U, N, DP, DV) / (sizeof(float) * kEntryFloats * U * SL);   // entries
     if (G > 1 && (size_t)G > room) return hipErrorInvalidValue;
     // Shares of the increments: G, where what would be idle is worth the entries that come on top, which take time to write and to sum: two or three
-    // segments of 256 tokens or more, four of 384 (more segments leave little idle), and where the workspace holds two entries a segment.
-    // (us, G - 1 shares and G: 200 units of 448 tokens 62.3, 62.0, of 512 69.2, 67.5, of 768 96.5, 92.7, of 2048 237, 222; 256 of 448 64.6, 65.2, of 512
-    // 71.6, 71.0; 160 of 448 49.2, 50.7, of 768 74.9, 73.7, of 2048 176, 167; 128 of 512 46.0, 48.3, of 1024 77.9, 78.3, of 1400 100.2, 101.2, of 1500 105.4,
-    // 104.3, of 2048 139.9, 137.8; 104 of 1400 96.6, 96.2, of 1600 108.8, 105.1; 110 of 4096 255.7, 246.2; d_v 128: 100 of 512 69.2, 67.6, of 2048 234.6, 221.3.)
+    // segments of 256 tokens or more, four of 1024 (more segments leave little idle), and where the workspace holds two entries a segment.
+    // (us, inputs from memory, G - 1 shares and G: 200 units of 400 tokens 60.5, 58.9, of 512 71.1, 69.1, of 768 98.8, 94.7, of 2048 238, 222; 256 of 449 68.8, 67.1, of
+    // 512 73.2, 72.5; from a state 200 of 400 65.1, 66.5; 150 of 449 53.3, 54.6, of 700 72.0, 70.5, of 2048 174.7, 165.8; 170 of 768 76.9, 76.8; 128 of 1500 106.9,
+    // 106.3, of 2048 142.3, 141.1, on another GPU 144.7, 147.6, of 4100 275.0, 270.3; 110 of 2048 136.2, 131.9.)
     // With G chunks or more to a segment no share ends with a segment but the last: the i-th ends less than i chunks past i - i / G segments.
     int inc_len = len, entries = G;
     const int share = ((G - 1) * (len / C) + G - 1) / G * C, share_entries = 2 * (G - 1) + (has_init & 1);
-    const bool shared = !DECAY && G > 1 && G <= 4 && len >= (G < 4 ? 256 : 384) && (size_t)share_entries <= room;
+    const bool shared = !DECAY && G > 1 && G <= 4 && len >= (G < 4 ? 256 : 1024) && (size_t)share_entries <= room;
     if (shared) {
         inc_len = share;
         entries = share_entries;
