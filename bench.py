@@ -44,7 +44,7 @@ MEASURED_TRAFFIC = {
     # key: (entry point, workload) -> (bytes per launch, source files the kernel is built from, their hash)
     ("based_prefill", "prefill_1p3b"): (338461696, ("linattn_prefill_mfma.hip",), "1aaf9c90eb32"),
     ("based_prefill", "prefill_360m"): (119147840, ("linattn_prefill_mfma.hip",), "1aaf9c90eb32"),
-    ("based_prefill", "prefill_long"): (372214208, ("linattn_prefill_mfma32.hip",), "839f7a5ba2d4"),   # both launches
+    ("based_prefill", "prefill_long"): (372231520, ("linattn_prefill_mfma32.hip",), "3d4e0f93d89e"),   # both launches
     ("based_swa_prefill", "prefill_1p3b"): (553832896, ("swa_prefill_mfma16.hip",), "6d81285cd196"),
     ("based_swa_prefill", "prefill_360m"): (142855936, ("swa_prefill_mfma.hip",), "3e1a66d76ef7"),
     ("based_swa_prefill", "prefill_long"): (277081344, ("swa_prefill_mfma.hip",), "3e1a66d76ef7"),
