@@ -554,8 +554,10 @@ hipError_t launch(const void *q, const void *k, const void *v, void *y, float *s
     // and two: d' 32, fp32, 100 units N 160 83.2, 73.1, N 512 210, 183, 90 units N 1024 395, 335, d_v 128, 60 units N 700 280, 242; d' 24, bf16, 200 units N
     // 160 66.8, 66.2, N 200 78.9, 78.7, N 224 85.9, 83.4, N 512 172, 165, 256 units N 200 80.2, 80.6, N 1024 328, 310; d' 8, fp32, 350 units N 512 61.4, 58.1, N
     // 1000 110.7, 102.6, bf16, 400 units N 320 50.0, 50.0, N 512 73.5, 72.6, N 1000 136.1, 130.8.  Without the one more, d' 32, 100 units N 160 79.8, N 224 98.8;
-    // with the first segment rounded up to two equal pieces, d' 24, bf16, 200 units N 200 83.6, N 336 119.5 instead of 114.7.)
-    const bool shared = G == 2 && !(has_init & 1) && !dec.gamma && (DP == 32 || N > (DP == 24 ? 208 : 511));
+    // with the first segment rounded up to two equal pieces, d' 24, bf16, 200 units N 200 83.6, N 336 119.5 instead of 114.7.  Where it is the number of tokens that allows no third segment there is room for the second piece: d' 24, 16 units
+    // N 160 48.6, 41.8, d' 8, fp32, 4 units N 168 17.3, 15.3, bf16, 30 units N 176 19.5, 17.2, but 300 units N 152 27.0, 27.3, 340 27.5, 27.9.)
+    const bool room = (DP == 8 ? 4l : 3l) * U * SL <= 256 * resident(DP);
+    const bool shared = G == 2 && !(has_init & 1) && !dec.gamma && (room || DP == 32 || N > (DP == 24 ? 208 : 511));
     const int len = segment_len(N, G) + (shared && (N + C - 1) / C % 4 == 2 ? C : 0);
     while (G > 1 && (G - 1) * len >= N) --G;   // rounding the length up can empty trailing segments
     if ((long long)U * SL * G >= (1ll << 31)) return hipErrorInvalidValue;

@@ -282,15 +282,16 @@ def test_prefill_fp32_shared_increments(based, U, dv, N, init):
     check_close(z[:few], zw, TOL["f32"], "z")
 
 
-# .. and on the fp32 matrix instructions: two segments, the increment of the first one shared by two workgroups (d' = 24: from 209 tokens on, 8: from 512 on), an even
+# .. and on the fp32 matrix instructions: two segments, the increment of the first one shared by two workgroups (d' = 24: from 209 tokens on, 8: from 512 on, or with few units), an even
 # and an odd number of chunks in it, and one more than half of them; then from the state that this left, where it is not
 @pytest.mark.parametrize("dtype,dp,dv,U,N1,N", [("f32", 32, 64, 90, 200, 390), ("f32", 32, 128, 64, 129, 129), ("bf16", 24, 128, 100, 170, 345), ("f32", 24, 64, 256, 161, 161),
                                                 ("f32", 8, 64, 343, 641, 800), ("bf16", 8, 128, 256, 639, 639), ("f32", 32, 64, 100, 160, 160), ("f32", 32, 128, 50, 145, 145),
                                                 ("bf16", 24, 64, 180, 209, 417), ("f32", 24, 128, 90, 224, 300), ("bf16", 24, 64, 200, 256, 256), ("f32", 24, 64, 172, 273, 273),
-                                                ("bf16", 8, 64, 400, 511, 600), ("f32", 8, 128, 200, 512, 512), ("bf16", 8, 64, 345, 543, 543), ("f32", 8, 64, 360, 561, 561)])
+                                                ("bf16", 8, 64, 400, 511, 600), ("f32", 8, 128, 200, 512, 512), ("bf16", 8, 64, 345, 543, 543), ("f32", 8, 64, 360, 561, 561),
+                                                ("f32", 24, 64, 4, 150, 150), ("bf16", 24, 128, 85, 128, 128), ("bf16", 24, 128, 86, 129, 129), ("bf16", 8, 64, 3, 190, 190), ("f32", 8, 128, 128, 160, 160), ("f32", 8, 128, 129, 160, 160)])
 def test_prefill_fp32_halved_increment(based, dtype, dp, dv, U, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": dp, "dtype": dtype})
-    few = 5
+    few = min(U, 5)
     q, k, v = synth.linattn_inputs(wl, units=few, N=N)
     state, at = based.alloc_state(1, U, dp, dv), np.arange(U) % few
     got = [down(based.prefill(*(up(a[at, lo:hi], dtype, (1, U, hi - lo, d)) for a, d in ((q, dp), (k, dp), (v, dv))), state=state,
