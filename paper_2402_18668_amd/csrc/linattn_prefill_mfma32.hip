@@ -10,8 +10,8 @@
 // counts.  528 pair rows instead of 1024; the constant's row is kept apart.  Rows are built without the 1 / sqrt(2) of Eq. 4: the readout weighs a
 // pair of different features 1 and a square (tile 0) 1/2.  Keys are staged halved, rows hold sum (k_a / 2) (k_b / 2) v, sum (k_a / 2) v, and the outputs
 // and denominators are summed as quarters: then nothing inside overflows before the state of Eq. 4 and the kernel's values do.  (Powers of two: no result
-// changes by it.  Unhalved and now, us, inputs from memory: 32 units of 16384 tokens 172.8, 172.9, 512 of 2048 235.8, 235.1, 128 of 2048 94.8, 93.7, 128 of
-// 200 from a state 30.0, 30.4; with the rows of V written after those of K 174.0, 235.1, 94.5, 30.3.)
+// changes by it.  Unhalved and now, us, inputs from memory: 32 units of 16384 tokens 166.0, 166.9, 512 of 2048 236.6, 236.0, 128 of 2048 91.6, 91.3, 16 of 2048
+// 36.8, 37.0, 2 of 105 12.5, 12.6.)
 //
 // Work split.  A workgroup of eight waves takes 64 columns of one (unit, segment).  Wave w owns tiles 2 w, 2 w + 1 (both column tiles of
 // 32) and one more product, in accumulators throughout.  A block's phases:
@@ -167,7 +167,9 @@ __device__ __forceinline__ CanonRows canon_rows(int T, int fl, bool packed_state
 }
 // what a row is multiplied with on its way out (sum (k_a / 2) (k_b / 2) v to sum k_a k_b v / sqrt(2), sum (k_a / 2) v to sum k_a v)
 __device__ __forceinline__ float out_scale(CanonRows c) { return c.r1 > DP ? 4.f * kRsqrt2 : 2.f; }
-__device__ __forceinline__ float in_scale(CanonRows c) { return c.r1 > DP ? 0.5f * kRsqrt2 : 0.5f; }   // and in
+// and in, and which rows are padding, from the tile: their canonical rows, worked out again, cost a call from a state 1.3 us (7 units of 152 tokens 23.8, 22.4)
+__device__ __forceinline__ float in_scale(int T) { return T == 16 ? 0.5f : 0.5f * kRsqrt2; }
+__device__ __forceinline__ bool is_padding(int T, int fl) { return T == 17 && (fl & 8) != 0; }
 
 constexpr int kMaxSegments = 16;
 struct SegTable { int begin[kMaxSegments + 1]; };
@@ -297,9 +299,8 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
                 for (int j = 0; j < BATCH; ++j) {
                     const int i = (s0 + j) * NT + tid, row = i >> 3;
-                    const CanonRows cr = canon_rows(row >> 5, row & 31, packed_state);
                     *reinterpret_cast<f32x4 *>(image + row * IMG_LD + 4 * (i & 7)) =
-                        cr.r1 < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : (0.5f * t[j][0] + 0.5f * t[j][1]) * in_scale(cr);   // (halves: the sum may overflow)
+                        is_padding(row >> 5, row & 31) ? f32x4{0.f, 0.f, 0.f, 0.f} : (0.5f * t[j][0] + 0.5f * t[j][1]) * in_scale(row >> 5);   // (halves: the sum may overflow)
                 }
             }
             __syncthreads();
@@ -435,9 +436,6 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
             for (int h = 0; h < 4; ++h) raw.v[h] = (tid >> 3) + 64 * h < rows ? raw.v[h] : zero;
         }
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-            *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
         u32x4 half[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -454,6 +452,9 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             if (!INC) *reinterpret_cast<u32x4 *>(&krow[t0 + h][8 * (c ^ ((t0 >> 2) & 3))]) = half[h];
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            *reinterpret_cast<u32x4 *>(&kv.v[(tid >> 3) + 64 * h][8 * ((tid & 7) ^ (((tid >> 4) & 1) << 2))]) = raw.v[h];
     };
 
     // ---- operands ---------------------------------------------------------------------------------
