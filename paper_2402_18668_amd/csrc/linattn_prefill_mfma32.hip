@@ -839,7 +839,8 @@ __global__ __launch_bounds__(NT, 2) void prefill_kernel(
 // 1024 48.6, 54.2, N 4096 178, 156).  Two segments whose increment two workgroups share (without a state) are the shorter chain from 41 tiles on with up to 104 groups
 // (one and two: 87 units N 1000 47.4, 47.7, N 1400 63.4, 58.3, N 1664 73.0, 64.5; 100 units N 1280 57.3, 57.8, N 1400 63.7, 60.8, N 1664 73.4, 67.6; 128
 // units N 1400 64.1, 67.3, N 1664 73.7, 76.0).  At d_v 128 a state goes through a launch of its own anyhow, which increments can share: room for three is used from 9
-// tiles on (one and three: 33 units N 384 40.1, 38.2, N 513 48.4, 40.3, N 769 58.3, 46.1; 42 units N 289 40.1, 39.8, N 448 43.8, 41.5, N 769 59.5, 48.9).
+// tiles on (one and three: 33 units N 384 40.1, 38.2, N 513 48.4, 40.3, N 769 58.3, 46.1; 42 units N 289 40.1, 39.8, N 448 43.8, 41.5, N 769 59.5, 48.9; with
+// the import of a state as it was, 1 us more for either).
 static int pick_segments(int U, int N, int dv, int has_init)
 {
     const int groups = U * (dv / COLS), tiles = (N + QT - 1) / QT, room = 256 / groups;

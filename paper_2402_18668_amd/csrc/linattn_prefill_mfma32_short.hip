@@ -34,7 +34,7 @@
 // partial outputs; 5000 cycles in all, because the eight waves do the same things at the same time.  (Operands built by one wave and shared through
 // LDS: the same time, more LDS.  Four waves with 512 registers and half the exchange: the same, a lone wave issues a
 // vector instruction every 4 cycles instead of 2.  Reading operands' rows a phase ahead: no gain.)
-// Measured (d_v 64, us, against blocks of 256 tokens): 16 units from a state, of 17 tokens 15.6, 20.3, of 64 17.9, 20.6, of 128 22.0, 21.8.
+// Measured (d_v 64, us, against blocks of 256 tokens): 16 units from a state, of 64 tokens 17.8, 19.2, of 96 20.1, 20.2.
 #include "common.h"
 
 #include <cmath>
@@ -783,34 +783,38 @@ static int make_segments(int N, int G, SegTable &t)
 
 }  // namespace dp32s
 
-static constexpr int kLongest = 736, kLongestMid = 352;
+static constexpr int kLongest[2] = {736, 512};   // without and from a state
 
-// Up to 32 tokens, up to 96 from a state (a block's readout is one wave's for 32 queries; here all eight waves have a part), and from 257, 385 or 513
-// tokens on, by the number of groups of 64 columns, up to 736 (a last block that is mostly empty, chains of increments of whole blocks).  From a state, 257 to 352 tokens
-// of a few more groups; at d_v 128, where blocks take a state through a launch of their own, from 225 tokens on, and 257 to 352 tokens of up to 80 groups.
+// Up to 32 tokens, up to 96 from a state (a block's readout is one wave's for 32 queries; here all eight waves have a part).  From 257, 385 or 513
+// tokens on, by the number of groups of 64 columns, up to 736 (a last block that is mostly empty, chains of increments of whole blocks).  From a state, which
+// blocks read faster, 257 to 512 tokens of up to 24 groups; at d_v 128, where they take it through a launch of their own, 225 to 512 of up to 64.
 // (This kernel and blocks, us: 16 groups N 32 10.0, 11.9, N 33 12.2, 12.0, N 272 20.2, 20.2, N 448 23.9, 25.3, N 768 30.0, 28.2; 200 groups N 32 14.9, 15.2, N 33 17.0,
-// 15.3; 512 groups N 32 30.5, 30.4, N 33 34.7, 30.8; 8 groups N 384 21.6, 22.5, N 640 25.9, 28.3; 24 groups N 300 22.1, 21.8, from a state 28.9, 30.6, N 416
-// 22.9, 25.4, N 512 25.9, 26.4; 32 groups N 300 23.0, 22.2, from a state 30.7, 31.2, N 384 33.3, 32.3, without 23.8, 23.4, N 385 24.0, 25.7, N 416 23.9, 25.7, N 480 25.7, 26.6, N 512 26.8, 26.6, N 704 29.7,
-// 30.7, N 768 32.1, 30.9; 48 groups N 384 25.7, 23.9, N 480 28.6, 27.2; 64 groups N 512 30.3, 27.7, N 700 34.1, 34.2, N 1000 from a state 55.6, 52.1; d_v
-// 128 from a state, 8 units N 160 28.8, 28.8, N 227 26.8, 29.7, N 400 30.2, 38.3, N 600 33.0, 33.1, 32 units N 227 33.2, 33.2, N 300 35.7, 38.5, N 512 39.3, 43.1,
-// N 600 41.4, 40.2, 48 units N 400 45.7, 44.4, 36 units N 225 36.0, 35.0, N 257 36.2, 37.9, N 320 37.0, 38.2, N 384 39.0, 38.9, 41 units N 320 40.0, 39.7.)
+// 15.3; 512 groups N 32 30.5, 30.4, N 33 34.7, 30.8; 8 groups N 384 21.6, 22.5, N 640 25.9, 28.3; 24 groups N 300 22.1, 21.8, N 416 22.9, 25.4, N 512 25.9,
+// 26.4; 32 groups N 300 23.0, 22.2, N 384 23.8, 23.4, N 385 24.0, 25.7, N 416 23.9, 25.7, N 480 25.7, 26.6, N 512 26.8, 26.6, N 704 29.7, 30.7, N 768 32.1,
+// 30.9; 48 groups N 384 25.7, 23.9, N 480 28.6, 27.2; 64 groups N 512 30.3, 27.7, N 700 34.1, 34.2.  From a state 16 groups N 300 28.2, 29.3, N 512 33.3, 33.8, N
+// 513 33.3, 32.4; 32 groups N 300 30.8, 30.0; d_v 128, 8 units N 225 27.4, 29.0, N 400 30.8, 37.8, N 513 33.4, 32.5; 32 units N 225 34.2, 33.0, N 300 36.9, 38.1, N
+// 512 40.9, 42.5, N 513 40.2, 39.2.)
 bool prefill_mfma32_short_takes(int U, int N, int dv, int has_init)
 {
     const int groups = U * (dv / dp32s::COLS);
-    const bool two = has_init && dv == 128, mid = has_init && N > 256 && N <= kLongestMid;
-    const int from = two ? 224 : groups <= (mid ? 32 : 28) ? 256 : groups <= 40 ? 384 : 512;
-    return N <= (has_init ? 96 : 32) || (groups <= (two && mid ? 80 : 64) && N > from && N <= kLongest);
+    if (N <= (has_init ? 96 : 32)) return true;
+    const int most = has_init && dv == 64 ? 24 : 64;
+    const int from = has_init ? (dv == 64 ? 256 : 224) : groups <= 28 ? 256 : groups <= 40 ? 384 : 512;
+    return groups <= most && N > from && N <= kLongest[has_init];
 }
 
 // One entry per (unit, slice, segment), for a call of N tokens and for every shorter one that comes here: segments only get more with N.
 size_t prefill_mfma32_short_workspace_bytes(int U, int N, int dv)
 {
     const int groups = U * (dv / dp32s::COLS);
-    for (int longest : {kLongest, kLongestMid}) {
-        if (longest > N) longest = N;
-        if (prefill_mfma32_short_takes(U, longest, dv, 1)) return (size_t)groups * dp32s::pick_segments(groups, longest) * dp32s::kWsEntryFloats * sizeof(float);
+    int most = 0;
+    for (int has_init = 0; has_init < 2; ++has_init) {
+        const int longest = N < kLongest[has_init] ? N : kLongest[has_init];
+        if (!prefill_mfma32_short_takes(U, longest, dv, has_init)) continue;   // (up to 96 tokens are one segment, for which blocks need as much)
+        const int G = dp32s::pick_segments(groups, longest);
+        if (G > most) most = G;
     }
-    return 0;   // (up to 96 tokens are one segment, for which blocks need as much)
+    return (size_t)groups * most * dp32s::kWsEntryFloats * sizeof(float);
 }
 
 hipError_t launch_prefill_mfma32_short(const void *q, const void *k, const void *v, void *y, float *state,
