@@ -783,16 +783,18 @@ static int make_segments(int N, int G, SegTable &t)
 
 }  // namespace dp32s
 
-static constexpr int kLongest[2] = {736, 512};   // without and from a state
+static constexpr int kLongest[2] = {736, 512};   // without and from a state (there 609 to 672 too: the calls of that length without one need as much)
 
 // Up to 32 tokens, up to 96 from a state (a block's readout is one wave's for 32 queries; here all eight waves have a part).  From 257, 385 or 513
 // tokens on, by the number of groups of 64 columns, up to 736 (a last block that is mostly empty, chains of increments of whole blocks).  From a state, which
-// blocks read faster, 257 to 512 tokens of up to 24 groups; at d_v 128, where they take it through a launch of their own, 225 to 512 of up to 64.
+// blocks read faster, 257 to 512 tokens of up to 24 groups; at d_v 128, where they take it through a launch of their own, 225 to 512 of up to 64; at both widths
+// 609 to 672 of up to 28 groups (20 and 21 tiles in three segments of blocks; 22 are four).
 // (This kernel and blocks, us: 16 groups N 32 10.0, 11.9, N 33 12.2, 12.0, N 272 20.2, 20.2, N 448 23.9, 25.3, N 768 30.0, 28.2; 200 groups N 32 14.9, 15.2, N 33 17.0,
 // 15.3; 512 groups N 32 30.5, 30.4, N 33 34.7, 30.8; 8 groups N 384 21.6, 22.5, N 640 25.9, 28.3; 24 groups N 300 22.1, 21.8, N 416 22.9, 25.4, N 512 25.9,
 // 26.4; 32 groups N 300 23.0, 22.2, N 384 23.8, 23.4, N 385 24.0, 25.7, N 416 23.9, 25.7, N 480 25.7, 26.6, N 512 26.8, 26.6, N 704 29.7, 30.7, N 768 32.1,
 // 30.9; 48 groups N 384 25.7, 23.9, N 480 28.6, 27.2; 64 groups N 512 30.3, 27.7, N 700 34.1, 34.2.  From a state 16 groups N 300 28.2, 29.3, N 512 33.3, 33.8, N
-// 513 33.3, 32.4; 32 groups N 300 30.8, 30.0; d_v 128, 8 units N 225 27.4, 29.0, N 400 30.8, 37.8, N 513 33.4, 32.5; 32 units N 225 34.2, 33.0, N 300 36.9, 38.1, N
+// 513 33.3, 32.4; 16 groups N 608 32.8, 32.0, N 609 33.0, 34.3, N 656 32.9, 34.3, N 673 32.9, 33.3; 28 groups N 608 35.9, 34.2, N 656 36.1,
+// 36.5, N 673 36.1, 35.8; 32 groups N 300 30.8, 30.0, N 640 37.0, 36.8; d_v 128, 8 units N 225 27.4, 29.0, N 400 30.8, 37.8, N 513 33.4, 32.5; 32 units N 225 34.2, 33.0, N 300 36.9, 38.1, N
 // 512 40.9, 42.5, N 513 40.2, 39.2.)
 bool prefill_mfma32_short_takes(int U, int N, int dv, int has_init)
 {
@@ -800,6 +802,7 @@ bool prefill_mfma32_short_takes(int U, int N, int dv, int has_init)
     if (N <= (has_init ? 96 : 32)) return true;
     const int most = has_init && dv == 64 ? 24 : 64;
     const int from = has_init ? (dv == 64 ? 256 : 224) : groups <= 28 ? 256 : groups <= 40 ? 384 : 512;
+    if (has_init && groups <= 28 && N > 608 && N <= 672) return true;
     return groups <= most && N > from && N <= kLongest[has_init];
 }
 

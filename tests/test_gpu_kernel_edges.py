@@ -347,13 +347,14 @@ def test_prefill_dp32_blocks(based, numerator, U, dv, N1, N):
     check_close(z[:few], zw, TOL["bf16"], "z")
 
 
-# .. where a rule takes a call to other segments or the other kernel: up to 24 groups from a state of 257 to 512 tokens, up to 40 without from 385 on; d_v 128
+# .. where a rule takes a call to other segments or the other kernel: up to 24 groups from a state of 257 to 512 tokens, up to 28 of 609 to 672, up to 40 without from 385 on; d_v 128
 # from a state of 225 to 512 tokens up to 64 groups, beyond in three segments from 9 tiles on; 65 to 85 groups in three
 # segments from 25 tiles on, 86 to 128 in two from 41 (up to 104 groups without a state) or 56; every unit against one with the same values
 @pytest.mark.parametrize("U,dv,N1,N", [(33, 128, 33, 33 + 256), (33, 128, 33, 33 + 257), (40, 128, 40, 40 + 352), (40, 128, 40, 40 + 353), (41, 128, 20, 20 + 288),
                                        (41, 128, 64, 64 + 289), (42, 128, 97, 97 + 513), (43, 128, 50, 50 + 600), (37, 128, 64, 64 + 800), (31, 64, 70, 70 + 257), (33, 64, 384, 384 + 385), (24, 64, 40, 40 + 257), (24, 64, 512, 512 + 512), (24, 64, 40, 40 + 513), (25, 64, 33, 33 + 300), (32, 128, 40, 40 + 512),
                                        (32, 128, 40, 40 + 513), (32, 128, 225, 225 + 224), (65, 64, 0, 768), (83, 64, 769, 769 + 769), (85, 64, 0, 864), (36, 128, 0, 801), (104, 64, 0, 1280), (104, 64, 0, 1281), (105, 64, 0, 1281), (90, 64, 33, 33 + 1760),
-                                       (90, 64, 33, 33 + 1761), (45, 128, 33, 33 + 1761), (64, 128, 40, 40 + 1800), (105, 64, 0, 1761)])
+                                       (90, 64, 33, 33 + 1761), (24, 64, 40, 40 + 608), (28, 64, 40, 40 + 609), (8, 64, 33, 33 + 672), (8, 64, 33, 33 + 673), (29, 64, 40, 40 + 640), (14, 128, 64, 64 + 640),
+                                       (45, 128, 33, 33 + 1761), (64, 128, 40, 40 + 1800), (105, 64, 0, 1761)])
 def test_prefill_dp32_rules(based, U, dv, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv, "d_feat": 32})
     few = min(U, 5)
