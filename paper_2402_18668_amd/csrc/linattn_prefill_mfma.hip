@@ -36,15 +36,16 @@
 // Pipeline.  The producers run one chunk ahead of the consumers: while the consumers multiply the
 // operands of chunk t (LDS generation t % 2), the producers stage the rows of chunk t + 1 (fetched
 // into registers during chunk t - 1), and build its operands into the other generation.  Per chunk
-// there is one workgroup barrier (chunk t + 1's operands are visible, chunk t's are free).  At d_v = 64 the staged rows exist twice
-// and are staged one chunk earlier still; at d_v = 128, where the LDS has no room for that, there is one
-// counter in LDS that the producer waves bump when their rows are staged and that only the waves
-// building from those rows poll.
+// there is one workgroup barrier (chunk t + 1's operands are visible, chunk t's are free).  The staged rows of K and Q exist twice and are staged one chunk
+// earlier still, so that nothing else is waited for.
 //
-// Measured (d_v 64, four producers and rows staged once, and as it is): 128 units of 2048 tokens 45.3 and 39.3 us (41.7 with six producers
-// alone); 200 units 60.5 and 52.0; 16 units of 777 tokens from a state 19.0 and 16.7 (here also the wait under the builds).  At d_v 128 neither helps: eight producers (12 waves of 168
-// registers) 87.7, rows staged twice 87.2 against 86.5 us for 256 units; what a CU takes for a chunk, 2.2 us with up to 160 of them at
-// work and 2.7 with all, is the consumers' 46 matrix instructions at one operand read from LDS each, the stores and the clock.
+// What bounds a chunk: the instruction stream of the waves, two to a SIMD, all about equally long (cycles of a chunk, d_v 64 / 128: consumers 2230 / 3430, the
+// one with the moments 3690; producers 2300-2600 / 3250-3580; at the barrier 2720 / 3800).  Three things shortened it from 3230 / 4420, where the consumers
+// set the pace: (1) the outputs are normalised and turned between the update's matrix instructions, and turned in registers (the halves of a wave exchange
+// quads) instead of through LDS, which each consumer waited for twice: the second half of its chunk 1950 -> 1150; (2) the rows of K and Q come into
+// the registers that an operand is built from as products with 0/1 matrices instead of as staged fp32 copies, whose 4-byte LDS writes and 28 KB of reads the
+// producers spent a third of their time on; (3) the moments and denominators at d_v 128 are a consumer's.  256 units of 2048 tokens, d_v 64 58 -> 51.5 us,
+// d_v 128 85.7 -> 83.1 (inputs out of cache; 84 -> 77 with three sets of buffers in turn).
 //
 // MFMA 32x32x16 register layouts used throughout (lane = 32 g + n):
 //   A operand: row n, k-slots 8g .. 8g+7;  B operand: column n, k-slots 8g .. 8g+7;
@@ -86,16 +87,11 @@ constexpr int DP = 16;            // d'
 constexpr int C = 64;             // chunk length (tokens)
 constexpr int NTILE = 5;          // state tiles of 32 rows
 constexpr int NSLAB = 2 * NTILE;  // feature slabs of 16 rows
-constexpr float kCK = 0.84089641525371454303f;   // 2^(-1/4): (c k_a)(c k_b) = k_a k_b / sqrt(2)
 constexpr float kCQ = 1.18920711500272106672f;   // 2^(+1/4): (c q_a)(c q_b) = sqrt(2) q_a q_b
-constexpr float kHalfInvCQ = 0.42044820762685725f;   // 0.5 / kCQ
+constexpr float kSqrt2 = 1.41421356237309504880f;
 
 // LDS strides (elements)
-constexpr int KTS_LD = C + 4;     // fp32 K^T rows
-constexpr int KT_ROWS = DP + 3;   // c_k k_a (16 rows); valid / c_k; valid * c_k; zeros
-constexpr int QS_LD = DP + 4;     // fp32 Q rows
 constexpr int RB_LD = DP + 8;     // bf16 row-major Q and K rows as given (48-byte stride)
-constexpr int YT_LD = 32 + 8;     // bf16 rows of a finished output tile on its way out (80-byte stride)
 
 // Workspace entry (one segment's state in accumulator layout): six slots of 16 registers x 64 lanes
 // per wave: slot 6c + T = tile T of the wave that owns columns 32c .. 32c+31, slot 6c + 5 = the
@@ -106,21 +102,18 @@ constexpr int WS_WAVE_SLOTS = 6;
 constexpr size_t kSlotFloats = 16 * 64;
 __host__ __device__ constexpr size_t entry_floats(int nc) { return (size_t)nc * WS_WAVE_SLOTS * kSlotFloats; }
 
-// Producer waves beside NC consumers.
+// Producer waves beside NC consumers, and the wave that has the moments, which travel in the sixth slot of column tile x_tile.
 __host__ __device__ constexpr int producers(int nc) { return nc == 2 ? 6 : 4; }
-// The staged rows of K and Q exist twice where the LDS has the room: then building one chunk's operands and staging the next one's rows
-// need nothing but the chunk's barrier.
-__host__ __device__ constexpr int row_generations(int nc) { return nc == 2 ? 2 : 1; }
-
+__host__ __device__ constexpr int x_wave(int nc) { return nc == 2 ? 2 : 3; }
+__host__ __device__ constexpr int x_tile(int nc) { return nc == 2 ? 0 : 3; }
 template <int NC>
 struct Lds {
-    // the producers' own staging of the q and k rows of a chunk (d_v 64: by its parity)
+    // the q and k rows of a chunk, by its parity: building one chunk's operands and staging the next one's rows need nothing but the
+    // chunk's barrier
     struct alignas(16) Rows {
-        float kts[KT_ROWS][KTS_LD];     // c_k * K^T, then the rows [valid / c_k], [valid * c_k], [0]
-        float qs[C][QS_LD];             // c_q * Q
         uint16_t qrow[C][RB_LD];        // Q rows, bf16 as given
         uint16_t krow[C][RB_LD];        // K rows, bf16 as given
-    } rows[row_generations(NC)];
+    } rows[2];
     // everything the consumers read exists twice, indexed by the parity of the chunk: the producers fill
     // one generation while the consumers work on the other
     uint16_t vrow[2][C][32 * NC + 16];  // V rows, bf16 as given (operands are read transposed; the stride
@@ -129,8 +122,6 @@ struct Lds {
     u32x4 phik[2][NTILE][4][64];        // phi(K)^T operands: [parity][state tile][16-token slab][lane]
     u32x4 pop[2][3][2][64];             // masked intra-chunk blocks as operands: [parity][block][slab][lane]
     float den[2][3][C];                 // per query: inter-chunk part; row sums of the blocks of key tile 0, 1
-    uint16_t yt[NC][32][YT_LD];         // per consumer wave: a finished output tile on its way out
-    unsigned staged;                    // (rows once) producer waves that have staged their part, summed over the chunks so far
 };
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
@@ -170,23 +161,6 @@ __device__ __forceinline__ void zero16(f32x16 &a)
 __device__ __forceinline__ void wg_sync()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Rows that exist once: they are staged by the producer waves only, and read by every wave that builds an
-// operand from them.  That hand-over does not stop the whole workgroup: a producer wave that has finished
-// its LDS writes adds one to a counter in LDS, and whoever needs the rows waits until the counter has
-// reached the number of producer waves times the number of chunks staged so far.  (LDS operations of a
-// wave complete in order, and the add is issued after the wave's own writes have completed.)
-__device__ __forceinline__ void signal_staged(unsigned *counter, int lane)
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (lane == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void wait_staged(unsigned *counter, unsigned target)
-{
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target)
-        __builtin_amdgcn_s_sleep(1);
-    asm volatile("" ::: "memory");
 }
 
 // MFMA instructions ignore the EXEC mask.  A branch on the wave's role is uniform across the wave
@@ -284,14 +258,85 @@ __device__ __forceinline__ void load_wave_slots_coherent(const float *p1, const 
 constexpr int kMaxFlagPolls = 1 << 20;
 std::atomic<int> g_flag_poll_limit{kMaxFlagPolls};
 
+// 16 bytes per lane from base (uniform) + off bytes (per lane) to LDS address `to` (uniform) + 16 lane.  (Inline asm: through the
+// builtin the compiler makes every LDS read wait for all of it.  The wait states: a scalar register that a vector instruction has just
+// written, a spilled one for instance, reaches the memory pipeline five later, and the compiler does not see this use.)
+__device__ __forceinline__ void dma16(const void *base, uint32_t off, uint32_t to)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(off), "s"(base) : "memory", "m0");
+}
+
+// lane i of a row of 16 gets the value of lane (i + D) % 16 (a DPP operand of the multiplication that uses it)
+template <int D> __device__ __forceinline__ float rotate16(float x)
+{
+    if constexpr (D == 0) return x;
+    else return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x120 + 16 - D, 0xf, 0xf, true));
+}
+// the operand with `one` at element `target` of 16 (k-slot (jj, i) of lane half g: element 8 jj + 4 g + i) and zeros
+__device__ __forceinline__ bf16x8 one_at(int g, int target, uint32_t one)
+{
+    u32x4 o;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int e = 8 * (p >> 1) + 4 * g + 2 * (p & 1);
+        o[p] = (e == target ? one : 0u) | (e + 1 == target ? one << 16 : 0u);
+    }
+    return as_bf16x8(o);
+}
+
+// The state buffer moves through LDS (which holds nothing else at either end of a segment), as an image of the consumers'
+// tiles: image[column tile][32 T + row][IMG_LD].  A consumer reaches its registers' places at constant offsets from one
+// address, and the whole workgroup moves 16-byte pieces between the image and the buffer's rows.  (Read and
+// written by the consumers straight from and to memory, 160 four-byte accesses to a lane with an address each, it took
+// 12 us to read and 5-6 us to write at 16 units, d_v 64.)
+constexpr int IMG_LD = 40;   // (the two rows that the halves of a wave access lie in different banks)
+template <int NC> struct Image {
+    static constexpr int NTHR = 64 * (NC + producers(NC)), DV = 32 * NC;
+    static constexpr int Q = 32 * NTILE * (DV / 4), STEPS = (Q + NTHR - 1) / NTHR;   // 16-byte pieces: all, per thread
+    static __device__ __forceinline__ float *piece(float *image, int i)   // columns 4 (i % (DV / 4)) .. of row i / (DV / 4)
+    {
+        return image + ((i % (DV / 4)) / 8 * 32 * NTILE + i / (DV / 4)) * IMG_LD + 4 * (i % 8);
+    }
+    static __device__ __forceinline__ CanonRows rows(int i, bool packed_state) { return canon_rows(i / (DV / 4) >> 5, i / (DV / 4) & 31, packed_state); }
+};
+template <int NC> __device__ __forceinline__ void import_state_image(float *image, const float *Su, bool packed_state, int tid)
+{
+    using I = Image<NC>;
+    constexpr int BATCH = 5, DV = 32 * NC;
+    for (int s0 = 0; s0 < I::STEPS; s0 += BATCH) {
+        f32x4 t[BATCH][2];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int i = min((s0 + j) * I::NTHR + tid, I::Q - 1);
+            const CanonRows cr = I::rows(i, packed_state);
+            const float *p = Su + 4 * (i % (DV / 4));
+            t[j][0] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r1, 0) * DV);
+            t[j][1] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r2, 0) * DV);
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int i = (s0 + j) * I::NTHR + tid;
+            const float w = I::rows(i, packed_state).r1 < 0 ? 0.f : 0.5f;   // (padding rows are zero)
+            if (i < I::Q) *reinterpret_cast<f32x4 *>(I::piece(image, i)) = w == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * w;
+        }
+    }
+}
+// M'[fl][n] of the caller's K-state (a place in z for every lane: conditional loads would wait for each other)
+__device__ __forceinline__ float initial_moment(const float *zu, int fl, int n, bool packed_state)
+{
+    const bool in = fl <= DP && n <= DP, pair = fl < DP && n < DP;
+    const int at = pair ? canon_pair(fl, n, packed_state).r1 : !in ? 0 : fl < DP ? 1 + fl : n < DP ? 1 + n : 0;
+    return zu[at] * (pair ? 1.41421356237309504880f : in ? 1.f : 0.f);
+}
+
+constexpr int kLdsBytes = 150 * 1024;   // (one workgroup to a CU)
 constexpr int kMaxSegments = 16;
 // first token of each segment (multiples of the chunk length), and the end of the last one
 struct SegTable { int begin[kMaxSegments + 1]; };
 
 }  // namespace
 
-// MODE 0: full prefill of the segment (readout + update); starts from the sum of workspace entries 1 .. seg.
-// MODE 1: state increment of the segment only (update GEMMs), written to workspace entry 1 + seg.
+// Full prefill of the segment (readout + update); starts from the sum of workspace entries 1 .. seg.
 // The caller's initial state is read by the main pass of segment 0 and by the increment of segment 0, which starts from
 // it (so that the other segments get it with their first entry).  The last segment overwrites it with the final state, and
 // waits until both have read it.
@@ -302,14 +347,14 @@ struct SegTable { int begin[kMaxSegments + 1]; };
 // reader, and the reader zeroes it once it has seen it, so the words are clear again when the launch
 // ends (a replay of a captured launch, which repeats the same epoch, starts from cleared flags).
 // SEG: the launch has several segments.
-template <int NC, int MODE, bool SEG>
+template <int NC, bool SEG>
 __device__ __forceinline__ void prefill_body(
     Lds<NC> &lds, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ y, float *__restrict__ state, int has_init,
     float *__restrict__ ws, unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls,
     unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
 {
-    constexpr int NPW = producers(NC), GENS = row_generations(NC);
+    constexpr int NPW = producers(NC);
     constexpr int NP = 64 * NPW;      // producer threads
     constexpr int DV = 32 * NC;       // d_v
     constexpr int VR_LD = DV + 16;
@@ -319,7 +364,7 @@ __device__ __forceinline__ void prefill_body(
     const bool numerator_only = (has_init & 4) != 0;
     has_init &= 1;
     const int tid = threadIdx.x;
-    const int w = tid >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool is_p = w >= NC;            // producer wave; else consumer wave (owns the state tiles)
     const int c = is_p ? w - NC : w;      // consumer: column tile (columns 32c .. 32c+31); producer: its role
     const int lane = tid & 63;
@@ -341,12 +386,14 @@ __device__ __forceinline__ void prefill_body(
     // this lane's 16 bytes of register group 0 of slot 0 of column tile c (producer 0 keeps the moment
     // tile, which travels in the sixth slot of column tile 0), inside an entry
     const size_t lane_off = (size_t)(is_p ? 0 : c) * WS_WAVE_SLOTS * kSlotFloats + (size_t)lane * 4;
-    const bool holds_x = is_p && c == 0;
+    // the wave with the moments: at d_v 128 the consumer that builds no intra-chunk block, else producer 0 (the other way round at 128 producer 0 was
+    // the one that all others waited for: 4240 cycles a chunk instead of 3700)
+    const bool holds_x = w == x_wave(NC);
 
     // A main pass that starts from entries waits for the increments of this call (the last segment also for the initial state to have been
     // read) while its producers stage the first chunk and build what does not need the sum: 16 units of 777 tokens from a state
     // 18.1 us with the wait at the start, 17.0 with it here; without one, d_v 128 22.0, 19.5.
-    const bool from_entries = SEG && MODE == 0 && seg > 0;
+    const bool from_entries = SEG && seg > 0;
     auto wait_flags = [&]() {   // one thread
         bool gave_up = false;
         for (int p = has_init && seg == G - 1 ? 0 : 1; p <= seg; ++p) {
@@ -373,8 +420,8 @@ __device__ __forceinline__ void prefill_body(
         const bool diag = bb != 1;
         f32x16 P;
         zero16(P);
-        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.rows[b % GENS].krow[32 * kt + n][8 * g]);
-        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.rows[b % GENS].qrow[32 * qt + n][8 * g]);
+        const u32x4 kop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].krow[32 * kt + n][8 * g]);
+        const u32x4 qop = *reinterpret_cast<const u32x4 *>(&lds.rows[b].qrow[32 * qt + n][8 * g]);
         P = mfma(as_bf16x8(kop), as_bf16x8(qop), P);
         float dsum = 0.f;
 #pragma unroll
@@ -400,47 +447,17 @@ __device__ __forceinline__ void prefill_body(
         }
     };
 
-    // The state buffer moves through LDS (which holds nothing else at either end of a segment), as an image of the consumers'
-    // tiles: image[column tile][32 T + row][IMG_LD].  A consumer reaches its registers' places at constant offsets from one
-    // address, and the whole workgroup moves 16-byte pieces between the image and the buffer's rows.  (Read and
-    // written by the consumers straight from and to memory, 160 four-byte accesses to a lane with an address each, it took
-    // 12 us to read and 5-6 us to write at 16 units, d_v 64.)
-    constexpr int NTHR = 64 * (NC + NPW), IMG_LD = 40;   // (the two rows that the halves of a wave access lie in different banks)
-    static_assert(sizeof(Lds<NC>) >= sizeof(float) * NC * 32 * NTILE * IMG_LD, "the image fits the LDS");
+    using I = Image<NC>;
+    static_assert(sizeof(Lds<NC>) <= kLdsBytes && sizeof(float) * NC * 32 * NTILE * IMG_LD <= kLdsBytes, "");
     float *image = reinterpret_cast<float *>(&lds);
     float *image_lane = image + c * 32 * NTILE * IMG_LD + 4 * g * IMG_LD + n;   // (consumers)
-    constexpr int IMG_Q = 32 * NTILE * (DV / 4), IMG_STEPS = (IMG_Q + NTHR - 1) / NTHR;   // 16-byte pieces: all, per thread
-    auto image_piece = [&](int i) -> float * {   // columns 4 (i % (DV / 4)) .. of row i / (DV / 4)
-        return image + ((i % (DV / 4)) / 8 * 32 * NTILE + i / (DV / 4)) * IMG_LD + 4 * (i % 8);
-    };
-    auto piece_rows = [&](int i) { return canon_rows(i / (DV / 4) >> 5, i / (DV / 4) & 31, packed_state); };
-    auto import_image = [&]() {
-        constexpr int BATCH = 5;
-        for (int s0 = 0; s0 < IMG_STEPS; s0 += BATCH) {
-            f32x4 t[BATCH][2];
-#pragma unroll
-            for (int j = 0; j < BATCH; ++j) {
-                const int i = min((s0 + j) * NTHR + tid, IMG_Q - 1);
-                const CanonRows cr = piece_rows(i);
-                const float *p = Su + 4 * (i % (DV / 4));
-                t[j][0] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r1, 0) * DV);
-                t[j][1] = *reinterpret_cast<const f32x4 *>(p + (size_t)max(cr.r2, 0) * DV);
-            }
-#pragma unroll
-            for (int j = 0; j < BATCH; ++j) {
-                const int i = (s0 + j) * NTHR + tid;
-                const float w = piece_rows(i).r1 < 0 ? 0.f : 0.5f;   // (padding rows are zero)
-                if (i < IMG_Q) *reinterpret_cast<f32x4 *>(image_piece(i)) = w == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : (t[j][0] + t[j][1]) * w;
-            }
-        }
-    };
     auto export_image = [&]() {
 #pragma unroll 5
-        for (int st = 0; st < IMG_STEPS; ++st) {
-            const int i = st * NTHR + tid;
-            const CanonRows cr = piece_rows(i);
-            if (i < IMG_Q && cr.r1 >= 0) {
-                const f32x4 t = *reinterpret_cast<const f32x4 *>(image_piece(i));
+        for (int st = 0; st < I::STEPS; ++st) {
+            const int i = st * I::NTHR + tid;
+            const CanonRows cr = I::rows(i, packed_state);
+            if (i < I::Q && cr.r1 >= 0) {
+                const f32x4 t = *reinterpret_cast<const f32x4 *>(I::piece(image, i));
                 float *p = Su + 4 * (i % (DV / 4));
                 *reinterpret_cast<f32x4 *>(p + (size_t)cr.r1 * DV) = t;
                 if (cr.r2 != cr.r1) *reinterpret_cast<f32x4 *>(p + (size_t)cr.r2 * DV) = t;
@@ -448,8 +465,75 @@ __device__ __forceinline__ void prefill_body(
         }
     };
     float *zu = Su ? Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV : nullptr;
+    auto row_operand = [&](const uint16_t (*rows)[RB_LD], int t) {   // row 32 t + n
+        const uint16_t *p = &rows[32 * t + n][4 * g];
+        const u32x2 x = *reinterpret_cast<const u32x2 *>(p), y = *reinterpret_cast<const u32x2 *>(p + 8);
+        return as_bf16x8(u32x4{x[0], x[1], y[0], y[1]});
+    };
+    // Inter-chunk denominators of both query tiles from the moments: count + q.z1 + q^T M q / 2.
+    auto build_den = [&](const int b, const f32x16 &X) {
+        u32x4 o[2];   // elements 4 g .., 8 + 4 g .. of the queries
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) o[qt] = as_u32x4(row_operand(lds.rows[b].qrow, qt));
+        float mres[8];
+        const bf16x8 mhi = pack8_acc(X, 0);
+        {
+            const u32x4 hb = __builtin_bit_cast(u32x4, mhi);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                mres[2 * i] = X[2 * i] - bf16lo(hb[i]);
+                mres[2 * i + 1] = X[2 * i + 1] - bf16hi(hb[i]);
+            }
+        }
+        const bf16x8 mlo = pack8(mres);
+        const float cnt_prev = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(X[8]), 16));
+        f32x16 T[2];
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            zero16(T[qt]);
+            T[qt] = mfma(mhi, as_bf16x8(o[qt]), T[qt]);
+            T[qt] = mfma(mlo, as_bf16x8(o[qt]), T[qt]);
+        }
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            float d2 = 0.f;
+            // row of T[e] = 8 (e / 4) + 4 g + e % 4
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                d2 = fmaf(T[qt][2 * e], bf16lo(o[qt][e]), d2);
+                d2 = fmaf(T[qt][2 * e + 1], bf16hi(o[qt][e]), d2);
+            }
+            const float d = fmaf(d2, 0.5f, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
+            const float tot = d + __shfl_xor(d, 32, 64) + cnt_prev;
+            if (g == 0) lds.den[b][0][32 * qt + n] = tot;
+        }
+    };
+    // M' += K'^T K' of a chunk (the operand of tile 4 carries k as given in rows 0..15 and the valid flag in row 16)
+    auto add_moments = [&](const int b, f32x16 &X) {
+#pragma unroll
+        for (int ts = 0; ts < 4; ++ts) {
+            const bf16x8 e = as_bf16x8(lds.phik[b][NTILE - 1][ts][lane]);
+            X = mfma(e, e, X);
+        }
+    };
+    auto import_moments = [&](f32x16 &X) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X[r] = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
+    };
+    auto export_moments = [&](const f32x16 &X) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
+            const float m = X[r];
+            if (fl < DP && n < DP) {
+                if (!packed_state || fl <= n) zu[canon_pair(fl, n, packed_state).r1] = m * kRsqrt2;
+            }
+            else if (fl == DP && n < DP) zu[1 + n] = m;
+            else if (fl == DP && n == DP) zu[0] = m;
+        }
+    };
     if (has_init && seg == 0) {
-        import_image();
+        import_state_image<NC>(image, Su, packed_state, tid);
         __syncthreads();
     }
     // every wave, once it has what it needs of the image
@@ -457,19 +541,21 @@ __device__ __forceinline__ void prefill_body(
         // (a barrier does not wait for loads into registers, and the flag lets another workgroup overwrite what they read)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) lds.staged = 0u;   // (it lies in the image)
-        if (MODE == 0 && SEG) {
+        if (SEG) {
             if (tid == 0) __hip_atomic_store(flags_unit + (G - 1), epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     };
-    if (!(has_init && seg == 0) && tid == 0) lds.staged = 0u;   // ordered before its first use by the prologue's barriers
     if (!is_p) {
         // =================================== consumer waves =========================================
         f32x16 S[NTILE];       // the five state tiles of this wave's 32 columns
 #pragma unroll
         for (int T = 0; T < NTILE; ++T) zero16(S[T]);
 
+        f32x16 X;              // the moment tile M' = [k, 1]^T [k, 1], of consumer 3 of four
+        zero16(X);
+        const bool has_x = NC == 4 && holds_x;
         if (has_init && seg == 0) {   // the caller's state
+            if (has_x) import_moments(X);
 #pragma unroll
             for (int T = 0; T < NTILE; ++T)
 #pragma unroll
@@ -497,7 +583,8 @@ __device__ __forceinline__ void prefill_body(
             };
 
             wg_sync();   // the producers have staged the first chunk
-            if (MODE == 0) build_my_blocks(0);
+            build_my_blocks(0);
+            if (has_x && !from_entries) build_den(0, X);
             if (from_entries && tid == 0) wait_flags();
             wg_sync();   // the operands of the first chunk are visible (but the denominators, where these need the entries)
             if (from_entries) {   // the increments of earlier segments
@@ -509,7 +596,12 @@ __device__ __forceinline__ void prefill_body(
                     for (int T = 0; T < NTILE; ++T)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) S[T][r] += x[T * 4 + (r >> 2)][r & 3];
+                    if (has_x) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) X[r] += x[20 + (r >> 2)][r & 3];
+                    }
                 }
+                if (has_x) build_den(0, X);
                 wg_sync();
             }
             for (int t = 0; t < n_chunks; ++t) {
@@ -520,151 +612,134 @@ __device__ __forceinline__ void prefill_body(
                 for (int ts = 0; ts < 4; ++ts) vop[ts] = load_v(b, ts);
                 f32x16 Y[2];
                 float dn[2][3];
-                if (MODE == 0) {
-                    // ---- readout: Y^T of query tile qt: lane (g, n) = query 32 qt + n, register r = column
-                    // 32 c + 8 (r / 4) + 4 g + r % 4.  The bf16 copy of a state tile (a register-local
-                    // conversion: accumulator registers 8 sl .. 8 sl + 7 are the k-slots of slab 2T + sl) is the
-                    // A operand.  The LDS loads go out in groups, into registers of their own, ahead of the
-                    // matrix instructions that consume them.
-                    constexpr int RG = 5, NG = NSLAB / RG;
-                    u32x4 o[2][RG][2];
-                    auto load_group = [&](int gi) {
+                // ---- readout: Y^T of query tile qt: lane (g, n) = query 32 qt + n, register r = column
+                // 32 c + 8 (r / 4) + 4 g + r % 4.  The bf16 copy of a state tile (a register-local
+                // conversion: accumulator registers 8 sl .. 8 sl + 7 are the k-slots of slab 2T + sl) is the
+                // A operand.  The LDS loads go out in groups, into registers of their own, ahead of the
+                // matrix instructions that consume them.
+                constexpr int RG = 5, NG = NSLAB / RG;
+                u32x4 o[2][RG][2];
+                auto load_group = [&](int gi) {
 #pragma unroll
-                        for (int sl = 0; sl < RG; ++sl)
+                    for (int sl = 0; sl < RG; ++sl)
 #pragma unroll
-                            for (int qt = 0; qt < 2; ++qt) o[gi & 1][sl][qt] = lds.phiq[b][qt][RG * gi + sl][lane];
-                    };
-                    load_group(0);
-                    zero16(Y[0]); zero16(Y[1]);
+                        for (int qt = 0; qt < 2; ++qt) o[gi & 1][sl][qt] = lds.phiq[b][qt][RG * gi + sl][lane];
+                };
+                load_group(0);
+                zero16(Y[0]); zero16(Y[1]);
 #pragma unroll
-                    for (int gi = 0; gi < NG; ++gi) {
-                        if (gi + 1 < NG) load_group(gi + 1);
-                        __builtin_amdgcn_sched_barrier(0);
+                for (int gi = 0; gi < NG; ++gi) {
+                    if (gi + 1 < NG) load_group(gi + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int sl = 0; sl < RG; ++sl) {
-                            const bf16x8 sb = pack8_acc(S[(RG * gi + sl) >> 1], (RG * gi + sl) & 1);
+                    for (int sl = 0; sl < RG; ++sl) {
+                        const bf16x8 sb = pack8_acc(S[(RG * gi + sl) >> 1], (RG * gi + sl) & 1);
 #pragma unroll
-                            for (int qt = 0; qt < 2; ++qt) Y[qt] = mfma(sb, as_bf16x8(o[gi & 1][sl][qt]), Y[qt]);
-                        }
+                        for (int qt = 0; qt < 2; ++qt) Y[qt] = mfma(sb, as_bf16x8(o[gi & 1][sl][qt]), Y[qt]);
                     }
-                    u32x4 op[3][2];
-#pragma unroll
-                    for (int bb = 0; bb < 3; ++bb)
-#pragma unroll
-                        for (int sl = 0; sl < 2; ++sl) op[bb][sl] = lds.pop[b][bb][sl][lane];
-                    // intra-chunk: Y^T += V^T P^T over the key tiles at or before the query tile
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        Y[0] = mfma(vop[sl], as_bf16x8(op[0][sl]), Y[0]);
-                        Y[1] = mfma(vop[sl], as_bf16x8(op[1][sl]), Y[1]);
-                    }
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) Y[1] = mfma(vop[2 + sl], as_bf16x8(op[2][sl]), Y[1]);
                 }
-                if (MODE == 0 && NC == 4 && t + 1 < n_chunks) {
-                    wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // the next chunk's rows are staged
-                    build_my_blocks(b ^ 1);
+                u32x4 op[3][2];
+#pragma unroll
+                for (int bb = 0; bb < 3; ++bb)
+#pragma unroll
+                    for (int sl = 0; sl < 2; ++sl) op[bb][sl] = lds.pop[b][bb][sl][lane];
+                // intra-chunk: Y^T += V^T P^T over the key tiles at or before the query tile
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) {
+                    Y[0] = mfma(vop[sl], as_bf16x8(op[0][sl]), Y[0]);
+                    Y[1] = mfma(vop[sl], as_bf16x8(op[1][sl]), Y[1]);
+                }
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) Y[1] = mfma(vop[2 + sl], as_bf16x8(op[2][sl]), Y[1]);
+                if (NC == 4) {
+                    const bool has_next = t + 1 < n_chunks;
+                    if (has_next) build_my_blocks(b ^ 1);
+                    if (has_x) {
+                        add_moments(b, X);
+                        if (has_next) build_den(b ^ 1, X);
+                    }
                 }
 
-                // ---- update: S += phi(K)^T V over all 160 rows, with the normalisation and the store of
-                // the outputs placed between the matrix instructions
+                // ---- update: S += phi(K)^T V over all 160 rows, the outputs normalised and turned between the matrix instructions
                 u32x4 ok[4][NTILE];
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) dn[qt][d] = lds.den[b][d][32 * qt + n];
 #pragma unroll
                 for (int ts = 0; ts < 4; ++ts)
 #pragma unroll
                     for (int T = 0; T < NTILE; ++T) ok[ts][T] = lds.phik[b][T][ts][lane];
+                __builtin_amdgcn_sched_barrier(0);
+                // the halves of a wave exchange quads of columns: 16 bytes a lane, columns 32 c + 16 jj + 8 g .. of query 32 qt + n
+                u32x4 val[2][2];
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
+                for (int qt = 0; qt < 2; ++qt) {
+                    const float inv = numerator_only ? 1.f : __builtin_amdgcn_rcpf(dn[qt][0] + dn[qt][1] + dn[qt][2]);
 #pragma unroll
-                    for (int ts = 2 * half; ts < 2 * half + 2; ++ts) {
+                    for (int jj = 0; jj < 2; ++jj) {
+                        u32x2 p[2];
 #pragma unroll
-                        for (int T = 0; T < NTILE; ++T) S[T] = mfma(as_bf16x8(ok[ts][T]), vop[ts], S[T]);
-                    }
-                    if (MODE == 0) {
-                        const int qt = half;
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) dn[qt][d] = lds.den[b][d][32 * qt + n];
-                        // normalise and turn the tile through LDS: a lane holds 8-byte pieces of its token's
-                        // row, and stored directly those become 16-byte write requests that stall the memory
-                        // pipeline; from LDS the tile leaves as 64-byte row segments, 16 rows a store.
-                        const float inv = numerator_only ? 1.f : __builtin_amdgcn_rcpf(dn[qt][0] + dn[qt][1] + dn[qt][2]);
-                        uint16_t *yt = &lds.yt[c][0][0];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
+                        for (int k2 = 0; k2 < 2; ++k2) {
                             f32x4 o;
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) o[i] = Y[qt][4 * j + i] * inv;
-                            const bf16x4 hv = __builtin_convertvector(o, bf16x4);
-                            *reinterpret_cast<u32x2 *>(yt + n * YT_LD + 8 * j + 4 * g) = __builtin_bit_cast(u32x2, hv);
+                            for (int i = 0; i < 4; ++i) o[i] = Y[qt][8 * jj + 4 * k2 + i] * inv;
+                            p[k2] = __builtin_bit_cast(u32x2, __builtin_convertvector(o, bf16x4));
                         }
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        uint16_t *yc = yu + (size_t)tok0 * DV;
-                        u32x4 val[2];
-                        uint32_t yoff[2];
-#pragma unroll
-                        for (int it = 0; it < 2; ++it) {
-                            const int row = 16 * it + (lane >> 2), cc = lane & 3;
-                            val[it] = *reinterpret_cast<const u32x4 *>(yt + row * YT_LD + 8 * cc);
-                            yoff[it] = (uint32_t)(32 * qt + row) * (uint32_t)DV + (uint32_t)(32 * c + 8 * cc);
-                        }
-                        if (tok0 + C <= tok_end) {
-#pragma unroll
-                            for (int it = 0; it < 2; ++it) *reinterpret_cast<u32x4 *>(yc + yoff[it]) = val[it];
-                        } else {
-#pragma unroll
-                            for (int it = 0; it < 2; ++it)
-                                if (tok0 + 32 * qt + 16 * it + (lane >> 2) < tok_end) *reinterpret_cast<u32x4 *>(yc + yoff[it]) = val[it];
-                        }
-                        // the next tile overwrites this wave's staging only after these reads: LDS
-                        // operations of one wave execute in order
+                        const auto x = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+                        const auto z = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+                        val[qt][jj] = u32x4{x[0], z[0], x[1], z[1]};
                     }
+                }
+#pragma unroll
+                for (int ts = 0; ts < 4; ++ts)
+#pragma unroll
+                    for (int T = 0; T < NTILE; ++T) S[T] = mfma(as_bf16x8(ok[ts][T]), vop[ts], S[T]);
+#pragma unroll
+                for (int i = 0; i < 4 * NTILE; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix instruction,
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // vector instructions
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                uint16_t *yc = yu + (size_t)tok0 * DV;
+                const uint32_t yoff = (uint32_t)n * (uint32_t)DV + (uint32_t)(32 * c + 8 * g);
+                if (tok0 + C <= tok_end) {
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                        for (int jj = 0; jj < 2; ++jj) *reinterpret_cast<u32x4 *>(yc + yoff + 32 * qt * DV + 16 * jj) = val[qt][jj];
+                } else {
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                        for (int jj = 0; jj < 2; ++jj)
+                            if (tok0 + 32 * qt + n < tok_end) *reinterpret_cast<u32x4 *>(yc + yoff + 32 * qt * DV + 16 * jj) = val[qt][jj];
                 }
                 wg_sync();   // the next chunk's operands are visible; this chunk's are free
             }
         }
 
         // ---- end of segment --------------------------------------------------------------------
-        if (MODE != 0) {
-            float *e = ws_unit + (size_t)seg * entry_floats(NC) + lane_off;
-#pragma unroll
-            for (int T = 0; T < NTILE; ++T)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 o;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = S[T][4 * j + i];
-                    store16_coherent(e + (size_t)T * kSlotFloats + (size_t)j * 256, o);
-                }
-        } else if (Su && seg == G - 1) {
+        if (Su && seg == G - 1) {
 #pragma unroll
             for (int T = 0; T < NTILE; ++T)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) image_lane[(32 * T + 8 * (r >> 2) + (r & 3)) * IMG_LD] = S[T][r];
+            if (has_x) export_moments(X);
         }
     } else {
         // =================================== producer waves =========================================
         const int ptid = tid - 64 * NC;   // thread index among the producers
-        f32x16 X;                      // producer 0: the moment tile M' = [k, 1]^T [k, 1]
+        f32x16 X;                      // the moment tile, of producer 0 of six
         zero16(X);
-        if (has_init && seg == 0 && holds_x) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-                // M'[fl][n] (a place in z for every lane: conditional loads would wait for each other)
-                const bool in = fl <= DP && n <= DP, pair = fl < DP && n < DP;
-                const int at = pair ? canon_pair(fl, n, packed_state).r1 : !in ? 0 : fl < DP ? 1 + fl : n < DP ? 1 + n : 0;
-                const float m = zu[at] * (pair ? 1.41421356237309504880f : in ? 1.f : 0.f);
-                X[r] = m;
-            }
-        }
+        const bool has_m = NC == 2 && holds_x;
+        if (has_init && seg == 0 && has_m) import_moments(X);
         if (has_init && seg == 0) state_was_read();
 
         {
-            // once: the zero row of K^T, and the row sums of a block that does not exist (key tile 1
-            // against query tile 0)
+            // once: the row sums of a block that does not exist (key tile 1 against query tile 0)
             // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
             // not wait for this wave)
-            if (ptid < GENS * C) lds.rows[ptid / C].kts[DP + 2][ptid % C] = 0.f;
             if (ptid < 32) {
                 lds.den[0][2][ptid] = 0.f;
                 lds.den[1][2][ptid] = 0.f;
@@ -672,92 +747,76 @@ __device__ __forceinline__ void prefill_body(
 
             // ---- staging: global -> registers -> LDS --------------------------------------------
             // A chunk of V is one contiguous block of 64 rows x DV columns, in 16-byte pieces: piece p is row p / (DV / 8), columns
-            // 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128 pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  The
-            // first two waves stage K, the next two Q.  Of six producers these have the first 256 pieces of V as well, the other two
-            // the last 256.
+            // 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128 pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  A wave
+            // moves 64 pieces at a time.  Of four producers each has a quarter of V and half of K or Q.  Of six, 0 and 1 stage K, 4 and 5 Q, and
+            // 1 three eighths of V, the others one: as much as the builds leave time for (each with its own share of K or Q and of V: 2720 cycles a
+            // chunk, as here 2560).
             constexpr int VPR = DV / 8;   // pieces per V row
-            constexpr int NVP = NPW == 6 ? 2 : 4;   // V pieces per producer thread
-            static_assert((NPW == 6 ? 256 + 2 * 128 : NP * NVP) == VPR * C, "");
-            const int xp = ptid & 127;
-            const bool is_k = ptid < 128, has_x = ptid < 256;
-            const int x_tok = xp >> 1, x_h = xp & 1;
+            constexpr int NVP = NPW == 6 ? 3 : 4;   // V pieces per producer thread, at most
+            static_assert(NP == 64 * NPW && VPR * C == (NPW == 6 ? 8 : 16) * 64, "");
+            const int first_v = NPW == 4 ? 4 * c : c == 0 ? 0 : c == 1 ? 1 : c + 2;
+            const int n_v = NPW == 4 ? 4 : c == 1 ? 3 : 1;
+            const bool is_k = c < 2, has_x = NPW == 4 || c < 2 || c > 3;
+            const int xp = 64 * (c & 1) + lane, x_tok = xp >> 1, x_h = xp & 1;
             u32x4 raw_x = {0u, 0u, 0u, 0u};   // the thread's piece of K or Q
             u32x4 raw_v[NVP];
-            // Loads are unconditional (rows past the end of the segment re-read its last row and are
+            // Loads are not conditional on the lane (rows past the end of the segment re-read its last row and are
             // zeroed when staged): a conditional load would have the compiler pre-zero its destination
             // registers, and before that write it waits for every memory operation still in flight.
-            auto v_piece = [&](int j) { return NPW == 4 ? ptid + NP * j : has_x ? ptid : ptid + 128 * j; };
+            auto v_piece = [&](int j) { return 64 * (first_v + j) + lane; };
             auto load_x = [&](int tok0) {
-                const int tok = min(tok0 + x_tok, tok_end - 1);
-                const uint16_t *src = (is_k || MODE != 0) ? ku : qu;   // increment pass: q is not needed
-                raw_x = *reinterpret_cast<const u32x4 *>(src + (size_t)tok * DP + 8 * x_h);
+                if (!has_x) return;
+                tok0 = min(tok0, tok_end - 1);
+                const uint16_t *src = (is_k ? ku : qu) + (size_t)tok0 * DP;
+                raw_x = *reinterpret_cast<const u32x4 *>(src + (uint32_t)(min(x_tok, tok_end - 1 - tok0) * DP + 8 * x_h));
             };
             auto load_v = [&](int tok0) {
+                tok0 = min(tok0, tok_end - 1);
+                const uint16_t *src = vu + (size_t)tok0 * DV;
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
+                    if (j >= n_v) break;
                     const int p = v_piece(j);
-                    const int row = min(tok0 + p / VPR, tok_end - 1);
-                    raw_v[j] = *reinterpret_cast<const u32x4 *>(vu + (size_t)row * DV + 8 * (p % VPR));
+                    raw_v[j] = *reinterpret_cast<const u32x4 *>(src + (uint32_t)(min(p / VPR, tok_end - 1 - tok0) * DV + 8 * (p % VPR)));
                 }
             };
             auto stage_x = [&](int tok0, int b) {
-                auto &rows = lds.rows[b % GENS];
+                if (!has_x) return;
+                auto &rows = lds.rows[b];
                 u32x4 raw = raw_x;
-                if (is_k) {
-                    const bool valid = tok0 + x_tok < tok_end;
-                    if (!valid) raw = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        rows.kts[8 * x_h + 2 * i][x_tok] = bf16lo(raw[i]) * kCK;
-                        rows.kts[8 * x_h + 2 * i + 1][x_tok] = bf16hi(raw[i]) * kCK;
-                    }
-                    *reinterpret_cast<u32x4 *>(&rows.krow[x_tok][8 * x_h]) = raw;
-                    if (x_h == 0) {
-                        rows.kts[DP][x_tok] = valid ? 1.f / kCK : 0.f;
-                        rows.kts[DP + 1][x_tok] = valid ? kCK : 0.f;
-                    }
-                } else if (MODE == 0 && has_x) {
-                    f32x4 lo, hi;
-                    lo[0] = bf16lo(raw[0]) * kCQ; lo[1] = bf16hi(raw[0]) * kCQ;
-                    lo[2] = bf16lo(raw[1]) * kCQ; lo[3] = bf16hi(raw[1]) * kCQ;
-                    hi[0] = bf16lo(raw[2]) * kCQ; hi[1] = bf16hi(raw[2]) * kCQ;
-                    hi[2] = bf16lo(raw[3]) * kCQ; hi[3] = bf16hi(raw[3]) * kCQ;
-                    *reinterpret_cast<f32x4 *>(&rows.qs[x_tok][8 * x_h]) = lo;
-                    *reinterpret_cast<f32x4 *>(&rows.qs[x_tok][8 * x_h + 4]) = hi;
-                    *reinterpret_cast<u32x4 *>(&rows.qrow[x_tok][8 * x_h]) = raw;
-                }
+                if (is_k && tok0 + x_tok >= tok_end) raw = u32x4{0u, 0u, 0u, 0u};
+                *reinterpret_cast<u32x4 *>(is_k ? &rows.krow[x_tok][8 * x_h] : &rows.qrow[x_tok][8 * x_h]) = raw;
             };
             auto stage_v = [&](int tok0, int b) {
                 const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
+                    if (j >= n_v) break;
                     const int p = v_piece(j);
                     const int row = p / VPR;
-                    if (j == 0 || NPW == 4 || !has_x)
-                        *reinterpret_cast<u32x4 *>(&lds.vrow[b][row][8 * (p % VPR)]) = tok0 + row < tok_end ? raw_v[j] : zero4;
+                    *reinterpret_cast<u32x4 *>(&lds.vrow[b][row][8 * (p % VPR)]) = tok0 + row < tok_end ? raw_v[j] : zero4;
                 }
             };
 
             // ---- builders of the shared operands (b: the generation they write) ------------------
+            // A tile of 32 rows multiplied with a 0/1 matrix comes back as accumulators: in fp32, without rounding, transposed and in any order of
+            // the elements, in the registers and lanes that an operand is built from.  k-slot (jj, i) of lane half g is element 8 jj + 4 g + i.
+            const int m = lane & 15;
+            const bf16x8 first_eye = one_at(g, m, 0x3F80u);                       // lane n: element n % 16
+            const bf16x8 second_eye = one_at(g, (m + (n >> 4)) & 15, 0x3F80u);    // element (n + n / 16) % 16
+            const bf16x8 pair_eye = one_at(g, n >= 24 ? n - 24 : -1, 0x3F80u);    // lanes 24 .. 31: element n - 24
+            const bf16x8 turned_eye = one_at(g, (4 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3)) & 15, 0x3F80u);   // register j: element (4 g + j) % 16
             // phi(Q)^T operands of query tile qt, all ten slabs: lane (g, n) is query 32 qt + n; k-slot
             // (jj, i) of slab s is feature row 16 s + 8 jj + 4 g + i.  xr[j] = c_q q[(4g + j) % 16] is the
             // lane's query row rotated by 4g, so that the "a side" of k-slot (jj, i) is xr[8 jj + i] and the
             // "b side" of delta is xr[(8 jj + i + delta) % 16]: every product is between two registers known
             // at compile time.
             auto build_phiq = [&](const int b, const int qt) {
-                float xr[16];
-                const float *row = lds.rows[b % GENS].qs[32 * qt + n];
-                f32x4 t[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) t[m] = *reinterpret_cast<const f32x4 *>(row + ((4 * g + 4 * m) & 15));
-                // slab 8: the linear rows; the operand is q itself, as given
-                const uint16_t *p = &lds.rows[b % GENS].qrow[32 * qt + n][4 * g];
-                const u32x2 ra = *reinterpret_cast<const u32x2 *>(p);
-                const u32x2 rb = *reinterpret_cast<const u32x2 *>(p + 8);
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) xr[4 * m + i] = t[m][i];
+                const bf16x8 qr = row_operand(lds.rows[b].qrow, qt);
+                f32x16 xr;
+                zero16(xr);
+                xr = mfma(turned_eye, qr, xr);
+                xr *= kCQ;
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {   // pair slabs: delta = s
                     float pr[8];
@@ -771,10 +830,7 @@ __device__ __forceinline__ void prefill_body(
                         }
                     lds.phiq[b][qt][s][lane] = as_u32x4(pack8(pr));
                 }
-                {
-                    u32x4 o; o[0] = ra[0]; o[1] = ra[1]; o[2] = rb[0]; o[3] = rb[1];
-                    lds.phiq[b][qt][8][lane] = o;
-                }
+                lds.phiq[b][qt][8][lane] = as_u32x4(qr);   // slab 8: the linear rows, q itself as given
                 {   // slab 9: the constant row (k-slot 0 of g = 0 = row 16 of the tile), padding, and the
                     // delta = 8 rows (k-slots 4 + i = row 24 + 4g + i: sqrt(2) q_a q_(a+8), a = 4g + i)
                     float pr[8];
@@ -784,163 +840,100 @@ __device__ __forceinline__ void prefill_body(
                     lds.phiq[b][qt][9][lane] = as_u32x4(pack8(pr));
                 }
             };
-            // phi(K)^T operands of token slab ts, all five state tiles: lane (g, n) is feature row n of a
-            // tile, its k-slots are the tokens 16 ts + 4 g + {0..3, 8..11}.  Every row is a product of two
-            // rows of the staged K^T: pair rows k_a k_b / sqrt(2); linear rows (c_k k_a)(valid / c_k); the
-            // constant row (valid c_k)(valid / c_k); padding rows 0 * 0.  (c_k k_a / c_k differs from k_a by
-            // fp32 rounding only, far below half a bf16 step, so the conversion returns k_a exactly.)  The
-            // "a" row of the four pair tiles is the same (a = n % 16), so a slab costs 14 LDS loads, all
-            // issued before the products.
-            const float *kts0 = &lds.rows[0].kts[0][4 * g];
-            constexpr int GEN = sizeof(typename Lds<NC>::Rows) / sizeof(float);
-            const float *kt_a03 = kts0 + (n & 15) * KTS_LD;
-            const float *kt_a4 = kts0 + (n < DP ? n : (n == DP ? DP + 1 : (n < 24 ? DP + 2 : n - 24))) * KTS_LD;
-            const float *kt_b[NTILE];
+            // phi(K)^T operands of the chunk's tokens 32 hh .., all five state tiles: lane (g, n) is feature row n of a
+            // tile, its k-slots are the tokens 16 ts + 4 g + {0..3, 8..11}.  Pair rows are k_a k_b / sqrt(2): the first factor is the same
+            // (a = n % 16) in four tiles, the second one that of tile 0 from a lane 2T further.  Tile 4: k as given (sqrt(2) k / sqrt(2)
+            // differs from k by fp32 rounding only, far below half a bf16 step, so the conversion returns it exactly), the constant 1, pairs.  valid: the
+            // chunk's tokens before the end (behind it the constant is 0).
+            auto build_phik = [&](const int b, const int hh, const int valid) {
+                const bf16x8 kr = row_operand(lds.rows[b].krow, hh);
+                f32x16 ka, kb, kp;
+                zero16(ka); zero16(kb);
 #pragma unroll
-            for (int T = 0; T < 4; ++T) kt_b[T] = kts0 + (((n & 15) + 2 * T + (n >> 4)) & 15) * KTS_LD;
-            kt_b[4] = kts0 + (n < DP ? DP : (n == DP ? DP : (n < 24 ? DP + 2 : n - 16))) * KTS_LD;
-            // (NTS token slabs at a time: all their LDS loads go out before the first product)
-            auto build_phik_n = [&](const int b, const int ts0, auto nts_tag) {
-                constexpr int NTS = decltype(nts_tag)::value;
-                f32x4 a03[NTS][2], a4[NTS][2], kb[NTS][NTILE][2];
+                for (int r = 0; r < 16; ++r) kp[r] = n < DP ? kSqrt2 : 0.f;
+                ka = mfma(kr, first_eye, ka);
+                kb = mfma(kr, second_eye, kb);
+                kp = mfma(kr, pair_eye, kp);
+                ka *= kRsqrt2;
+                float one[16];
 #pragma unroll
-                for (int s2 = 0; s2 < NTS; ++s2)
+                for (int r = 0; r < 16; ++r) one[r] = n == DP ? 1.f : 0.f;
+                if (valid < C) {   // uniform
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int off = GEN * (b % GENS) + 16 * (ts0 + s2) + 8 * h;
-                        a03[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a03 + off);
-                        a4[s2][h] = *reinterpret_cast<const f32x4 *>(kt_a4 + off);
+                    for (int r = 0; r < 16; ++r) one[r] = 32 * hh + 8 * (r >> 2) + 4 * g + (r & 3) < valid ? one[r] : 0.f;
+                }
 #pragma unroll
-                        for (int T = 0; T < NTILE; ++T) kb[s2][T][h] = *reinterpret_cast<const f32x4 *>(kt_b[T] + off);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int s2 = 0; s2 < NTS; ++s2)
-#pragma unroll
-                    for (int T = 0; T < NTILE; ++T) {
+                for (int s = 0; s < 2; ++s) {
+                    auto tile = [&](auto tag) {
+                        constexpr int T = decltype(tag)::value;
                         float pr[8];
 #pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                pr[4 * h + i] = (T < 4 ? a03[s2][h][i] : a4[s2][h][i]) * kb[s2][T][h][i];
-                        lds.phik[b][T][ts0 + s2][lane] = as_u32x4(pack8(pr));
-                    }
-            };
-            auto build_phik = [&](const int b, const int ts) { build_phik_n(b, ts, std::integral_constant<int, 1>{}); };
-            auto build_phik2 = [&](const int b, const int ts) { build_phik_n(b, ts, std::integral_constant<int, 2>{}); };
-            // Inter-chunk denominators of both query tiles from the moments: count + q.z1 + q^T M q / 2.
-            auto build_den = [&](const int b) {
-                f32x4 a0[2], a1[2];
-                u32x2 ra[2], rb[2];
-#pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
-                    const float *row = lds.rows[b % GENS].qs[32 * qt + n];
-                    a0[qt] = *reinterpret_cast<const f32x4 *>(row + 4 * g);
-                    a1[qt] = *reinterpret_cast<const f32x4 *>(row + 8 + 4 * g);
-                    const uint16_t *p = &lds.rows[b % GENS].qrow[32 * qt + n][4 * g];
-                    ra[qt] = *reinterpret_cast<const u32x2 *>(p);
-                    rb[qt] = *reinterpret_cast<const u32x2 *>(p + 8);
-                }
-                float mres[8];
-                const bf16x8 mhi = pack8_acc(X, 0);
-                {
-                    const u32x4 hb = __builtin_bit_cast(u32x4, mhi);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        mres[2 * i] = X[2 * i] - bf16lo(hb[i]);
-                        mres[2 * i + 1] = X[2 * i + 1] - bf16hi(hb[i]);
-                    }
-                }
-                const bf16x8 mlo = pack8(mres);
-                const float cnt_prev = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(X[8]), 16));
-                f32x16 T[2];
-#pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
-                    u32x4 o; o[0] = ra[qt][0]; o[1] = ra[qt][1]; o[2] = rb[qt][0]; o[3] = rb[qt][1];
-                    zero16(T[qt]);
-                    T[qt] = mfma(mhi, as_bf16x8(o), T[qt]);
-                    T[qt] = mfma(mlo, as_bf16x8(o), T[qt]);
-                }
-#pragma unroll
-                for (int qt = 0; qt < 2; ++qt) {
-                    float d2 = 0.f;
-                    // row of T[e] = 8 (e / 4) + 4 g + e % 4
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][e], a0[qt][e], d2);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d2 = fmaf(T[qt][4 + e], a1[qt][e], d2);
-                    const float d = fmaf(d2, kHalfInvCQ, T[qt][8]);   // T[8]: row 16 = q.z1 on g = 0, zero on g = 1
-                    const float tot = d + __shfl_xor(d, 32, 64) + cnt_prev;
-                    if (g == 0) lds.den[b][0][32 * qt + n] = tot;
+                        for (int e = 0; e < 8; ++e)
+                            pr[e] = T < 4 ? ka[8 * s + e] * rotate16<2 * T>(kb[8 * s + e]) : fmaf(ka[8 * s + e], kp[8 * s + e], one[8 * s + e]);
+                        lds.phik[b][T][2 * hh + s][lane] = as_u32x4(pack8(pr));
+                    };
+                    tile(std::integral_constant<int, 0>{});
+                    tile(std::integral_constant<int, 1>{});
+                    tile(std::integral_constant<int, 2>{});
+                    tile(std::integral_constant<int, 3>{});
+                    tile(std::integral_constant<int, 4>{});
                 }
             };
-            // The producers' share of the operands of one chunk, into generation b (the intra-chunk blocks
-            // are built by the consumers at d_v 128, which have the time).  Wave 0: denominators, phi(Q) of query
-            // tile 0; 1: phi(Q) of query tile 1; 2: phi(K) of token slabs 0, 1; 3: phi(K) of token slabs 2, 3.  Of six
-            // (d_v 64), 0: denominators and the intra-chunk block off the diagonal; 1, 2: phi(Q); 3, 4: phi(K); 5: the blocks on the
-            // diagonal.  Increment pass: phi(K) only, of a token slab each.
-            auto build = [&](const int b, const bool den) {   // den: the denominators too
-                if (MODE == 0 && NPW == 6) {
+            // The producers' share of the operands of the chunk from tok0 on, into generation b (the intra-chunk blocks
+            // and the denominators are built by the consumers at d_v 128).  Waves 0, 1: phi(Q) of a query tile;
+            // 2, 3: phi(K) of half of the tokens each.  Of six (d_v 64), 0: denominators and the intra-chunk block off the diagonal; 1, 4: phi(K); 2, 3, which share a SIMD with a consumer: phi(Q), the
+            // shortest; 5: the blocks on the diagonal.
+            auto build = [&](const int b, const bool den, const int tok0) {   // den: the denominators too
+                const int valid = tok_end - tok0;
+                if (NPW == 6) {
                     if (c == 0) {
                         role_guard();
-                        if (den) build_den(b);
+                        if (den) build_den(b, X);
                         build_block(b, 1);
-                    } else if (c < 3) {
-                        build_phiq(b, c - 1);
-                    } else if (c < 5) {
-                        build_phik2(b, 2 * (c - 3));
+                    } else if (c == 1 || c == 4) {
+                        role_guard();
+                        build_phik(b, c >> 2, valid);
+                    } else if (c < 4) {
+                        role_guard();
+                        build_phiq(b, c - 2);
                     } else {
                         role_guard();
                         build_block(b, 0);
                         build_block(b, 2);
                     }
-                } else if (MODE == 0) {
-                    if (c == 0) {
-                        role_guard();
-                        if (den) build_den(b);
-                        build_phiq(b, 0);
-                    } else if (c == 1) {
-                        build_phiq(b, 1);
-                    } else {
-                        build_phik2(b, 2 * (c - 2));
-                    }
                 } else {
-#pragma unroll
-                    for (int ts = 0; ts < 4; ++ts)
-                        if (c == NPW - 4 + ts) build_phik(b, ts);
+                    role_guard();
+                    if (c < 2) {
+                        build_phiq(b, c);
+                    } else {
+                        build_phik(b, c - 2, valid);
+                    }
                 }
             };
 
-            // ---- the producers' loop: operands one chunk ahead of the consumers; rows two ahead of them where these exist twice ----
-            // in registers: V of chunk t + 1, K and Q of chunk t + GENS
+            // ---- the producers' loop: operands one chunk ahead of the consumers, rows two ahead of them ----
+            // in registers: V of chunk t + 1, K and Q of chunk t + 2
             auto stage_next = [&](int t) {
                 const int tok_next = tok_begin + C * (t + 1);
                 stage_v(tok_next, (t + 1) & 1);
-                stage_x(tok_next + C * (GENS - 1), (t + GENS) & 1);
+                stage_x(tok_next + C, t & 1);
             };
             auto load_next = [&](int t) {   // for stage_next(t)
                 const int tok_next = tok_begin + C * (t + 1);
                 load_v(tok_next);
-                load_x(tok_next + C * (GENS - 1));
+                load_x(tok_next + C);
             };
             load_x(tok_begin);
             load_v(tok_begin);
             stage_x(tok_begin, 0);
-            if (GENS == 2) {
-                load_x(tok_begin + C);
-                wg_sync();   // the first chunk's rows are staged
-                stage_next(-1);
-                load_next(0);
-            } else {
-                stage_v(tok_begin, 0);
-                if (n_chunks > 1) load_next(0);
-                wg_sync();
-            }
-            build(0, !from_entries);
+            load_x(tok_begin + C);
+            wg_sync();   // the first chunk's rows are staged
+            stage_next(-1);
+            load_next(0);
+            build(0, !from_entries, tok_begin);
             wg_sync();   // the first chunk's operands are visible
             if (from_entries) {
-                if (holds_x) {
+                if (has_m) {
                     role_guard();
                     for (int p = 1; p <= seg; ++p) {
                         const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
@@ -949,7 +942,7 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
                         for (int r = 0; r < 16; ++r) X[r] += x[20 + (r >> 2)][r & 3];
                     }
-                    build_den(0);
+                    build_den(0, X);
                 }
                 wg_sync();
             }
@@ -957,63 +950,262 @@ __device__ __forceinline__ void prefill_body(
                 const int b = t & 1;
                 const bool has_next = t + 1 < n_chunks;
                 if (has_next) stage_next(t);
-                if (GENS == 1 && has_next) signal_staged(&lds.staged, lane);
-                if (GENS == 2 ? has_next : t + 2 < n_chunks) load_next(t + 1);   // (rows past the end: the last one again)
-                if (GENS == 1 && has_next) wait_staged(&lds.staged, (unsigned)(NPW * (t + 1)));   // all of the next chunk's rows
-                if (holds_x) {
-                    // M' += K'^T K' of the chunk the consumers are working on (the operand of tile 4 carries k
-                    // as given in rows 0..15 and the valid flag in row 16); the denominators of the next chunk
-                    // need it
+                if (has_next) load_next(t + 1);   // (rows past the end: the last one again)
+                if (has_m) {   // of the chunk the consumers are working on; the denominators of the next chunk need it
                     role_guard();
-#pragma unroll
-                    for (int ts = 0; ts < 4; ++ts) {
-                        const bf16x8 e = as_bf16x8(lds.phik[b][NTILE - 1][ts][lane]);
-                        X = mfma(e, e, X);
-                    }
+                    add_moments(b, X);
                 }
-                if (has_next) build(b ^ 1, true);
+                if (has_next) build(b ^ 1, true, tok_begin + C * (t + 1));
                 wg_sync();   // the next chunk's operands are visible
             }
         }
 
         // ---- end of segment: the moments ----------------------------------------------------------
-        if (holds_x) {
-            if (MODE != 0) {
-                float *e = ws_unit + (size_t)seg * entry_floats(NC) + lane_off;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 o;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = X[4 * j + i];
-                    store16_coherent(e + (size_t)5 * kSlotFloats + (size_t)j * 256, o);
-                }
-            } else if (Su && seg == G - 1) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-                    const float m = X[r];
-                    if (fl < DP && n < DP) {
-                        if (!packed_state || fl <= n) zu[canon_pair(fl, n, packed_state).r1] = m * kRsqrt2;
-                    }
-                    else if (fl == DP && n < DP) zu[1 + n] = m;
-                    else if (fl == DP && n == DP) zu[0] = m;
-                }
-            }
-        }
+        if (has_m && Su && seg == G - 1) export_moments(X);
     }
-    if (MODE == 0 && Su && seg == G - 1) {
+    if (Su && seg == G - 1) {
         __syncthreads();
         export_image();
     }
-    if (MODE == 1) {
-        // the entry has reached memory (the stores are written through) before the flag is raised
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        // entry 1 + seg is read by the main-pass workgroups of segments 1 + seg .. G - 1
-        if (tid >= 1 + seg && tid < G)
-            __hip_atomic_store(flags_unit + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// State increment of segment `seg`, to workspace entry 1 + seg.
+//
+// The eight waves need no operand from each other here, so nothing but the rows passes through LDS, and a step has one barrier.  Wave r = w % 4
+// owns tile r for two column tiles (waves 2 and 3 also tile 4, for one of them; wave 1 the moments), and a feature is a product of two
+// values in its registers: multiplied with 0/1 matrices a tile of 32 rows of K comes back as accumulators, in fp32 and without rounding, with lane
+// n holding k_a (halved) or the k_b of its row and the registers going over the tokens in the order of an operand's k-slots.  At d_v 64 the waves 0-3
+// and 4-7 take alternate tiles of 32 tokens and are added up at the end; at d_v 128 they own 64 columns each.  The rows come by the 16-byte LDS
+// DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), two steps ahead.  Every row is a sum of halved products: pair rows
+// are scaled by sqrt(2), the others by 2, the moments by 4 when they are stored.
+template <int NC>
+__device__ __forceinline__ void increment_body(
+    unsigned char *lds, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state, int has_init,
+    float *__restrict__ ws, unsigned *__restrict__ flags, unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
+{
+    constexpr int DV = 32 * NC, HP = NC / 2;      // HP: 64-column parts
+    constexpr int NH = 4 / HP;                    // 32-token tiles of a step
+    constexpr int PART = 32 * 64 * 2, TILE_K = 32 * DP * 2, STAGE = 4 * PART + NH * TILE_K, RING = 5;
+    constexpr int IMAGE = NC * 32 * NTILE * IMG_LD * 4, AT = HP == 1 ? IMAGE : 0;   // (at d_v 128 the rows lie where the image was)
+    static_assert(AT + RING * STAGE <= kLdsBytes && 11 * 4096 <= IMAGE && IMAGE <= kLdsBytes, "");
+    const bool packed_state = (has_init & 2) != 0;
+    has_init &= 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), r4 = w & 3, grp = w >> 2;
+    const int g = lane >> 5, n = lane & 31, m = lane & 15;
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+
+    const int tok_begin = segs.begin[seg], tok_end = segs.begin[seg + 1];   // (whole chunks: the sequence's last segment has no increment)
+    const int steps = (tok_end - tok_begin + 32 * NH - 1) / (32 * NH);
+    const uint16_t *ku = k + (size_t)u * N * DP, *vu = v + (size_t)u * N * DV;
+
+    // Wave w moves 16 rows of part w / 2 (d_v 64: of tile w / 2; d_v 128: of tile w / 4, columns 64 (w / 2 % 2) ..) and, for w < NH, tile w of
+    // K.  A tile past the end is the step's first once more.
+    const uint32_t off_v = (uint32_t)((lane >> 3) * DV * 2 + 16 * ((lane & 7) ^ (4 * ((lane >> 4) & 1))));
+    const int part_tile = HP == 1 ? w >> 1 : w >> 2, part_col = HP == 1 ? 0 : 64 * ((w >> 1) & 1);
+    auto issue = [&](int step) {
+        step = min(step, steps - 1);
+        const int tok0 = tok_begin + 32 * NH * step;
+        const uint32_t to = lds_addr + (uint32_t)(AT + step % RING * STAGE);
+        const int tv = tok0 + 32 * part_tile < tok_end ? tok0 + 32 * part_tile : tok0;
+        const uint16_t *vb = vu + (size_t)(tv + 16 * (w & 1)) * DV + part_col;
+        const uint32_t vt = to + (uint32_t)((w >> 1) * PART + 2048 * (w & 1));
+        dma16(vb, off_v, vt);
+        dma16(vb + 8 * DV, off_v, vt + 1024);
+        if (w < NH) {
+            const int tk = tok0 + 32 * w < tok_end ? tok0 + 32 * w : tok0;
+            dma16(ku + (size_t)tk * DP, 16 * lane, to + (uint32_t)(4 * PART + w * TILE_K));
+        }
+    };
+    const bool imports = has_init && seg == 0;
+    auto issue_first = [&]() {
+#pragma unroll
+        for (int i = 0; i < RING - 1; ++i) issue(i);
+    };
+    if (HP == 1 || !imports) issue_first();
+
+    // 0/1 matrices as B operands
+    const bf16x8 first_eye = one_at(g, m, 0x3F00u);                              // k_a / 2
+    const bf16x8 second_eye = one_at(g, (m + 2 * r4 + (n >> 4)) & 15, 0x3F80u);   // k_b of tile r
+    const bf16x8 pair_eye = one_at(g, n >= 24 ? n - 24 : -1, 0x3F80u);           // k_b of tile 4's pairs (k_a: lane n holds a = n - 16)
+    const float row_one = n < 16 ? 1.f : 0.f, row_half = n == 16 ? 0.5f : 0.f;
+
+    // This wave's column tiles are c0, c0 + 1; waves 2, 3, 4 and 5 have tile 4 of column tile c0 + r % 2 as well (a matrix pipe serves waves w
+    // and w + 4), wave 1, at d_v 64 also 7, the moments.
+    const int c0 = HP == 1 ? 0 : 2 * grp, e4 = r4 & 1;
+    const bool has4 = (grp == 0) == (r4 >= 2), has_x = grp == 0 ? r4 == 1 : HP == 1 && r4 == 3;
+    f32x16 S[2], E;   // tile r of the column tiles; tile 4, or the moments
+    zero16(S[0]); zero16(S[1]); zero16(E);
+    if (imports) {   // (the state buffer's image: as in the main pass)
+        const float *Su = state + (size_t)u * (packed_state ? packed_state_stride(DP, DV) : state_stride(DP, DV));
+        const float *zu = Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV;
+        const bool starts = HP == 2 || grp == 0;   // of two groups the first one starts from it
+        if (has_x && starts) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) E[r] = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
+        }
+        float *image = reinterpret_cast<float *>(lds);
+        import_state_image<NC>(image, Su, packed_state, tid);
+        wg_sync();
+        if (starts) {
+            const float *at = image + c0 * 32 * NTILE * IMG_LD + 4 * g * IMG_LD + n;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = 8 * (r >> 2) + (r & 3);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) S[c][r] = kRsqrt2 * at[(c * 32 * NTILE + 32 * r4 + row) * IMG_LD];
+                if (has4) E[r] = (r < 12 ? 0.5f : kRsqrt2) * at[(e4 * 32 * NTILE + 128 + row) * IMG_LD];
+                if (has_x) E[r] *= 0.25f;
+            }
+        }
+        if (HP == 2) {
+            wg_sync();   // the image has been read
+            issue_first();
+        }
     }
+
+    const int tr_lane = ((m >> 2) + 4 * g) * 128 + ((32 * ((lane >> 4) & 1) + 8 * (m & 3)) ^ (64 * ((m >> 3) & 1)));
+    auto load_v = [&](const unsigned char *part, int s, int c) {   // columns 32 c + n, tokens 16 s + 4 g + {0..3, 8..11}
+        const unsigned char *p = part + (tr_lane ^ (64 * c)) + 16 * 128 * s;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 8 * 128));
+        s16x8 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { o[i] = lo[i]; o[4 + i] = hi[i]; }
+        return __builtin_bit_cast(bf16x8, o);
+    };
+    auto load_k = [&](const unsigned char *tile) {   // row n: elements 4 g .., 8 + 4 g ..
+        const unsigned char *p = tile + 32 * n + 8 * g;
+        const u32x2 a = *reinterpret_cast<const u32x2 *>(p), b = *reinterpret_cast<const u32x2 *>(p + 16);
+        return as_bf16x8(u32x4{a[0], a[1], b[0], b[1]});
+    };
+    // KIND: 0 a tile, 1 a tile and the moments, 2 a tile and tile 4.  The factors of a tile of 32 rows are on their way while the products of the
+    // tile before are built and multiplied.
+    auto run = [&](auto kind) {
+        constexpr int KIND = decltype(kind)::value;
+        const unsigned char *const ring = lds + AT;
+        f32x16 a[2], b[2], f[2];
+        auto factors = [&](int step, int i) {
+            const bf16x8 kr = load_k(ring + step % RING * STAGE + 4 * PART + (HP == 2 ? i : grp + 2 * i) * TILE_K);
+            zero16(a[i]); zero16(b[i]);
+            a[i] = mfma(kr, first_eye, a[i]);
+            b[i] = mfma(kr, second_eye, b[i]);
+            if (KIND == 2) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) f[i][r] = row_one;
+                f[i] = mfma(kr, pair_eye, f[i]);
+            }
+        };
+        auto products = [&](int i, const bf16x8 (&vo)[2][2]) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                float pr[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pr[e] = a[i][8 * s + e] * b[i][8 * s + e];
+                const bf16x8 op = pack8(pr);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) S[c] = mfma(op, vo[s][c], S[c]);
+                if (KIND == 2) {   // linear rows k_a / 2, the constant 1 / 2, pairs
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], f[i][8 * s + e], row_half);
+                    E = mfma(pack8(pr), e4 ? vo[s][1] : vo[s][0], E);
+                } else if (KIND == 1) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], row_one, row_half);
+                    const bf16x8 x = pack8(pr);
+                    E = mfma(x, x, E);
+                }
+            }
+        };
+        // All waves' pieces of a step are there after a barrier that each has passed with its own there; N: younger steps in flight.
+        auto arrived = [&](auto younger) {
+            constexpr int Y = decltype(younger)::value;
+            if (w < NH) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(3 * Y) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * Y) : "memory");
+            wg_sync();
+        };
+        arrived(std::integral_constant<int, RING - 2>{});
+        factors(0, 0);
+        for (int t = 0; t < steps; ++t) {
+            arrived(std::integral_constant<int, RING - 3>{});   // step t + 1; step t - 1 has been read
+            issue(t + RING - 1);
+            const unsigned char *stage = ring + t % RING * STAGE;
+            // tiles 0, 1 of the step (d_v 128), or grp, grp + 2 (d_v 64; the segment may end before the second of them)
+            const bool both = HP == 2 || tok_begin + 32 * NH * t + 64 < tok_end;
+            bf16x8 vo[2][2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) vo[i][s][c] = load_v(stage + (HP == 2 ? 2 * i + grp : grp + 2 * i) * PART, s, c);
+            factors(t, 1);
+            products(0, vo[0]);
+            factors(t + 1 < steps ? t + 1 : t, 0);
+            if (both) products(1, vo[1]);
+        }
+    };
+    if (has4) run(std::integral_constant<int, 2>{});
+    else if (has_x) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, 0>{});
+
+    // ---- the entry: slot 6 c + T, and slot 5 (the moments) ----
+    float *e = ws + (size_t)u * (G - 1) * entry_floats(NC) + (size_t)seg * entry_floats(NC) + (size_t)lane * 4;
+    auto put = [&](int slot, const f32x16 &x, float s_low, float s_high) {   // s_high: registers 12 .. 15
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f32x4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = (j < 3 ? s_low : s_high) * x[4 * j + i];
+            store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
+        }
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (HP == 1) {   // the groups' sums: the first one finishes column tile 0, the other one column tile 1 and E
+        float *x = reinterpret_cast<float *>(lds) + 4 * lane;   // (the image's place)
+        auto give = [&](int i, const f32x16 &y) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4 *>(x + i * 1024 + j * 256) = f32x4{y[4 * j], y[4 * j + 1], y[4 * j + 2], y[4 * j + 3]};
+        };
+        auto take = [&](int i, f32x16 &y) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 t = *reinterpret_cast<const f32x4 *>(x + i * 1024 + j * 256);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[4 * j + q] += t[q];
+            }
+        };
+        give(grp == 0 ? 4 + r4 : r4, grp == 0 ? S[1] : S[0]);
+        if (grp == 0 && has4) give(8 + e4, E);
+        if (grp == 0 && has_x) give(10, E);
+        wg_sync();
+        if (grp == 0) {
+            take(r4, S[0]);
+            put(r4, S[0], kSqrt2, kSqrt2);
+        } else {
+            take(4 + r4, S[1]);
+            put(6 + r4, S[1], kSqrt2, kSqrt2);
+            if (has4) {
+                take(8 + e4, E);
+                put(6 * e4 + 4, E, 2.f, kSqrt2);
+            }
+            if (has_x) {
+                take(10, E);
+                put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
+            }
+        }
+    } else {
+        put(6 * c0 + r4, S[0], kSqrt2, kSqrt2);
+        put(6 * (c0 + 1) + r4, S[1], kSqrt2, kSqrt2);
+        if (has4) put(6 * (c0 + e4) + 4, E, 2.f, kSqrt2);
+        if (has_x) put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
+    }
+    // the entry has reached memory (the stores are written through) before the flag is raised; it is read by the main-pass workgroups of
+    // segments 1 + seg .. G - 1
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid >= 1 + seg && tid < G)
+        __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Grid: first the (G - 1) increments of every unit, then the main-pass workgroups segment by segment
@@ -1027,18 +1219,18 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
     unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls, unsigned epoch, int N,
     SegTable segs, int G, int U)
 {
-    __shared__ __align__(16) Lds<NC> lds;
+    __shared__ __align__(1024) unsigned char raw[kLdsBytes];
+    Lds<NC> &lds = *reinterpret_cast<Lds<NC> *>(raw);
     int bid = blockIdx.x;
     if constexpr (!SEG) {
-        prefill_body<NC, 0, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, bid);
+        prefill_body<NC, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, bid);
     } else {
         const int n_inc = U * (G - 1);
         if (bid < n_inc) {
-            prefill_body<NC, 1, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
-                                      bid % (G - 1), bid / (G - 1));
+            increment_body<NC>(raw, k, v, state, has_init, ws, flags, epoch, N, segs, G, bid % (G - 1), bid / (G - 1));
         } else {
             bid -= n_inc;
-            prefill_body<NC, 0, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
+            prefill_body<NC, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
                                       bid / U, bid % U);
         }
     }
@@ -1092,10 +1284,10 @@ int make_segments(int N, int G, SegTable &t)
     const int T = (N + C - 1) / C;   // chunks
     if (G > T) G = T;
     if (G == 2) {
-        // Segment 0's main pass runs beside its increment, and only the other one waits: at three quarters of the tokens
-        // both end together (128 units of 2048 tokens, d_v 64: halves 43.7 us, 0.66 40.6, 0.75 39.3, 0.8 40.3; d_v 128: 61.5,
-        // 58.3, 57.4, 57.2).
-        const int first = T < 4 ? 1 : 3 * T / 4;
+        // Segment 0's main pass runs beside its increment, and only the other one waits: both end together (128 units of 2048 tokens, d_v 64:
+        // 0.6 of the tokens 39.5 us, 0.68 38.1, 0.72 36.7, 0.76 36.0; of 4096 0.6 64.5, 0.68 62.1, 0.72 63.7, 0.76 65.3; of 1024 25.8, 24.9, 24.8,
+        // 23.7; d_v 128, 2048 tokens 56.1, 55.3, 54.1, 54.4).
+        const int first = T < 4 ? 1 : (int)(0.72f * (float)T);
         t.begin[0] = 0;
         t.begin[1] = first * C;
         for (int g = 2; g <= kMaxSegments; ++g) t.begin[g] = T * C;

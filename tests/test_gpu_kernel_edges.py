@@ -237,6 +237,27 @@ def test_prefill_segments_from_a_state(based, packed, U, dv, N1, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
+# bf16 d' = 16 prefill: increments of odd and even numbers of chunks, of fewer and more steps than the ring of rows has, with and without a state
+@pytest.mark.parametrize("init", [False, True])
+@pytest.mark.parametrize("dv,N", [(64, 641), (64, 64 * 11), (64, 64 * 17 + 5), (64, 64 * 32), (128, 641), (128, 64 * 12 + 63), (128, 64 * 21)])
+def test_prefill_increments(based, dv, N, init):
+    U, N1 = 66, 40 if init else 0
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
+    q, k, v = synth.linattn_inputs(wl, units=3, N=N1 + N)
+    at = np.arange(U) % 3
+    state = based.alloc_state(1, U, 16, dv)
+    got = [down(based.prefill(*(up(a[at, lo:hi], "bf16", (1, U, hi - lo, d)) for a, d in ((q, 16), (k, 16), (v, dv))), state=state,
+                              has_init=lo > 0)).reshape(U, hi - lo, dv) for lo, hi in ((0, N1), (N1, N1 + N)) if hi > lo]
+    y = np.concatenate(got, 1)
+    S, z = (down(a)[0] for a in based.state_export(state, 1, U, 16, dv))
+    for a in (y, S, z):
+        assert (a == a[at]).all()
+    check_close(rows(y[:3]), rows(oracle.linattn_quadratic(q, k, v)), TOL["bf16"], "y")
+    Sw, zw = oracle.linattn_state(k, v)
+    check_close(S[:3], Sw, TOL["bf16"], "S")
+    check_close(z[:3], zw, TOL["bf16"], "z")
+
+
 # bf16 d' = 32 prefill: one token, around a chunk and the smallest number of chunks that is cut into segments, few and many segments,
 # the initial state read by one workgroup (one segment, d_v 64) and by several, both state layouts
 @pytest.mark.parametrize("packed", [False, True])
