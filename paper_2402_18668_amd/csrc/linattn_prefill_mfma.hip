@@ -59,10 +59,9 @@
 // accumulator tile), i.e. sum k_a k_b, sum k_a and the token count; phi(q).z =
 // count + q.z1 + q^T M q / 2 is evaluated with two small MFMAs (M' split into bf16 hi + lo).
 //
-// Long sequences / few units: the sequence is cut into G segments.  Update-only workgroups compute
-// each segment's state increment, and the main-pass workgroup of a segment starts from the sum of
-// the increments before it.  Both kinds run in one launch: the increment workgroups come first in
-// the grid, the main-pass workgroups wait (bounded) on per-entry ready flags in the workspace.
+// Long sequences / few units: the sequence is cut into G segments, a workgroup each.  The workgroup of segment g > 0 first computes the state
+// increment of segment g - 1; its main pass starts from that and the sum of the increments before, which the other workgroups leave in the workspace
+// and for which it waits (bounded) on per-entry ready flags.
 #include "common.h"
 
 #include <atomic>
@@ -106,6 +105,10 @@ __host__ __device__ constexpr size_t entry_floats(int nc) { return (size_t)nc * 
 __host__ __device__ constexpr int producers(int nc) { return nc == 2 ? 6 : 4; }
 __host__ __device__ constexpr int x_wave(int nc) { return nc == 2 ? 2 : 3; }
 __host__ __device__ constexpr int x_tile(int nc) { return nc == 2 ? 0 : 3; }
+// Bytes of the state buffer's image in LDS; where the increment's rows lie there and, afterwards, what it leaves to the main pass.
+constexpr int IMG_LD = 40;   // (the two rows that the halves of a wave access lie in different banks)
+__host__ __device__ constexpr int image_bytes(int nc) { return nc * 32 * NTILE * IMG_LD * 4; }
+__host__ __device__ constexpr int hand_at(int nc) { return nc == 2 ? image_bytes(2) : 0; }   // (at d_v 128 where the image was)
 template <int NC>
 struct Lds {
     // the q and k rows of a chunk, by its parity: building one chunk's operands and staging the next one's rows need nothing but the
@@ -289,7 +292,6 @@ __device__ __forceinline__ bf16x8 one_at(int g, int target, uint32_t one)
 // address, and the whole workgroup moves 16-byte pieces between the image and the buffer's rows.  (Read and
 // written by the consumers straight from and to memory, 160 four-byte accesses to a lane with an address each, it took
 // 12 us to read and 5-6 us to write at 16 units, d_v 64.)
-constexpr int IMG_LD = 40;   // (the two rows that the halves of a wave access lie in different banks)
 template <int NC> struct Image {
     static constexpr int NTHR = 64 * (NC + producers(NC)), DV = 32 * NC;
     static constexpr int Q = 32 * NTILE * (DV / 4), STEPS = (Q + NTHR - 1) / NTHR;   // 16-byte pieces: all, per thread
@@ -336,14 +338,13 @@ struct SegTable { int begin[kMaxSegments + 1]; };
 
 }  // namespace
 
-// Full prefill of the segment (readout + update); starts from the sum of workspace entries 1 .. seg.
+// Full prefill of the segment (readout + update); starts from what the workgroup's own increment has left in LDS (seg > 0) and the sum of workspace
+// entries 1 .. seg - 1.
 // The caller's initial state is read by the main pass of segment 0 and by the increment of segment 0, which starts from
 // it (so that the other segments get it with their first entry).  The last segment overwrites it with the final state, and
 // waits until both have read it.
-// Increments and main pass run in ONE launch.  A main-pass workgroup of segment g > 0 waits (bounded)
-// for the flags of the increments before it.  Flag word F[unit][p][g] == epoch tells the main-pass
-// workgroup of segment g that entry p of this call is complete (p = 0, g = G - 1: that the main pass of segment 0
-// has read the initial state): every word has one writer and one
+// Flag word F[unit][p][g] == epoch tells the workgroup of segment g that entry p (the increment of segment p - 1, p < g) of this call is complete (p = 0,
+// g = G - 1: that the main pass of segment 0 has read the initial state): every word has one writer and one
 // reader, and the reader zeroes it once it has seen it, so the words are clear again when the launch
 // ends (a replay of a captured launch, which repeats the same epoch, starts from cleared flags).
 // SEG: the launch has several segments.
@@ -393,10 +394,21 @@ __device__ __forceinline__ void prefill_body(
     // A main pass that starts from entries waits for the increments of this call (the last segment also for the initial state to have been
     // read) while its producers stage the first chunk and build what does not need the sum: 16 units of 777 tokens from a state
     // 18.1 us with the wait at the start, 17.0 with it here; without one, d_v 128 22.0, 19.5.
-    const bool from_entries = SEG && seg > 0;
+    const bool handed = SEG && seg > 0, from_entries = SEG && seg > 1, waits = SEG && (seg > 1 || (seg == 1 && has_init && G == 2));
+    const float *hand = reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(&lds) + hand_at(NC)) + 4 * lane;
+    auto handed_tile = [&](int slot) {   // what the workgroup's own increment has left
+        f32x16 x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 t = *reinterpret_cast<const f32x4 *>(hand + slot * kSlotFloats + j * 256);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[4 * j + i] = t[i];
+        }
+        return x;
+    };
     auto wait_flags = [&]() {   // one thread
         bool gave_up = false;
-        for (int p = has_init && seg == G - 1 ? 0 : 1; p <= seg; ++p) {
+        for (int p = has_init && seg == G - 1 ? 0 : 1; p < seg; ++p) {
             unsigned *f = flags_unit + p * G + seg;
             int polls = 0;
             while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != epoch) {
@@ -562,6 +574,12 @@ __device__ __forceinline__ void prefill_body(
                 for (int r = 0; r < 16; ++r) S[T][r] = image_lane[(32 * T + 8 * (r >> 2) + (r & 3)) * IMG_LD];
             state_was_read();
         }
+        if (handed) {
+#pragma unroll
+            for (int T = 0; T < NTILE; ++T) S[T] = handed_tile(6 * c + T);
+            if (has_x) X = handed_tile(6 * x_tile(NC) + 5);
+            wg_sync();
+        }
 
         {
             // V operand of an MFMA (lane (g, n): column 32 c + n at the 8 tokens of its k-slots, two runs of
@@ -585,10 +603,10 @@ __device__ __forceinline__ void prefill_body(
             wg_sync();   // the producers have staged the first chunk
             build_my_blocks(0);
             if (has_x && !from_entries) build_den(0, X);
-            if (from_entries && tid == 0) wait_flags();
+            if (waits && tid == 0) wait_flags();
             wg_sync();   // the operands of the first chunk are visible (but the denominators, where these need the entries)
             if (from_entries) {   // the increments of earlier segments
-                for (int p = 1; p <= seg; ++p) {
+                for (int p = 1; p < seg; ++p) {
                     const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
                     f32x4 x[24];
                     load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, x);
@@ -734,17 +752,9 @@ __device__ __forceinline__ void prefill_body(
         zero16(X);
         const bool has_m = NC == 2 && holds_x;
         if (has_init && seg == 0 && has_m) import_moments(X);
-        if (has_init && seg == 0) state_was_read();
+        if (handed && has_m) X = handed_tile(6 * x_tile(NC) + 5);
 
         {
-            // once: the row sums of a block that does not exist (key tile 1 against query tile 0)
-            // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
-            // not wait for this wave)
-            if (ptid < 32) {
-                lds.den[0][2][ptid] = 0.f;
-                lds.den[1][2][ptid] = 0.f;
-            }
-
             // ---- staging: global -> registers -> LDS --------------------------------------------
             // A chunk of V is one contiguous block of 64 rows x DV columns, in 16-byte pieces: piece p is row p / (DV / 8), columns
             // 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128 pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  A wave
@@ -925,6 +935,15 @@ __device__ __forceinline__ void prefill_body(
             };
             load_x(tok_begin);
             load_v(tok_begin);
+            if (has_init && seg == 0) state_was_read();
+            if (handed) wg_sync();   // what the increment has left has been read
+            // once: the row sums of a block that does not exist (key tile 1 against query tile 0)
+            // (only the first 32 queries of den[.][2]: the other half belongs to block 2, whose builder does
+            // not wait for this wave)
+            if (ptid < 32) {
+                lds.den[0][2][ptid] = 0.f;
+                lds.den[1][2][ptid] = 0.f;
+            }
             stage_x(tok_begin, 0);
             load_x(tok_begin + C);
             wg_sync();   // the first chunk's rows are staged
@@ -935,7 +954,7 @@ __device__ __forceinline__ void prefill_body(
             if (from_entries) {
                 if (has_m) {
                     role_guard();
-                    for (int p = 1; p <= seg; ++p) {
+                    for (int p = 1; p < seg; ++p) {
                         const float *e = ws_unit + (size_t)(p - 1) * entry_floats(NC) + lane_off;
                         f32x4 x[24];
                         load_wave_slots_coherent(e + 1 * kSlotFloats, e + 3 * kSlotFloats, e + 5 * kSlotFloats, x);
@@ -969,15 +988,18 @@ __device__ __forceinline__ void prefill_body(
     }
 }
 
-// State increment of segment `seg`, to workspace entry 1 + seg.
+// State increment of segment `seg`, left in LDS for the main pass of the next segment and, where a later one needs it too, in workspace entry 1 + seg.
 //
 // The eight waves need no operand from each other here, so nothing but the rows passes through LDS, and a step has one barrier.  Wave r = w % 4
 // owns tile r for two column tiles (waves 2 and 3 also tile 4, for one of them; wave 1 the moments), and a feature is a product of two
 // values in its registers: multiplied with 0/1 matrices a tile of 32 rows of K comes back as accumulators, in fp32 and without rounding, with lane
 // n holding k_a (halved) or the k_b of its row and the registers going over the tokens in the order of an operand's k-slots.  At d_v 64 the waves 0-3
 // and 4-7 take alternate tiles of 32 tokens and are added up at the end; at d_v 128 they own 64 columns each.  The rows come by the 16-byte LDS
-// DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), two steps ahead.  Every row is a sum of halved products: pair rows
-// are scaled by sqrt(2), the others by 2, the moments by 4 when they are stored.
+// DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  Every row is a sum of halved products: pair rows
+// are scaled by sqrt(2), the others by 2, the moments by 4 when they are put away.
+//
+// Bound: memory, with half of the chip at increments and half at main passes (128 units: 1300 cycles a chunk at d_v 64, 2300 at 128, 4.1 TB/s together;
+// 16 units 1200); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
 template <int NC>
 __device__ __forceinline__ void increment_body(
     unsigned char *lds, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state, int has_init,
@@ -986,8 +1008,8 @@ __device__ __forceinline__ void increment_body(
     constexpr int DV = 32 * NC, HP = NC / 2;      // HP: 64-column parts
     constexpr int NH = 4 / HP;                    // 32-token tiles of a step
     constexpr int PART = 32 * 64 * 2, TILE_K = 32 * DP * 2, STAGE = 4 * PART + NH * TILE_K, RING = 5;
-    constexpr int IMAGE = NC * 32 * NTILE * IMG_LD * 4, AT = HP == 1 ? IMAGE : 0;   // (at d_v 128 the rows lie where the image was)
-    static_assert(AT + RING * STAGE <= kLdsBytes && 11 * 4096 <= IMAGE && IMAGE <= kLdsBytes, "");
+    constexpr int IMAGE = image_bytes(NC), AT = hand_at(NC);
+    static_assert(AT + RING * STAGE <= kLdsBytes && 11 * 4096 <= IMAGE && IMAGE <= kLdsBytes && AT + NC * 6 * 4096 <= kLdsBytes, "");
     const bool packed_state = (has_init & 2) != 0;
     has_init &= 1;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1150,14 +1172,17 @@ __device__ __forceinline__ void increment_body(
     else run(std::integral_constant<int, 0>{});
 
     // ---- the entry: slot 6 c + T, and slot 5 (the moments) ----
+    const bool publish = seg + 2 < G;   // later segments need it, too
     float *e = ws + (size_t)u * (G - 1) * entry_floats(NC) + (size_t)seg * entry_floats(NC) + (size_t)lane * 4;
+    float *hand = reinterpret_cast<float *>(lds + AT) + 4 * lane;
     auto put = [&](int slot, const f32x16 &x, float s_low, float s_high) {   // s_high: registers 12 .. 15
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             f32x4 o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = (j < 3 ? s_low : s_high) * x[4 * j + i];
-            store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
+            *reinterpret_cast<f32x4 *>(hand + slot * kSlotFloats + j * 256) = o;
+            if (publish) store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
         }
     };
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1195,23 +1220,29 @@ __device__ __forceinline__ void increment_body(
             }
         }
     } else {
+        wg_sync();   // (the last rows have been read)
         put(6 * c0 + r4, S[0], kSqrt2, kSqrt2);
         put(6 * (c0 + 1) + r4, S[1], kSqrt2, kSqrt2);
         if (has4) put(6 * (c0 + e4) + 4, E, 2.f, kSqrt2);
         if (has_x) put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
     }
-    // the entry has reached memory (the stores are written through) before the flag is raised; it is read by the main-pass workgroups of
-    // segments 1 + seg .. G - 1
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid >= 1 + seg && tid < G)
-        __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (publish) {   // the entry has reached memory (the stores are written through) before the flags are raised
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid >= 2 + seg && tid < G)
+            __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else {
+        wg_sync();
+    }
 }
 
-// Grid: first the (G - 1) increments of every unit, then the main-pass workgroups segment by segment
-// (all segment-0 workgroups first: they depend on nothing and fill the slots the increment
-// workgroups leave free).  A launch of one segment is a kernel of its own, without the code of increments and entries: a short call runs
-// its code once and waits for its instructions (16 units of 64 tokens: 6.5 and 7.8 us at the two widths with one kernel for all, 6.1 and 7.3).
+// Grid: segment by segment, so that a workgroup only waits for workgroups before it.  A launch of one segment is a kernel of its own, without the code of
+// increments and entries: a short call runs its code once and waits for its instructions (16 units of 64 tokens: 6.5 and 7.8 us at the two widths with
+// one kernel for all, 6.1 and 7.3).
+// The workgroup of a segment g > 0 computes the increment of segment g - 1 itself, hands it to its main pass in LDS, and publishes it only if a later segment needs
+// it.  (Before, increments were workgroups of their own and all main passes fetched entries: 128 units of 2048 tokens, d_v 64 36.7 -> 35.2 us, d_v 128
+// 54.4 -> 49.1, 1024 tokens 33.5 -> 29.4; 64 units of 1024 20.8 -> 17.2, of 777, d_v 128, 25.7 -> 21.3: three and more segments of that many units were two
+// rounds of the chip.)
 template <int NC, bool SEG>
 __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
@@ -1221,78 +1252,55 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
 {
     __shared__ __align__(1024) unsigned char raw[kLdsBytes];
     Lds<NC> &lds = *reinterpret_cast<Lds<NC> *>(raw);
-    int bid = blockIdx.x;
     if constexpr (!SEG) {
-        prefill_body<NC, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, bid);
+        prefill_body<NC, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, blockIdx.x);
     } else {
-        const int n_inc = U * (G - 1);
-        if (bid < n_inc) {
-            increment_body<NC>(raw, k, v, state, has_init, ws, flags, epoch, N, segs, G, bid % (G - 1), bid / (G - 1));
-        } else {
-            bid -= n_inc;
-            prefill_body<NC, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G,
-                                      bid / U, bid % U);
-        }
+        const int seg = blockIdx.x / U, u = blockIdx.x % U;
+        if (seg > 0) increment_body<NC>(raw, k, v, state, has_init, ws, flags, epoch, N, segs, G, seg - 1, u);
+        prefill_body<NC, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G, seg, u);
     }
 }
 
 // ---- host side ----------------------------------------------------------------------------------
 namespace {
 
-// Segments per sequence.  At most what fills the chip once (one workgroup per CU fits): beyond that more segments only add
-// increment work and workspace traffic (d_v 64, 2048 tokens: 128 units 1 segment 50.5 us, 2 39.6, 3 51.9; 86 units 49.8, 38.2, 39.1; 129 units
-// 50.6, 55.8, 51.9; 200 units 50.9, 70.0, 70.9).  With few units the chip is not the limit: G segments make a chain of chunks / G increment chunks,
-// G entries to sum up and chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 13 chunks 1 segment
-// 22.6 us, 3 16.6, 5 14.8, 8 16.9; 24 chunks 2 28.7, 4 21.2, 6 18.1, 8 18.5, 12 24.3; 64 chunks 8 28.1, 12 27.6, 16 31.7); below 6 chunks
-// a second segment does not pay for its hand-over (4 chunks: 1 segment 10.0 us, 2 10.6, 3 11.1; 5 chunks 11.6, 11.9, 11.8; 6 chunks 12.9, 12.5, 11.8).
-// Two exceptions:
-// - Below 10 chunks the hand-over is a large part of the call, the more so the wider the heads and the more units share the memory:
-//   one segment with more than 40 units (d_v 128, up to 7 chunks), 51 (d_v 64, 6 chunks) or 85 (d_v 128, and d_v 64 up to 7 chunks), and no
-//   more than three up to 8 chunks or with more than 42 units at d_v 128.  (us without and from a state; d_v 128, 384 tokens: 40
-//   units 1 segment 17.6, 19.6, 3 16.7, 19.7; 41 units 1 17.5, 19.7, 3 17.6, 21.7; 60 units 1 18.0, 20.2, 3 20.9, 23.2; 128 units 1 19.1, 22.3, 2 22.0,
-//   26.0; 448 tokens, 60 units 1 19.8, 22.0, 2 18.9, 23.6; 512 tokens, 60 units 1 21.6, 23.9, 3 21.8, 23.8, 4 26.4, 25.3; 72 units 1 21.8, 24.1, 3 21.9,
-//   24.9; d_v 64, 384 tokens, 52 units 1 13.5, 15.2, 3 14.7, 17.3; 448 tokens, 86 units 1 15.5, 17.0, 2 16.8, 21.5; 512 tokens, 48 units 3 13.7,
-//   16.2, 4 15.5, 16.0.)  The lines are from before one segment had a kernel of its own, which moved them a little: just below, one segment
-//   would gain (85 units of 512 tokens, d_v 128, 3 as chosen 23.6, 26.4, 1 22.0, 24.6; d_v 64, 86 units of 512 2 17.4, 21.5, 1 17.0, 18.5; 51 of 384 3 14.1,
-//   17.5, 1 13.4, 15.1).
-// - Long sequences, 86 .. 102 units: 5 U workgroups, three segments, are two rounds of the chip like the two segments' 3 U (d_v
-//   64, 100 units: 4096 tokens 2 segments 71.7 us, 3 70.6; 8192 138, 130; 110 units 8192 139, 160; d_v 128, 86 units: 4096 94.6, 92.5; 16384
-//   364, 342).
+// Segments per sequence.  At most what fills the chip once (one workgroup per CU fits): beyond that a segment's workgroup waits for a CU as well (d_v 64, 2048
+// tokens: 64 units 4 segments 25.5 us, 5 33.5; 128 units 2 35.2, 3 48.9).  With few units the chip is not the limit: G segments make a chain of
+// chunks / G increment chunks, G - 2 entries to sum up and chunks / G chunks of the main pass, shortest for G ~ sqrt(2 chunks) (16 units, d_v 64: 8 chunks 1
+// segment 15.2, 3 12.3, 4 11.9, 5 12.7; 13 chunks 1 21.8, 4 14.3, 5 13.7, 6 14.3; 32 chunks 5 21.5, 6 20.4, 8 19.1, 10 20.9; 64 chunks 6 29.6, 8 26.4, 10 25.4; d_v 128,
+// 13 chunks 4 18.9, 5 17.5, 6 18.5; 32 chunks 6 26.4, 8 24.7, 10 26.9).  Below that a second segment does not pay for its increment (1 segment and 2, 16 and 128
+// units: d_v 64, 4 chunks 9.9, 10.4 and 11.4, 12.0; 5 chunks 11.1, 10.5 and 12.7, 12.2; d_v 128, 5 chunks 13.9, 14.2 and 16.2, 16.6; 6 chunks 15.6, 15.2 and 17.8, 17.8,
+// from a state 17.8, 17.8 and 20.9, 21.4; three of 6 chunks, 16 units: 10.9 and 13.9).
 int pick_segments(int U, int N, int dv)
 {
     const int chunks = (N + C - 1) / C;
-    if (chunks < 6) return 1;
     const bool wide = dv == 128;
+    if (chunks < (wide ? U > 85 ? 7 : 6 : 5)) return 1;
     int G = 256 / U;
-    if (G == 2 && 5 * U <= 512 && chunks >= 64) G = 3;
-    if (chunks < 10) {
-        if (U > 85 ? wide || chunks < 8 : wide ? U > 40 && chunks < 8 : U > 51 && chunks < 7) return 1;
-        if (G > 3 && (chunks < 9 || (wide && U > 42))) G = 3;
-    }
-    const int chain = (int)(sqrtf(2.f * (float)chunks) + 0.5f);
+    const int chain = chunks == 5 ? 2 : (int)(sqrtf(2.f * (float)chunks) + 0.5f);
     if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
     return G < 1 ? 1 : G;
 }
 
-// Segment boundaries.  The main pass starts segment g by summing g workspace entries and the last
-// segment also writes the final state, so later segments get fewer chunks, so that the main-pass
-// workgroups, which run side by side, end close together.
-// Returns the number of segments actually used (a short sequence may leave trailing ones empty).
-int make_segments(int N, int G, SegTable &t)
+// Segment boundaries (multiples of the chunk length).  Returns the number of segments.
+int make_segments(int N, int G, int dv, SegTable &t)
 {
     const int T = (N + C - 1) / C;   // chunks
     if (G > T) G = T;
     if (G == 2) {
-        // Segment 0's main pass runs beside its increment, and only the other one waits: both end together (128 units of 2048 tokens, d_v 64:
-        // 0.6 of the tokens 39.5 us, 0.68 38.1, 0.72 36.7, 0.76 36.0; of 4096 0.6 64.5, 0.68 62.1, 0.72 63.7, 0.76 65.3; of 1024 25.8, 24.9, 24.8,
-        // 23.7; d_v 128, 2048 tokens 56.1, 55.3, 54.1, 54.4).
-        const int first = T < 4 ? 1 : (int)(0.72f * (float)T);
+        // The first segment's main pass takes as long as its increment and the main pass of the second: a chunk of the increment is 0.46 of one of the main
+        // pass (d_v 128: 0.6, where it is bound by memory), the second workgroup also fills its pipelines twice and writes the state (128 units, a chunk less, as
+        // here and a chunk more: d_v 64, 1024 tokens 22.8, 21.9, 22.9 us, 2048 35.9, 35.2, 36.2, 4096 61.6, 63.3, 64.7; d_v 128 29.8, 29.4, 30.0,
+        // 49.4, 49.1, 49.2, 99.5, 99.9, 97.8).
+        const int first = dv == 64 ? (int)(0.65f * (float)T + 2.f) : (int)(0.72f * (float)T + 1.5f);
         t.begin[0] = 0;
-        t.begin[1] = first * C;
+        t.begin[1] = (first < T ? first : T - 1) * C;
         for (int g = 2; g <= kMaxSegments; ++g) t.begin[g] = T * C;
-        return T < 2 ? T : 2;
+        return 2;
     }
+    // More segments: all of them wait for the longest increment, and the main pass of segment g then sums g - 1 entries, the last one also writes the final
+    // state, so later segments get fewer chunks.
     int len[kMaxSegments];
     int sum = 0;
     for (int g = 0; g < G; ++g) {
@@ -1313,8 +1321,7 @@ int make_segments(int N, int G, SegTable &t)
     return G;
 }
 
-// Workspace: room for G entries per unit (G - 1 are used; what fits the static scratch is part of the interface and stays as it
-// was), then G x G ready-flag words per unit (256-byte aligned).
+// Workspace: room for G entries per unit (G - 2 are used; what fits the static scratch is part of the interface), then G x G ready-flag words per unit (256-byte aligned).
 size_t ws_entry_bytes(int U, int N, int dv)
 {
     return (size_t)U * pick_segments(U, N, dv) * entry_floats(dv / 32) * sizeof(float);
@@ -1334,10 +1341,10 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     SegTable segs;
     // a smaller G only uses a prefix of the workspace that was sized for pick_segments()
     const int Gmax = pick_segments(U, N, dv);
-    const int G = make_segments(N, Gmax, segs);
+    const int G = make_segments(N, Gmax, dv, segs);
     // what the kernels index must lie inside what the workspace was sized for
     if (G < 1 || G > Gmax || segs.begin[G] < N) return hipErrorInvalidValue;
-    if ((long long)U * (2 * G - 1) >= (1ll << 31)) return hipErrorInvalidValue;
+    if ((long long)U * G >= (1ll << 31)) return hipErrorInvalidValue;
     float *ws = static_cast<float *>(workspace);
     unsigned *flags = reinterpret_cast<unsigned *>((char *)workspace + ws_entry_bytes(U, N, dv));
     // Every call raises its flags to a value no earlier call used: the flag words of a workspace
@@ -1345,7 +1352,7 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     static std::atomic<unsigned> calls{0};
     const unsigned epoch = 0x5EED0000u + calls.fetch_add(1u) + 1u;
     const auto kernel = G > 1 ? prefill_mfma_kernel<NC, true> : prefill_mfma_kernel<NC, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(U * (2 * G - 1))), dim3(64 * (NC + producers(NC))), 0, s, q, k, v,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(U * G)), dim3(64 * (NC + producers(NC))), 0, s, q, k, v,
                        y, state, flags_word, ws, flags, status, g_flag_poll_limit.load(), epoch, N, segs, G, U);
     return hipGetLastError();
 }

@@ -728,11 +728,11 @@ def test_prefill_dp32_group_counts(based, U, dv, N):
     check_close(z[:few], zw, TOL["bf16"], "z")
 
 
-# bf16 d' = 16 prefill: the exceptions of the rule for the number of segments (below 10 chunks one segment, or at most three, from so many
-# units on; long sequences of 86 to 102 units in three segments), and its neighbours
+# bf16 d' = 16 prefill: around the lines of the rule for the number of segments, few and many units of few and many chunks
 @pytest.mark.parametrize("U,dv,N", [(60, 64, 380), (60, 128, 600), (86, 128, 513), (48, 128, 384), (86, 64, 4033), (102, 64, 4100), (103, 64, 4100),
                                     (100, 128, 4097), (51, 64, 384), (52, 64, 384), (85, 64, 448), (86, 64, 448), (40, 128, 448), (41, 128, 400), (72, 128, 449),
-                                    (86, 128, 576), (42, 128, 576), (43, 128, 576), (48, 64, 512)])
+                                    (86, 128, 576), (42, 128, 576), (43, 128, 576), (48, 64, 512), (128, 64, 257), (128, 64, 256),
+                                    (128, 128, 385), (129, 64, 700), (3, 64, 321), (1, 64, 64 * 128 + 1)])
 def test_prefill_segment_rule(based, U, dv, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
     q, k, v = synth.linattn_inputs(wl, units=U, N=N)
