@@ -99,6 +99,10 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
 // vmcnt), so ST - 1 stages stay in flight.  Steps past the end re-read the last one, which keeps the count
 // constant.  (The DMA is inline asm: through the builtin the compiler makes every LDS read wait for all of it.)
 //
+// Groups.  KG > 1: groups of WM x WN waves, with stages of their own, take a KG-th of the steps each, and the first one adds up (all go through as
+// many steps: a group whose share is one shorter starts one step early and clears its accumulators after that).  The stages of all groups are in flight at once, and a
+// group's barriers and operand reads hide behind the others' products.
+//
 // The operand reads of the next slab and the DMA pieces sit one by one between the matrix instructions: in bursts they
 // hold up the wave, and with it the matrix pipe, until the LDS and the memory pipeline have taken them.  16x16x32 matrix
 // instructions, not 32x32x16: they move half the accumulator registers per product, and under this load the chip does not hold
@@ -108,9 +112,10 @@ __device__ __forceinline__ RowPos row_after(RowPos p, int delta, int seq_len)
 constexpr int MT = 16;         // MFMA tile: 16 x 16, in
 constexpr int SD = 32;         // slabs of 32 (the 16x16x32 instruction)
 constexpr int BK = 64;         // columns of a stage
-template <int BM_, int BN_, int WM_, int WN_, int ST_, int SPREAD_ = 8> struct Tile {
+template <int BM_, int BN_, int WM_, int WN_, int ST_, int SPREAD_ = 8, int KG_ = 1> struct Tile {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_, SPREAD = SPREAD_;
-    static constexpr int NW = WM * WN, NT = 64 * NW;
+    static constexpr int KG = KG_;                               // groups of NW waves that share out the steps
+    static constexpr int NW = WM * WN, NT = 64 * NW * KG;
     static constexpr int TI = BM / WM / MT, TJ = BN / WN / MT;   // MFMA tiles of a wave: tokens, features
     static constexpr int CPR = BK / 8;                           // 16-byte pieces per staged row
     static constexpr int RPI = 64 / CPR;                         // rows one DMA instruction moves
@@ -119,8 +124,9 @@ template <int BM_, int BN_, int WM_, int WN_, int ST_, int SPREAD_ = 8> struct T
     static constexpr int STAGE = (BM + BN) * BK * 2;             // bytes
     static constexpr int OUT_LD = BN / WN + 8;                   // bf16 elements per row of a wave's output staging
     static constexpr int OUT = NW * 32 * OUT_LD * 2;
-    static constexpr int LDS = ST * STAGE > OUT ? ST * STAGE : OUT;
+    static constexpr int RING = ST * STAGE > OUT ? ST * STAGE : OUT, LDS = KG * RING;
     static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0 && KS % 2 == 0, "");
+    static_assert(KG == 1 || 4 * BM * BN <= RING, "");
 };
 
 // f(0), f(1), .. f(N - 1) with constant arguments (the loops over accumulators must unroll, however long)
@@ -151,7 +157,8 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
 {
     constexpr int TI = T::TI, TJ = T::TJ, KS = T::KS, P = T::P, ST = T::ST, CPR = T::CPR;
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane / MT, n = lane % MT;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane / MT, n = lane % MT;
+    const int w = wave % T::NW, group = wave / T::NW;
     const int wm = w / T::WN, wn = w % T::WN;
 
     // permutation of the 16-byte pieces of a row
@@ -175,15 +182,25 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
 #pragma unroll
         for (int p = 0; p < T::BP; ++p) src[T::AP + p] = (uint32_t)(2 * ((size_t)((p * T::NW + w) * T::RPI + r) * K + c));
     }
+    if (T::KG > 1) lds += group * T::RING;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds + (uint32_t)w * 1024;
-    const int steps = K / BK;
+    const int all_steps = K / BK, steps = (all_steps + T::KG - 1) / T::KG;   // of the tile, of a group
     int next = 0;   // the step the addresses stand at
+    bool extra = false;   // the group's first step is the one before its share, and taken out again
+    if (T::KG > 1 && group > 0) {
+        next = (group * all_steps + T::KG - 1) / T::KG;
+        extra = ((group + 1) * all_steps + T::KG - 1) / T::KG - next < steps;
+        if (extra) --next;
+        wbase += BK * next;
+        const int head = HEADS_IN ? next * BK / hl.d_in : 0;
+        xbase += HEADS_IN ? (size_t)head * hl.seq_len * hl.d_in + (next * BK - head * hl.d_in) : (size_t)(BK * next);
+    }
     auto issue = [&](int p, int slot) {
         const int at = p < T::AP ? p * T::NW : T::BM / T::RPI + (p - T::AP) * T::NW;
         dma16(p < T::AP ? xbase : wbase, src[p], lds0 + (uint32_t)(slot * T::STAGE + at * 1024));
     };
     auto advance = [&]() {   // (the last step is re-read instead of a step past the end)
-        if (next + 1 >= steps) return;
+        if (next + 1 >= all_steps) return;
         ++next;
         wbase += BK;
         xbase += BK;   // head-major x: column k0 % d_in of head k0 / d_in, one head = seq_len rows on
@@ -253,8 +270,21 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
             });
         });
         slot = after;
+        if (T::KG > 1 && kt == 0 && extra) {   // (uniform)
+            constexpr_for<NM>([&](auto mc) { acc[decltype(mc)::value / TI][decltype(mc)::value % TI] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+        }
     }
     dma_barrier<0>();   // nothing lands in LDS any more
+    if constexpr (T::KG > 1) {   // the other groups' sums, through their stages
+        unsigned char *first = lds - group * T::RING;
+        auto sums = [&](int of, int m) -> f32x4 & { return reinterpret_cast<f32x4 *>(first + of * T::RING)[(m * T::NW + w) * 64 + lane]; };
+        if (group > 0) constexpr_for<NM>([&](auto mc) { sums(group, decltype(mc)::value) = acc[decltype(mc)::value / TI][decltype(mc)::value % TI]; });
+        __syncthreads();
+        if (group > 0) return;
+        constexpr_for<T::KG - 1>([&](auto gc) {
+            constexpr_for<NM>([&](auto mc) { acc[decltype(mc)::value / TI][decltype(mc)::value % TI] += sums(decltype(gc)::value + 1, decltype(mc)::value); });
+        });
+    }
 
     // epilogue: lane (g, n) of tile (j, i) holds token MT (TI wm + i) + n, features MT (TJ wn + j) + 4 g + e in register e.  32
     // tokens at a time through this wave's staging rows, then whole row segments.
@@ -298,28 +328,38 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
 }
 
 // Blocks 0 .. : the first `whole` tiles of T; the blocks after them: the remaining tiles in halves of BM / 2 tokens (T2).
-// Block -> tile: XCD b % 8 works through a contiguous eighth of the tiles, features fastest, so that the tiles it has in
-// hand share rows of x and W in its L2 (and a problem of one band of rows still uses all XCDs).
+// Block -> tile: XCD b % 8 works through a contiguous eighth of the tiles, so that the tiles it has in hand share rows of x and W in
+// its L2 (and a problem of one band of rows still uses all XCDs).  Where x is the larger operand, features fastest: an XCD reads an
+// eighth of x and all of W.  With 4 M < 3 N, rows fastest: an eighth of W and all of x.  (us, q / k / v projection 1792 -> 2560 features and output
+// projection 2048 -> 1792 in turn, features fastest and rows fastest: 100 tokens 14.2, 11.6, 256 17.0, 14.5, 512 22.6, 20.3, 777 31.7, 25.7,
+// 1024 32.3, 28.8, 1500 38.7, 36.5; 2048, the first one alone over the line, 44.0, 44.2, 2400 50.8, 51.2.)
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
-__global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NW / 4 : T::NW / 2) void linear_tile_kernel(
+__global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NT / 256 : T::NW / 2) void linear_tile_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, uint16_t *__restrict__ y, int M, int K, int N,
     int tiles_n, int whole, int halves, HeadLayout hl)
 {
     __shared__ __align__(1024) unsigned char lds[T::LDS];
     const int per = (whole + kXcds - 1) / kXcds;
+    struct RowCol { int row, col; };
+    auto place = [&](int tile) {
+        const int bands = (M + T::BM - 1) / T::BM;
+        return 4ll * M < 3ll * N ? RowCol{tile % bands * T::BM, tile / bands * T::BN} : RowCol{tile / tiles_n * T::BM, tile % tiles_n * T::BN};
+    };
     int b = blockIdx.x;
     if (b < per * kXcds) {
         const int tile = b % kXcds * per + b / kXcds;
         if (tile >= whole) return;   // uniform
-        tile_body<T, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, tile / tiles_n * T::BM, tile % tiles_n * T::BN, hl);
+        const RowCol at = place(tile);
+        tile_body<T, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, at.row, at.col, hl);
     } else if constexpr (!std::is_same_v<T, T2>) {
         static_assert(T2::BM * 2 == T::BM && T2::BN == T::BN && T2::NT == T::NT && T2::LDS <= T::LDS, "");
         b -= per * kXcds;
         const int per2 = (halves + kXcds - 1) / kXcds, h = b % kXcds * per2 + b / kXcds;
         if (h >= halves) return;     // uniform
-        const int tile = whole + h / 2, row0 = tile / tiles_n * T::BM + h % 2 * T2::BM;
+        const RowCol at = place(whole + h / 2);
+        const int row0 = at.row + h % 2 * T2::BM;
         if (row0 >= M) return;       // uniform: the second half of a last band
-        tile_body<T2, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, row0, tile % tiles_n * T::BN, hl);
+        tile_body<T2, SPLIT_OUT, HEADS_IN>(lds, x, W, y, M, K, N, row0, at.col, hl);
     }
 }
 
@@ -417,11 +457,13 @@ using T128N = Tile<128, 64, 2, 2, 3>;              // 72 KB: two
 using T128 = Tile<128, 128, 2, 2, 2, 5>;       // 64 KB: two
 using T256 = Tile<256, 256, 2, 2, 2, 6>;       // 128 KB: one
 using T256H = Tile<128, 256, 2, 2, 2, 6>;
-enum Variant { ROWS1, ROWS2, TILE64, TILE128N, TILE128, TILE256 };
+using T32S = Tile<32, 32, 1, 2, 4, 8, 4>;          // 128 KB: one
+using T64S = Tile<64, 32, 2, 1, 3, 8, 4>;          // 144 KB: one
+enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64, TILE128N, TILE128, TILE256 };
 
 inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
 
-// A handful of tokens: 16 or 32 per workgroup (above 32 the 64 x 64 tiles, which read W fewer times, are as fast or faster).
+// A handful of tokens: 16 or 32 per workgroup (above 32 tiles, which read W fewer times, are as fast or faster).
 // Otherwise the tiling with the smallest expected time.  The figures are microseconds per 64-deep step, measured at
 // K 768 .. 2048, 40 .. 5120 tiles: a launch of up to 256 tiles (one per CU) is bound by the latency of a step, after
 // that each further tile per CU adds its share.  (The larger the tile the less it reads per product: at 32768 x 1792 x
@@ -429,7 +471,15 @@ inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm 
 inline Variant pick_variant(int M, int K, int N)
 {
     if (M <= 16) return ROWS1;
-    if (M <= 32 || K >= (1 << 22)) return ROWS2;   // (tiles address their rows with 32-bit offsets)
+    if (M <= 18 || K >= (1 << 22)) return ROWS2;   // (tiles address their rows with 32-bit offsets)
+    // Few tiles are bound by what a CU takes in of x and W and by the latency of a step: the smallest tiles that leave each CU at most one, the steps
+    // shared out over four groups of waves.  (us, 64 x 64 tiles and these, q / k / v projection 1792 -> 2560 features, which does not get below the 5.0
+    // that its call takes the host, and output projection 2048 -> 1792, each by itself: 40 and 64 tokens 7.0, 5.0 and 9.3, 5.8 with 32 x 32, 128 7.0, 5.7 with 64 x 32 and
+    // 9.2, 5.8, 200 9.3, 7.5 with 64 x 32; 17 tokens 5.4, 5.0 and 5.4, 5.8 there and with ROWS2, 24 5.9, 5.0 and 6.1, 5.8, 32 6.5, 4.9 and 6.7, 5.8.  512 features
+    // from 512: 100 tokens 4.3, 4.1, 400 4.4, 4.2.  More tiles than CUs take two rounds: 200 tokens to 2560 features 8.3, 17 with 32 x 32, 13 with 64 x 32.)
+    if (tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
+    if (M <= 32) return ROWS2;
+    if (tiles_of(M, N, T64S::BM, T64S::BN) <= 256) return TILE64S;
     auto per_cu = [](long tiles) { return (float)((tiles + 255) / 256); };
     Variant best = TILE64;
     float t = 0.05f + 0.21f * per_cu(tiles_of(M, N, T64::BM, T64::BN));
@@ -474,6 +524,8 @@ hipError_t launch_variant(Variant v, const uint16_t *x, const uint16_t *W, uint1
     case ROWS1: launch_rows<1, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case ROWS2: launch_rows<2, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE64: launch_tile<T64, T64, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE32S: launch_tile<T32S, T32S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE64S: launch_tile<T64S, T64S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE128N: launch_tile<T128N, T128N, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE128: launch_tile<T128, T128, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE256: launch_tile<T256, T256H, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
