@@ -330,20 +330,20 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
 // Blocks 0 .. : the first `whole` tiles of T; the blocks after them: the remaining tiles in halves of BM / 2 tokens (T2).
 // Block -> tile: XCD b % 8 works through a contiguous eighth of the tiles, so that the tiles it has in hand share rows of x and W in
 // its L2 (and a problem of one band of rows still uses all XCDs).  Where x is the larger operand, features fastest: an XCD reads an
-// eighth of x and all of W.  With 4 M < 3 N, rows fastest: an eighth of W and all of x.  (us, q / k / v projection 1792 -> 2560 features and output
+// eighth of x and all of W.  With 4 M < 3 N (launch_tile), rows fastest: `fast` tiles, an eighth of W and all of x.  (us, q / k / v projection 1792 -> 2560 features and output
 // projection 2048 -> 1792 in turn, features fastest and rows fastest: 100 tokens 14.2, 11.6, 256 17.0, 14.5, 512 22.6, 20.3, 777 31.7, 25.7,
 // 1024 32.3, 28.8, 1500 38.7, 36.5; 2048, the first one alone over the line, 44.0, 44.2, 2400 50.8, 51.2.)
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
 __global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NT / 256 : T::NW / 2) void linear_tile_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, uint16_t *__restrict__ y, int M, int K, int N,
-    int tiles_n, int whole, int halves, HeadLayout hl)
+    int fast, int rows_fast, int whole, int halves, HeadLayout hl)
 {
     __shared__ __align__(1024) unsigned char lds[T::LDS];
     const int per = (whole + kXcds - 1) / kXcds;
     struct RowCol { int row, col; };
     auto place = [&](int tile) {
-        const int bands = (M + T::BM - 1) / T::BM;
-        return 4ll * M < 3ll * N ? RowCol{tile % bands * T::BM, tile / bands * T::BN} : RowCol{tile / tiles_n * T::BM, tile % tiles_n * T::BN};
+        const int slow = __builtin_amdgcn_readfirstlane(tile / fast), rest = tile - slow * fast;
+        return RowCol{(rows_fast ? rest : slow) * T::BM, (rows_fast ? slow : rest) * T::BN};
     };
     int b = blockIdx.x;
     if (b < per * kXcds) {
@@ -459,7 +459,8 @@ using T256 = Tile<256, 256, 2, 2, 2, 6>;       // 128 KB: one
 using T256H = Tile<128, 256, 2, 2, 2, 6>;
 using T32S = Tile<32, 32, 1, 2, 4, 8, 4>;          // 128 KB: one
 using T64S = Tile<64, 32, 2, 1, 3, 8, 4>;          // 144 KB: one
-enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64, TILE128N, TILE128, TILE256 };
+using T64D = Tile<64, 64, 2, 2, 4, 8, 2>;          // 128 KB: one
+enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64D, TILE64, TILE128N, TILE128, TILE256 };
 
 inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
 
@@ -479,7 +480,7 @@ inline Variant pick_variant(int M, int K, int N)
     // from 512: 100 tokens 4.3, 4.1, 400 4.4, 4.2.  More tiles than CUs take two rounds: 200 tokens to 2560 features 8.3, 17 with 32 x 32, 13 with 64 x 32.)
     if (tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
     if (M <= 32) return ROWS2;
-    if (tiles_of(M, N, T64S::BM, T64S::BN) <= 256) return TILE64S;
+    if (tiles_of(M, N, T64S::BM, T64S::BN) <= 256 && K >= 12 * BK) return TILE64S;
     auto per_cu = [](long tiles) { return (float)((tiles + 255) / 256); };
     Variant best = TILE64;
     float t = 0.05f + 0.21f * per_cu(tiles_of(M, N, T64::BM, T64::BN));
@@ -493,7 +494,9 @@ inline Variant pick_variant(int M, int K, int N)
         const long n256 = tiles_of(M, N, T256::BM, T256::BN), rem = n256 % 256;
         offer(TILE256, 1.5f * (float)(n256 / 256) + (rem == 0 ? 0.f : rem <= 128 ? 1.f : 1.5f));   // (see launch_tile)
     }
-    return best;
+    // 64 x 64 tiles, one to a CU: two groups of waves.  (us, with one and two: 256 tokens, 1792 -> 2560 features 7.3, 7.0, 300, 400 and 512 tokens, 2048 -> 1792 9.3, 8.3,
+    // 9.4, 8.3 and 9.5, 8.5, 1000 tokens, 1024 -> 896 6.2, 6.0, but 512 -> 896 3 % slower.  128 x 64 the same way: 512 tokens, 1792 -> 2560, 9.4, 9.1, 1024, 2048 -> 1792, 12.5, 12.8.)
+    return best == TILE64 && tiles_of(M, N, T64::BM, T64::BN) <= 256 && K >= 16 * BK ? TILE64D : best;
 }
 
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
@@ -502,9 +505,10 @@ void launch_tile(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K
     const long tiles = tiles_of(M, N, T::BM, T::BN);
     // a last round of the chip that would be at most half full is dealt out in half tiles
     const long rem = tiles % 256, halves = !std::is_same_v<T, T2> && rem <= 128 ? 2 * rem : 0, whole = tiles - halves / 2;
+    const bool rows_fast = 4ll * M < 3ll * N;
     const long grid = (whole + kXcds - 1) / kXcds * kXcds + (halves + kXcds - 1) / kXcds * kXcds;
     hipLaunchKernelGGL((linear_tile_kernel<T, T2, SPLIT_OUT, HEADS_IN>), dim3((unsigned)grid), dim3(T::NT), 0, s, x, W, y, M, K,
-                       N, N / T::BN, (int)whole, (int)halves, hl);
+                       N, rows_fast ? (M + T::BM - 1) / T::BM : N / T::BN, (int)rows_fast, (int)whole, (int)halves, hl);
 }
 template <int TT, bool SPLIT_OUT, bool HEADS_IN>
 void launch_rows(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K, int N, const HeadLayout &hl, hipStream_t s)
@@ -523,6 +527,7 @@ hipError_t launch_variant(Variant v, const uint16_t *x, const uint16_t *W, uint1
     switch (v) {
     case ROWS1: launch_rows<1, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case ROWS2: launch_rows<2, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
+    case TILE64D: launch_tile<T64D, T64D, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE64: launch_tile<T64, T64, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE32S: launch_tile<T32S, T32S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE64S: launch_tile<T64S, T64S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;

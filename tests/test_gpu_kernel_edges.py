@@ -32,11 +32,12 @@ def test_linear_tilings(based, M, K, N):
     check_close(y[at], oracle.linear(x[at], W), TOL["bf16"], f"linear {M}x{K}x{N}")
 
 
-# small tiles whose steps four groups of waves share: fewer steps than groups, one short and several; bands of 32 and 64 tokens that end inside a tile; the
+# small tiles whose steps two or four groups of waves share: fewer steps than groups, one short and several; bands of 32 and 64 tokens that end inside a tile; the
 # last sizes with a tile to a CU and the first with more, with up to 32 tokens and above; a step that starts inside a head; and a last round of 256 x 256
 # tiles in halves where the tiles go rows fastest, the second half of its last band past the end
 @pytest.mark.parametrize("M,K,N", [(19, 64, 128), (32, 128, 256), (33, 192, 128), (63, 448, 256), (96, 320, 2560), (97, 320, 2560), (200, 576, 1792),
-                                   (257, 64, 1792), (32, 64, 8192), (32, 64, 8320), (512, 1792, 512), (513, 256, 512), (2100, 64, 9216)])
+                                   (257, 64, 1792), (32, 64, 8192), (32, 64, 8320), (512, 1792, 512), (513, 256, 512), (257, 1088, 2560), (1100, 1024, 896),
+                                   (1025, 960, 896), (2100, 64, 9216)])
 def test_linear_shared_steps(based, M, K, N):
     x, W = synth.linear_inputs(69, M, K, N)
     check_close(down(based.linear(up(x, "bf16"), up(W, "bf16"))), oracle.linear(x, W), TOL["bf16"], f"linear {M}x{K}x{N}")
