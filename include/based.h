@@ -120,8 +120,8 @@ int based_state_import(void *state, const float *S, const float *z, int B, int H
  *          y and the final state of that call are then INVALID although based_prefill itself
  *          returned BASED_OK (it returns when the work is enqueued).  based_prefill_status
  *          reports it.  The wait cannot time out as long as the device starts the workgroups of
- *          a launch in grid order (the workgroups waited for come first in the grid and wait for
- *          nothing), which is how the hardware dispatcher works but is not a documented promise.
+ *          a launch in grid order (what is waited for is done by workgroups before the waiting one,
+ *          and before they wait), which is how the hardware dispatcher works but is not a documented promise.
  *
  * Calls sharing a workspace or a state buffer must be ordered on one stream.
  *
