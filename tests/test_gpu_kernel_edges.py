@@ -318,6 +318,13 @@ def test_prefill_fp32_shared_increments(based, U, dv, N, init):
     check_close(z[:few], zw, TOL["f32"], "z")
 
 
+# .. and segments for one and for two workgroups to a CU, on either side of the line and well below it
+@pytest.mark.parametrize("U,dv,N,init", [(32, 64, 1152, False), (32, 64, 1153, False), (16, 128, 1152, True), (16, 128, 1153, True), (40, 64, 648, True), (40, 64, 649, False),
+                                         (20, 64, 1100, False), (8, 64, 4000, True)])
+def test_prefill_fp32_segments_to_a_cu(based, U, dv, N, init):
+    test_prefill_fp32_shared_increments(based, U, dv, N, init)
+
+
 # .. and on the fp32 matrix instructions: two segments, the increment of the first one shared by two workgroups (d' = 24: from 209 tokens on, 8: from 512 on, or with few units), an even
 # and an odd number of chunks in it, and one more than half of them; then from the state that this left, where it is not
 @pytest.mark.parametrize("dtype,dp,dv,U,N1,N", [("f32", 32, 64, 90, 200, 390), ("f32", 32, 128, 64, 129, 129), ("bf16", 24, 128, 100, 170, 345), ("f32", 24, 64, 256, 161, 161),
