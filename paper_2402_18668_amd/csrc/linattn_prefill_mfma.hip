@@ -287,6 +287,18 @@ __device__ __forceinline__ bf16x8 one_at(int g, int target, uint32_t one)
     return as_bf16x8(o);
 }
 
+// Keys and queries that are not finite.  A product with a 0/1 matrix makes NaN of the whole row of such an element, and so of features without it.  Whether
+// there are any shows in products at hand, and the features of their tile (of an increment: its entry) are then built from the rows' elements.  (us, without
+// and with this look: 256 units of 2048 tokens, d_v 128, 81.5, 82.3; 128 of 2048, d_v 64, 35.0, 35.0; 16 of 777 from a state 15.55, 15.72.)
+__device__ __forceinline__ bool any_not_finite(float x) { return __builtin_expect(__any(!(fabsf(x) < INFINITY)), 0); }
+__device__ __forceinline__ float bf16_at(const uint16_t *p) { return __uint_as_float((uint32_t)*p << 16); }
+// Feature row n of state tile T of a token, from its row of K: a pair's product times `pair`, k_a times `linear`, the constant `one`
+__device__ __forceinline__ float phik_element(const uint16_t *kr, int T, int n, float pair, float linear, float one)
+{
+    const float a = bf16_at(kr + (n & 15)), b = bf16_at(kr + ((T < 4 ? n + 2 * T + (n >> 4) : n - 24) & 15));
+    return T < 4 || n >= 24 ? a * pair * b : n < DP ? a * linear : n == DP ? one : 0.f;
+}
+
 // The state buffer moves through LDS (which holds nothing else at either end of a segment), as an image of the consumers'
 // tiles: image[column tile][32 T + row][IMG_LD].  A consumer reaches its registers' places at constant offsets from one
 // address, and the whole workgroup moves 16-byte pieces between the image and the buffer's rows.  (Read and
@@ -827,6 +839,17 @@ __device__ __forceinline__ void prefill_body(
                 zero16(xr);
                 xr = mfma(turned_eye, qr, xr);
                 xr *= kCQ;
+                if (any_not_finite(xr[0])) {   // (every element takes part in it)
+                    const uint16_t *row = lds.rows[b].qrow[32 * qt + n];
+#pragma unroll 1
+                    for (int i = 0; i < 8 * NSLAB; ++i) {   // element e of slab s
+                        const int s = i >> 3, e = i & 7, a = s < 8 ? (4 * g + e + (e & 4)) & 15 : 4 * g + (e & 3);
+                        const float x = bf16_at(row + a) * (s == 0 ? 0.5f * kCQ : kCQ), pr = x * (bf16_at(row + ((a + (s < 8 ? s : 8)) & 15)) * kCQ);
+                        const float v = s == 8 ? bf16_at(row + a + 2 * (e & 4)) : s == 9 && e < 4 ? (i == 72 && g == 0 ? 1.f : 0.f) : pr;
+                        reinterpret_cast<__bf16 *>(&lds.phiq[b][qt][s][lane])[e] = (__bf16)v;
+                    }
+                    return;
+                }
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {   // pair slabs: delta = s
                     float pr[8];
@@ -861,9 +884,20 @@ __device__ __forceinline__ void prefill_body(
                 zero16(ka); zero16(kb);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) kp[r] = n < DP ? kSqrt2 : 0.f;
+                // (a column of this one is two tokens; every element of theirs takes part in each of its values)
+                const f32x4 seen = __builtin_amdgcn_mfma_f32_16x16x32_bf16(first_eye, kr, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 ka = mfma(kr, first_eye, ka);
                 kb = mfma(kr, second_eye, kb);
                 kp = mfma(kr, pair_eye, kp);
+                if (any_not_finite(seen[0])) {
+#pragma unroll 1
+                    for (int i = 0; i < 16 * NTILE; ++i) {   // element e of slab ts of tile T
+                        const int e = i & 7, ts = 2 * hh + (i >> 3 & 1), T = i >> 4, tok = 16 * ts + 8 * (e >> 2) + 4 * g + (e & 3);
+                        const float v = phik_element(lds.rows[b].krow[tok], T, n, kRsqrt2, 1.f, tok < valid ? 1.f : 0.f);
+                        reinterpret_cast<__bf16 *>(&lds.phik[b][T][ts][lane])[e] = (__bf16)v;
+                    }
+                    return;
+                }
                 ka *= kRsqrt2;
                 float one[16];
 #pragma unroll
@@ -998,12 +1032,15 @@ __device__ __forceinline__ void prefill_body(
 // DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  Every row is a sum of halved products: pair rows
 // are scaled by sqrt(2), the others by 2, the moments by 4 when they are put away.
 //
+// A key with an element that is not finite makes NaN of all its features here, the count of tokens too.  The waves with the moments see that at the
+// end, and the entry is computed anew, feature by feature; the loop does not look.
+//
 // Bound: memory, with half of the chip at increments and half at main passes (128 units: 1300 cycles a chunk at d_v 64, 2300 at 128, 4.1 TB/s together;
 // 16 units 1200); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
 template <int NC>
 __device__ __forceinline__ void increment_body(
-    unsigned char *lds, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state, int has_init,
-    float *__restrict__ ws, unsigned *__restrict__ flags, unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
+    unsigned char *lds, unsigned &anew, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state,
+    int has_init, float *__restrict__ ws, unsigned *__restrict__ flags, unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
 {
     constexpr int DV = 32 * NC, HP = NC / 2;      // HP: 64-column parts
     constexpr int NH = 4 / HP;                    // 32-token tiles of a step
@@ -1045,6 +1082,7 @@ __device__ __forceinline__ void increment_body(
         for (int i = 0; i < RING - 1; ++i) issue(i);
     };
     if (HP == 1 || !imports) issue_first();
+    if (tid == 0) anew = 0u;   // (ordered before its use by the loop's barriers)
 
     // 0/1 matrices as B operands
     const bf16x8 first_eye = one_at(g, m, 0x3F00u);                              // k_a / 2
@@ -1185,7 +1223,48 @@ __device__ __forceinline__ void increment_body(
             if (publish) store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
         }
     };
+    // The entry from rows of K and V in memory, the same products in the same order: a wave takes a slot at a time, in the layout of its accumulators.
+    auto put_by_element = [&]() {
+        const float *Su = imports ? state + (size_t)u * (packed_state ? packed_state_stride(DP, DV) : state_stride(DP, DV)) : nullptr;
+        for (int i = w; i < NC * NTILE + 1; i += 8) {
+            const bool x = i == NC * NTILE;   // the moments
+            const int c = i / NTILE, T = x ? NTILE - 1 : i % NTILE, slot = x ? 6 * x_tile(NC) + 5 : 6 * c + T;
+            f32x16 acc[NH / 2];   // (of each group)
+#pragma unroll
+            for (int h = 0; h < NH / 2; ++h) zero16(acc[h]);
+            if (imports) {   // (through the slot's place in LDS: the loop need not be unrolled)
+                float *own = hand + slot * kSlotFloats;
+#pragma unroll 1
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r >> 2) + 4 * g + (r & 3);
+                    const CanonRows cr = canon_rows(T, row, packed_state);
+                    const float *at = Su + 32 * c + n;
+                    own[(r >> 2) * 256 + (r & 3)] = x ? 0.25f * initial_moment(Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV, row, n, packed_state)
+                                                  : cr.r1 < 0 ? 0.f : (T < 4 || r >= 12 ? kRsqrt2 : 0.5f) * ((at[(size_t)cr.r1 * DV] + at[(size_t)cr.r2 * DV]) * 0.5f);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[0][r] = own[(r >> 2) * 256 + (r & 3)];
+            }
+#pragma unroll
+            for (int h = 0; h < NH / 2; ++h)   // 16 tokens at a time; of two groups every second pair each
+#pragma unroll 1
+                for (int t = tok_begin + 32 * h; t < tok_end; t += NH == 4 && (t & 16) ? 48 : 16) {
+                    float ke[8], ve[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const size_t tok = t + 8 * (e >> 2) + 4 * g + (e & 3);
+                        ke[e] = x && n > DP ? 0.f : phik_element(ku + tok * DP, T, n, 0.5f, 0.5f, 0.5f);
+                        ve[e] = x ? ke[e] : bf16_at(vu + tok * DV + 32 * c + n);
+                    }
+                    acc[h] = mfma(pack8(ke), pack8(ve), acc[h]);
+                }
+            if (NH == 4) acc[0] += acc[NH / 2 - 1];
+            put(slot, acc[0], x ? 4.f : T < 4 ? kSqrt2 : 2.f, x ? 4.f : kSqrt2);
+        }
+    };
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (has_x && __any(E[8] != E[8])) anew = 1u;   // (register 8: the row of the constant)
+    unsigned again = 0u;
     if (HP == 1) {   // the groups' sums: the first one finishes column tile 0, the other one column tile 1 and E
         float *x = reinterpret_cast<float *>(lds) + 4 * lane;   // (the image's place)
         auto give = [&](int i, const f32x16 &y) {
@@ -1204,6 +1283,7 @@ __device__ __forceinline__ void increment_body(
         if (grp == 0 && has4) give(8 + e4, E);
         if (grp == 0 && has_x) give(10, E);
         wg_sync();
+        again = anew;
         if (grp == 0) {
             take(r4, S[0]);
             put(r4, S[0], kSqrt2, kSqrt2);
@@ -1221,19 +1301,22 @@ __device__ __forceinline__ void increment_body(
         }
     } else {
         wg_sync();   // (the last rows have been read)
+        again = anew;
         put(6 * c0 + r4, S[0], kSqrt2, kSqrt2);
         put(6 * (c0 + 1) + r4, S[1], kSqrt2, kSqrt2);
         if (has4) put(6 * (c0 + e4) + 4, E, 2.f, kSqrt2);
         if (has_x) put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
     }
-    if (publish) {   // the entry has reached memory (the stores are written through) before the flags are raised
+    // (the entry has reached memory, its stores are written through, before the flags are raised)
+    if (publish) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    wg_sync();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(again) != 0u, 0)) {
+        put_by_element();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid >= 2 + seg && tid < G)
-            __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    } else {
         wg_sync();
     }
+    if (publish && tid >= 2 + seg && tid < G)
+        __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Grid: segment by segment, so that a workgroup only waits for workgroups before it.  A launch of one segment is a kernel of its own, without the code of
@@ -1256,7 +1339,8 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
         prefill_body<NC, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, blockIdx.x);
     } else {
         const int seg = blockIdx.x / U, u = blockIdx.x % U;
-        if (seg > 0) increment_body<NC>(raw, k, v, state, has_init, ws, flags, epoch, N, segs, G, seg - 1, u);
+        __shared__ unsigned anew;
+        if (seg > 0) increment_body<NC>(raw, anew, k, v, state, has_init, ws, flags, epoch, N, segs, G, seg - 1, u);
         prefill_body<NC, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G, seg, u);
     }
 }

@@ -273,6 +273,52 @@ def test_prefill_increments(based, dv, N, init):
     check_close(z[:3], zw, TOL["bf16"], "z")
 
 
+# .. a key that is not finite reaches the state's rows with its element, later tokens and nothing else: what does not see it has the bits of the call with a
+# zero there.  One segment, the increments of several (their first and last tokens, both tiles of a step) and the last segment, its last chunk ends inside
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N,at", [(2, 64, 200, (70, 199)), (2, 128, 200, (0, 131)), (3, 64, 64 * 13 - 7, (0, 300, 800)), (3, 128, 64 * 20 + 1, (63, 400, 1280)),
+                                       (120, 64, 64 * 9, (100, 390, 575)), (120, 128, 64 * 9 - 1, (32, 389, 574))])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_prefill_nonfinite_keys(based, packed, U, dv, N, at, bad):
+    wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
+    q, k, v = (a[np.arange(U) % 3] for a in synth.linattn_inputs(wl, units=3, N=64 + N))
+
+    def call(value):
+        tq, tk, tv = (up(a, "bf16", (1, U, 64 + N, d)) for a, d in ((q, 16), (k, 16), (v, dv)))
+        for u, t in enumerate(at[:U]):
+            tk[0, u, 64 + t, 3 + u] = value
+        state = (based.alloc_packed_state if packed else based.alloc_state)(1, U, 16, dv)
+        y = [based.prefill(*(a[:, :, s].contiguous() for a in (tq, tk, tv)), state=state, has_init=s.start > 0, packed=packed) for s in (slice(0, 64), slice(64, 64 + N))]
+        if packed:
+            state = based.state_unpack(state, based.alloc_state(1, U, 16, dv), 1, U, 16, dv)
+        return (down(y[1])[0], *(down(a)[0] for a in based.state_export(state, 1, U, 16, dv)))
+
+    (y, S, z), (y0, S0, z0) = call(bad), call(0.0)
+    sees, has = np.zeros((U, N), dtype=bool), np.zeros((U, 273), dtype=bool)
+    for u, t in enumerate(at[:U]):
+        sees[u, t:] = True
+        pair = np.zeros((16, 16), dtype=bool)
+        pair[3 + u] = pair[:, 3 + u] = True
+        has[u, 4 + u] = True
+        has[u, 17:] = pair.reshape(-1)
+    assert not np.isfinite(y[sees]).any() and (y[~sees] == y0[~sees]).all()
+    assert not np.isfinite(S[has]).any() and (S[~has] == S0[~has]).all()
+    assert not np.isfinite(z[has]).any() and (z[~has] == z0[~has]).all()
+
+
+# .. a query that is not finite its own output: with keys, values and queries above zero an infinite one's numerators are infinite in every column
+@pytest.mark.parametrize("U,dv,N", [(2, 64, 200), (3, 128, 64 * 12 + 9)])
+def test_prefill_nonfinite_queries(based, U, dv, N):
+    q, k, v = (synth.round_to(np.abs(synth.normal(60 + i, (1, U, N, d), 0.5)) + 0.1, "bf16") for i, d in enumerate((16, 16, dv)))
+    want = down(based.prefill(*(up(a, "bf16") for a in (q, k, v)), numerator_only=True))
+    at = np.array([64, 100, N - 1])[:U]
+    q[0, np.arange(U), at, 2 + np.arange(U)] = np.inf
+    got = down(based.prefill(*(up(a, "bf16") for a in (q, k, v)), numerator_only=True))
+    own = np.zeros((U, N), dtype=bool)
+    own[np.arange(U), at] = True
+    assert np.isposinf(got[0, own]).all() and (got[0, ~own] == want[0, ~own]).all()
+
+
 # bf16 d' = 32 prefill: one token, around a chunk and the smallest number of chunks that is cut into segments, few and many segments,
 # the initial state read by one workgroup (one segment, d_v 64) and by several, both state layouts
 @pytest.mark.parametrize("packed", [False, True])
