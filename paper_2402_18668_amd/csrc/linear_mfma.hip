@@ -329,10 +329,8 @@ __device__ __forceinline__ void tile_body(unsigned char *lds, const uint16_t *__
 
 // Blocks 0 .. : the first `whole` tiles of T; the blocks after them: the remaining tiles in halves of BM / 2 tokens (T2).
 // Block -> tile: XCD b % 8 works through a contiguous eighth of the tiles, so that the tiles it has in hand share rows of x and W in
-// its L2 (and a problem of one band of rows still uses all XCDs).  Where x is the larger operand, features fastest: an XCD reads an
-// eighth of x and all of W.  With 4 M < 3 N (launch_tile), rows fastest: `fast` tiles, an eighth of W and all of x.  (us, q / k / v projection 1792 -> 2560 features and output
-// projection 2048 -> 1792 in turn, features fastest and rows fastest: 100 tokens 14.2, 11.6, 256 17.0, 14.5, 512 22.6, 20.3, 777 31.7, 25.7,
-// 1024 32.3, 28.8, 1500 38.7, 36.5; 2048, the first one alone over the line, 44.0, 44.2, 2400 50.8, 51.2.)
+// its L2 (and a problem of one band of rows still uses all XCDs).  Features fastest, an XCD reads an eighth of x and all of W; rows fastest (rows_first;
+// `fast` tiles), an eighth of W and all of x.
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
 __global__ __launch_bounds__(T::NT, T::LDS > 80 * 1024 ? T::NT / 256 : T::NW / 2) void linear_tile_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ W, uint16_t *__restrict__ y, int M, int K, int N,
@@ -464,6 +462,11 @@ enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64D, TILE64, TILE128N, TILE12
 
 inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
 
+// Rows fastest over the XCDs: where W is enough larger than x, and the operands, not the output, are what a tile moves.  (us of a launch, features and rows
+// fastest: 1792 -> 2560 features 300 tokens 10.5, 6.8, 512 11.6, 9.3, 1000 19.3, 16.5, 1500 19.4, 18.8, 1919 24.45, 24.4, 1280 -> 2560 1919 19.6, 20.1; 2048 -> 1792 700
+// 12.6, 10.5, 1000 13.2, 12.8, 1344 18.8, 18.2; 1280 -> 512 2048 6.0, 9.3; 512 -> 4096 2048 12.6, 11.9, 192 -> 4096 8.1, 8.5.)
+inline bool rows_first(long M, int K, long N) { return 10 * M < 7 * N && K >= 5 * BK; }
+
 // A handful of tokens: 16 or 32 per workgroup (above 32 tiles, which read W fewer times, are as fast or faster).
 // Otherwise the tiling with the smallest expected time.  The figures are microseconds per 64-deep step, measured at
 // K 768 .. 2048, 40 .. 5120 tiles: a launch of up to 256 tiles (one per CU) is bound by the latency of a step, after
@@ -474,13 +477,15 @@ inline Variant pick_variant(int M, int K, int N)
     if (M <= 16) return ROWS1;
     if (M <= 18 || K >= (1 << 22)) return ROWS2;   // (tiles address their rows with 32-bit offsets)
     // Few tiles are bound by what a CU takes in of x and W and by the latency of a step: the smallest tiles that leave each CU at most one, the steps
-    // shared out over four groups of waves.  (us, 64 x 64 tiles and these, q / k / v projection 1792 -> 2560 features, which does not get below the 5.0
-    // that its call takes the host, and output projection 2048 -> 1792, each by itself: 40 and 64 tokens 7.0, 5.0 and 9.3, 5.8 with 32 x 32, 128 7.0, 5.7 with 64 x 32 and
-    // 9.2, 5.8, 200 9.3, 7.5 with 64 x 32; 17 tokens 5.4, 5.0 and 5.4, 5.8 there and with ROWS2, 24 5.9, 5.0 and 6.1, 5.8, 32 6.5, 4.9 and 6.7, 5.8.  512 features
-    // from 512: 100 tokens 4.3, 4.1, 400 4.4, 4.2.  More tiles than CUs take two rounds: 200 tokens to 2560 features 8.3, 17 with 32 x 32, 13 with 64 x 32.)
-    if (tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
+    // shared out over groups of waves, where there are enough of them to pay for the groups' start and sum.  (us of a launch:
+    // 32 x 32 in four groups, before (ROWS2; 64 x 64) and so: 24 tokens, 64 -> 1024 features 3.1, 3.4, 128 -> 1024 3.9, 3.35, 1792 -> 2560 6.0, 4.7; 64 tokens to 2560
+    // features, K 64 2.8, 3.5, 448 3.73, 3.74, 512 3.86, 3.71, 640 4.1, 3.9, 1792 6.9, 4.8; 300 tokens to 512, K 448 3.67, 3.68, 640 4.1, 3.9, 1792 6.9, 4.8.
+    // 64 x 32 in four and 64 x 64 in one and two groups: 128 tokens to 2560 features, K 1152 5.35, 5.3, 5.3, 1280 5.4, 5.65, 5.6, 1792 6.0, 6.8, 6.5; 200 to 1792, K
+    // 1152 5.6, 5.4, 5.4, 1280 5.5, 5.75, 5.6, 2048 6.6, 7.5, 6.95; nearly a tile to each CU, 128 to 4096, K 1280 5.9, 5.7, 5.7, 1792 6.7, 6.8, 6.5.  More tiles than CUs
+    // take two rounds: 200 tokens, 1792 -> 2560, 8.3 with 64 x 64, 17 with 32 x 32, 13 with 64 x 32.)
+    if (K >= (M <= 32 ? 2 : 9) * BK && tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
     if (M <= 32) return ROWS2;
-    if (tiles_of(M, N, T64S::BM, T64S::BN) <= 256 && K >= 12 * BK) return TILE64S;
+    if (K >= 20 * BK && tiles_of(M, N, T64S::BM, T64S::BN) <= 224) return TILE64S;
     auto per_cu = [](long tiles) { return (float)((tiles + 255) / 256); };
     Variant best = TILE64;
     float t = 0.05f + 0.21f * per_cu(tiles_of(M, N, T64::BM, T64::BN));
@@ -494,9 +499,9 @@ inline Variant pick_variant(int M, int K, int N)
         const long n256 = tiles_of(M, N, T256::BM, T256::BN), rem = n256 % 256;
         offer(TILE256, 1.5f * (float)(n256 / 256) + (rem == 0 ? 0.f : rem <= 128 ? 1.f : 1.5f));   // (see launch_tile)
     }
-    // 64 x 64 tiles, one to a CU: two groups of waves.  (us, with one and two: 256 tokens, 1792 -> 2560 features 7.3, 7.0, 300, 400 and 512 tokens, 2048 -> 1792 9.3, 8.3,
-    // 9.4, 8.3 and 9.5, 8.5, 1000 tokens, 1024 -> 896 6.2, 6.0, but 512 -> 896 3 % slower.  128 x 64 the same way: 512 tokens, 1792 -> 2560, 9.4, 9.1, 1024, 2048 -> 1792, 12.5, 12.8.)
-    return best == TILE64 && tiles_of(M, N, T64::BM, T64::BN) <= 256 && K >= 16 * BK ? TILE64D : best;
+    // 64 x 64 tiles, one to a CU: two groups of waves.  (us, with one and two: 256 tokens to 2560 features, K 1024 5.2, 5.3, 1152 5.5, 5.5, 1792 7.1, 6.7; 400 to 1792, K 2048 7.75, 7.3;
+    // features fastest, 1344 tokens, 1280 -> 512 5.8, 5.75, 1500 5.9, 5.9, 2048, 256 tiles, 6.0, 6.5, 1000 tokens, 1280 -> 1024 6.05, 6.5.)
+    return best == TILE64 && K >= 18 * BK && tiles_of(M, N, T64::BM, T64::BN) <= (rows_first(M, K, N) ? 256 : 192) ? TILE64D : best;
 }
 
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
@@ -505,7 +510,7 @@ void launch_tile(const uint16_t *x, const uint16_t *W, uint16_t *y, int M, int K
     const long tiles = tiles_of(M, N, T::BM, T::BN);
     // a last round of the chip that would be at most half full is dealt out in half tiles
     const long rem = tiles % 256, halves = !std::is_same_v<T, T2> && rem <= 128 ? 2 * rem : 0, whole = tiles - halves / 2;
-    const bool rows_fast = 4ll * M < 3ll * N;
+    const bool rows_fast = rows_first(M, K, N);
     const long grid = (whole + kXcds - 1) / kXcds * kXcds + (halves + kXcds - 1) / kXcds * kXcds;
     hipLaunchKernelGGL((linear_tile_kernel<T, T2, SPLIT_OUT, HEADS_IN>), dim3((unsigned)grid), dim3(T::NT), 0, s, x, W, y, M, K,
                        N, rows_fast ? (M + T::BM - 1) / T::BM : N / T::BN, (int)rows_fast, (int)whole, (int)halves, hl);

@@ -47,6 +47,49 @@ def test_linear_shared_steps(based, M, K, N):
             check_close(rows(down(based.project_out(up(yh, "bf16"), up(W, "bf16")))), rows(oracle.project_out(yh, W)), TOL["bf16"], f"project out {dv}")
 
 
+def tile_of(call):
+    """The tiling a projection runs with, by its kernel's name: tokens and features of a tile, groups of waves that share its steps (0, 0, 0: without tiles)."""
+    import re
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+        call()
+        torch.cuda.synchronize()
+    names = [e.key for e in profile.key_averages() if "based::lin::" in e.key]
+    assert len(names) == 1, names
+    found = re.search(r"linear_tile_kernel<based::lin::Tile<(\d+), (\d+), \d+, \d+, \d+, \d+, (\d+)>", names[0])
+    return tuple(int(x) for x in found.groups()) if found else (0, 0, 0)
+
+
+# the lines between the tilings of few tokens, on either side; the groups' shares with every remainder of the steps, bands that end inside a tile, features
+# and rows fastest
+@pytest.mark.parametrize("M,K,N,tile", [(18, 128, 128, (0, 0, 0)), (19, 64, 128, (0, 0, 0)), (19, 128, 128, (32, 32, 4)), (32, 128, 8192, (32, 32, 4)), (32, 128, 8320, (0, 0, 0)),
+                                        (33, 512, 128, (64, 64, 1)), (33, 576, 128, (32, 32, 4)), (513, 640, 512, (64, 64, 1)),
+                                        (97, 1216, 2560, (64, 64, 2)), (97, 1280, 2560, (64, 32, 4)), (129, 1408, 1792, (64, 32, 4)), (190, 1472, 1792, (64, 32, 4)),
+                                        (200, 1344, 1792, (64, 32, 4)), (257, 1280, 1792, (64, 64, 2)), (97, 1088, 2560, (64, 64, 1)), (256, 1152, 4096, (64, 64, 2)),
+                                        (1500, 1152, 512, (64, 64, 2)), (1540, 1152, 512, (64, 64, 1)), (321, 1280, 3584, (128, 64, 1))])
+def test_linear_tile_choice(based, M, K, N, tile):
+    x, W = synth.linear_inputs(71, M, K, N)
+    dx, dW = up(x, "bf16"), up(W, "bf16")
+    assert tile_of(lambda: based.linear(dx, dW)) == tile
+    check_close(down(based.linear(dx, dW)), oracle.linear(x, W), TOL["bf16"], f"linear {M}x{K}x{N}")
+
+
+# .. with the outputs split into heads, and the inputs (a step is half of a head's columns): sequences that end inside a tile
+@pytest.mark.parametrize("B,N,tile_in,tile_out", [(5, 7, (32, 32, 4), (32, 32, 4)), (3, 41, (64, 32, 4), (32, 32, 4)), (3, 43, (64, 64, 2), (64, 32, 4)), (4, 65, (64, 64, 2), (64, 64, 2))])
+def test_projection_tile_choice(based, B, N, tile_in, tile_out):
+    dm, H, dp, dv = 1792, 16, 16, 128
+    x, W = synth.linear_inputs(72, B * N, dm, H * (2 * dp + dv))
+    dx, dW = up(x, "bf16", (B, N, dm)), up(W, "bf16")
+    assert tile_of(lambda: based.project_qkv(dx, dW, H, dp, dv)) == tile_in
+    f = H * dp
+    for got, Wp in zip(based.project_qkv(dx, dW, H, dp, dv), (W[:f], W[f:2 * f], W[2 * f:])):
+        check_close(rows(down(got)), rows(oracle.project_heads(x.reshape(B, N, dm), Wp, H)), TOL["bf16"], "q k v")
+    y, Wo = synth.linear_inputs(73, B * H * N, dv, 8)[0].reshape(B, H, N, dv), synth.linear_inputs(74, 8, H * dv, dm)[1]
+    dy, dWo = up(y, "bf16"), up(Wo, "bf16")
+    assert tile_of(lambda: based.project_out(dy, dWo)) == tile_out
+    check_close(rows(down(based.project_out(dy, dWo))), rows(oracle.project_out(y, Wo)), TOL["bf16"], "project out")
+
+
 # a decode batch: 4 to 16 features to a workgroup, the last one with fewer; K shorter than the eight waves share
 @pytest.mark.parametrize("M,K,N", [(1, 64, 1024), (9, 128, 1408), (16, 256, 2304), (5, 1792, 2560), (17, 64, 3328), (31, 320, 4224)])
 def test_linear_rows_features(based, M, K, N):
