@@ -1354,14 +1354,17 @@ namespace {
 // segment 15.2, 3 12.3, 4 11.9, 5 12.7; 13 chunks 1 21.8, 4 14.3, 5 13.7, 6 14.3; 32 chunks 5 21.5, 6 20.4, 8 19.1, 10 20.9; 64 chunks 6 29.6, 8 26.4, 10 25.4; d_v 128,
 // 13 chunks 4 18.9, 5 17.5, 6 18.5; 32 chunks 6 26.4, 8 24.7, 10 26.9).  Below that a second segment does not pay for its increment (1 segment and 2, 16 and 128
 // units: d_v 64, 4 chunks 9.9, 10.4 and 11.4, 12.0; 5 chunks 11.1, 10.5 and 12.7, 12.2; d_v 128, 5 chunks 13.9, 14.2 and 16.2, 16.6; 6 chunks 15.6, 15.2 and 17.8, 17.8,
-// from a state 17.8, 17.8 and 20.9, 21.4; three of 6 chunks, 16 units: 10.9 and 13.9).
+// three of 6 chunks, 16 units: 10.9 and 13.9).  Four segments pay from 8 chunks on, at d_v 128 from 9 (us,
+// three and four: d_v 64, 7 chunks, 16 units 11.1, 11.9, 51 12.2, 14.3, 64 12.1, 12.8, 8 chunks, 16 units 12.4, 11.8, 64 13.2, 12.9; d_v 128, 7 chunks 15.1, 15.3, 17.3,
+// 20.6, 16.8, 17.3, 8 chunks 15.4, 15.4, 17.4, 20.6, 17.0, 17.1, 9 chunks, 16 units 16.7, 16.3, 64 18.5, 18.3).
 int pick_segments(int U, int N, int dv)
 {
     const int chunks = (N + C - 1) / C;
     const bool wide = dv == 128;
     if (chunks < (wide ? U > 85 ? 7 : 6 : 5)) return 1;
     int G = 256 / U;
-    const int chain = chunks == 5 ? 2 : (int)(sqrtf(2.f * (float)chunks) + 0.5f);
+    int chain = chunks == 5 ? 2 : (int)(sqrtf(2.f * (float)chunks) + 0.5f);
+    if (chunks < (wide ? 9 : 8) && chain > 3) chain = 3;
     if (G > chain) G = chain;
     if (G > kMaxSegments) G = kMaxSegments;
     return G < 1 ? 1 : G;

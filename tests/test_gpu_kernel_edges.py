@@ -857,6 +857,38 @@ def test_prefill_segment_rule(based, U, dv, N):
     check_close(down(z)[0, at], zw, TOL["bf16"], "z")
 
 
+def segments_of(call, U, tmp_path):
+    """Segments per sequence of a bf16 d' = 16 prefill, by its kernel's grid."""
+    import json
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+        call()
+        torch.cuda.synchronize()
+    trace = tmp_path / "trace.json"
+    profile.export_chrome_trace(str(trace))
+    grids = [e["args"]["grid"][0] for e in json.loads(trace.read_text())["traceEvents"] if "prefill_mfma_kernel" in e.get("name", "")]
+    assert len(grids) == 1 and grids[0] % U == 0
+    return grids[0] // U
+
+
+# .. which number it is, on either side of the lines
+@pytest.mark.parametrize("U,dv,N,G", [(16, 64, 256, 1), (16, 64, 257, 2), (16, 64, 321, 3), (51, 64, 448, 3), (51, 64, 449, 4), (16, 64, 801, 5), (16, 128, 320, 1), (51, 128, 321, 3),
+                                      (51, 128, 512, 3), (51, 128, 513, 4), (86, 128, 384, 1), (86, 128, 385, 2), (129, 64, 2048, 1), (1, 64, 64 * 128, 16)])
+def test_prefill_segment_counts(based, U, dv, N, G, tmp_path):
+    q, k, v = (up(synth.round_to(synth.normal(40 + i, (1, U, N, d), 0.5), "bf16"), "bf16") for i, d in enumerate((16, 16, dv)))
+    state = based.alloc_state(1, U, 16, dv)
+    y = [None]
+
+    def call():
+        y[0] = based.prefill(q, k, v, state=state)
+
+    assert segments_of(call, U, tmp_path) == G
+    at = np.unique([0, U - 1])
+    a = [down(x)[0, at] for x in (q, k, v)]
+    check_close(rows(down(y[0])[0, at]), rows(oracle.linattn_quadratic(*a)), TOL["bf16"], "y")
+    check_close(down(based.state_export(state, 1, U, 16, dv)[0])[0, at], oracle.linattn_state(*a[1:])[0], TOL["bf16"], "S")
+
+
 # outputs are allocated past the dispatcher, except under a mode that looks at every operator
 def test_outputs_under_a_dispatch_mode(based):
     import torch
