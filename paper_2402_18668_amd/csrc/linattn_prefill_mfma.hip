@@ -1357,11 +1357,19 @@ namespace {
 // three of 6 chunks, 16 units: 10.9 and 13.9).  Four segments pay from 8 chunks on, at d_v 128 from 9 (us,
 // three and four: d_v 64, 7 chunks, 16 units 11.1, 11.9, 51 12.2, 14.3, 64 12.1, 12.8, 8 chunks, 16 units 12.4, 11.8, 64 13.2, 12.9; d_v 128, 7 chunks 15.1, 15.3, 17.3,
 // 20.6, 16.8, 17.3, 8 chunks 15.4, 15.4, 17.4, 20.6, 17.0, 17.1, 9 chunks, 16 units 16.7, 16.3, 64 18.5, 18.3).
-int pick_segments(int U, int N, int dv)
+// From a state (launch; the workspace has room for the number without one) the state is read twice and written by a third workgroup.  With a number of units that
+// 8 divides these are on one XCD; otherwise the state travels between them, the longer the more units there are, and segments pay later.  (us from a state, one segment
+// and several.  d_v 64: 42 units 6 chunks 14.5, 14.6, 7 15.9, 14.7; 60 units 6 14.8, 15.2, 7 16.1, 15.2; 85 units 6 15.1, 16.3, 8 17.8, 17.5, 9 19.1, 19.1; 102 units 9 19.4,
+// 20.2, 10 20.8, 20.3; but 64 units 5 13.3, 13.0, 128 5 14.3, 14.2.  d_v 128: 12 units 6 17.8, 17.4; 28 units 7 19.8, 19.9, 8 21.3, 20.0; 51 units 8 21.7, 22.3, 9 23.4, 22.7; 85
+// units 10 26.1, 26.4, 12 28.9, 27.9; 102 units 12 29.6, 29.6; but 64 units 6 19.0, 18.5, 96 6 19.8, 20.2, 8 22.6, 22.0, 128 7 22.4, 22.6, 8 23.1, 22.5.)
+int pick_segments(int U, int N, int dv, bool from_state = false)
 {
     const int chunks = (N + C - 1) / C;
     const bool wide = dv == 128;
-    if (chunks < (wide ? U > 85 ? 7 : 6 : 5)) return 1;
+    int least = !wide ? 5 : U > 85 ? 7 : 6;
+    if (from_state && U % 8 != 0) least = wide ? 6 + U / 16 : U > 85 ? 10 : 5 + U / 24;
+    else if (from_state && wide && U > 85) least = 8;
+    if (chunks < least) return 1;
     int G = 256 / U;
     int chain = chunks == 5 ? 2 : (int)(sqrtf(2.f * (float)chunks) + 0.5f);
     if (chunks < (wide ? 9 : 8) && chain > 3) chain = 3;
@@ -1428,7 +1436,7 @@ hipError_t launch(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint1
     SegTable segs;
     // a smaller G only uses a prefix of the workspace that was sized for pick_segments()
     const int Gmax = pick_segments(U, N, dv);
-    const int G = make_segments(N, Gmax, dv, segs);
+    const int G = make_segments(N, pick_segments(U, N, dv, (flags_word & 1) != 0), dv, segs);
     // what the kernels index must lie inside what the workspace was sized for
     if (G < 1 || G > Gmax || segs.begin[G] < N) return hipErrorInvalidValue;
     if ((long long)U * G >= (1ll << 31)) return hipErrorInvalidValue;

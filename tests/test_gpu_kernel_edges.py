@@ -889,6 +889,30 @@ def test_prefill_segment_counts(based, U, dv, N, G, tmp_path):
     check_close(down(based.state_export(state, 1, U, 16, dv)[0])[0, at], oracle.linattn_state(*a[1:])[0], TOL["bf16"], "S")
 
 
+# .. from a state: later where a unit's segments are on several XCDs
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("U,dv,N,G", [(16, 64, 257, 2), (51, 64, 384, 1), (51, 64, 385, 3), (85, 64, 448, 1), (85, 64, 449, 3), (102, 64, 576, 1), (102, 64, 577, 2), (128, 64, 257, 2),
+                                      (51, 128, 512, 1), (51, 128, 513, 4), (64, 128, 321, 3), (88, 128, 448, 1), (88, 128, 449, 2), (102, 128, 704, 1), (102, 128, 705, 2),
+                                      (3, 128, 321, 3)])
+def test_prefill_segment_counts_from_a_state(based, packed, U, dv, N, G, tmp_path):
+    q, k, v = (synth.round_to(synth.normal(43 + i, (U, 64 + N, d), 0.5), "bf16") for i, d in enumerate((16, 16, dv)))
+    state = (based.alloc_packed_state if packed else based.alloc_state)(1, U, 16, dv)
+    args = [[up(a[:, lo:hi], "bf16", (1, U, hi - lo, a.shape[2])) for a in (q, k, v)] for lo, hi in ((0, 64), (64, 64 + N))]
+    workspace = based.alloc_prefill_workspace(1, U, N, 16, dv, based.BF16)
+    based.prefill(*args[0], state=state, packed=packed)
+    y = [None]
+
+    def call():
+        y[0] = based.prefill(*args[1], state=state, has_init=True, workspace=workspace, packed=packed)
+
+    assert segments_of(call, U, tmp_path) == G
+    at = np.unique([0, 1, U - 1])
+    check_close(rows(down(y[0])[0, at]), rows(oracle.linattn_quadratic(q[at], k[at], v[at])[:, 64:]), TOL["bf16"], "y")
+    if packed:
+        state = based.state_unpack(state, based.alloc_state(1, U, 16, dv), 1, U, 16, dv)
+    check_close(down(based.state_export(state, 1, U, 16, dv)[0])[0, at], oracle.linattn_state(k[at], v[at])[0], TOL["bf16"], "S")
+
+
 # outputs are allocated past the dispatcher, except under a mode that looks at every operator
 def test_outputs_under_a_dispatch_mode(based):
     import torch
