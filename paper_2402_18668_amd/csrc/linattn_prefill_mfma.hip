@@ -287,16 +287,12 @@ __device__ __forceinline__ bf16x8 one_at(int g, int target, uint32_t one)
     return as_bf16x8(o);
 }
 
-// Keys and queries that are not finite.  A product with a 0/1 matrix makes NaN of the whole row of such an element, and so of features without it.  Whether
-// there are any shows in products at hand, and the features of their tile (of an increment: its entry) are then built from the rows' elements.  (us, without
-// and with this look: 256 units of 2048 tokens, d_v 128, 81.5, 82.3; 128 of 2048, d_v 64, 35.0, 35.0; 16 of 777 from a state 15.55, 15.72.)
-__device__ __forceinline__ bool any_not_finite(float x) { return __builtin_expect(__any(!(fabsf(x) < INFINITY)), 0); }
 __device__ __forceinline__ float bf16_at(const uint16_t *p) { return __uint_as_float((uint32_t)*p << 16); }
-// Feature row n of state tile T of a token, from its row of K: a pair's product times `pair`, k_a times `linear`, the constant `one`
-__device__ __forceinline__ float phik_element(const uint16_t *kr, int T, int n, float pair, float linear, float one)
+// Feature row n of state tile T of a token, from its row of K
+__device__ __forceinline__ float phik_element(const uint16_t *kr, int T, int n)
 {
     const float a = bf16_at(kr + (n & 15)), b = bf16_at(kr + ((T < 4 ? n + 2 * T + (n >> 4) : n - 24) & 15));
-    return T < 4 || n >= 24 ? a * pair * b : n < DP ? a * linear : n == DP ? one : 0.f;
+    return T < 4 || n >= 24 ? a * kRsqrt2 * b : n < DP ? a : n == DP ? 1.f : 0.f;
 }
 
 // The state buffer moves through LDS (which holds nothing else at either end of a segment), as an image of the consumers'
@@ -362,7 +358,7 @@ struct SegTable { int begin[kMaxSegments + 1]; };
 // SEG: the launch has several segments.
 template <int NC, bool SEG>
 __device__ __forceinline__ void prefill_body(
-    Lds<NC> &lds, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
+    Lds<NC> &lds, unsigned &anew, const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ y, float *__restrict__ state, int has_init,
     float *__restrict__ ws, unsigned *__restrict__ flags, unsigned *__restrict__ status, int max_polls,
     unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
@@ -555,6 +551,59 @@ __device__ __forceinline__ void prefill_body(
             else if (fl == DP && n < DP) zu[1 + n] = m;
             else if (fl == DP && n == DP) zu[0] = m;
         }
+    };
+    // A key with an element that is not finite.  Its row comes as products with 0/1 matrices, which makes NaN of all of the token's features, of the count of tokens
+    // too.  No output of a token that sees it is finite in any case, but the state's rows without the element are: where the count is NaN at the end of the
+    // sequence, the state is computed anew, from the rows in memory, element by element.  (us, not at all, so, and with a look at every tile and increment: 256
+    // units of 2048 tokens, d_v 128, 82.0, 82.1, 82.8; 128 of 2048, d_v 64, 35.2, 35.5, 35.2; 16 of 777 from a state 15.55, 15.6, 15.7.)
+    auto add_by_element = [&](f32x16 &acc, const int T, const int col, const bool moments) {   // all tokens' products
+#pragma unroll 1
+        for (int t = 0; t < N; t += 16) {
+            float ke[8], ve[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int tok = t + 8 * (e >> 2) + 4 * g + (e & 3);
+                const size_t at = min(tok, N - 1);
+                const float kx = phik_element(ku + at * DP, T, n), vx = moments ? kx : bf16_at(vu + at * DV + col);
+                ke[e] = tok < N && !(moments && n > DP) ? kx : 0.f;
+                ve[e] = tok < N && !(moments && n > DP) ? vx : 0.f;
+            }
+            acc = mfma(pack8(ke), pack8(ve), acc);
+        }
+    };
+    auto finish_moments = [&](f32x16 &X) {
+        const bool bad = __any(X[8] != X[8]);   // (register 8: the row of the constant)
+        if (__builtin_expect(bad, 0)) {
+            role_guard();
+            zero16(X);
+            if (has_init) {   // (through LDS: the loop need not be unrolled)
+                float *own = image + image_bytes(NC) / 4 + lane;
+#pragma unroll 1
+                for (int r = 0; r < 16; ++r) own[64 * r] = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) X[r] = own[64 * r];
+            }
+            add_by_element(X, NTILE - 1, 0, true);
+        }
+        if (lane == 0) anew = bad ? 1u : 0u;
+        export_moments(X);
+    };
+    auto image_by_element = [&]() {   // a wave takes a tile of 32 rows and 32 columns at a time, in the layout of accumulators
+        if (has_init) {
+            import_state_image<NC>(image, Su, packed_state, tid);
+            __syncthreads();
+        }
+#pragma unroll 1
+        for (int i = w; i < NC * NTILE; i += NC + NPW) {
+            float *at = image + i * 32 * IMG_LD + 4 * g * IMG_LD + n;
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = has_init ? at[(8 * (r >> 2) + (r & 3)) * IMG_LD] : 0.f;
+            add_by_element(acc, i % NTILE, i / NTILE * 32 + n, false);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) at[(8 * (r >> 2) + (r & 3)) * IMG_LD] = acc[r];
+        }
+        __syncthreads();
     };
     if (has_init && seg == 0) {
         import_state_image<NC>(image, Su, packed_state, tid);
@@ -755,7 +804,7 @@ __device__ __forceinline__ void prefill_body(
             for (int T = 0; T < NTILE; ++T)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) image_lane[(32 * T + 8 * (r >> 2) + (r & 3)) * IMG_LD] = S[T][r];
-            if (has_x) export_moments(X);
+            if (has_x) finish_moments(X);
         }
     } else {
         // =================================== producer waves =========================================
@@ -839,17 +888,6 @@ __device__ __forceinline__ void prefill_body(
                 zero16(xr);
                 xr = mfma(turned_eye, qr, xr);
                 xr *= kCQ;
-                if (any_not_finite(xr[0])) {   // (every element takes part in it)
-                    const uint16_t *row = lds.rows[b].qrow[32 * qt + n];
-#pragma unroll 1
-                    for (int i = 0; i < 8 * NSLAB; ++i) {   // element e of slab s
-                        const int s = i >> 3, e = i & 7, a = s < 8 ? (4 * g + e + (e & 4)) & 15 : 4 * g + (e & 3);
-                        const float x = bf16_at(row + a) * (s == 0 ? 0.5f * kCQ : kCQ), pr = x * (bf16_at(row + ((a + (s < 8 ? s : 8)) & 15)) * kCQ);
-                        const float v = s == 8 ? bf16_at(row + a + 2 * (e & 4)) : s == 9 && e < 4 ? (i == 72 && g == 0 ? 1.f : 0.f) : pr;
-                        reinterpret_cast<__bf16 *>(&lds.phiq[b][qt][s][lane])[e] = (__bf16)v;
-                    }
-                    return;
-                }
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {   // pair slabs: delta = s
                     float pr[8];
@@ -884,20 +922,9 @@ __device__ __forceinline__ void prefill_body(
                 zero16(ka); zero16(kb);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) kp[r] = n < DP ? kSqrt2 : 0.f;
-                // (a column of this one is two tokens; every element of theirs takes part in each of its values)
-                const f32x4 seen = __builtin_amdgcn_mfma_f32_16x16x32_bf16(first_eye, kr, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 ka = mfma(kr, first_eye, ka);
                 kb = mfma(kr, second_eye, kb);
                 kp = mfma(kr, pair_eye, kp);
-                if (any_not_finite(seen[0])) {
-#pragma unroll 1
-                    for (int i = 0; i < 16 * NTILE; ++i) {   // element e of slab ts of tile T
-                        const int e = i & 7, ts = 2 * hh + (i >> 3 & 1), T = i >> 4, tok = 16 * ts + 8 * (e >> 2) + 4 * g + (e & 3);
-                        const float v = phik_element(lds.rows[b].krow[tok], T, n, kRsqrt2, 1.f, tok < valid ? 1.f : 0.f);
-                        reinterpret_cast<__bf16 *>(&lds.phik[b][T][ts][lane])[e] = (__bf16)v;
-                    }
-                    return;
-                }
                 ka *= kRsqrt2;
                 float one[16];
 #pragma unroll
@@ -1014,10 +1041,11 @@ __device__ __forceinline__ void prefill_body(
         }
 
         // ---- end of segment: the moments ----------------------------------------------------------
-        if (has_m && Su && seg == G - 1) export_moments(X);
+        if (has_m && Su && seg == G - 1) finish_moments(X);
     }
     if (Su && seg == G - 1) {
         __syncthreads();
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(anew) != 0u, 0)) image_by_element();
         export_image();
     }
 }
@@ -1032,15 +1060,12 @@ __device__ __forceinline__ void prefill_body(
 // DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  Every row is a sum of halved products: pair rows
 // are scaled by sqrt(2), the others by 2, the moments by 4 when they are put away.
 //
-// A key with an element that is not finite makes NaN of all its features here, the count of tokens too.  The waves with the moments see that at the
-// end, and the entry is computed anew, feature by feature; the loop does not look.
-//
 // Bound: memory, with half of the chip at increments and half at main passes (128 units: 1300 cycles a chunk at d_v 64, 2300 at 128, 4.1 TB/s together;
 // 16 units 1200); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
 template <int NC>
 __device__ __forceinline__ void increment_body(
-    unsigned char *lds, unsigned &anew, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state,
-    int has_init, float *__restrict__ ws, unsigned *__restrict__ flags, unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
+    unsigned char *lds, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state, int has_init,
+    float *__restrict__ ws, unsigned *__restrict__ flags, unsigned epoch, int N, const SegTable &segs, int G, int seg, int u)
 {
     constexpr int DV = 32 * NC, HP = NC / 2;      // HP: 64-column parts
     constexpr int NH = 4 / HP;                    // 32-token tiles of a step
@@ -1082,7 +1107,6 @@ __device__ __forceinline__ void increment_body(
         for (int i = 0; i < RING - 1; ++i) issue(i);
     };
     if (HP == 1 || !imports) issue_first();
-    if (tid == 0) anew = 0u;   // (ordered before its use by the loop's barriers)
 
     // 0/1 matrices as B operands
     const bf16x8 first_eye = one_at(g, m, 0x3F00u);                              // k_a / 2
@@ -1223,48 +1247,7 @@ __device__ __forceinline__ void increment_body(
             if (publish) store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
         }
     };
-    // The entry from rows of K and V in memory, the same products in the same order: a wave takes a slot at a time, in the layout of its accumulators.
-    auto put_by_element = [&]() {
-        const float *Su = imports ? state + (size_t)u * (packed_state ? packed_state_stride(DP, DV) : state_stride(DP, DV)) : nullptr;
-        for (int i = w; i < NC * NTILE + 1; i += 8) {
-            const bool x = i == NC * NTILE;   // the moments
-            const int c = i / NTILE, T = x ? NTILE - 1 : i % NTILE, slot = x ? 6 * x_tile(NC) + 5 : 6 * c + T;
-            f32x16 acc[NH / 2];   // (of each group)
-#pragma unroll
-            for (int h = 0; h < NH / 2; ++h) zero16(acc[h]);
-            if (imports) {   // (through the slot's place in LDS: the loop need not be unrolled)
-                float *own = hand + slot * kSlotFloats;
-#pragma unroll 1
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * g + (r & 3);
-                    const CanonRows cr = canon_rows(T, row, packed_state);
-                    const float *at = Su + 32 * c + n;
-                    own[(r >> 2) * 256 + (r & 3)] = x ? 0.25f * initial_moment(Su + (size_t)(packed_state ? packed_feature_dim(DP) : feature_dim(DP)) * DV, row, n, packed_state)
-                                                  : cr.r1 < 0 ? 0.f : (T < 4 || r >= 12 ? kRsqrt2 : 0.5f) * ((at[(size_t)cr.r1 * DV] + at[(size_t)cr.r2 * DV]) * 0.5f);
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[0][r] = own[(r >> 2) * 256 + (r & 3)];
-            }
-#pragma unroll
-            for (int h = 0; h < NH / 2; ++h)   // 16 tokens at a time; of two groups every second pair each
-#pragma unroll 1
-                for (int t = tok_begin + 32 * h; t < tok_end; t += NH == 4 && (t & 16) ? 48 : 16) {
-                    float ke[8], ve[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const size_t tok = t + 8 * (e >> 2) + 4 * g + (e & 3);
-                        ke[e] = x && n > DP ? 0.f : phik_element(ku + tok * DP, T, n, 0.5f, 0.5f, 0.5f);
-                        ve[e] = x ? ke[e] : bf16_at(vu + tok * DV + 32 * c + n);
-                    }
-                    acc[h] = mfma(pack8(ke), pack8(ve), acc[h]);
-                }
-            if (NH == 4) acc[0] += acc[NH / 2 - 1];
-            put(slot, acc[0], x ? 4.f : T < 4 ? kSqrt2 : 2.f, x ? 4.f : kSqrt2);
-        }
-    };
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (has_x && __any(E[8] != E[8])) anew = 1u;   // (register 8: the row of the constant)
-    unsigned again = 0u;
     if (HP == 1) {   // the groups' sums: the first one finishes column tile 0, the other one column tile 1 and E
         float *x = reinterpret_cast<float *>(lds) + 4 * lane;   // (the image's place)
         auto give = [&](int i, const f32x16 &y) {
@@ -1283,7 +1266,6 @@ __device__ __forceinline__ void increment_body(
         if (grp == 0 && has4) give(8 + e4, E);
         if (grp == 0 && has_x) give(10, E);
         wg_sync();
-        again = anew;
         if (grp == 0) {
             take(r4, S[0]);
             put(r4, S[0], kSqrt2, kSqrt2);
@@ -1301,22 +1283,19 @@ __device__ __forceinline__ void increment_body(
         }
     } else {
         wg_sync();   // (the last rows have been read)
-        again = anew;
         put(6 * c0 + r4, S[0], kSqrt2, kSqrt2);
         put(6 * (c0 + 1) + r4, S[1], kSqrt2, kSqrt2);
         if (has4) put(6 * (c0 + e4) + 4, E, 2.f, kSqrt2);
         if (has_x) put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
     }
-    // (the entry has reached memory, its stores are written through, before the flags are raised)
-    if (publish) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    wg_sync();
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane(again) != 0u, 0)) {
-        put_by_element();
+    if (publish) {   // the entry has reached memory (the stores are written through) before the flags are raised
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid >= 2 + seg && tid < G)
+            __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else {
         wg_sync();
     }
-    if (publish && tid >= 2 + seg && tid < G)
-        __hip_atomic_store(flags + (size_t)u * G * G + (1 + seg) * G + tid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Grid: segment by segment, so that a workgroup only waits for workgroups before it.  A launch of one segment is a kernel of its own, without the code of
@@ -1334,14 +1313,14 @@ __global__ __launch_bounds__(64 * (NC + producers(NC)), 2) void prefill_mfma_ker
     SegTable segs, int G, int U)
 {
     __shared__ __align__(1024) unsigned char raw[kLdsBytes];
+    __shared__ unsigned anew;
     Lds<NC> &lds = *reinterpret_cast<Lds<NC> *>(raw);
     if constexpr (!SEG) {
-        prefill_body<NC, false>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, blockIdx.x);
+        prefill_body<NC, false>(lds, anew, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, 1, 0, blockIdx.x);
     } else {
         const int seg = blockIdx.x / U, u = blockIdx.x % U;
-        __shared__ unsigned anew;
-        if (seg > 0) increment_body<NC>(raw, anew, k, v, state, has_init, ws, flags, epoch, N, segs, G, seg - 1, u);
-        prefill_body<NC, true>(lds, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G, seg, u);
+        if (seg > 0) increment_body<NC>(raw, k, v, state, has_init, ws, flags, epoch, N, segs, G, seg - 1, u);
+        prefill_body<NC, true>(lds, anew, q, k, v, y, state, has_init, ws, flags, status, max_polls, epoch, N, segs, G, seg, u);
     }
 }
 
