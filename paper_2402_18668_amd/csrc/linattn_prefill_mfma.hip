@@ -540,18 +540,16 @@ __device__ __forceinline__ void prefill_body(
 #pragma unroll
         for (int r = 0; r < 16; ++r) X[r] = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
     };
-    auto export_moments = [&](const f32x16 &X) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
-            const float m = X[r];
-            if (fl < DP && n < DP) {
-                if (!packed_state || fl <= n) zu[canon_pair(fl, n, packed_state).r1] = m * kRsqrt2;
-            }
-            else if (fl == DP && n < DP) zu[1 + n] = m;
-            else if (fl == DP && n == DP) zu[0] = m;
-        }
+    // where row 8 (r / 4) + 4 g + r % 4 of the moments goes, column n (-1: nowhere), and its value from there
+    auto moment_place = [&](int r) {
+        const int fl = 8 * (r >> 2) + 4 * g + (r & 3);
+        if (fl < DP && n < DP) return !packed_state || fl <= n ? canon_pair(fl, n, packed_state).r1 : -1;
+        return fl != DP || n > DP ? -1 : n == DP ? 0 : 1 + n;
     };
+    auto export_moment = [&](int place, float m) {
+        if (place >= 0) zu[place] = place > DP ? m * kRsqrt2 : m;
+    };
+    auto moments_lds = [&](int r) -> float & { return reinterpret_cast<float *>(&lds)[image_bytes(NC) / 4 + 64 * r + (threadIdx.x & 63)]; };   // register r
     // A key with an element that is not finite.  Its row comes as products with 0/1 matrices, which makes NaN of all of the token's features, of the count of tokens
     // too.  No output of a token that sees it is finite in any case, but the state's rows without the element are: where the count is NaN at the end of the
     // sequence, the state is computed anew, from the rows in memory, element by element.  (us, not at all, so, and with a look at every tile and increment: 256
@@ -571,22 +569,24 @@ __device__ __forceinline__ void prefill_body(
             acc = mfma(pack8(ke), pack8(ve), acc);
         }
     };
+    // The moments' wave leaves them in LDS; the first four producers, which wait for the end, have worked out where they go.  (us, by that wave itself and so, in a
+    // graph: 16 units of 64 tokens, d_v 64 5.9, 5.75, d_v 128, where it is a consumer, 7.6, 7.3; 300 units 13.2, 12.9 and 18.6, 17.9.)
     auto finish_moments = [&](f32x16 &X) {
         const bool bad = __any(X[8] != X[8]);   // (register 8: the row of the constant)
         if (__builtin_expect(bad, 0)) {
             role_guard();
             zero16(X);
             if (has_init) {   // (through LDS: the loop need not be unrolled)
-                float *own = image + image_bytes(NC) / 4 + lane;
 #pragma unroll 1
-                for (int r = 0; r < 16; ++r) own[64 * r] = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
+                for (int r = 0; r < 16; ++r) moments_lds(r) = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) X[r] = own[64 * r];
+                for (int r = 0; r < 16; ++r) X[r] = moments_lds(r);
             }
             add_by_element(X, NTILE - 1, 0, true);
         }
         if (lane == 0) anew = bad ? 1u : 0u;
-        export_moments(X);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) moments_lds(r) = X[r];
     };
     auto image_by_element = [&]() {   // a wave takes a tile of 32 rows and 32 columns at a time, in the layout of accumulators
         if (has_init) {
@@ -618,6 +618,7 @@ __device__ __forceinline__ void prefill_body(
             if (tid == 0) __hip_atomic_store(flags_unit + (G - 1), epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     };
+    int place[4];   // of the moments that the first four producers write
     if (!is_p) {
         // =================================== consumer waves =========================================
         f32x16 S[NTILE];       // the five state tiles of this wave's 32 columns
@@ -1042,9 +1043,17 @@ __device__ __forceinline__ void prefill_body(
 
         // ---- end of segment: the moments ----------------------------------------------------------
         if (has_m && Su && seg == G - 1) finish_moments(X);
+        if (c < 4) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) place[j] = moment_place(4 * c + j);
+        }
     }
     if (Su && seg == G - 1) {
         __syncthreads();
+        if (is_p && c < 4) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) export_moment(place[j], moments_lds(4 * c + j));
+        }
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(anew) != 0u, 0)) image_by_element();
         export_image();
     }
