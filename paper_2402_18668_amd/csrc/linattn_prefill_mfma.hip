@@ -553,58 +553,50 @@ __device__ __forceinline__ void prefill_body(
     // A key with an element that is not finite.  Its row comes as products with 0/1 matrices, which makes NaN of all of the token's features, of the count of tokens
     // too.  No output of a token that sees it is finite in any case, but the state's rows without the element are: where the count is NaN at the end of the
     // sequence, the state is computed anew, from the rows in memory, element by element.  (us, not at all, so, and with a look at every tile and increment: 256
-    // units of 2048 tokens, d_v 128, 82.0, 82.1, 82.8; 128 of 2048, d_v 64, 35.2, 35.5, 35.2; 16 of 777 from a state 15.55, 15.6, 15.7.)
-    auto add_by_element = [&](f32x16 &acc, const int T, const int col, const bool moments) {   // all tokens' products
-#pragma unroll 1
-        for (int t = 0; t < N; t += 16) {
-            float ke[8], ve[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int tok = t + 8 * (e >> 2) + 4 * g + (e & 3);
-                const size_t at = min(tok, N - 1);
-                const float kx = phik_element(ku + at * DP, T, n), vx = moments ? kx : bf16_at(vu + at * DV + col);
-                ke[e] = tok < N && !(moments && n > DP) ? kx : 0.f;
-                ve[e] = tok < N && !(moments && n > DP) ? vx : 0.f;
-            }
-            acc = mfma(pack8(ke), pack8(ve), acc);
-        }
-    };
-    // The moments' wave leaves them in LDS; the first four producers, which wait for the end, have worked out where they go.  (us, by that wave itself and so, in a
-    // graph: 16 units of 64 tokens, d_v 64 5.9, 5.75, d_v 128, where it is a consumer, 7.6, 7.3; 300 units 13.2, 12.9 and 18.6, 17.9.)
-    auto finish_moments = [&](f32x16 &X) {
-        const bool bad = __any(X[8] != X[8]);   // (register 8: the row of the constant)
-        if (__builtin_expect(bad, 0)) {
-            role_guard();
-            zero16(X);
-            if (has_init) {   // (through LDS: the loop need not be unrolled)
-#pragma unroll 1
-                for (int r = 0; r < 16; ++r) moments_lds(r) = initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) X[r] = moments_lds(r);
-            }
-            add_by_element(X, NTILE - 1, 0, true);
-        }
-        if (lane == 0) anew = bad ? 1u : 0u;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) moments_lds(r) = X[r];
-    };
-    auto image_by_element = [&]() {   // a wave takes a tile of 32 rows and 32 columns at a time, in the layout of accumulators
+    // units of 2048 tokens, d_v 128, 82.0, 82.1, 82.8; 128 of 2048, d_v 64, 35.2, 35.1, 35.2; 16 of 777 from a state 15.55, 15.7, 15.7.)
+    auto state_by_element = [&]() {   // a wave takes a tile of 32 rows and 32 columns at a time, or the moments, in the layout of accumulators
         if (has_init) {
             import_state_image<NC>(image, Su, packed_state, tid);
             __syncthreads();
         }
 #pragma unroll 1
-        for (int i = w; i < NC * NTILE; i += NC + NPW) {
-            float *at = image + i * 32 * IMG_LD + 4 * g * IMG_LD + n;
+        for (int i = w; i < NC * NTILE + 1; i += NC + NPW) {
+            const bool x = i == NC * NTILE;
+            const int T = x ? NTILE - 1 : i % NTILE, col = i / NTILE * 32 + n;
+            if (x) {
+#pragma unroll 1
+                for (int r = 0; r < 16; ++r) moments_lds(r) = has_init ? initial_moment(zu, 8 * (r >> 2) + 4 * g + (r & 3), n, packed_state) : 0.f;
+            }
+            float *at = x ? &moments_lds(0) : image + i * 32 * IMG_LD + 4 * g * IMG_LD + n;
             f32x16 acc;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = has_init ? at[(8 * (r >> 2) + (r & 3)) * IMG_LD] : 0.f;
-            add_by_element(acc, i % NTILE, i / NTILE * 32 + n, false);
+            for (int r = 0; r < 16; ++r) acc[r] = x || has_init ? at[x ? 64 * r : (8 * (r >> 2) + (r & 3)) * IMG_LD] : 0.f;
+#pragma unroll 1
+            for (int t = 0; t < N; t += 16) {
+                float ke[8], ve[8];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) at[(8 * (r >> 2) + (r & 3)) * IMG_LD] = acc[r];
+                for (int e = 0; e < 8; ++e) {
+                    const int tok = t + 8 * (e >> 2) + 4 * g + (e & 3);
+                    const size_t row = min(tok, N - 1);
+                    const float kx = phik_element(ku + row * DP, T, n), vx = bf16_at(vu + row * DV + (x ? 0 : col));
+                    ke[e] = tok < N && !(x && n > DP) ? kx : 0.f;
+                    ve[e] = x ? ke[e] : tok < N ? vx : 0.f;
+                }
+                acc = mfma(pack8(ke), pack8(ve), acc);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) at[x ? 64 * r : (8 * (r >> 2) + (r & 3)) * IMG_LD] = acc[r];
         }
         __syncthreads();
     };
+    // The moments' wave leaves them in LDS; the first four producers, which wait for the end, have worked out where they go.  (us, by that wave itself and so, in a
+    // graph: 16 units of 64 tokens, d_v 64 5.9, 5.75, d_v 128, where it is a consumer, 7.5, 7.3; 300 units 13.05, 12.8 and 18.4, 17.85.)
+    auto finish_moments = [&](const f32x16 &X) {
+        if (X[8] != X[8]) anew = 1u;   // (register 8: the row of the constant)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) moments_lds(r) = X[r];
+    };
+    if (tid == 0) anew = 0u;   // (ordered before its use by the barriers of the first chunk)
     if (has_init && seg == 0) {
         import_state_image<NC>(image, Su, packed_state, tid);
         __syncthreads();
@@ -1050,11 +1042,11 @@ __device__ __forceinline__ void prefill_body(
     }
     if (Su && seg == G - 1) {
         __syncthreads();
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(anew) != 0u, 0)) state_by_element();
         if (is_p && c < 4) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) export_moment(place[j], moments_lds(4 * c + j));
         }
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane(anew) != 0u, 0)) image_by_element();
         export_image();
     }
 }
