@@ -32,9 +32,8 @@ def test_linear_tilings(based, M, K, N):
     check_close(y[at], oracle.linear(x[at], W), TOL["bf16"], f"linear {M}x{K}x{N}")
 
 
-# small tiles whose steps two or four groups of waves share: fewer steps than groups, one short and several; bands of 32 and 64 tokens that end inside a tile; the
-# last sizes with a tile to a CU and the first with more, with up to 32 tokens and above; a step that starts inside a head; and a last round of 256 x 256
-# tiles in halves where the tiles go rows fastest, the second half of its last band past the end
+# few tokens and few columns, around a tile to a CU, also from inputs in heads of one and two steps (which tiling a size takes: below); and a last round of
+# 256 x 256 tiles in halves, the second half of its last band past the end
 @pytest.mark.parametrize("M,K,N", [(19, 64, 128), (32, 128, 256), (33, 192, 128), (63, 448, 256), (96, 320, 2560), (97, 320, 2560), (200, 576, 1792),
                                    (257, 64, 1792), (32, 64, 8192), (32, 64, 8320), (512, 1792, 512), (513, 256, 512), (257, 1088, 2560), (1100, 1024, 896),
                                    (1025, 960, 896), (2100, 64, 9216)])
@@ -60,9 +59,9 @@ def tile_of(call):
     return tuple(int(x) for x in found.groups()) if found else (0, 0, 0)
 
 
-# the lines between the tilings of few tokens, on either side; the groups' shares with every remainder of the steps, bands that end inside a tile, features
-# and rows fastest
-@pytest.mark.parametrize("M,K,N,tile", [(18, 128, 128, (0, 0, 0)), (19, 64, 128, (0, 0, 0)), (19, 128, 128, (32, 32, 4)), (32, 128, 8192, (32, 32, 4)), (32, 128, 8320, (0, 0, 0)),
+# the lines between the tilings of few tokens, on either side; fewer steps than groups, and the groups' shares with every remainder of the steps; bands that end
+# inside a tile; features and rows fastest
+@pytest.mark.parametrize("M,K,N,tile", [(18, 128, 128, (0, 0, 0)), (19, 64, 128, (0, 0, 0)), (19, 128, 128, (32, 32, 4)), (32, 128, 8192, (32, 32, 4)), (32, 128, 8320, (0, 0, 0)), (24, 192, 256, (32, 32, 4)), (31, 320, 2560, (32, 32, 4)),
                                         (33, 512, 128, (64, 64, 1)), (33, 576, 128, (32, 32, 4)), (513, 640, 512, (64, 64, 1)),
                                         (97, 1216, 2560, (64, 64, 2)), (97, 1280, 2560, (64, 32, 4)), (129, 1408, 1792, (64, 32, 4)), (190, 1472, 1792, (64, 32, 4)),
                                         (200, 1344, 1792, (64, 32, 4)), (257, 1280, 1792, (64, 64, 2)), (97, 1088, 2560, (64, 64, 1)), (256, 1152, 4096, (64, 64, 2)),
@@ -274,11 +273,11 @@ def test_prefill_decay_edges(based, dtype, dp, dv, N):
     check_close(down(z).reshape(zw.shape), zw, 1e-4, "z")
 
 
-# bf16 d' = 16 prefill: the rule for the number of segments (below and at 6 chunks, few units with many short segments, two
-# uneven segments), the initial state read by two workgroups and overwritten by a third, both state layouts
+# bf16 d' = 16 prefill from a state, both layouts: one segment (a few chunks, and 120 units of 6 at d_v 128), many short ones of few units, and two uneven ones, where the
+# second one's workgroup reads the state for its increment, beside the first one's, and overwrites it
 @pytest.mark.parametrize("packed", [False, True])
 @pytest.mark.parametrize("U,dv,N1,N", [(3, 64, 70, 380), (3, 64, 70, 385 + 70), (2, 128, 1, 900), (3, 128, 64, 2300), (120, 64, 65, 450),
-                                       (120, 128, 17, 401)])
+                                       (120, 128, 17, 401), (120, 128, 17, 17 + 449), (128, 128, 64, 64 + 700)])
 def test_prefill_segments_from_a_state(based, packed, U, dv, N1, N):
     wl = synth.Workload(**{**synth.WORKLOADS["prefill_360m"].__dict__, "d_v": dv})
     q, k, v = synth.linattn_inputs(wl, units=U, N=N)
