@@ -1056,10 +1056,11 @@ __device__ __forceinline__ void prefill_body(
 // The eight waves need no operand from each other here, so nothing but the rows passes through LDS, and a step has one barrier.  Wave r = w % 4
 // owns tile r for two column tiles (waves 2 and 3 also tile 4, for one of them; wave 1 the moments), and a feature is a product of two
 // values in its registers: multiplied with 0/1 matrices a tile of 32 rows of K comes back as accumulators, in fp32 and without rounding, with lane
-// n holding k_a (halved) or the k_b of its row and the registers going over the tokens in the order of an operand's k-slots.  At d_v 64 the waves 0-3
+// n holding k_a / sqrt(2) or the k_b of its row and the registers going over the tokens in the order of an operand's k-slots.  At d_v 64 the waves 0-3
 // and 4-7 take alternate tiles of 32 tokens and are added up at the end; at d_v 128 they own 64 columns each.  The rows come by the 16-byte LDS
-// DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  Every row is a sum of halved products: pair rows
-// are scaled by sqrt(2), the others by 2, the moments by 4 when they are put away.
+// DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  The features are the main pass's to
+// the bit: rounded as k_a k_b / 2, the sums scaled at the end, they left the state 0.2 to 0.5 % further from float64 (128 units of 2048 tokens, d_v 64 36.8 us either way, d_v 128
+// 57.0, now 58.6; 16 of 777 from a state 16.0, now 15.6).
 //
 // Bound: memory, with half of the chip at increments and half at main passes (128 units: 1300 cycles a chunk at d_v 64, 2300 at 128, 4.1 TB/s together;
 // 16 units 1200); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
@@ -1110,10 +1111,10 @@ __device__ __forceinline__ void increment_body(
     if (HP == 1 || !imports) issue_first();
 
     // 0/1 matrices as B operands
-    const bf16x8 first_eye = one_at(g, m, 0x3F00u);                              // k_a / 2
+    const bf16x8 first_eye = one_at(g, m, 0x3F80u);                              // k_a
     const bf16x8 second_eye = one_at(g, (m + 2 * r4 + (n >> 4)) & 15, 0x3F80u);   // k_b of tile r
     const bf16x8 pair_eye = one_at(g, n >= 24 ? n - 24 : -1, 0x3F80u);           // k_b of tile 4's pairs (k_a: lane n holds a = n - 16)
-    const float row_one = n < 16 ? 1.f : 0.f, row_half = n == 16 ? 0.5f : 0.f;
+    const float row_linear = n < 16 ? kSqrt2 : 0.f, row_one = n == 16 ? 1.f : 0.f;
 
     // This wave's column tiles are c0, c0 + 1; waves 2, 3, 4 and 5 have tile 4 of column tile c0 + r % 2 as well (a matrix pipe serves waves w
     // and w + 4), wave 1, at d_v 64 also 7, the moments.
@@ -1138,9 +1139,8 @@ __device__ __forceinline__ void increment_body(
             for (int r = 0; r < 16; ++r) {
                 const int row = 8 * (r >> 2) + (r & 3);
 #pragma unroll
-                for (int c = 0; c < 2; ++c) S[c][r] = kRsqrt2 * at[(c * 32 * NTILE + 32 * r4 + row) * IMG_LD];
-                if (has4) E[r] = (r < 12 ? 0.5f : kRsqrt2) * at[(e4 * 32 * NTILE + 128 + row) * IMG_LD];
-                if (has_x) E[r] *= 0.25f;
+                for (int c = 0; c < 2; ++c) S[c][r] = at[(c * 32 * NTILE + 32 * r4 + row) * IMG_LD];
+                if (has4) E[r] = at[(e4 * 32 * NTILE + 128 + row) * IMG_LD];
             }
         }
         if (HP == 2) {
@@ -1175,9 +1175,10 @@ __device__ __forceinline__ void increment_body(
             zero16(a[i]); zero16(b[i]);
             a[i] = mfma(kr, first_eye, a[i]);
             b[i] = mfma(kr, second_eye, b[i]);
+            a[i] *= kRsqrt2;
             if (KIND == 2) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) f[i][r] = row_one;
+                for (int r = 0; r < 16; ++r) f[i][r] = row_linear;
                 f[i] = mfma(kr, pair_eye, f[i]);
             }
         };
@@ -1190,13 +1191,13 @@ __device__ __forceinline__ void increment_body(
                 const bf16x8 op = pack8(pr);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) S[c] = mfma(op, vo[s][c], S[c]);
-                if (KIND == 2) {   // linear rows k_a / 2, the constant 1 / 2, pairs
+                if (KIND == 2) {   // linear rows, the constant, pairs
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], f[i][8 * s + e], row_half);
+                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], f[i][8 * s + e], row_one);
                     E = mfma(pack8(pr), e4 ? vo[s][1] : vo[s][0], E);
                 } else if (KIND == 1) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], row_one, row_half);
+                    for (int e = 0; e < 8; ++e) pr[e] = fmaf(a[i][8 * s + e], row_linear, row_one);
                     const bf16x8 x = pack8(pr);
                     E = mfma(x, x, E);
                 }
@@ -1238,12 +1239,10 @@ __device__ __forceinline__ void increment_body(
     const bool publish = seg + 2 < G;   // later segments need it, too
     float *e = ws + (size_t)u * (G - 1) * entry_floats(NC) + (size_t)seg * entry_floats(NC) + (size_t)lane * 4;
     float *hand = reinterpret_cast<float *>(lds + AT) + 4 * lane;
-    auto put = [&](int slot, const f32x16 &x, float s_low, float s_high) {   // s_high: registers 12 .. 15
+    auto put = [&](int slot, const f32x16 &x) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            f32x4 o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (j < 3 ? s_low : s_high) * x[4 * j + i];
+            const f32x4 o = {x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]};
             *reinterpret_cast<f32x4 *>(hand + slot * kSlotFloats + j * 256) = o;
             if (publish) store16_coherent(e + (size_t)slot * kSlotFloats + (size_t)j * 256, o);
         }
@@ -1269,25 +1268,25 @@ __device__ __forceinline__ void increment_body(
         wg_sync();
         if (grp == 0) {
             take(r4, S[0]);
-            put(r4, S[0], kSqrt2, kSqrt2);
+            put(r4, S[0]);
         } else {
             take(4 + r4, S[1]);
-            put(6 + r4, S[1], kSqrt2, kSqrt2);
+            put(6 + r4, S[1]);
             if (has4) {
                 take(8 + e4, E);
-                put(6 * e4 + 4, E, 2.f, kSqrt2);
+                put(6 * e4 + 4, E);
             }
             if (has_x) {
                 take(10, E);
-                put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
+                put(6 * x_tile(NC) + 5, E);
             }
         }
     } else {
         wg_sync();   // (the last rows have been read)
-        put(6 * c0 + r4, S[0], kSqrt2, kSqrt2);
-        put(6 * (c0 + 1) + r4, S[1], kSqrt2, kSqrt2);
-        if (has4) put(6 * (c0 + e4) + 4, E, 2.f, kSqrt2);
-        if (has_x) put(6 * x_tile(NC) + 5, E, 4.f, 4.f);
+        put(6 * c0 + r4, S[0]);
+        put(6 * (c0 + 1) + r4, S[1]);
+        if (has4) put(6 * (c0 + e4) + 4, E);
+        if (has_x) put(6 * x_tile(NC) + 5, E);
     }
     if (publish) {   // the entry has reached memory (the stores are written through) before the flags are raised
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

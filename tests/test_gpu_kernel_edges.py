@@ -315,6 +315,23 @@ def test_prefill_increments(based, dv, N, init):
     check_close(z[:3], zw, TOL["bf16"], "z")
 
 
+# .. an increment rounds features as the main pass does: a state of several segments is that of one, but for the order of its fp32 sums (at most N terms, each way
+# N 2^-24 of the sum of their absolute values; the same key in all tokens and V of one sign, so that another rounding would not average out)
+@pytest.mark.parametrize("dv,U,N", [(64, 16, 64 * 13), (64, 128, 64 * 20 + 7), (128, 12, 64 * 24), (128, 100, 64 * 16)])
+def test_prefill_increment_rounding(based, dv, U, N):
+    rng = np.random.default_rng(75)
+    q, k = (np.broadcast_to(0.5 * rng.standard_normal((U, 1, 16)), (U, N, 16)) for _ in range(2))
+    v = np.abs(rng.standard_normal((U, N, dv)))
+
+    def state_of(copies):
+        state = based.alloc_state(1, copies * U, 16, dv)
+        based.prefill(*(up(synth.round_to(np.tile(a, (copies, 1, 1)).astype(np.float32), "bf16"), "bf16", (1, copies * U, N, a.shape[2])) for a in (q, k, v)), state=state)
+        return [down(a)[0, :U] for a in based.state_export(state, 1, copies * U, 16, dv)]
+
+    for several, one in zip(state_of(1), state_of(-(-129 // U))):
+        assert (np.abs(several - one) <= 2 * N * 2.0 ** -24 * np.abs(one)).all()
+
+
 # .. a key that is not finite reaches the state's rows with its element, later tokens and nothing else: outputs that do not see it have the bits of the call with a
 # zero there, the other rows its values.  One segment, increments (first and last tokens, both tiles of a step) and the last segment, its last chunk ends inside
 @pytest.mark.parametrize("packed", [False, True])
