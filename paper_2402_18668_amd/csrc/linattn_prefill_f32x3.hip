@@ -763,21 +763,29 @@ __global__ __launch_bounds__(NT, 4) void prefill_kernel(const float *__restrict_
     if (writes_state) export_image();
 }
 
+inline int segment_len(int N, int G) { return ((N + G - 1) / G + C - 1) / C * C; }
+
 // Segments of at least 64 tokens, at most 64 of them, in one round of the chip.  Two workgroups to a CU take 1.35 times as long for a token of theirs as one does
 // (0.235 us for a token of a segment, its increment included, against 0.174) and have twice the entries to sum, about 1 us for each of the first 16 more.  So
-// one to a CU up to 18 tokens for each pair of a segment and an entry more.  (us, d_v 64, one and two to a CU: 16 units N 2048 38.1, 46.8, N 6000 81.2, 75.8; 8
+// one to a CU while its segments (rounded up to chunks) have up to 15 tokens for an entry more.  (us, d_v 64, one and two to a CU: 16 units N 2048 38.1, 46.8, N 6000 81.2, 75.8; 8
 // units N 2048 30.6 with one, there are no more segments, N 6000 51.8, 58.5; 32 units N 777 32.6, 32.4, N 2048 58.9, 54.1, N 6000 144.8, 113.6; 64 units N 777 49.0, 43.4, N 2048
-// 101.6, 80.9.)
+// 101.6, 80.9.)  But not where rounding makes it leave a fifth of the CUs idle and hardly a CU would get two: 24 units N 974, 8 segments of 128 tokens and 11 of 96, 32.8, 29.0.
 inline int segments(int U, int N, int dv)
 {
     const long groups = (long)U * (dv / COLS);
+    struct Cut { int G, len; long workgroups; };
+    auto cut = [&](long G) {
+        if (G > N / 64) G = N / 64;
+        if (G > kMaxSegments) G = kMaxSegments;
+        if (G < 1) G = 1;
+        const int len = segment_len(N, (int)G);
+        return Cut{(int)G, len, groups * ((N + len - 1) / len)};
+    };
     const long one = 256 / groups, more = one < 16 ? one : 16;
-    long G = one > 0 && N <= 18 * one * more ? one : 512 / groups;
-    if (G > N / 64) G = N / 64;
-    if (G > kMaxSegments) G = kMaxSegments;
-    return G < 1 ? 1 : (int)G;
+    const Cut few = cut(one), many = cut(512 / groups);
+    const bool idle = few.workgroups <= 208 && many.workgroups <= 288 && many.len < few.len;
+    return few.len <= 15 * more && !idle ? few.G : many.G;
 }
-inline int segment_len(int N, int G) { return ((N + G - 1) / G + C - 1) / C * C; }
 
 template <int DV, bool DECAY>
 hipError_t launch(const void *q, const void *k, const void *v, void *y, float *state, int has_init, void *workspace, int U, int N,

@@ -411,7 +411,7 @@ def test_prefill_fp32_shared_increments(based, U, dv, N, init):
     check_close(z[:few], zw, TOL["f32"], "z")
 
 
-# .. and segments for one and for two workgroups to a CU, on either side of the line and well below it
+# .. and segments for one and for two workgroups to a CU (which a size takes: test_prefill_fp32_segment_counts)
 @pytest.mark.parametrize("U,dv,N,init", [(32, 64, 1152, False), (32, 64, 1153, False), (16, 128, 1152, True), (16, 128, 1153, True), (40, 64, 648, True), (40, 64, 649, False),
                                          (20, 64, 1100, False), (8, 64, 4000, True)])
 def test_prefill_fp32_segments_to_a_cu(based, U, dv, N, init):
@@ -915,6 +915,29 @@ def test_prefill_segment_counts_from_a_state(based, packed, U, dv, N, G, tmp_pat
     if packed:
         state = based.state_unpack(state, based.alloc_state(1, U, 16, dv), 1, U, 16, dv)
     check_close(down(based.state_export(state, 1, U, 16, dv)[0])[0, at], oracle.linattn_state(k[at], v[at])[0], TOL["bf16"], "S")
+
+
+# fp32 d' = 16 prefill: the number of segments, by the grid of the main launch: one workgroup to a CU up to 15 tokens of a segment for an entry more, on either side,
+# and not where a fifth of the CUs would be idle (974 tokens, not 1024, where two to a CU are more than a few)
+@pytest.mark.parametrize("U,dv,N,G", [(24, 64, 974, 11), (12, 128, 974, 11), (24, 64, 1024, 8), (24, 64, 1280, 10), (6, 128, 2046, 22), (6, 128, 2300, 18), (16, 64, 3584, 16), (16, 64, 3585, 29),
+                                      (40, 64, 648, 7), (32, 64, 768, 8), (32, 64, 769, 9), (300, 64, 777, 1)])
+def test_prefill_fp32_segment_counts(based, U, dv, N, G, tmp_path):
+    import json
+    import torch
+    q, k, v = (up(synth.normal(46 + i, (1, U, N, d), 0.5), "f32") for i, d in enumerate((16, 16, dv)))
+    state = based.alloc_state(1, U, 16, dv)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+        y = based.prefill(q, k, v, state=state)
+        torch.cuda.synchronize()
+    trace = tmp_path / "trace.json"
+    profile.export_chrome_trace(str(trace))
+    kernels = [e for e in json.loads(trace.read_text())["traceEvents"] if "f32x3::prefill_kernel" in e.get("name", "")]
+    grid = max(kernels, key=lambda e: e["ts"])["args"]["grid"]
+    assert grid[0] * grid[1] == U * (dv // 64) * G
+    at = np.unique([0, U - 1])
+    a = [down(x)[0, at] for x in (q, k, v)]
+    check_close(rows(down(y)[0, at]), rows(oracle.linattn_quadratic(*a)), TOL["f32"], "y")
+    check_close(down(based.state_export(state, 1, U, 16, dv)[0])[0, at], oracle.linattn_state(*a[1:])[0], TOL["f32"], "S")
 
 
 # outputs are allocated past the dispatcher, except under a mode that looks at every operator
