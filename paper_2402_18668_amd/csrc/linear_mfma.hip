@@ -457,15 +457,20 @@ using T256 = Tile<256, 256, 2, 2, 2, 6>;       // 128 KB: one
 using T256H = Tile<128, 256, 2, 2, 2, 6>;
 using T32S = Tile<32, 32, 1, 2, 4, 8, 4>;          // 128 KB: one
 using T64S = Tile<64, 32, 2, 1, 3, 8, 4>;          // 144 KB: one
-using T64D = Tile<64, 64, 2, 2, 4, 8, 2>;          // 128 KB: one
-enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64D, TILE64, TILE128N, TILE128, TILE256 };
+enum Variant { ROWS1, ROWS2, TILE32S, TILE64S, TILE64, TILE128N, TILE128, TILE256 };
 
 inline long tiles_of(long M, long N, int bm, int bn) { return (M + bm - 1) / bm * (N / bn); }
 
-// Rows fastest over the XCDs: where W is enough larger than x, and the operands, not the output, are what a tile moves.  (us of a launch, features and rows
-// fastest: 1792 -> 2560 features 300 tokens 10.5, 6.8, 512 11.6, 9.3, 1000 19.3, 16.5, 1500 19.4, 18.8, 1919 24.45, 24.4, 1280 -> 2560 1919 19.6, 20.1; 2048 -> 1792 700
-// 12.6, 10.5, 1000 13.2, 12.8, 1344 18.8, 18.2; 1280 -> 512 2048 6.0, 9.3; 512 -> 4096 2048 12.6, 11.9, 192 -> 4096 8.1, 8.5.)
-inline bool rows_first(long M, int K, long N) { return 10 * M < 7 * N && K >= 5 * BK; }
+// The ratios below are of launch times in three settings: the same operands again (they stay in the L2); other operands each time, in the last-level cache; and W
+// from memory, as in a model whose weights that cache does not hold.
+//
+// Rows fastest over the XCDs: where W is enough larger than x, and the operands, not the output, are what a tile moves.  (Time of rows fastest by that of features
+// fastest, 10 M < 7 N: 64 x 64 tiles, 16 steps of 64 columns and more, 0.94, 0.93, 0.98, up to 8 steps and 128 tiles 1.02, 1.02, 1.00; with 7 N <= 10 M < 10 N 0.99, 0.99, 0.98, beyond that up
+// to 1.11, 1.09, 1.01.  128 x 64 tiles, up to 256 0.93, 0.95, 0.98, up to 512 0.88, 0.90, 1.04; over 1024 1.02 to 1.1.)
+inline bool rows_first(long M, int K, long N)
+{
+    return 10 * M < 7 * N && K >= (tiles_of(M, N, 64, 64) > 128 ? 5 : 8) * BK && tiles_of(M, N, 128, 64) <= 1024;
+}
 
 // A handful of tokens: 16 or 32 per workgroup (above 32 tiles, which read W fewer times, are as fast or faster).
 // Otherwise the tiling with the smallest expected time.  The figures are microseconds per 64-deep step, measured at
@@ -477,15 +482,17 @@ inline Variant pick_variant(int M, int K, int N)
     if (M <= 16) return ROWS1;
     if (M <= 18 || K >= (1 << 22)) return ROWS2;   // (tiles address their rows with 32-bit offsets)
     // Few tiles are bound by what a CU takes in of x and W and by the latency of a step: the smallest tiles that leave each CU at most one, the steps
-    // shared out over groups of waves, where there are enough of them to pay for the groups' start and sum.  (us of a launch:
-    // 32 x 32 in four groups, before (ROWS2; 64 x 64) and so: 24 tokens, 64 -> 1024 features 3.1, 3.4, 128 -> 1024 3.9, 3.35, 1792 -> 2560 6.0, 4.7; 64 tokens to 2560
-    // features, K 64 2.8, 3.5, 448 3.73, 3.74, 512 3.86, 3.71, 640 4.1, 3.9, 1792 6.9, 4.8; 300 tokens to 512, K 448 3.67, 3.68, 640 4.1, 3.9, 1792 6.9, 4.8.
-    // 64 x 32 in four and 64 x 64 in one and two groups: 128 tokens to 2560 features, K 1152 5.35, 5.3, 5.3, 1280 5.4, 5.65, 5.6, 1792 6.0, 6.8, 6.5; 200 to 1792, K
-    // 1152 5.6, 5.4, 5.4, 1280 5.5, 5.75, 5.6, 2048 6.6, 7.5, 6.95; nearly a tile to each CU, 128 to 4096, K 1280 5.9, 5.7, 5.7, 1792 6.7, 6.8, 6.5.  More tiles than CUs
-    // take two rounds: 200 tokens, 1792 -> 2560, 8.3 with 64 x 64, 17 with 32 x 32, 13 with 64 x 32.)
-    if (K >= (M <= 32 ? 2 : 9) * BK && tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
+    // shared out over four groups of waves, where there are enough of them to pay for the groups' start and sum.  (Time of
+    // 32 x 32 by that before.  33 tokens and more, by 64 x 64, 10 M < 7 N: 9 steps 1.00, 1.00, 10 0.96, 0.97, 16 0.84, 0.86, 20 and more 0.75, 0.79, all with W from memory 0.76; otherwise 10
+    // steps 0.94, 0.95 to 1.03, 0.89, 12 0.91, 0.92 to 1.00, 0.87, 26 0.73, 0.78 to 0.89, 0.72.  19 to 32, by ROWS2: 1
+    // step 1.08, 1.10, 2 0.87, 0.88, 3 and more 0.74, 0.76, and with W from memory up to 17 steps 0.86, but from 18 on 1.05, there ROWS2 asks for more of W at once.
+    // 64 x 32 by 64 x 64, 10 M < 7 N: 16 to 23 steps 0.97, 1.03, 0.93, 24 to 27 0.93, 1.00, 0.88, 28 and more 0.88, 0.96, 0.86; otherwise x is the larger operand and
+    // read by twice as many tiles, 32 steps and more 0.88, 1.1, 0.86.  64 x 64 in two groups by one: 32 steps and more 0.95, 1.08, 1.01, fewer 0.97 to 1.02, 1.10, 1.04.  More
+    // tiles than CUs take two rounds: 200 tokens, 1792 -> 2560, 8.3 us with 64 x 64, 17 with 32 x 32, 13 with 64 x 32.)
+    const bool wide = 10ll * M < 7ll * N;
+    if (K >= (M <= 32 ? 2 : wide ? 10 : 12) * BK && tiles_of(M, N, T32S::BM, T32S::BN) <= 256) return TILE32S;
     if (M <= 32) return ROWS2;
-    if (K >= 20 * BK && tiles_of(M, N, T64S::BM, T64S::BN) <= 224) return TILE64S;
+    if (wide && K >= 28 * BK && tiles_of(M, N, T64S::BM, T64S::BN) <= 224) return TILE64S;
     auto per_cu = [](long tiles) { return (float)((tiles + 255) / 256); };
     Variant best = TILE64;
     float t = 0.05f + 0.21f * per_cu(tiles_of(M, N, T64::BM, T64::BN));
@@ -499,9 +506,7 @@ inline Variant pick_variant(int M, int K, int N)
         const long n256 = tiles_of(M, N, T256::BM, T256::BN), rem = n256 % 256;
         offer(TILE256, 1.5f * (float)(n256 / 256) + (rem == 0 ? 0.f : rem <= 128 ? 1.f : 1.5f));   // (see launch_tile)
     }
-    // 64 x 64 tiles, one to a CU: two groups of waves.  (us, with one and two: 256 tokens to 2560 features, K 1024 5.2, 5.3, 1152 5.5, 5.5, 1792 7.1, 6.7; 400 to 1792, K 2048 7.75, 7.3;
-    // features fastest, 1344 tokens, 1280 -> 512 5.8, 5.75, 1500 5.9, 5.9, 2048, 256 tiles, 6.0, 6.5, 1000 tokens, 1280 -> 1024 6.05, 6.5.)
-    return best == TILE64 && K >= 18 * BK && tiles_of(M, N, T64::BM, T64::BN) <= (rows_first(M, K, N) ? 256 : 192) ? TILE64D : best;
+    return best;
 }
 
 template <typename T, typename T2, bool SPLIT_OUT, bool HEADS_IN>
@@ -532,7 +537,6 @@ hipError_t launch_variant(Variant v, const uint16_t *x, const uint16_t *W, uint1
     switch (v) {
     case ROWS1: launch_rows<1, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case ROWS2: launch_rows<2, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
-    case TILE64D: launch_tile<T64D, T64D, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE64: launch_tile<T64, T64, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE32S: launch_tile<T32S, T32S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
     case TILE64S: launch_tile<T64S, T64S, SPLIT_OUT, HEADS_IN>(x, W, y, M, K, N, hl, s); break;
