@@ -1339,14 +1339,14 @@ namespace {
 // From a state (launch; the workspace has room for the number without one) the state is read twice and written by a third workgroup.  With a number of units that
 // 8 divides these are on one XCD; otherwise the state travels between them, the longer the more units there are, and segments pay later.  (us from a state, one segment
 // and several.  d_v 64: 42 units 6 chunks 14.5, 14.6, 7 15.9, 14.7; 60 units 6 14.8, 15.2, 7 16.1, 15.2; 85 units 6 15.1, 16.3, 8 17.8, 17.5, 9 19.1, 19.1; 102 units 9 19.4,
-// 20.2, 10 20.8, 20.3; but 64 units 5 13.3, 13.0, 128 5 14.3, 14.2.  d_v 128: 12 units 6 17.8, 17.4; 28 units 7 19.8, 19.9, 8 21.3, 20.0; 51 units 8 21.7, 22.3, 9 23.4, 22.7; 85
+// 20.2, 10 20.8, 20.3; but 64 units 5 13.3, 13.0, 128 5 14.3, 14.2.  d_v 128: 12 units 6 17.8, 17.4; 28 units 7 19.8, 19.9, 8 21.3, 20.0; 29 units 7 20.4, 21.6; 44 units 8 22.1, 22.1; 45 units 8 22.7, 24.4; 51 units 8 21.7, 22.3, 9 23.4, 22.7; 85
 // units 10 26.1, 26.4, 12 28.9, 27.9; 102 units 12 29.6, 29.6; but 64 units 6 19.0, 18.5, 96 6 19.8, 20.2, 8 22.6, 22.0, 128 7 22.4, 22.6, 8 23.1, 22.5.)
 int pick_segments(int U, int N, int dv, bool from_state = false)
 {
     const int chunks = (N + C - 1) / C;
     const bool wide = dv == 128;
     int least = !wide ? 5 : U > 85 ? 7 : 6;
-    if (from_state && U % 8 != 0) least = wide ? 6 + U / 16 : U > 85 ? 10 : 5 + U / 24;
+    if (from_state && U % 8 != 0) least = wide ? 6 + (U + 3) / 16 : U > 85 ? 10 : 5 + U / 24;
     else if (from_state && wide && U > 85) least = 8;
     if (chunks < least) return 1;
     int G = 256 / U;

@@ -896,7 +896,7 @@ def test_prefill_segment_counts(based, U, dv, N, G, tmp_path):
 # .. from a state: later where a unit's segments are on several XCDs
 @pytest.mark.parametrize("packed", [False, True])
 @pytest.mark.parametrize("U,dv,N,G", [(16, 64, 257, 2), (51, 64, 384, 1), (51, 64, 385, 3), (85, 64, 448, 1), (85, 64, 449, 3), (102, 64, 576, 1), (102, 64, 577, 2), (128, 64, 257, 2),
-                                      (51, 128, 512, 1), (51, 128, 513, 4), (64, 128, 321, 3), (88, 128, 448, 1), (88, 128, 449, 2), (102, 128, 704, 1), (102, 128, 705, 2),
+                                      (45, 128, 512, 1), (45, 128, 513, 4), (51, 128, 512, 1), (51, 128, 513, 4), (64, 128, 321, 3), (88, 128, 448, 1), (88, 128, 449, 2), (102, 128, 704, 1), (102, 128, 705, 2),
                                       (3, 128, 321, 3)])
 def test_prefill_segment_counts_from_a_state(based, packed, U, dv, N, G, tmp_path):
     q, k, v = (synth.round_to(synth.normal(43 + i, (U, 64 + N, d), 0.5), "bf16") for i, d in enumerate((16, 16, dv)))
