@@ -39,9 +39,9 @@
 // there is one workgroup barrier (chunk t + 1's operands are visible, chunk t's are free).  The staged rows of K and Q exist twice and are staged one chunk
 // earlier still, so that nothing else is waited for.
 //
-// What bounds a chunk: the instruction stream of the waves, two to a SIMD, all about equally long (cycles of a chunk, d_v 64 / 128: consumers 2230 / 3430, the
-// one with the moments 3690; producers 2300-2600 / 3250-3580; at the barrier 2720 / 3800).  Three things shortened it from 3230 / 4420, where the consumers
-// set the pace: (1) the outputs are normalised and turned between the update's matrix instructions, and turned in registers (the halves of a wave exchange
+// What bounds a chunk: the instruction stream of the waves, two to a SIMD, all about equally long (cycles of a chunk with all CUs at work, d_v 64 / 128: 2850 / 3740, with a few
+// 2370 / 3300; each wave up to the barrier, reading the counter included: consumers 2300 / 3460, the one with the moments 3720; producers 2500-2950 / 3200-3520).  Three
+// things shortened it, where the consumers set the pace: (1) the outputs are normalised and turned between the update's matrix instructions, and turned in registers (the halves of a wave exchange
 // quads) instead of through LDS, which each consumer waited for twice: the second half of its chunk 1950 -> 1150; (2) the rows of K and Q come into
 // the registers that an operand is built from as products with 0/1 matrices instead of as staged fp32 copies, whose 4-byte LDS writes and 28 KB of reads the
 // producers spent a third of their time on; (3) the moments and denominators at d_v 128 are a consumer's.  256 units of 2048 tokens, d_v 64 58 -> 51.5 us,
@@ -93,9 +93,9 @@ constexpr float kSqrt2 = 1.41421356237309504880f;
 constexpr int RB_LD = DP + 8;     // bf16 row-major Q and K rows as given (48-byte stride)
 
 // Workspace entry (one segment's state in accumulator layout): six slots of 16 registers x 64 lanes
-// per wave: slot 6c + T = tile T of the wave that owns columns 32c .. 32c+31, slot 6c + 5 = the
-// moment tile (kept by wave 0 only; the others' sixth slot is never written and its contents are
-// never used).  Within a slot: [r / 4][lane][r % 4], so one 16-byte access per lane is contiguous
+// per column tile: slot 6c + T = state tile T of columns 32c .. 32c+31, slot 6 x_tile + 5 = the
+// moment tile (the other sixth slots are never written and their contents are never used).
+// Within a slot: [r / 4][lane][r % 4], so one 16-byte access per lane is contiguous
 // across the wave.
 constexpr int WS_WAVE_SLOTS = 6;
 constexpr size_t kSlotFloats = 16 * 64;
@@ -392,8 +392,8 @@ __device__ __forceinline__ void prefill_body(
     // (entry p = 1 .. G - 1 of the unit starts at (p - 1) entry_floats)
     float *ws_unit = ws ? ws + (size_t)u * (G - 1) * entry_floats(NC) : nullptr;
     unsigned *flags_unit = flags ? flags + (size_t)u * G * G : nullptr;
-    // this lane's 16 bytes of register group 0 of slot 0 of column tile c (producer 0 keeps the moment
-    // tile, which travels in the sixth slot of column tile 0), inside an entry
+    // this lane's 16 bytes of register group 0 of slot 0 of column tile c, inside an entry (producers: column tile 0, which at
+    // d_v 64, where the moments are one's, is the one whose sixth slot holds them)
     const size_t lane_off = (size_t)(is_p ? 0 : c) * WS_WAVE_SLOTS * kSlotFloats + (size_t)lane * 4;
     // the wave with the moments: at d_v 128 the consumer that builds no intra-chunk block, else producer 0 (the other way round at 128 producer 0 was
     // the one that all others waited for: 4240 cycles a chunk instead of 3700)
@@ -813,8 +813,8 @@ __device__ __forceinline__ void prefill_body(
             // A chunk of V is one contiguous block of 64 rows x DV columns, in 16-byte pieces: piece p is row p / (DV / 8), columns
             // 8 (p % (DV / 8)) ...  A chunk of K (and of Q) is 128 pieces: piece p holds elements 8 (p % 2) .. of token p / 2.  A wave
             // moves 64 pieces at a time.  Of four producers each has a quarter of V and half of K or Q.  Of six, 0 and 1 stage K, 4 and 5 Q, and
-            // 1 three eighths of V, the others one: as much as the builds leave time for (each with its own share of K or Q and of V: 2720 cycles a
-            // chunk, as here 2560).
+            // 1 three eighths of V, the others one: as much as the builds leave time for (each with its own share of K or Q and of V: a chunk takes 6 % more
+            // cycles).
             constexpr int VPR = DV / 8;   // pieces per V row
             constexpr int NVP = NPW == 6 ? 3 : 4;   // V pieces per producer thread, at most
             static_assert(NP == 64 * NPW && VPR * C == (NPW == 6 ? 8 : 16) * 64, "");
@@ -1062,8 +1062,8 @@ __device__ __forceinline__ void prefill_body(
 // the bit: rounded as k_a k_b / 2, the sums scaled at the end, they left the state 0.2 to 0.5 % further from float64 (128 units of 2048 tokens, d_v 64 36.8 us either way, d_v 128
 // 57.0, now 58.6; 16 of 777 from a state 16.0, now 15.6).
 //
-// Bound: memory, with half of the chip at increments and half at main passes (128 units: 1300 cycles a chunk at d_v 64, 2300 at 128, 4.1 TB/s together;
-// 16 units 1200); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
+// Bound: memory, with half of the chip at increments and half at main passes (128 units: 1530 cycles a chunk at d_v 64, 2570 at 128, its start and the
+// hand-over included); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
 template <int NC>
 __device__ __forceinline__ void increment_body(
     unsigned char *lds, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v, const float *__restrict__ state, int has_init,
@@ -1373,8 +1373,9 @@ int make_segments(int N, int G, int dv, SegTable &t)
         for (int g = 2; g <= kMaxSegments; ++g) t.begin[g] = T * C;
         return 2;
     }
-    // More segments: all of them wait for the longest increment, and the main pass of segment g then sums g - 1 entries, the last one also writes the final
-    // state, so later segments get fewer chunks.
+    // More segments: the main pass of segment g waits for the increments of segments 0 .. g - 2 and sums as many entries, the last one also writes the final
+    // state, so later segments get fewer chunks.  (The figures were set when the increments were workgroups of their own and not again since; segment 0, whose
+    // workgroup has no increment to compute, gets no more for that.)
     int len[kMaxSegments];
     int sum = 0;
     for (int g = 0; g < G; ++g) {
