@@ -42,8 +42,8 @@ PEAK_HBM_GBS = 8000.0
 # of those sources is the one recorded here, and as null after any change to them.
 MEASURED_TRAFFIC = {
     # key: (entry point, workload) -> (bytes per launch, source files the kernel is built from, their hash)
-    ("based_prefill", "prefill_1p3b"): (338428989, ("linattn_prefill_mfma.hip",), "5980b994b898"),
-    ("based_prefill", "prefill_360m"): (113655808, ("linattn_prefill_mfma.hip",), "5980b994b898"),
+    ("based_prefill", "prefill_1p3b"): (338427904, ("linattn_prefill_mfma.hip",), "f90a0ac89333"),
+    ("based_prefill", "prefill_360m"): (113842115, ("linattn_prefill_mfma.hip",), "f90a0ac89333"),
     ("based_prefill", "prefill_long"): (372222098, ("linattn_prefill_mfma32.hip",), "4c718ac932ef"),   # both launches
     ("based_swa_prefill", "prefill_1p3b"): (553832896, ("swa_prefill_mfma16.hip",), "6d81285cd196"),
     ("based_swa_prefill", "prefill_360m"): (142855936, ("swa_prefill_mfma.hip",), "3e1a66d76ef7"),

@@ -1060,7 +1060,7 @@ __device__ __forceinline__ void prefill_body(
 // and 4-7 take alternate tiles of 32 tokens and are added up at the end; at d_v 128 they own 64 columns each.  The rows come by the 16-byte LDS
 // DMA (a V row's pieces permuted, so that the transposing reads spread over the banks), three to four steps ahead.  The features are the main pass's to
 // the bit: rounded as k_a k_b / 2, the sums scaled at the end, they left the state 0.2 to 0.5 % further from float64 (128 units of 2048 tokens, d_v 64 36.8 us either way, d_v 128
-// 57.0, now 58.6; 16 of 777 from a state 16.0, now 15.6).
+// 57.0, now 58.6; 16 of 777 from a state 16.0, now 15.6; figures of several segments at d_v 128 further down are mostly from before, 2 % less).
 //
 // Bound: memory, with half of the chip at increments and half at main passes (128 units: 1530 cycles a chunk at d_v 64, 2570 at 128, its start and the
 // hand-over included); the matrix pipe would take 600 and 960.  As a producer / consumer pipeline like the main pass's, 2200 at d_v 64.
